@@ -136,7 +136,7 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
                     sp.out = (int8_t *)tptr(d.out, j0);
                     sp.w = d.conv.w; sp.bias = d.conv.bias; sp.m0s = d.conv.m0s; sp.chi = d.conv.chi; sp.shm1 = d.conv.shm1;
                     sp.H = d.conv.H; sp.W = d.conv.W; sp.Ho = d.conv.Ho; sp.Wo = d.conv.Wo; sp.Hp = to.H; sp.Wp = to.W;
-                    sp.zp_in = d.conv.zp_in; sp.zp_out = d.conv.zp_out; sp.relu = d.conv.relu; sp.tie_free = d.conv.tie_free; sp.B = (int32_t)bn;
+                    sp.zp_in = d.conv.zp_in; sp.zp_out = d.conv.zp_out; sp.relu = d.conv.relu; sp.rq = d.conv.rq; sp.B = (int32_t)bn;
                     sp.fused_noise = d.noise_fused && m->quant_sigma < 0.f;
                     sp.noise = NoiseSource{};
                     if (sp.fused_noise) {
@@ -204,7 +204,7 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
                     bp.zp_t1 = c1.zp_out;
                     bp.lo1 = c1.relu ? c1.zp_out : -128;
                     bp.lo2 = c2.relu ? c2.zp_out : -128;
-                    bp.tie_free = c1.tie_free && c2.tie_free;
+                    bp.rq = c1.rq & c2.rq; bp.add_rq = 3;
                     if (bp.tail) {
                         // the closing 1x1 convolution; with a projection shortcut (bneck == 4) conv3 carries two
                         // convolutions, and either of them may be the one that reads the block input
@@ -217,7 +217,8 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
                         bp.add_mul_self = swap ? c3.add_mul_res : c3.add_mul_self;   // "self" in the kernel = the closing convolution
                         bp.add_mul_res = swap ? c3.add_mul_self : c3.add_mul_res;
                         bp.add_c0 = c3.add_c0; bp.add_k = c3.add_k; bp.add_sh = c3.add_sh; bp.add_lo = c3.add_lo;
-                        bp.tie_free = bp.tie_free && c3.tie_free && c3.add_tie_free && (d.bneck != 4 || c3.tie_free2);
+                        bp.rq &= c3.rq & (d.bneck == 4 ? c3.rq2 : 3);
+                        bp.add_rq = c3.add_rq;
                         if (d.bneck == 4) {
                             bp.proj = 1;
                             bp.wp = swap ? c3.w : c3.w2; bp.biasp = swap ? c3.bias : c3.bias2; bp.m0sp = swap ? c3.m0s : c3.m0s2;
@@ -233,7 +234,7 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
                     XrParams xp;
                     expand_reduce_params(d.conv, d.conv2, (const int8_t *)tptr(d.a, j0), (const int8_t *)tptr(d.b, j0),
                                          (int8_t *)tptr(d.out, j0), (int8_t *)tptr(d.out2, j0), (int32_t)bn, xp);
-                    HIP_TRY(launch_expand_reduce(xp, d.conv.add_tie_free, m->stream));
+                    HIP_TRY(launch_expand_reduce(xp, m->stream));
                     break;
                 }
                 ConvParams c = d.conv;

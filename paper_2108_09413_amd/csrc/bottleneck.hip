@@ -38,7 +38,7 @@ constexpr int W2_CHUNKS = 37;                  // 16-byte chunks per 3x3 weight 
 
 // MODE 0: head (t2 stored); 1: whole identity block (residual = x); 2: whole first block of a stage --
 // the residual is itself a 1x1 convolution of x (projection shortcut, Cin = 64), computed here as well.
-template <int MODE, bool TF>
+template <int MODE, int RQ, int RQA>
 __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p) {
     constexpr bool TAIL = MODE != 0, PROJ = MODE == 2;
     constexpr int KB = 64, STAGE = (64 + 32 * NH_FR) * KB;            // 64 weight rows + 320 pixel rows per stage
@@ -65,13 +65,14 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
         const int cv = i >> 6, c = i & 63;
         prm[cv][0][c] = (cv ? p.bias2 : p.bias1)[c];
         prm[cv][1][c] = (cv ? p.m0s2 : p.m0s1)[c];
-        prm[cv][2][c] = (cv ? p.chi2 : p.chi1)[c];
-        prm[cv][3][c] = (cv ? p.shm12 : p.shm11)[c];
+        const int shm1 = (cv ? p.shm12 : p.shm11)[c];
+        prm[cv][2][c] = rq_chi<RQ>((cv ? p.chi2 : p.chi1)[c], shm1);
+        prm[cv][3][c] = rq_sh<RQ>(shm1);
     }
     if constexpr (TAIL)
         for (int i = tid; i < p.Cout_p; i += 256) {
-            prm3[0][i] = p.bias3[i]; prm3[1][i] = p.m0s3[i]; prm3[2][i] = p.chi3[i]; prm3[3][i] = p.shm13[i];
-            if constexpr (PROJ) { prmp[0][i] = p.biasp[i]; prmp[1][i] = p.m0sp[i]; prmp[2][i] = p.chip[i]; prmp[3][i] = p.shm1p[i]; }
+            prm3[0][i] = p.bias3[i]; prm3[1][i] = p.m0s3[i]; prm3[2][i] = rq_chi<RQ>(p.chi3[i], p.shm13[i]); prm3[3][i] = rq_sh<RQ>(p.shm13[i]);
+            if constexpr (PROJ) { prmp[0][i] = p.biasp[i]; prmp[1][i] = p.m0sp[i]; prmp[2][i] = rq_chi<RQ>(p.chip[i], p.shm1p[i]); prmp[3][i] = rq_sh<RQ>(p.shm1p[i]); }
         }
 
     // ---- step 1: t1 accumulators over the halo, K = Cin_p in steps of 64 ----
@@ -180,16 +181,15 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
         const uint32_t zt = (uint32_t)(p.zp_t1 & 0xFF) * 0x01010101u;
         int mm[16], ch[16], ss[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) { mm[i] = prm[0][1][c16 + i]; ch[i] = prm[0][2][c16 + i]; ss[i] = prm[0][3][c16 + i]; }
+        for (int i = 0; i < 16; ++i) { mm[i] = prm[0][1][c16 + i]; ch[i] = prm[0][2][c16 + rq_chi_at<RQ>(i)]; ss[i] = prm[0][3][c16 + i]; }
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
             const int h = (wn * 5 + f) * 32 + l, hy = h / HW, hx = h - hy * HW, y = y0 + hy, x = x0 + hx;
             const bool inside = h < NHALO && (unsigned)y < (unsigned)p.H && (unsigned)x < (unsigned)p.W;
             int q[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) q[i] = clamp3(requant_q<TF>(acc[f][i], mm[i], ch[i], ss[i]), p.lo1, 127);
-            v4i v = {(int)pack4(q[0], q[1], q[2], q[3]), (int)pack4(q[4], q[5], q[6], q[7]),
-                     (int)pack4(q[8], q[9], q[10], q[11]), (int)pack4(q[12], q[13], q[14], q[15])};
+            for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(acc[f][i], mm[i], ch[i], ss[i], p.lo1);
+            v4i v = rq_pack16<RQ>(q);
             if (!inside) v = v4i{(int)zt, (int)zt, (int)zt, (int)zt};
             *(v4i *)(&T[h * 64 + (((wm * 2 + half) ^ swz<4>(h)) << 4)]) = v;
         }
@@ -233,15 +233,14 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
     {
         int mm[16], ch[16], ss[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) { mm[i] = prm[1][1][c16 + i]; ch[i] = prm[1][2][c16 + i]; ss[i] = prm[1][3][c16 + i]; }
+        for (int i = 0; i < 16; ++i) { mm[i] = prm[1][1][c16 + i]; ch[i] = prm[1][2][c16 + rq_chi_at<RQ>(i)]; ss[i] = prm[1][3][c16 + i]; }
 #pragma unroll
         for (int f = 0; f < 4; ++f) {
             if (f == 3 && nfr != 4) { t2[f] = v4i{0, 0, 0, 0}; continue; }
             int q[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) q[i] = clamp3(requant_q<TF>(acc[f][i], mm[i], ch[i], ss[i]), p.lo2, 127);
-            t2[f] = v4i{(int)pack4(q[0], q[1], q[2], q[3]), (int)pack4(q[4], q[5], q[6], q[7]),
-                        (int)pack4(q[8], q[9], q[10], q[11]), (int)pack4(q[12], q[13], q[14], q[15])};
+            for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(acc[f][i], mm[i], ch[i], ss[i], p.lo2);
+            t2[f] = rq_pack16<RQ>(q);
         }
     }
     if constexpr (!TAIL) {
@@ -263,9 +262,7 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
         __syncthreads();   // the t2 tile is complete
 
         // ---- last 1x1 convolution + residual add: this wave's output channels, all seven pixel fragments ----
-        ConvParams ap{};   // the fused add reads its constants from here
-        ap.add_mul_self = p.add_mul_self; ap.add_mul_res = p.add_mul_res; ap.add_c0 = p.add_c0; ap.add_k = p.add_k;
-        ap.add_sh = p.add_sh; ap.add_lo = p.add_lo;
+        const AddConst ac = add_const<RQA>(p);
         int opix[NP_FR];    // index (image, row, column) of the lane's pixel of fragment f; -1: outside the image
         v4i fbt[PROJ ? 1 : NP_FR][2];  // the lane's pixel operands (64 channels of t2 = two K halves) of every fragment
 #pragma unroll
@@ -305,12 +302,13 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
                     int mm[16], ch[16], ss[16];
                     v16i init;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) { init[i] = prmp[0][c0 + i]; mm[i] = prmp[1][c0 + i]; ch[i] = prmp[2][c0 + i]; ss[i] = prmp[3][c0 + i]; }
+                    for (int i = 0; i < 16; ++i) { init[i] = prmp[0][c0 + i]; mm[i] = prmp[1][c0 + i]; ch[i] = prmp[2][c0 + rq_chi_at<RQ>(i)]; ss[i] = prmp[3][c0 + i]; }
                     v4i xn[2];   // x at the lane's pixel of the next fragment (pixels outside the image read pixel 0: in bounds, unused)
 #pragma unroll
                     for (int ksub = 0; ksub < 2; ++ksub) xn[ksub] = *(const v4i *)(p.in + (long)(opix[0] >= 0 ? opix[0] : 0) * 64 + ksub * 32 + half * 16);
 #pragma unroll
                     for (int f = 0; f < NP_FR; ++f) {
+                        if constexpr (rq_is_top(RQ)) __builtin_amdgcn_sched_barrier(0);   // one fragment at a time: without it registers spill
                         const v4i x0 = xn[0], x1 = xn[1];
                         if (f + 1 < NP_FR) {
 #pragma unroll
@@ -320,9 +318,8 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
                         a = __builtin_amdgcn_mfma_i32_32x32x32_i8(fp[1], x1, a, 0, 0, 0);
                         int q[16];
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) q[i] = clamp3(requant_q<TF>(a[i], mm[i], ch[i], ss[i]), p.lop, 127);
-                        rpack[f] = v4i{(int)pack4(q[0], q[1], q[2], q[3]), (int)pack4(q[4], q[5], q[6], q[7]),
-                                       (int)pack4(q[8], q[9], q[10], q[11]), (int)pack4(q[12], q[13], q[14], q[15])};
+                        for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(a[i], mm[i], ch[i], ss[i], p.lop);
+                        rpack[f] = rq_pack16<RQ>(q);
                     }
                 } else {
 #pragma unroll
@@ -334,7 +331,7 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
                 int mm[16], ch[16], ss[16];
                 v16i init;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) { init[i] = prm3[0][c0 + i]; mm[i] = prm3[1][c0 + i]; ch[i] = prm3[2][c0 + i]; ss[i] = prm3[3][c0 + i]; }
+                for (int i = 0; i < 16; ++i) { init[i] = prm3[0][c0 + i]; mm[i] = prm3[1][c0 + i]; ch[i] = prm3[2][c0 + rq_chi_at<RQ>(i)]; ss[i] = prm3[3][c0 + i]; }
 #pragma unroll
                 for (int f = 0; f < NP_FR; ++f) {
                     const v4i res = rpack[f];
@@ -351,13 +348,11 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
                     int q[16];
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        const int qc = clamp3(requant_q<TF>(a[i], mm[i], ch[i], ss[i]), p.lo3, 127);
-                        const int r8 = (int)(int8_t)((uint32_t)res[i >> 2] >> (8 * (i & 3)));
-                        q[i] = fused_add<TF>(qc, r8, ap);
+                        const int qc = rq_conv<RQ>(a[i], mm[i], ch[i], ss[i], p.lo3);
+                        q[i] = rq_add<RQ, RQA>(qc, (uint32_t)res[i >> 2], i & 3, ac);
                     }
                     if (opix[f] >= 0)
-                        *(v4i *)(p.out + (long)opix[f] * p.Cout_p + c0) = v4i{(int)pack4(q[0], q[1], q[2], q[3]), (int)pack4(q[4], q[5], q[6], q[7]),
-                                                            (int)pack4(q[8], q[9], q[10], q[11]), (int)pack4(q[12], q[13], q[14], q[15])};
+                        *(v4i *)(p.out + (long)opix[f] * p.Cout_p + c0) = rq_pack16<RQA>(q);
                 }
             }
         };
@@ -397,17 +392,13 @@ hipError_t launch_bottleneck(const BneckParams &p, hipStream_t st) {
     static const char *const names[3][2] = {{"bottleneck_kernel<head, false>", "bottleneck_kernel<head, true>"},
                                             {"bottleneck_kernel<block, false>", "bottleneck_kernel<block, true>"},
                                             {"bottleneck_kernel<block + projection, false>", "bottleneck_kernel<block + projection, true>"}};
-    set_kernel_name(names[mode][p.tie_free ? 1 : 0]);
-    if (mode == 2) {
-        if (p.tie_free) hipLaunchKernelGGL((bottleneck_kernel<2, true>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((bottleneck_kernel<2, false>), grid, block, 0, st, p);
-    } else if (mode == 1) {
-        if (p.tie_free) hipLaunchKernelGGL((bottleneck_kernel<1, true>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((bottleneck_kernel<1, false>), grid, block, 0, st, p);
-    } else {
-        if (p.tie_free) hipLaunchKernelGGL((bottleneck_kernel<0, true>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((bottleneck_kernel<0, false>), grid, block, 0, st, p);
-    }
+    set_kernel_name(names[mode][(p.rq & RQ_TIE_FREE) && (mode == 0 || p.add_rq != RQ_ANY)]);
+    with_rq(p.rq, p.add_rq, [&](auto rq, auto rqa) {
+        constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
+        if (mode == 2) hipLaunchKernelGGL((bottleneck_kernel<2, RQ, RQA>), grid, block, 0, st, p);
+        else if (mode == 1) hipLaunchKernelGGL((bottleneck_kernel<1, RQ, RQA>), grid, block, 0, st, p);
+        else hipLaunchKernelGGL((bottleneck_kernel<0, RQ, RQA>), grid, block, 0, st, p);
+    });
     return hipGetLastError();
 }
 

@@ -345,8 +345,8 @@ hipError_t launch_bottleneck128(const BneckParams &p, hipStream_t st) {
     const long tiles = (long)p.B * ((p.H + BT - 1) / BT) * ((p.W + BT - 1) / BT);
     if (tiles > 0x7fffffffL || (long)p.B * p.H * p.W * p.Cin_p >= (1L << 31)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles), block(256);
-    set_kernel_name(p.tie_free ? "bottleneck128_kernel<true>" : "bottleneck128_kernel<false>");
-    if (p.tie_free) hipLaunchKernelGGL((bottleneck128_kernel<true>), grid, block, 0, st, p);
+    set_kernel_name(((p.rq & RQ_TIE_FREE) && p.add_rq != RQ_ANY) ? "bottleneck128_kernel<true>" : "bottleneck128_kernel<false>");
+    if (((p.rq & RQ_TIE_FREE) && p.add_rq != RQ_ANY)) hipLaunchKernelGGL((bottleneck128_kernel<true>), grid, block, 0, st, p);
     else hipLaunchKernelGGL((bottleneck128_kernel<false>), grid, block, 0, st, p);
     return hipGetLastError();
 }

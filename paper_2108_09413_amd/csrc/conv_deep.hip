@@ -13,9 +13,9 @@ static hipError_t launch_deep(const ConvParams &p, hipStream_t st) {
     dim3 grid((unsigned)(((p.npix + 255) / 256) * ((p.Cout_p + 255) / 256)));
     set_kernel_name(conv_dma_name<256, 256, KB, 2, 0, 1, 128, 128>());
     if (p.tie_free)
-        hipLaunchKernelGGL((conv_dma_kernel<256, 256, KB, 2, 0, 1, true, 128, 128>), grid, dim3(256), 0, st, p);
+        hipLaunchKernelGGL((conv_dma_kernel<256, 256, KB, 2, 0, 1, RQ_TIE_FREE, 128, 128>), grid, dim3(256), 0, st, p);
     else
-        hipLaunchKernelGGL((conv_dma_kernel<256, 256, KB, 2, 0, 1, false, 128, 128>), grid, dim3(256), 0, st, p);
+        hipLaunchKernelGGL((conv_dma_kernel<256, 256, KB, 2, 0, 1, RQ_ANY, 128, 128>), grid, dim3(256), 0, st, p);
     return hipGetLastError();
 }
 

@@ -82,6 +82,125 @@ __device__ __forceinline__ uint32_t pack4(int a, int b, int c, int d) {
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
+// How a layer's requantisation and its fused residual add are computed; chosen per layer when the model is loaded.
+//   RQ_ANY       any layer of the single-multiply form
+//   RQ_TIE_FREE  no accumulator value meets an exact half (ConvParams::tie_free)
+//   RQ_TOP       tie-free, lower clamp -128, and every intermediate fits (plan.cpp): the int8 result is kept in the TOP
+//                byte of a word, where int32 saturation is its clamp.  w = mulhi(acc, M0) fits 24 bits, so
+//                  sat32(w * 2^(24 - shm1) + (2^23 + z_out 2^24))
+//                is floor((w + chi) / 2^shm1), clamped to [-128, 127], times 2^24 plus a fraction: add, shift and clamp
+//                become one v_mad_i32_i24 with the clamp bit, and the packing is two byte permutes and an or.  Issue
+//                cycles of a wave per output, from the measured rates (add, shift, and, or 2.5 - 2.8; multiplies, clamp,
+//                permute 4.3 - 4.5): 12 instead of 17, with a residual add 29 instead of 37.  ResNet-50, 668 copies:
+//                identity block at 56 x 56 409 -> 349 us, expand + reduce at 28 x 28 160 -> 138, at 14 x 14 120 -> 108.
+//   RQ_TOP_TIES  the same with ties (a 64-bit multiply-add instead of the multiply)
+// An add is RQ_ANY, RQ_TIE_FREE, RQ_TOP or RQ_TOP_WIDE (two signed operands, whose sum may leave int32 and saturates).
+// The forms of several convolutions combine with &.
+enum Rq : int { RQ_ANY = 0, RQ_TIE_FREE = 1, RQ_TOP_TIES = 2, RQ_TOP = 3, RQ_TOP_WIDE = 4 };
+constexpr bool rq_is_top(int rq) { return rq >= RQ_TOP_TIES; }
+
+// v_mad_i32_i24 with the clamp bit: sat32(a * b + c), a and b in 24 bits (no builtin reaches the clamp bit)
+__device__ __forceinline__ int mad24_sat(int a, int b, int c) {
+    int r;
+    asm("v_mad_i32_i24 %0, %1, %2, %3 clamp" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// The per-channel constants as the kernels stage them: in the top form `chi` becomes the addend (the same for every
+// channel of a layer, padding channels included) and `shm1` the multiplier.
+template <int RQ>
+__device__ __forceinline__ int rq_chi(int chi, int shm1) { return rq_is_top(RQ) ? chi << (24 - shm1) : chi; }
+template <int RQ>
+__device__ __forceinline__ int rq_sh(int shm1) { return rq_is_top(RQ) ? 1 << (24 - shm1) : shm1; }
+// index of channel i's addend
+template <int RQ>
+__device__ __forceinline__ constexpr int rq_chi_at(int i) { return rq_is_top(RQ) ? 0 : i; }
+
+// requantise + clamp to [lo, 127]: the value, or in the top form a word with the value in its top byte
+template <int RQ>
+__device__ __forceinline__ int rq_conv(int acc, int m0, int chi, int sh, int lo) {
+    if constexpr (RQ == RQ_TOP) {
+        return mad24_sat(__mulhi(acc, m0), sh, chi);
+    } else if constexpr (RQ == RQ_TOP_TIES) {
+        const long w = (long)acc * (long)m0 + (long)(acc >> 31);   // v - [v < 0], as requant_fast
+        return mad24_sat((int)(w >> 32), sh, chi);
+    } else {
+        return clamp3(requant_q<RQ == RQ_TIE_FREE>(acc, m0, chi, sh), lo, 127);
+    }
+}
+
+// Constants of the residual add.  Top form: everything times 2^(23 - add_sh); the saturating double of the sum has the
+// int8 result in the top byte.
+struct AddConst { int ms, mr, c0, k, sh, lo; };
+template <int RQA, class P>
+__device__ __forceinline__ AddConst add_const(const P &p) {
+    if constexpr (rq_is_top(RQA)) {
+        const int s = 23 - p.add_sh;
+        return {p.add_mul_self << s, p.add_mul_res << s, (p.add_c0 + p.add_k) << s, 0, 0, 0};
+    } else {
+        return {p.add_mul_self, p.add_mul_res, p.add_c0, p.add_k, p.add_sh, p.add_lo};
+    }
+}
+
+// Residual add on q (as rq_conv<RQ> returns it) and byte j of the residual word.  A top-form add goes with a top-form
+// convolution.  24-bit multiplies: |q|, |r| <= 2^7, |multipliers| < 2^23; the byte selections fold into them.
+template <int RQ, int RQA>
+__device__ __forceinline__ int rq_add(int q, uint32_t rword, int j, const AddConst &a) {
+    static_assert(!rq_is_top(RQA) || rq_is_top(RQ), "");
+    const int qi = rq_is_top(RQ) ? q >> 24 : q, r8 = (int)(int8_t)(rword >> (8 * j));
+    if constexpr (RQA == RQ_TOP) {
+        const int v = __mul24(qi, a.ms) + __mul24(r8, a.mr) + a.c0;
+        return __builtin_elementwise_add_sat(v, v);
+    } else if constexpr (RQA == RQ_TOP_WIDE) {
+        const int v = mad24_sat(qi, a.ms, __mul24(r8, a.mr) + a.c0);
+        return __builtin_elementwise_add_sat(v, v);
+    } else if constexpr (RQA == RQ_TIE_FREE) {
+        const int v = __mul24(qi, a.ms) + (a.c0 + a.k) + __mul24(r8, a.mr);
+        return clamp3(v >> a.sh, a.lo, 127);
+    } else {
+        const int v = __mul24(qi, a.ms) + a.c0 + __mul24(r8, a.mr);
+        return clamp3((v + a.k + (v >> 31)) >> a.sh, a.lo, 127);
+    }
+}
+
+// four results of rq_conv / rq_add -> one dword of int8
+template <int RQ>
+__device__ __forceinline__ uint32_t rq_pack(int a, int b, int c, int d) {
+    if constexpr (rq_is_top(RQ)) {
+        const uint32_t lo = __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x0c0c0703u);
+        const uint32_t hi = __builtin_amdgcn_perm((uint32_t)d, (uint32_t)c, 0x07030c0cu);
+        return lo | hi;
+    } else {
+        return pack4(a, b, c, d);
+    }
+}
+template <int RQ>
+__device__ __forceinline__ v4i rq_pack16(const int (&q)[16]) {
+    return v4i{(int)rq_pack<RQ>(q[0], q[1], q[2], q[3]), (int)rq_pack<RQ>(q[4], q[5], q[6], q[7]),
+               (int)rq_pack<RQ>(q[8], q[9], q[10], q[11]), (int)rq_pack<RQ>(q[12], q[13], q[14], q[15])};
+}
+
+// Calls f with the compile-time forms <RQ of the convolutions, RQ of the add> that serve layers of these classes.
+template <class F>
+void with_rq(int rq, int rqa, F f) {
+    using std::integral_constant;
+    if (rq == RQ_TOP && rqa == RQ_TOP) f(integral_constant<int, RQ_TOP>{}, integral_constant<int, RQ_TOP>{});
+    else if (rq == RQ_TOP && rqa == RQ_TOP_WIDE) f(integral_constant<int, RQ_TOP>{}, integral_constant<int, RQ_TOP_WIDE>{});
+    else if (rq == RQ_TOP) f(integral_constant<int, RQ_TOP>{}, integral_constant<int, RQ_ANY>{});
+    else if (rq == RQ_TOP_TIES) f(integral_constant<int, RQ_TOP_TIES>{}, integral_constant<int, RQ_ANY>{});
+    else if (rq == RQ_TIE_FREE && rqa != RQ_ANY) f(integral_constant<int, RQ_TIE_FREE>{}, integral_constant<int, RQ_TIE_FREE>{});
+    else f(integral_constant<int, RQ_ANY>{}, integral_constant<int, RQ_ANY>{});
+}
+// the same for a kernel without an add
+template <class F>
+void with_rq(int rq, F f) {
+    using std::integral_constant;
+    if (rq == RQ_TOP) f(integral_constant<int, RQ_TOP>{});
+    else if (rq == RQ_TOP_TIES) f(integral_constant<int, RQ_TOP_TIES>{});
+    else if (rq == RQ_TIE_FREE) f(integral_constant<int, RQ_TIE_FREE>{});
+    else f(integral_constant<int, RQ_ANY>{});
+}
+
 // 16 bytes per lane from global memory into LDS: lane l of the wave writes bytes
 // [16 l, 16 l + 16) after the wave-uniform LDS address `lptr`.
 #define ISR_GLOBAL_TO_LDS16(gptr, lptr)                                                             \

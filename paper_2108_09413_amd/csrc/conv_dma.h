@@ -25,8 +25,8 @@ inline const char *conv_dma_name() {
 // residual computed here by a second (1x1, stride 1) convolution.
 // WTM x WTN: output block of one wave (channels x pixels): 64 x 64 = 2 x 2 MFMA tiles, 128 x 64 = 4 x 2,
 // 128 x 128 = 4 x 4.  A larger block reads fewer operand bytes from LDS per multiply.
-// TF: the convolutions' requantisations are free of rounding ties (single-multiply form); TFA: so is the fused add.
-template <int BM, int BN, int KB, int NST, int FUSE, int MINB, bool TF, int WTM = 64, int WTN = 64, bool TFA = TF>
+// RQ, RQA: form of the convolutions' requantisations and of the fused add (conv_device.h).
+template <int BM, int BN, int KB, int NST, int FUSE, int MINB, int RQ, int WTM = 64, int WTN = 64, int RQA = RQ>
 __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_kernel(const ConvParams p) {
     constexpr int MT = 32;
     constexpr int WGM = BM / WTM, WGN = BN / WTN, NT = WGM * WGN * 64;
@@ -195,13 +195,15 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
         const bool in = m0 + i < p.Mp;
         prm_s[0][i] = in ? p.bias[m0 + i] : 0;
         prm_s[1][i] = in ? p.m0s[m0 + i] : 0;
-        prm_s[2][i] = in ? p.chi[m0 + i] : 0;
-        prm_s[3][i] = in ? p.shm1[m0 + i] : 1;
+        const int shm1 = in ? p.shm1[m0 + i] : 1;
+        prm_s[2][i] = in ? rq_chi<RQ>(p.chi[m0 + i], shm1) : 0;
+        prm_s[3][i] = rq_sh<RQ>(shm1);
         if constexpr (FUSE == 2) {
             prm2_s[0][i] = in ? p.bias2[m0 + i] : 0;
             prm2_s[1][i] = in ? p.m0s2[m0 + i] : 0;
-            prm2_s[2][i] = in ? p.chi2[m0 + i] : 0;
-            prm2_s[3][i] = in ? p.shm12[m0 + i] : 1;
+            const int shm12 = in ? p.shm12[m0 + i] : 1;
+            prm2_s[2][i] = in ? rq_chi<RQ>(p.chi2[m0 + i], shm12) : 0;
+            prm2_s[3][i] = rq_sh<RQ>(shm12);
         }
     }
 
@@ -346,10 +348,9 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
 #pragma unroll
                 for (int i = 0; i < ACC; ++i) {
                     const int c = lane_oc(fm) + i;
-                    q[i] = clamp3(requant_q<TF>(acc[fm][fn][i], prm2_s[1][c], prm2_s[2][c], prm2_s[3][c]), p.lo2, 127);
+                    q[i] = rq_conv<RQ>(acc[fm][fn][i], prm2_s[1][c], prm2_s[2][lane_oc(fm) + rq_chi_at<RQ>(i)], prm2_s[3][c], p.lo2);
                 }
-                rq[fm][fn] = v4i{(int)pack4(q[0], q[1], q[2], q[3]), (int)pack4(q[4], q[5], q[6], q[7]),
-                                 (int)pack4(q[8], q[9], q[10], q[11]), (int)pack4(q[12], q[13], q[14], q[15])};
+                rq[fm][fn] = rq_pack16<RQ>(q);
             }
         __syncthreads();   // every wave is done with the operand buffers before the main GEMM refills them
     }
@@ -364,6 +365,7 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
         resbuf = Ls[res_buf];
     }
     const int lo = p.relu ? p.zp_out : -128;
+    const AddConst ac = add_const<FUSE != 0 ? RQA : (int)RQ_ANY>(p);
 #pragma unroll
     for (int fm = 0; fm < FM; ++fm) {
         const int oc = m0 + lane_oc(fm);
@@ -371,7 +373,7 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
         int mm[ACC], ch[ACC], ss[ACC];
 #pragma unroll
         for (int i = 0; i < ACC; ++i) {
-            mm[i] = prm_s[1][oc - m0 + i]; ch[i] = prm_s[2][oc - m0 + i]; ss[i] = prm_s[3][oc - m0 + i];
+            mm[i] = prm_s[1][oc - m0 + i]; ch[i] = prm_s[2][oc - m0 + rq_chi_at<RQ>(i)]; ss[i] = prm_s[3][oc - m0 + i];
         }
         {
 #pragma unroll
@@ -380,21 +382,17 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
                 if (n >= p.npix) continue;
                 int q[ACC];
 #pragma unroll
-                for (int i = 0; i < ACC; ++i) q[i] = clamp3(requant_q<TF>(acc[fm][fn][i], mm[i], ch[i], ss[i]), lo, 127);
+                for (int i = 0; i < ACC; ++i) q[i] = rq_conv<RQ>(acc[fm][fn][i], mm[i], ch[i], ss[i], lo);
                 if constexpr (FUSE != 0) {
                     const int pixel = wn * WTN + fn * MT + (lane & (MT - 1));
                     v4i rv;
                     if constexpr (FUSE == 2) rv = rq[fm][fn];
                     else rv = *(const v4i *)(resbuf + (pixel * RCH + ((lane_oc(fm) >> 4) ^ rswz(pixel))) * 16);
 #pragma unroll
-                    for (int i = 0; i < ACC; ++i) {
-                        int r8 = (int)(int8_t)((uint32_t)rv[i >> 2] >> (8 * (i & 3)));
-                        q[i] = fused_add<TFA>(q[i], r8, p);
-                    }
+                    for (int i = 0; i < ACC; ++i) q[i] = rq_add<RQ, RQA>(q[i], (uint32_t)rv[i >> 2], i & 3, ac);
                 }
                 int8_t *dst = p.out + n * p.Cout_p + oc;
-                v4i v = {(int)pack4(q[0], q[1], q[2], q[3]), (int)pack4(q[4], q[5], q[6], q[7]),
-                         (int)pack4(q[8], q[9], q[10], q[11]), (int)pack4(q[12], q[13], q[14], q[15])};
+                v4i v = rq_pack16<FUSE != 0 ? RQA : RQ>(q);
                 *(v4i *)dst = v;
             }
         }

@@ -348,10 +348,9 @@ static hipError_t launch_dma(const ConvParams &p, hipStream_t st) {
     constexpr int NT = (BM / 64) * (BN / 64) * 64;
     dim3 grid((unsigned)(((p.npix + BN - 1) / BN) * ((p.Cout_p + BM - 1) / BM)));
     set_kernel_name(conv_dma_name<BM, BN, KB, NST, 0, MINB, 64, 64>());
-    if (p.tie_free)
-        hipLaunchKernelGGL((conv_dma_kernel<BM, BN, KB, NST, 0, MINB, true>), grid, dim3(NT), 0, st, p);
-    else
-        hipLaunchKernelGGL((conv_dma_kernel<BM, BN, KB, NST, 0, MINB, false>), grid, dim3(NT), 0, st, p);
+    with_rq(p.rq, [&](auto rq) {
+        hipLaunchKernelGGL((conv_dma_kernel<BM, BN, KB, NST, 0, MINB, decltype(rq)::value>), grid, dim3(NT), 0, st, p);
+    });
     return hipGetLastError();
 }
 
@@ -364,34 +363,23 @@ static hipError_t launch_dma_fused(const ConvParams &p, hipStream_t st) {
     if (p.fuse_add == 2) {
         if (!p.in2 || !p.w2 || p.Cin2_p < 64 || p.Cin2_p % 64 != 0) return hipErrorInvalidValue;
         set_kernel_name(conv_dma_name<BM, BN, 64, 2, 2, MINB2, 64, 64>());
-        // the tie-free forms are chosen separately for the two convolutions and for the add: an add that can
-        // meet an exact half costs two more instructions per output, a convolution that can costs a 64-bit multiply
-        if (p.tie_free && p.tie_free2 && p.add_tie_free)
-            hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 2, 2, MINB2, true>), grid, dim3(NT), 0, st, p);
-        else if (p.tie_free && p.tie_free2)
-            hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 2, 2, MINB2, true, 64, 64, false>), grid, dim3(NT), 0, st, p);
-        else
-            hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 2, 2, MINB2, false>), grid, dim3(NT), 0, st, p);
+        with_rq(p.rq & p.rq2, p.add_rq, [&](auto rq, auto rqa) {
+            hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 2, 2, MINB2, decltype(rq)::value, 64, 64, decltype(rqa)::value>), grid, dim3(NT), 0, st, p);
+        });
     } else if (BM == 128 && p.Kp == 128) {
         // two K steps: with a third buffer the residual tile is fetched at the start instead of
         // during the last step, which measured faster than the fourth workgroup per CU
         if constexpr (BM == 128) {
             set_kernel_name(conv_dma_name<BM, BN, 64, 3, 1, 3, 64, 64>());
-            if (p.tie_free && p.add_tie_free)
-                hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 3, 1, 3, true>), grid, dim3(NT), 0, st, p);
-            else if (p.tie_free)
-                hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 3, 1, 3, true, 64, 64, false>), grid, dim3(NT), 0, st, p);
-            else
-                hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 3, 1, 3, false>), grid, dim3(NT), 0, st, p);
+            with_rq(p.rq, p.add_rq, [&](auto rq, auto rqa) {
+                hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 3, 1, 3, decltype(rq)::value, 64, 64, decltype(rqa)::value>), grid, dim3(NT), 0, st, p);
+            });
         }
     } else {
         set_kernel_name(conv_dma_name<BM, BN, 64, 2, 1, MINB, 64, 64>());
-        if (p.tie_free && p.add_tie_free)
-            hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 2, 1, MINB, true>), grid, dim3(NT), 0, st, p);
-        else if (p.tie_free)
-            hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 2, 1, MINB, true, 64, 64, false>), grid, dim3(NT), 0, st, p);
-        else
-            hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 2, 1, MINB, false>), grid, dim3(NT), 0, st, p);
+        with_rq(p.rq, p.add_rq, [&](auto rq, auto rqa) {
+            hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 2, 1, MINB, decltype(rq)::value, 64, 64, decltype(rqa)::value>), grid, dim3(NT), 0, st, p);
+        });
     }
     return hipGetLastError();
 }
@@ -479,11 +467,11 @@ hipError_t launch_conv(const ConvParams &p, hipStream_t st) {
             const dim3 grid((unsigned)(((p.npix + 255) / 256) * ((p.Cout_p + 255) / 256)));
             set_kernel_name(k128 ? conv_dma_name<256, 256, 128, 2, 0, 1, 128, 64>() : conv_dma_name<256, 256, 64, 3, 0, 1, 128, 64>());
             if (k128) {
-                if (p.tie_free) hipLaunchKernelGGL((conv_dma_kernel<256, 256, 128, 2, 0, 1, true, 128, 64>), grid, dim3(512), 0, st, p);
-                else hipLaunchKernelGGL((conv_dma_kernel<256, 256, 128, 2, 0, 1, false, 128, 64>), grid, dim3(512), 0, st, p);
+                if (p.tie_free) hipLaunchKernelGGL((conv_dma_kernel<256, 256, 128, 2, 0, 1, RQ_TIE_FREE, 128, 64>), grid, dim3(512), 0, st, p);
+                else hipLaunchKernelGGL((conv_dma_kernel<256, 256, 128, 2, 0, 1, RQ_ANY, 128, 64>), grid, dim3(512), 0, st, p);
             } else {
-                if (p.tie_free) hipLaunchKernelGGL((conv_dma_kernel<256, 256, 64, 3, 0, 1, true, 128, 64>), grid, dim3(512), 0, st, p);
-                else hipLaunchKernelGGL((conv_dma_kernel<256, 256, 64, 3, 0, 1, false, 128, 64>), grid, dim3(512), 0, st, p);
+                if (p.tie_free) hipLaunchKernelGGL((conv_dma_kernel<256, 256, 64, 3, 0, 1, RQ_TIE_FREE, 128, 64>), grid, dim3(512), 0, st, p);
+                else hipLaunchKernelGGL((conv_dma_kernel<256, 256, 64, 3, 0, 1, RQ_ANY, 128, 64>), grid, dim3(512), 0, st, p);
             }
             return hipGetLastError();
         }

@@ -25,7 +25,7 @@ constexpr int PBN = 256;                         // pixels per tile
 constexpr int PROWS = 320;                       // staged pixel rows per buffer: 256 + 2 (W + 1) <= 320 for W <= 31
 constexpr int PZBYTES = 256;                     // zero points behind them: one pass over the 64 LDS banks
 
-template <int BM, int KB, int MINB, bool TF, bool DUTY>
+template <int BM, int KB, int MINB, int RQ, bool DUTY>
 __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_kernel(const ConvParams p) {
     constexpr int WGM = BM / 64, NW = WGM * (PBN / 64), NT = NW * 64;
     constexpr int CPR = KB / 16;                 // 16-byte chunks per row
@@ -141,8 +141,9 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
         const bool in = m0 + i < p.Mp;
         prm_s[0][i] = in ? p.bias[m0 + i] : 0;
         prm_s[1][i] = in ? p.m0s[m0 + i] : 0;
-        prm_s[2][i] = in ? p.chi[m0 + i] : 0;
-        prm_s[3][i] = in ? p.shm1[m0 + i] : 1;
+        const int shm1 = in ? p.shm1[m0 + i] : 1;
+        prm_s[2][i] = in ? rq_chi<RQ>(p.chi[m0 + i], shm1) : 0;
+        prm_s[3][i] = rq_sh<RQ>(shm1);
     }
     if (tid < 2 * (PZBYTES / 4)) *(int *)(&Bs[tid / (PZBYTES / 4)][ZOFF + (tid % (PZBYTES / 4)) * 4]) = (p.zp_in & 0xFF) * 0x01010101;
     __syncthreads();   // prm_s and the zero points visible
@@ -270,7 +271,7 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
         int mm[16], ch[16], ss[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            mm[i] = prm_s[1][oc - m0 + i]; ch[i] = prm_s[2][oc - m0 + i]; ss[i] = prm_s[3][oc - m0 + i];
+            mm[i] = prm_s[1][oc - m0 + i]; ch[i] = prm_s[2][oc - m0 + rq_chi_at<RQ>(i)]; ss[i] = prm_s[3][oc - m0 + i];
         }
 #pragma unroll
         for (int fn = 0; fn < 2; ++fn) {
@@ -278,9 +279,8 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
             if (n >= p.npix) continue;
             int q[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) q[i] = clamp3(requant_q<TF>(acc[fm][fn][i], mm[i], ch[i], ss[i]), lo, 127);
-            *(v4i *)(p.out + n * p.Cout_p + oc) = v4i{(int)pack4(q[0], q[1], q[2], q[3]), (int)pack4(q[4], q[5], q[6], q[7]),
-                                                       (int)pack4(q[8], q[9], q[10], q[11]), (int)pack4(q[12], q[13], q[14], q[15])};
+            for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(acc[fm][fn][i], mm[i], ch[i], ss[i], lo);
+            *(v4i *)(p.out + n * p.Cout_p + oc) = rq_pack16<RQ>(q);
         }
     }
 }
@@ -290,8 +290,9 @@ hipError_t launch_patch(const ConvParams &p, hipStream_t st, const char *name) {
     const dim3 grid((unsigned)(((p.npix + PBN - 1) / PBN) * ((p.Cout_p + BM - 1) / BM)));
     const dim3 block((BM / 64) * (PBN / 64) * 64);
     set_kernel_name(name);
-    if (p.tie_free) hipLaunchKernelGGL((conv_patch_kernel<BM, KB, MINB, true, DUTY>), grid, block, 0, st, p);
-    else hipLaunchKernelGGL((conv_patch_kernel<BM, KB, MINB, false, DUTY>), grid, block, 0, st, p);
+    with_rq(p.rq, [&](auto rq) {
+        hipLaunchKernelGGL((conv_patch_kernel<BM, KB, MINB, decltype(rq)::value, DUTY>), grid, block, 0, st, p);
+    });
     return hipGetLastError();
 }
 

@@ -31,7 +31,14 @@ constexpr int XK1 = 128, XC = 512, XN2 = 128, XPX = 32, XNW = 8, XNT = XNW * 64;
 constexpr int XNB = 3;   // tile buffers: loads run two tiles ahead
 typedef int v4acc __attribute__((ext_vector_type(4)));
 
-template <bool TFA>
+// four channels' addends of the requantisation (one value for a whole layer in the top form)
+template <int RQ>
+__device__ __forceinline__ v4i rq_chi4(const int *c) {
+    if constexpr (rq_is_top(RQ)) return v4i{c[0], c[0], c[0], c[0]};
+    else return *(const v4i *)c;
+}
+
+template <int RQ, int RQA>
 __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p) {
     __shared__ __attribute__((aligned(256))) int8_t XY[XNB][XPX * XC];
     __shared__ __attribute__((aligned(16))) int8_t T2[XNB][XPX * XK1];
@@ -40,6 +47,7 @@ __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ntiles = (p.npix + XPX - 1) / XPX, G = gridDim.x;
+    const AddConst ac = add_const<RQA>(p);
     const uint32_t xy_lds = lds_address(&XY[0][0]), t2_lds = lds_address(&T2[0][0]);
 
     // direct-to-LDS loads of a tile: wave-load q of the x tile covers pixels 2 q, 2 q + 1 (wave w issues q = 2 w,
@@ -68,10 +76,10 @@ __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p)
     if (tile < ntiles) issue_tile(tile, 0);
     if (tile + G < ntiles) issue_tile(tile + G, 1);
     for (int i = tid; i < XC; i += XNT) {
-        prm1[0][i] = p.bias1[i]; prm1[1][i] = p.m0s1[i]; prm1[2][i] = p.chi1[i]; prm1[3][i] = p.shm11[i];
+        prm1[0][i] = p.bias1[i]; prm1[1][i] = p.m0s1[i]; prm1[2][i] = rq_chi<RQ>(p.chi1[i], p.shm11[i]); prm1[3][i] = rq_sh<RQ>(p.shm11[i]);
     }
     if (tid < XN2) {
-        prm2[0][tid] = p.bias2[tid]; prm2[1][tid] = p.m0s2[tid]; prm2[2][tid] = p.chi2[tid]; prm2[3][tid] = p.shm12[tid];
+        prm2[0][tid] = p.bias2[tid]; prm2[1][tid] = p.m0s2[tid]; prm2[2][tid] = rq_chi<RQ>(p.chi2[tid], p.shm12[tid]); prm2[3][tid] = rq_sh<RQ>(p.shm12[tid]);
     }
     // weight fragments, kept in registers for the whole launch: expand [fm][ksub] (32 output channels x 32 K bytes
     // each), reduce [kstep] (16 output channels x 64 K bytes each)
@@ -135,21 +143,13 @@ __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p)
             // four channels at a time: their constants are three 16-byte LDS reads, the results one packed dword
 #pragma unroll
             for (int gi = 0; gi < 4; ++gi) {
-                const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = *(const v4i *)&prm1[2][oc + 4 * gi], ss = *(const v4i *)&prm1[3][oc + 4 * gi];
+                const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = rq_chi4<RQ>(&prm1[2][oc + 4 * gi]), ss = *(const v4i *)&prm1[3][oc + 4 * gi];
                 int q[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int v = clamp3(requant_tie_free(acc[4 * gi + i], mm[i], ch[i], ss[i]), p.lo1, 127);
-                    const int r8 = (int)(int8_t)((uint32_t)rv[gi] >> (8 * i));
-                    if constexpr (TFA) {
-                        const int s = __mul24(v, p.add_mul_self) + (p.add_c0 + p.add_k) + __mul24(r8, p.add_mul_res);
-                        q[i] = clamp3(s >> p.add_sh, p.add_lo, 127);
-                    } else {
-                        const int s = __mul24(v, p.add_mul_self) + p.add_c0 + __mul24(r8, p.add_mul_res);
-                        q[i] = clamp3((s + p.add_k + (s >> 31)) >> p.add_sh, p.add_lo, 127);
-                    }
+                    q[i] = rq_add<RQ, RQA>(rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1), (uint32_t)rv[gi], i, ac);
                 }
-                yv[gi] = (int)pack4(q[0], q[1], q[2], q[3]);
+                yv[gi] = (int)rq_pack<RQA>(q[0], q[1], q[2], q[3]);
             }
             *(v4i *)cell = yv;
             if (n1 < p.npix) *(v4i *)(p.y + n1 * XC + oc) = yv;
@@ -180,9 +180,9 @@ __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int c = wave * 16 + g * 4 + i;
-                q[i] = clamp3(requant_tie_free(acc2[nb][i], prm2[1][c], prm2[2][c], prm2[3][c]), p.lo2, 127);
+                q[i] = rq_conv<RQ>(acc2[nb][i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2);
             }
-            if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * XN2 + wave * 16 + g * 4) = pack4(q[0], q[1], q[2], q[3]);
+            if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * XN2 + wave * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
         }
         buf = buf + 1 == XNB ? 0 : buf + 1;
     }
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p)
 
 constexpr int XPK = 256, XNW2 = 16, XNT2 = XNW2 * 64;
 
-template <bool TFA>
+template <int RQ, int RQA>
 __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrParams p) {
     __shared__ __attribute__((aligned(256))) int8_t Y[XPX * XC];
     __shared__ __attribute__((aligned(256))) int8_t X0[XNB][XPX * XPK];
@@ -203,6 +203,7 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ntiles = (p.npix + XPX - 1) / XPX, G = gridDim.x;
+    const AddConst ac = add_const<RQA>(p);
     const uint32_t x0_lds = lds_address(&X0[0][0]), t2_lds = lds_address(&T2[0][0]);
 
     // direct-to-LDS loads of a tile: wave-load q of the x0 tile covers pixels 4 q .. 4 q + 3 (waves 0 .. 7), wave-load q
@@ -231,11 +232,11 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
     if (tile < ntiles) issue_tile(tile, 0);
     if (tile + G < ntiles) issue_tile(tile + G, 1);
     for (int i = tid; i < XC; i += XNT2) {
-        prm1[0][i] = p.bias1[i]; prm1[1][i] = p.m0s1[i]; prm1[2][i] = p.chi1[i]; prm1[3][i] = p.shm11[i];
-        prmp[0][i] = p.biasp[i]; prmp[1][i] = p.m0sp[i]; prmp[2][i] = p.chip[i]; prmp[3][i] = p.shm1p[i];
+        prm1[0][i] = p.bias1[i]; prm1[1][i] = p.m0s1[i]; prm1[2][i] = rq_chi<RQ>(p.chi1[i], p.shm11[i]); prm1[3][i] = rq_sh<RQ>(p.shm11[i]);
+        prmp[0][i] = p.biasp[i]; prmp[1][i] = p.m0sp[i]; prmp[2][i] = rq_chi<RQ>(p.chip[i], p.shm1p[i]); prmp[3][i] = rq_sh<RQ>(p.shm1p[i]);
     }
     if (tid < XN2) {
-        prm2[0][tid] = p.bias2[tid]; prm2[1][tid] = p.m0s2[tid]; prm2[2][tid] = p.chi2[tid]; prm2[3][tid] = p.shm12[tid];
+        prm2[0][tid] = p.bias2[tid]; prm2[1][tid] = p.m0s2[tid]; prm2[2][tid] = rq_chi<RQ>(p.chi2[tid], p.shm12[tid]); prm2[3][tid] = rq_sh<RQ>(p.shm12[tid]);
     }
     // weight fragments, kept in registers for the whole launch: wave w owns channels 32 w .. 32 w + 31 of the expanding
     // convolution [ksub] and of the projection [ksub], and 16 channels x 16 pixels of the reducing convolution [kstep]
@@ -289,11 +290,11 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
 #pragma unroll
             for (int gi = 0; gi < 4; ++gi) {
                 __builtin_amdgcn_sched_barrier(0);   // one group's constants at a time: the registers are needed for weight fragments
-                const v4i mm = *(const v4i *)&prmp[1][oc + 4 * gi], ch = *(const v4i *)&prmp[2][oc + 4 * gi], ss = *(const v4i *)&prmp[3][oc + 4 * gi];
+                const v4i mm = *(const v4i *)&prmp[1][oc + 4 * gi], ch = rq_chi4<RQ>(&prmp[2][oc + 4 * gi]), ss = *(const v4i *)&prmp[3][oc + 4 * gi];
                 int q[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) q[i] = clamp3(requant_tie_free(acc[4 * gi + i], mm[i], ch[i], ss[i]), p.lop, 127);
-                rq[gi] = (int)pack4(q[0], q[1], q[2], q[3]);
+                for (int i = 0; i < 4; ++i) q[i] = rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lop);
+                rq[gi] = (int)rq_pack<RQ>(q[0], q[1], q[2], q[3]);
             }
         }
         // ---- expand + add ----
@@ -312,21 +313,13 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
 #pragma unroll
             for (int gi = 0; gi < 4; ++gi) {
                 __builtin_amdgcn_sched_barrier(0);
-                const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = *(const v4i *)&prm1[2][oc + 4 * gi], ss = *(const v4i *)&prm1[3][oc + 4 * gi];
+                const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = rq_chi4<RQ>(&prm1[2][oc + 4 * gi]), ss = *(const v4i *)&prm1[3][oc + 4 * gi];
                 int q[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int v = clamp3(requant_tie_free(acc[4 * gi + i], mm[i], ch[i], ss[i]), p.lo1, 127);
-                    const int r8 = (int)(int8_t)((uint32_t)rq[gi] >> (8 * i));
-                    if constexpr (TFA) {
-                        const int s = __mul24(v, p.add_mul_self) + (p.add_c0 + p.add_k) + __mul24(r8, p.add_mul_res);
-                        q[i] = clamp3(s >> p.add_sh, p.add_lo, 127);
-                    } else {
-                        const int s = __mul24(v, p.add_mul_self) + p.add_c0 + __mul24(r8, p.add_mul_res);
-                        q[i] = clamp3((s + p.add_k + (s >> 31)) >> p.add_sh, p.add_lo, 127);
-                    }
+                    q[i] = rq_add<RQ, RQA>(rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1), (uint32_t)rq[gi], i, ac);
                 }
-                yv[gi] = (int)pack4(q[0], q[1], q[2], q[3]);
+                yv[gi] = (int)rq_pack<RQA>(q[0], q[1], q[2], q[3]);
             }
             *(v4i *)(Y + px1 * XC + (((oc >> 4) ^ (px1 & 15)) << 4)) = yv;
             const long n1 = (long)n0 + px1;
@@ -351,10 +344,10 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int c = mb * 16 + g * 4 + i;
-                q[i] = clamp3(requant_tie_free(acc2[i], prm2[1][c], prm2[2][c], prm2[3][c]), p.lo2, 127);
+                q[i] = rq_conv<RQ>(acc2[i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2);
             }
             const long n2 = (long)n0 + px;
-            if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * XN2 + mb * 16 + g * 4) = pack4(q[0], q[1], q[2], q[3]);
+            if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * XN2 + mb * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
         }
         buf = buf + 1 == XNB ? 0 : buf + 1;
     }
@@ -366,7 +359,7 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
 
 constexpr int XN2W = 256;
 
-template <bool TFA>
+template <int RQ, int RQA>
 __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParams p) {
     __shared__ __attribute__((aligned(256))) int8_t XY[XNB][XPX * XC];
     __shared__ __attribute__((aligned(16))) int8_t T2[XNB][XPX * XK1];
@@ -375,6 +368,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ntiles = (p.npix + XPX - 1) / XPX, G = gridDim.x;
+    const AddConst ac = add_const<RQA>(p);
     const uint32_t xy_lds = lds_address(&XY[0][0]), t2_lds = lds_address(&T2[0][0]);
 
     // direct-to-LDS loads of a tile: wave w fetches pixels 2 w, 2 w + 1 of the x tile, waves 0 .. 3 also pixels
@@ -401,10 +395,10 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
     if (tile < ntiles) issue_tile(tile, 0);
     if (tile + G < ntiles) issue_tile(tile + G, 1);
     for (int i = tid; i < XC; i += XNT2) {
-        prm1[0][i] = p.bias1[i]; prm1[1][i] = p.m0s1[i]; prm1[2][i] = p.chi1[i]; prm1[3][i] = p.shm11[i];
+        prm1[0][i] = p.bias1[i]; prm1[1][i] = p.m0s1[i]; prm1[2][i] = rq_chi<RQ>(p.chi1[i], p.shm11[i]); prm1[3][i] = rq_sh<RQ>(p.shm11[i]);
     }
     if (tid < XN2W) {
-        prm2[0][tid] = p.bias2[tid]; prm2[1][tid] = p.m0s2[tid]; prm2[2][tid] = p.chi2[tid]; prm2[3][tid] = p.shm12[tid];
+        prm2[0][tid] = p.bias2[tid]; prm2[1][tid] = p.m0s2[tid]; prm2[2][tid] = rq_chi<RQ>(p.chi2[tid], p.shm12[tid]); prm2[3][tid] = rq_sh<RQ>(p.shm12[tid]);
     }
     const uint32_t lane16 = (uint32_t)lane * 16;
     v4i a1[XK1 / 32], a2[XC / 64];   // weight fragments, kept in registers for the whole launch
@@ -457,21 +451,13 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
 #pragma unroll
             for (int gi = 0; gi < 4; ++gi) {
                 __builtin_amdgcn_sched_barrier(0);
-                const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = *(const v4i *)&prm1[2][oc + 4 * gi], ss = *(const v4i *)&prm1[3][oc + 4 * gi];
+                const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = rq_chi4<RQ>(&prm1[2][oc + 4 * gi]), ss = *(const v4i *)&prm1[3][oc + 4 * gi];
                 int q[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int v = clamp3(requant_tie_free(acc[4 * gi + i], mm[i], ch[i], ss[i]), p.lo1, 127);
-                    const int r8 = (int)(int8_t)((uint32_t)rv[gi] >> (8 * i));
-                    if constexpr (TFA) {
-                        const int s = __mul24(v, p.add_mul_self) + (p.add_c0 + p.add_k) + __mul24(r8, p.add_mul_res);
-                        q[i] = clamp3(s >> p.add_sh, p.add_lo, 127);
-                    } else {
-                        const int s = __mul24(v, p.add_mul_self) + p.add_c0 + __mul24(r8, p.add_mul_res);
-                        q[i] = clamp3((s + p.add_k + (s >> 31)) >> p.add_sh, p.add_lo, 127);
-                    }
+                    q[i] = rq_add<RQ, RQA>(rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1), (uint32_t)rv[gi], i, ac);
                 }
-                yv[gi] = (int)pack4(q[0], q[1], q[2], q[3]);
+                yv[gi] = (int)rq_pack<RQA>(q[0], q[1], q[2], q[3]);
             }
             *(v4i *)cell = yv;
             const long n1 = (long)n0 + px1;
@@ -503,9 +489,9 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int c = wave * 16 + g * 4 + i;
-                    q[i] = clamp3(requant_tie_free(acc2[nb][i], prm2[1][c], prm2[2][c], prm2[3][c]), p.lo2, 127);
+                    q[i] = rq_conv<RQ>(acc2[nb][i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2);
                 }
-                if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * XN2W + wave * 16 + g * 4) = pack4(q[0], q[1], q[2], q[3]);
+                if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * XN2W + wave * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
             }
         }
         buf = buf + 1 == XNB ? 0 : buf + 1;
@@ -521,7 +507,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
 
 constexpr int DK1 = 256, DC = 1024, DN2 = 256;
 
-template <bool TFA>
+template <int RQ, int RQA>
 __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrParams p) {
     __shared__ __attribute__((aligned(256))) int8_t XY[XNB][XPX * DC];
     __shared__ __attribute__((aligned(256))) int8_t T2[XNB][XPX * DK1];
@@ -530,6 +516,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ntiles = (p.npix + XPX - 1) / XPX, G = gridDim.x;
+    const AddConst ac = add_const<RQA>(p);
     const uint32_t xy_lds = lds_address(&XY[0][0]), t2_lds = lds_address(&T2[0][0]);
 
     // direct-to-LDS loads of a tile: wave w fetches pixels 2 w and 2 w + 1 of the x tile (one 1024-byte row per load),
@@ -557,10 +544,10 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
     if (tile < ntiles) issue_tile(tile, 0);
     if (tile + G < ntiles) issue_tile(tile + G, 1);
     for (int i = tid; i < DC; i += XNT2) {
-        prm1[0][i] = p.bias1[i]; prm1[1][i] = p.m0s1[i]; prm1[2][i] = p.chi1[i]; prm1[3][i] = p.shm11[i];
+        prm1[0][i] = p.bias1[i]; prm1[1][i] = p.m0s1[i]; prm1[2][i] = rq_chi<RQ>(p.chi1[i], p.shm11[i]); prm1[3][i] = rq_sh<RQ>(p.shm11[i]);
     }
     if (tid < DN2) {
-        prm2[0][tid] = p.bias2[tid]; prm2[1][tid] = p.m0s2[tid]; prm2[2][tid] = p.chi2[tid]; prm2[3][tid] = p.shm12[tid];
+        prm2[0][tid] = p.bias2[tid]; prm2[1][tid] = p.m0s2[tid]; prm2[2][tid] = rq_chi<RQ>(p.chi2[tid], p.shm12[tid]); prm2[3][tid] = rq_sh<RQ>(p.shm12[tid]);
     }
     const uint32_t lane16 = (uint32_t)lane * 16;
     // expand fragments [fm][ksub], kept in registers for the whole launch
@@ -615,21 +602,13 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
 #pragma unroll
             for (int gi = 0; gi < 4; ++gi) {
                 __builtin_amdgcn_sched_barrier(0);   // one group's constants at a time: the registers are needed for weight fragments
-                const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = *(const v4i *)&prm1[2][oc + 4 * gi], ss = *(const v4i *)&prm1[3][oc + 4 * gi];
+                const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = rq_chi4<RQ>(&prm1[2][oc + 4 * gi]), ss = *(const v4i *)&prm1[3][oc + 4 * gi];
                 int q[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int v = clamp3(requant_tie_free(acc[4 * gi + i], mm[i], ch[i], ss[i]), p.lo1, 127);
-                    const int r8 = (int)(int8_t)((uint32_t)rv[gi] >> (8 * i));
-                    if constexpr (TFA) {
-                        const int s = __mul24(v, p.add_mul_self) + (p.add_c0 + p.add_k) + __mul24(r8, p.add_mul_res);
-                        q[i] = clamp3(s >> p.add_sh, p.add_lo, 127);
-                    } else {
-                        const int s = __mul24(v, p.add_mul_self) + p.add_c0 + __mul24(r8, p.add_mul_res);
-                        q[i] = clamp3((s + p.add_k + (s >> 31)) >> p.add_sh, p.add_lo, 127);
-                    }
+                    q[i] = rq_add<RQ, RQA>(rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1), (uint32_t)rv[gi], i, ac);
                 }
-                yv[gi] = (int)pack4(q[0], q[1], q[2], q[3]);
+                yv[gi] = (int)rq_pack<RQA>(q[0], q[1], q[2], q[3]);
             }
             *(v4i *)cell = yv;
             if (n1 < p.npix) *(v4i *)(p.y + n1 * DC + oc) = yv;
@@ -673,9 +652,9 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int c = wave * 16 + g * 4 + i;
-                    q[i] = clamp3(requant_tie_free(acc2[nb][i], prm2[1][c], prm2[2][c], prm2[3][c]), p.lo2, 127);
+                    q[i] = rq_conv<RQ>(acc2[nb][i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2);
                 }
-                if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * DN2 + wave * 16 + g * 4) = pack4(q[0], q[1], q[2], q[3]);
+                if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * DN2 + wave * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
             }
         }
         buf = buf + 1 == XNB ? 0 : buf + 1;
@@ -717,6 +696,8 @@ void expand_reduce_params(const ConvParams &e, const ConvParams &r, const int8_t
     xp.y = y; xp.t1n = t1n;
     xp.a2 = r.wfrag; xp.bias2 = r.bias; xp.m0s2 = r.m0s; xp.chi2 = r.chi; xp.shm12 = r.shm1;
     xp.lo2 = r.relu ? r.zp_out : -128;
+    xp.rq = e.rq & r.rq & (e.fuse_add == 2 ? e.rq2 : RQ_TOP);
+    xp.add_rq = e.add_rq;
     xp.add_c0 = e.add_c0; xp.add_k = e.add_k; xp.add_sh = e.add_sh; xp.add_lo = e.add_lo;
     xp.npix = copies * e.Ho * e.Wo;
     xp.n2 = r.Cout_p;
@@ -742,35 +723,38 @@ void expand_reduce_params(const ConvParams &e, const ConvParams &r, const int8_t
     }
 }
 
-hipError_t launch_expand_reduce(const XrParams &p, int add_tie_free, hipStream_t st) {
+// the kernels serve tie-free convolutions only
+template <class F>
+static void with_tie_free_rq(const XrParams &p, F f) {
+    with_rq(p.rq, p.add_rq, [&](auto rq, auto rqa) { if constexpr ((decltype(rq)::value & RQ_TIE_FREE) != 0) f(rq, rqa); });
+}
+
+hipError_t launch_expand_reduce(const XrParams &p, hipStream_t st) {
     if (p.npix <= 0) return hipSuccess;
+    if (!(p.rq & RQ_TIE_FREE)) return hipErrorInvalidValue;
     if ((long)p.npix * DC >= (1l << 32)) return hipErrorInvalidValue;   // 32-bit byte offsets inside the tensors
     const int ntiles = (p.npix + XPX - 1) / XPX;
     if (p.k1 == DK1) {
         const dim3 grid((unsigned)(ntiles < 256 ? ntiles : 256));
         set_kernel_name("expand_reduce_kernel<256, 1024, 256>");
-        if (add_tie_free) hipLaunchKernelGGL((expand_reduce1024_kernel<true>), grid, dim3(XNT2), 0, st, p);
-        else hipLaunchKernelGGL((expand_reduce1024_kernel<false>), grid, dim3(XNT2), 0, st, p);
+        with_tie_free_rq(p, [&](auto rq, auto rqa) { hipLaunchKernelGGL((expand_reduce1024_kernel<decltype(rq)::value, decltype(rqa)::value>), grid, dim3(XNT2), 0, st, p); });
         return hipGetLastError();
     }
     if (p.in2) {
         const dim3 grid((unsigned)(ntiles < 256 ? ntiles : 256));   // one workgroup of sixteen waves per CU
         set_kernel_name("proj_expand_reduce_kernel<256, 128, 512, 128>");
-        if (add_tie_free) hipLaunchKernelGGL((proj_expand_reduce_kernel<true>), grid, dim3(XNT2), 0, st, p);
-        else hipLaunchKernelGGL((proj_expand_reduce_kernel<false>), grid, dim3(XNT2), 0, st, p);
+        with_tie_free_rq(p, [&](auto rq, auto rqa) { hipLaunchKernelGGL((proj_expand_reduce_kernel<decltype(rq)::value, decltype(rqa)::value>), grid, dim3(XNT2), 0, st, p); });
         return hipGetLastError();
     }
     if (p.n2 == XN2W) {
         const dim3 grid((unsigned)(ntiles < 256 ? ntiles : 256));
         set_kernel_name("expand_reduce_kernel<128, 512, 256>");
-        if (add_tie_free) hipLaunchKernelGGL((expand_reduce256_kernel<true>), grid, dim3(XNT2), 0, st, p);
-        else hipLaunchKernelGGL((expand_reduce256_kernel<false>), grid, dim3(XNT2), 0, st, p);
+        with_tie_free_rq(p, [&](auto rq, auto rqa) { hipLaunchKernelGGL((expand_reduce256_kernel<decltype(rq)::value, decltype(rqa)::value>), grid, dim3(XNT2), 0, st, p); });
         return hipGetLastError();
     }
     const dim3 grid((unsigned)(ntiles < 512 ? ntiles : 512));
     set_kernel_name("expand_reduce_kernel<128, 512, 128>");
-    if (add_tie_free) hipLaunchKernelGGL((expand_reduce_kernel<true>), grid, dim3(XNT), 0, st, p);
-    else hipLaunchKernelGGL((expand_reduce_kernel<false>), grid, dim3(XNT), 0, st, p);
+    with_tie_free_rq(p, [&](auto rq, auto rqa) { hipLaunchKernelGGL((expand_reduce_kernel<decltype(rq)::value, decltype(rqa)::value>), grid, dim3(XNT), 0, st, p); });
     return hipGetLastError();
 }
 

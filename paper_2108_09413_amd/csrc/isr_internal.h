@@ -103,11 +103,13 @@ struct ConvParams {
     // never rounds an exact half and the sign correction of the rounding term is dead: the kernel then
     // takes (mulhi(acc, M0) + chi) >> (shift - 1) (decided per layer when the model is loaded)
     int32_t tie_free;
+    int32_t rq;              // Rq form of this convolution's requantisation (conv_device.h)
     // residual add folded into the epilogue (fuse_add != 0): with q the int8 result above,
     //   v = q * add_mul_self + res * add_mul_res + add_c0            (= (q-z)Ms + (res-zr)Mr)
     //   out = clamp((v + add_k + (v >> 31)) >> add_sh, add_lo, 127)  (add_k = 2^(sh-1) + z_o 2^sh)
     const int8_t *res;       // [B][Ho][Wo][Cout_p] other input of the add
     int32_t fuse_add, add_mul_self, add_mul_res, add_c0, add_k, add_sh, add_lo;
+    int32_t add_rq;          // Rq form of the add
     int32_t add_tie_free;    // 1: no pair of int8 inputs makes v a negative exact half: out = clamp((v + add_k) >> add_sh)
     // fuse_add == 2: the residual is itself the output of a 1x1 stride-1 convolution (same pixels, same
     // channels) that has no other reader; the kernel computes it first, keeps it in registers and never
@@ -115,7 +117,7 @@ struct ConvParams {
     const int8_t *in2;       // [B][Ho][Wo][Cin2_p]
     const int8_t *w2;        // [Mp][Cin2_p] rows in MFMA row order
     const int32_t *bias2, *m0s2, *chi2, *shm12;   // as bias / m0s / chi / shm1
-    int32_t Cin2_p, lo2, tie_free2;                // lo2: lower clamp of the residual tensor
+    int32_t Cin2_p, lo2, tie_free2, rq2;              // lo2: lower clamp of the residual tensor
     const uint32_t *ktab;    // [Kp/16] per 16-byte K chunk: ky | kx<<8, 0xFFFFFFFF = padding chunk; null = plain GEMM
     const int32_t *ktoff;    // [Kp/16] byte offset (ky*W + kx)*Cin_p + channel of the chunk
     const int8_t *zpad;      // 16 bytes of z_in: source of out-of-image taps for loads that go straight to LDS
@@ -140,7 +142,7 @@ struct StemPoolParams {
     const int8_t *w;         // [>= 64][256] rows in MFMA row order, K = (ky, kx padded to 8, channel padded to 4)
     const int32_t *bias, *m0s, *chi, *shm1;   // as in ConvParams (single-multiply requantisation)
     int32_t H, W, Ho, Wo, Hp, Wp;
-    int32_t zp_in, zp_out, relu, tie_free, B;
+    int32_t zp_in, zp_out, relu, rq, B;
     // fused_noise != 0: `in` is unused; the kernel draws the noisy input rows of its band itself (the
     // sampler of the noise stage on the same counter-based stream), copy b of the launch from `noise`
     int32_t fused_noise;
@@ -198,7 +200,7 @@ struct BneckParams {
     int32_t zp_t1;           // zero-point of the first convolution's output (padding value of the 3x3)
     int32_t lo1, lo2, lo3;   // lower clamps of the three int8 results
     int32_t add_mul_self, add_mul_res, add_c0, add_k, add_sh, add_lo;   // as in ConvParams
-    int32_t tie_free;        // every requantisation (and the add) is free of rounding ties
+    int32_t rq, add_rq;      // Rq form (conv_device.h) that serves every convolution of the block; that of the add
 };
 
 // Closing 1x1 convolution + residual add of one bottleneck block and the opening 1x1 convolution of the next
@@ -219,6 +221,7 @@ struct XrParams {
     const int32_t *bias2, *m0s2, *chi2, *shm12;   // reducing convolution [128]
     int32_t lo1, lo2;        // lower clamps of the two convolutions' int8 results
     int32_t add_mul_self, add_mul_res, add_c0, add_k, add_sh, add_lo;   // as in ConvParams
+    int32_t rq, add_rq;      // Rq form that serves every convolution (at least tie-free); that of the add
     int32_t npix;
     int32_t n2;              // output channels of the reducing convolution: 128, or 256 (stored residual only)
     int32_t k1;              // input channels of the expanding convolution: 128 (512 block channels) or 256 (1024; stored residual, n2 = 256)
@@ -362,7 +365,7 @@ hipError_t launch_bottleneck128(const BneckParams &p, hipStream_t st);
 bool expand_reduce_supported(const ConvParams &expand, const ConvParams &reduce);
 void expand_reduce_params(const ConvParams &expand, const ConvParams &reduce, const int8_t *a, const int8_t *b, int8_t *y,
                           int8_t *t1n, int32_t copies, XrParams &xp);
-hipError_t launch_expand_reduce(const XrParams &p, int add_tie_free, hipStream_t st);   // expand_reduce.hip   // 128 middle channels, identity blocks (bottleneck128.hip)
+hipError_t launch_expand_reduce(const XrParams &p, hipStream_t st);   // expand_reduce.hip   // 128 middle channels, identity blocks (bottleneck128.hip)
 bool bottleneck128_supported(int cin_p, int cmid_p, int cout_p);
 hipError_t launch_trans_block(const TransParams &p, hipStream_t st);
 bool trans_block_supported(int cout, int size_out);

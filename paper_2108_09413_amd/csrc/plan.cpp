@@ -157,6 +157,16 @@ void fuse_adds(const ParsedModel &pm, const std::vector<DevOp> &plain, std::vect
                         if (v < 0 && (v & mask) == halfbit) { add_ties = true; break; }
                     }
                 c.conv.add_tie_free = add_ties ? 0 : 1;
+                {   // top form (conv_device.h): multipliers in 24 bits; every sum, or at least each half of it, in
+                    // int32 after scaling by 2^(23 - sh)
+                    const int64_t scale = a.sh <= 23 ? 1ll << (23 - a.sh) : 0;
+                    const int64_t self_lo = std::min(-128 * m_self, 127 * m_self), self_hi = std::max(-128 * m_self, 127 * m_self);
+                    const int64_t res_lo = std::min(-128 * m_res, 127 * m_res) + c0 + k, res_hi = std::max(-128 * m_res, 127 * m_res) + c0 + k;
+                    auto fits = [&](int64_t lo, int64_t hi) { return lo * scale >= INT32_MIN && hi * scale <= INT32_MAX; };
+                    const bool top = scale && c.conv.add_lo == -128 && mag(m_self) * scale < (1 << 23) && mag(m_res) * scale < (1 << 23) &&
+                                     fits(res_lo, res_hi) && fits(self_lo + c0 + k, self_hi + c0 + k);
+                    c.conv.add_rq = add_ties ? 0 : !top ? 1 : fits(self_lo + res_lo, self_hi + res_hi) ? 3 : 4;
+                }
                 c.b = res;
                 c.out = d.out;
                 c.bytes_per_sample += d.bytes_per_sample / 3.0;   // the residual read
@@ -177,6 +187,7 @@ void fuse_adds(const ParsedModel &pm, const std::vector<DevOp> &plain, std::vect
                         merged.conv.wfrag2 = rc.wfrag;
                         merged.conv.lo2 = rc.relu ? rc.zp_out : -128;
                         merged.conv.tie_free2 = rc.tie_free;
+                        merged.conv.rq2 = rc.rq;
                         merged.b = r.a;   // second input tensor (kept alive until this op is issued)
                         merged.ops_per_sample += r.ops_per_sample;
                         merged.bytes_per_sample += r.bytes_per_sample - 2.0 * d.bytes_per_sample / 3.0;   // no residual write + read
@@ -411,6 +422,7 @@ int build_device_ops(const ParsedModel &pm, std::vector<DevOp> &ops, ConstArena 
             std::vector<int8_t> w((size_t)Mp * Kp, 0);
             std::vector<int32_t> bias(Mp, 0);
             bool tie_free = fast;
+            bool top = (o.relu ? to.zp : -128) == -128;   // top form of the requantisation (conv_device.h)
             const int64_t maxdev = std::max<int64_t>(127 - ti.zp, ti.zp + 128);   // |q - z_in| of an int8 input
             std::vector<uint32_t> m0x2(Mp, 0x80000000u), rlo(Mp, 0), rhi(Mp, 1), sh(Mp, 1);
             std::vector<int32_t> m0s(Mp, 1 << 30), chi(Mp, 1 + 2 * to.zp), shm1(Mp, 1);
@@ -431,6 +443,8 @@ int build_device_ops(const ParsedModel &pm, std::vector<DevOp> &ops, ConstArena 
                     const int64_t accmax = std::llabs((int64_t)o.bias[oc]) + maxdev * wabs;
                     const int need = 30 + o.shift[oc] - __builtin_ctz((unsigned)o.M0[oc]);
                     if (need < 40 && accmax >= (1ll << need)) tie_free = false;
+                    // |mulhi(acc, M0)| < 2^23 and 2^(24 - shm1) < 2^23 as 24-bit operands
+                    if ((__int128)accmax * o.M0[oc] >= ((__int128)((1 << 23) - 1) << 32) || o.shift[oc] < 3) top = false;
                 }
                 int64_t b = (int64_t)o.bias[oc] - (int64_t)ti.zp * wsum;
                 if (b < INT32_MIN || b > INT32_MAX) return ISR_ERR_UNSUPPORTED;
@@ -471,6 +485,7 @@ int build_device_ops(const ParsedModel &pm, std::vector<DevOp> &ops, ConstArena 
             c.shm1 = (const int32_t *)arena.put(shm1.data(), shm1.size() * 4);
             c.fast_requant = fast ? 1 : 0;
             c.tie_free = tie_free ? 1 : 0;
+            c.rq = (tie_free ? 1 : 0) | (top ? 2 : 0);
             const std::vector<int8_t> zfill(16, (int8_t)ti.zp);
             c.zpad = (const int8_t *)arena.put(zfill.data(), zfill.size());
             // fragment-major copies for the kernel that runs an expanding 1x1 + add and the next reducing 1x1 together

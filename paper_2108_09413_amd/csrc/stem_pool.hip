@@ -33,6 +33,7 @@ constexpr int SP_STRIP = 31;            // pooled columns per wave
 constexpr int SP_IN_BYTES = 23 * (SP_WMAX + 8) * 4;
 static_assert(39 * (4 * SP_STRIP + 8) * 4 <= SP_IN_BYTES, "one-strip band fits");
 
+template <int RQ>
 __global__ __launch_bounds__(256, 3) void stem_pool_kernel(const StemPoolParams p) {
     __shared__ __attribute__((aligned(16))) int8_t Wl[64 * SP_KP];
     __shared__ __attribute__((aligned(16))) int8_t In[SP_IN_BYTES];
@@ -55,7 +56,7 @@ __global__ __launch_bounds__(256, 3) void stem_pool_kernel(const StemPoolParams 
         const int r = i >> 4, c = i & 15;
         *(v4i *)(&Wl[r * SP_KP + ((c ^ (r & 15)) << 4)]) = *(const v4i *)(p.w + (long)r * SP_KP + c * 16);
     }
-    if (tid < 64) { prm[0][tid] = p.bias[tid]; prm[1][tid] = p.m0s[tid]; prm[2][tid] = p.chi[tid]; prm[3][tid] = p.shm1[tid]; }
+    if (tid < 64) { prm[0][tid] = p.bias[tid]; prm[1][tid] = p.m0s[tid]; prm[2][tid] = rq_chi<RQ>(p.chi[tid], p.shm1[tid]); prm[3][tid] = rq_sh<RQ>(p.shm1[tid]); }
     // input band: pixel (row r, input column x) at patch column x + 3
     const int wchunks = p.W >> 2;             // 16-byte chunks (4 pixels) per input row
     if (p.fused_noise) {
@@ -122,19 +123,12 @@ __global__ __launch_bounds__(256, 3) void stem_pool_kernel(const StemPoolParams 
 #pragma unroll
         for (int i = 0; i < 16; ++i) va[i] = vb[i] = INT_MIN;
 
-        auto emit_as = [&](const int *v, int py, auto tie_free) {
-            int q[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                q[i] = clamp3(requant_q<decltype(tie_free)::value>(v[i], prm[1][oc + i], prm[2][oc + i], prm[3][oc + i]), lo, 127);
-            const v4i o = {(int)pack4(q[0], q[1], q[2], q[3]), (int)pack4(q[4], q[5], q[6], q[7]),
-                           (int)pack4(q[8], q[9], q[10], q[11]), (int)pack4(q[12], q[13], q[14], q[15])};
-            *(v4i *)(p.out + ((((long)b * p.Hp + py) * p.Wp + px) << 6) + oc) = o;
-        };
         auto emit = [&](const int *v, int py) {
             if (py >= p.Hp || !pxok) return;
-            if (p.tie_free) emit_as(v, py, std::true_type{});
-            else emit_as(v, py, std::false_type{});
+            int q[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(v[i], prm[1][oc + i], prm[2][oc + rq_chi_at<RQ>(i)], prm[3][oc + i], lo);
+            *(v4i *)(p.out + ((((long)b * p.Hp + py) * p.Wp + px) << 6) + oc) = rq_pack16<RQ>(q);
         };
 
 #pragma unroll
@@ -194,7 +188,7 @@ hipError_t launch_stem_pool(const StemPoolParams &p, hipStream_t st) {
     const long blocks = (long)p.B * ((p.Hp + P - 1) / P);
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
     set_kernel_name(p.fused_noise ? "stem_pool_kernel (+noise)" : "stem_pool_kernel");
-    hipLaunchKernelGGL(stem_pool_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p);
+    with_rq(p.rq, [&](auto rq) { hipLaunchKernelGGL((stem_pool_kernel<decltype(rq)::value>), dim3((unsigned)blocks), dim3(256), 0, st, p); });
     return hipGetLastError();
 }
 

@@ -458,6 +458,46 @@ def test_exact_halves_in_both_requantisations(isr):
     _check_all_tensors(isr, b.blob(), x, 64, sample=2, chunk=3)
 
 
+@pytest.mark.parametrize("sh,m0,zp,relu_a,ma,mb,add_sh", [
+    (3, (1 << 31) - 1, -128, True, (1 << 20) - 1, (1 << 20) - 3, 20),     # smallest shift of the top-byte form: nearly every output saturates
+    (9, None, 0, True, 700001, 800003, 20),                               # identity block: a rectified and a signed operand
+    (9, None, 5, False, 900001, 1000003, 20),                             # two signed operands: the sum leaves int32 and saturates
+    (10, None, -128, False, -900001, 1000003, 20),                        # a negative multiplier
+    (9, None, 127, False, (1 << 23) - 1, (1 << 22) + 1, 23),              # largest shift of the add in the top-byte form
+    (8, None, -3, True, 5, 3, 2),                                         # small multipliers and shift
+    (22, (1 << 31) - 1, 0, False, 700001, 800003, 20),                    # largest shift: every output at its zero point
+    (9, 3 << 29, 0, True, 700001, 800003, 20),                            # convolution with exact halves
+    (2, None, 0, True, 700001, 800003, 20),                               # shift below the top-byte form
+    (9, None, 0, True, (1 << 20) + 7, 800003, 20),                        # add multiplier above it
+])
+def test_forms_of_the_requantisation(isr, sh, m0, zp, relu_a, ma, mb, add_sh):
+    """Every form of the epilogue (value or top byte, with and without ties, narrow and wide add) at the ends of its
+    range, in the direct-to-LDS kernel (plain, fused add, dual convolution) and the bottleneck kernel."""
+    _say(f"requantisation forms {sh} {m0} {zp} {relu_a} {ma} {mb} {add_sh}")
+    b = NetBuilder(rng=np.random.default_rng(71), in_shape=(3, 9, 12), num_classes=5)
+    kw = lambda c: dict(sh=np.full(c, sh), m0=None if m0 is None else np.full(c, m0, dtype=np.int64))
+    t0 = b.tensor(3, 9, 12, 0, 74.0)
+    t1 = b.conv(t0, 64, 3, 1, 1, relu_a, sh=np.full(64, 8))
+    u = b.conv(t1, 64, 1, 1, 0, True, **kw(64))
+    u = b.conv(u, 64, 3, 1, 1, True, **kw(64))
+    u = b.conv(u, 64, 1, 1, 0, False, zp_out=zp, **kw(64))
+    t2 = b.add(t1, u, True, ma=ma, mb=mb, sh=add_sh)           # identity bottleneck block
+    s_ = b.conv(t2, 256, 1, 1, 0, False, zp_out=zp, **kw(256))
+    u = b.conv(t2, 64, 1, 1, 0, True, **kw(64))
+    u = b.conv(u, 64, 3, 1, 1, True, **kw(64))
+    u = b.conv(u, 256, 1, 1, 0, False, **kw(256))
+    t3 = b.add(s_, u, False, ma=ma, mb=mb, sh=add_sh, zp_out=-128)   # projection bottleneck block
+    u = b.conv(t3, 128, 3, 1, 1, False, zp_out=zp, **kw(128))
+    v = b.conv(u, 128, 3, 1, 1, relu_a, **kw(128))
+    t4 = b.add(v, u, True, ma=ma, mb=mb, sh=add_sh)            # residual add in a convolution's epilogue
+    s_ = b.conv(t4, 192, 1, 1, 0, False, zp_out=zp, **kw(192))
+    u = b.conv(t4, 192, 3, 1, 1, False, **kw(192))
+    t5 = b.add(u, s_, True, ma=ma, mb=mb, sh=add_sh)           # the residual a second convolution
+    b.fc(b.gap(t5), 5)
+    x = np.random.default_rng(9).integers(0, 256, size=(3, 9, 12)).astype(np.uint8)
+    _check_all_tensors(isr, b.blob(), x, 64, sample=2, chunk=3)
+
+
 # ---- S6-S8: logits, votes, decisions -----------------------------------------
 
 def test_config0_full_certify_and_predict(isr):
