@@ -156,7 +156,7 @@ def run_config(isr, synth, torch, cfg_id, chunk, steps, profile_every, n_overrid
     return dt, steps * batch * (n0 + n), stats, results[-1], ctx
 
 
-FP32_MFMA_PEAK_TFLOPS = 157.3   # MI355X dense fp32 matrix peak
+FP32_MFMA_PEAK_TFLOPS = 2500.0 / 3   # dense bfloat16 matrix peak over the three exact products of an fp32 activation
 
 
 def run_float_system(isr, synth, torch, cfg_id, chunk, system, n, steps, profile_every=4):

@@ -62,6 +62,14 @@ int mfma_row_of_channel(int c) {
     return 8 * a + 4 * h + b;
 }
 
+// the upper half of the fp32 number: exact for 8-bit integers
+uint16_t bf16_of_int8(int8_t v) {
+    const float f = v;
+    uint32_t bits;
+    std::memcpy(&bits, &f, 4);
+    return (uint16_t)(bits >> 16);
+}
+
 size_t put(std::vector<uint8_t> &arena, const void *src, size_t bytes) {
     const size_t off = (arena.size() + 255) & ~(size_t)255;
     arena.resize(off + bytes);
@@ -78,11 +86,12 @@ int build_conv(const ParsedModel &pm, const HostOp &o, int k, int stride, int pa
     c.H = ti.H; c.W = ti.W; c.Cin_p = ti.Cp; c.Ho = to.H; c.Wo = to.W; c.Cout_p = to.Cp;
     const int bm = fconv_tile_m(c.Cout_p);
     c.Cout_pp = (c.Cout_p + bm - 1) / bm * bm;
-    c.stride = stride; c.pad = pad;
+    c.k = k; c.stride = stride; c.pad = pad;
     const int kq_real = k * k * ti.Cp / 4;
-    c.Kq = (kq_real + 3) & ~3;
+    c.Kq = (kq_real + 7) & ~7;
     c.relu = fc ? 0 : o.relu;
-    std::vector<float> w((size_t)c.Kq * c.Cout_pp * 4, 0.f), bias(c.Cout_pp, 0.f), scale(c.Cout_pp, 0.f);
+    std::vector<uint16_t> w((size_t)c.Kq * c.Cout_pp * 4, 0);
+    std::vector<float> bias(c.Cout_pp, 0.f), scale(c.Cout_pp, 0.f);
     std::vector<int32_t> ktab(c.Kq, -1);
     for (int kq = 0; kq < kq_real; ++kq) {
         const int tap = 4 * kq / ti.Cp, coff = 4 * kq % ti.Cp;
@@ -93,13 +102,13 @@ int build_conv(const ParsedModel &pm, const HostOp &o, int k, int stride, int pa
         for (int ic = 0; ic < ti.C; ++ic)
             for (int t = 0; t < k * k; ++t) {
                 const int kidx = t * ti.Cp + ic;
-                w[((size_t)(kidx / 4) * c.Cout_pp + row) * 4 + kidx % 4] = (float)o.w[((size_t)oc * ti.C + ic) * k * k + t];
+                w[((size_t)(kidx / 32) * c.Cout_pp + row) * 32 + kidx % 32] = bf16_of_int8(o.w[((size_t)oc * ti.C + ic) * k * k + t]);
             }
         bias[oc] = (float)o.bias[oc];
         scale[oc] = fc ? 1.f : (float)std::ldexp((double)o.M0[oc], -(31 + o.shift[oc]));
     }
     // offsets now, pointers after the upload
-    c.w = (const float *)put(arena, w.data(), w.size() * 4);
+    c.w = (const uint16_t *)put(arena, w.data(), w.size() * 2);
     c.bias = (const float *)put(arena, bias.data(), bias.size() * 4);
     c.scale = (const float *)put(arena, scale.data(), scale.size() * 4);
     c.ktab = (const int32_t *)put(arena, ktab.data(), ktab.size() * 4);
@@ -168,7 +177,8 @@ int build_float_net(isr_model *m) {
     for (FloatOp &f : net->ops)
         if (f.type == OP_CONV || f.type == OP_FC) {
             FConvParams &c = f.conv;
-            c.w = (const float *)(net->dconst + (size_t)c.w);
+            c.w = (const uint16_t *)(net->dconst + (size_t)c.w);
+            c.zeros = (const float *)net->dconst;   // the arena starts with 256 zero bytes
             c.bias = (const float *)(net->dconst + (size_t)c.bias);
             c.scale = (const float *)(net->dconst + (size_t)c.scale);
             c.ktab = (const int32_t *)(net->dconst + (size_t)c.ktab);

@@ -1,9 +1,12 @@
 // Kernels of the two floating-point comparison systems of the paper's evaluation (section
 // "Experiments": FloatRS-quant, FloatRS-fp): continuous Gaussian noise on the image, then either
 // rounding back onto the pixel grid (the int8 network follows) or the fp32 network, whose
-// convolutions run here as implicit GEMMs on the fp32 MFMA.
+// convolutions run here as implicit GEMMs on the bfloat16 MFMA with exactly split operands.
 #include <hip/hip_runtime.h>
 
+#include <string>
+
+#include "conv_device.h"
 #include "isr_internal.h"
 #include "noise_device.h"
 
@@ -13,7 +16,6 @@ namespace {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
-typedef int v4i __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // The binary32 standard-normal sampler.  Every step is one IEEE operation (+, -, *, /, sqrt,
@@ -148,27 +150,57 @@ __global__ __launch_bounds__(256) void float_noise_kernel(const FloatNoiseParams
 }
 
 // ---------------------------------------------------------------------------
-// fp32 convolution: implicit GEMM on v_mfma_f32_32x32x2_f32.  A = weights (rows = output channels),
-// B = im2col pixels (columns), K = (tap, channel) cut into quads of 4 consecutive channels; a step
-// of the main loop covers 4 quads.  Both operands are staged in LDS as [quad][row][4 floats]; in a
-// step's MFMA pair index the lanes 0-31 (k = 0) take their element from quad 2h and the lanes 32-63
-// (k = 1) from quad 2h + 1, so each lane reads one 16-byte vector per fragment and uses all of it.
-// Global loads of the next step are issued before the MFMAs of the current one (registers), stored
-// to the other LDS stage after them; one barrier per step.
+// fp32 convolution: implicit GEMM on v_mfma_f32_32x32x16_bf16 with exact operands.  A = weights (rows = output channels),
+// B = im2col pixels (columns), K = (tap, channel) in steps of 32.
 //
-// Workgroup tile: 32 MT WM channels x 32 NT WN pixels, four waves as WM x WN.
+// The weights are the int8 codes of the quantized network: whole numbers of at most 8 bits, exact in bfloat16.  An fp32
+// activation is the exact sum of three bfloat16 numbers, x = x1 + x2 + x3, each the leading 8 bits of what the ones before
+// leave (24 = 8 + 8 + 8).  So x w = x1 w + x2 w + x3 w with every product exact in fp32 (8 x 8 bits) and fp32
+// accumulation: the arithmetic of an fp32 matrix instruction without its rounding of the products, at a third of the
+// bfloat16 rate (2500 / 3 = 833 TFLOP/s nominal) instead of the fp32 one (157).
+//
+// Both operands go from global memory straight into LDS, two steps deep: the weights as bfloat16 rows of 64 bytes, the
+// pixels as fp32 rows of 128 bytes (4 bytes an element to read where three stored parts would be 6); 16-byte chunks
+// swizzled on the global side (conv_device.h).  Out-of-image taps come from a page of zeros.  Each of the four waves owns all BM channels of its own
+// 32 NT pixels, so a pixel fragment is split in registers by one wave only: 5.5 instructions an element, for MT MFMAs of
+// 32 cycles per 8 of them.
+//
+// ResNet-50 at 224 x 224, 668 copies: 58 -> 26.8 ms for all layers (1x1 layers at 56 x 56 within 1.05 - 1.6 of a copy at
+// 5 TB/s, 3x3 layers 2.0 - 2.8 times the matrix time: the split and the loads), 96 -> 213 TFLOP/s on 128-channel tiles.
+// Error of the logits against binary64 (2-norm): ResNet-20 2.0e-7 -> 1.6e-7, ResNet-50 8.2e-7 -> 6.4e-7, ResNet-110
+// 3.1e-7 -> 5.6e-7 (the matrix unit rounds to nearest when it adds to the accumulator, but cuts the products of a group
+// of 8 at 2^-24 of the largest).
+//
+// FLAT: 1x1 stride-1 layers; else TABLE: K chunks of 4 channels looked up in ktab (a tap changes inside a step), else a
+// step lies inside one tap (Cin a multiple of 32) and its tap is counted along.
 
-template <int MT, int NT, int WM, int WN>
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+enum FAddress { F_FLAT, F_TAP, F_TABLE };
+
+// the three bfloat16 parts of 8 floats, 8 to a register quadruple
+__device__ __forceinline__ void split_bf16(const v4f &lo, const v4f &hi, v4i (&part)[3]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = i < 2 ? lo[2 * i] : hi[2 * i - 4], b = i < 2 ? lo[2 * i + 1] : hi[2 * i - 3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            part[k][i] = (int)__builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);   // both upper halves
+            if (k < 2) {
+                a = a - __uint_as_float(__float_as_uint(a) & 0xFFFF0000u);   // exact
+                b = b - __uint_as_float(__float_as_uint(b) & 0xFFFF0000u);
+            }
+        }
+    }
+}
+
+template <int MT, int NT, int ADDR>
 __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
-    constexpr int BM = 32 * MT * WM, BN = 32 * NT * WN;
-    constexpr int ASTR = BM * 4 + 8, BSTR = BN * 4 + 8;        // floats per quad row group; +8 words keeps the 4 quads on distinct banks
-    constexpr int STAGE = 4 * ASTR + 4 * BSTR;
-    constexpr int NA = (BM * 4 + 255) / 256, NB = BN * 4 / 256;
-    static_assert(WM * WN == 4 && BN * 4 % 256 == 0, "four waves; whole float4 rounds for the pixel operand");
-    __shared__ __attribute__((aligned(16))) float lds[2 * STAGE];
+    constexpr int BM = 32 * MT, BN = 128 * NT;
+    constexpr int ASTAGE = BM * 64, STAGE = ASTAGE + BN * 128;   // bytes
+    constexpr int NA = (BM + 63) / 64, NB = BN / 32;             // direct-to-LDS loads per lane and step
+    __shared__ __attribute__((aligned(256))) int8_t lds[2 * STAGE];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % WM, wn = wave / WM;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const int mtiles = p.Cout_pp / BM;
     // Workgroup ids are dealt round-robin over the 8 XCDs (each with its own L2): renumber them so that an XCD
@@ -179,23 +211,68 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
     const long bid = xcd * per + (xcd < rem ? xcd : rem) + slot;   // XCD x owns per (+1 for x < rem) consecutive ids
     const int ch0 = (int)(bid % mtiles) * BM;
     const long px0 = (bid / mtiles) * BN;
+    const uint32_t lds0 = lds_address(lds);
 
-    const int bq = tid & 3;
-    int b_iy0[NB], b_ix0[NB];
-    long b_base[NB];
-    bool b_ok[NB];
+    // The lane's place in a step: of the pixels, 16-byte chunk `bc` (4 channels) of rows tid / 8 + 32 j; of the weights,
+    // chunk `ac` (8 channels) of rows tid / 4 + 64 j.  LDS position (row, c) holds chunk c ^ swz(row), the same for all
+    // rows of a lane.
+    const int brow = tid >> 3, bc = (tid & 7) ^ swz<8>(brow);
+    const int arow = tid >> 2, ac = (tid & 3) ^ swz<4>(arow);
+    const uint8_t *wsrc = (const uint8_t *)p.w + ((size_t)(ch0 + arow) * 64 + ac * 16);
+    const uint8_t *in = (const uint8_t *)p.in;
+    uint32_t boff[NB];          // byte offset of tap (0, 0) of the lane's pixel (of the pixel itself: FLAT), wrapping below 0
+    int iy0[NB], ix0[NB];
     const int hw_o = p.Ho * p.Wo;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-        const long P = px0 + (tid >> 2) + 64 * j;
-        b_ok[j] = P < p.npix;
-        const long Pc = b_ok[j] ? P : 0;
-        const int b = (int)(Pc / hw_o), r = (int)(Pc - (long)b * hw_o);
-        const int oy = r / p.Wo, ox = r - oy * p.Wo;
-        b_iy0[j] = oy * p.stride - p.pad;
-        b_ix0[j] = ox * p.stride - p.pad;
-        b_base[j] = (long)b * p.H * p.W;
+        const long P = px0 + brow + 32 * j;
+        const int n = (int)(P < p.npix ? P : p.npix - 1);      // pixels past the end repeat the last one; never stored
+        if constexpr (ADDR == F_FLAT) {
+            boff[j] = (uint32_t)n * (uint32_t)(p.Cin_p * 4) + (uint32_t)(bc * 16);
+        } else {
+            const int b = n / hw_o, r = n - b * hw_o, oy = r / p.Wo, ox = r - oy * p.Wo;
+            const int y = oy * p.stride - p.pad, x = ox * p.stride - p.pad;
+            iy0[j] = y;
+            ix0[j] = x;
+            boff[j] = (uint32_t)(((b * p.H + y) * p.W + x) * p.Cin_p * 4) + (ADDR == F_TAP ? (uint32_t)(bc * 16) : 0u);
+        }
     }
+    const int nsteps = p.Kq >> 3;
+    int dy = 0, dx = 0, c0 = 0;                 // F_TAP: tap and first channel of the next step to fetch
+    int entry = ADDR == F_TABLE ? p.ktab[bc] : 0;   // F_TABLE: the lane's quad of the next step to fetch
+    auto issue = [&](int step, int buf) {
+        const uint32_t a = lds0 + buf * STAGE + wave * 1024, b = lds0 + buf * STAGE + ASTAGE + wave * 1024;
+#pragma unroll
+        for (int j = 0; j < NA; ++j)
+            if (BM >= 64 || wave < 2)
+                ISR_GLOBAL_TO_LDS16_AT(wsrc + (size_t)step * p.Cout_pp * 64 + j * 4096, a + j * 4096);
+        if constexpr (ADDR == F_FLAT) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j) ISR_GLOBAL_TO_LDS16_AT(in + (boff[j] + (uint32_t)step * 128u), b + j * 4096);
+        } else {
+            bool real = true;
+            uint32_t toff;
+            if constexpr (ADDR == F_TAP) {
+                toff = (uint32_t)(((dy * p.W + dx) * p.Cin_p + c0) * 4);
+            } else {
+                const int e = entry;
+                if (step + 1 < nsteps) entry = p.ktab[(step + 1) * 8 + bc];
+                dy = e >> 24; dx = (e >> 16) & 0xFF;
+                toff = (uint32_t)(((dy * p.W + dx) * p.Cin_p + (e & 0xFFFF)) * 4);
+                real = e >= 0;
+            }
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const bool ok = (int)real & (int)((unsigned)(iy0[j] + dy) < (unsigned)p.H) & (int)((unsigned)(ix0[j] + dx) < (unsigned)p.W);
+                const uint8_t *src = in + (boff[j] + toff);
+                ISR_GLOBAL_TO_LDS16_AT(ok ? src : (const uint8_t *)p.zeros, b + j * 4096);
+            }
+            if constexpr (ADDR == F_TAP) {
+                c0 += 32;
+                if (c0 == p.Cin_p) { c0 = 0; if (++dx == p.k) { dx = 0; ++dy; } }
+            }
+        }
+    };
 
     v16f acc[MT][NT];
 #pragma unroll
@@ -205,71 +282,44 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
-    v4f ga[NA], gb[NB];
-    auto gload = [&](int step) {
+    issue(0, 0);
+    for (int step = 0; step < nsteps; ++step) {
+        wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();   // every wave's loads of this step landed; every wave is done reading the other buffer
+        if (step + 1 < nsteps) issue(step + 1, (step + 1) & 1);
+        const int8_t *A = lds + (step & 1) * STAGE, *B = A + ASTAGE;
 #pragma unroll
-        for (int j = 0; j < NA; ++j) {
-            const int idx = tid + 256 * j;
-            if (idx < BM * 4) {
-                const int q = idx / BM, row = idx % BM;
-                ga[j] = *(const v4f *)(p.w + ((long)(step * 4 + q) * p.Cout_pp + ch0 + row) * 4);
+        for (int ks = 0; ks < 2; ++ks) {
+            v4i af[MT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const int r = i * 32 + l32;
+                af[i] = *(const v4i *)(A + r * 64 + (((2 * ks + half) ^ swz<4>(r)) << 4));
+            }
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const int r = (wave * NT + j) * 32 + l32, c = 4 * ks + 2 * half;
+                const v4f x0 = *(const v4f *)(B + r * 128 + ((c ^ swz<8>(r)) << 4)), x1 = *(const v4f *)(B + r * 128 + (((c + 1) ^ swz<8>(r)) << 4));
+                v4i part[3];
+                split_bf16(x0, x1, part);
+#pragma unroll
+                for (int k = 2; k >= 0; --k)    // the small parts first
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, af[i]), __builtin_bit_cast(v8bf, part[k]),
+                                                                             acc[i][j], 0, 0, 0);
             }
         }
-        const int e = p.ktab[step * 4 + bq];
-        const int dy = e >> 24, dx = (e >> 16) & 0xFF, coff = e & 0xFFFF;
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const int iy = b_iy0[j] + dy, ix = b_ix0[j] + dx;
-            const bool inb = b_ok[j] && e >= 0 && (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W;
-            gb[j] = inb ? *(const v4f *)(p.in + (b_base[j] + (long)iy * p.W + ix) * p.Cin_p + coff) : v4f{0.f, 0.f, 0.f, 0.f};
-        }
-    };
-    auto lstore = [&](int stage) {
-        float *A = lds + stage * STAGE, *B = A + 4 * ASTR;
-#pragma unroll
-        for (int j = 0; j < NA; ++j) {
-            const int idx = tid + 256 * j;
-            if (idx < BM * 4) *(v4f *)(A + (idx / BM) * ASTR + (idx % BM) * 4) = ga[j];
-        }
-#pragma unroll
-        for (int j = 0; j < NB; ++j) *(v4f *)(B + bq * BSTR + ((tid >> 2) + 64 * j) * 4) = gb[j];
-    };
-
-    const int nsteps = p.Kq >> 2;
-    gload(0);
-    lstore(0);
-    __syncthreads();
-    for (int step = 0; step < nsteps; ++step) {
-        if (step + 1 < nsteps) gload(step + 1);
-        const float *A = lds + (step & 1) * STAGE, *B = A + 4 * ASTR;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int q = 2 * h + half;
-            v4f af[MT], bf[NT];
-#pragma unroll
-            for (int i = 0; i < MT; ++i) af[i] = *(const v4f *)(A + q * ASTR + ((wm * MT + i) * 32 + l32) * 4);
-#pragma unroll
-            for (int j = 0; j < NT; ++j) bf[j] = *(const v4f *)(B + q * BSTR + ((wn * NT + j) * 32 + l32) * 4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
-#pragma unroll
-                    for (int j = 0; j < NT; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][e], bf[j][e], acc[i][j], 0, 0, 0);
-        }
-        if (step + 1 < nsteps) lstore((step + 1) & 1);
-        __syncthreads();
     }
 
     // epilogue: with the weight rows in MFMA row order a lane holds 16 consecutive channels of one pixel
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-        const long P = px0 + (wn * NT + j) * 32 + l32;
+        const long P = px0 + (wave * NT + j) * 32 + l32;
         if (P >= p.npix) continue;
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
-            const int chb = ch0 + (wm * MT + i) * 32 + 16 * half;
+            const int chb = ch0 + i * 32 + 16 * half;
             if (chb >= p.Cout_p) continue;                     // Cout_p is a multiple of 16: the run is stored whole or not at all
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
@@ -398,24 +448,39 @@ hipError_t launch_float_noise(const FloatNoiseParams &p, hipStream_t st) {
 
 int fconv_tile_m(int cout_p) { return cout_p <= 32 ? 32 : (cout_p <= 64 ? 64 : 128); }
 
+template <int MT, int NT>
+static hipError_t launch_fconv_tile(const FConvParams &p, hipStream_t st) {
+    const long blocks = (((long)p.npix + 128 * NT - 1) / (128 * NT)) * (p.Cout_pp / (32 * MT));
+    if (blocks > 0x7FFFFFFFL) return hipErrorInvalidValue;
+    static const std::string name = "fconv_kernel<" + std::to_string(32 * MT) + " x " + std::to_string(128 * NT) + ">";
+    set_kernel_name(name.c_str());
+    const dim3 grid((unsigned)blocks), block(256);
+    if (p.k == 1 && p.stride == 1 && p.pad == 0 && p.Cin_p % 32 == 0) hipLaunchKernelGGL((fconv_kernel<MT, NT, F_FLAT>), grid, block, 0, st, p);
+    else if (p.Cin_p % 32 == 0) hipLaunchKernelGGL((fconv_kernel<MT, NT, F_TAP>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((fconv_kernel<MT, NT, F_TABLE>), grid, block, 0, st, p);
+    return hipGetLastError();
+}
+
 hipError_t launch_fconv(const FConvParams &p, hipStream_t st) {
     if (p.npix <= 0) return hipSuccess;
     const int bm = fconv_tile_m(p.Cout_p);
-    if (p.Kq <= 0 || (p.Kq & 3) || p.Cout_pp % bm != 0 || p.Cout_p > p.Cout_pp || (p.Cout_p & 15) || (p.Cin_p & 3))
+    // 32-bit byte offsets inside the input tensor
+    if (p.Kq <= 0 || (p.Kq & 7) || p.Cout_pp % bm != 0 || p.Cout_p > p.Cout_pp || (p.Cout_p & 15) || (p.Cin_p & 3) || !p.zeros ||
+        (long)p.npix / ((long)p.Ho * p.Wo) * p.H * p.W * p.Cin_p >= (1L << 30))
         return hipErrorInvalidValue;
-    const long ptiles = ((long)p.npix + 127) / 128, blocks = ptiles * (p.Cout_pp / bm);
-    if (blocks > 0x7FFFFFFFL) return hipErrorInvalidValue;
+    // The largest tile (fewest bytes into LDS and fewest splits per multiply) that still gives every CU its two
+    // workgroups; launches with few pixels take smaller ones.
+    auto tiles = [&](int m, int n) { return (((long)p.npix + n - 1) / n) * (p.Cout_pp / m); };
+    constexpr long FULL = 512;
     if (bm == 128) {
-        set_kernel_name("fconv_kernel<128 x 128>");
-        hipLaunchKernelGGL((fconv_kernel<2, 2, 2, 2>), dim3((unsigned)blocks), dim3(256), 0, st, p);
-    } else if (bm == 64) {
-        set_kernel_name("fconv_kernel<64 x 128>");
-        hipLaunchKernelGGL((fconv_kernel<2, 1, 1, 4>), dim3((unsigned)blocks), dim3(256), 0, st, p);
-    } else {
-        set_kernel_name("fconv_kernel<32 x 128>");
-        hipLaunchKernelGGL((fconv_kernel<1, 1, 1, 4>), dim3((unsigned)blocks), dim3(256), 0, st, p);
+        if (tiles(128, 256) >= FULL) return launch_fconv_tile<4, 2>(p, st);
+        if (tiles(128, 128) >= FULL) return launch_fconv_tile<4, 1>(p, st);
     }
-    return hipGetLastError();
+    if (bm >= 64) {
+        if (tiles(64, 256) >= FULL) return launch_fconv_tile<2, 2>(p, st);
+        if (tiles(64, 128) >= FULL) return launch_fconv_tile<2, 1>(p, st);
+    }
+    return tiles(32, 256) >= FULL ? launch_fconv_tile<1, 2>(p, st) : launch_fconv_tile<1, 1>(p, st);
 }
 
 hipError_t launch_fadd(const FAddParams &p, hipStream_t st) {

@@ -320,10 +320,11 @@ struct FConvParams {
     const float *in;         // [B][H][W][Cin_p]
     float *out;              // [B][Ho][Wo][Cout_p]
     const float *res;        // [B][Ho][Wo][Cout_p] or null
-    const float *w;          // [Kq][Cout_pp][4]: quad kq holds k = 4 kq .. 4 kq + 3 of K = (tap, channel); rows in MFMA row order per 32 channels
+    const uint16_t *w;       // bfloat16 [Kq / 8][Cout_pp][32]: step s holds k = 32 s .. + 31 of K = (tap, channel); rows in MFMA row order per 32 channels
+    const float *zeros;      // 16 bytes of zeros: source of out-of-image taps
     const float *bias, *scale;   // [Cout_pp], by channel
     const int32_t *ktab;     // [Kq]: dy << 24 | dx << 16 | channel offset of the quad; -1 = padding quad
-    int32_t H, W, Cin_p, Ho, Wo, Cout_p, Cout_pp, stride, pad, Kq;   // Kq a multiple of 4
+    int32_t H, W, Cin_p, Ho, Wo, Cout_p, Cout_pp, k, stride, pad, Kq;   // k x k taps; Kq quads of K, a multiple of 8
     int32_t npix;            // B * Ho * Wo
     int32_t relu, add_relu;
     float ma, mb;

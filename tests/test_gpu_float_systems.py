@@ -153,6 +153,36 @@ def test_floatrs_fp_layer_tensors(isr, cfg, size):
     m.close()
 
 
+@pytest.mark.parametrize("copies", [1, 9, 40, 80])
+def test_floatrs_fp_every_tile_and_addressing_form(isr, copies):
+    """The fp32 convolution on every tile its launcher picks (few to many pixels), with plain, tap-wise and table
+    addressing, on maps whose pixels and channels divide no tile; the last copies' logits against the oracle."""
+    _say(f"FloatRS-fp tiles, {copies} copies")
+    from synth.models import NetBuilder
+    b = NetBuilder(rng=np.random.default_rng(81), in_shape=(3, 43, 44), num_classes=6)
+    t0 = b.tensor(3, 43, 44, 0, 74.0)
+    t = b.conv(t0, 128, 3, 1, 1, True)           # table: 4 stored channels, 128-channel tiles
+    u = b.conv(t, 128, 3, 1, 1, True)            # tap by tap
+    u = b.conv(u, 128, 1, 1, 0, False)           # plain, fused add
+    t = b.add(t, u, True)
+    t = b.conv(t, 64, 1, 1, 0, True)
+    t = b.conv(t, 48, 5, 2, 2, True)             # 64-channel tiles, 48 of them real; stride 2
+    t = b.conv(t, 80, 3, 1, 0, True)             # table: a step of 32 spans taps; unpadded
+    t = b.conv(t, 32, 1, 2, 0, True)
+    t = b.conv(t, 16, 3, 1, 1, True)
+    b.fc(b.gap(t), 6)
+    blob = b.blob()
+    m = _load(isr, blob, 4 * copies)
+    om = oracle.Model(blob)
+    x = np.random.default_rng(5).integers(0, 256, size=(3, 43, 44)).astype(np.uint8)
+    lg, am, cnt = isr.isr_float_debug_forward(m, x, 63.75, 3, 1, 1, 50, copies, FP)
+    k = min(copies, 3)
+    wl = om.mc_float(x, 63.75, 3, 1, 1, 50 + copies - k, k, FP)[0]
+    _check_fp_logits(lg[-k:], wl, am[-k:])
+    assert cnt.sum() == copies
+    m.close()
+
+
 def test_floatrs_fp_resnet50_full_size(isr):
     """224 x 224 inputs in the benchmarked chunk: a few scattered sample indices of a long run."""
     _say("FloatRS-fp ResNet-50 full size")
