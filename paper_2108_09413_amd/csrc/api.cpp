@@ -52,6 +52,105 @@ int get_table(isr_model *m, uint32_t sigma, const DeviceNoiseTable **out) {
     return ISR_OK;
 }
 
+// The constant arguments of the narrow-net ops of the fused plans: block descriptors and per-channel constants packed
+// in the form the kernel stages them, in one device buffer.  `arena` is the host image of the constants at m->dconst.
+int build_narrow_ops(isr_model *m, const ConstArena &arena) {
+    std::vector<NarrowBlock> blocks;
+    std::vector<int32_t> consts;
+    auto host = [&](const int32_t *dev) { return (const int32_t *)(arena.host.data() + ((const uint8_t *)dev - m->dconst)); };
+    auto form_of = [](int rq, bool add_top) { return rq == RQ_TOP && add_top ? 0 : rq_is_top(rq) ? 1 : 2; };
+    auto pack = [&](const ConvParams &c, int form) {   // [4][C], returns its offset
+        const size_t off = consts.size();
+        const int C = c.Cout_p;
+        consts.resize(off + 4 * C);
+        int32_t *k = consts.data() + off;
+        for (int i = 0; i < C; ++i) {
+            const int shm1 = host(c.shm1)[i];
+            k[i] = host(c.bias)[i];
+            k[C + i] = host(c.m0s)[i];
+            k[2 * C + i] = form < 2 ? (int32_t)((uint32_t)host(c.chi)[i] << (24 - shm1)) : host(c.chi)[i];
+            k[3 * C + i] = form < 2 ? 1 << (24 - shm1) : shm1;
+        }
+        return off;
+    };
+    auto add_of = [](const ConvParams &c, bool top) {
+        AddConst a{c.add_mul_self, c.add_mul_res, c.add_c0, c.add_k, c.add_sh, c.add_lo};
+        if (top) {   // as add_const of the kernels
+            const int s = 23 - c.add_sh;
+            a = AddConst{c.add_mul_self << s, c.add_mul_res << s, (c.add_c0 + c.add_k) << s, 0, 0, 0};
+        }
+        return a;
+    };
+    auto lo_of = [](const ConvParams &c) { return c.relu ? c.zp_out : -128; };
+    for (int pi = 1; pi <= 2; ++pi)
+        for (DevOp &d : m->plan[pi].ops) {
+            if (!d.narrow) continue;
+            NarrowParams &np = d.np;
+            // offsets now (+ 1: 0 stays "none"), pointers after the upload
+            for (const DevOp &q : d.parts) {
+                const ConvParams &c1 = q.conv, &c2 = q.conv2, &cp = q.conv3;
+                if (q.stem16) {
+                    np.stem = 1;
+                    np.form0 = form_of(c1.rq, true);
+                    np.w0 = c1.w; np.zp_in = c1.zp_in; np.lo0 = lo_of(c1);
+                    np.prm0 = (const int32_t *)(pack(c1, np.form0) + 1);
+                } else if (q.block) {
+                    np.nblocks = (int32_t)q.chain.size();
+                    np.blocks = (const NarrowBlock *)(blocks.size() + 1);
+                    for (const auto &blk : q.chain) {
+                        const ConvParams &a = blk.first, &b = blk.second;
+                        NarrowBlock nb{};
+                        nb.form = form_of(a.rq & b.rq, b.add_rq == RQ_TOP);
+                        nb.w1 = a.w; nb.w2 = b.w;
+                        nb.prm1 = (const int32_t *)pack(a, nb.form);
+                        nb.prm2 = (const int32_t *)pack(b, nb.form);
+                        nb.zp_x = a.zp_in; nb.zp_t = a.zp_out; nb.lo1 = lo_of(a); nb.lo2 = lo_of(b);
+                        nb.add = add_of(b, nb.form == 0);
+                        blocks.push_back(nb);
+                    }
+                } else if (q.trans) {
+                    np.tail = 1;
+                    np.tform = form_of(c1.rq & c2.rq & cp.rq, rq_is_top(cp.add_rq));
+                    np.tw1 = c1.w; np.tw2 = c2.w; np.twp = cp.w;
+                    np.tprm = (const int32_t *)(pack(c1, np.tform) + 1);
+                    pack(c2, np.tform);
+                    pack(cp, np.tform);
+                    np.tzp_x = c1.zp_in; np.tzp_t = c1.zp_out;
+                    np.tlo1 = lo_of(c1); np.tlo2 = lo_of(c2); np.tlop = lo_of(cp);
+                    np.tadd = add_of(cp, np.tform == 0);
+                } else if (q.type == OP_CONV) {
+                    np.tail = 2;
+                    np.tform = form_of(c1.rq, true);
+                    np.tw1 = c1.w;
+                    np.tprm = (const int32_t *)(pack(c1, np.tform) + 1);
+                    consts.resize(consts.size() + 2 * 4 * c1.Cout_p);   // the kernel stages three convolutions' constants
+                    np.tzp_x = c1.zp_in; np.tzp_t = c1.zp_out; np.tlo1 = lo_of(c1);
+                } else if (q.type == OP_GAP) {
+                    np.head = 1;
+                    np.gap_zp_in = q.gap.zp_in; np.gap_zp_out = q.gap.zp_out; np.gap_M0 = q.gap.M0; np.gap_sh = q.gap.sh;
+                } else {
+                    np.fc_w = q.fc.w; np.fc_bias = q.fc.bias; np.classes = q.fc.classes; np.classes_p = q.fc.classes_p;
+                }
+            }
+        }
+    if (blocks.empty() && consts.empty()) return ISR_OK;
+    const size_t block_bytes = (blocks.size() * sizeof(NarrowBlock) + 255) & ~(size_t)255;
+    HIP_TRY(hipMalloc((void **)&m->dnarrow, block_bytes + consts.size() * 4));
+    const int32_t *dconsts = (const int32_t *)(m->dnarrow + block_bytes);
+    for (NarrowBlock &nb : blocks) { nb.prm1 = dconsts + (size_t)nb.prm1; nb.prm2 = dconsts + (size_t)nb.prm2; }
+    for (int pi = 1; pi <= 2; ++pi)
+        for (DevOp &d : m->plan[pi].ops) {
+            NarrowParams &np = d.np;
+            if (!d.narrow) continue;
+            if (np.prm0) np.prm0 = dconsts + (size_t)np.prm0 - 1;
+            if (np.tprm) np.tprm = dconsts + (size_t)np.tprm - 1;
+            if (np.blocks) np.blocks = (const NarrowBlock *)m->dnarrow + (size_t)np.blocks - 1;
+        }
+    if (!blocks.empty()) HIP_TRY(hipMemcpy(m->dnarrow, blocks.data(), blocks.size() * sizeof(NarrowBlock), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(m->dnarrow + block_bytes, consts.data(), consts.size() * 4, hipMemcpyHostToDevice));
+    return ISR_OK;
+}
+
 // A batched call: items (device array) that own n_per_item consecutive slots each.
 struct BatchCtx {
     const NoiseItem *items;
@@ -123,6 +222,16 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
             ev_work.push_back({last_kernel_name(), 0, 0.0, (double)bn * pm.H * pm.W * 4});
             return ISR_OK;
         };
+        // where the copies from j0 on draw their noise, for a first layer that draws its own input
+        auto noise_source = [&](uint32_t j0) {
+            NoiseSource ns{};
+            ns.x = x; ns.table = table; ns.items = nullptr;
+            ns.key0 = (uint32_t)seed; ns.key1 = (uint32_t)(seed >> 32);
+            ns.image = image; ns.phase = phase; ns.sample_begin = begin + (uint32_t)done + j0;
+            ns.C = pm.C; ns.H = pm.H; ns.W = pm.W;
+            if (bc) { ns.items = bc->items; ns.n_per_item = bc->n_per_item; ns.slot_begin = done + j0; }
+            return ns;
+        };
         // copies [j0, j0 + bn) of the chunk through one op of the plan
         auto run_op = [&](const DevOp &d, uint32_t j0, uint32_t bn) -> int {
             if ((prc = mark()) != ISR_OK) return prc;
@@ -138,16 +247,7 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
                     sp.H = d.conv.H; sp.W = d.conv.W; sp.Ho = d.conv.Ho; sp.Wo = d.conv.Wo; sp.Hp = to.H; sp.Wp = to.W;
                     sp.zp_in = d.conv.zp_in; sp.zp_out = d.conv.zp_out; sp.relu = d.conv.relu; sp.rq = d.conv.rq; sp.B = (int32_t)bn;
                     sp.fused_noise = d.noise_fused && m->quant_sigma < 0.f;
-                    sp.noise = NoiseSource{};
-                    if (sp.fused_noise) {
-                        NoiseSource &ns = sp.noise;
-                        ns.x = x; ns.table = table; ns.items = nullptr;
-                        ns.key0 = (uint32_t)seed; ns.key1 = (uint32_t)(seed >> 32);
-                        ns.image = image; ns.phase = phase; ns.sample_begin = begin + (uint32_t)done + j0;
-                        ns.n_per_item = 0; ns.slot_begin = 0;
-                        ns.C = pm.C; ns.H = pm.H; ns.W = pm.W;
-                        if (bc) { ns.items = bc->items; ns.n_per_item = bc->n_per_item; ns.slot_begin = done + j0; }
-                    }
+                    sp.noise = sp.fused_noise ? noise_source(j0) : NoiseSource{};
                     HIP_TRY(launch_stem_pool(sp, m->stream));
                     break;
                 }
@@ -162,34 +262,20 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
                     HIP_TRY(launch_stem16(sp, m->stream));
                     break;
                 }
-                if (d.block) {
-                    BlockParams bp{};
-                    bp.in = (const int8_t *)tptr(d.a, j0);
-                    bp.out = (int8_t *)tptr(d.out, j0);
-                    bp.blocks = m->dblocks + d.chain_off;
-                    bp.nblocks = (int32_t)d.chain.size();
-                    bp.C = d.conv.Cout_p; bp.S = d.conv.H; bp.B = (int32_t)bn;
-                    bp.tie_free = d.conv.tie_free && d.conv2.tie_free && d.conv2.add_tie_free;
-                    HIP_TRY(launch_basic_block(bp, m->stream));
-                    break;
-                }
-                if (d.trans) {
-                    const ConvParams &c1 = d.conv, &c2 = d.conv2, &cp = d.conv3;
-                    TransParams tp{};
-                    tp.in = (const int8_t *)tptr(d.a, j0);
-                    tp.out = (int8_t *)tptr(d.out, j0);
-                    tp.w1 = c1.w; tp.bias1 = c1.bias; tp.m0s1 = c1.m0s; tp.chi1 = c1.chi; tp.shm11 = c1.shm1;
-                    tp.w2 = c2.w; tp.bias2 = c2.bias; tp.m0s2 = c2.m0s; tp.chi2 = c2.chi; tp.shm12 = c2.shm1;
-                    tp.wp = cp.w; tp.biasp = cp.bias; tp.m0sp = cp.m0s; tp.chip = cp.chi; tp.shm1p = cp.shm1;
-                    tp.C = c1.Cout_p; tp.S = c1.Ho; tp.B = (int32_t)bn;
-                    tp.zp_x = c1.zp_in; tp.zp_t = c1.zp_out;
-                    tp.lo1 = c1.relu ? c1.zp_out : -128;
-                    tp.lo2 = c2.relu ? c2.zp_out : -128;
-                    tp.lop = cp.relu ? cp.zp_out : -128;
-                    tp.add_mul_self = cp.add_mul_self; tp.add_mul_res = cp.add_mul_res; tp.add_c0 = cp.add_c0;
-                    tp.add_k = cp.add_k; tp.add_sh = cp.add_sh; tp.add_lo = cp.add_lo;
-                    tp.tie_free = c1.tie_free && c2.tie_free && cp.tie_free && cp.add_tie_free;
-                    HIP_TRY(launch_trans_block(tp, m->stream));
+                if (d.narrow) {
+                    NarrowParams np = d.np;
+                    np.in = (const int8_t *)tptr(d.a, j0);
+                    np.out = d.head ? nullptr : (int8_t *)tptr(d.out, j0);
+                    np.B = (int32_t)bn;
+                    np.fused_noise = d.noise_fused && m->quant_sigma < 0.f;
+                    if (np.fused_noise) np.noise = noise_source(j0);
+                    if (d.head) {
+                        np.logits = logits_host ? (int32_t *)(ws + pl.logits_off) + (size_t)j0 * pm.classes : nullptr;
+                        np.argmax = argmax_host ? (int32_t *)(ws + pl.argmax_off) + j0 : nullptr;
+                        np.counts = dcounts;
+                        if (bc) { np.n_per_item = bc->n_per_item; np.slot_begin = done + j0; }
+                    }
+                    HIP_TRY(launch_narrow(np, d.narrow, m->stream));
                     break;
                 }
                 if (d.bneck) {
@@ -464,30 +550,7 @@ int isr_load_model(const void *blob_host, size_t bytes, isr_model **out) {
     m->plan[0].ops = m->ops;
     build_fused_plan(m->pm, m->ops, m->plan[1].ops, false);
     build_fused_plan(m->pm, m->ops, m->plan[2].ops, true);
-    {   // descriptors of the identity-block chains, in device memory
-        std::vector<BlockDesc> descs;
-        for (int pi = 1; pi <= 2; ++pi)
-        for (DevOp &d : m->plan[pi].ops) {
-            if (!d.block) continue;
-            d.chain_off = descs.size();
-            for (const auto &blk : d.chain) {
-                const ConvParams &c1 = blk.first, &c2 = blk.second;
-                BlockDesc b{};
-                b.w1 = c1.w; b.bias1 = c1.bias; b.m0s1 = c1.m0s; b.chi1 = c1.chi; b.shm11 = c1.shm1;
-                b.w2 = c2.w; b.bias2 = c2.bias; b.m0s2 = c2.m0s; b.chi2 = c2.chi; b.shm12 = c2.shm1;
-                b.zp_x = c1.zp_in; b.zp_t = c1.zp_out; b.relu1 = c1.relu;
-                b.zp_u = c2.zp_out; b.relu2 = c2.relu;
-                b.add_mul_self = c2.add_mul_self; b.add_mul_res = c2.add_mul_res; b.add_c0 = c2.add_c0;
-                b.add_k = c2.add_k; b.add_sh = c2.add_sh; b.add_lo = c2.add_lo;
-                descs.push_back(b);
-            }
-        }
-        if (!descs.empty()) {
-            e = hipMalloc((void **)&m->dblocks, descs.size() * sizeof(BlockDesc));
-            if (e == hipSuccess) e = hipMemcpy(m->dblocks, descs.data(), descs.size() * sizeof(BlockDesc), hipMemcpyHostToDevice);
-            if (e != hipSuccess) { g_last_hip_error = (int)e; return cleanup(ISR_ERR_DEVICE); }
-        }
-    }
+    if ((rc = build_narrow_ops(m, arena)) != ISR_OK) return cleanup(rc);
     *out = m;
     return ISR_OK;
 }
@@ -557,7 +620,7 @@ int isr_free_model(isr_model *m) {
     if (m->htables) (void)hipHostFree(m->htables);
     if (m->dcounts) (void)hipFree(m->dcounts);
     if (m->hcounts) (void)hipHostFree(m->hcounts);
-    if (m->dblocks) (void)hipFree(m->dblocks);
+    if (m->dnarrow) (void)hipFree(m->dnarrow);
     if (m->ditems) (void)hipFree(m->ditems);
     if (m->hitems) (void)hipHostFree(m->hitems);
     if (m->dcounts_b) (void)hipFree(m->dcounts_b);

@@ -96,9 +96,6 @@ __device__ __forceinline__ uint32_t pack4(int a, int b, int c, int d) {
 //   RQ_TOP_TIES  the same with ties (a 64-bit multiply-add instead of the multiply)
 // An add is RQ_ANY, RQ_TIE_FREE, RQ_TOP or RQ_TOP_WIDE (two signed operands, whose sum may leave int32 and saturates).
 // The forms of several convolutions combine with &.
-enum Rq : int { RQ_ANY = 0, RQ_TIE_FREE = 1, RQ_TOP_TIES = 2, RQ_TOP = 3, RQ_TOP_WIDE = 4 };
-constexpr bool rq_is_top(int rq) { return rq >= RQ_TOP_TIES; }
-
 // v_mad_i32_i24 with the clamp bit: sat32(a * b + c), a and b in 24 bits (no builtin reaches the clamp bit)
 __device__ __forceinline__ int mad24_sat(int a, int b, int c) {
     int r;
@@ -131,9 +128,8 @@ __device__ __forceinline__ int rq_conv(int acc, int m0, int chi, int sh, int lo)
 
 // Constants of the residual add.  Top form: everything times 2^(23 - add_sh); the saturating double of the sum has the
 // int8 result in the top byte.
-struct AddConst { int ms, mr, c0, k, sh, lo; };
 template <int RQA, class P>
-__device__ __forceinline__ AddConst add_const(const P &p) {
+__host__ __device__ __forceinline__ AddConst add_const(const P &p) {
     if constexpr (rq_is_top(RQA)) {
         const int s = 23 - p.add_sh;
         return {p.add_mul_self << s, p.add_mul_res << s, (p.add_c0 + p.add_k) << s, 0, 0, 0};
@@ -142,12 +138,12 @@ __device__ __forceinline__ AddConst add_const(const P &p) {
     }
 }
 
-// Residual add on q (as rq_conv<RQ> returns it) and byte j of the residual word.  A top-form add goes with a top-form
-// convolution.  24-bit multiplies: |q|, |r| <= 2^7, |multipliers| < 2^23; the byte selections fold into them.
+// Residual add of q (as rq_conv<RQ> returns it) and the int8 value r8.  A top-form add goes with a top-form convolution.
+// 24-bit multiplies: |q|, |r| <= 2^7, |multipliers| < 2^23.
 template <int RQ, int RQA>
-__device__ __forceinline__ int rq_add(int q, uint32_t rword, int j, const AddConst &a) {
+__device__ __forceinline__ int rq_add_value(int q, int r8, const AddConst &a) {
     static_assert(!rq_is_top(RQA) || rq_is_top(RQ), "");
-    const int qi = rq_is_top(RQ) ? q >> 24 : q, r8 = (int)(int8_t)(rword >> (8 * j));
+    const int qi = rq_is_top(RQ) ? q >> 24 : q;
     if constexpr (RQA == RQ_TOP) {
         const int v = __mul24(qi, a.ms) + __mul24(r8, a.mr) + a.c0;
         return __builtin_elementwise_add_sat(v, v);
@@ -161,6 +157,11 @@ __device__ __forceinline__ int rq_add(int q, uint32_t rword, int j, const AddCon
         const int v = __mul24(qi, a.ms) + a.c0 + __mul24(r8, a.mr);
         return clamp3((v + a.k + (v >> 31)) >> a.sh, a.lo, 127);
     }
+}
+// r = byte j of the residual word (the byte selections fold into the multiplies)
+template <int RQ, int RQA>
+__device__ __forceinline__ int rq_add(int q, uint32_t rword, int j, const AddConst &a) {
+    return rq_add_value<RQ, RQA>(q, (int)(int8_t)(rword >> (8 * j)), a);
 }
 
 // four results of rq_conv / rq_add -> one dword of int8

@@ -86,6 +86,11 @@ struct ParsedModel {
 int parse_model(const void *blob, size_t bytes, ParsedModel &out, std::string &why);
 
 // ---- device-side op descriptors -------------------------------------------
+// Forms of the requantisation and of the residual add (conv_device.h)
+enum Rq : int { RQ_ANY = 0, RQ_TIE_FREE = 1, RQ_TOP_TIES = 2, RQ_TOP = 3, RQ_TOP_WIDE = 4 };
+constexpr bool rq_is_top(int rq) { return rq >= RQ_TOP_TIES; }
+struct AddConst { int32_t ms, mr, c0, k, sh, lo; };   // constants of a residual add in its form
+
 struct ConvParams {
     const int8_t *in;        // [B][H][W][Cin_p]
     int8_t *out;             // [B][Ho][Wo][Cout_p]
@@ -159,24 +164,44 @@ struct Stem16Params {
     int32_t H, W, B, zp_in, lo, tie_free;
 };
 
-// Identity residual block in one kernel: t = conv3x3(x), y = add(conv3x3(t), x); both
-// convolutions C -> C channels, stride 1, pad 1, on S x S images (basic_block.hip).
-struct BlockDesc {           // one block of a chain, stored in device memory
+// The nets on 32 x 32 images with 16 / 32 / 64 channels at 32 / 16 / 8 pixels, one launch per stage (narrow_net.hip).
+// Per-channel constants come packed, int32 [4][C]: bias, M0, chi, shift-1 (top form: addend and multiplier, see rq_chi).
+struct NarrowBlock {         // identity residual block, stored in device memory
     const int8_t *w1, *w2;   // [>= C][Kp] each, K = (tap, channel), Kp = 9 C rounded up to 64
-    const int32_t *bias1, *m0s1, *chi1, *shm11;   // first convolution, as in ConvParams
-    const int32_t *bias2, *m0s2, *chi2, *shm12;   // second convolution
-    int32_t zp_x, zp_t, relu1;   // zero-points of x and t; lower clamp of t is zp_t when relu1
-    int32_t zp_u, relu2;         // the same for the second convolution's own int8 result
-    int32_t add_mul_self, add_mul_res, add_c0, add_k, add_sh, add_lo;   // as in ConvParams
+    const int32_t *prm1, *prm2;
+    int32_t zp_x, zp_t;      // zero-points of the block input and of the middle tensor
+    int32_t lo1, lo2;        // lower clamps of the two convolutions
+    int32_t form;            // 0: RQ_TOP, add RQ_TOP; 1: RQ_TOP_TIES, add RQ_ANY; 2: RQ_ANY, add RQ_ANY
+    AddConst add;
     int32_t pad_;
 };
-struct BlockParams {
-    const int8_t *in;        // [B][S][S][C] input x of the first block
-    int8_t *out;             // [B][S][S][C] output of the last block
-    const BlockDesc *blocks; // [nblocks] (device): a chain of blocks of one shape, each feeding the next
+struct NarrowParams {
+    const int8_t *in;        // [B][S][S][C], or the NHWC4 image [B][S][S][4] (stem != 0)
+    int8_t *out;             // [B][S][S][C]; tail != 0: [B][S/2][S/2][2C]; unused with a head
+    int32_t B;
+    // first layer, 3x3 into 16 channels; with fused_noise the kernel draws its own input
+    int32_t stem, fused_noise, zp_in, lo0, form0;   // form0: 0 RQ_TOP, 2 RQ_ANY
+    const int8_t *w0;
+    const int32_t *prm0;
+    NoiseSource noise;
+    // chain of identity blocks
     int32_t nblocks;
-    int32_t C, S, B;
-    int32_t tie_free;        // every convolution and add of the chain is free of rounding ties
+    const NarrowBlock *blocks;
+    // tail 1: down-sampling block t = conv3x3/2(x), u = conv3x3(t), r = conv1x1/2(x), y = add(r, u); 2: t alone
+    int32_t tail, tform;     // form 0: RQ_TOP, add RQ_TOP_WIDE; 1, 2 as above
+    const int8_t *tw1, *tw2, *twp;
+    const int32_t *tprm;     // [3][4][2C]: t, u, r
+    int32_t tzp_x, tzp_t, tlo1, tlo2, tlop;
+    AddConst tadd;           // "self" is the projection r
+    // head: global average pooling of the last tensor, fully connected layer, votes
+    int32_t head, gap_zp_in, gap_zp_out, gap_M0, gap_sh;
+    const int8_t *fc_w;
+    const int32_t *fc_bias;
+    int32_t classes, classes_p;
+    int32_t *logits, *argmax;
+    uint32_t *counts;
+    uint32_t n_per_item;     // as in FcParams
+    uint64_t slot_begin;
 };
 
 // Bottleneck block in one kernel: conv1x1 -> conv3x3 [-> conv1x1 + residual add with the block input
@@ -225,22 +250,6 @@ struct XrParams {
     int32_t npix;
     int32_t n2;              // output channels of the reducing convolution: 128, or 256 (stored residual only)
     int32_t k1;              // input channels of the expanding convolution: 128 (512 block channels) or 256 (1024; stored residual, n2 = 256)
-};
-
-// Down-sampling residual block in one kernel (trans_block.hip): t = conv3x3/2(x), u = conv3x3(t),
-// r = conv1x1/2(x), y = add(r, u); x has C/2 channels on 2S x 2S pixels.
-struct TransParams {
-    const int8_t *in;        // [B][2S][2S][C/2]
-    int8_t *out;             // [B][S][S][C]
-    const int8_t *w1, *w2, *wp;   // weight rows in MFMA row order: [C][9 C/2 -> 64-multiple], [C][9 C -> 64-multiple], [C][64]
-    const int32_t *bias1, *m0s1, *chi1, *shm11;   // as in ConvParams, per convolution
-    const int32_t *bias2, *m0s2, *chi2, *shm12;
-    const int32_t *biasp, *m0sp, *chip, *shm1p;
-    int32_t C, S, B;
-    int32_t zp_x, zp_t;      // zero-points of x and t (their padding values)
-    int32_t lo1, lo2, lop;   // lower clamps of t, u, r
-    int32_t add_mul_self, add_mul_res, add_c0, add_k, add_sh, add_lo;   // as in ConvParams; "self" is the projection r
-    int32_t tie_free;
 };
 
 struct AddParams {
@@ -358,7 +367,7 @@ bool stem_pool_supported(int k, int stride, int pad, int cout_p, int H, int W, i
                          int pool_stride, int pool_pad);
 hipError_t launch_stem16(const Stem16Params &p, hipStream_t st);
 bool stem16_supported(int k, int stride, int pad, int cout_p, int H, int W, int fast_requant);
-hipError_t launch_basic_block(const BlockParams &p, hipStream_t st);
+hipError_t launch_narrow(const NarrowParams &p, int channels, hipStream_t st);   // narrow_net.hip
 bool basic_block_supported(int channels, int size);
 hipError_t launch_bottleneck(const BneckParams &p, hipStream_t st);
 bool bottleneck_supported(int cin_p, int cmid_p, int cout_p, int tail);
@@ -368,7 +377,6 @@ void expand_reduce_params(const ConvParams &expand, const ConvParams &reduce, co
                           int8_t *t1n, int32_t copies, XrParams &xp);
 hipError_t launch_expand_reduce(const XrParams &p, hipStream_t st);   // expand_reduce.hip   // 128 middle channels, identity blocks (bottleneck128.hip)
 bool bottleneck128_supported(int cin_p, int cmid_p, int cout_p);
-hipError_t launch_trans_block(const TransParams &p, hipStream_t st);
 bool trans_block_supported(int cout, int size_out);
 hipError_t launch_add(const AddParams &p, hipStream_t st);
 hipError_t launch_maxpool(const PoolParams &p, hipStream_t st);

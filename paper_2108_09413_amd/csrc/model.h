@@ -15,7 +15,7 @@ struct FloatNet;   // float_api.cpp: the float network of the FloatRS-fp compari
 void free_float_net(FloatNet *net);
 }  // namespace isr
 
-using isr::Plan; using isr::DevOp; using isr::ParsedModel; using isr::DeviceNoiseTable; using isr::BlockDesc; using isr::NoiseItem;
+using isr::Plan; using isr::DevOp; using isr::ParsedModel; using isr::DeviceNoiseTable; using isr::NoiseItem;
 using isr::TABLE_SLOTS;
 
 struct isr_model {
@@ -31,7 +31,7 @@ struct isr_model {
     int table_next = 0;
     uint32_t *dcounts = nullptr;        // 2 * classes
     uint32_t *hcounts = nullptr;        // pinned, 2 * classes
-    BlockDesc *dblocks = nullptr;       // descriptors of the identity-block chains of plan[1] and plan[2]
+    uint8_t *dnarrow = nullptr;         // block descriptors and packed constants of the narrow-net ops of plan[1] and plan[2]
     // batched calls: item descriptors and per-item vote counters, grown on demand
     NoiseItem *ditems = nullptr, *hitems = nullptr;
     uint32_t *dcounts_b = nullptr, *hcounts_b = nullptr;   // 2 * items_cap * classes each

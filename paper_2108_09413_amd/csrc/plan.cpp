@@ -97,7 +97,7 @@ void plan_workspace(const ParsedModel &pm, uint32_t B, Plan &pl) {
         const int end = seg < pl.segments.size() ? (int)std::min(pl.segments[seg].end, pl.ops.size()) : i + 1;
         for (int j = i; j < end; ++j) {
             const DevOp &o = pl.ops[j];
-            if (o.type != OP_FC) { pl.toff[o.out] = alloc(tbytes(o.out)); pl.has[o.out] = 1; }
+            if (o.type != OP_FC && !o.head) { pl.toff[o.out] = alloc(tbytes(o.out)); pl.has[o.out] = 1; }
             if (o.out2 >= 0) { pl.toff[o.out2] = alloc(tbytes(o.out2)); pl.has[o.out2] = 1; }
         }
         for (int j = i; j < end; ++j) {
@@ -240,12 +240,10 @@ void chain_basic_blocks(const ParsedModel &pm, std::vector<DevOp> &ops) {
         if (d.a >= 0) uses[d.a]++;
         if (d.b >= 0) uses[d.b]++;
     }
-    auto tf = [](const DevOp &d) { return d.conv.tie_free && d.conv2.tie_free && d.conv2.add_tie_free; };
     for (size_t i = 0; i + 1 < ops.size();) {
         DevOp &a = ops[i];
         const DevOp &b = ops[i + 1];
-        if (a.block && b.block && b.a == a.out && uses[a.out] == 1 && a.conv.Cout_p == b.conv.Cout_p && a.conv.H == b.conv.H &&
-            tf(a) == tf(b) && a.chain.size() < 64) {
+        if (a.block && b.block && b.a == a.out && uses[a.out] == 1 && a.conv.Cout_p == b.conv.Cout_p && a.conv.H == b.conv.H) {
             a.chain.insert(a.chain.end(), b.chain.begin(), b.chain.end());
             a.ops_per_sample += b.ops_per_sample;
             a.bytes_per_sample = (a.bytes_per_sample + b.bytes_per_sample) / 2;   // one read of the first input, one write of the last output
@@ -292,6 +290,60 @@ void fuse_trans_blocks(const ParsedModel &pm, std::vector<DevOp> &ops) {
     }
 }
 
+// Joins the ops of one stage of the nets on 32 x 32 images into one op (narrow_net.hip): the first layer before a chain of
+// identity blocks, the chain, the down-sampling block after it (or a single 3x3 stride-2 convolution into 32 channels),
+// and the pooling, fully connected layer and votes after the last stage.
+void fuse_narrow(const ParsedModel &pm, std::vector<DevOp> &ops) {
+    std::vector<int> uses(pm.tensors.size(), 0);
+    for (const DevOp &d : ops) {
+        if (d.a >= 0) uses[d.a]++;
+        if (d.b >= 0) uses[d.b]++;
+    }
+    for (size_t i = 0; i < ops.size(); ++i) {
+        const bool stem = ops[i].stem16 && ops[i].conv.H == 32 && ops[i].conv.W == 32;
+        if (!stem && !ops[i].block && !ops[i].trans) continue;
+        const int C = stem ? 16 : ops[i].trans ? ops[i].conv.Cin_p : ops[i].conv.Cout_p;
+        size_t end = i + 1;
+        // the next op when it continues the group: the only reader of what the group has made so far
+        auto next = [&]() -> const DevOp * { return end < ops.size() && ops[end].a == ops[end - 1].out && uses[ops[end].a] == 1 ? &ops[end] : nullptr; };
+        if (stem && next() && next()->block && next()->conv.Cout_p == C) ++end;
+        int channels = C;   // of the group's last tensor
+        int pixels = C == 16 ? 32 * 32 : C == 32 ? 16 * 16 : 8 * 8;
+        const DevOp *n = next();
+        if (!ops[i].trans && n && n->trans && n->conv.Cin_p == C) {
+            ++end;
+            channels = 2 * C; pixels /= 4;
+        } else if (stem && n && n->type == OP_CONV && !n->block && !n->trans && !n->bneck && !n->xr && !n->stem_pool && !n->stem16 &&
+                   !n->conv.fuse_add && n->conv.fast_requant && !n->conv.c4 && n->conv.k == 3 && n->conv.stride == 2 && n->conv.pad == 1 &&
+                   n->conv.Cin_p == 16 && n->conv.Cout_p == 32 && n->conv.H == 32 && n->conv.W == 32 && n->conv.Kp == 192) {
+            ++end;
+            channels = 32; pixels = 256;
+        }
+        bool head = false;
+        const bool down = end > i + 1 && !ops[end - 1].trans && !ops[end - 1].block && !ops[end - 1].stem16;   // ends in the single convolution
+        if ((C == 64 || down) && next() && next()->type == OP_GAP && next()->gap.HW == pixels && end + 1 < ops.size() &&
+            ops[end + 1].type == OP_FC && ops[end + 1].a == ops[end].out && uses[ops[end].out] == 1 && ops[end + 1].fc.Kp == channels &&
+            end + 2 == ops.size()) {
+            end += 2;
+            head = true;
+        }
+        DevOp g;
+        g.type = OP_CONV;
+        g.narrow = C;
+        g.head = head;
+        g.a = ops[i].a;
+        g.out = ops[end - 1].out;
+        const TensorDesc &ti = pm.tensors[g.a], &to = pm.tensors[g.out];
+        g.bytes_per_sample = (double)ti.C * ti.H * ti.W + (head ? 0.0 : (double)to.C * to.H * to.W);
+        for (size_t j = i; j < end; ++j) g.ops_per_sample += ops[j].ops_per_sample;
+        g.parts.assign(ops.begin() + i, ops.begin() + end);
+        // the first layer draws its own noisy input when it is the only reader of the input tensor
+        g.noise_fused = stem && g.a == 0 && uses[0] == 1;
+        ops.erase(ops.begin() + i + 1, ops.begin() + end);
+        ops[i] = g;
+    }
+}
+
 // Folds conv1x1 (-> 64 or 128 channels) -> conv3x3 of a bottleneck block into one kernel, and with
 // them the closing conv1x1 + residual add when the residual is the block input (with 128 middle
 // channels only whole blocks are folded).
@@ -303,7 +355,7 @@ void fuse_bottlenecks(const ParsedModel &pm, std::vector<DevOp> &ops, bool wide)
         if (d.b >= 0) uses[d.b]++;
     }
     auto plain = [](const DevOp &d) {
-        return d.type == OP_CONV && !d.stem_pool && !d.stem16 && !d.block && !d.trans && !d.bneck && !d.conv.c4 && d.conv.fast_requant;
+        return d.type == OP_CONV && !d.stem_pool && !d.stem16 && !d.narrow && !d.bneck && !d.conv.c4 && d.conv.fast_requant;
     };
     for (size_t i = 0; i + 1 < ops.size(); ++i) {
         DevOp &a = ops[i];
@@ -350,7 +402,7 @@ void fuse_bottlenecks(const ParsedModel &pm, std::vector<DevOp> &ops, bool wide)
         if (a.bneck == 1 && i + 1 < ops.size()) {
             const DevOp &m = ops[i + 1];
             const ConvParams &c3 = m.conv;
-            if (m.type == OP_CONV && !m.stem_pool && !m.stem16 && !m.block && !m.trans && !m.bneck && c3.fuse_add == 2 &&
+            if (m.type == OP_CONV && !m.stem_pool && !m.stem16 && !m.narrow && !m.bneck && c3.fuse_add == 2 &&
                 c3.k == 1 && c3.stride == 1 && c3.pad == 0 && c3.Cin_p == 64 && c3.Kp == 64 && c3.Cin2_p == 64 && c3.fast_requant &&
                 ((m.a == a.out && m.b == a.a) || (m.a == a.a && m.b == a.out)) && uses[a.out] == 1 && c1.Cin_p == 64 &&
                 bottleneck_supported(64, 64, c3.Cout_p, 2)) {
@@ -600,7 +652,7 @@ namespace {
 // next block's add reads it), but not read back by a second kernel.
 void fuse_expand_reduce(const ParsedModel &pm, std::vector<DevOp> &ops) {
     auto plain = [](const DevOp &d) {
-        return d.type == OP_CONV && !d.stem_pool && !d.stem16 && !d.block && !d.trans && !d.bneck && !d.xr;
+        return d.type == OP_CONV && !d.stem_pool && !d.stem16 && !d.narrow && !d.bneck && !d.xr;
     };
     for (size_t i = 0; i + 1 < ops.size(); ++i) {
         DevOp &a = ops[i];
@@ -637,6 +689,7 @@ void build_fused_plan(const ParsedModel &pm, const std::vector<DevOp> &plain, st
     fuse_basic_blocks(pm, fused);
     chain_basic_blocks(pm, fused);
     fuse_trans_blocks(pm, fused);
+    fuse_narrow(pm, fused);
     fuse_bottlenecks(pm, fused, wide_bottlenecks);
     fuse_expand_reduce(pm, fused);
 }

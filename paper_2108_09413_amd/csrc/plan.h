@@ -20,8 +20,11 @@ struct DevOp {
     int stem16 = 0;                     // first 3x3 convolution into 16 channels: the LDS-resident kernel
     int block = 0;                      // identity residual block: this conv, conv2 and the add in one kernel
     std::vector<std::pair<ConvParams, ConvParams>> chain;   // block != 0: the blocks of the chain this op runs (each feeds the next)
-    size_t chain_off = 0;               // first BlockDesc of the chain in the model's device array
     int trans = 0;                      // down-sampling block: this conv (3x3/2), conv2 (3x3) and conv3 (1x1/2 + add) in one kernel
+    int narrow = 0;                     // channels of the stage whose ops (parts) run in one launch of narrow_net.hip
+    int head = 0;                       // narrow != 0: the last parts are the pooling and the fully connected layer (no output tensor)
+    std::vector<DevOp> parts;
+    NarrowParams np{};                  // narrow != 0: the launch's constant arguments
     int bneck = 0;                      // 1: this 1x1 conv and the 3x3 conv2 in one kernel; 2: plus conv3 (1x1 + residual add); 3: as 2 with 128 middle channels; 4: as 2 with the residual computed by a projection 1x1 convolution of the block input (conv3 carries it as its second convolution)
     int xr = 0;                         // this expanding 1x1 + residual add and the reducing 1x1 that reads its sum (conv2, output out2) in one kernel
     int out2 = -1;                      // second output tensor of the op (xr != 0)

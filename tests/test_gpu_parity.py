@@ -315,6 +315,50 @@ def test_downsampling_residual_blocks_in_one_kernel(isr):
         m.close()
 
 
+@pytest.mark.parametrize("copies", [1, 3, 256, 257, 259])
+@pytest.mark.parametrize("net", ["stages", "down"])
+def test_stages_of_the_nets_on_32x32_images(isr, net, copies):
+    """One launch per stage: first layer + blocks + down-sampling, a stage without blocks, blocks + pooling + fully
+    connected layer with more classes than a wave has lanes; constants in the top-byte form, with ties, and in the
+    general form; one and several images per workgroup with ragged last ones; single votes and batched ones."""
+    _say(f"narrow stages {net} {copies}")
+    b = NetBuilder(rng=np.random.default_rng(91), in_shape=(3, 32, 32), num_classes=70)
+    t = b.conv(b.tensor(3, 32, 32, 0, 74.0), 16, 3, 1, 1, True)
+    def block(t, ch, zo=-128, **kw):
+        u = b.conv(t, ch, 3, 1, 1, True, **({"m0": np.full(ch, 1 << 30, dtype=np.int64)} if "ma" in kw else {}))
+        return b.add(t, b.conv(u, ch, 3, 1, 1, False), True, zp_out=zo, **kw)
+    def down(t, ch):
+        u = b.conv(b.conv(t, ch, 3, 2, 1, True), ch, 3, 1, 1, False)
+        return b.add(b.conv(t, ch, 1, 2, 0, False), u, True)
+    if net == "stages":
+        t = block(t, 16)
+        t = block(t, 16, ma=1 << 19, mb=1 << 19, sh=20)        # exact halves in the first convolution and in the add
+        t = down(block(t, 16, zo=-100), 32)                    # general form; another zero-point in the border of x
+        t = down(t, 64)
+        t = block(block(block(t, 64), 64, zo=-90), 64)
+    else:
+        t = b.conv(t, 32, 3, 2, 1, True)
+    b.fc(b.gap(t), 70)
+    blob = b.blob()
+    m = _load(isr, blob, copies)
+    om = oracle.Model(blob)
+    x = np.random.default_rng(12).integers(0, 256, size=(3, 32, 32)).astype(np.uint8)
+    lg, am, cnt = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 100, copies)
+    k = min(copies, 5)
+    olg, oam, _ = om.mc(x, 64, 2, 1, 1, 100 + copies - k, k)
+    assert np.array_equal(lg[-k:], olg) and np.array_equal(am[-k:], oam)
+    assert np.array_equal(cnt, np.bincount(am, minlength=70))
+    isr.isr_set_fusion(m, 0)
+    lg0, am0, cnt0 = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 100, copies)
+    assert np.array_equal(lg, lg0) and np.array_equal(am, am0) and np.array_equal(cnt, cnt0)
+    votes = []
+    for fusion in (0, 1):
+        isr.isr_set_fusion(m, fusion)
+        votes.append(isr.isr_predict_batch(m, np.stack([x, 255 - x]), [(0, 64, 1), (1, 32, 2), (0, 32, 3)], copies, ALPHA, seed=5)[1])
+    assert np.array_equal(votes[0], votes[1]) and (votes[0].sum(axis=1) == copies).all()
+    m.close()
+
+
 @pytest.mark.parametrize("shape", [(30, 20), (28, 28), (5, 40)])
 def test_bottleneck_blocks_in_one_kernel(isr, shape):
     """conv1x1 -> conv3x3 (64 middle channels) [-> conv1x1 + add with the block input] as one
