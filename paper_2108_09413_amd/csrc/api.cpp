@@ -58,7 +58,18 @@ int build_narrow_ops(isr_model *m, const ConstArena &arena) {
     std::vector<NarrowBlock> blocks;
     std::vector<int32_t> consts;
     auto host = [&](const int32_t *dev) { return (const int32_t *)(arena.host.data() + ((const uint8_t *)dev - m->dconst)); };
-    auto form_of = [](int rq, bool add_top) { return rq == RQ_TOP && add_top ? 0 : rq_is_top(rq) ? 1 : 2; };
+    // one shift for all channels
+    auto one_shift = [&](const ConvParams &c) {
+        const int32_t *s = host(c.shm1);
+        for (int i = 1; i < c.Cout_p; ++i)
+            if (s[i] != s[0]) return false;
+        return true;
+    };
+    auto form_of = [&](int rq, bool add_top, std::initializer_list<const ConvParams *> convs) {
+        bool uniform = true;
+        for (const ConvParams *c : convs) uniform = uniform && one_shift(*c);
+        return rq == RQ_TOP && uniform ? (add_top ? 0 : 1) : 2;
+    };
     auto pack = [&](const ConvParams &c, int form) {   // [4][C], returns its offset
         const size_t off = consts.size();
         const int C = c.Cout_p;
@@ -91,7 +102,7 @@ int build_narrow_ops(isr_model *m, const ConstArena &arena) {
                 const ConvParams &c1 = q.conv, &c2 = q.conv2, &cp = q.conv3;
                 if (q.stem16) {
                     np.stem = 1;
-                    np.form0 = form_of(c1.rq, true);
+                    np.form0 = form_of(c1.rq, true, {&c1});
                     np.w0 = c1.w; np.zp_in = c1.zp_in; np.lo0 = lo_of(c1);
                     np.prm0 = (const int32_t *)(pack(c1, np.form0) + 1);
                 } else if (q.block) {
@@ -100,7 +111,7 @@ int build_narrow_ops(isr_model *m, const ConstArena &arena) {
                     for (const auto &blk : q.chain) {
                         const ConvParams &a = blk.first, &b = blk.second;
                         NarrowBlock nb{};
-                        nb.form = form_of(a.rq & b.rq, b.add_rq == RQ_TOP);
+                        nb.form = form_of(a.rq & b.rq, b.add_rq == RQ_TOP, {&a, &b});
                         nb.w1 = a.w; nb.w2 = b.w;
                         nb.prm1 = (const int32_t *)pack(a, nb.form);
                         nb.prm2 = (const int32_t *)pack(b, nb.form);
@@ -110,7 +121,7 @@ int build_narrow_ops(isr_model *m, const ConstArena &arena) {
                     }
                 } else if (q.trans) {
                     np.tail = 1;
-                    np.tform = form_of(c1.rq & c2.rq & cp.rq, rq_is_top(cp.add_rq));
+                    np.tform = form_of(c1.rq & c2.rq & cp.rq, rq_is_top(cp.add_rq), {&c1, &c2, &cp});
                     np.tw1 = c1.w; np.tw2 = c2.w; np.twp = cp.w;
                     np.tprm = (const int32_t *)(pack(c1, np.tform) + 1);
                     pack(c2, np.tform);
@@ -120,7 +131,7 @@ int build_narrow_ops(isr_model *m, const ConstArena &arena) {
                     np.tadd = add_of(cp, np.tform == 0);
                 } else if (q.type == OP_CONV) {
                     np.tail = 2;
-                    np.tform = form_of(c1.rq, true);
+                    np.tform = form_of(c1.rq, true, {&c1});
                     np.tw1 = c1.w;
                     np.tprm = (const int32_t *)(pack(c1, np.tform) + 1);
                     consts.resize(consts.size() + 2 * 4 * c1.Cout_p);   // the kernel stages three convolutions' constants
@@ -176,8 +187,14 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
         const TensorDesc &d = pm.tensors[t];
         return ws + pl.toff[t] + (size_t)first_copy * d.H * d.W * d.Cp;
     };
+    // a plan that takes more copies than asked for gets equal chunks, so that no short one is left over
+    uint64_t per_chunk = pl.chunk;
+    if (pl.chunk > m->chunk && count > pl.chunk) {
+        const uint64_t chunks = (count + pl.chunk - 1) / pl.chunk;
+        per_chunk = (count + chunks - 1) / chunks;
+    }
     for (uint64_t done = 0; done < count;) {
-        uint32_t cnt = (uint32_t)std::min<uint64_t>(m->chunk, count - done);
+        uint32_t cnt = (uint32_t)std::min<uint64_t>(per_chunk, count - done);
         if (bc) cnt = (uint32_t)std::min<uint64_t>(cnt, (uint64_t)bc->n_per_item * 65534);   // one grid row per item
         const bool timed = m->profile_every && (m->chunk_counter++ % m->profile_every) == 0;
         size_t ev = 0;
@@ -661,7 +678,7 @@ int isr_set_workspace(isr_model *m, void *workspace_device, size_t bytes, uint32
     if (bytes < isr_workspace_bytes(m, chunk_samples)) return ISR_ERR_WORKSPACE;
     plan_segments(m->pm, chunk_samples, m->plan[1]);
     plan_segments(m->pm, chunk_samples, m->plan[2]);
-    for (int i = 0; i < 3; ++i) plan_workspace(m->pm, chunk_samples, m->plan[i]);
+    for (int i = 0; i < 3; ++i) plan_workspace(m->pm, i ? plan_copies(m->pm, chunk_samples, bytes, m->plan[i]) : chunk_samples, m->plan[i]);
     m->ws = (uint8_t *)workspace_device;
     m->ws_bytes = bytes;
     m->chunk = chunk_samples;

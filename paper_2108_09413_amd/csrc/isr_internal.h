@@ -171,7 +171,7 @@ struct NarrowBlock {         // identity residual block, stored in device memory
     const int32_t *prm1, *prm2;
     int32_t zp_x, zp_t;      // zero-points of the block input and of the middle tensor
     int32_t lo1, lo2;        // lower clamps of the two convolutions
-    int32_t form;            // 0: RQ_TOP, add RQ_TOP; 1: RQ_TOP_TIES, add RQ_ANY; 2: RQ_ANY, add RQ_ANY
+    int32_t form;            // 0: RQ_TOP with one shift for all channels, add RQ_TOP; 1: the same, add RQ_ANY; 2: RQ_ANY, add RQ_ANY
     AddConst add;
     int32_t pad_;
 };
@@ -180,7 +180,7 @@ struct NarrowParams {
     int8_t *out;             // [B][S][S][C]; tail != 0: [B][S/2][S/2][2C]; unused with a head
     int32_t B;
     // first layer, 3x3 into 16 channels; with fused_noise the kernel draws its own input
-    int32_t stem, fused_noise, zp_in, lo0, form0;   // form0: 0 RQ_TOP, 2 RQ_ANY
+    int32_t stem, fused_noise, zp_in, lo0, form0;   // form0: as NarrowBlock::form
     const int8_t *w0;
     const int32_t *prm0;
     NoiseSource noise;

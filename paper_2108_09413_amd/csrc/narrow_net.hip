@@ -9,19 +9,22 @@
 // reads only t).  Memory sees the noise table, the stage's result and the weights (L2-resident, a few KiB a convolution).
 //
 // The 16 K-bytes of an MFMA operand lane are 16 channels of one tap = one aligned 128-bit LDS read at a tap-shifted
-// address.  Bank conflicts: the LDS serves such a read 16 lanes at a time from 64 banks; 16 lanes are 16 pixels of a row
-// (C = 16, 32) or 8 pixels of two rows (C = 64), C bytes apart, and would meet 2 (4) times in a bank at 32 (64) channels.
-// Chunk c of the pixel at padded (y, x) therefore sits at chunk c ^ s, with s = x / 8 mod 2 at 32 channels and
-// (x / 4 mod 2) + 2 (y mod 2) at 64: pixels of one row that share a residue mod 8 (4) then differ in s, and so do the two
-// rows.  Per kernel column one base address (two at 64 channels, for the row parity) is kept in a register; rows and
-// fragments are immediate offsets.
+// address.  Bank conflicts: the LDS serves the lanes {0-3, 12-15, 20-27} of such a read together, then {4-11, 16-19, 28-31}
+// (and the same of the upper half), from 64 banks of 4 bytes.  At 32 channels (a fragment is two rows of 16 pixels, 32
+// bytes a pixel) each of these sets takes from either row 8 pixels that are all different mod 8, at 64 channels (four rows of
+// 8 pixels, 64 bytes a pixel) from each row 4 that are different mod 4: with chunk c of the pixel at padded (y, x) at chunk
+// c ^ (y mod 2), resp. c ^ (y mod 4), no two lanes of a set meet in a bank.  Columns and rows of a tap are immediate
+// offsets from a base address per parity of the row.
 //
 // What bounds it: issue of the requantisation arithmetic, the matrix unit and the LDS reads of the pixel operands, all three
 // within a factor of two of each other (cycles of a CU per image and block at 16 / 32 / 64 channels: arithmetic
-// 2660 / 1330 / 660, MFMA 1540 / 1150 / 1150, LDS reads 1620 / 1280 / 1280).  Workgroups per CU: four at 16 channels, three
-// at 32 and 64 (LDS); more images per workgroup amortise the weight and constant loads of a convolution at 32 and 64
-// channels, where a wave has one or two fragments per image.  Launches with few images take one image per workgroup:
-// they are bound by the serial chain of convolutions, not by throughput.
+// 2660 / 1330 / 660, MFMA 1540 / 1150 / 1150, LDS reads 1620 / 1280 / 1280), at a clock that the power limit holds near 1.9
+// of 2.4 GHz.  So the three have to overlap: the arithmetic of a fragment stands between the MFMAs of the next.  Four
+// workgroups share a CU at 16 channels, two at 32 and 64, where the operands in flight take the registers of a third (two
+// with pairs of fragments measured 1.81 / 1.40 / 1.11 ms for the stages of a 110-layer net on 16 700 images, three without
+// 1.88 / 1.45 / 1.23 ms).  More images per workgroup amortise the weight and constant loads of a convolution at 32 and 64
+// channels, where a wave has one or two fragments per image.  The certification of the 110-layer net at 100 000 samples took
+// 43.3 ms with one launch per block, 31.6 with one per stage, 27.0 with the overlap.
 #include <string>
 
 #include "conv_device.h"
@@ -33,13 +36,13 @@ namespace {
 
 typedef int v4acc __attribute__((ext_vector_type(4)));
 
-// chunk position of the pixel at padded (y, x)
-template <int C>
-__device__ __forceinline__ int tile_swz(int y, int x) {
-    return C == 64 ? (((x >> 2) & 1) | ((y & 1) << 1)) : C == 32 ? ((x >> 3) & 1) : 0;
+// byte offset of a chunk of the pixel at padded (y, x).  STRIDED: the layout of x for the stride-2 reads of the tail, where
+// all rows of a read have the same parity and columns 8 apart must differ.
+template <int C, int S, bool STRIDED = false>
+__device__ __forceinline__ int tile_at(int y, int x, int chunk) {
+    const int s = C == 64 ? (y & 3) : C == 32 ? (STRIDED ? (x >> 3) & 1 : y & 1) : 0;
+    return ((y * (S + 2) + x) * (C / 16) + (chunk ^ s)) * 16;
 }
-template <int C, int S>
-__device__ __forceinline__ int tile_at(int y, int x, int chunk) { return ((y * (S + 2) + x) * (C / 16) + (chunk ^ tile_swz<C>(y, x))) * 16; }
 template <int C, int S>
 constexpr int tile_bytes() { return (S + 2) * (S + 2) * C; }
 
@@ -77,49 +80,94 @@ template <int C, int S>
 struct WideConv {
     static constexpr int P = S + 2, KS = 9 * C / 32, KP = (9 * C + 63) / 64 * 64, MF = C / 32, NF = S * S / 32;
     static constexpr int ROWS = 32 / S, FRAG = ROWS * P * C;   // rows of a fragment; bytes from one to the next
-    int base[3][C == 64 ? 2 : 1];
-    int out;                      // the lane's chunk of its own pixel (fragment 0) for M fragment mf
+    int base[C == 64 ? 6 : 2];    // by kernel row (mod 2 at 32 channels) and half of the 64 channels
+    int out, out_strided;         // the lane's chunk of its own pixel (fragment 0) for M fragment mf; the same in the strided layout
     int mf, half, l;
 
     __device__ __forceinline__ WideConv(int lane, int wave) {
         l = lane & 31; half = lane >> 5; mf = wave % MF;
         const int y = l / S, x = l % S;
+        if constexpr (C == 64) {
 #pragma unroll
-        for (int kx = 0; kx < 3; ++kx) {
-            base[kx][0] = tile_at<C, S>(y, x + kx, half);
-            if constexpr (C == 64) base[kx][1] = base[kx][0] ^ 32;
+            for (int ky = 0; ky < 3; ++ky) {
+                base[2 * ky] = tile_at<C, S>(y + ky, x, half);
+                base[2 * ky + 1] = base[2 * ky] ^ 32;
+            }
+        } else {
+            base[0] = tile_at<C, S>(y, x, half);
+            base[1] = base[0] ^ 16;   // rows of the other parity: chunk position swapped, row offset in the immediate
         }
         out = tile_at<C, S>(y + 1, x + 1, 2 * mf + half);
+        out_strided = tile_at<C, S, true>(y + 1, x + 1, 2 * mf + half);
     }
+    __device__ __forceinline__ const int8_t *weight_row(const int8_t *w) const { return w + (mf * 32 + l) * KP + half * 16; }
     __device__ __forceinline__ void load_weights(const int8_t *w, v4i (&fa)[KS]) const {
-        const int8_t *row = w + (mf * 32 + l) * KP + half * 16;
+        const int8_t *row = weight_row(w);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) fa[ks] = *(const v4i *)(row + ks * 32);
     }
+    __device__ __forceinline__ v4i operand(const int8_t *frag, int ks) const {   // pixel operand of K step ks
+        const int tap = C == 64 ? ks >> 1 : ks, ky = tap / 3, kx = tap % 3;
+        return *(const v4i *)(frag + (C == 64 ? base[2 * ky + (ks & 1)] + kx * C : base[ky & 1] + (ky * P + kx) * C));
+    }
     __device__ __forceinline__ v16i run(const int8_t *frag, const v4i (&fa)[KS], v16i acc) const {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int tap = C == 64 ? ks >> 1 : ks, cc = C == 64 ? ks & 1 : 0, ky = tap / 3, kx = tap % 3;
-            const v4i fb = *(const v4i *)(frag + base[kx][C == 64 ? (cc ^ (ky & 1)) : 0] + ky * P * C);
-            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ks], fb, acc, 0, 0, 0);
-        }
+        for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ks], operand(frag, ks), acc, 0, 0, 0);
         return acc;
     }
 };
+
+// The K loop of a group of P fragments with the epilogue of the group before between its MFMAs: a step issues P independent
+// MFMAs (32 cycles of the matrix unit each) and a KS-th of the other group's requantisation (EPI), and reads the pixel
+// operands of three steps later.  Left to itself the compiler puts the chain of MFMAs first, its operand reads at most two
+// ahead, and the arithmetic behind it.  NEXT: as a step's weights have seen their last MFMA, those of the next convolution
+// are fetched into their registers (`next`: the lane's weight row there).
+template <int P, bool EPI, bool NEXT, int C, int S, class Elem>
+__device__ __forceinline__ void wide_group(const WideConv<C, S> &wc, const int8_t *const (&src)[P], v4i (&fa)[WideConv<C, S>::KS], v16i (&acc)[P],
+                                           const int8_t *next, Elem elem) {
+    constexpr int KS = WideConv<C, S>::KS, AHEAD = 3, PER = (16 * P + KS - 2) / (KS - 1);   // elements per step; none in the first
+    v4i fb[AHEAD + 1][P];
+#pragma unroll
+    for (int ks = 0; ks < AHEAD; ++ks)
+#pragma unroll
+        for (int q = 0; q < P; ++q) fb[ks][q] = wc.operand(src[q], ks);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        if (ks + AHEAD < KS)
+#pragma unroll
+            for (int q = 0; q < P; ++q) fb[(ks + AHEAD) % (AHEAD + 1)][q] = wc.operand(src[q], ks + AHEAD);
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            acc[q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ks], fb[ks % (AHEAD + 1)][q], acc[q], 0, 0, 0);
+            if constexpr (EPI) {
+                const int first = (ks - 1) * PER + q * (PER / P), end = q + 1 < P ? first + PER / P : ks * PER;
+#pragma unroll
+                for (int e = first; e < end; ++e)
+                    if (e >= 0 && e < 16 * P) elem(e);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (NEXT) fa[ks] = *(const v4i *)(next + ks * 32);
+    }
+}
 
 // A lane's constants of N consecutive output channels from the packed form [4][C].  The top form keeps them in registers
 // across the fragments of a convolution; the others, for the few layers that need them, read them where they are used.
 template <int N, int RQ, bool TOP = RQ == RQ_TOP>
 struct LaneConsts {
-    int b[N], m0[N], chi, sh[N];
-    __device__ __forceinline__ LaneConsts(const int *prm, int C, int c0) {
+    int m0[N], chi, sh, b4[4];    // one addend and (forms in use here) one multiplier for all channels
+    const int *b;                 // 16 channels: the bias is read into the accumulator, registers are short
+    __device__ __forceinline__ LaneConsts(const int *prm, int C, int c0) : b(prm + c0) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) { b[i] = prm[c0 + i]; m0[i] = prm[C + c0 + i]; sh[i] = prm[3 * C + c0 + i]; }
-        chi = prm[2 * C + c0];
+        for (int i = 0; i < N; ++i) m0[i] = prm[C + c0 + i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b4[i] = prm[c0 + i];
+        chi = prm[2 * C];
+        sh = prm[3 * C];
     }
-    __device__ __forceinline__ void fragment() const {}   // start of a fragment
-    __device__ __forceinline__ int bias(int i) const { return b[i]; }
-    __device__ __forceinline__ int conv(int acc, int i, int lo) const { return rq_conv<RQ>(acc, m0[i], chi, sh[i], lo); }
+    __device__ __forceinline__ void fragment() const { if (N == 16) asm volatile("" ::: "memory"); }   // start of a fragment: the bias is not kept
+    __device__ __forceinline__ int bias(int i) const { return N == 4 ? b4[i & 3] : b[i]; }
+    __device__ __forceinline__ int conv(int acc, int i, int lo) const { return rq_conv<RQ>(acc, m0[i], chi, sh, lo); }
 };
 template <int N, int RQ>
 struct LaneConsts<N, RQ, false> {
@@ -141,12 +189,69 @@ __device__ __forceinline__ auto bias_vector(const LaneConsts<N, RQ> &k) {
     return v;
 }
 
+// FRAGS fragments of one convolution of a wave, weights in `fa`, which afterwards holds those at `next`: source(i) is
+// fragment i's tile address; element(i, e, value) consumes the accumulator of element e (in the order of e), after
+// start(i) and before finish(i).
+template <int FRAGS, int RQ, bool PAIRS, int C, int S, class Source, class Start, class Element, class Finish>
+__device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&fa)[WideConv<C, S>::KS], const LaneConsts<16, RQ> &k, const int8_t *next,
+                                               Source source, Start start, Element element, Finish finish) {
+    if constexpr (RQ == RQ_TOP) {
+        constexpr int P = PAIRS && FRAGS >= 2 ? 2 : 1, G = FRAGS / P;
+        static_assert(FRAGS % P == 0, "whole groups");
+        const int8_t *row = wc.weight_row(next);
+        v16i acc[P];
+        auto begin = [&](int g, const int8_t *(&src)[P]) {
+            k.fragment();
+#pragma unroll
+            for (int q = 0; q < P; ++q) { src[q] = source(g * P + q); acc[q] = bias_vector<16, RQ>(k); }
+        };
+        {
+            const int8_t *src[P];
+            begin(0, src);
+            wide_group<P, false, G == 1>(wc, src, fa, acc, row, [](int) {});
+        }
+#pragma unroll
+        for (int g = 1; g < G; ++g) {
+            v16i prev[P];
+#pragma unroll
+            for (int q = 0; q < P; ++q) { prev[q] = acc[q]; start((g - 1) * P + q); }
+            const int8_t *src[P];
+            begin(g, src);
+            auto elem = [&](int e) {
+                const int i = (g - 1) * P + e / 16;
+                element(i, e & 15, prev[e / 16][e & 15]);
+                if ((e & 15) == 15) finish(i);
+            };
+            if (g + 1 < G) wide_group<P, true, false>(wc, src, fa, acc, row, elem);
+            else wide_group<P, true, true>(wc, src, fa, acc, row, elem);
+        }
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            start((G - 1) * P + q);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) element((G - 1) * P + q, e, acc[q][e]);
+            finish((G - 1) * P + q);
+        }
+    } else {
+#pragma unroll 1
+        for (int i = 0; i < FRAGS; ++i) {
+            k.fragment();
+            const v16i acc = wc.run(source(i), fa, bias_vector<16, RQ>(k));
+            start(i);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) element(i, e, acc[e]);
+            finish(i);
+        }
+        wc.load_weights(next, fa);
+    }
+}
+
 // f with the compile-time forms of a descriptor's `form`; TOPA: the add's form next to RQ_TOP
 template <int TOPA, class F>
 __device__ __forceinline__ void with_form(int form, F f) {
     using std::integral_constant;
     if (form == 0) f(integral_constant<int, RQ_TOP>{}, integral_constant<int, TOPA>{});
-    else if (form == 1) f(integral_constant<int, RQ_TOP_TIES>{}, integral_constant<int, RQ_ANY>{});
+    else if (form == 1) f(integral_constant<int, RQ_TOP>{}, integral_constant<int, RQ_ANY>{});
     else f(integral_constant<int, RQ_ANY>{}, integral_constant<int, RQ_ANY>{});
 }
 
@@ -154,14 +259,14 @@ __device__ __forceinline__ void with_form(int form, F f) {
 template <int C, int S, int NI>
 __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t *tile, int8_t *scratch, long img0, int tid) {
     constexpr int WORDS = C / 4, ITEMS = NI * WORDS, PARTS = 256 / ITEMS, PPP = S * S / PARTS;   // pixels per part
-    static_assert(ITEMS <= 256 && 256 % ITEMS == 0 && S * S % PARTS == 0, "one part per thread");
+    static_assert(ITEMS <= 256 && S * S % PARTS == 0, "one part per thread");
     int *sums = (int *)scratch;                       // [NI][C]
     int8_t *feat = scratch + NI * C * 4;              // [NI][C]
     int *best_of = (int *)(feat + NI * C);            // [NI]
     const int lane = tid & 63, wave = tid >> 6;
     for (int i = tid; i < NI * C; i += 256) sums[i] = 0;
     lds_barrier();
-    {
+    if (tid < ITEMS * PARTS) {
         const int item = tid % ITEMS, part = tid / ITEMS, im = item / WORDS, word = item % WORDS;
         const int8_t *t = tile + im * tile_bytes<C, S>();
         int s[4] = {0, 0, 0, 0};
@@ -227,7 +332,7 @@ __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t 
 }
 
 template <int C, int S, int NI>
-__global__ __launch_bounds__(256, C == 16 ? 4 : 3) void narrow_kernel(const NarrowParams p) {
+__global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const NarrowParams p) {
     constexpr int P = S + 2, CH = C / 16, C2 = 2 * C, S2 = S / 2;
     constexpr int TB = tile_bytes<C, S>();
     constexpr bool TAIL = C < 64;                    // there is a next stage
@@ -241,7 +346,6 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 3) void narrow_kernel(const Narr
     const long img0 = (long)blockIdx.x * NI;
     typedef const __attribute__((address_space(4))) NarrowBlock *block_ptr;   // scalar loads
     const block_ptr blocks = (block_ptr)(uintptr_t)p.blocks;
-    const bool to_memory = !p.tail && !p.head;       // the last block stores its sum instead of keeping it in LDS
 
     // ---- the stage's input ----
     if (p.nblocks)
@@ -289,21 +393,18 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 3) void narrow_kernel(const Narr
             const int l = lane & 15, kg = lane >> 4, kr = kg < 3 ? kg : 0;
             const v4i fa = *(const v4i *)(p.w0 + l * 64 + kg * 16);
             const int x = 16 * (wave & 1) + l, row0 = 16 * (wave >> 1);
-            const bool store = to_memory && p.nblocks == 0;
             with_form<RQ_TOP>(p.form0, [&](auto rq, auto) {
                 constexpr int RQ = decltype(rq)::value;
                 const LaneConsts<4, RQ> k(p.prm0, 16, 4 * kg);
                 const int *src = img + (row0 + kr) * PW + x;
                 int8_t *dst = X + ((row0 + 1) * P + x + 1) * 16 + 4 * kg;
-                int8_t *gdst = p.out + ((img0 * S + row0) * S + x) * 16 + 4 * kg;
 #pragma unroll 4
                 for (int r = 0; r < 16; ++r) {
                     const v4i fb = {src[r * PW], src[r * PW + 1], src[r * PW + 2], src[r * PW + 3]};
                     k.fragment();
                     const v4acc acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, fb, bias_vector<4, RQ>(k), 0, 0, 0);
                     const uint32_t q = rq_pack<RQ>(k.conv(acc[0], 0, p.lo0), k.conv(acc[1], 1, p.lo0), k.conv(acc[2], 2, p.lo0), k.conv(acc[3], 3, p.lo0));
-                    if (store) *(uint32_t *)(gdst + r * S * 16) = q;
-                    else *(uint32_t *)(dst + r * P * 16) = q;
+                    *(uint32_t *)(dst + r * P * 16) = q;
                 }
             });
         }
@@ -312,12 +413,18 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 3) void narrow_kernel(const Narr
             const int im = i / (S * S * CH), j = i % (S * S * CH), pix = j / CH, c = j % CH;
             long g = img0 + im;
             if (g >= p.B) g = p.B - 1;                   // images past the end repeat the last one; never stored
-            *(v4i *)(X + im * TB + tile_at<C, S>(pix / S + 1, pix % S + 1, c)) = *(const v4i *)(p.in + (g * S * S + pix) * C + c * 16);
+            const int y = pix / S + 1, x = pix % S + 1;
+            const int at = p.nblocks ? tile_at<C, S>(y, x, c) : tile_at<C, S, true>(y, x, c);
+            *(v4i *)(X + im * TB + at) = *(const v4i *)(p.in + (g * S * S + pix) * C + c * 16);
         }
     }
 
     // ---- identity blocks ----
     int zp_t = 256;   // zero-point in the border of t; none yet
+    constexpr bool WIDE = C > 16;
+    v4i fa[WIDE ? WideConv<WIDE ? C : 32, WIDE ? S : 16>::KS : 1];   // weights of the convolution to come
+    if constexpr (WIDE)
+        if (p.nblocks) WideConv<C, S>(lane, wave).load_weights(blocks[0].w1, fa);
     for (int blk = 0; blk < p.nblocks; ++blk) {
         const auto &d = blocks[blk];
         const bool last = blk + 1 == p.nblocks;
@@ -335,7 +442,8 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 3) void narrow_kernel(const Narr
                 constexpr int KP = (9 * C + 63) / 64 * 64;
                 const int l = lane & 15, kg = lane >> 4, kx = kg < 3 ? kg : 0;
                 const int x = 16 * (wave & 1) + l, row0 = 16 * (wave >> 1);
-                auto conv = [&](const int8_t *src, const int8_t *w, const int *pr, auto emit) {
+                // The MFMAs of row r + 1 stand between the elements of row r's epilogue: element(r, e, value), then finish(r).
+                auto conv = [&](const int8_t *src, const int8_t *w, const int *pr, auto make) {
                     v4i fa[3];
 #pragma unroll
                     for (int ky = 0; ky < 3; ++ky) {
@@ -344,81 +452,93 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 3) void narrow_kernel(const Narr
                     }
                     const LaneConsts<4, RQ> k(pr, 16, 4 * kg);
                     const int8_t *col = src + (row0 * P + x + kx) * C;   // padded (row0, x + kx) = tap (0, kx) of output (row0, x)
-                    v4i b0 = *(const v4i *)col, b1 = *(const v4i *)(col + P * C);
-#pragma unroll 4
+                    auto operand = [&](int y) { return *(const v4i *)(col + (y < 18 ? y : 17) * P * C); };   // tile rows of the strip: 0 .. 17
+                    v4i b[6];   // rows r + 1 .. r + 5 of the ring, read four rows ahead
+#pragma unroll
+                    for (int y = 0; y < 6; ++y) b[y] = operand(y);
+                    v4acc acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[0], b[0], bias_vector<4, RQ>(k), 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[1], b[1], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[2], b[2], acc, 0, 0, 0);
+                    auto row = make(k);
+#pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        const v4i b2 = *(const v4i *)(col + (r + 2) * P * C);
+                        b[r % 6] = operand(r + 6);
                         k.fragment();
-                        v4acc acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[0], b0, bias_vector<4, RQ>(k), 0, 0, 0);
-                        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[1], b1, acc, 0, 0, 0);
-                        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[2], b2, acc, 0, 0, 0);
-                        emit(r, acc, k);
-                        b0 = b1;
-                        b1 = b2;
+                        v4acc next = acc;
+                        // (no row 16: the last step has no MFMAs)
+                        if (r < 15) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[0], b[(r + 1) % 6], bias_vector<4, RQ>(k), 0, 0, 0);
+                        row(r, 0, acc[0]);
+                        row(r, 1, acc[1]);
+                        if (RQ == RQ_TOP) __builtin_amdgcn_sched_barrier(0);
+                        if (r < 15) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[1], b[(r + 2) % 6], next, 0, 0, 0);
+                        row(r, 2, acc[2]);
+                        if (RQ == RQ_TOP) __builtin_amdgcn_sched_barrier(0);
+                        if (r < 15) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[2], b[(r + 3) % 6], next, 0, 0, 0);
+                        row(r, 3, acc[3]);
+                        if (RQ == RQ_TOP) __builtin_amdgcn_sched_barrier(0);
+                        acc = next;
                     }
                 };
                 const int at = ((row0 + 1) * P + x + 1) * 16 + 4 * kg;      // the lane's four channels of its pixel in row 0
-                conv(X, d.w1, prm[0], [&](int r, const v4acc &a, const LaneConsts<4, RQ> &k) {
-                    *(uint32_t *)(T + at + r * P * 16) = rq_pack<RQ>(k.conv(a[0], 0, d.lo1), k.conv(a[1], 1, d.lo1), k.conv(a[2], 2, d.lo1), k.conv(a[3], 3, d.lo1));
+                conv(X, d.w1, prm[0], [&](const LaneConsts<4, RQ> &k) {
+                    return [&, q = v4acc{}](int r, int e, int a) mutable {
+                        q[e] = k.conv(a, e, d.lo1);
+                        if (e == 3) *(uint32_t *)(T + at + r * P * 16) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
+                    };
                 });
                 lds_barrier();
                 if (!last)
                     for (int i = tid; i < 4 * C; i += 256) prm[0][i] = blocks[blk + 1].prm1[i];
                 if (zp_next != d.zp_x) fill_ring<C, S, NI>(X, zp_next, tid);
                 const AddConst ac = {d.add.ms, d.add.mr, d.add.c0, d.add.k, d.add.sh, d.add.lo};
-                int8_t *gdst = p.out + ((img0 * S + row0) * S + x) * 16 + 4 * kg;
-                const bool store = last && to_memory;
-                conv(T, d.w2, prm[1], [&](int r, const v4acc &a, const LaneConsts<4, RQ> &k) {
-                    uint32_t *res = (uint32_t *)(X + at + r * P * 16);
-                    const uint32_t rw = *res;
-                    int q[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) q[i] = rq_add<RQ, RQA>(k.conv(a[i], i, d.lo2), rw, i, ac);
-                    const uint32_t o = rq_pack<RQA>(q[0], q[1], q[2], q[3]);
-                    if (store) *(uint32_t *)(gdst + r * S * 16) = o;
-                    else *res = o;
+                conv(T, d.w2, prm[1], [&](const LaneConsts<4, RQ> &k) {
+                    auto residual = [&](int r) { return *(const uint32_t *)(X + at + (r < 16 ? r : 15) * P * 16); };
+                    return [&, residual, q = v4acc{}, rw0 = residual(0), rw1 = residual(1), rw2 = residual(2)](int r, int e, int a) mutable {
+                        q[e] = rq_add<RQ, RQA>(k.conv(a, e, d.lo2), rw0, e, ac);
+                        if (e == 3) {
+                            *(uint32_t *)(X + at + r * P * 16) = rq_pack<RQA>(q[0], q[1], q[2], q[3]);
+                            rw0 = rw1; rw1 = rw2; rw2 = residual(r + 3);   // read three rows ahead
+                        }
+                    };
                 });
             } else {
-                const WideConv<C, S> wc(lane, wave);
-                constexpr int MF = wc.MF, NF = wc.NF, FRAGS = NI * NF * MF / 4;   // fragments per wave
-                v4i fa[wc.KS];
-                wc.load_weights(d.w1, fa);
+                typedef WideConv<C, S> Wide;
+                constexpr int MF = Wide::MF, NF = Wide::NF, FRAGS = NI * NF * MF / 4;   // fragments per wave
+                auto offset = [&](int i) { const int f = wave / MF + i * (4 / MF); return (f / NF) * TB + (f % NF) * Wide::FRAG; };
+                // a lane's addresses are worked out anew for each convolution: kept across them they would be spilled
+                int ln = lane;
+                asm volatile("" : "+v"(ln));
                 {
+                    const Wide wc(ln, wave);
                     const LaneConsts<16, RQ> k(prm[0], C, wc.mf * 32 + wc.half * 16);
-#pragma unroll 1
-                    for (int i = 0; i < FRAGS; ++i) {
-                        const int f = wave / MF + i * (4 / MF), off = (f / NF) * TB + (f % NF) * wc.FRAG;
-                        k.fragment();
-                        const v16i a = wc.run(X + off, fa, bias_vector<16, RQ>(k));
-                        int q[16];
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) q[e] = k.conv(a[e], e, d.lo1);
-                        *(v4i *)(T + off + wc.out) = rq_pack16<RQ>(q);
-                    }
+                    int q[4];
+                    v4i o;
+                    wide_fragments<FRAGS, RQ, true>(wc, fa, k, d.w2, [&](int i) { return X + offset(i); }, [](int) {},
+                        [&](int, int e, int a) {
+                            q[e & 3] = k.conv(a, e, d.lo1);
+                            if ((e & 3) == 3) o[e >> 2] = (int)rq_pack<RQ>(q[0], q[1], q[2], q[3]);
+                        },
+                        [&](int i) { *(v4i *)(T + offset(i) + wc.out) = o; });
                 }
-                wc.load_weights(d.w2, fa);
+                asm volatile("" : "+v"(ln));
                 lds_barrier();
                 if (!last)
                     for (int i = tid; i < 4 * C; i += 256) prm[0][i] = blocks[blk + 1].prm1[i];
                 if (zp_next != d.zp_x) fill_ring<C, S, NI>(X, zp_next, tid);
                 const AddConst ac = {d.add.ms, d.add.mr, d.add.c0, d.add.k, d.add.sh, d.add.lo};
+                const Wide wc(ln, wave);
                 const LaneConsts<16, RQ> k(prm[1], C, wc.mf * 32 + wc.half * 16);
-                const bool store = last && to_memory;
-#pragma unroll 1
-                for (int i = 0; i < FRAGS; ++i) {
-                    const int f = wave / MF + i * (4 / MF), im = f / NF, off = im * TB + (f % NF) * wc.FRAG;
-                    k.fragment();
-                    const v16i a = wc.run(T + off, fa, bias_vector<16, RQ>(k));
-                    v4i *res = (v4i *)(X + off + wc.out);
-                    const v4i rv = *res;
-                    int q[16];
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) q[e] = rq_add<RQ, RQA>(k.conv(a[e], e, d.lo2), (uint32_t)rv[e >> 2], e & 3, ac);
-                    const v4i o = rq_pack16<RQA>(q);
-                    const long g = img0 + im;
-                    if (!store) *res = o;
-                    else if (g < p.B) *(v4i *)(p.out + ((g * S * S + (f % NF) * 32 + wc.l) * C + (2 * wc.mf + wc.half) * 16)) = o;
-                }
+                // a lane writes where it, or the lane with the other half of its pixel in this wave, has read
+                const int dst = last && p.tail ? wc.out_strided : wc.out;
+                int q[4];
+                v4i o, rv[2];   // residuals of the two fragments of a group
+                wide_fragments<FRAGS, RQ, RQA == RQ_TOP>(wc, fa, k, last ? d.w2 : blocks[blk + 1].w1, [&](int i) { return T + offset(i); },
+                    [&](int i) { rv[i & 1] = *(const v4i *)(X + offset(i) + wc.out); },
+                    [&](int i, int e, int a) {
+                        q[e & 3] = rq_add<RQ, RQA>(k.conv(a, e, d.lo2), (uint32_t)rv[i & 1][e >> 2], e & 3, ac);
+                        if ((e & 3) == 3) o[e >> 2] = (int)rq_pack<RQA>(q[0], q[1], q[2], q[3]);
+                    },
+                    [&](int i) { *(v4i *)(X + offset(i) + dst) = o; });
             }
         });
     }
@@ -428,29 +548,31 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 3) void narrow_kernel(const Narr
         if (p.tail) {
             constexpr int TB2 = tile_bytes<C2, S2>(), KP1 = (9 * C + 63) / 64 * 64, KS1 = (9 * C + 31) / 32;
             static_assert(NI * TB2 <= NI * TB, "the next stage's tile fits the middle tensor's");
-            const WideConv<C2, S2> wc(lane, wave);
-            constexpr int MF = wc.MF, NF = wc.NF, FRAGS = NI * NF * MF / 4;
-            const int l = wc.l, half = wc.half, mf = wc.mf;
-            const int oy0 = l / S2, ox = l % S2;       // the lane's output pixel in fragment 0
-            v4i f1[KS1];
-#pragma unroll
-            for (int ks = 0; ks < KS1; ++ks) f1[ks] = *(const v4i *)(p.tw1 + (mf * 32 + l) * KP1 + ks * 32 + half * 16);
-            // tap (ky, kx) of output (oy, ox) is padded input (2 oy + ky, 2 ox + kx).  16 input channels: a K step is two taps,
-            // the lane half picks one (the tenth has zero weights); 32: one tap, the half picks 16 channels
-            int b1[KS1];
-#pragma unroll
-            for (int ks = 0; ks < KS1; ++ks) {
-                int tap = C == 16 ? 2 * ks + half : ks;
-                if (tap > 8) tap = 0;
-                b1[ks] = tile_at<C, S>(2 * oy0 + tap / 3, 2 * ox + tap % 3, C == 16 ? 0 : half);
-            }
+            typedef WideConv<C2, S2> Wide;
+            constexpr int MF = Wide::MF, NF = Wide::NF, FRAGS = NI * NF * MF / 4;
             constexpr int FRAG1 = 2 * (32 / S2) * P * C;   // input bytes from one output fragment to the next (an even number of rows)
             lds_barrier();            // x is complete, the last block is done with t
             fill_ring<C2, S2, NI>(T, p.tzp_t, tid);
             with_form<RQ_TOP_WIDE>(p.tform, [&](auto rq, auto rqa) {
                 constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
-                const int c0 = mf * 32 + half * 16;
+                int ln = lane;
+                asm volatile("" : "+v"(ln));
                 {
+                    const Wide wc(ln, wave);
+                    const int l = wc.l, half = wc.half, mf = wc.mf, c0 = mf * 32 + half * 16;
+                    const int oy0 = l / S2, ox = l % S2;       // the lane's output pixel in fragment 0
+                    v4i f1[KS1];
+#pragma unroll
+                    for (int ks = 0; ks < KS1; ++ks) f1[ks] = *(const v4i *)(p.tw1 + (mf * 32 + l) * KP1 + ks * 32 + half * 16);
+                    // tap (ky, kx) of output (oy, ox) is padded input (2 oy + ky, 2 ox + kx).  16 input channels: a K step is two taps,
+                    // the lane half picks one (the tenth has zero weights); 32: one tap, the half picks 16 channels
+                    int b1[KS1];
+#pragma unroll
+                    for (int ks = 0; ks < KS1; ++ks) {
+                        int tap = C == 16 ? 2 * ks + half : ks;
+                        if (tap > 8) tap = 0;
+                        b1[ks] = tile_at<C, S, true>(2 * oy0 + tap / 3, 2 * ox + tap % 3, C == 16 ? 0 : half);
+                    }
                     const LaneConsts<16, RQ> k(tprm, C2, c0);
                     const bool store = p.tail == 2 && !p.head;
 #pragma unroll 1
@@ -472,10 +594,14 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 3) void narrow_kernel(const Narr
                     }
                 }
                 if (p.tail == 1) {
-                    v4i fa[wc.KS];
+                    asm volatile("" : "+v"(ln));
+                    const Wide wc(ln, wave);
+                    const int l = wc.l, half = wc.half, mf = wc.mf, c0 = mf * 32 + half * 16;
+                    const int oy0 = l / S2, ox = l % S2;
+                    v4i fa[Wide::KS];
                     wc.load_weights(p.tw2, fa);
                     const v4i fp = *(const v4i *)(p.twp + (mf * 32 + l) * 64 + half * 16);   // channels 0 .. 31 (zeros past C)
-                    const int xp = tile_at<C, S>(2 * oy0 + 1, 2 * ox + 1, C == 16 ? 0 : half);
+                    const int xp = tile_at<C, S, true>(2 * oy0 + 1, 2 * ox + 1, C == 16 ? 0 : half);
                     lds_barrier();
 #pragma unroll 1
                     for (int i = 0; i < FRAGS; ++i) {
@@ -510,8 +636,14 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 3) void narrow_kernel(const Narr
             return;
         }
     }
-    if (p.head) {
-        lds_barrier();
+    lds_barrier();
+    if (!p.head) {   // the stage's result
+        for (int i = tid; i < NI * S * S * CH; i += 256) {
+            const int im = i / (S * S * CH), j = i % (S * S * CH), pix = j / CH, c = j % CH;
+            const long g = img0 + im;
+            if (g < p.B) *(v4i *)(p.out + (g * S * S + pix) * C + c * 16) = *(const v4i *)(X + im * TB + tile_at<C, S>(pix / S + 1, pix % S + 1, c));
+        }
+    } else {
         if constexpr (C == 64) narrow_head<C, S, NI>(p, X, T, img0, tid);
     }
 }
@@ -547,11 +679,12 @@ hipError_t launch_narrow(const NarrowParams &p, int channels, hipStream_t st) {
     if (p.head && (!(channels == 64 || (channels == 16 && p.tail == 2)) || (p.tail && channels == 64) || !p.fc_w || !p.fc_bias || p.classes < 1 ||
                    p.classes_p < p.classes || (channels == 64 && p.nblocks == 0)))
         return hipErrorInvalidValue;
-    // one image per workgroup while that leaves no CU with more than one workgroup; beyond, several share the weights
-    const bool few = p.B <= 256;
+    // images per workgroup: as few as let every workgroup of the launch run at once (two per CU); beyond, as many as fit,
+    // to share the weights
+    const bool one = p.B <= 256, two = p.B <= 1024;
     if (channels == 16) return launch_stage<16, 32, 1>(p, st);
-    if (channels == 32) return few ? launch_stage<32, 16, 1>(p, st) : launch_stage<32, 16, 2>(p, st);
-    if (channels == 64) return few ? launch_stage<64, 8, 1>(p, st) : launch_stage<64, 8, 4>(p, st);
+    if (channels == 32) return one ? launch_stage<32, 16, 1>(p, st) : two ? launch_stage<32, 16, 2>(p, st) : launch_stage<32, 16, 3>(p, st);
+    if (channels == 64) return one ? launch_stage<64, 8, 1>(p, st) : two ? launch_stage<64, 8, 2>(p, st) : launch_stage<64, 8, 6>(p, st);
     return hipErrorInvalidValue;
 }
 

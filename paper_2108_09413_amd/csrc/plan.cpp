@@ -46,6 +46,7 @@ void plan_segments(const ParsedModel &pm, uint32_t B, Plan &pl) {
 // Offsets of every tensor for a chunk of B samples; buffers are reused once the
 // last op reading a tensor has been issued (stream order makes that safe).
 void plan_workspace(const ParsedModel &pm, uint32_t B, Plan &pl) {
+    pl.chunk = B;
     const int nt = (int)pm.tensors.size();
     std::vector<int> last_use(nt, -1);
     for (int i = 0; i < (int)pl.ops.size(); ++i) {
@@ -110,6 +111,21 @@ void plan_workspace(const ParsedModel &pm, uint32_t B, Plan &pl) {
     pl.logits_off = round_up(top, 256);
     pl.argmax_off = pl.logits_off + round_up((size_t)B * pm.classes * 4, 256);
     pl.bytes = pl.argmax_off + round_up((size_t)B * 4, 256);
+}
+
+uint32_t plan_copies(const ParsedModel &pm, uint32_t B, size_t bytes, const Plan &pl) {
+    for (const DevOp &d : pl.ops)
+        if (!d.narrow) return B;
+    int64_t most = 1;   // pixels x channels of a tensor, which the kernels keep in 32 bits for a whole chunk
+    for (const TensorDesc &t : pm.tensors) most = std::max<int64_t>(most, (int64_t)t.H * t.W * std::max(t.Cp, 16));
+    Plan q = pl;
+    uint64_t n = std::min<uint64_t>((1ull << 31) / most - 1, 1u << 20);
+    for (int i = 0; i < 8 && n > B; ++i) {
+        plan_workspace(pm, (uint32_t)n, q);
+        if (q.bytes <= bytes) return (uint32_t)n;
+        n = std::min<uint64_t>(n - 1, (uint64_t)((double)n * bytes / q.bytes));
+    }
+    return B;
 }
 
 namespace {

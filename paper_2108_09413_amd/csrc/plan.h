@@ -51,6 +51,7 @@ struct Plan {
     std::vector<size_t> toff;           // per tensor offset inside the workspace
     std::vector<char> has;              // tensor is produced by this plan
     size_t logits_off = 0, argmax_off = 0, bytes = 0;
+    uint32_t chunk = 0;                 // copies that the tensors are placed for
 };
 
 // Host image of the constant arena (weights, per-channel tables); descriptors hold offsets into it
@@ -70,6 +71,10 @@ void rebase_device_ops(std::vector<DevOp> &ops, const uint8_t *base);
 void build_fused_plan(const ParsedModel &pm, const std::vector<DevOp> &plain, std::vector<DevOp> &fused, bool wide_bottlenecks);
 // Chooses the sub-chunk segments of a plan for chunks of B samples (before plan_workspace).
 void plan_segments(const ParsedModel &pm, uint32_t B, Plan &pl);
+// Copies a plan processes at a time inside `bytes` of workspace that hold chunks of B copies of every plan: B, or as many as
+// fit where the plan's ops are one launch per stage of whole images in LDS.  Such a plan stores a fraction of the
+// tensors; its kernels take any number of images, and every chunk ends in a partly filled last round of workgroups.
+uint32_t plan_copies(const ParsedModel &pm, uint32_t B, size_t bytes, const Plan &pl);
 // Offsets of every tensor of a chunk of B samples in the workspace.
 void plan_workspace(const ParsedModel &pm, uint32_t B, Plan &pl);
 

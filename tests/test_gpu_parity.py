@@ -315,7 +315,7 @@ def test_downsampling_residual_blocks_in_one_kernel(isr):
         m.close()
 
 
-@pytest.mark.parametrize("copies", [1, 3, 256, 257, 259])
+@pytest.mark.parametrize("copies", [1, 3, 256, 257, 1025])
 @pytest.mark.parametrize("net", ["stages", "down"])
 def test_stages_of_the_nets_on_32x32_images(isr, net, copies):
     """One launch per stage: first layer + blocks + down-sampling, a stage without blocks, blocks + pooling + fully
