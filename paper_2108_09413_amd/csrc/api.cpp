@@ -5,6 +5,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <new>
 #include <string>
 
@@ -51,6 +52,66 @@ int get_table(isr_model *m, uint32_t sigma, const DeviceNoiseTable **out) {
     *out = m->dtables + slot;
     return ISR_OK;
 }
+
+// Device tables of isr_noise_bank: a call has one to itself until its stream is synchronised and hands it back; the next call
+// on the GPU with the same sigma finds it filled.  At most BANK_TABLES wait for the next call, the others are freed, and
+// all are when the process ends (registered after the HIP runtime's own handlers, so run before them).
+constexpr size_t BANK_TABLE_BYTES = 128 * 1024;   // sigma 1024 takes 126 840
+constexpr size_t BANK_TABLES = 4;
+struct BankTable {
+    int device = -1;
+    uint32_t sigma = 0, R = 0;                // of the contents; 0: none
+    size_t words = 0;
+    uint32_t *dev = nullptr, *host = nullptr; // host: pinned staging
+    void free() { if (dev) (void)hipFree(dev); if (host) (void)hipHostFree(host); dev = host = nullptr; }
+};
+class BankTables {
+  public:
+    hipError_t take(uint32_t sigma, BankTable &t) {
+        int device = 0;
+        hipError_t e = hipGetDevice(&device);
+        if (e != hipSuccess) return e;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            int best = -1;
+            for (size_t i = 0; i < idle_.size(); ++i)
+                if (idle_[i].device == device && (best < 0 || idle_[i].sigma == sigma)) best = (int)i;
+            if (best >= 0 && (idle_[best].sigma == sigma || idle_.size() == BANK_TABLES)) {
+                t = idle_[best];
+                idle_.erase(idle_.begin() + best);
+                return hipSuccess;
+            }
+        }
+        t = BankTable();
+        t.device = device;
+        e = hipMalloc((void **)&t.dev, BANK_TABLE_BYTES);
+        if (e == hipSuccess) e = hipHostMalloc((void **)&t.host, BANK_TABLE_BYTES, hipHostMallocDefault);
+        if (e != hipSuccess) t.free();
+        return e;
+    }
+    void give_back(BankTable &t) {
+        if (!t.dev) return;
+        BankTable oldest;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            static const int at_exit = std::atexit([] { all().clear(); });
+            (void)at_exit;
+            idle_.push_back(t);
+            if (idle_.size() > BANK_TABLES) { oldest = idle_.front(); idle_.erase(idle_.begin()); }
+        }
+        oldest.free();
+    }
+    void clear() {
+        std::lock_guard<std::mutex> lock(mu_);
+        for (BankTable &t : idle_) t.free();
+        idle_.clear();
+    }
+    static BankTables &all() { static BankTables &t = *new BankTables; return t; }   // outlives static destruction
+
+  private:
+    std::mutex mu_;
+    std::vector<BankTable> idle_;   // oldest first
+};
 
 // The constant arguments of the narrow-net ops of the fused plans: block descriptors and per-channel constants packed
 // in the form the kernel stages them, in one device buffer.  `arena` is the host image of the constants at m->dconst.
@@ -584,22 +645,32 @@ int isr_noise_bank(uint32_t sigma, uint64_t seed, uint32_t bank_id, uint32_t fir
     if (sigma < 1 || sigma > 1024 || !out_device || d == 0 || (d & 3) != 0) return ISR_ERR_ARG;
     if ((uint64_t)first + count > (1ull << 32)) return ISR_ERR_ARG;
     if (count == 0) return ISR_OK;
-    std::vector<uint32_t> host;
-    uint32_t n = 0, R = 0;
-    if (!build_bank_table(sigma, host, n, R)) return ISR_ERR_ARG;
     hipStream_t st = (hipStream_t)hip_stream;
-    uint32_t *dev = nullptr;
-    HIP_TRY(hipMalloc((void **)&dev, host.size() * 4));
-    hipError_t e = hipMemcpyAsync(dev, host.data(), host.size() * 4, hipMemcpyHostToDevice, st);
+    BankTable t;
+    hipError_t e = BankTables::all().take(sigma, t);
+    if (e == hipSuccess && t.sigma != sigma) {
+        std::vector<uint32_t> words;
+        uint32_t n = 0;
+        t.sigma = 0;
+        if (!build_bank_table(sigma, words, n, t.R) || words.size() * 4 > BANK_TABLE_BYTES) {
+            BankTables::all().give_back(t);
+            return ISR_ERR_ARG;
+        }
+        t.words = words.size();
+        std::memcpy(t.host, words.data(), t.words * 4);
+        e = hipMemcpyAsync(t.dev, t.host, t.words * 4, hipMemcpyHostToDevice, st);
+    }
     if (e == hipSuccess) {
         NoiseBankParams p;
-        p.thi = dev; p.tlo = dev + n; p.guide = (const uint16_t *)(dev + 2 * n);
-        p.n = (int32_t)n; p.R = (int32_t)R; p.out = out_device; p.d = d;
+        set_bank_table(p, t.dev, t.words, t.R);
+        p.out = out_device; p.d = d;
         p.key0 = (uint32_t)seed; p.key1 = (uint32_t)(seed >> 32); p.bank = bank_id; p.first = first; p.count = count;
         e = launch_noise_bank(p, st);
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(st);   // the staging vector and the table die with this call
-    (void)hipFree(dev);
+    const hipError_t done = hipStreamSynchronize(st);   // the table is handed back with this call
+    if (e == hipSuccess) e = done;
+    t.sigma = e == hipSuccess ? sigma : 0;
+    BankTables::all().give_back(t);
     if (e != hipSuccess) { g_last_hip_error = (int)e; return ISR_ERR_DEVICE; }
     return ISR_OK;
 }

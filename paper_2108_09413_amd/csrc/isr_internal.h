@@ -15,16 +15,26 @@
 namespace isr {
 
 // ---- noise table -----------------------------------------------------------
-constexpr uint32_t NOISE_TABLE_MAX = 512;   // >= 510 thresholds between -255 and 255
-constexpr uint32_t NOISE_GUIDE_BITS = 12;
-constexpr uint32_t NOISE_GUIDE_SIZE = 1u << NOISE_GUIDE_BITS;
-
+// The threshold table T (2R ascending 64-bit values, T[2R - 1 - i] = ~T[i]) in the form of the device samplers.  A uniform
+// u left of the centre draws #{i < R : T[i] <= u} - R, one right of it the mirrored value of ~u.  So with x the high
+// word of u or ~u, whichever is below 2^31, one word of a guide table indexed by the exponent and the leading mantissa bits
+// of float(x) tells the count: buckets get narrower towards the tail with the thresholds, and none holds two.
+//   guide word = lowest index bit (31) | mantissa bits below the index of the bucket's threshold (all ones: none), left-aligned
+//                below it | R - count before the threshold = |draw| left of it (bits 0 .. 13)
+// A mantissa equal to the threshold's, or x below `lo`, is decided by the 64-bit thresholds themselves.
+constexpr uint32_t NOISE_DRAW_MASK = 0x3FFF;  // sigma 1024: R = 8690
+constexpr uint32_t NOISE_HALF_MAX = 256;      // pixels: thresholds of draws -255 .. -1 (saturation makes the rest meet 0 or 255)
+constexpr uint32_t NOISE_GUIDE_MAX = 1920;    // words of a pixel table's guide
+struct NoiseSampler {
+    uint32_t shift, mask;       // byte offset of the guide word = (bits of float(x) >> shift) & mask
+    uint32_t key_shift;         // lowest index bit and the mantissa bits below it, left-aligned = bits << key_shift
+    uint32_t reach;             // thresholds in use: draws are -reach .. reach
+    float lo, hi;               // float(x) is clamped to these
+};
 struct DeviceNoiseTable {
-    uint32_t hi[NOISE_TABLE_MAX];
-    uint32_t lo[NOISE_TABLE_MAX];
-    uint16_t guide[NOISE_GUIDE_SIZE + 2];
-    uint32_t n;      // thresholds in use
-    int32_t dmin;    // delta = dmin + #{j < n : T[j] <= u}
+    NoiseSampler s;
+    uint32_t hi[NOISE_HALF_MAX], lo[NOISE_HALF_MAX];   // high and low words of the thresholds
+    alignas(16) uint32_t guide[NOISE_GUIDE_MAX];
 };
 
 bool build_noise_table(uint32_t sigma, std::vector<uint64_t> &T, uint32_t &R);
@@ -34,8 +44,11 @@ struct NoiseTable {
 };
 // Shared, immutable table of a sigma (built on first use); null for sigma outside 1..1024.
 std::shared_ptr<const NoiseTable> cached_noise_table(uint32_t sigma);
-// Table of the stored-noise generator as one block of 32-bit words: n high words, n low words, guide table.
+// Table of the stored-noise generator as one block of 32-bit words: guide table, n = R high words, n low words.
 bool build_bank_table(uint32_t sigma, std::vector<uint32_t> &words, uint32_t &n_out, uint32_t &R_out);
+struct NoiseBankParams;
+// The table arguments of a launch from such a block in device memory (16-byte aligned).
+void set_bank_table(NoiseBankParams &p, const uint32_t *dev, size_t words, uint32_t R);
 // Records the hipError_t that isr_last_device_error() reports on this thread.
 void set_last_device_error(int hip_error);
 bool build_device_table(uint32_t sigma, DeviceNoiseTable &out);
@@ -303,9 +316,10 @@ struct NoiseParams {
 
 // Stored-noise generator: count tensors of d draws each, int16.
 struct NoiseBankParams {
-    const uint32_t *thi, *tlo;   // [n] high / low words of the ascending thresholds (device)
-    const uint16_t *guide;       // [NOISE_GUIDE_SIZE + 2]: #{j : thi[j] < (b << (32 - NOISE_GUIDE_BITS))} (device)
-    int32_t n, R;                // n = 2R thresholds; draw = #{j : T[j] <= u} - R
+    const uint32_t *thi, *tlo;   // [s.reach] high / low words of the ascending thresholds below the centre (device)
+    const uint32_t *guide;       // guide table (device)
+    uint32_t guide_words;
+    NoiseSampler s;
     int16_t *out;                // [count][d]
     uint32_t d;                  // draws per tensor, a multiple of 4
     uint32_t key0, key1, bank, first, count;

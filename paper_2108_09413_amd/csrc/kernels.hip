@@ -16,7 +16,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 // The low half is generated only when the high word ties with a threshold.
 
 __global__ __launch_bounds__(256) void noise_kernel(const NoiseParams p) {
-    __shared__ NoiseLds t;
+    __shared__ __attribute__((aligned(16))) NoiseLds t;
     // what this workgroup draws: one image, one table, a range of sample indices, a range of output copies
     const uint8_t *xim = p.x;
     const DeviceNoiseTable *tab = p.table;
@@ -36,8 +36,7 @@ __global__ __launch_bounds__(256) void noise_kernel(const NoiseParams p) {
         out_copy0 = (long)(lo - p.slot_begin);
     }
     stage_noise_table(t, tab, threadIdx.x, 256);
-    const int n = (int)tab->n;
-    const int dmin = tab->dmin;
+    const NoiseSampler smp = tab->s;
     __syncthreads();
 
     const int W4 = p.W >> 2;
@@ -49,7 +48,7 @@ __global__ __launch_bounds__(256) void noise_kernel(const NoiseParams p) {
         const int y = rem / W4, x4 = rem - y * W4;
         const uint32_t sample = sample_begin + s_local;
         uint32_t packed[4];
-        noisy_quad(t, n, dmin, xim, p.C, p.H, p.W, y, x4, sample, image_id, p.phase, p.key0, p.key1, packed);
+        noisy_quad(t, smp, tab, xim, p.C, p.H, p.W, y, x4, sample, image_id, p.phase, p.key0, p.key1, packed);
         v4i o = {(int)packed[0], (int)packed[1], (int)packed[2], (int)packed[3]};
         *(v4i *)(p.out + ((out_copy0 + s_local) * groups_per_sample + rem) * 16) = o;
     }
@@ -77,70 +76,46 @@ hipError_t launch_noise(const NoiseParams &p, hipStream_t st) {
 // ---------------------------------------------------------------------------
 // Noise bank: the discrete-Gaussian draws themselves (no image, no saturation), int16, for
 // noise that is sampled ahead of training and stored.  Same generator and counter layout as
-// above with the tensor index in the sample word, the bank id in the image word and phase 2;
-// the whole threshold table (2R entries) is searched, bucketed by a guide table on the top
-// 12 bits; the guide and the high words are staged into LDS (dynamic, 4 bytes per threshold),
-// the low words stay in global memory (read on a tie of the high words only).
-
-// #{j < n : T[j] <= u} when the guide bucket of u holds more than one candidate or the high
-// word ties with a threshold (rare): binary search inside the bucket, then the low words.
-__device__ __noinline__ int bank_count_slow(const uint32_t *thi_s, const uint16_t *guide, const NoiseBankParams &p,
-                                            uint32_t u, uint32_t grp, uint32_t tensor, int word) {
-    const uint32_t b = u >> (32 - NOISE_GUIDE_BITS);
-    int a = guide[b], e = guide[b + 1];              // thresholds with a high word below u end before guide[b + 1]
-    while (a < e) {                                  // first index whose high word is >= u
-        const int mid = (a + e) >> 1;
-        if (thi_s[mid] < u) a = mid + 1; else e = mid;
-    }
-    int c = a;
-    if (c < p.n && thi_s[c] == u) {                  // equal high words: the low words decide
-        uint32_t lo[4];
-        philox4x32_10(grp, tensor, p.bank, 5u, p.key0, p.key1, lo);
-        while (c < p.n && thi_s[c] == u && p.tlo[c] <= lo[word & 3]) ++c;
-    }
-    return c;
-}
-
-__global__ __launch_bounds__(256) void noise_bank_kernel(const NoiseBankParams p) {
-    __shared__ uint16_t guide[NOISE_GUIDE_SIZE + 2];
-    extern __shared__ uint32_t thi_s[];              // n high words, then two entries of 0xFFFFFFFF
-    for (int i = threadIdx.x; i < (int)(NOISE_GUIDE_SIZE + 2) / 2; i += 256)
-        ((uint32_t *)guide)[i] = ((const uint32_t *)p.guide)[i];
-    for (int i = threadIdx.x; i < p.n + 2; i += 256) thi_s[i] = i < p.n ? p.thi[i] : 0xFFFFFFFFu;
+// above with the tensor index in the sample word, the bank id in the image word and phase 2.  The guide table (7.5 KB up
+// to sigma 86, 57 KB at sigma 1024) is staged into LDS; the thresholds stay in memory, for the few draws that it leaves open.
+//
+// Bound by the issue of the generator's and the sampler's integer arithmetic, about 100 instructions per four draws (two
+// blocks at a time, for more independent instructions, measured the same).  A search in buckets of equal width left a
+// wave in three (sigma 32) or nearly every one (sigma 256) a draw in the tail to search for, and divided 64-bit indices per
+// draw: 50 000 x 3072 draws took 212 us at sigma 32 and 280 at sigma 1000, now 129 and 145.
+__global__ __launch_bounds__(1024) void noise_bank_kernel(const NoiseBankParams p) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t guide[];
+    const uint32_t threads = blockDim.x;
+    for (uint32_t i = threadIdx.x; i < p.guide_words / 4; i += threads) ((uint4 *)guide)[i] = ((const uint4 *)p.guide)[i];
     __syncthreads();
-    const uint64_t groups_per_tensor = p.d >> 2, total = groups_per_tensor * p.count;
-    for (uint64_t g = (uint64_t)blockIdx.x * 256 + threadIdx.x; g < total; g += (uint64_t)gridDim.x * 256) {
-        const uint32_t t = (uint32_t)(g / groups_per_tensor), grp = (uint32_t)(g - (uint64_t)t * groups_per_tensor);
-        const uint32_t tensor = p.first + t;
-        uint32_t hi[4];
-        philox4x32_10(grp, tensor, p.bank, 4u, p.key0, p.key1, hi);
-        int d4[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t u = hi[j];
-            int c = guide[u >> (32 - NOISE_GUIDE_BITS)];
-            const uint32_t t0 = thi_s[c], t1 = thi_s[c + 1];
-            c += t0 < u;
-            // common case: at most one threshold below u in the bucket and no tie
-            if ((t0 < u ? t1 : t0) <= u) c = bank_count_slow(thi_s, guide, p, u, grp, tensor, j);
-            d4[j] = c - p.R;
-        }
-        const uint32_t w0 = (uint32_t)(d4[0] & 0xFFFF) | ((uint32_t)d4[1] << 16), w1 = (uint32_t)(d4[2] & 0xFFFF) | ((uint32_t)d4[3] << 16);
-        *(uint2 *)(p.out + ((uint64_t)t * p.d + 4ull * grp)) = make_uint2(w0, w1);
+    const uint32_t groups_per_tensor = p.d >> 2;
+    const uint64_t total = (uint64_t)groups_per_tensor * p.count, step = (uint64_t)gridDim.x * threads;
+    const uint32_t dt = (uint32_t)(step / groups_per_tensor), dg = (uint32_t)(step % groups_per_tensor);
+    uint64_t g = (uint64_t)blockIdx.x * threads;
+    uint32_t t = (uint32_t)((g + threadIdx.x) / groups_per_tensor), grp = (uint32_t)(g + threadIdx.x - (uint64_t)t * groups_per_tensor);
+    for (; g < total; g += step) {   // uniform
+        int d[4];
+        noise_draw4(guide, p.s, p.thi, p.tlo, grp, p.first + t, p.bank, 4u, p.key0, p.key1, d);
+        const uint32_t w0 = __builtin_amdgcn_perm((uint32_t)d[1], (uint32_t)d[0], 0x05040100u), w1 = __builtin_amdgcn_perm((uint32_t)d[3], (uint32_t)d[2], 0x05040100u);
+        if (threadIdx.x < total - g) ((uint2 *)(p.out + 4 * g))[threadIdx.x] = make_uint2(w0, w1);
+        t += dt;
+        grp += dg;
+        if (grp >= groups_per_tensor) { grp -= groups_per_tensor; ++t; }
     }
 }
 
 hipError_t launch_noise_bank(const NoiseBankParams &p, hipStream_t st) {
     if (p.count == 0) return hipSuccess;
-    if (p.d == 0 || (p.d & 3) != 0 || p.n < 2 || p.n > 32768 || !p.thi || !p.tlo || !p.guide || !p.out) return hipErrorInvalidValue;
+    if (p.d == 0 || (p.d & 3) != 0 || p.s.reach < 1 || p.s.reach > 16384 || !p.thi || !p.tlo || !p.guide || !p.out) return hipErrorInvalidValue;
+    const size_t lds = (size_t)p.guide_words * 4;
+    if (lds <= (p.s.mask >> 1) || lds > 64 * 1024 || (p.guide_words & 3)) return hipErrorInvalidValue;   // the index's leading exponent bit is set for the largest x
+    // the waves of a workgroup share a guide: large ones where eight workgroups' guides would not fit a CU
+    const unsigned threads = lds > 16 * 1024 ? 1024 : 256;
     const uint64_t total = (uint64_t)(p.d >> 2) * p.count;
-    uint64_t blocks = (total + 255) / 256;
-    if (blocks > 256 * 8) blocks = 256 * 8;
-    const size_t lds = ((size_t)p.n + 2) * 4;   // at most 128 KiB plus the 8 KiB guide: within the 160 KiB of a CU (sigma 1024 needs 72 KiB)
-    hipError_t e = hipFuncSetAttribute((const void *)noise_bank_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    uint64_t blocks = (total + threads - 1) / threads;
+    if (blocks > 256 * (2048 / threads)) blocks = 256 * (2048 / threads);   // a full chip
     set_kernel_name("noise_bank_kernel");
-    hipLaunchKernelGGL(noise_bank_kernel, dim3((unsigned)blocks), dim3(256), lds, st, p);
+    hipLaunchKernelGGL(noise_bank_kernel, dim3((unsigned)blocks), dim3(threads), lds, st, p);
     return hipGetLastError();
 }
 

@@ -377,9 +377,9 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
                 uint32_t image_id, sample;
                 resolve_noise_source(p.noise, img0, xim, src, image_id, sample);
                 stage_noise_table(*tab, src, tid, 256);
-                const int n = (int)src->n, dmin = src->dmin;
+                const NoiseSampler smp = src->s;
                 lds_barrier();
-                noisy_quad(*tab, n, dmin, xim, p.noise.C, S, S, y, x4, sample, image_id, p.noise.phase, p.noise.key0, p.noise.key1, v);
+                noisy_quad(*tab, smp, src, xim, p.noise.C, S, S, y, x4, sample, image_id, p.noise.phase, p.noise.key0, p.noise.key1, v);
             } else {
                 const v4i w = *(const v4i *)(p.in + ((img0 * S + y) * S + 4 * x4) * 4);
 #pragma unroll

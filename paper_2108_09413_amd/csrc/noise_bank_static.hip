@@ -9,8 +9,8 @@
 
 namespace {
 
-// Room for the table of every sigma up to about 420 grid units (8 bytes per threshold, 2R = about
-// 18 sigma thresholds, plus the 8200-byte guide table).  Every GPU the library runs on holds its
+// Room for the table of every sigma up to about 500 grid units (8 bytes per threshold, R = about
+// 9 sigma thresholds, plus a guide table of 7.5 to 28 KB).  Every GPU the library runs on holds its
 // own copy of this array until the process ends.
 constexpr size_t SCRATCH_BYTES = 64 * 1024;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
@@ -56,13 +56,12 @@ extern "C" int isr_noise_bank_static(uint32_t sigma, uint64_t seed, uint32_t ban
     hipError_t e = scratch_address(&ptr);
     hipStream_t st = (hipStream_t)hip_stream;
     // every call on this GPU writes the same array: the whole table of this sigma replaces what
-    // the last call left (the kernel reads n entries and the guide, nothing beyond)
+    // the last call left (the kernel reads n thresholds and the guide, nothing beyond)
     if (e == hipSuccess) e = hipMemcpyAsync(ptr, host.data(), host.size() * 4, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) {
-        uint32_t *dev = (uint32_t *)ptr;
         NoiseBankParams p;
-        p.thi = dev; p.tlo = dev + n; p.guide = (const uint16_t *)(dev + 2 * n);
-        p.n = (int32_t)n; p.R = (int32_t)R; p.out = out_device; p.d = d;
+        set_bank_table(p, (const uint32_t *)ptr, host.size(), R);
+        p.out = out_device; p.d = d;
         p.key0 = (uint32_t)seed; p.key1 = (uint32_t)(seed >> 32); p.bank = bank_id; p.first = first; p.count = count;
         e = launch_noise_bank(p, st);
     }

@@ -11,15 +11,17 @@
 
 namespace isr {
 
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
+
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                               uint32_t k0, uint32_t k1, uint32_t out[4]) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         uint64_t p0 = (uint64_t)0xD2511F53u * c0;   // one 32x32->64 multiply gives both halves
         uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-        c0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
+        c0 = xor3((uint32_t)(p1 >> 32), c1, k0);
         c1 = (uint32_t)p1;
-        c2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+        c2 = xor3((uint32_t)(p0 >> 32), c3, k1);
         c3 = (uint32_t)p0;
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
@@ -27,73 +29,90 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
     out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
-struct NoiseLds {
-    uint32_t hi[NOISE_TABLE_MAX + 2];   // entries >= n hold 0xFFFFFFFF
-    uint32_t lo[NOISE_TABLE_MAX];
-    uint16_t guide[NOISE_GUIDE_SIZE + 2];
-};
-
-// #{j < n : T[j] <= u} when the guide bucket holds more than one candidate or the
-// high word ties with a threshold: binary search inside the bucket, then the
-// 64-bit comparison for the (rare) equal high words.
-__device__ __noinline__ int threshold_count_slow(const NoiseLds &t, int n, uint32_t uhi, uint32_t grp,
-                                                 uint32_t sample, uint32_t image, uint32_t phase, uint32_t key0,
-                                                 uint32_t key1, int word) {
-    const uint32_t b = uhi >> (32 - NOISE_GUIDE_BITS);
-    int lo = t.guide[b], hi = t.guide[b + 1];    // every threshold with high word < uhi lies below guide[b+1]
-    while (lo < hi) {                             // first index whose high word is >= uhi
-        int mid = (lo + hi) >> 1;
-        if (t.hi[mid] < uhi) lo = mid + 1; else hi = mid;
+// The draw of a high word u that the guide word does not decide: x = u or ~u meets threshold `base`, or lies below all buckets
+// (thresholds 0 .. base there).  Binary search for the first high word not below x, then the low words.
+__device__ __noinline__ int noise_draw_slow(const uint32_t *thi, const uint32_t *tlo, const NoiseSampler &s, uint32_t u, uint32_t base,
+                                            uint32_t grp, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t key0, uint32_t key1, int word) {
+    const bool right = (int)u < 0;
+    const uint32_t x = right ? ~u : u;
+    uint32_t a = (float)x <= s.lo ? 0 : base, e = base + 1;
+    if (e > s.reach) e = s.reach;
+    while (a < e) {
+        const uint32_t mid = (a + e) >> 1;
+        if (thi[mid] < x) a = mid + 1; else e = mid;
     }
-    int c = lo;
-    if (c < n && t.hi[c] == uhi) {
+    if (a < s.reach && thi[a] == x) {
         uint32_t lo4[4];
-        philox4x32_10(grp, sample, image, phase * 2u + 1u, key0, key1, lo4);
-        const uint32_t ulo = lo4[word & 3];
-        while (c < n && t.hi[c] == uhi && t.lo[c] <= ulo) ++c;
+        philox4x32_10(grp, c1, c2, c3 + 1, key0, key1, lo4);
+        uint32_t ulo = lo4[0];
+        if (word == 1) ulo = lo4[1];
+        if (word == 2) ulo = lo4[2];
+        if (word == 3) ulo = lo4[3];
+        if (right) ulo = ~ulo;
+        // left of the centre a threshold equal to u counts, the mirrored one of the right does not
+        while (a < s.reach && thi[a] == x && (right ? tlo[a] < ulo : tlo[a] <= ulo)) ++a;
     }
-    return c;
+    const int d = (int)a - (int)s.reach;
+    return right ? -d : d;
 }
+
+// The four draws of the Philox block of counter (grp, c1, c2, c3).  A draw is one LDS read and about a dozen instructions: the
+// difference of its guide word and its own mantissa bits tells by the sign on which side of the bucket's threshold it lies,
+// and by a small value that this is open.
+__device__ __forceinline__ void noise_draw4(const uint32_t *guide, const NoiseSampler &s, const uint32_t *thi, const uint32_t *tlo,
+                                            uint32_t grp, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t key0, uint32_t key1, int (&d)[4]) {
+    uint32_t u[4], t[4], e[4];
+    philox4x32_10(grp, c1, c2, c3, key0, key1, u);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int right = (int)u[j] >> 31;
+        const uint32_t bits = __float_as_uint(__builtin_amdgcn_fmed3f((float)(u[j] ^ (uint32_t)right), s.lo, s.hi));
+        e[j] = *(const uint32_t *)((const uint8_t *)guide + ((bits >> s.shift) & s.mask));
+        t[j] = e[j] - (bits << s.key_shift);
+        const int m = (int)(e[j] & NOISE_DRAW_MASK) + ((int)t[j] >> 31);   // |draw|
+        d[j] = right - (m ^ right);
+    }
+    if (min(min(t[0], t[1]), min(t[2], t[3])) <= NOISE_DRAW_MASK) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (t[j] <= NOISE_DRAW_MASK)
+                d[j] = noise_draw_slow(thi, tlo, s, u[j], s.reach - (e[j] & NOISE_DRAW_MASK), grp, c1, c2, c3, key0, key1, j);
+    }
+}
+
+struct NoiseLds {
+    uint32_t guide[NOISE_GUIDE_MAX];
+};
 
 // Stages a table into LDS (all threads of the workgroup; followed by a barrier at the caller).
 __device__ __forceinline__ void stage_noise_table(NoiseLds &t, const DeviceNoiseTable *tab, int tid, int nthreads) {
-    for (int i = tid; i < (int)NOISE_TABLE_MAX; i += nthreads) {
-        t.hi[i] = tab->hi[i];
-        t.lo[i] = tab->lo[i];
-    }
-    if (tid < 2) t.hi[NOISE_TABLE_MAX + tid] = 0xFFFFFFFFu;
-    for (int i = tid; i < (int)(NOISE_GUIDE_SIZE + 2) / 2; i += nthreads)   // two 16-bit entries per word
-        ((uint32_t *)t.guide)[i] = ((const uint32_t *)tab->guide)[i];
+    for (int i = tid; i < (int)NOISE_GUIDE_MAX / 4; i += nthreads) ((uint4 *)t.guide)[i] = ((const uint4 *)tab->guide)[i];
 }
 
 // Four horizontally adjacent noisy pixels (x4 * 4 .. x4 * 4 + 3 of row y) of one copy as NHWC4 words:
 // byte c of word j = clamp(x[c][y][4 x4 + j] + delta, 0, 255) - 128, byte 3 = 0.
-__device__ __forceinline__ void noisy_quad(const NoiseLds &t, int n, int dmin, const uint8_t *xim, int C, int H, int W, int y,
-                                           int x4, uint32_t sample, uint32_t image_id, uint32_t phase, uint32_t key0,
+__device__ __forceinline__ void noisy_quad(const NoiseLds &t, const NoiseSampler &s, const DeviceNoiseTable *tab, const uint8_t *xim, int C, int H,
+                                           int W, int y, int x4, uint32_t sample, uint32_t image_id, uint32_t phase, uint32_t key0,
                                            uint32_t key1, uint32_t packed[4]) {
-    packed[0] = packed[1] = packed[2] = packed[3] = 0;
+    int v[3][4];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[c][j] = 128;   // channels the image has not hold 0 after the recentring
         if (c < C) {
             const uint32_t pix = (uint32_t)((c * H + y) * W + x4 * 4);   // multiple of 4
-            const uint32_t grp = pix >> 2;
-            uint32_t hi[4];
-            philox4x32_10(grp, sample, image_id, phase * 2u, key0, key1, hi);
             const uint32_t px4 = *(const uint32_t *)(xim + pix);
+            noise_draw4(t.guide, s, tab->hi, tab->lo, pix >> 2, sample, image_id, phase * 2u, key0, key1, v[c]);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t u = hi[j];
-                int cnt = t.guide[u >> (32 - NOISE_GUIDE_BITS)];
-                const uint32_t t0 = t.hi[cnt], t1 = t.hi[cnt + 1];
-                cnt += t0 < u;
-                // common case: at most one threshold below u in the bucket and no tie
-                if ((t0 < u ? t1 : t0) <= u)
-                    cnt = threshold_count_slow(t, n, u, grp, sample, image_id, phase, key0, key1, j);
-                int v = (int)((px4 >> (8 * j)) & 0xFF) + dmin + cnt;
-                v = (v < 0 ? 0 : (v > 255 ? 255 : v)) - 128;
-                packed[j] |= (uint32_t)(v & 0xFF) << (8 * c);
-            }
+            for (int j = 0; j < 4; ++j) v[c][j] += (int)((px4 >> (8 * j)) & 0xFF);
         }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {   // saturation of two 16-bit values to bytes at once
+        uint32_t lo = __builtin_amdgcn_perm((uint32_t)v[1][j], (uint32_t)v[0][j], 0x05040100u), hi = (uint32_t)v[2][j];
+        asm("v_sat_pk_u8_i16 %0, %1" : "=v"(lo) : "v"(lo));
+        asm("v_sat_pk_u8_i16 %0, %1" : "=v"(hi) : "v"(hi));
+        packed[j] = ((hi << 16) | lo) ^ 0x00808080u;
     }
 }
 

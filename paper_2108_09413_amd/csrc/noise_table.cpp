@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <cstring>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -67,55 +68,110 @@ std::shared_ptr<const NoiseTable> cached_noise_table(uint32_t sigma) {
     return t;
 }
 
+namespace {
+
+uint32_t float_bits(uint32_t x) {
+    const float f = (float)x;   // to nearest, as the device converts
+    uint32_t b;
+    std::memcpy(&b, &f, 4);
+    return b;
+}
+
+// Guide tables: `mant` leading mantissa bits and the low `expo` exponent bits make the index; the exponent of the
+// largest x is 157 and `first`, that of the lowest buckets, differs from it in those bits only.
+struct GuideShape {
+    uint32_t mant, expo, first;
+    size_t words() const { return (size_t)((157u & ((1u << expo) - 1)) + 1) << mant; }
+};
+// More buckets per octave as sigma grows.  Five exponent bits put x below `lo` at 2^-21 of the draws; tables of the large
+// sigmas keep to four (57 KB of LDS at sigma 1024, x below 2^18 in 2^-13 of the draws).
+const GuideShape BANK_SHAPES[] = {{6, 5, 137}, {7, 5, 137}, {8, 5, 137}, {9, 4, 145}, {10, 4, 145}};
+// Pixels need the thresholds of draws within 255 only: a large sigma has none far out in the tail.
+const GuideShape PIXEL_SHAPES[] = {{6, 5, 137}, {7, 4, 144}, {8, 3, 152}, {9, 2, 156}, {10, 0, 157}};
+
+// The largest float below the lowest buckets' exponent: x below them is clamped to it.  Where there are thresholds down
+// there, its guide word holds a threshold of the same mantissa, and the draw is looked up.
+float floor_of(const GuideShape &g) { return std::nextafter(std::ldexp(1.0f, (int)g.first - 127), 0.0f); }
+bool has_below(const GuideShape &g, const uint64_t *T, uint32_t reach) {
+    return reach && float_bits((uint32_t)(T[0] >> 32)) < g.first << 23;
+}
+
+NoiseSampler sampler_of(const GuideShape &g, uint32_t reach, bool below) {
+    NoiseSampler s;
+    s.shift = 21 - g.mant;
+    s.mask = ((1u << (g.mant + g.expo)) - 1) << 2;
+    s.key_shift = 8 + g.mant;
+    s.reach = reach;
+    s.lo = below ? floor_of(g) : std::ldexp(1.0f, (int)g.first - 127);
+    s.hi = std::nextafter(std::ldexp(1.0f, 31), 0.0f);
+    return s;
+}
+
+// false: two thresholds in one bucket
+bool fill_guide(const GuideShape &g, const uint64_t *T, uint32_t reach, uint32_t *guide) {
+    const uint32_t rest = 23 - g.mant, index_mask = (1u << (g.mant + g.expo)) - 1, ones = (1u << rest) - 1;
+    auto bits = [&](uint32_t j) { return float_bits((uint32_t)(T[j] >> 32)); };
+    auto put = [&](uint32_t bucket, uint32_t thr, uint32_t count) {
+        guide[bucket & index_mask] = bucket << 31 | thr << (8 + g.mant) | (reach - count);
+    };
+    for (size_t i = 0; i < g.words(); ++i) guide[i] = 0;
+    uint32_t j = 0;
+    while (j < reach && bits(j) < g.first << 23) ++j;
+    if (j) {
+        const uint32_t b = (g.first << g.mant) - 1;   // the bucket of floor_of
+        if ((b & index_mask) >= g.words()) return false;
+        put(b, ones, j - 1);
+    }
+    for (uint32_t b = g.first << g.mant; b < 158u << g.mant; ++b) {
+        const uint32_t count = j;
+        uint32_t thr = ones;
+        if (j < reach && bits(j) >> rest == b) thr = bits(j++) & ones;
+        if (j < reach && bits(j) >> rest == b) return false;
+        put(b, thr, count);
+    }
+    return j == reach;
+}
+
+}  // namespace
+
 // Device form.  Pixels lie in [0, 255], so after saturation only
-// clamp(delta, -255, 255) matters: keep the (at most 510) thresholds between
-// -255 and 255, split into high/low words, plus a guide table on the top
-// GUIDE_BITS bits of the high word: guide[b] = #{j : hi[j] < (b << (32-GUIDE_BITS))}.
+// clamp(delta, -255, 255) matters: keep the thresholds between -255 and 255.
 bool build_device_table(uint32_t sigma, DeviceNoiseTable &out) {
     const auto tab = cached_noise_table(sigma);
     if (!tab) return false;
-    const std::vector<uint64_t> &T = tab->T;
-    const uint32_t R = tab->R;
-    uint32_t reach = R < 255 ? R : 255;
-    uint32_t first = R - reach;
-    uint32_t n = 2 * reach;
-    out.n = n;
-    out.dmin = -(int32_t)reach;
-    for (uint32_t j = 0; j < NOISE_TABLE_MAX; ++j) {
-        uint64_t t = j < n ? T[first + j] : ~0ull;
-        out.hi[j] = (uint32_t)(t >> 32);
-        out.lo[j] = (uint32_t)t;
-    }
-    uint32_t j = 0;
-    for (uint32_t b = 0; b <= NOISE_GUIDE_SIZE; ++b) {
-        uint64_t start = (uint64_t)b << (32 - NOISE_GUIDE_BITS);
-        while (j < n && (uint64_t)out.hi[j] < start) ++j;
-        out.guide[b] = (uint16_t)j;
-    }
-    return true;
+    const uint32_t reach = tab->R < 255 ? tab->R : 255;
+    const uint64_t *T = tab->T.data() + (tab->R - reach);
+    std::memset(&out, 0, sizeof(out));
+    for (uint32_t j = 0; j < reach; ++j) { out.hi[j] = (uint32_t)(T[j] >> 32); out.lo[j] = (uint32_t)T[j]; }
+    for (const GuideShape &g : PIXEL_SHAPES)
+        if (g.words() <= NOISE_GUIDE_MAX && fill_guide(g, T, reach, out.guide)) { out.s = sampler_of(g, reach, has_below(g, T, reach)); return true; }
+    return false;
 }
 
-// Form read by the stored-noise generator, as 32-bit words so that one upload carries all:
-// n high words, n low words, then the guide table (NOISE_GUIDE_SIZE + 2 entries of 16 bits) on
-// the top bits of the high word over all n = 2R thresholds.
 bool build_bank_table(uint32_t sigma, std::vector<uint32_t> &words, uint32_t &n_out, uint32_t &R_out) {
     const auto tab = cached_noise_table(sigma);
     if (!tab) return false;
-    const std::vector<uint64_t> &T = tab->T;
-    const size_t n = T.size();
-    const size_t guide_words = (NOISE_GUIDE_SIZE + 2) / 2;
-    words.assign(2 * n + guide_words, 0);
-    for (size_t j = 0; j < n; ++j) { words[j] = (uint32_t)(T[j] >> 32); words[n + j] = (uint32_t)T[j]; }
-    uint16_t *guide = (uint16_t *)(words.data() + 2 * n);
-    size_t j = 0;
-    for (uint32_t b = 0; b <= NOISE_GUIDE_SIZE; ++b) {
-        const uint64_t start = (uint64_t)b << (32 - NOISE_GUIDE_BITS);
-        while (j < n && (uint64_t)words[j] < start) ++j;
-        guide[b] = (uint16_t)j;
+    const uint64_t *T = tab->T.data();
+    const size_t R = tab->R;
+    for (const GuideShape &g : BANK_SHAPES) {
+        words.assign(2 * R + g.words(), 0);
+        if (!fill_guide(g, T, (uint32_t)R, words.data())) continue;
+        uint32_t *hi = words.data() + g.words(), *lo = hi + R;
+        for (size_t j = 0; j < R; ++j) { hi[j] = (uint32_t)(T[j] >> 32); lo[j] = (uint32_t)T[j]; }
+        n_out = R_out = (uint32_t)R;
+        return true;
     }
-    n_out = (uint32_t)n;
-    R_out = tab->R;
-    return true;
+    return false;
+}
+
+void set_bank_table(NoiseBankParams &p, const uint32_t *dev, size_t words, uint32_t R) {
+    p.guide = dev;
+    p.guide_words = (uint32_t)(words - 2 * (size_t)R);
+    p.thi = dev + p.guide_words;
+    p.tlo = p.thi + R;
+    p.s = {};
+    for (const GuideShape &g : BANK_SHAPES)
+        if (g.words() == p.guide_words) p.s = sampler_of(g, R, true);   // the lowest thresholds are below all buckets
 }
 
 }  // namespace isr

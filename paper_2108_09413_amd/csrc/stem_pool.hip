@@ -38,7 +38,7 @@ __global__ __launch_bounds__(256, 3) void stem_pool_kernel(const StemPoolParams 
     __shared__ __attribute__((aligned(16))) int8_t Wl[64 * SP_KP];
     __shared__ __attribute__((aligned(16))) int8_t In[SP_IN_BYTES];
     __shared__ int prm[4][64];
-    __shared__ NoiseLds ntab;                 // the sampler's table when the kernel draws its own input
+    __shared__ __attribute__((aligned(16))) NoiseLds ntab;                 // the sampler's table when the kernel draws its own input
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nstrips = (p.Wp + SP_STRIP - 1) / SP_STRIP;       // 1 or 2 (checked by the launcher)
@@ -67,13 +67,13 @@ __global__ __launch_bounds__(256, 3) void stem_pool_kernel(const StemPoolParams 
         uint32_t image_id, sample;
         resolve_noise_source(p.noise, b, xim, tab, image_id, sample);
         stage_noise_table(ntab, tab, tid, 256);
-        const int n = (int)tab->n, dmin = tab->dmin;
+        const NoiseSampler smp = tab->s;
         __syncthreads();
         for (int i = tid; i < IR * wchunks; i += 256) {
             const int r = i / wchunks, c = i - r * wchunks, iy = iy0 + r;
             uint32_t v[4] = {zb, zb, zb, zb};
             if ((unsigned)iy < (unsigned)p.H)
-                noisy_quad(ntab, n, dmin, xim, p.noise.C, p.H, p.W, iy, c, sample, image_id, p.noise.phase, p.noise.key0, p.noise.key1, v);
+                noisy_quad(ntab, smp, tab, xim, p.noise.C, p.H, p.W, iy, c, sample, image_id, p.noise.phase, p.noise.key0, p.noise.key1, v);
             int *dst = (int *)(&In[(r * PW + 3 + 4 * c) * 4]);
             dst[0] = (int)v[0]; dst[1] = (int)v[1]; dst[2] = (int)v[2]; dst[3] = (int)v[3];
         }

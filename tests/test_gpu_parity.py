@@ -92,6 +92,21 @@ def test_stored_training_noise_bank(isr, sigma):
     assert isr.lib().isr_noise_bank(sigma, ctypes.c_uint64(0), 0, 0, 1, 8, None, None) == isr.ISR_ERR_ARG
 
 
+@pytest.mark.parametrize("sigma", [44, 88, 175, 343, 800])
+def test_sampler_guide_tables_of_every_resolution(isr, sigma):
+    """One sigma for each number of buckets per octave of the guide tables, enough draws that some meet a threshold's
+    leading bits and (large sigma) some lie below all buckets: stored draws and noisy pixels, bit-exact."""
+    _say(f"sampler tables sigma={sigma}")
+    got = isr.isr_noise_bank(sigma, 77, 3, 5, 70, 3 * 32 * 32).cpu().numpy()
+    assert np.array_equal(got, oracle.noise_bank(sigma, 77, 3, 5, 70, 3 * 32 * 32))
+    m = _load(isr, synth.build_model(0), 32)
+    x = synth.make_image(0, 1)
+    got = isr.isr_debug_noisy(m, x, sigma, 78, 9, 0, 3, 32)
+    for s in range(32):
+        assert np.array_equal(got[s], oracle.noisy(x, sigma, 78, 9, 0, 3 + s))
+    m.close()
+
+
 @pytest.mark.parametrize("sigma", [2, 32])
 def test_device_sampler_law_at_scale(isr, sigma):
     """1.5e8 draws of the device sampler (a full stored-noise bank) against Def. 3.3 itself:
