@@ -223,26 +223,16 @@ int build_narrow_ops(isr_model *m, const ConstArena &arena) {
     return ISR_OK;
 }
 
-// A batched call: items (device array) that own n_per_item consecutive slots each.
-struct BatchCtx {
-    const NoiseItem *items;
-    uint32_t n_items, n_per_item;
-};
-
-// Enqueues the Monte-Carlo loop for sample indices [begin, begin+count) of one
-// phase.  Optional outputs: per-sample logits / argmax (device buffers inside
-// the workspace, copied to the host pointers chunk by chunk) and the device
-// vote counters.  stop_tensor >= 0 ends each forward right after that tensor.
-// With `bc` the loop runs over the n_items * n_per_item slots of a batch instead
-// (x = the image array, table = the table array, dcounts = [items][classes];
-// image / begin / count are ignored): chunks are cut from the slot list without
-// regard to item boundaries, so short per-item runs still fill the device.
-int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseTable *table, uint64_t seed,
-              uint32_t image, uint32_t phase, uint32_t begin, uint64_t count, int32_t *logits_host,
-              int32_t *argmax_host, uint32_t *dcounts, int stop_tensor, const BatchCtx *bc = nullptr) {
+// Enqueues the Monte-Carlo loop over the slots of a call.  Optional outputs: per-sample logits / argmax (device
+// buffers inside the workspace, copied to the host pointers chunk by chunk) and the device vote counters,
+// [phases][pairs][classes].  stop_tensor >= 0 ends each forward right after that tensor.  Chunks are cut from the slot list
+// without regard to the boundaries of pairs and phases, so short runs still fill the device.
+int run_slots(isr_model *m, const Plan &pl, const Draw &draw, int32_t *logits_host, int32_t *argmax_host, uint32_t *dcounts,
+              int stop_tensor) {
     const ParsedModel &pm = m->pm;
     uint8_t *ws = m->ws;
-    if (bc) count = (uint64_t)bc->n_items * bc->n_per_item;
+    Slots slots = draw.slots;
+    const uint64_t count = slots.split + (uint64_t)slots.pairs * slots.n[1];
     // bytes of one copy of a tensor: copies are contiguous, so a range of copies of a chunk is a sub-chunk
     auto tptr = [&](int t, uint32_t first_copy) -> uint8_t * {
         const TensorDesc &d = pm.tensors[t];
@@ -256,7 +246,6 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
     }
     for (uint64_t done = 0; done < count;) {
         uint32_t cnt = (uint32_t)std::min<uint64_t>(per_chunk, count - done);
-        if (bc) cnt = (uint32_t)std::min<uint64_t>(cnt, (uint64_t)bc->n_per_item * 65534);   // one grid row per item
         const bool timed = m->profile_every && (m->chunk_counter++ % m->profile_every) == 0;
         size_t ev = 0;
         auto mark = [&]() -> int {   // event before a launch / after the last one
@@ -273,42 +262,50 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
         std::vector<Work> ev_work;   // per timed launch: the kernel instance and its algorithmic work
         int prc;
 
-        // copies [j0, j0 + bn) of the chunk through the noise stage
-        auto run_noise = [&](uint32_t j0, uint32_t bn) -> int {
-            NoiseParams np;
-            np.x = x; np.table = table; np.out = (int8_t *)tptr(0, j0);
-            np.C = pm.C; np.H = pm.H; np.W = pm.W;
-            np.key0 = (uint32_t)seed; np.key1 = (uint32_t)(seed >> 32);
-            np.image = image; np.phase = phase; np.sample_begin = begin + (uint32_t)done + j0; np.count = bn;
-            np.items = nullptr; np.n_per_item = 0; np.item_first = 0; np.item_count = 0; np.slot_begin = 0;
-            if (bc) {
-                const uint64_t s0 = done + j0;
-                np.items = bc->items; np.n_per_item = bc->n_per_item; np.slot_begin = s0;
-                np.item_first = (uint32_t)(s0 / bc->n_per_item);
-                np.item_count = (uint32_t)((s0 + bn - 1) / bc->n_per_item) - np.item_first + 1;
-            }
-            if ((prc = mark()) != ISR_OK) return prc;
-            if (m->quant_sigma >= 0.f) {   // FloatRS-quant: continuous noise rounded onto the pixel grid (single pair only)
-                FloatNoiseParams fp{};
-                fp.x = x; fp.out = np.out; fp.C = pm.C; fp.H = pm.H; fp.W = pm.W;
-                fp.key0 = np.key0; fp.key1 = np.key1; fp.image = image; fp.phase = phase;
-                fp.sample_begin = np.sample_begin; fp.count = bn; fp.sigma = m->quant_sigma; fp.center = 0.f; fp.quant = 1;
-                HIP_TRY(launch_float_noise(fp, m->stream));
-            } else {
-                HIP_TRY(launch_noise(np, m->stream));
-            }
-            ev_work.push_back({last_kernel_name(), 0, 0.0, (double)bn * pm.H * pm.W * 4});
-            return ISR_OK;
-        };
-        // where the copies from j0 on draw their noise, for a first layer that draws its own input
+        // where the copies from j0 on are in the list, and draw their noise
+        auto slots_at = [&](uint32_t j0) { Slots l = slots; l.begin = done + j0; return l; };
         auto noise_source = [&](uint32_t j0) {
             NoiseSource ns{};
-            ns.x = x; ns.table = table; ns.items = nullptr;
-            ns.key0 = (uint32_t)seed; ns.key1 = (uint32_t)(seed >> 32);
-            ns.image = image; ns.phase = phase; ns.sample_begin = begin + (uint32_t)done + j0;
+            ns.x = draw.x; ns.table = draw.table; ns.items = draw.items;
+            ns.key0 = (uint32_t)draw.seed; ns.key1 = (uint32_t)(draw.seed >> 32); ns.image = draw.image;
             ns.C = pm.C; ns.H = pm.H; ns.W = pm.W;
-            if (bc) { ns.items = bc->items; ns.n_per_item = bc->n_per_item; ns.slot_begin = done + j0; }
+            ns.slots = slots_at(j0);
             return ns;
+        };
+        // copies [j0, j0 + bn) of the chunk through the noise stage, for plans that have it as a launch of its own
+        auto run_noise = [&](uint32_t j0, uint32_t bn) -> int {
+            for (uint32_t j = j0; j < j0 + bn;) {
+                // one phase, and at most one grid row per pair
+                const uint64_t slot = done + j;
+                const uint32_t second = slot >= slots.split, n = slots.n[second];
+                const uint64_t s0 = second ? slot - slots.split : slot;
+                uint64_t bm = std::min<uint64_t>(j0 + bn - j, second ? count - slot : slots.split - slot);
+                if (slots.pairs > 1) bm = std::min<uint64_t>(bm, (uint64_t)n * 65534);
+                NoiseParams np;
+                np.x = draw.x; np.table = draw.table; np.out = (int8_t *)tptr(0, j);
+                np.C = pm.C; np.H = pm.H; np.W = pm.W;
+                np.key0 = (uint32_t)draw.seed; np.key1 = (uint32_t)(draw.seed >> 32);
+                np.image = draw.image; np.phase = slots.phase + second; np.sample_begin = slots.first + (uint32_t)s0; np.count = (uint32_t)bm;
+                np.items = draw.items; np.n_per_item = 0; np.item_first = 0; np.item_count = 0; np.slot_begin = 0;
+                if (draw.items) {
+                    np.n_per_item = n; np.slot_begin = s0;
+                    np.item_first = (uint32_t)(s0 / n);
+                    np.item_count = (uint32_t)((s0 + bm - 1) / n) - np.item_first + 1;
+                }
+                if ((prc = mark()) != ISR_OK) return prc;
+                if (m->quant_sigma >= 0.f) {   // FloatRS-quant: continuous noise rounded onto the pixel grid (single pair only)
+                    FloatNoiseParams fp{};
+                    fp.x = draw.x; fp.out = np.out; fp.C = pm.C; fp.H = pm.H; fp.W = pm.W;
+                    fp.key0 = np.key0; fp.key1 = np.key1; fp.image = np.image; fp.phase = np.phase;
+                    fp.sample_begin = np.sample_begin; fp.count = np.count; fp.sigma = m->quant_sigma; fp.center = 0.f; fp.quant = 1;
+                    HIP_TRY(launch_float_noise(fp, m->stream));
+                } else {
+                    HIP_TRY(launch_noise(np, m->stream));
+                }
+                if (timed) ev_work.push_back({last_kernel_name(), 0, 0.0, (double)bm * pm.H * pm.W * 4});
+                j += (uint32_t)bm;
+            }
+            return ISR_OK;
         };
         // copies [j0, j0 + bn) of the chunk through one op of the plan
         auto run_op = [&](const DevOp &d, uint32_t j0, uint32_t bn) -> int {
@@ -351,7 +348,7 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
                         np.logits = logits_host ? (int32_t *)(ws + pl.logits_off) + (size_t)j0 * pm.classes : nullptr;
                         np.argmax = argmax_host ? (int32_t *)(ws + pl.argmax_off) + j0 : nullptr;
                         np.counts = dcounts;
-                        if (bc) { np.n_per_item = bc->n_per_item; np.slot_begin = done + j0; }
+                        np.slots = slots_at(j0);
                     }
                     HIP_TRY(launch_narrow(np, d.narrow, m->stream));
                     break;
@@ -440,11 +437,11 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
                 f.logits = logits_host ? (int32_t *)(ws + pl.logits_off) + (size_t)j0 * pm.classes : nullptr;
                 f.argmax = argmax_host ? (int32_t *)(ws + pl.argmax_off) + j0 : nullptr;
                 f.counts = dcounts;
-                if (bc) { f.n_per_item = bc->n_per_item; f.slot_begin = done + j0; }
+                f.slots = slots_at(j0);
                 HIP_TRY(launch_fc(f, m->stream));
                 break; }
             }
-            ev_work.push_back({last_kernel_name(), d.type == OP_CONV ? 1 : 0, d.ops_per_sample * bn, d.bytes_per_sample * bn});
+            if (timed) ev_work.push_back({last_kernel_name(), d.type == OP_CONV ? 1 : 0, d.ops_per_sample * bn, d.bytes_per_sample * bn});
             return ISR_OK;
         };
 
@@ -511,14 +508,26 @@ int run_range(isr_model *m, const Plan &pl, const uint8_t *x, const DeviceNoiseT
 
 }  // namespace
 
-int isr::run_quant_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uint32_t image, uint32_t phase,
-                         uint32_t begin, uint64_t count, int32_t *logits_host, int32_t *argmax_host, uint32_t *dcounts,
-                         int stop_tensor) {
+int isr::run_quant(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uint32_t image, const Slots &slots,
+                   int32_t *logits_host, int32_t *argmax_host, uint32_t *dcounts, int stop_tensor) {
     m->quant_sigma = sigma;
-    const int rc = run_range(m, m->plan[m->use_fused], x, nullptr, seed, image, phase, begin, count, logits_host, argmax_host,
-                             dcounts, stop_tensor);
+    const int rc = run_slots(m, m->plan[m->use_fused], Draw{x, nullptr, nullptr, seed, image, slots}, logits_host, argmax_host, dcounts, stop_tensor);
     m->quant_sigma = -1.f;
     return rc;
+}
+
+// The counters are zero between calls: the last kernel of a call leaves them so.  After a call that failed on its way (and
+// before the first) they are cleared here.
+int isr::open_counts(isr_model *m) {
+    if (!m->counts_clean) HIP_TRY(launch_fill_u32(m->dcounts, 0, 2 * (size_t)m->pm.classes, m->stream));
+    m->counts_clean = false;
+    return ISR_OK;
+}
+int isr::close_counts(isr_model *m, uint32_t phases) {
+    HIP_TRY(launch_publish(m->dcounts, m->hcounts_dev, (size_t)phases * m->pm.classes, m->stream));
+    HIP_TRY(hipStreamSynchronize(m->stream));
+    m->counts_clean = true;
+    return ISR_OK;
 }
 
 namespace {
@@ -554,10 +563,8 @@ int get_tables(isr_model *m, const std::vector<uint32_t> &sigmas, std::vector<ui
     return ISR_OK;
 }
 
-// Validates a batch, uploads its item descriptors and clears its vote counters
-// (phases * n_items * classes words).
-int prepare_batch(isr_model *m, const void *x, uint32_t n_images, const isr_item *items, uint32_t n_items, double alpha,
-                  int phases) {
+// Validates a batch, uploads its item descriptors and sees to clean vote counters.
+int prepare_batch(isr_model *m, const void *x, uint32_t n_images, const isr_item *items, uint32_t n_items, double alpha) {
     if (!m || !x || !items || n_images == 0 || n_items == 0) return ISR_ERR_ARG;
     if (!(alpha > 0.0 && alpha < 1.0)) return ISR_ERR_ARG;
     if (!m->ws || m->chunk == 0) return ISR_ERR_WORKSPACE;
@@ -581,14 +588,25 @@ int prepare_batch(isr_model *m, const void *x, uint32_t n_images, const isr_item
         HIP_TRY(hipHostMalloc((void **)&m->hitems, sizeof(NoiseItem) * cap, hipHostMallocDefault));
         HIP_TRY(hipMalloc((void **)&m->dcounts_b, sizeof(uint32_t) * 2 * cap * C));
         HIP_TRY(hipHostMalloc((void **)&m->hcounts_b, sizeof(uint32_t) * 2 * cap * C, hipHostMallocDefault));
+        HIP_TRY(hipHostGetDevicePointer((void **)&m->hcounts_b_dev, m->hcounts_b, 0));
         m->items_cap = cap;
+        m->counts_b_clean = false;
     }
     int rc = get_tables(m, sigmas, slots);
     if (rc != ISR_OK) return rc;
     HIP_TRY(hipStreamSynchronize(m->stream));   // the pinned descriptors of an earlier call may still be in flight
     for (uint32_t i = 0; i < n_items; ++i) m->hitems[i] = NoiseItem{items[i].image, slots[i], items[i].image_id};
     HIP_TRY(hipMemcpyAsync(m->ditems, m->hitems, sizeof(NoiseItem) * n_items, hipMemcpyHostToDevice, m->stream));
-    HIP_TRY(launch_fill_u32(m->dcounts_b, 0, (size_t)phases * n_items * C, m->stream));
+    if (!m->counts_b_clean) HIP_TRY(launch_fill_u32(m->dcounts_b, 0, (size_t)2 * m->items_cap * C, m->stream));
+    m->counts_b_clean = false;
+    return ISR_OK;
+}
+
+// The tallies of a batched call on the host, zeros on the device (as close_counts).
+int finish_batch(isr_model *m, size_t words) {
+    HIP_TRY(launch_publish(m->dcounts_b, m->hcounts_b_dev, words, m->stream));
+    HIP_TRY(hipStreamSynchronize(m->stream));
+    m->counts_b_clean = true;
     return ISR_OK;
 }
 
@@ -623,6 +641,7 @@ int isr_load_model(const void *blob_host, size_t bytes, isr_model **out) {
     if (e == hipSuccess) e = hipHostMalloc((void **)&m->htables, sizeof(DeviceNoiseTable) * TABLE_SLOTS, hipHostMallocDefault);
     if (e == hipSuccess) e = hipMalloc((void **)&m->dcounts, sizeof(uint32_t) * 2 * m->pm.classes);
     if (e == hipSuccess) e = hipHostMalloc((void **)&m->hcounts, sizeof(uint32_t) * 2 * m->pm.classes, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&m->hcounts_dev, m->hcounts, 0);
     if (e != hipSuccess) { g_last_hip_error = (int)e; return cleanup(ISR_ERR_DEVICE); }
     rebase_device_ops(m->ops, m->dconst);
     m->plan[0].ops = m->ops;
@@ -765,11 +784,10 @@ int isr_certify(isr_model *m, const uint8_t *x_device, uint32_t sigma, uint32_t 
     const uint32_t C = (uint32_t)m->pm.classes;
     const DeviceNoiseTable *table = nullptr;
     if ((rc = get_table(m, sigma, &table)) != ISR_OK) return rc;
-    HIP_TRY(launch_fill_u32(m->dcounts, 0, 2 * C, m->stream));
-    if ((rc = run_range(m, m->plan[m->use_fused], x_device, table, seed, image_id, 0, 0, n0, nullptr, nullptr, m->dcounts, -1)) != ISR_OK) return rc;
-    if ((rc = run_range(m, m->plan[m->use_fused], x_device, table, seed, image_id, 1, 0, n, nullptr, nullptr, m->dcounts + C, -1)) != ISR_OK) return rc;
-    HIP_TRY(hipMemcpyAsync(m->hcounts, m->dcounts, sizeof(uint32_t) * 2 * C, hipMemcpyDeviceToHost, m->stream));
-    HIP_TRY(hipStreamSynchronize(m->stream));
+    if ((rc = open_counts(m)) != ISR_OK) return rc;
+    const Draw draw{x_device, table, nullptr, seed, image_id, Slots{0, n0, {n0, n}, 1, 0, 0}};
+    if ((rc = run_slots(m, m->plan[m->use_fused], draw, nullptr, nullptr, m->dcounts, -1)) != ISR_OK) return rc;
+    if ((rc = close_counts(m, 2)) != ISR_OK) return rc;
     if (counts0_host) std::memcpy(counts0_host, m->hcounts, sizeof(uint32_t) * C);
     if (counts1_host) std::memcpy(counts1_host, m->hcounts + C, sizeof(uint32_t) * C);
     return isr_decide_certify(m->hcounts, m->hcounts + C, C, (double)sigma, n, alpha, out);
@@ -783,10 +801,10 @@ int isr_predict(isr_model *m, const uint8_t *x_device, uint32_t sigma, uint32_t 
     const uint32_t C = (uint32_t)m->pm.classes;
     const DeviceNoiseTable *table = nullptr;
     if ((rc = get_table(m, sigma, &table)) != ISR_OK) return rc;
-    HIP_TRY(launch_fill_u32(m->dcounts, 0, C, m->stream));
-    if ((rc = run_range(m, m->plan[m->use_fused], x_device, table, seed, image_id, 0, 0, n, nullptr, nullptr, m->dcounts, -1)) != ISR_OK) return rc;
-    HIP_TRY(hipMemcpyAsync(m->hcounts, m->dcounts, sizeof(uint32_t) * C, hipMemcpyDeviceToHost, m->stream));
-    HIP_TRY(hipStreamSynchronize(m->stream));
+    if ((rc = open_counts(m)) != ISR_OK) return rc;
+    const Draw draw{x_device, table, nullptr, seed, image_id, one_phase(0, 0, n)};
+    if ((rc = run_slots(m, m->plan[m->use_fused], draw, nullptr, nullptr, m->dcounts, -1)) != ISR_OK) return rc;
+    if ((rc = close_counts(m, 1)) != ISR_OK) return rc;
     if (counts_host) std::memcpy(counts_host, m->hcounts, sizeof(uint32_t) * C);
     return isr_decide_predict(m->hcounts, C, alpha, out);
 }
@@ -795,16 +813,12 @@ int isr_certify_batch(isr_model *m, const uint8_t *x_device, uint32_t n_images, 
                       uint32_t n_items, uint32_t n0, uint32_t n, double alpha, uint64_t seed, isr_result *out_host,
                       uint32_t *counts0_host, uint32_t *counts1_host) {
     if (!out_host || n0 == 0 || n == 0) return ISR_ERR_ARG;
-    int rc = prepare_batch(m, x_device, n_images, items_host, n_items, alpha, 2);
+    int rc = prepare_batch(m, x_device, n_images, items_host, n_items, alpha);
     if (rc != ISR_OK) return rc;
     const size_t C = (size_t)m->pm.classes, per_phase = (size_t)n_items * C;
-    const Plan &pl = m->plan[m->use_fused];
-    BatchCtx bc{m->ditems, n_items, n0};
-    if ((rc = run_range(m, pl, x_device, m->dtables, seed, 0, 0, 0, 0, nullptr, nullptr, m->dcounts_b, -1, &bc)) != ISR_OK) return rc;
-    bc.n_per_item = n;
-    if ((rc = run_range(m, pl, x_device, m->dtables, seed, 0, 1, 0, 0, nullptr, nullptr, m->dcounts_b + per_phase, -1, &bc)) != ISR_OK) return rc;
-    HIP_TRY(hipMemcpyAsync(m->hcounts_b, m->dcounts_b, sizeof(uint32_t) * 2 * per_phase, hipMemcpyDeviceToHost, m->stream));
-    HIP_TRY(hipStreamSynchronize(m->stream));
+    const Draw draw{x_device, m->dtables, m->ditems, seed, 0, Slots{0, (uint64_t)n_items * n0, {n0, n}, n_items, 0, 0}};
+    if ((rc = run_slots(m, m->plan[m->use_fused], draw, nullptr, nullptr, m->dcounts_b, -1)) != ISR_OK) return rc;
+    if ((rc = finish_batch(m, 2 * per_phase)) != ISR_OK) return rc;
     if (counts0_host) std::memcpy(counts0_host, m->hcounts_b, sizeof(uint32_t) * per_phase);
     if (counts1_host) std::memcpy(counts1_host, m->hcounts_b + per_phase, sizeof(uint32_t) * per_phase);
     for (uint32_t i = 0; i < n_items; ++i) {
@@ -819,13 +833,12 @@ int isr_predict_batch(isr_model *m, const uint8_t *x_device, uint32_t n_images, 
                       uint32_t n_items, uint32_t n, double alpha, uint64_t seed, isr_result *out_host,
                       uint32_t *counts_host) {
     if (!out_host || n == 0) return ISR_ERR_ARG;
-    int rc = prepare_batch(m, x_device, n_images, items_host, n_items, alpha, 1);
+    int rc = prepare_batch(m, x_device, n_images, items_host, n_items, alpha);
     if (rc != ISR_OK) return rc;
     const size_t C = (size_t)m->pm.classes, per_phase = (size_t)n_items * C;
-    BatchCtx bc{m->ditems, n_items, n};
-    if ((rc = run_range(m, m->plan[m->use_fused], x_device, m->dtables, seed, 0, 0, 0, 0, nullptr, nullptr, m->dcounts_b, -1, &bc)) != ISR_OK) return rc;
-    HIP_TRY(hipMemcpyAsync(m->hcounts_b, m->dcounts_b, sizeof(uint32_t) * per_phase, hipMemcpyDeviceToHost, m->stream));
-    HIP_TRY(hipStreamSynchronize(m->stream));
+    const Draw draw{x_device, m->dtables, m->ditems, seed, 0, Slots{0, (uint64_t)n_items * n, {n, 0}, n_items, 0, 0}};
+    if ((rc = run_slots(m, m->plan[m->use_fused], draw, nullptr, nullptr, m->dcounts_b, -1)) != ISR_OK) return rc;
+    if ((rc = finish_batch(m, per_phase)) != ISR_OK) return rc;
     if (counts_host) std::memcpy(counts_host, m->hcounts_b, sizeof(uint32_t) * per_phase);
     for (uint32_t i = 0; i < n_items; ++i) {
         rc = isr_decide_predict(m->hcounts_b + i * C, (uint32_t)C, alpha, out_host + i);
@@ -841,7 +854,7 @@ int isr_debug_noisy(isr_model *m, const uint8_t *x_device, uint32_t sigma, uint6
     if (!out_host || count == 0 || count > m->chunk || phase > 1) return ISR_ERR_ARG;
     const DeviceNoiseTable *table = nullptr;
     if ((rc = get_table(m, sigma, &table)) != ISR_OK) return rc;
-    if ((rc = run_range(m, m->plan[m->use_fused], x_device, table, seed, image_id, phase, sample_begin, count, nullptr, nullptr, nullptr, 0)) != ISR_OK) return rc;
+    if ((rc = run_slots(m, m->plan[m->use_fused], Draw{x_device, table, nullptr, seed, image_id, one_phase(phase, sample_begin, count)}, nullptr, nullptr, nullptr, 0)) != ISR_OK) return rc;
     const ParsedModel &pm = m->pm;
     const size_t hw = (size_t)pm.H * pm.W;
     std::vector<int8_t> tmp(count * hw * 4);
@@ -862,13 +875,12 @@ int isr_debug_forward(isr_model *m, const uint8_t *x_device, uint32_t sigma, uin
     const uint32_t C = (uint32_t)m->pm.classes;
     const DeviceNoiseTable *table = nullptr;
     if ((rc = get_table(m, sigma, &table)) != ISR_OK) return rc;
-    if (counts_host) HIP_TRY(launch_fill_u32(m->dcounts, 0, C, m->stream));
-    rc = run_range(m, m->plan[m->use_fused], x_device, table, seed, image_id, phase, sample_begin, count, logits_host, argmax_host,
-                   counts_host ? m->dcounts : nullptr, -1);
+    if (counts_host && (rc = open_counts(m)) != ISR_OK) return rc;
+    const Draw draw{x_device, table, nullptr, seed, image_id, one_phase(phase, sample_begin, count)};
+    rc = run_slots(m, m->plan[m->use_fused], draw, logits_host, argmax_host, counts_host ? m->dcounts : nullptr, -1);
     if (rc != ISR_OK) return rc;
     if (counts_host) {
-        HIP_TRY(hipMemcpyAsync(m->hcounts, m->dcounts, sizeof(uint32_t) * C, hipMemcpyDeviceToHost, m->stream));
-        HIP_TRY(hipStreamSynchronize(m->stream));
+        if ((rc = close_counts(m, 1)) != ISR_OK) return rc;
         for (uint32_t i = 0; i < C; ++i) counts_host[i] += m->hcounts[i];
     } else {
         HIP_TRY(hipStreamSynchronize(m->stream));
@@ -887,7 +899,7 @@ int isr_debug_tensor(isr_model *m, const uint8_t *x_device, uint32_t sigma, uint
     if ((rc = get_table(m, sigma, &table)) != ISR_OK) return rc;
     // tensors that the fused plan never materialises come from the op-by-op plan
     const Plan &pl = (m->use_fused && m->plan[m->use_fused].has[tensor_id]) ? m->plan[m->use_fused] : m->plan[0];
-    if ((rc = run_range(m, pl, x_device, table, seed, image_id, phase, sample, 1, nullptr, nullptr, nullptr, tensor_id)) != ISR_OK) return rc;
+    if ((rc = run_slots(m, pl, Draw{x_device, table, nullptr, seed, image_id, one_phase(phase, sample, 1)}, nullptr, nullptr, nullptr, tensor_id)) != ISR_OK) return rc;
     const TensorDesc &t = pm.tensors[tensor_id];
     const size_t hw = (size_t)t.H * t.W;
     std::vector<int8_t> tmp(hw * t.Cp);

@@ -339,7 +339,7 @@ int check_float_call(isr_model *m, const void *x, float sigma, int system) {
 int run_system(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uint32_t image, uint32_t phase, uint32_t begin,
                uint64_t count, int system, void *logits_host, int32_t *argmax_host, uint32_t *dcounts) {
     if (system == ISR_FLOATRS_QUANT)
-        return run_quant_range(m, x, sigma, seed, image, phase, begin, count, (int32_t *)logits_host, argmax_host, dcounts, -1);
+        return run_quant(m, x, sigma, seed, image, one_phase(phase, begin, (uint32_t)count), (int32_t *)logits_host, argmax_host, dcounts, -1);
     return run_fp_range(m, x, sigma, seed, image, phase, begin, count, (float *)logits_host, argmax_host, dcounts, false);
 }
 
@@ -368,11 +368,14 @@ int isr_float_certify(isr_model *m, const uint8_t *x_device, float sigma, uint32
     if (rc != ISR_OK) return rc;
     if (!out || n0 == 0 || n == 0 || !(alpha > 0.0 && alpha < 1.0)) return ISR_ERR_ARG;
     const uint32_t C = (uint32_t)m->pm.classes;
-    HIP_TRY(launch_fill_u32(m->dcounts, 0, 2 * C, m->stream));
-    if ((rc = run_system(m, x_device, sigma, seed, image_id, 0, 0, n0, system, nullptr, nullptr, m->dcounts)) != ISR_OK) return rc;
-    if ((rc = run_system(m, x_device, sigma, seed, image_id, 1, 0, n, system, nullptr, nullptr, m->dcounts + C)) != ISR_OK) return rc;
-    HIP_TRY(hipMemcpyAsync(m->hcounts, m->dcounts, sizeof(uint32_t) * 2 * C, hipMemcpyDeviceToHost, m->stream));
-    HIP_TRY(hipStreamSynchronize(m->stream));
+    if ((rc = open_counts(m)) != ISR_OK) return rc;
+    if (system == ISR_FLOATRS_QUANT) {
+        if ((rc = run_quant(m, x_device, sigma, seed, image_id, Slots{0, n0, {n0, n}, 1, 0, 0}, nullptr, nullptr, m->dcounts, -1)) != ISR_OK) return rc;
+    } else {
+        if ((rc = run_system(m, x_device, sigma, seed, image_id, 0, 0, n0, system, nullptr, nullptr, m->dcounts)) != ISR_OK) return rc;
+        if ((rc = run_system(m, x_device, sigma, seed, image_id, 1, 0, n, system, nullptr, nullptr, m->dcounts + C)) != ISR_OK) return rc;
+    }
+    if ((rc = close_counts(m, 2)) != ISR_OK) return rc;
     if (counts0_host) std::memcpy(counts0_host, m->hcounts, sizeof(uint32_t) * C);
     if (counts1_host) std::memcpy(counts1_host, m->hcounts + C, sizeof(uint32_t) * C);
     rc = isr_decide_certify(m->hcounts, m->hcounts + C, C, (double)sigma, n, alpha, out);
@@ -389,7 +392,7 @@ int isr_float_debug_noisy(isr_model *m, const uint8_t *x_device, float sigma, ui
     const ParsedModel &pm = m->pm;
     const size_t hw = (size_t)pm.H * pm.W;
     if (system == ISR_FLOATRS_QUANT) {
-        if ((rc = run_quant_range(m, x_device, sigma, seed, image_id, phase, sample_begin, count, nullptr, nullptr, nullptr, 0)) != ISR_OK) return rc;
+        if ((rc = run_quant(m, x_device, sigma, seed, image_id, one_phase(phase, sample_begin, count), nullptr, nullptr, nullptr, 0)) != ISR_OK) return rc;
         std::vector<int8_t> tmp(count * hw * 4);
         HIP_TRY(hipMemcpyAsync(tmp.data(), m->ws + m->plan[m->use_fused].toff[0], tmp.size(), hipMemcpyDeviceToHost, m->stream));
         HIP_TRY(hipStreamSynchronize(m->stream));
@@ -417,13 +420,12 @@ int isr_float_debug_forward(isr_model *m, const uint8_t *x_device, float sigma, 
     if (rc != ISR_OK) return rc;
     if (count == 0 || phase > 1) return ISR_ERR_ARG;
     const uint32_t C = (uint32_t)m->pm.classes;
-    if (counts_host) HIP_TRY(launch_fill_u32(m->dcounts, 0, C, m->stream));
+    if (counts_host && (rc = open_counts(m)) != ISR_OK) return rc;
     rc = run_system(m, x_device, sigma, seed, image_id, phase, sample_begin, count, system, logits_host, argmax_host,
                     counts_host ? m->dcounts : nullptr);
     if (rc != ISR_OK) return rc;
     if (counts_host) {
-        HIP_TRY(hipMemcpyAsync(m->hcounts, m->dcounts, sizeof(uint32_t) * C, hipMemcpyDeviceToHost, m->stream));
-        HIP_TRY(hipStreamSynchronize(m->stream));
+        if ((rc = close_counts(m, 1)) != ISR_OK) return rc;
         for (uint32_t i = 0; i < C; ++i) counts_host[i] += m->hcounts[i];
     } else {
         HIP_TRY(hipStreamSynchronize(m->stream));

@@ -60,16 +60,45 @@ struct NoiseItem {
     uint32_t image_id;       // counter word of the random stream
 };
 
-// Which image, table and sample index copy `copy` of a chunk draws from.  Single pair: the call's
-// own; batch mode (items != null): copy s is slot slot_begin + s of a list in which item i owns
-// the n_per_item slots from i * n_per_item on.
+// The copies of a call are one list of slots: n[0] samples of phase `phase` for each (image, sigma) pair, one pair after the
+// other, then n[1] samples of the next phase likewise.  A launch works on the slots from `begin` on.
+struct Slots {
+    uint64_t begin;
+    uint64_t split;                  // pairs * n[0]: the first slot of the second phase
+    uint32_t n[2];
+    uint32_t pairs, phase, first;    // first: sample index of a pair's first slot
+};
+// What the copy in a slot is: its random stream (phase, sample) and the tally row of its vote, [phases][pairs].
+struct SlotUse {
+    uint32_t phase, pair, sample, row;
+};
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline SlotUse slot_use(const Slots &l, uint64_t copy) {
+    uint64_t s = l.begin + copy;
+    const uint32_t second = s >= l.split;
+    if (second) s -= l.split;
+    uint32_t pair = 0;
+    if (l.pairs > 1) {
+        const uint32_t n = second ? l.n[1] : l.n[0];
+        pair = (uint32_t)(s / n);
+        s -= (uint64_t)pair * n;
+    }
+    return {l.phase + second, pair, l.first + (uint32_t)s, second * l.pairs + pair};
+}
+
+inline bool valid_slots(const Slots &l) { return l.pairs == 1 || (l.pairs > 1 && l.n[0] > 0); }
+
+// Where the copies of a launch draw from.  Single pair: the call's own image and table; batch mode (items != null): the
+// pair's of the slot.
 struct NoiseSource {
     const uint8_t *x;                // [C][H][W] clean image ([images][C][H][W] in batch mode)
     const DeviceNoiseTable *table;   // the table (batch mode: table 0 of the array indexed by table_slot)
     const NoiseItem *items;
-    uint32_t key0, key1, image, phase, sample_begin, n_per_item;
-    uint64_t slot_begin;
+    uint32_t key0, key1, image;
     int32_t C, H, W;
+    Slots slots;
 };
 
 // ---- parsed model (host) ---------------------------------------------------
@@ -213,8 +242,7 @@ struct NarrowParams {
     int32_t classes, classes_p;
     int32_t *logits, *argmax;
     uint32_t *counts;
-    uint32_t n_per_item;     // as in FcParams
-    uint64_t slot_begin;
+    Slots slots;             // of the votes
 };
 
 // Bottleneck block in one kernel: conv1x1 -> conv3x3 [-> conv1x1 + residual add with the block input
@@ -292,13 +320,9 @@ struct FcParams {
     int32_t Kp, classes, classes_p, B;   // classes_p: classes rounded up to a multiple of 4
     int32_t *logits;         // [B][classes] or null
     int32_t *argmax;         // [B] or null
-    uint32_t *counts;        // [classes] (accumulated) or null; [items][classes] in batch mode
-    // batch mode (n_per_item != 0): copy s of the chunk is slot slot_begin + s of a list in which
-    // every item owns n_per_item consecutive slots; its vote goes to counts[slot / n_per_item]
-    uint32_t n_per_item;
-    uint64_t slot_begin;
+    uint32_t *counts;        // [phases][pairs][classes] (accumulated) or null
+    Slots slots;             // of the votes
 };
-
 
 struct NoiseParams {
     const uint8_t *x;        // [C][H][W] clean image ([images][C][H][W] in batch mode)
@@ -396,6 +420,7 @@ hipError_t launch_add(const AddParams &p, hipStream_t st);
 hipError_t launch_maxpool(const PoolParams &p, hipStream_t st);
 hipError_t launch_gap(const GapParams &p, hipStream_t st);
 hipError_t launch_fc(const FcParams &p, hipStream_t st);
+hipError_t launch_publish(uint32_t *counts, uint32_t *host, size_t n, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, size_t n, hipStream_t st);
 // Tile geometry of the convolution kernel chosen for (Cout_p): rows per M tile.
 int conv_tile_m(int cout_p);

@@ -256,8 +256,8 @@ hipError_t launch_gap(const GapParams &p, hipStream_t st) {
 constexpr int FC_MAX_CLASSES = 1024;
 
 __global__ __launch_bounds__(256) void fc_vote_kernel(const FcParams p) {
-    __shared__ uint32_t hist[FC_MAX_CLASSES];
-    for (int i = threadIdx.x; i < p.classes; i += 256) hist[i] = 0;
+    __shared__ uint32_t hist[2 * FC_MAX_CLASSES];   // single pair: the workgroup's votes of the two phases
+    for (int i = threadIdx.x; i < 2 * p.classes; i += 256) hist[i] = 0;
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (long s = (long)blockIdx.x * 4 + wave; s < p.B; s += (long)gridDim.x * 4) {
@@ -285,14 +285,14 @@ __global__ __launch_bounds__(256) void fc_vote_kernel(const FcParams p) {
         if (lane == 0) {
             if (p.argmax) p.argmax[s] = best_idx;
             if (p.counts) {
-                if (p.n_per_item) atomicAdd(&p.counts[(p.slot_begin + (uint64_t)s) / p.n_per_item * p.classes + best_idx], 1u);
-                else atomicAdd(&hist[best_idx], 1u);
+                const uint32_t at = slot_use(p.slots, (uint64_t)s).row * p.classes + best_idx;
+                atomicAdd(p.slots.pairs > 1 ? &p.counts[at] : &hist[at], 1u);
             }
         }
     }
     __syncthreads();
-    if (p.counts && !p.n_per_item)
-        for (int i = threadIdx.x; i < p.classes; i += 256)
+    if (p.counts && p.slots.pairs == 1)
+        for (int i = threadIdx.x; i < 2 * p.classes; i += 256)
             if (hist[i]) atomicAdd(&p.counts[i], hist[i]);
 }
 
@@ -338,8 +338,7 @@ __global__ __launch_bounds__(256) void fc_vote_ksplit_kernel(const FcParams p) {
             if (lane == 0) {
                 if (p.argmax) p.argmax[s] = best_idx;
                 if (p.counts) {
-                    const uint64_t row = p.n_per_item ? (p.slot_begin + (uint64_t)s) / p.n_per_item : 0;
-                    atomicAdd(&p.counts[row * p.classes + best_idx], 1u);
+                    atomicAdd(&p.counts[(size_t)slot_use(p.slots, (uint64_t)s).row * p.classes + best_idx], 1u);
                 }
             }
         }
@@ -349,7 +348,7 @@ __global__ __launch_bounds__(256) void fc_vote_ksplit_kernel(const FcParams p) {
 
 hipError_t launch_fc(const FcParams &p, hipStream_t st) {
     if (p.B <= 0) return hipSuccess;
-    if (p.classes < 1 || p.classes > FC_MAX_CLASSES || p.Kp % 16 != 0 || p.classes_p < p.classes) return hipErrorInvalidValue;
+    if (p.classes < 1 || p.classes > FC_MAX_CLASSES || p.Kp % 16 != 0 || p.classes_p < p.classes || (p.counts && !valid_slots(p.slots))) return hipErrorInvalidValue;
     if (p.Kp % 1024 == 0) {
         long blocks = p.B;
         if (blocks > 256 * 16) blocks = 256 * 16;
@@ -361,6 +360,22 @@ hipError_t launch_fc(const FcParams &p, hipStream_t st) {
     if (blocks > 256 * 8) blocks = 256 * 8;
     set_kernel_name("fc_vote_kernel");
     hipLaunchKernelGGL(fc_vote_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p);
+    return hipGetLastError();
+}
+
+// Tallies to the host's pinned memory, and zeros in their place for the next call.
+__global__ void publish_kernel(uint32_t *counts, uint32_t *host, size_t n) {
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
+        host[i] = counts[i];
+        counts[i] = 0;
+    }
+}
+
+hipError_t launch_publish(uint32_t *counts, uint32_t *host, size_t n, hipStream_t st) {
+    if (n == 0) return hipSuccess;
+    size_t blocks = (n + 255) / 256;
+    if (blocks > 1024) blocks = 1024;
+    hipLaunchKernelGGL(publish_kernel, dim3((unsigned)blocks), dim3(256), 0, st, counts, host, n);
     return hipGetLastError();
 }
 

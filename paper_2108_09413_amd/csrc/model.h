@@ -30,11 +30,12 @@ struct isr_model {
     uint32_t table_sigma[TABLE_SLOTS] = {0};
     int table_next = 0;
     uint32_t *dcounts = nullptr;        // 2 * classes
-    uint32_t *hcounts = nullptr;        // pinned, 2 * classes
+    uint32_t *hcounts = nullptr, *hcounts_dev = nullptr;   // pinned, 2 * classes, and its address for kernels
+    bool counts_clean = false, counts_b_clean = false;     // dcounts, dcounts_b hold zeros
     uint8_t *dnarrow = nullptr;         // block descriptors and packed constants of the narrow-net ops of plan[1] and plan[2]
     // batched calls: item descriptors and per-item vote counters, grown on demand
     NoiseItem *ditems = nullptr, *hitems = nullptr;
-    uint32_t *dcounts_b = nullptr, *hcounts_b = nullptr;   // 2 * items_cap * classes each
+    uint32_t *dcounts_b = nullptr, *hcounts_b = nullptr, *hcounts_b_dev = nullptr;   // 2 * items_cap * classes each
     uint32_t items_cap = 0;
     // workspace
     uint8_t *ws = nullptr;
@@ -52,11 +53,24 @@ struct isr_model {
 };
 
 namespace isr {
+// What the copies of a call are drawn from (NoiseSource without the launch's place in the list).
+struct Draw {
+    const uint8_t *x;
+    const DeviceNoiseTable *table;
+    const NoiseItem *items;
+    uint64_t seed;
+    uint32_t image;
+    Slots slots;
+};
+inline Slots one_phase(uint32_t phase, uint32_t first, uint32_t n) { return Slots{0, n, {n, 0}, 1, phase, first}; }
+
 // The integer path's Monte-Carlo loop with the input stage of FloatRS-quant (api.cpp): noisy copies are
 // clamp(round(x + sigma z)) with continuous z instead of discrete-Gaussian draws; everything after is the int8 network.
-int run_quant_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uint32_t image, uint32_t phase,
-                    uint32_t begin, uint64_t count, int32_t *logits_host, int32_t *argmax_host, uint32_t *dcounts,
-                    int stop_tensor);
+int run_quant(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uint32_t image, const Slots &slots,
+              int32_t *logits_host, int32_t *argmax_host, uint32_t *dcounts, int stop_tensor);
+// The vote counters m->dcounts before a call's first vote: zero; and after its last: on the host in m->hcounts.
+int open_counts(isr_model *m);
+int close_counts(isr_model *m, uint32_t phases);
 }  // namespace isr
 
 #endif

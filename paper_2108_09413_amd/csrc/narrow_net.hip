@@ -318,7 +318,7 @@ __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t 
     lds_barrier();
     if (tid < NI && best_of[tid] >= 0) {
         // one global addition per distinct (row, class) of the workgroup, by its first image
-        auto row = [&](int im) { return p.n_per_item ? (uint32_t)((p.slot_begin + (uint64_t)(img0 + im)) / p.n_per_item) : 0u; };
+        auto row = [&](int im) { return slot_use(p.slots, (uint64_t)(img0 + im)).row; };
         const uint32_t r = row(tid);
         uint32_t n = 0;
         bool first = true;
@@ -374,12 +374,12 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
             if (p.fused_noise) {
                 const uint8_t *xim;
                 const DeviceNoiseTable *src;
-                uint32_t image_id, sample;
-                resolve_noise_source(p.noise, img0, xim, src, image_id, sample);
+                uint32_t image_id;
+                const SlotUse use = resolve_noise_source(p.noise, img0, xim, src, image_id);
                 stage_noise_table(*tab, src, tid, 256);
                 const NoiseSampler smp = src->s;
                 lds_barrier();
-                noisy_quad(*tab, smp, src, xim, p.noise.C, S, S, y, x4, sample, image_id, p.noise.phase, p.noise.key0, p.noise.key1, v);
+                noisy_quad(*tab, smp, src, xim, p.noise.C, S, S, y, x4, use.sample, image_id, use.phase, p.noise.key0, p.noise.key1, v);
             } else {
                 const v4i w = *(const v4i *)(p.in + ((img0 * S + y) * S + 4 * x4) * 4);
 #pragma unroll
@@ -673,12 +673,13 @@ hipError_t launch_narrow(const NarrowParams &p, int channels, hipStream_t st) {
         return hipErrorInvalidValue;
     if (p.fused_noise) {
         const NoiseSource &ns = p.noise;
-        if (!from_image || !ns.x || !ns.table || ns.C < 1 || ns.C > 3 || ns.H != 32 || ns.W != 32 || (ns.items && ns.n_per_item == 0)) return hipErrorInvalidValue;
+        if (!from_image || !ns.x || !ns.table || ns.C < 1 || ns.C > 3 || ns.H != 32 || ns.W != 32 || !valid_slots(ns.slots)) return hipErrorInvalidValue;
     }
     if (p.tail && (channels == 64 || !p.tw1 || !p.tprm || (p.tail == 1 && (!p.tw2 || !p.twp)) || p.tail > 2)) return hipErrorInvalidValue;
     if (p.head && (!(channels == 64 || (channels == 16 && p.tail == 2)) || (p.tail && channels == 64) || !p.fc_w || !p.fc_bias || p.classes < 1 ||
                    p.classes_p < p.classes || (channels == 64 && p.nblocks == 0)))
         return hipErrorInvalidValue;
+    if (p.head && p.counts && !valid_slots(p.slots)) return hipErrorInvalidValue;
     // images per workgroup: as few as let every workgroup of the launch run at once (two per CU); beyond, as many as fit,
     // to share the weights
     const bool one = p.B <= 256, two = p.B <= 1024;

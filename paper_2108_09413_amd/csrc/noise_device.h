@@ -116,17 +116,17 @@ __device__ __forceinline__ void noisy_quad(const NoiseLds &t, const NoiseSampler
     }
 }
 
-__device__ __forceinline__ void resolve_noise_source(const NoiseSource &s, long copy, const uint8_t *&xim,
-                                                     const DeviceNoiseTable *&tab, uint32_t &image_id, uint32_t &sample) {
-    xim = s.x; tab = s.table; image_id = s.image; sample = s.sample_begin + (uint32_t)copy;
+__device__ __forceinline__ SlotUse resolve_noise_source(const NoiseSource &s, long copy, const uint8_t *&xim,
+                                                        const DeviceNoiseTable *&tab, uint32_t &image_id) {
+    const SlotUse use = slot_use(s.slots, (uint64_t)copy);
+    xim = s.x; tab = s.table; image_id = s.image;
     if (s.items) {
-        const uint64_t slot = s.slot_begin + (uint64_t)copy, item = slot / s.n_per_item;
-        const NoiseItem it = s.items[item];
+        const NoiseItem it = s.items[use.pair];
         xim = s.x + (size_t)it.image * s.C * s.H * s.W;
         tab = s.table + it.table_slot;
         image_id = it.image_id;
-        sample = (uint32_t)(slot - item * s.n_per_item);
     }
+    return use;
 }
 
 }  // namespace isr

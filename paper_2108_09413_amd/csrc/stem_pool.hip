@@ -64,8 +64,8 @@ __global__ __launch_bounds__(256, 3) void stem_pool_kernel(const StemPoolParams 
         // so the rows that neighbouring bands share are simply drawn again, bit for bit the same
         const uint8_t *xim;
         const DeviceNoiseTable *tab;
-        uint32_t image_id, sample;
-        resolve_noise_source(p.noise, b, xim, tab, image_id, sample);
+        uint32_t image_id;
+        const SlotUse use = resolve_noise_source(p.noise, b, xim, tab, image_id);
         stage_noise_table(ntab, tab, tid, 256);
         const NoiseSampler smp = tab->s;
         __syncthreads();
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256, 3) void stem_pool_kernel(const StemPoolParams 
             const int r = i / wchunks, c = i - r * wchunks, iy = iy0 + r;
             uint32_t v[4] = {zb, zb, zb, zb};
             if ((unsigned)iy < (unsigned)p.H)
-                noisy_quad(ntab, smp, tab, xim, p.noise.C, p.H, p.W, iy, c, sample, image_id, p.noise.phase, p.noise.key0, p.noise.key1, v);
+                noisy_quad(ntab, smp, tab, xim, p.noise.C, p.H, p.W, iy, c, use.sample, image_id, use.phase, p.noise.key0, p.noise.key1, v);
             int *dst = (int *)(&In[(r * PW + 3 + 4 * c) * 4]);
             dst[0] = (int)v[0]; dst[1] = (int)v[1]; dst[2] = (int)v[2]; dst[3] = (int)v[3];
         }
@@ -179,7 +179,7 @@ hipError_t launch_stem_pool(const StemPoolParams &p, hipStream_t st) {
         return hipErrorInvalidValue;
     if (p.fused_noise) {
         const NoiseSource &ns = p.noise;
-        if (!ns.x || !ns.table || ns.C < 1 || ns.C > 3 || ns.H != p.H || ns.W != p.W || (ns.items && ns.n_per_item == 0)) return hipErrorInvalidValue;
+        if (!ns.x || !ns.table || ns.C < 1 || ns.C > 3 || ns.H != p.H || ns.W != p.W || !valid_slots(ns.slots)) return hipErrorInvalidValue;
     } else if (!p.in) {
         return hipErrorInvalidValue;
     }

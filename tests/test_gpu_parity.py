@@ -374,6 +374,39 @@ def test_stages_of_the_nets_on_32x32_images(isr, net, copies):
     m.close()
 
 
+@pytest.mark.parametrize("first", ["16 channels", "7x7 and pooling", "noise launch"])
+def test_both_phases_of_a_certification_in_one_list(isr, first):
+    """Chunks and launches that end inside either phase and inside a pair: tallies against those of the phases alone, for first
+    layers that draw their own noise and for the noise launch, single calls and batches, and the rounded continuous noise."""
+    _say(f"phases in one list: {first}")
+    b = NetBuilder(rng=np.random.default_rng(17), in_shape=(3, 32, 32), num_classes=9)
+    t = b.tensor(3, 32, 32, 0, 74.0)
+    if first == "16 channels":
+        t = b.conv(t, 16, 3, 1, 1, True)
+        t = b.add(t, b.conv(b.conv(t, 16, 3, 1, 1, True), 16, 3, 1, 1, False), True)
+    else:
+        t = b.maxpool(b.conv(t, 64, 7, 2, 3, True), 3, 2, 1)
+    b.fc(b.gap(t), 9)
+    m = _load(isr, b.blob(), 7)
+    isr.isr_set_fusion(m, 0 if first == "noise launch" else 1)
+    x = np.random.default_rng(18).integers(0, 256, size=(3, 32, 32)).astype(np.uint8)
+    tally = lambda img, sigma, image_id, phase, n: isr.isr_debug_forward(m, img, sigma, 3, image_id, phase, 0, n)[2]
+    for n0, n in ((5, 16), (7, 7), (23, 1)):
+        _, c0, c1 = isr.isr_certify(m, x, 48, n0, n, ALPHA, seed=3, image_id=6)
+        assert np.array_equal(c0, tally(x, 48, 6, 0, n0)) and np.array_equal(c1, tally(x, 48, 6, 1, n))
+        _, c = isr.isr_predict(m, x, 48, n0, ALPHA, seed=3, image_id=6)
+        assert np.array_equal(c, c0)
+        items = [(0, 48, 1), (1, 90, 2), (0, 90, 3)]
+        _, c0, c1 = isr.isr_certify_batch(m, np.stack([x, 255 - x]), items, n0, n, ALPHA, seed=3)
+        for i, (im, sigma, image_id) in enumerate(items):
+            img = 255 - x if im else x
+            assert np.array_equal(c0[i], tally(img, sigma, image_id, 0, n0)) and np.array_equal(c1[i], tally(img, sigma, image_id, 1, n))
+        _, q0, q1 = isr.isr_float_certify(m, x, 48.0, n0, n, ALPHA, isr.FLOATRS_QUANT, seed=3, image_id=6)
+        for phase, k, q in ((0, n0, q0), (1, n, q1)):
+            assert np.array_equal(q, isr.isr_float_debug_forward(m, x, 48.0, 3, 6, phase, 0, k, isr.FLOATRS_QUANT)[2])
+    m.close()
+
+
 @pytest.mark.parametrize("shape", [(30, 20), (28, 28), (5, 40)])
 def test_bottleneck_blocks_in_one_kernel(isr, shape):
     """conv1x1 -> conv3x3 (64 middle channels) [-> conv1x1 + add with the block input] as one
