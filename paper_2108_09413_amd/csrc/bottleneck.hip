@@ -2,10 +2,10 @@
 //   t1 = clamp(requant(conv1x1(x)))                     Cin -> 64
 //   t2 = clamp(requant(conv3x3(t1)))                    64 -> 64, stride 1, pad 1
 //   y  = add_requant(clamp(requant(conv1x1(t2))), x)    64 -> Cout = Cin   (TAIL only)
-// A workgroup of four waves makes an 8 x 28 pixel tile of one image: 224 output pixels = seven full
+// A workgroup of eight waves makes 8 x 28 pixel tiles of images: 224 output pixels = seven full
 // 32-pixel MFMA fragments (no padding columns in the two later convolutions, whose requantisation
 // arithmetic is what bounds this kernel), 10 x 30 = 300 halo pixels = ten fragments for the first.
-//   1. The first convolution runs as a GEMM over the halo pixels (wave = 32 channels x 5 fragments):
+//   1. The first convolution runs as a GEMM over the halo pixels (wave = 32 channels x 3 or 2 fragments):
 //      K steps of 64 input channels go from global memory straight into two LDS stages.
 //      Recomputing the halo costs a third more of this (cheap) GEMM and saves writing and
 //      re-reading t1.
@@ -14,15 +14,18 @@
 //   3. The 3x3 convolution reads its pixel operands from that tile at tap-shifted addresses
 //      (no gather from memory) and its weights from LDS (fetched while step 2 runs, into
 //      the space of the two operand stages): 18 K steps of 32, no barrier inside
-//      (wave = 32 channels x 4 or 3 fragments).
+//      (wave = 32 channels x 2 or 1 fragments).
 //   4. HEAD: t2 is requantised and stored.  TAIL: t2 replaces t1 in LDS, and the last 1x1
-//      convolution + residual add is split over the waves by OUTPUT CHANNEL: each wave owns 64 of
-//      every 256 channels for all seven pixel fragments, so the four waves (one per SIMD) carry
-//      the same load; its weight fragments and per-channel constants are loaded once per 32
-//      channels, the pixel operands come from the t2 tile (held in registers), and the residual --
-//      x at the wave's own 64 channels, which are the input channels of one K step of step 1 -- was
+//      convolution + residual add is split over the waves by OUTPUT CHANNEL: each wave owns 32 of
+//      every 256 channels for all seven pixel fragments, so that all carry the same load; its weight fragments and
+//      multipliers are loaded once, the pixel operands come from the t2 tile, and the residual --
+//      x at the wave's own channels, input channels of one K step of step 1 -- was
 //      copied from that step's LDS stage into registers: x is read from memory once.
 // x is read once (plus halo, mostly cache hits), t1 and t2 never leave the CU.
+//
+// Bounds, 668 images of 56 x 56 x 256 (identity block): memory 1.07 GB = 210 us at the rate of a large copy, issue of the
+// requantisation and its data movement about 200 us, matrix unit 60 us, in phases that barriers separate.
+// Two workgroups of eight waves a CU instead of two of four: 344 -> 322 us (projection block 360 -> 340).
 #include "conv_device.h"
 
 namespace isr {
@@ -39,7 +42,7 @@ constexpr int W2_CHUNKS = 37;                  // 16-byte chunks per 3x3 weight 
 // MODE 0: head (t2 stored); 1: whole identity block (residual = x); 2: whole first block of a stage --
 // the residual is itself a 1x1 convolution of x (projection shortcut, Cin = 64), computed here as well.
 template <int MODE, int RQ, int RQA>
-__global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p) {
+__global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p) {
     constexpr bool TAIL = MODE != 0, PROJ = MODE == 2;
     constexpr int KB = 64, STAGE = (64 + 32 * NH_FR) * KB;            // 64 weight rows + 320 pixel rows per stage
     static_assert(64 * W2_CHUNKS * 16 <= 2 * STAGE, "3x3 weights fit the operand stages");
@@ -51,7 +54,9 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = lane & 31, half = lane >> 5;
-    const int wm = wave & 1, wn = wave >> 1;   // first two convolutions: 32 channels x one half of the fragments
+    // first two convolutions: 32 channels x a quarter of the fragments; waves w and w + 4 share a SIMD and together
+    // have the same number of fragments as the other pairs (five of the ten), resp. one more or less (seven)
+    const int wm = wave & 1, wn = wave >> 1;
     // tiles that share halo rows run on the same XCD (workgroup ids are dealt round-robin over 8 XCDs)
     const int nblk = gridDim.x;
     const int xcd = blockIdx.x & 7, per = nblk >> 3, extra = nblk & 7;
@@ -61,7 +66,7 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
     const int oy0 = (t / tiles_x) * TH, ox0 = (t % tiles_x) * TW;     // first output pixel of the tile
     const int y0 = oy0 - 1, x0 = ox0 - 1;                            // image position of halo pixel (0, 0)
 
-    for (int i = tid; i < 2 * 64; i += 256) {
+    for (int i = tid; i < 2 * 64; i += 512) {
         const int cv = i >> 6, c = i & 63;
         prm[cv][0][c] = (cv ? p.bias2 : p.bias1)[c];
         prm[cv][1][c] = (cv ? p.m0s2 : p.m0s1)[c];
@@ -70,35 +75,32 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
         prm[cv][3][c] = rq_sh<RQ>(shm1);
     }
     if constexpr (TAIL)
-        for (int i = tid; i < p.Cout_p; i += 256) {
+        for (int i = tid; i < p.Cout_p; i += 512) {
             prm3[0][i] = p.bias3[i]; prm3[1][i] = p.m0s3[i]; prm3[2][i] = rq_chi<RQ>(p.chi3[i], p.shm13[i]); prm3[3][i] = rq_sh<RQ>(p.shm13[i]);
             if constexpr (PROJ) { prmp[0][i] = p.biasp[i]; prmp[1][i] = p.m0sp[i]; prmp[2][i] = rq_chi<RQ>(p.chip[i], p.shm1p[i]); prmp[3][i] = rq_sh<RQ>(p.shm1p[i]); }
         }
 
     // ---- step 1: t1 accumulators over the halo, K = Cin_p in steps of 64 ----
     // LDS position (row, col) of a stage holds K chunk col ^ swz(row); a lane fetches the same
-    // chunk `cl` for all its rows (their numbers differ by multiples of 64)
+    // chunk `cl` for all its rows (their numbers differ by multiples of 128): the weight row tid / 4 (waves 0 .. 3) or
+    // pixel row tid / 4 - 64, and two more pixel rows
     const int col = tid & 3, row0 = tid >> 2, cl = col ^ swz<4>(row0);
-    const int8_t *wrow = p.w1 + (long)row0 * p.Cin_p + cl * 16;
-    uint32_t boff[5];
-    bool bok[5];
+    const int8_t *row[3];
+    bool inside[3];
 #pragma unroll
-    for (int j = 0; j < 5; ++j) {
-        const int h = row0 + 64 * j, hy = h / HW, hx = h - hy * HW, y = y0 + hy, x = x0 + hx;
-        bok[j] = h < NHALO && (unsigned)y < (unsigned)p.H && (unsigned)x < (unsigned)p.W;
-        boff[j] = bok[j] ? (uint32_t)((((long)b * p.H + y) * p.W + x) * p.Cin_p + cl * 16) : 0u;
+    for (int j = 0; j < 3; ++j) {
+        const int h = row0 + 128 * j - 64, hy = h / HW, hx = h - hy * HW, y = y0 + hy, x = x0 + hx;
+        inside[j] = h >= 0 && h < NHALO && (unsigned)y < (unsigned)p.H && (unsigned)x < (unsigned)p.W;
+        row[j] = p.in + (((long)b * p.H + y) * p.W + x) * p.Cin_p + cl * 16;
+        if (j == 0 && wave < 4) { inside[j] = true; row[j] = p.w1 + (long)row0 * p.Cin_p + cl * 16; }
+        // halo pixels outside the image (and the 20 columns past the halo): any readable bytes,
+        // their results are replaced in step 2 or never used
+        if (!inside[j]) row[j] = p.zpad;
     }
     auto issue = [&](int ks, int buf) {
-        int8_t *sa = &Ls[buf * STAGE + wave * 1024];
-        ISR_GLOBAL_TO_LDS16(wrow + ks * KB, sa);
-        int8_t *sb = sa + 64 * KB;
 #pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            // halo pixels outside the image (and the 20 columns past the halo): any readable bytes,
-            // their results are replaced in step 2 or never used
-            const int8_t *src = bok[j] ? p.in + (boff[j] + (uint32_t)(ks * KB)) : p.zpad;
-            ISR_GLOBAL_TO_LDS16(src, sb + j * 4096);
-        }
+        for (int j = 0; j < 3; ++j)
+            ISR_GLOBAL_TO_LDS16(row[j] + (inside[j] ? ks * KB : 0), &Ls[buf * STAGE + j * 8192 + wave * 1024]);
     };
     const int nk = p.Cin_p / KB;
     issue(0, 0);
@@ -106,59 +108,59 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
     __syncthreads();                    // prm visible
 
     const int c16 = wm * 32 + 16 * half;   // first of the lane's 16 channels in the first two convolutions
-    v16i acc[5];
+    const int f1 = wn * 3 - (wn == 3), n1 = wn < 2 ? 3 : 2;   // first fragment and their number: 3, 3, 2, 2
+    v16i acc[3];
     {
         v16i init;
 #pragma unroll
         for (int i = 0; i < 16; ++i) init[i] = prm[0][0][c16 + i];
 #pragma unroll
-        for (int f = 0; f < 5; ++f) acc[f] = init;
+        for (int f = 0; f < 3; ++f) acc[f] = init;
     }
-    // TAIL: the residual of the closing add is x itself.  Wave w will own output channels [64 w, 64 w + 64) there,
-    // which are exactly the input channels of K step w of this GEMM: while that step's pixel rows sit in the
-    // LDS stage the wave copies its residual values (its 64 channels of the seven fragments' pixels) into
-    // registers, so x is not read from memory a second time.
+    // TAIL: the residual of the closing add is x itself.  Wave w will own output channels [32 w, 32 w + 32) there,
+    // input channels of K step w / 2 of this GEMM: while that step's pixel rows sit in the LDS stage the wave copies
+    // its residual values (its 32 channels of the seven fragments' pixels) into registers, so x is not read from memory
+    // a second time.
     // (With a projection shortcut x has only 64 channels and is the pixel operand of a second GEMM: it is
-    // read again from memory -- cache hits, a fifth of the block's traffic at most -- rather than held in 56 registers.)
-    v4i resid[MODE == 1 ? NP_FR : 1][2];
+    // read again from memory -- cache hits, a fifth of the block's traffic at most.)
+    v4i resid[NP_FR];
     {
-        int aoff[2], boffs[2][5];   // [K half of the step][fragment]
+        int aoff[2], boffs[2][3];   // [K half of the step][fragment]
 #pragma unroll
         for (int ksub = 0; ksub < 2; ++ksub) {
             const int c = ksub * 2 + half;
             const int ra = wm * 32 + l;
             aoff[ksub] = ra * KB + ((c ^ swz<4>(ra)) << 4);
 #pragma unroll
-            for (int f = 0; f < 5; ++f) {
-                const int rb = (wn * 5 + f) * 32 + l;
+            for (int f = 0; f < 3; ++f) {
+                const int rb = (f1 + (f < n1 ? f : 0)) * 32 + l;
                 boffs[ksub][f] = 64 * KB + rb * KB + ((c ^ swz<4>(rb)) << 4);
             }
         }
         for (int ks = 0; ks < nk; ++ks) {
-            if (ks == 0 && nk > 1) wait_vmcnt<6>();   // step 0 landed; the 6 loads of step 1 may still be in flight
+            if (ks == 0 && nk > 1) wait_vmcnt<3>();   // step 0 landed; the 3 loads of step 1 may still be in flight
             else wait_vmcnt<0>();
             __builtin_amdgcn_s_barrier();   // every wave's loads of step ks landed; every wave is done with step ks - 1
             if (ks >= 1 && ks + 1 < nk) issue(ks + 1, (ks + 1) & 1);
             const int8_t *base = &Ls[(ks & 1) * STAGE];
             if constexpr (MODE == 1) {
-                if (ks == wave) {   // wave-uniform
+                if (ks == wave >> 1) {   // wave-uniform
 #pragma unroll
                     for (int f = 0; f < NP_FR; ++f) {
                         const int o = f * 32 + l, oy = o / TW, ox = o - oy * TW, hp = (oy + 1) * HW + ox + 1;   // the output pixel's own halo position
-#pragma unroll
-                        for (int mi = 0; mi < 2; ++mi)
-                            resid[f][mi] = *(const v4i *)(base + 64 * KB + hp * KB + (((mi * 2 + half) ^ swz<4>(hp)) << 4));
+                        resid[f] = *(const v4i *)(base + 64 * KB + hp * KB + (((wm * 2 + half) ^ swz<4>(hp)) << 4));
                     }
                 }
             }
 #pragma unroll
             for (int ksub = 0; ksub < 2; ++ksub) {
                 const v4i fa = *(const v4i *)(base + aoff[ksub]);
-                v4i fb[5];
+                v4i fb[3];
 #pragma unroll
-                for (int f = 0; f < 5; ++f) fb[f] = *(const v4i *)(base + boffs[ksub][f]);
+                for (int f = 0; f < 3; ++f) fb[f] = *(const v4i *)(base + boffs[ksub][f]);
 #pragma unroll
-                for (int f = 0; f < 5; ++f) acc[f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa, fb[f], acc[f], 0, 0, 0);
+                for (int f = 0; f < 3; ++f)
+                    if (f < 2 || n1 == 3) acc[f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa, fb[f], acc[f], 0, 0, 0);
             }
         }
     }
@@ -166,12 +168,12 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
 
     // 3x3 weights -> LDS (the space of the stages): row r at chunk r * 37, 36 chunks + 1 pad
     {
-        constexpr int TOTAL = 64 * W2_CHUNKS;            // 2368 = 9 * 256 + 64: the last pass is wave 0 alone
+        constexpr int TOTAL = 64 * W2_CHUNKS;            // 2368 = 4 * 512 + 5 * 64: the last pass is waves 0 .. 4
 #pragma unroll
-        for (int pass = 0; pass < (TOTAL + 255) / 256; ++pass) {
-            if (pass * 256 + wave * 64 < TOTAL) {        // wave-uniform
-                const int q = pass * 256 + tid, r = q / W2_CHUNKS, c = q % W2_CHUNKS;
-                ISR_GLOBAL_TO_LDS16(p.w2 + (long)r * 576 + (c < 36 ? c : 0) * 16, &Ls[(pass * 256 + wave * 64) * 16]);
+        for (int pass = 0; pass < (TOTAL + 511) / 512; ++pass) {
+            if (pass * 512 + wave * 64 < TOTAL) {        // wave-uniform
+                const int q = pass * 512 + tid, r = q / W2_CHUNKS, c = q % W2_CHUNKS;
+                ISR_GLOBAL_TO_LDS16(p.w2 + (long)r * 576 + (c < 36 ? c : 0) * 16, &Ls[(pass * 512 + wave * 64) * 16]);
             }
         }
     }
@@ -183,26 +185,27 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
 #pragma unroll
         for (int i = 0; i < 16; ++i) { mm[i] = prm[0][1][c16 + i]; ch[i] = prm[0][2][c16 + rq_chi_at<RQ>(i)]; ss[i] = prm[0][3][c16 + i]; }
 #pragma unroll
-        for (int f = 0; f < 5; ++f) {
-            const int h = (wn * 5 + f) * 32 + l, hy = h / HW, hx = h - hy * HW, y = y0 + hy, x = x0 + hx;
-            const bool inside = h < NHALO && (unsigned)y < (unsigned)p.H && (unsigned)x < (unsigned)p.W;
+        for (int f = 0; f < 3; ++f) {
+            if (f == 2 && n1 != 3) continue;   // wave-uniform
+            const int h = (f1 + f) * 32 + l, hy = h / HW, hx = h - hy * HW, y = y0 + hy, x = x0 + hx;
+            const bool ok = h < NHALO && (unsigned)y < (unsigned)p.H && (unsigned)x < (unsigned)p.W;
             int q[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(acc[f][i], mm[i], ch[i], ss[i], p.lo1);
             v4i v = rq_pack16<RQ>(q);
-            if (!inside) v = v4i{(int)zt, (int)zt, (int)zt, (int)zt};
+            if (!ok) v = v4i{(int)zt, (int)zt, (int)zt, (int)zt};
             *(v4i *)(&T[h * 64 + (((wm * 2 + half) ^ swz<4>(h)) << 4)]) = v;
         }
     }
     wait_vmcnt<0>();
     __syncthreads();   // t1 tile and 3x3 weights in LDS
 
-    // ---- step 3: 3x3 convolution from LDS: this wave's 32 channels x its 4 (wn = 0) or 3 (wn = 1) fragments ----
-    const int nfr = wn ? NP_FR - 4 : 4;   // wave-uniform
-    int hb[4];                            // halo pixel of tap (0, 0) of the lane's output pixel in fragment f
+    // ---- step 3: 3x3 convolution from LDS: this wave's 32 channels x its 2 (wn < 3) or 1 fragments ----
+    const int nfr = wn < 3 ? 2 : 1;   // wave-uniform
+    int hb[2];                            // halo pixel of tap (0, 0) of the lane's output pixel in fragment f
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
-        const int o = (wn * 4 + f) * 32 + l;
+    for (int f = 0; f < 2; ++f) {
+        const int o = (wn * 2 + f) * 32 + l;
         const int oo = o < TH * TW ? o : 0, oy = oo / TW, ox = oo - oy * TW;
         hb[f] = oy * HW + ox;
     }
@@ -211,32 +214,32 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
 #pragma unroll
         for (int i = 0; i < 16; ++i) init[i] = prm[1][0][c16 + i];
 #pragma unroll
-        for (int f = 0; f < 4; ++f) acc[f] = init;
+        for (int f = 0; f < 2; ++f) acc[f] = init;
     }
 #pragma unroll
     for (int ks = 0; ks < 18; ++ks) {
         const int tap = ks >> 1, ky = tap / 3, kx = tap % 3, cc = (ks & 1) * 2 + half;
         const v4i fa = *(const v4i *)(&Ls[((wm * 32 + l) * W2_CHUNKS + 2 * ks + half) * 16]);
-        v4i fb[4];
+        v4i fb[2];
 #pragma unroll
-        for (int f = 0; f < 4; ++f) {
+        for (int f = 0; f < 2; ++f) {
             const int hp = hb[f] + ky * HW + kx;
             fb[f] = *(const v4i *)(&T[hp * 64 + ((cc ^ swz<4>(hp)) << 4)]);
         }
 #pragma unroll
-        for (int f = 0; f < 4; ++f)
-            if (f < 3 || nfr == 4) acc[f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa, fb[f], acc[f], 0, 0, 0);
+        for (int f = 0; f < 2; ++f)
+            if (f < 1 || nfr == 2) acc[f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa, fb[f], acc[f], 0, 0, 0);
     }
 
     // ---- step 4: requantise t2 ----
-    v4i t2[4];
+    v4i t2[2];
     {
         int mm[16], ch[16], ss[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) { mm[i] = prm[1][1][c16 + i]; ch[i] = prm[1][2][c16 + rq_chi_at<RQ>(i)]; ss[i] = prm[1][3][c16 + i]; }
 #pragma unroll
-        for (int f = 0; f < 4; ++f) {
-            if (f == 3 && nfr != 4) { t2[f] = v4i{0, 0, 0, 0}; continue; }
+        for (int f = 0; f < 2; ++f) {
+            if (f == 1 && nfr != 2) { t2[f] = v4i{0, 0, 0, 0}; continue; }
             int q[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(acc[f][i], mm[i], ch[i], ss[i], p.lo2);
@@ -245,126 +248,94 @@ __global__ __launch_bounds__(256, 2) void bottleneck_kernel(const BneckParams p)
     }
     if constexpr (!TAIL) {
 #pragma unroll
-        for (int f = 0; f < 4; ++f) {
-            if (f == 3 && nfr != 4) continue;
-            const int o = (wn * 4 + f) * 32 + l, oy = o / TW, ox = o - oy * TW;
+        for (int f = 0; f < 2; ++f) {
+            if (f == 1 && nfr != 2) continue;
+            const int o = (wn * 2 + f) * 32 + l, oy = o / TW, ox = o - oy * TW;
             if (oy0 + oy < p.H && ox0 + ox < p.W)
                 *(v4i *)(p.out + (((long)b * p.H + oy0 + oy) * p.W + ox0 + ox) * 64 + c16) = t2[f];
         }
     } else {
         __syncthreads();   // every wave is done reading the t1 tile: t2 takes its place, [output pixel][64 channels]
 #pragma unroll
-        for (int f = 0; f < 4; ++f) {
-            if (f == 3 && nfr != 4) continue;
-            const int o = (wn * 4 + f) * 32 + l;
+        for (int f = 0; f < 2; ++f) {
+            if (f == 1 && nfr != 2) continue;
+            const int o = (wn * 2 + f) * 32 + l;
             *(v4i *)(&T[o * 64 + (((wm * 2 + half) ^ swz<4>(o)) << 4)]) = t2[f];
         }
         __syncthreads();   // the t2 tile is complete
 
-        // ---- last 1x1 convolution + residual add: this wave's output channels, all seven pixel fragments ----
+        // ---- last 1x1 convolution + residual add: this wave's 32 output channels, all seven pixel fragments ----
+        // Registers are short: one fragment at a time, its accumulators start from the bias in LDS, and the forms of the
+        // requantisation with three constants a channel read those there as well.
+        if (wave * 32 >= p.Cout_p) return;   // no barrier follows
         const AddConst ac = add_const<RQA>(p);
-        int opix[NP_FR];    // index (image, row, column) of the lane's pixel of fragment f; -1: outside the image
-        v4i fbt[PROJ ? 1 : NP_FR][2];  // the lane's pixel operands (64 channels of t2 = two K halves) of every fragment
+        const int m0 = wave * 32, c0 = m0 + 16 * half;   // the lane's 16 channels
+        // index (image, row, column) of the lane's pixel of fragment f; -1: outside the image
+        auto pixel = [&](int f) {
+            int o = f * 32 + l;
+            asm volatile("" : "+v"(o));   // worked out where it is used, not kept
+            const int oy = o / TW, ox = o - oy * TW;
+            return oy0 + oy < p.H && ox0 + ox < p.W ? (b * p.H + oy0 + oy) * p.W + ox0 + ox : -1;
+        };
+        // the fragments of one 1x1 convolution from 64 channels: operand(f, K half), then use(f, requantised values)
+        auto conv64 = [&](const int8_t *w, const auto &prm, int lo, auto operand, auto use) {
+            asm volatile("" ::: "memory");
+            v4i fa[2];
 #pragma unroll
-        for (int f = 0; f < NP_FR; ++f) {
-            const int o = f * 32 + l, oy = o / TW, ox = o - oy * TW;
-            const bool st = oy0 + oy < p.H && ox0 + ox < p.W;
-            opix[f] = st ? ((b * p.H + oy0 + oy) * p.W + ox0 + ox) : -1;
-            if constexpr (!PROJ) {
+            for (int ksub = 0; ksub < 2; ++ksub) fa[ksub] = *(const v4i *)(w + (long)(m0 + l) * 64 + ksub * 32 + half * 16);
+            int mm[16], ch[16], ss[16];
+            auto constants = [&]() {
 #pragma unroll
-                for (int ksub = 0; ksub < 2; ++ksub) fbt[f][ksub] = *(const v4i *)(&T[o * 64 + (((ksub * 2 + half) ^ swz<4>(o)) << 4)]);
-            }
-        }
-        // this wave's 64 output channels (Cout <= 256 = four waves x 64): two groups of 32
-        const int nmf = p.Cout_p >> 5;   // 32-channel groups of the output
-        // weight fragments of both groups, fetched before the first group's stores: a load issued behind stores
-        // waits for them as well (loads and stores share one counter)
-        v4i fa_pre[2][2];
-        if (2 * wave < nmf) {
+                for (int i = 0; i < 16; ++i) { mm[i] = prm[1][c0 + i]; ch[i] = prm[2][c0 + rq_chi_at<RQ>(i)]; ss[i] = prm[3][c0 + i]; }
+            };
+            if constexpr (rq_is_top(RQ)) constants();
 #pragma unroll
-            for (int g = 0; g < 2; ++g)
+            for (int f = 0; f < NP_FR; ++f) {
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+                v16i a;
 #pragma unroll
-                for (int ksub = 0; ksub < 2; ++ksub) {
-                    fa_pre[g][ksub] = *(const v4i *)(p.w3 + (long)((2 * wave + g) * 32 + l) * 64 + ksub * 32 + half * 16);
-                }
-        }
-        // one group of 32 output channels; mi is a compile-time constant for the identity block (it selects
-        // registers of the residual copy) and a loop variable for the projection block
-        auto channel_group = [&](auto mi) {
-            {
-                const int m0 = (2 * wave + (int)mi) * 32, c0 = m0 + 16 * half;   // the lane's 16 channels
-                v4i rpack[NP_FR];   // the residual of every fragment, packed int8
-                if constexpr (PROJ) {
-                    // projection shortcut first: r = clamp(requant(Wp x)), kept packed
-                    v4i fp[2];
+                for (int i = 0; i < 16; ++i) a[i] = prm[0][c0 + i];
 #pragma unroll
-                    for (int ksub = 0; ksub < 2; ++ksub) fp[ksub] = *(const v4i *)(p.wp + (long)(m0 + l) * 64 + ksub * 32 + half * 16);
-                    int mm[16], ch[16], ss[16];
-                    v16i init;
+                for (int ksub = 0; ksub < 2; ++ksub) a = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ksub], operand(f, ksub), a, 0, 0, 0);
+                if constexpr (!rq_is_top(RQ)) constants();
+                int q[16];
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) { init[i] = prmp[0][c0 + i]; mm[i] = prmp[1][c0 + i]; ch[i] = prmp[2][c0 + rq_chi_at<RQ>(i)]; ss[i] = prmp[3][c0 + i]; }
-                    v4i xn[2];   // x at the lane's pixel of the next fragment (pixels outside the image read pixel 0: in bounds, unused)
-#pragma unroll
-                    for (int ksub = 0; ksub < 2; ++ksub) xn[ksub] = *(const v4i *)(p.in + (long)(opix[0] >= 0 ? opix[0] : 0) * 64 + ksub * 32 + half * 16);
-#pragma unroll
-                    for (int f = 0; f < NP_FR; ++f) {
-                        if constexpr (rq_is_top(RQ)) __builtin_amdgcn_sched_barrier(0);   // one fragment at a time: without it registers spill
-                        const v4i x0 = xn[0], x1 = xn[1];
-                        if (f + 1 < NP_FR) {
-#pragma unroll
-                            for (int ksub = 0; ksub < 2; ++ksub) xn[ksub] = *(const v4i *)(p.in + (long)(opix[f + 1] >= 0 ? opix[f + 1] : 0) * 64 + ksub * 32 + half * 16);
-                        }
-                        v16i a = __builtin_amdgcn_mfma_i32_32x32x32_i8(fp[0], x0, init, 0, 0, 0);
-                        a = __builtin_amdgcn_mfma_i32_32x32x32_i8(fp[1], x1, a, 0, 0, 0);
-                        int q[16];
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(a[i], mm[i], ch[i], ss[i], p.lop);
-                        rpack[f] = rq_pack16<RQ>(q);
-                    }
-                } else {
-#pragma unroll
-                    for (int f = 0; f < NP_FR; ++f) rpack[f] = resid[f][decltype(mi)::value];
-                }
-                v4i fa[2];
-#pragma unroll
-                for (int ksub = 0; ksub < 2; ++ksub) fa[ksub] = mi == 0 ? fa_pre[0][ksub] : fa_pre[1][ksub];
-                int mm[16], ch[16], ss[16];
-                v16i init;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) { init[i] = prm3[0][c0 + i]; mm[i] = prm3[1][c0 + i]; ch[i] = prm3[2][c0 + rq_chi_at<RQ>(i)]; ss[i] = prm3[3][c0 + i]; }
-#pragma unroll
-                for (int f = 0; f < NP_FR; ++f) {
-                    const v4i res = rpack[f];
-                    v4i fb[2];
-                    if constexpr (PROJ) {   // the pixel operands are re-read from the t2 tile: the registers hold x
-                        const int o = f * 32 + l;
-#pragma unroll
-                        for (int ksub = 0; ksub < 2; ++ksub) fb[ksub] = *(const v4i *)(&T[o * 64 + (((ksub * 2 + half) ^ swz<4>(o)) << 4)]);
-                    } else {
-                        fb[0] = fbt[f][0]; fb[1] = fbt[f][1];
-                    }
-                    v16i a = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[0], fb[0], init, 0, 0, 0);
-                    a = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[1], fb[1], a, 0, 0, 0);
-                    int q[16];
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int qc = rq_conv<RQ>(a[i], mm[i], ch[i], ss[i], p.lo3);
-                        q[i] = rq_add<RQ, RQA>(qc, (uint32_t)res[i >> 2], i & 3, ac);
-                    }
-                    if (opix[f] >= 0)
-                        *(v4i *)(p.out + (long)opix[f] * p.Cout_p + c0) = rq_pack16<RQA>(q);
-                }
+                for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(a[i], mm[i], ch[i], ss[i], lo);
+                use(f, q);
             }
         };
-        if (2 * wave < nmf) {
-            if constexpr (PROJ) {
-#pragma unroll 1
-                for (int mi = 0; mi < 2; ++mi) channel_group(mi);
-            } else {
-                channel_group(std::integral_constant<int, 0>{});
-                channel_group(std::integral_constant<int, 1>{});
-            }
+        if constexpr (PROJ) {
+            // projection shortcut first: r = clamp(requant(Wp x)), kept packed; x at the lane's pixel is fetched a fragment
+            // ahead (pixels outside the image read pixel 0: in bounds, unused)
+            v4i xn[2], x[2];
+            auto fetch = [&](int f) {
+                const int px = pixel(f);
+#pragma unroll
+                for (int ksub = 0; ksub < 2; ++ksub) xn[ksub] = *(const v4i *)(p.in + (long)(px >= 0 ? px : 0) * 64 + ksub * 32 + half * 16);
+            };
+            fetch(0);
+            conv64(p.wp, prmp, p.lop, [&](int f, int ksub) {
+                if (ksub == 0) {
+                    x[0] = xn[0]; x[1] = xn[1];
+                    if (f + 1 < NP_FR) fetch(f + 1);
+                }
+                return x[ksub];
+            }, [&](int f, const int (&q)[16]) {
+                resid[f] = rq_pack16<RQ>(q);
+                asm volatile("" : "+v"(resid[f]));   // packed: the compiler would keep the sixteen values
+            });
         }
+        conv64(p.w3, prm3, p.lo3, [&](int f, int ksub) {
+            const int o = f * 32 + l;
+            return *(const v4i *)(&T[o * 64 + (((ksub * 2 + half) ^ swz<4>(o)) << 4)]);
+        }, [&](int f, const int (&qc)[16]) {
+            int q[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) q[i] = rq_add<RQ, RQA>(qc[i], (uint32_t)resid[f][i >> 2], i & 3, ac);
+            const int px = pixel(f);
+            if (px >= 0) *(v4i *)(p.out + (long)px * p.Cout_p + c0) = rq_pack16<RQA>(q);
+        });
     }
 }
 
@@ -387,7 +358,7 @@ hipError_t launch_bottleneck(const BneckParams &p, hipStream_t st) {
         return hipErrorInvalidValue;
     const long tiles = (long)p.B * ((p.H + TH - 1) / TH) * ((p.W + TW - 1) / TW);
     if (tiles > 0x7fffffffL || (long)p.B * p.H * p.W * (p.Cin_p > 64 ? p.Cin_p : 64) >= (1L << 31)) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)tiles), block(256);
+    const dim3 grid((unsigned)tiles), block(512);
     const int mode = p.tail ? (p.proj ? 2 : 1) : 0;
     static const char *const names[3][2] = {{"bottleneck_kernel<head, false>", "bottleneck_kernel<head, true>"},
                                             {"bottleneck_kernel<block, false>", "bottleneck_kernel<block, true>"},
