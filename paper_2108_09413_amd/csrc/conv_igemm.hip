@@ -412,11 +412,8 @@ static DmaTile pick_tile(const ConvParams &p) {
     if (forced == T256x256P && conv_patch_supported(p)) return T256x256P;
     static const char *deep = std::getenv("ISR_DEEP_TILE");   // A/B switch for tuning: W, H, N (no conv_patch.hip) or unset
     // 3x3 layers: the staged-rows kernel moves about 40 % fewer bytes into LDS per multiply (measured 7-10 % faster on
-    // the 14 x 14 and 28 x 28 layers of a ResNet-50); its tile is 256 pixels wide, so it wants launches that give
-    // at least half of the CUs a tile
-    if (!(deep && deep[0] == 'N') && conv_patch_supported(p) &&
-        ((long)(p.npix + 255) / 256) * ((p.Cout_p + 255) / 256) >= 128)
-        return T256x256P;
+    // the 14 x 14 and 28 x 28 layers of a ResNet-50), and in launches with few tiles it waits less per K step
+    if (!(deep && deep[0] == 'N') && conv_patch_supported(p)) return T256x256P;
     if (p.Cout_p > 128 && p.Kp < 1024) return T128x128;
     // cost of a candidate: workgroups per CU (rounded up: the last round costs a full
     // one) x tile area / relative K-loop throughput of the tile, as measured

@@ -25,7 +25,8 @@ constexpr int PBN = 256;                         // pixels per tile
 constexpr int PROWS = 320;                       // staged pixel rows per buffer: 256 + 2 (W + 1) <= 320 for W <= 31
 constexpr int PZBYTES = 256;                     // zero points behind them: one pass over the 64 LDS banks
 
-template <int BM, int KB, int MINB, int RQ, bool DUTY>
+// NAB: weight buffers; the weights of step t + NAB - 1 are fetched as step t begins.
+template <int BM, int KB, int NAB, int MINB, int RQ, bool DUTY>
 __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_kernel(const ConvParams p) {
     constexpr int WGM = BM / 64, NW = WGM * (PBN / 64), NT = NW * 64;
     constexpr int CPR = KB / 16;                 // 16-byte chunks per row
@@ -33,10 +34,11 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     constexpr int NA = BM / RPP;                 // weight loads per lane per step
     constexpr int KS = KB / 32;
     constexpr int ABUF = BM * KB, ZOFF = PROWS * KB, BBUF = ZOFF + PZBYTES;
-    static_assert(RPP == 128 && BM % RPP == 0 && (KB == 64 || KB == 128) && ZOFF % 256 == 0, "tile shape");
+    constexpr int BPP = (PROWS + RPP - 1) / RPP; // pixel rows of a lane
+    static_assert((RPP == 128 || (RPP == 64 && !DUTY)) && BM % RPP == 0 && (KB == 64 || KB == 128) && ZOFF % 256 == 0, "tile shape");
 
     __shared__ __attribute__((aligned(256))) int8_t Bs[2][BBUF];
-    __shared__ __attribute__((aligned(16))) int8_t As[2][ABUF];
+    __shared__ __attribute__((aligned(16))) int8_t As[NAB][ABUF];
     __shared__ __attribute__((aligned(16))) int prm_s[4][BM];   // bias, M0, chi, shift-1 of this M tile
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -93,7 +95,7 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     const int col = tid % CPR, row0 = tid / CPR;
     const int cl = col ^ swz<CPR>(row0);
     const int8_t *wrow[DUTY ? 1 : NA];
-    uint32_t prow[DUTY ? 1 : 3];
+    uint32_t prow[DUTY ? 1 : BPP];
     if constexpr (!DUTY) {
 #pragma unroll
         for (int j = 0; j < NA; ++j) {
@@ -102,13 +104,13 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
         }
         // staged row rho holds pixel n0 - halo + rho; pixels outside the tensor are clamped (only taps outside the image would read them)
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
+        for (int j = 0; j < BPP; ++j) {
             int g = n0 - halo + row0 + RPP * j;
             g = g < 0 ? 0 : (g >= p.npix ? p.npix - 1 : g);
             prow[j] = (uint32_t)g * (uint32_t)p.Cin_p + cl * 16;
         }
     }
-    // weights of step t = (slice, tap) into buffer t & 1
+    // weights of step t = (slice, tap) into buffer t mod NAB
     auto issue_a = [&](int slice, int tap, int buf) {
         if constexpr (DUTY) issue_a_duty(slice, tap, buf);
         else {
@@ -121,8 +123,14 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     // pass j (128 rows; the third pass covers rows 256..319 with the first half of the waves) of a slice's pixel rows
     auto issue_b = [&](int slice, int j, int buf) {
         if constexpr (DUTY) issue_b_duty(slice, j, buf);
-        else if (j < 2 || wave < NW / 2)
-            ISR_GLOBAL_TO_LDS16_AT(p.in + (prow[j] + (uint32_t)(slice * KB)), b_lds0 + wave * 1024 + buf * BBUF + j * (NT * 16));
+        else {
+#pragma unroll
+            for (int h = 0; h < 128 / RPP; ++h) {
+                const int r = j * (128 / RPP) + h;
+                if (r < BPP && (r + 1 < BPP || PROWS % RPP == 0 || wave < NW / 2))
+                    ISR_GLOBAL_TO_LDS16_AT(p.in + (prow[r < BPP ? r : 0] + (uint32_t)(slice * KB)), b_lds0 + wave * 1024 + buf * BBUF + r * (NT * 16));
+            }
+        }
     };
 
     if constexpr (DUTY) {
@@ -130,11 +138,14 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
         if (grp == 0) issue_a(0, 0, 0);
         if (grp == (NG == 4 ? 1 : 0)) { issue_b(0, 0, 0); issue_b(0, 2, 0); }
         if (grp == (NG == 4 ? 2 : 1)) issue_b(0, 1, 0);
-        if (grp == NG - 1) issue_a(0, 1, 1);   // step 1 is tap 1 of slice 0
+        // steps 1 .. are taps 1 .. of slice 0
+#pragma unroll
+        for (int u = 1; u < NAB; ++u)
+            if (grp == u % NG) issue_a(0, u, u);
     } else {
         issue_b(0, 0, 0); issue_b(0, 1, 0); issue_b(0, 2, 0);
-        issue_a(0, 0, 0);
-        issue_a(0, 1, 1);   // step 1 is tap 1 of slice 0
+#pragma unroll
+        for (int u = 0; u < NAB; ++u) issue_a(0, u, u);   // steps 0 .. are taps 0 .. of slice 0
     }
 
     for (int i = tid; i < BM; i += NT) {
@@ -202,22 +213,23 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
             brow[fn] = (inside[fn] >> tap & 1) ? off : ZOFF + (off & (PZBYTES - 1));
         }
     };
-    // the loads that follow the barrier of step u = (slice, tap): the weights of step u + 1 into the buffer that step
+    // the loads that follow the barrier of step u = (slice, tap): the weights of step u + NAB - 1 into the buffer that step
     // u - 1 used, and, during the first three taps of a slice, a pass of the next slice's pixel rows into the
     // activation buffer that was last read in the previous slice
     auto refill = [&](int u, int slice, int tap) {
         if (!DUTY || (u & (NG - 1)) == grp) {
-            if (u >= 1 && u + 1 < nk) {
-                const int nt = tap + 1 == 9 ? 0 : tap + 1;
-                issue_a(slice + (tap + 1 == 9 ? 1 : 0), nt, (u + 1) & 1);
+            if (u >= 1 && u + NAB - 1 < nk) {
+                const int nt = tap + NAB - 1, wrap = nt >= 9;
+                issue_a(slice + wrap, wrap ? nt - 9 : nt, (u + NAB - 1) % NAB);
             }
             if (tap < 3 && slice + 1 < nslice) issue_b(slice + 1, tap, (slice + 1) & 1);
         }
     };
 
     // K loop with the fragment reads one sub-step ahead of the MFMAs (two register sets).  Before a step's barrier
-    // a wave waits for its own loads of that step (step 1's weights, issued last before the loop, may still be in
-    // flight at step 0).  At the last sub-step of a step the wave holds that sub-step's fragments already: it
+    // a wave waits for its own loads of that step.  Loads complete in issue order: the weights that it has fetched for
+    // later steps may still be in flight (PENDING loads while all those steps exist; pixel rows fetched in between
+    // make the wait longer than it need be, never shorter).  At the last sub-step of a step the wave holds that sub-step's fragments already: it
     // passes the next step's barrier, issues its refill and reads the next step's first fragments BEFORE it issues
     // those four MFMAs, so the matrix pipe has work queued while the workgroup goes through barrier, refill and
     // the first fragment reads (measured +1 to +3 % over reading each sub-step's fragments right before its MFMAs).
@@ -231,7 +243,8 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     };
     int slice = 0, tap = 0;
     int brow[2];
-    if (!DUTY) wait_vmcnt<NA>();
+    constexpr int PENDING = DUTY ? (NAB - 2) / NG * LA : (NAB - 2) * NA;
+    if (!DUTY) wait_vmcnt<(NAB - 1) * NA>();
     else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();   // step 0 landed
     refill(0, 0, 0);
@@ -239,7 +252,7 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     read_fragments(As[0], Bs[0], brow, 0, 0);
 #pragma unroll 1
     for (int t = 0; t < nk; ++t) {
-        const int8_t *abase = As[t & 1], *bbase = Bs[slice & 1];
+        const int8_t *abase = As[t % NAB], *bbase = Bs[slice & 1];
 #pragma unroll
         for (int ksub = 0; ksub < KS; ++ksub) {
             const int slot = ksub & 1;
@@ -247,12 +260,13 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
                 read_fragments(abase, bbase, brow, ksub + 1, slot ^ 1);
             } else if (t + 1 < nk) {
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of step t are complete
-                wait_vmcnt<0>();
+                if (PENDING > 0 && t + NAB - 1 < nk) wait_vmcnt<PENDING>();
+                else wait_vmcnt<0>();
                 __builtin_amdgcn_s_barrier();   // every wave's loads of step t + 1 landed; every wave is done reading step t
                 if (++tap == 9) { tap = 0; ++slice; }
                 refill(t + 1, slice, tap);
                 tap_rows(tap, brow);
-                read_fragments(As[(t + 1) & 1], Bs[slice & 1], brow, 0, slot ^ 1);
+                read_fragments(As[(t + 1) % NAB], Bs[slice & 1], brow, 0, slot ^ 1);
             }
 #pragma unroll
             for (int fm = 0; fm < 2; ++fm)
@@ -285,13 +299,13 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     }
 }
 
-template <int BM, int KB, int MINB, bool DUTY>
+template <int BM, int KB, int NAB, int MINB, bool DUTY>
 hipError_t launch_patch(const ConvParams &p, hipStream_t st, const char *name) {
     const dim3 grid((unsigned)(((p.npix + PBN - 1) / PBN) * ((p.Cout_p + BM - 1) / BM)));
     const dim3 block((BM / 64) * (PBN / 64) * 64);
     set_kernel_name(name);
     with_rq(p.rq, [&](auto rq) {
-        hipLaunchKernelGGL((conv_patch_kernel<BM, KB, MINB, decltype(rq)::value, DUTY>), grid, block, 0, st, p);
+        hipLaunchKernelGGL((conv_patch_kernel<BM, KB, NAB, MINB, decltype(rq)::value, DUTY>), grid, block, 0, st, p);
     });
     return hipGetLastError();
 }
@@ -308,14 +322,20 @@ bool conv_patch_supported(const ConvParams &p) {
     return p.Cout_p == 128 && p.kb == 64 && p.Cin_p % 64 == 0;
 }
 
+// tiles of 256 pixels x 256 channels
+static long conv_patch_tiles(const ConvParams &p) { return ((long)p.npix + PBN - 1) / PBN * ((p.Cout_p + 255) / 256); }
+
 hipError_t launch_conv_patch(const ConvParams &p, hipStream_t st) {
     if (p.npix <= 0) return hipSuccess;
     if (!conv_patch_supported(p) || p.Mp < p.Cout_p) return hipErrorInvalidValue;
     // One issuing wave per SIMD and step pays with two workgroups per CU (the other workgroup computes while that wave
     // is held at its loads: 1720 -> 1810 TOP/s on 3x3 128 -> 128 at 28 x 28); with one workgroup per CU the issuing
     // wave, which still has its own MFMAs to do, becomes the last to reach the barrier (2120 -> 2060).
-    if (p.Cout_p >= 256) return launch_patch<256, 128, 1, false>(p, st, "conv_patch_kernel<256, 256, 128>");
-    return launch_patch<128, 64, 2, true>(p, st, "conv_patch_kernel<128, 256, 64>");
+    if (p.Cout_p < 256) return launch_patch<128, 64, 4, 2, true>(p, st, "conv_patch_kernel<128, 256, 64>");
+    // Launches with tiles for less than half of the CUs are a chain of K steps that wait for weights, which nobody has
+    // brought into the caches before: half the channels per workgroup, weights fetched three steps ahead.
+    if (conv_patch_tiles(p) < 128) return launch_patch<128, 128, 4, 1, false>(p, st, "conv_patch_kernel<128, 256, 128>");
+    return launch_patch<256, 128, 2, 1, false>(p, st, "conv_patch_kernel<256, 256, 128>");
 }
 
 }  // namespace isr

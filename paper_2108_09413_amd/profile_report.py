@@ -43,27 +43,37 @@ def library_name(profiler_name: str) -> str:
     """The name the library's timing report uses for a kernel as the profiler prints it."""
     n = profiler_name.replace("void ", "").replace("isr::", "").replace("(anonymous namespace)::", "")
     n = re.sub(r"\(.*\)$", "", n)
-    m = re.match(r"conv_dma_kernel<(\d+), (\d+), (\d+), (\d+), (\d+), (\d+), (?:true|false), (\d+), (\d+)(?:, (?:true|false))?>", n)
+    form = r"(?:true|false|\d)"     # form of a requantisation
+    m = re.match(r"conv_dma_kernel<(\d+), (\d+), (\d+), (\d+), (\d+), (\d+), %s, (\d+), (\d+)(?:, %s)?>" % (form, form), n)
     if m:
         return "conv_dma_kernel<%s, %s, %s, %s, %s, %s, %sx%s>" % m.groups()
-    m = re.match(r"conv_patch_kernel<(\d+), (\d+), \d+, (?:true|false), (?:true|false)>", n)
+    m = re.match(r"conv_patch_kernel<(\d+), (\d+)(?:, \w+)+>", n)
     if m:
         return "conv_patch_kernel<%s, 256, %s>" % m.groups()      # channels x pixels of the tile, K bytes per step
-    if re.match(r"proj_expand_reduce_kernel<(?:true|false)>", n):
+    forms = r"<%s(?:, %s)?>" % (form, form)
+    if re.match("proj_expand_reduce_kernel" + forms, n):
         return "proj_expand_reduce_kernel<256, 128, 512, 128>"     # block input, middle, block and next middle channels
-    if re.match(r"expand_reduce1024_kernel<(?:true|false)>", n):
+    if re.match("expand_reduce1024_kernel" + forms, n):
         return "expand_reduce_kernel<256, 1024, 256>"
-    if re.match(r"expand_reduce256_kernel<(?:true|false)>", n):
+    if re.match("expand_reduce256_kernel" + forms, n):
         return "expand_reduce_kernel<128, 512, 256>"
-    if re.match(r"expand_reduce_kernel<(?:true|false)>", n):
+    if re.match("expand_reduce_kernel" + forms, n):
         return "expand_reduce_kernel<128, 512, 128>"               # middle, block and next middle channels
     m = re.match(r"bottleneck_kernel<(\d), (true|false)>", n)
     if m:
         return "bottleneck_kernel<%s, %s>" % (MODES[m.group(1)], m.group(2))
+    m = re.match(r"bottleneck_kernel<(\d), (\d), (\d)>", n)
+    if m:
+        exact_halves = m.group(2) in "02" or (m.group(1) != "0" and m.group(3) == "0")
+        return "bottleneck_kernel<%s, %s>" % (MODES[m.group(1)], "false" if exact_halves else "true")
     m = re.match(r"fconv_kernel<(\d), (\d), (\d), (\d)>", n)
     if m:
         mt, nt, wm, wn = map(int, m.groups())
         return "fconv_kernel<%d x %d>" % (32 * mt * wm, 32 * nt * wn)
+    m = re.match(r"fconv_kernel<(\d), (\d), \d>", n)
+    if m:
+        return "fconv_kernel<%d x %d>" % (32 * int(m.group(1)), 128 * int(m.group(2)))
+    n = re.sub(r"^stem_pool_kernel<\d>$", "stem_pool_kernel", n)
     if n == "stem_pool_kernel":
         return "stem_pool_kernel (+noise)"      # the default plan of the 224 x 224 workload draws the noise in this kernel
     return n

@@ -864,6 +864,26 @@ def test_3x3_layers_with_staged_pixel_rows_against_the_oracle(isr, in_shape, str
     m.close()
 
 
+@pytest.mark.parametrize("copies", [1, 9, 165, 168])
+def test_staged_rows_in_launches_of_few_and_many_tiles(isr, copies):
+    """127 tiles of 256 pixels x 256 channels and fewer (128 channels a workgroup, weights three K steps ahead), 129 and
+    more (256 channels): one to four slices of 128 channels, against the implicit-GEMM tile."""
+    _say(f"staged rows, {copies} copies")
+    b = NetBuilder(rng=np.random.default_rng(78), in_shape=(3, 28, 28), num_classes=9)
+    t = b.conv(b.tensor(3, 28, 28, 0, 74.0), 128, 3, 2, 1, True)
+    t = b.conv(b.conv(b.conv(t, 256, 3, 1, 1, True), 512, 3, 1, 1, True), 256, 3, 1, 1, False)
+    b.fc(b.conv(t, 16, 1, 1, 0, True), 9)
+    m = _load(isr, b.blob(), copies)
+    x = np.random.default_rng(79).integers(0, 256, size=(3, 28, 28)).astype(np.uint8)
+    out = []
+    for tile in (7, 1, 0):
+        isr.isr_set_conv_tile(m, tile)
+        out.append(isr.isr_debug_forward(m, x, 64, 2, 1, 1, 3, copies))
+    for lg, am, cnt in out[1:]:
+        assert np.array_equal(lg, out[0][0]) and np.array_equal(am, out[0][1]) and np.array_equal(cnt, out[0][2])
+    m.close()
+
+
 def test_expand_add_and_next_reduce_in_one_kernel(isr):
     """The kernels that run a block's closing 1x1 (128 -> 512) + residual add and the next block's opening 1x1
     (512 -> 128, or 256 for the first block of a next stage) on pixel tiles of all 512 channels.  Seven such pairs in a row (the last two with the 14x14 stage's 256 / 1024 channels): a first block whose residual is
