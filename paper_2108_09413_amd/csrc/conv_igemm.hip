@@ -452,6 +452,8 @@ hipError_t launch_conv(const ConvParams &p, hipStream_t st) {
             // shallow layers are epilogue-bound: two steps in flight suffice and a fourth
             // workgroup per CU hides more of the epilogue's memory latency
             if (!p.fuse_add && p.Kp < 1024 && !k128) return launch_dma<128, 128, 64, 2, 4>(p, st);
+            // one workgroup a CU has the LDS for three steps of 128 bytes
+            if (k128 && ((p.npix + 127) / 128) * ((p.Cout_p + 127) / 128) <= 256) return launch_dma<128, 128, 128, 3, 1>(p, st);
             return k128 ? launch_dma<128, 128, 128, 2, 2>(p, st) : launch_dma<128, 128, 64, 3, 3>(p, st);
         case T128x256:
             return k128 ? launch_dma<128, 256, 128, 2, 1>(p, st) : launch_dma<128, 256, 64, 3, 2>(p, st);
