@@ -274,6 +274,11 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
         }
     };
 
+    // one constant of the epilogue per thread: bias [BM], scale [BM]
+    static_assert(2 * BM <= 256 && 8 * BM <= STAGE, "one constant a thread, into one stage");
+    float bias_or_scale = 0.0f;
+    if (tid < 2 * BM) bias_or_scale = (tid < BM ? p.bias : p.scale)[ch0 + (tid < BM ? tid : tid - BM)];
+
     v16f acc[MT][NT];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -312,36 +317,66 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
         }
     }
 
-    // epilogue: with the weight rows in MFMA row order a lane holds 16 consecutive channels of one pixel
+    // Epilogue: with the weight rows in MFMA row order a lane holds 16 consecutive channels of one pixel.  Bias and scale come
+    // from LDS (the stage that the last step did not use), the residual is read three groups of 16 channels ahead: a load
+    // waits for the stores issued before it, and with bias, scale and residual loaded where they are used each of the 8 MT
+    // stores of a wave was waited for in turn (64 -> 256 with residual, 668 copies of 56 x 56: 1285 -> 1140 us).
+    float *bs = (float *)(lds + (nsteps & 1) * STAGE);
+    if (tid < 2 * BM) bs[tid] = bias_or_scale;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const float lo = p.relu ? 0.0f : -INFINITY, add_lo = p.add_relu ? 0.0f : -INFINITY;
+    auto finish = [&](auto full, auto with_res) {
+        constexpr bool FULL = decltype(full)::value, RES = decltype(with_res)::value;   // FULL: every pixel and channel of the tile exists
+        constexpr int U = NT * MT, AHEAD = 3;
+        long at[NT];
+        bool ok[NT];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
-        const long P = px0 + (wave * NT + j) * 32 + l32;
-        if (P >= p.npix) continue;
+        for (int j = 0; j < NT; ++j) {
+            const long P = px0 + (wave * NT + j) * 32 + l32;
+            ok[j] = FULL || P < p.npix;
+            at[j] = (ok[j] ? P : 0) * p.Cout_p + ch0 + 16 * half;
+        }
+        // Cout_p is a multiple of 16: the run of a lane is stored whole or not at all
+        auto there = [&](int u) { return FULL || (ok[u / MT] && ch0 + (u % MT) * 32 + 16 * half < p.Cout_p); };
+        v4f r[RES ? AHEAD + 1 : 1][4];
+        auto fetch = [&](int u) {
+            const float *src = p.res + (there(u) ? at[u / MT] + (u % MT) * 32 : 0);
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            const int chb = ch0 + i * 32 + 16 * half;
-            if (chb >= p.Cout_p) continue;                     // Cout_p is a multiple of 16: the run is stored whole or not at all
+            for (int g = 0; g < 4; ++g) r[RES ? u % (AHEAD + 1) : 0][g] = *(const v4f *)(src + 4 * g);
+        };
+        if constexpr (RES)
+#pragma unroll
+            for (int u = 0; u < AHEAD && u < U; ++u) fetch(u);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = u % MT, j = u / MT, ch = i * 32 + 16 * half;
+            if constexpr (RES)
+                if (u + AHEAD < U) fetch(u + AHEAD);
+            __builtin_amdgcn_sched_barrier(0);
+            v4f t[4];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const int ch = chb + 4 * g;
-                const v4f bias = *(const v4f *)(p.bias + ch), scale = *(const v4f *)(p.scale + ch);
-                v4f t;
+                const v4f bias = *(const v4f *)(bs + ch + 4 * g), scale = *(const v4f *)(bs + BM + ch + 4 * g);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    t[e] = (acc[i][j][4 * g + e] + bias[e]) * scale[e];
-                    if (p.relu) t[e] = fmaxf(t[e], 0.0f);
+                    t[g][e] = fmaxf((acc[i][j][4 * g + e] + bias[e]) * scale[e], lo);
+                    if constexpr (RES) t[g][e] = fmaxf(p.ma * t[g][e] + p.mb * r[u % (AHEAD + 1)][g][e], add_lo);
                 }
-                if (p.res) {
-                    const v4f r = *(const v4f *)(p.res + P * p.Cout_p + ch);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        t[e] = p.ma * t[e] + p.mb * r[e];
-                        if (p.add_relu) t[e] = fmaxf(t[e], 0.0f);
-                    }
-                }
-                *(v4f *)(p.out + P * p.Cout_p + ch) = t;
             }
+            if (there(u))
+#pragma unroll
+                for (int g = 0; g < 4; ++g) *(v4f *)(p.out + at[j] + i * 32 + 4 * g) = t[g];
         }
+    };
+    const bool full = px0 + BN <= p.npix && ch0 + BM <= p.Cout_p;
+    if (p.res) {
+        if (full) finish(std::true_type{}, std::true_type{});
+        else finish(std::false_type{}, std::true_type{});
+    } else {
+        if (full) finish(std::true_type{}, std::false_type{});
+        else finish(std::false_type{}, std::false_type{});
     }
 }
 
