@@ -66,20 +66,6 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
     const int oy0 = (t / tiles_x) * TH, ox0 = (t % tiles_x) * TW;     // first output pixel of the tile
     const int y0 = oy0 - 1, x0 = ox0 - 1;                            // image position of halo pixel (0, 0)
 
-    for (int i = tid; i < 2 * 64; i += 512) {
-        const int cv = i >> 6, c = i & 63;
-        prm[cv][0][c] = (cv ? p.bias2 : p.bias1)[c];
-        prm[cv][1][c] = (cv ? p.m0s2 : p.m0s1)[c];
-        const int shm1 = (cv ? p.shm12 : p.shm11)[c];
-        prm[cv][2][c] = rq_chi<RQ>((cv ? p.chi2 : p.chi1)[c], shm1);
-        prm[cv][3][c] = rq_sh<RQ>(shm1);
-    }
-    if constexpr (TAIL)
-        for (int i = tid; i < p.Cout_p; i += 512) {
-            prm3[0][i] = p.bias3[i]; prm3[1][i] = p.m0s3[i]; prm3[2][i] = rq_chi<RQ>(p.chi3[i], p.shm13[i]); prm3[3][i] = rq_sh<RQ>(p.shm13[i]);
-            if constexpr (PROJ) { prmp[0][i] = p.biasp[i]; prmp[1][i] = p.m0sp[i]; prmp[2][i] = rq_chi<RQ>(p.chip[i], p.shm1p[i]); prmp[3][i] = rq_sh<RQ>(p.shm1p[i]); }
-        }
-
     // ---- step 1: t1 accumulators over the halo, K = Cin_p in steps of 64 ----
     // LDS position (row, col) of a stage holds K chunk col ^ swz(row); a lane fetches the same
     // chunk `cl` for all its rows (their numbers differ by multiples of 128): the weight row tid / 4 (waves 0 .. 3) or
@@ -105,7 +91,23 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
     const int nk = p.Cin_p / KB;
     issue(0, 0);
     if (nk > 1) issue(1, 1);            // both stages are free at the start
-    __syncthreads();                    // prm visible
+    // the constants, all on their way behind the first operands before any is waited for
+    {
+        const int cv = (tid >> 6) & 1, c = tid & 63, ct = tid < p.Cout_p ? tid : 0;
+        const RqRaw r12 = cv ? rq_fetch(p.bias2, p.m0s2, p.chi2, p.shm12, c) : rq_fetch(p.bias1, p.m0s1, p.chi1, p.shm11, c);
+        RqRaw r3{}, rp{};
+        if constexpr (TAIL) r3 = rq_fetch(p.bias3, p.m0s3, p.chi3, p.shm13, ct);
+        if constexpr (PROJ) rp = rq_fetch(p.biasp, p.m0sp, p.chip, p.shm1p, ct);
+        if (tid < 128) rq_store<RQ>(prm[cv], r12, c);
+        if constexpr (TAIL)
+            if (tid < p.Cout_p) {
+                rq_store<RQ>(prm3, r3, ct);
+                if constexpr (PROJ) rq_store<RQ>(prmp, rp, ct);
+            }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();       // prm visible (the operands need not have landed)
+    asm volatile("" ::: "memory");
 
     const int c16 = wm * 32 + 16 * half;   // first of the lane's 16 channels in the first two convolutions
     const int f1 = wn * 3 - (wn == 3), n1 = wn < 2 ? 3 : 2;   // first fragment and their number: 3, 3, 2, 2

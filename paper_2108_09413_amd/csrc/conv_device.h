@@ -202,6 +202,19 @@ void with_rq(int rq, F f) {
     else f(integral_constant<int, RQ_ANY>{});
 }
 
+// One channel's requantisation constants as the model holds them, fetched before and stored to LDS in a kernel's form
+// after the loads that a workgroup starts with: a store waits for its loads, and the loads behind it start that much later.
+struct RqRaw {
+    int bias, m0s, chi, shm1;
+};
+__device__ __forceinline__ RqRaw rq_fetch(const int *bias, const int *m0s, const int *chi, const int *shm1, int c) {
+    return {bias[c], m0s[c], chi[c], shm1[c]};
+}
+template <int RQ, class Prm>
+__device__ __forceinline__ void rq_store(Prm &prm, const RqRaw &r, int c) {
+    prm[0][c] = r.bias; prm[1][c] = r.m0s; prm[2][c] = rq_chi<RQ>(r.chi, r.shm1); prm[3][c] = rq_sh<RQ>(r.shm1);
+}
+
 // 16 bytes per lane from global memory into LDS: lane l of the wave writes bytes
 // [16 l, 16 l + 16) after the wave-uniform LDS address `lptr`.
 #define ISR_GLOBAL_TO_LDS16(gptr, lptr)                                                             \

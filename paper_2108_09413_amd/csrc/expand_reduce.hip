@@ -75,12 +75,9 @@ __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p)
     int tile = blockIdx.x;
     if (tile < ntiles) issue_tile(tile, 0);
     if (tile + G < ntiles) issue_tile(tile + G, 1);
-    for (int i = tid; i < XC; i += XNT) {
-        prm1[0][i] = p.bias1[i]; prm1[1][i] = p.m0s1[i]; prm1[2][i] = rq_chi<RQ>(p.chi1[i], p.shm11[i]); prm1[3][i] = rq_sh<RQ>(p.shm11[i]);
-    }
-    if (tid < XN2) {
-        prm2[0][tid] = p.bias2[tid]; prm2[1][tid] = p.m0s2[tid]; prm2[2][tid] = rq_chi<RQ>(p.chi2[tid], p.shm12[tid]); prm2[3][tid] = rq_sh<RQ>(p.shm12[tid]);
-    }
+    // constants and weights, all on their way before any is waited for
+    const int i1 = tid < XC ? tid : 0, i2 = tid < XN2 ? tid : 0;
+    const RqRaw r1 = rq_fetch(p.bias1, p.m0s1, p.chi1, p.shm11, i1), r2 = rq_fetch(p.bias2, p.m0s2, p.chi2, p.shm12, i2);
     // weight fragments, kept in registers for the whole launch: expand [fm][ksub] (32 output channels x 32 K bytes
     // each), reduce [kstep] (16 output channels x 64 K bytes each)
     const uint32_t lane16 = (uint32_t)lane * 16;
@@ -92,6 +89,8 @@ __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p)
             a1[fm][ks] = *(const v4i *)(p.a1 + (size_t)wave * (2 * (XK1 / 32) * 1024) + (lane16 + (uint32_t)((fm * (XK1 / 32) + ks) * 1024)));
 #pragma unroll
     for (int ks = 0; ks < XC / 64; ++ks) a2[ks] = *(const v4i *)(p.a2 + (size_t)wave * (XC / 64) * 1024 + (lane16 + (uint32_t)(ks * 1024)));
+    if (tid < XC) rq_store<RQ>(prm1, r1, i1);
+    if (tid < XN2) rq_store<RQ>(prm2, r2, i2);
     wait_vmcnt<0>();
     __syncthreads();   // the constants are in LDS, the first tile has landed
 
@@ -231,13 +230,10 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
     int tile = blockIdx.x;
     if (tile < ntiles) issue_tile(tile, 0);
     if (tile + G < ntiles) issue_tile(tile + G, 1);
-    for (int i = tid; i < XC; i += XNT2) {
-        prm1[0][i] = p.bias1[i]; prm1[1][i] = p.m0s1[i]; prm1[2][i] = rq_chi<RQ>(p.chi1[i], p.shm11[i]); prm1[3][i] = rq_sh<RQ>(p.shm11[i]);
-        prmp[0][i] = p.biasp[i]; prmp[1][i] = p.m0sp[i]; prmp[2][i] = rq_chi<RQ>(p.chip[i], p.shm1p[i]); prmp[3][i] = rq_sh<RQ>(p.shm1p[i]);
-    }
-    if (tid < XN2) {
-        prm2[0][tid] = p.bias2[tid]; prm2[1][tid] = p.m0s2[tid]; prm2[2][tid] = rq_chi<RQ>(p.chi2[tid], p.shm12[tid]); prm2[3][tid] = rq_sh<RQ>(p.shm12[tid]);
-    }
+    // constants and weights, all on their way before any is waited for
+    const int i1 = tid < XC ? tid : 0, i2 = tid < XN2 ? tid : 0;
+    const RqRaw r1 = rq_fetch(p.bias1, p.m0s1, p.chi1, p.shm11, i1), r2 = rq_fetch(p.bias2, p.m0s2, p.chi2, p.shm12, i2);
+    const RqRaw rp = rq_fetch(p.biasp, p.m0sp, p.chip, p.shm1p, i1);
     // weight fragments, kept in registers for the whole launch: wave w owns channels 32 w .. 32 w + 31 of the expanding
     // convolution [ksub] and of the projection [ksub], and 16 channels x 16 pixels of the reducing convolution [kstep]
     const uint32_t lane16 = (uint32_t)lane * 16;
@@ -248,6 +244,11 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
     for (int ks = 0; ks < XPK / 32; ++ks) ap[ks] = *(const v4i *)(p.ap + (size_t)wave * (XPK / 32) * 1024 + (lane16 + (uint32_t)(ks * 1024)));
 #pragma unroll
     for (int ks = 0; ks < XC / 64; ++ks) a2[ks] = *(const v4i *)(p.a2 + (size_t)(wave >> 1) * (XC / 64) * 1024 + (lane16 + (uint32_t)(ks * 1024)));
+    if (tid < XC) {
+        rq_store<RQ>(prm1, r1, i1);
+        rq_store<RQ>(prmp, rp, i1);
+    }
+    if (tid < XN2) rq_store<RQ>(prm2, r2, i2);
     wait_vmcnt<0>();
     __syncthreads();   // the constants are in LDS, the first tile has landed
 
@@ -394,18 +395,17 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
     int tile = blockIdx.x;
     if (tile < ntiles) issue_tile(tile, 0);
     if (tile + G < ntiles) issue_tile(tile + G, 1);
-    for (int i = tid; i < XC; i += XNT2) {
-        prm1[0][i] = p.bias1[i]; prm1[1][i] = p.m0s1[i]; prm1[2][i] = rq_chi<RQ>(p.chi1[i], p.shm11[i]); prm1[3][i] = rq_sh<RQ>(p.shm11[i]);
-    }
-    if (tid < XN2W) {
-        prm2[0][tid] = p.bias2[tid]; prm2[1][tid] = p.m0s2[tid]; prm2[2][tid] = rq_chi<RQ>(p.chi2[tid], p.shm12[tid]); prm2[3][tid] = rq_sh<RQ>(p.shm12[tid]);
-    }
+    // constants and weights, all on their way before any is waited for
+    const int i1 = tid < XC ? tid : 0, i2 = tid < XN2W ? tid : 0;
+    const RqRaw r1 = rq_fetch(p.bias1, p.m0s1, p.chi1, p.shm11, i1), r2 = rq_fetch(p.bias2, p.m0s2, p.chi2, p.shm12, i2);
     const uint32_t lane16 = (uint32_t)lane * 16;
     v4i a1[XK1 / 32], a2[XC / 64];   // weight fragments, kept in registers for the whole launch
 #pragma unroll
     for (int ks = 0; ks < XK1 / 32; ++ks) a1[ks] = *(const v4i *)(p.a1 + (size_t)wave * (XK1 / 32) * 1024 + (lane16 + (uint32_t)(ks * 1024)));
 #pragma unroll
     for (int ks = 0; ks < XC / 64; ++ks) a2[ks] = *(const v4i *)(p.a2 + (size_t)wave * (XC / 64) * 1024 + (lane16 + (uint32_t)(ks * 1024)));
+    if (tid < XC) rq_store<RQ>(prm1, r1, i1);
+    if (tid < XN2W) rq_store<RQ>(prm2, r2, i2);
     wait_vmcnt<0>();
     __syncthreads();   // the constants are in LDS, the first tile has landed
 
@@ -543,12 +543,9 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
     int tile = blockIdx.x;
     if (tile < ntiles) issue_tile(tile, 0);
     if (tile + G < ntiles) issue_tile(tile + G, 1);
-    for (int i = tid; i < DC; i += XNT2) {
-        prm1[0][i] = p.bias1[i]; prm1[1][i] = p.m0s1[i]; prm1[2][i] = rq_chi<RQ>(p.chi1[i], p.shm11[i]); prm1[3][i] = rq_sh<RQ>(p.shm11[i]);
-    }
-    if (tid < DN2) {
-        prm2[0][tid] = p.bias2[tid]; prm2[1][tid] = p.m0s2[tid]; prm2[2][tid] = rq_chi<RQ>(p.chi2[tid], p.shm12[tid]); prm2[3][tid] = rq_sh<RQ>(p.shm12[tid]);
-    }
+    // constants and weights, all on their way before any is waited for
+    const int i1 = tid < DC ? tid : 0, i2 = tid < DN2 ? tid : 0;
+    const RqRaw r1 = rq_fetch(p.bias1, p.m0s1, p.chi1, p.shm11, i1), r2 = rq_fetch(p.bias2, p.m0s2, p.chi2, p.shm12, i2);
     const uint32_t lane16 = (uint32_t)lane * 16;
     // expand fragments [fm][ksub], kept in registers for the whole launch
     const int8_t *a1w = p.a1 + (size_t)wave * (2 * (DK1 / 32) * 1024);
@@ -560,6 +557,8 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
     // loop and waits for every outstanding memory operation at their first use in each tile)
 #pragma unroll
     for (int f = 0; f < 2 * (DK1 / 32); ++f) asm volatile("" : "+v"(a1[f]));
+    if (tid < DC) rq_store<RQ>(prm1, r1, i1);
+    if (tid < DN2) rq_store<RQ>(prm2, r2, i2);
     wait_vmcnt<0>();
     __syncthreads();   // the constants are in LDS, the first tile has landed
 

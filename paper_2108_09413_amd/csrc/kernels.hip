@@ -35,7 +35,7 @@ __global__ __launch_bounds__(256) void noise_kernel(const NoiseParams p) {
         count = (uint32_t)(hi - lo);
         out_copy0 = (long)(lo - p.slot_begin);
     }
-    stage_noise_table(t, tab, threadIdx.x, 256);
+    store_noise_table(t, fetch_noise_table(tab, threadIdx.x), threadIdx.x);
     const NoiseSampler smp = tab->s;
     __syncthreads();
 

@@ -348,13 +348,44 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
     const block_ptr blocks = (block_ptr)(uintptr_t)p.blocks;
 
     // ---- the stage's input ----
-    if (p.nblocks)
-        for (int i = tid; i < 4 * C; i += 256) prm[0][i] = blocks[0].prm1[i];
+    // constants, the sampler's table and the first weights are all on their way before any of them is waited for
+    constexpr bool WIDE = C > 16;
+    constexpr int NTP = TAIL ? (3 * 4 * C2 + 255) / 256 : 1;
+    static_assert(4 * C <= 256, "one constant a thread");
+    const bool from_image = C == 16 && p.stem;
+    int v0 = 0, v1 = 0, vt[NTP] = {};
+    v4i fa0 = {0, 0, 0, 0};
+    NoiseStage vn;
+    const uint8_t *xim = nullptr;
+    const DeviceNoiseTable *table = nullptr;
+    uint32_t image_id = 0;
+    SlotUse use{};
+    if (from_image) {
+        v1 = p.prm0[tid & 63];
+        fa0 = *(const v4i *)(p.w0 + (lane & 15) * 64 + (lane >> 4) * 16);
+        if (p.fused_noise) {
+            use = resolve_noise_source(p.noise, img0, xim, table, image_id);
+            vn = fetch_noise_table(table, tid);
+        }
+    }
+    if (p.nblocks && tid < 4 * C) v0 = blocks[0].prm1[tid];
     if (TAIL && p.tail)
-        for (int i = tid; i < 3 * 4 * C2; i += 256) tprm[i] = p.tprm[i];
+#pragma unroll
+        for (int j = 0; j < NTP; ++j)
+            if (tid + 256 * j < 3 * 4 * C2) vt[j] = p.tprm[tid + 256 * j];
+    v4i fa[WIDE ? WideConv<WIDE ? C : 32, WIDE ? S : 16>::KS : 1];   // weights of the convolution to come
+    if constexpr (WIDE)
+        if (p.nblocks) WideConv<C, S>(lane, wave).load_weights(blocks[0].w1, fa);
+    auto store_constants = [&]() {
+        if (p.nblocks && tid < 4 * C) prm[0][tid] = v0;
+        if (TAIL && p.tail)
+#pragma unroll
+            for (int j = 0; j < NTP; ++j)
+                if (tid + 256 * j < 3 * 4 * C2) tprm[tid + 256 * j] = vt[j];
+    };
     if (p.nblocks) fill_ring<C, S, NI>(X, blocks[0].zp_x, tid);
     else if (p.tail) fill_ring<C, S, NI>(X, p.tzp_x, tid);
-    if (C == 16 && p.stem) {
+    if (from_image) {
         if constexpr (C == 16) {
             // the noisy image as NHWC4 words, one pixel of padding left, three right; behind it the sampler's table
             constexpr int PW = S + 4;
@@ -372,14 +403,10 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
             const int y = tid / (S / 4), x4 = tid % (S / 4);   // one quad of pixels per thread
             uint32_t v[4];
             if (p.fused_noise) {
-                const uint8_t *xim;
-                const DeviceNoiseTable *src;
-                uint32_t image_id;
-                const SlotUse use = resolve_noise_source(p.noise, img0, xim, src, image_id);
-                stage_noise_table(*tab, src, tid, 256);
-                const NoiseSampler smp = src->s;
+                store_noise_table(*tab, vn, tid);
+                const NoiseSampler smp = table->s;
                 lds_barrier();
-                noisy_quad(*tab, smp, src, xim, p.noise.C, S, S, y, x4, use.sample, image_id, use.phase, p.noise.key0, p.noise.key1, v);
+                noisy_quad(*tab, smp, table, xim, p.noise.C, S, S, y, x4, use.sample, image_id, use.phase, p.noise.key0, p.noise.key1, v);
             } else {
                 const v4i w = *(const v4i *)(p.in + ((img0 * S + y) * S + 4 * x4) * 4);
 #pragma unroll
@@ -387,22 +414,23 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) img[(y + 1) * PW + 1 + 4 * x4 + j] = (int)v[j];
+            if (tid < 64) prm[1][tid] = v1;
+            store_constants();
             lds_barrier();
             // one v_mfma_i32_16x16x64_i8 per 16 pixels: lane group ky reads the 16 contiguous bytes of kernel row ky (4 pixels x
             // 4 stored channels, the fourth pixel and channel meeting zero weights), the fourth group zero weights
             const int l = lane & 15, kg = lane >> 4, kr = kg < 3 ? kg : 0;
-            const v4i fa = *(const v4i *)(p.w0 + l * 64 + kg * 16);
             const int x = 16 * (wave & 1) + l, row0 = 16 * (wave >> 1);
             with_form<RQ_TOP>(p.form0, [&](auto rq, auto) {
                 constexpr int RQ = decltype(rq)::value;
-                const LaneConsts<4, RQ> k(p.prm0, 16, 4 * kg);
+                const LaneConsts<4, RQ> k(prm[1], 16, 4 * kg);
                 const int *src = img + (row0 + kr) * PW + x;
                 int8_t *dst = X + ((row0 + 1) * P + x + 1) * 16 + 4 * kg;
 #pragma unroll 4
                 for (int r = 0; r < 16; ++r) {
                     const v4i fb = {src[r * PW], src[r * PW + 1], src[r * PW + 2], src[r * PW + 3]};
                     k.fragment();
-                    const v4acc acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, fb, bias_vector<4, RQ>(k), 0, 0, 0);
+                    const v4acc acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa0, fb, bias_vector<4, RQ>(k), 0, 0, 0);
                     const uint32_t q = rq_pack<RQ>(k.conv(acc[0], 0, p.lo0), k.conv(acc[1], 1, p.lo0), k.conv(acc[2], 2, p.lo0), k.conv(acc[3], 3, p.lo0));
                     *(uint32_t *)(dst + r * P * 16) = q;
                 }
@@ -417,14 +445,11 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
             const int at = p.nblocks ? tile_at<C, S>(y, x, c) : tile_at<C, S, true>(y, x, c);
             *(v4i *)(X + im * TB + at) = *(const v4i *)(p.in + (g * S * S + pix) * C + c * 16);
         }
+        store_constants();
     }
 
     // ---- identity blocks ----
     int zp_t = 256;   // zero-point in the border of t; none yet
-    constexpr bool WIDE = C > 16;
-    v4i fa[WIDE ? WideConv<WIDE ? C : 32, WIDE ? S : 16>::KS : 1];   // weights of the convolution to come
-    if constexpr (WIDE)
-        if (p.nblocks) WideConv<C, S>(lane, wave).load_weights(blocks[0].w1, fa);
     for (int blk = 0; blk < p.nblocks; ++blk) {
         const auto &d = blocks[blk];
         const bool last = blk + 1 == p.nblocks;

@@ -84,9 +84,19 @@ struct NoiseLds {
     uint32_t guide[NOISE_GUIDE_MAX];
 };
 
-// Stages a table into LDS (all threads of the workgroup; followed by a barrier at the caller).
-__device__ __forceinline__ void stage_noise_table(NoiseLds &t, const DeviceNoiseTable *tab, int tid, int nthreads) {
-    for (int i = tid; i < (int)NOISE_GUIDE_MAX / 4; i += nthreads) ((uint4 *)t.guide)[i] = ((const uint4 *)tab->guide)[i];
+// A workgroup of 256 threads stages a table into LDS: the loads, and later the stores (followed by a barrier at the caller).
+struct NoiseStage {
+    uint4 v[2];
+};
+__device__ __forceinline__ NoiseStage fetch_noise_table(const DeviceNoiseTable *tab, int tid) {
+    constexpr int N = NOISE_GUIDE_MAX / 4;
+    static_assert(N > 256 && N <= 512, "two loads a thread");
+    const uint4 *src = (const uint4 *)tab->guide;
+    return {{src[tid], src[tid + 256 < N ? tid + 256 : tid]}};
+}
+__device__ __forceinline__ void store_noise_table(NoiseLds &t, const NoiseStage &s, int tid) {
+    ((uint4 *)t.guide)[tid] = s.v[0];
+    if (tid + 256 < (int)NOISE_GUIDE_MAX / 4) ((uint4 *)t.guide)[tid + 256] = s.v[1];
 }
 
 // Four horizontally adjacent noisy pixels (x4 * 4 .. x4 * 4 + 3 of row y) of one copy as NHWC4 words:

@@ -51,22 +51,32 @@ __global__ __launch_bounds__(256, 3) void stem_pool_kernel(const StemPoolParams 
     const int PW = p.W + 8;                   // patch row stride in pixels
     const uint32_t zb = (uint32_t)(p.zp_in & 0xFF) * 0x01010101u;
 
-    // weights: row r, 16-byte chunk c at chunk position c ^ (r & 15)
-    for (int i = tid; i < 64 * (SP_KP / 16); i += 256) {
-        const int r = i >> 4, c = i & 15;
-        *(v4i *)(&Wl[r * SP_KP + ((c ^ (r & 15)) << 4)]) = *(const v4i *)(p.w + (long)r * SP_KP + c * 16);
+    // weights, constants and the sampler's table are all on their way before any of them is waited for
+    v4i wv[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) wv[j] = *(const v4i *)(p.w + (long)(tid + 256 * j) * 16);
+    const RqRaw raw = rq_fetch(p.bias, p.m0s, p.chi, p.shm1, tid & 63);
+    const uint8_t *xim = nullptr;
+    const DeviceNoiseTable *tab = nullptr;
+    uint32_t image_id = 0;
+    SlotUse use{};
+    if (p.fused_noise) {
+        use = resolve_noise_source(p.noise, b, xim, tab, image_id);
+        store_noise_table(ntab, fetch_noise_table(tab, tid), tid);
     }
-    if (tid < 64) { prm[0][tid] = p.bias[tid]; prm[1][tid] = p.m0s[tid]; prm[2][tid] = rq_chi<RQ>(p.chi[tid], p.shm1[tid]); prm[3][tid] = rq_sh<RQ>(p.shm1[tid]); }
+    // weights: row r, 16-byte chunk c at chunk position c ^ (r & 15)
+    static_assert(64 * (SP_KP / 16) == 4 * 256, "four chunks a thread");
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int r = (tid + 256 * j) >> 4, c = tid & 15;
+        *(v4i *)(&Wl[r * SP_KP + ((c ^ (r & 15)) << 4)]) = wv[j];
+    }
+    if (tid < 64) rq_store<RQ>(prm, raw, tid);
     // input band: pixel (row r, input column x) at patch column x + 3
     const int wchunks = p.W >> 2;             // 16-byte chunks (4 pixels) per input row
     if (p.fused_noise) {
         // the noisy rows are drawn here instead of being read back from memory: the stream is counter-based,
         // so the rows that neighbouring bands share are simply drawn again, bit for bit the same
-        const uint8_t *xim;
-        const DeviceNoiseTable *tab;
-        uint32_t image_id;
-        const SlotUse use = resolve_noise_source(p.noise, b, xim, tab, image_id);
-        stage_noise_table(ntab, tab, tid, 256);
         const NoiseSampler smp = tab->s;
         __syncthreads();
         for (int i = tid; i < IR * wchunks; i += 256) {
