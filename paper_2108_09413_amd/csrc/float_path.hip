@@ -52,8 +52,7 @@ __device__ __forceinline__ float neg_log_u24(uint32_t n) {
 // cos and sin of 2 pi t / 2^24, t in [0, 2^24).
 __device__ __forceinline__ void cos_sin_turn24(uint32_t t, float &co, float &si) {
 #pragma clang fp contract(off)
-    const uint32_t octant = t >> 21, q = t & 0x1FFFFFu;
-    const float phi = (float)q * 3.74507039e-07f;              // (pi/4) / 2^21
+    const float phi = (float)(t & 0x1FFFFFu) * 3.74507039e-07f;              // (pi/4) / 2^21
     const float x2 = phi * phi;
     float c = -2.755732e-07f;
     c = c * x2; c = c + 2.48015876e-05f;
@@ -70,16 +69,12 @@ __device__ __forceinline__ void cos_sin_turn24(uint32_t t, float &co, float &si)
     float d = c - s, e = c + s;
     d = d * 0.707106769f;
     e = e * 0.707106769f;
-    switch (octant) {
-    case 0: co = c; si = s; break;
-    case 1: co = d; si = e; break;
-    case 2: co = -s; si = c; break;
-    case 3: co = -e; si = d; break;
-    case 4: co = -c; si = -s; break;
-    case 5: co = -d; si = -e; break;
-    case 6: co = s; si = -c; break;
-    default: co = e; si = -d; break;
-    }
+    // odd octants: the angle pi/4 on, (d, e); then quarter turns: (p, q), (-q, p), (-p, -q), (q, -p).  By selection and sign
+    // bits: as a switch every wave went through all eight cases.
+    const float p = t & (1u << 21) ? d : c, q = t & (1u << 21) ? e : s;
+    const bool quarter = t & (1u << 22);
+    co = __uint_as_float(__float_as_uint(quarter ? q : p) ^ (((t << 8) ^ (t << 9)) & 0x80000000u));
+    si = __uint_as_float(__float_as_uint(quarter ? p : q) ^ ((t << 8) & 0x80000000u));
 }
 
 __device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float &za, float &zb) {
