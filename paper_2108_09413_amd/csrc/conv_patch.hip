@@ -35,7 +35,7 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     constexpr int KS = KB / 32;
     constexpr int ABUF = BM * KB, ZOFF = PROWS * KB, BBUF = ZOFF + PZBYTES;
     constexpr int BPP = (PROWS + RPP - 1) / RPP; // pixel rows of a lane
-    static_assert((RPP == 128 || (RPP == 64 && !DUTY)) && BM % RPP == 0 && (KB == 64 || KB == 128) && ZOFF % 256 == 0, "tile shape");
+    static_assert((RPP == 128 || (RPP < 128 && RPP % 32 == 0 && !DUTY)) && BM % RPP == 0 && (KB == 64 || KB == 128) && ZOFF % 256 == 0, "tile shape");
 
     __shared__ __attribute__((aligned(256))) int8_t Bs[2][BBUF];
     __shared__ __attribute__((aligned(16))) int8_t As[NAB][ABUF];
@@ -333,8 +333,10 @@ hipError_t launch_conv_patch(const ConvParams &p, hipStream_t st) {
     // wave, which still has its own MFMAs to do, becomes the last to reach the barrier (2120 -> 2060).
     if (p.Cout_p < 256) return launch_patch<128, 64, 4, 2, true>(p, st, "conv_patch_kernel<128, 256, 64>");
     // Launches with tiles for less than half of the CUs are a chain of K steps that wait for weights, which nobody has
-    // brought into the caches before: half the channels per workgroup, weights fetched three steps ahead.
-    if (conv_patch_tiles(p) < 128) return launch_patch<128, 128, 4, 1, false>(p, st, "conv_patch_kernel<128, 256, 128>");
+    // brought into the caches before: half or a quarter of the channels per workgroup, weights fetched three steps ahead.
+    const long tiles = conv_patch_tiles(p);
+    if (tiles < 64) return launch_patch<64, 128, 4, 1, false>(p, st, "conv_patch_kernel<64, 256, 128>");
+    if (tiles < 128) return launch_patch<128, 128, 4, 1, false>(p, st, "conv_patch_kernel<128, 256, 128>");
     return launch_patch<256, 128, 2, 1, false>(p, st, "conv_patch_kernel<256, 256, 128>");
 }
 

@@ -864,10 +864,10 @@ def test_3x3_layers_with_staged_pixel_rows_against_the_oracle(isr, in_shape, str
     m.close()
 
 
-@pytest.mark.parametrize("copies", [1, 9, 165, 168])
+@pytest.mark.parametrize("copies", [1, 9, 82, 84, 165, 168])
 def test_staged_rows_in_launches_of_few_and_many_tiles(isr, copies):
-    """127 tiles of 256 pixels x 256 channels and fewer (128 channels a workgroup, weights three K steps ahead), 129 and
-    more (256 channels): one to four slices of 128 channels, against the implicit-GEMM tile."""
+    """63 tiles of 256 pixels x 256 channels and fewer (64 channels a workgroup, weights three K steps ahead), 65 to 127
+    (128 channels), 129 and more (256): one to four slices of 128 channels, against the implicit-GEMM tile."""
     _say(f"staged rows, {copies} copies")
     b = NetBuilder(rng=np.random.default_rng(78), in_shape=(3, 28, 28), num_classes=9)
     t = b.conv(b.tensor(3, 28, 28, 0, 74.0), 128, 3, 2, 1, True)
