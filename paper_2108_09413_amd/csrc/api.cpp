@@ -113,9 +113,17 @@ class BankTables {
     std::vector<BankTable> idle_;   // oldest first
 };
 
+// Room that the constants of the narrow-net ops need at most: in either plan each convolution's once (three times where a
+// kernel stages as many), one descriptor per op.
+size_t narrow_ops_room(const std::vector<DevOp> &ops) {
+    size_t bytes = 512;
+    for (const DevOp &d : ops) bytes += 2 * (sizeof(NarrowBlock) + (d.type == OP_CONV ? (size_t)3 * 4 * 4 * d.conv.Cout_p : 0));
+    return bytes;
+}
+
 // The constant arguments of the narrow-net ops of the fused plans: block descriptors and per-channel constants packed
-// in the form the kernel stages them, in one device buffer.  `arena` is the host image of the constants at m->dconst.
-int build_narrow_ops(isr_model *m, const ConstArena &arena) {
+// in the form the kernel stages them, appended to `arena`, the host image of the constants at m->dconst.
+int build_narrow_ops(isr_model *m, ConstArena &arena, size_t limit) {
     std::vector<NarrowBlock> blocks;
     std::vector<int32_t> consts;
     auto host = [&](const int32_t *dev) { return (const int32_t *)(arena.host.data() + ((const uint8_t *)dev - m->dconst)); };
@@ -207,8 +215,9 @@ int build_narrow_ops(isr_model *m, const ConstArena &arena) {
         }
     if (blocks.empty() && consts.empty()) return ISR_OK;
     const size_t block_bytes = (blocks.size() * sizeof(NarrowBlock) + 255) & ~(size_t)255;
-    HIP_TRY(hipMalloc((void **)&m->dnarrow, block_bytes + consts.size() * 4));
-    const int32_t *dconsts = (const int32_t *)(m->dnarrow + block_bytes);
+    uint8_t *dnarrow = m->dconst + arena.host.size();   // the end of the constants on the device too
+    if (arena.host.size() + block_bytes + consts.size() * 4 > limit) return ISR_ERR_UNSUPPORTED;   // cannot happen: narrow_ops_room
+    const int32_t *dconsts = (const int32_t *)(dnarrow + block_bytes);
     for (NarrowBlock &nb : blocks) { nb.prm1 = dconsts + (size_t)nb.prm1; nb.prm2 = dconsts + (size_t)nb.prm2; }
     for (int pi = 1; pi <= 2; ++pi)
         for (DevOp &d : m->plan[pi].ops) {
@@ -216,10 +225,12 @@ int build_narrow_ops(isr_model *m, const ConstArena &arena) {
             if (!d.narrow) continue;
             if (np.prm0) np.prm0 = dconsts + (size_t)np.prm0 - 1;
             if (np.tprm) np.tprm = dconsts + (size_t)np.tprm - 1;
-            if (np.blocks) np.blocks = (const NarrowBlock *)m->dnarrow + (size_t)np.blocks - 1;
+            if (np.blocks) np.blocks = (const NarrowBlock *)dnarrow + (size_t)np.blocks - 1;
         }
-    if (!blocks.empty()) HIP_TRY(hipMemcpy(m->dnarrow, blocks.data(), blocks.size() * sizeof(NarrowBlock), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(m->dnarrow + block_bytes, consts.data(), consts.size() * 4, hipMemcpyHostToDevice));
+    const size_t at = arena.host.size();
+    arena.host.resize(at + block_bytes + consts.size() * 4);
+    std::memcpy(arena.host.data() + at, blocks.data(), blocks.size() * sizeof(NarrowBlock));
+    std::memcpy(arena.host.data() + at + block_bytes, consts.data(), consts.size() * 4);
     return ISR_OK;
 }
 
@@ -635,19 +646,27 @@ int isr_load_model(const void *blob_host, size_t bytes, isr_model **out) {
     rc = build_device_ops(m->pm, m->ops, arena);
     if (rc != ISR_OK) { delete m; return rc; }
     auto cleanup = [&](int code) { isr_free_model(m); return code; };
-    hipError_t e = hipMalloc((void **)&m->dconst, arena.host.size());
-    if (e == hipSuccess) e = hipMemcpy(m->dconst, arena.host.data(), arena.host.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void **)&m->dtables, sizeof(DeviceNoiseTable) * TABLE_SLOTS);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&m->htables, sizeof(DeviceNoiseTable) * TABLE_SLOTS, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipMalloc((void **)&m->dcounts, sizeof(uint32_t) * 2 * m->pm.classes);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&m->hcounts, sizeof(uint32_t) * 2 * m->pm.classes, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&m->hcounts_dev, m->hcounts, 0);
+    // one device allocation: [constants][room for those of the narrow-net ops][noise tables][counters], and one pinned one
+    auto round_256 = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    const size_t narrow_off = round_256(arena.host.size()), tables_off = round_256(narrow_off + narrow_ops_room(m->ops));
+    const size_t tables_bytes = round_256(sizeof(DeviceNoiseTable) * TABLE_SLOTS), counts_bytes = sizeof(uint32_t) * 2 * m->pm.classes;
+    hipError_t e = hipMalloc((void **)&m->dconst, tables_off + tables_bytes + counts_bytes);
+    if (e == hipSuccess) e = hipHostMalloc((void **)&m->htables, tables_bytes + counts_bytes, hipHostMallocDefault);
+    if (e == hipSuccess) {
+        m->dtables = (DeviceNoiseTable *)(m->dconst + tables_off);
+        m->dcounts = (uint32_t *)(m->dconst + tables_off + tables_bytes);
+        m->hcounts = (uint32_t *)((uint8_t *)m->htables + tables_bytes);
+        e = hipHostGetDevicePointer((void **)&m->hcounts_dev, m->hcounts, 0);
+    }
     if (e != hipSuccess) { g_last_hip_error = (int)e; return cleanup(ISR_ERR_DEVICE); }
     rebase_device_ops(m->ops, m->dconst);
     m->plan[0].ops = m->ops;
     build_fused_plan(m->pm, m->ops, m->plan[1].ops, false);
     build_fused_plan(m->pm, m->ops, m->plan[2].ops, true);
-    if ((rc = build_narrow_ops(m, arena)) != ISR_OK) return cleanup(rc);
+    arena.host.resize(narrow_off);
+    if ((rc = build_narrow_ops(m, arena, tables_off)) != ISR_OK) return cleanup(rc);
+    e = hipMemcpy(m->dconst, arena.host.data(), arena.host.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) { g_last_hip_error = (int)e; return cleanup(ISR_ERR_DEVICE); }
     *out = m;
     return ISR_OK;
 }
@@ -723,11 +742,7 @@ int isr_free_model(isr_model *m) {
     if (!m) return ISR_OK;
     for (hipEvent_t e : m->events) (void)hipEventDestroy(e);
     if (m->dconst) (void)hipFree(m->dconst);
-    if (m->dtables) (void)hipFree(m->dtables);
     if (m->htables) (void)hipHostFree(m->htables);
-    if (m->dcounts) (void)hipFree(m->dcounts);
-    if (m->hcounts) (void)hipHostFree(m->hcounts);
-    if (m->dnarrow) (void)hipFree(m->dnarrow);
     if (m->ditems) (void)hipFree(m->ditems);
     if (m->hitems) (void)hipHostFree(m->hitems);
     if (m->dcounts_b) (void)hipFree(m->dcounts_b);

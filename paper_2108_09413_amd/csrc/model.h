@@ -24,15 +24,14 @@ struct isr_model {
     Plan plan[3];                       // [0] op by op, [1] with the fusions that pay, [2] with every fusion the kernels cover
     int use_fused = 1;
     int conv_tile = 0;                  // forced conv output tile (0 = automatic)
-    uint8_t *dconst = nullptr;          // weights and per-channel tables
+    uint8_t *dconst = nullptr;          // weights and per-channel tables; dtables and dcounts are in the same allocation
     DeviceNoiseTable *dtables = nullptr;  // TABLE_SLOTS entries
-    DeviceNoiseTable *htables = nullptr;  // pinned staging, TABLE_SLOTS entries
+    DeviceNoiseTable *htables = nullptr;  // pinned staging, TABLE_SLOTS entries; hcounts is in the same allocation
     uint32_t table_sigma[TABLE_SLOTS] = {0};
     int table_next = 0;
     uint32_t *dcounts = nullptr;        // 2 * classes
     uint32_t *hcounts = nullptr, *hcounts_dev = nullptr;   // pinned, 2 * classes, and its address for kernels
     bool counts_clean = false, counts_b_clean = false;     // dcounts, dcounts_b hold zeros
-    uint8_t *dnarrow = nullptr;         // block descriptors and packed constants of the narrow-net ops of plan[1] and plan[2]
     // batched calls: item descriptors and per-item vote counters, grown on demand
     NoiseItem *ditems = nullptr, *hitems = nullptr;
     uint32_t *dcounts_b = nullptr, *hcounts_b = nullptr, *hcounts_b_dev = nullptr;   // 2 * items_cap * classes each
