@@ -398,6 +398,14 @@ int run_slots(isr_model *m, const Plan &pl, const Draw &draw, int32_t *logits_ho
                             bp.lop = swap ? lo_main : c3.lo2;
                         }
                     }
+                    if (d.reduce) {
+                        const ConvParams &c4 = d.conv4;
+                        bp.reduce = 1; bp.sparse = d.sparse;
+                        bp.out2 = (int8_t *)tptr(d.out2, j0);
+                        bp.wp = c4.wfrag; bp.biasp = c4.bias; bp.m0sp = c4.m0s; bp.chip = c4.chi; bp.shm1p = c4.shm1;
+                        bp.lop = c4.relu ? c4.zp_out : -128;
+                        bp.rq &= c4.rq;
+                    }
                     if (d.bneck == 3) HIP_TRY(launch_bottleneck128(bp, m->stream));
                     else HIP_TRY(launch_bottleneck(bp, m->stream));
                     break;

@@ -26,24 +26,32 @@
 // Bounds, 668 images of 56 x 56 x 256 (identity block): memory 1.07 GB = 210 us at the rate of a large copy, issue of the
 // requantisation and its data movement about 200 us, matrix unit 60 us, in phases that barriers separate.
 // Two workgroups of eight waves a CU instead of two of four: 344 -> 322 us (projection block 360 -> 340).
+// With the next stage's 1x1 convolution (256 -> 128) in the kernel the sum is not read back and, under a stride-2
+// projection, three quarters of it are not written: 441 us against 322 + 157 for two kernels.
 #include "conv_device.h"
 
 namespace isr {
 
 namespace {
 
+typedef int v4acc __attribute__((ext_vector_type(4)));
+template <int N>
+using Frag = std::integral_constant<int, N>;
+
 constexpr int TH = 8, TW = 28;                 // output tile
 constexpr int HH = TH + 2, HW = TW + 2;        // halo tile: 10 x 30 = 300 pixels
 constexpr int NHALO = HH * HW;                 // 300
 constexpr int NH_FR = 10;                      // fragments (of 32 GEMM columns) covering the halo: 320 columns
 constexpr int NP_FR = 7;                       // fragments covering the 224 output pixels, all full
+constexpr int RN = 128;                        // outputs of the next stage's first convolution
 constexpr int W2_CHUNKS = 37;                  // 16-byte chunks per 3x3 weight row in LDS: 36 + 1 pad (bank spread)
 
 // MODE 0: head (t2 stored); 1: whole identity block (residual = x); 2: whole first block of a stage --
-// the residual is itself a 1x1 convolution of x (projection shortcut, Cin = 64), computed here as well.
+// the residual is itself a 1x1 convolution of x (projection shortcut, Cin = 64), computed here as well; 3: an identity
+// block of 256 channels and the 1x1 convolution into 128 channels that reads its sum (the next stage's first).
 template <int MODE, int RQ, int RQA>
 __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p) {
-    constexpr bool TAIL = MODE != 0, PROJ = MODE == 2;
+    constexpr bool TAIL = MODE != 0, PROJ = MODE == 2, IDENTITY = MODE == 1 || MODE == 3, REDUCE = MODE == 3;
     constexpr int KB = 64, STAGE = (64 + 32 * NH_FR) * KB;            // 64 weight rows + 320 pixel rows per stage
     static_assert(64 * W2_CHUNKS * 16 <= 2 * STAGE, "3x3 weights fit the operand stages");
     __shared__ __attribute__((aligned(16))) int8_t Ls[2 * STAGE];     // step 1: two stages (A rows, then B rows); step 3: 3x3 weights
@@ -51,6 +59,7 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
     __shared__ int prm[2][4][64];                                     // bias, M0, chi, shift-1 of the first two convolutions
     __shared__ __attribute__((aligned(16))) int prm3[TAIL ? 4 : 1][TAIL ? 256 : 4];
     __shared__ __attribute__((aligned(16))) int prmp[PROJ ? 4 : 1][PROJ ? 256 : 4];   // the same for the projection
+    __shared__ __attribute__((aligned(16))) int prmr[REDUCE ? 4 : 1][REDUCE ? RN : 4];  // and for the next stage's convolution
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = lane & 31, half = lane >> 5;
@@ -98,12 +107,15 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
         RqRaw r3{}, rp{};
         if constexpr (TAIL) r3 = rq_fetch(p.bias3, p.m0s3, p.chi3, p.shm13, ct);
         if constexpr (PROJ) rp = rq_fetch(p.biasp, p.m0sp, p.chip, p.shm1p, ct);
+        if constexpr (REDUCE) rp = rq_fetch(p.biasp, p.m0sp, p.chip, p.shm1p, tid & (RN - 1));
         if (tid < 128) rq_store<RQ>(prm[cv], r12, c);
         if constexpr (TAIL)
             if (tid < p.Cout_p) {
                 rq_store<RQ>(prm3, r3, ct);
                 if constexpr (PROJ) rq_store<RQ>(prmp, rp, ct);
             }
+        if constexpr (REDUCE)
+            if (tid < RN) rq_store<RQ>(prmr, rp, tid);
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();       // prm visible (the operands need not have landed)
@@ -145,7 +157,7 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
             __builtin_amdgcn_s_barrier();   // every wave's loads of step ks landed; every wave is done with step ks - 1
             if (ks >= 1 && ks + 1 < nk) issue(ks + 1, (ks + 1) & 1);
             const int8_t *base = &Ls[(ks & 1) * STAGE];
-            if constexpr (MODE == 1) {
+            if constexpr (IDENTITY) {
                 if (ks == wave >> 1) {   // wave-uniform
 #pragma unroll
                     for (int f = 0; f < NP_FR; ++f) {
@@ -280,7 +292,7 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
             return oy0 + oy < p.H && ox0 + ox < p.W ? (b * p.H + oy0 + oy) * p.W + ox0 + ox : -1;
         };
         // the fragments of one 1x1 convolution from 64 channels: operand(f, K half), then use(f, requantised values)
-        auto conv64 = [&](const int8_t *w, const auto &prm, int lo, auto operand, auto use) {
+        auto conv64 = [&](const int8_t *w, const auto &prm, int lo, auto first, auto end, auto operand, auto use) {
             asm volatile("" ::: "memory");
             v4i fa[2];
 #pragma unroll
@@ -292,7 +304,7 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
             };
             if constexpr (rq_is_top(RQ)) constants();
 #pragma unroll
-            for (int f = 0; f < NP_FR; ++f) {
+            for (int f = decltype(first)::value; f < decltype(end)::value; ++f) {
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_sched_barrier(0);
                 v16i a;
@@ -317,7 +329,7 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
                 for (int ksub = 0; ksub < 2; ++ksub) xn[ksub] = *(const v4i *)(p.in + (long)(px >= 0 ? px : 0) * 64 + ksub * 32 + half * 16);
             };
             fetch(0);
-            conv64(p.wp, prmp, p.lop, [&](int f, int ksub) {
+            conv64(p.wp, prmp, p.lop, Frag<0>{}, Frag<NP_FR>{}, [&](int f, int ksub) {
                 if (ksub == 0) {
                     x[0] = xn[0]; x[1] = xn[1];
                     if (f + 1 < NP_FR) fetch(f + 1);
@@ -328,16 +340,74 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
                 asm volatile("" : "+v"(resid[f]));   // packed: the compiler would keep the sixteen values
             });
         }
-        conv64(p.w3, prm3, p.lo3, [&](int f, int ksub) {
+        auto t2_operand = [&](int f, int ksub) {
             const int o = f * 32 + l;
             return *(const v4i *)(&T[o * 64 + (((ksub * 2 + half) ^ swz<4>(o)) << 4)]);
-        }, [&](int f, const int (&qc)[16]) {
+        };
+        auto sum = [&](int f, const int (&qc)[16]) {
             int q[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) q[i] = rq_add<RQ, RQA>(qc[i], (uint32_t)resid[f][i >> 2], i & 3, ac);
-            const int px = pixel(f);
-            if (px >= 0) *(v4i *)(p.out + (long)px * p.Cout_p + c0) = rq_pack16<RQA>(q);
-        });
+            return rq_pack16<RQA>(q);
+        };
+        if constexpr (!REDUCE) {
+            conv64(p.w3, prm3, p.lo3, Frag<0>{}, Frag<NP_FR>{}, t2_operand, [&](int f, const int (&qc)[16]) {
+                const v4i y = sum(f, qc);
+                const int px = pixel(f);
+                if (px >= 0) *(v4i *)(p.out + (long)px * p.Cout_p + c0) = y;
+            });
+        } else {
+            // The sum goes to memory (only its even pixels where nothing but a stride-2 projection reads it) and, three, two
+            // and two fragments at a time, into LDS: [pixel][256 channels], chunk c of pixel p at c ^ (p & 15), in the space of
+            // the 3x3 weights.  After a barrier each wave makes 16 of the next convolution's channels of those pixels
+            // while the others go on to the next fragments, which have a region of their own.
+            auto group = [&](auto first, auto end, int region) {
+                constexpr int F0 = decltype(first)::value, F1 = decltype(end)::value;
+                const int ln = lane & 15, g = lane >> 4, oc = wave * 16 + 4 * g;
+                v4i fr[4];
+                auto weights = [&]() {
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks) fr[ks] = *(const v4i *)(p.wp + ((wave * 4 + ks) * 64 + lane) * 16);
+                };
+                if constexpr (F0 > 0) weights();   // (the first group's residual leaves no registers for them yet)
+                conv64(p.w3, prm3, p.lo3, first, end, t2_operand, [&](int f, const int (&qc)[16]) {
+                    const v4i y = sum(f, qc);
+                    const int px = pixel(f), i = (f - F0) * 32 + l;
+                    *(v4i *)(&Ls[region + i * 256 + (((2 * wave + half) ^ (i & 15)) << 4)]) = y;
+                    const int o = f * 32 + l, odd = (o / TW | o % TW) & 1;   // a tile starts at an even pixel
+                    const bool store = px >= 0 && !(p.sparse && odd);
+                    if (store) *(v4i *)(p.out + (long)px * 256 + c0) = y;
+                });
+                if constexpr (F0 == 0) weights();
+                int bias[4], mm[4], ch[4], ss[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { bias[i] = prmr[0][oc + i]; mm[i] = prmr[1][oc + i]; ch[i] = prmr[2][oc + rq_chi_at<RQ>(i)]; ss[i] = prmr[3][oc + i]; }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();   // the group's sums are complete
+                asm volatile("" ::: "memory");
+                const bool full = oy0 + TH <= p.H && ox0 + TW <= p.W;
+#pragma unroll
+                for (int nb = 0; nb < 2 * (F1 - F0); ++nb) {
+                    v4acc a = {bias[0], bias[1], bias[2], bias[3]};
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks)
+                        a = __builtin_amdgcn_mfma_i32_16x16x64_i8(fr[ks], *(const v4i *)(&Ls[region + (16 * nb + ln) * 256 + (((4 * ks + g) ^ ln) << 4)]), a, 0, 0, 0);
+                    int q[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) q[i] = rq_conv<RQ>(a[i], mm[i], ch[i], ss[i], p.lop);
+                    // sixteen pixels of the tile from a constant one on: they lie in one row or in two
+                    const int cy = (F0 * 32 + 16 * nb) / TW, cx = (F0 * 32 + 16 * nb) % TW;
+                    const bool wrap = cx + ln >= TW;
+                    const uint32_t at = (uint32_t)((b * p.H + oy0 + cy) * p.W + ox0 + cx) + (uint32_t)(ln + (wrap ? p.W - TW : 0));
+                    if (full || (oy0 + cy + wrap < p.H && ox0 + cx + ln - (wrap ? TW : 0) < p.W))
+                        *(uint32_t *)(p.out2 + (at * RN + (uint32_t)oc)) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
+                }
+            };
+            static_assert(5 * 32 * 256 <= 2 * STAGE && 3 + 2 + 2 == NP_FR, "regions");
+            group(Frag<0>{}, Frag<3>{}, 0);
+            group(Frag<3>{}, Frag<5>{}, 3 * 32 * 256);
+            group(Frag<5>{}, Frag<7>{}, 0);   // every wave is done with the first group: it has passed the second's barrier
+        }
     }
 }
 
@@ -356,19 +426,22 @@ hipError_t launch_bottleneck(const BneckParams &p, hipStream_t st) {
     if (p.B <= 0) return hipSuccess;
     if (!p.in || !p.out || !p.w1 || !p.w2 || !p.zpad || p.H < 1 || p.W < 1 ||
         !bottleneck_supported(p.Cin_p, 64, p.Cout_p, p.tail ? (p.proj ? 2 : 1) : 0) || (p.tail && !p.w3) ||
-        (p.proj && (!p.tail || !p.wp || !p.biasp || !p.m0sp || !p.chip || !p.shm1p)))
+        ((p.proj || p.reduce) && (!p.tail || !p.wp || !p.biasp || !p.m0sp || !p.chip || !p.shm1p)) ||
+        (p.reduce && (p.proj || !p.out2 || p.Cout_p != 256 || (p.sparse && (p.H & 1)))))
         return hipErrorInvalidValue;
     const long tiles = (long)p.B * ((p.H + TH - 1) / TH) * ((p.W + TW - 1) / TW);
     if (tiles > 0x7fffffffL || (long)p.B * p.H * p.W * (p.Cin_p > 64 ? p.Cin_p : 64) >= (1L << 31)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles), block(512);
-    const int mode = p.tail ? (p.proj ? 2 : 1) : 0;
-    static const char *const names[3][2] = {{"bottleneck_kernel<head, false>", "bottleneck_kernel<head, true>"},
+    const int mode = p.tail ? (p.proj ? 2 : p.reduce ? 3 : 1) : 0;
+    static const char *const names[4][2] = {{"bottleneck_kernel<head, false>", "bottleneck_kernel<head, true>"},
                                             {"bottleneck_kernel<block, false>", "bottleneck_kernel<block, true>"},
-                                            {"bottleneck_kernel<block + projection, false>", "bottleneck_kernel<block + projection, true>"}};
+                                            {"bottleneck_kernel<block + projection, false>", "bottleneck_kernel<block + projection, true>"},
+                                            {"bottleneck_kernel<block + next, false>", "bottleneck_kernel<block + next, true>"}};
     set_kernel_name(names[mode][(p.rq & RQ_TIE_FREE) && (mode == 0 || p.add_rq != RQ_ANY)]);
     with_rq(p.rq, p.add_rq, [&](auto rq, auto rqa) {
         constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
-        if (mode == 2) hipLaunchKernelGGL((bottleneck_kernel<2, RQ, RQA>), grid, block, 0, st, p);
+        if (mode == 3) hipLaunchKernelGGL((bottleneck_kernel<3, RQ, RQA>), grid, block, 0, st, p);
+        else if (mode == 2) hipLaunchKernelGGL((bottleneck_kernel<2, RQ, RQA>), grid, block, 0, st, p);
         else if (mode == 1) hipLaunchKernelGGL((bottleneck_kernel<1, RQ, RQA>), grid, block, 0, st, p);
         else hipLaunchKernelGGL((bottleneck_kernel<0, RQ, RQA>), grid, block, 0, st, p);
     });

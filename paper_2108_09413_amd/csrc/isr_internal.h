@@ -261,6 +261,11 @@ struct BneckParams {
     const int8_t *wp;
     const int32_t *biasp, *m0sp, *chip, *shm1p;
     int32_t proj, lop;       // lop: lower clamp of the projection's int8 result
+    // reduce != 0 (identity block of 256 channels): out2 = clamp(requant(conv1x1(out))), [B][H][W][128], computed from the
+    // sums in LDS; its weights (fragment-major, ConvParams::wfrag), constants and lower clamp in wp .. lop.  sparse: nothing
+    // else needs odd rows or columns of `out`, which are not written.
+    int32_t reduce, sparse;
+    int8_t *out2;
     const int8_t *zpad;      // 16 readable bytes (source of halo pixels outside the image)
     int32_t Cin_p, Cout_p, H, W, B, tail;
     int32_t zp_t1;           // zero-point of the first convolution's output (padding value of the 3x3)

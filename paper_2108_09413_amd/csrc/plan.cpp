@@ -98,7 +98,7 @@ void plan_workspace(const ParsedModel &pm, uint32_t B, Plan &pl) {
         const int end = seg < pl.segments.size() ? (int)std::min(pl.segments[seg].end, pl.ops.size()) : i + 1;
         for (int j = i; j < end; ++j) {
             const DevOp &o = pl.ops[j];
-            if (o.type != OP_FC && !o.head) { pl.toff[o.out] = alloc(tbytes(o.out)); pl.has[o.out] = 1; }
+            if (o.type != OP_FC && !o.head) { pl.toff[o.out] = alloc(tbytes(o.out)); pl.has[o.out] = !o.sparse; }
             if (o.out2 >= 0) { pl.toff[o.out2] = alloc(tbytes(o.out2)); pl.has[o.out2] = 1; }
         }
         for (int j = i; j < end; ++j) {
@@ -569,7 +569,7 @@ int build_device_ops(const ParsedModel &pm, std::vector<DevOp> &ops, ConstArena 
                             std::memcpy(&f[(((size_t)blk * (Kp / 32) + ks) * 64 + l) * 16],
                                         &w[(size_t)(32 * blk + (l & 31)) * Kp + ks * 32 + 16 * (l >> 5)], 16);
                 c.wfrag = (const int8_t *)arena.put(f.data(), f.size());
-            } else if (flat && fast && perm && Kp == cin_p && ((cin_p == 512 && (cout_p == 128 || cout_p == 256)) || (cin_p == 1024 && cout_p == 256))) {
+            } else if (flat && fast && perm && Kp == cin_p && ((cin_p == 256 && cout_p == 128) || (cin_p == 512 && (cout_p == 128 || cout_p == 256)) || (cin_p == 1024 && cout_p == 256))) {
                 // 16x16x64 fragments [16-channel block][K step of 64]: lane l = channel l & 15 of the block, K bytes 16 (l >> 4) ..
                 std::vector<int8_t> f((size_t)cout_p * Kp);
                 for (int mb = 0; mb < cout_p / 16; ++mb)
@@ -686,6 +686,41 @@ void fuse_expand_reduce(const ParsedModel &pm, std::vector<DevOp> &ops) {
 
 }  // namespace
 
+namespace {
+
+// Folds the 1x1 convolution into 128 channels that reads the sum of a 256-channel identity block (the first of a ResNet-50's
+// next stage) into the block's kernel.  Where the only other reader of the sum is a 1x1 stride-2 convolution, its other
+// pixels are not written.
+void fuse_block_and_next(const ParsedModel &pm, std::vector<DevOp> &ops) {
+    for (size_t i = 0; i + 1 < ops.size(); ++i) {
+        DevOp &a = ops[i];
+        const DevOp &b = ops[i + 1];
+        const ConvParams &c = b.conv;
+        if (a.bneck != 2 || a.conv3.Cout_p != 256 || b.type != OP_CONV || b.a != a.out || b.stem_pool || b.stem16 || b.narrow || b.bneck || b.xr ||
+            c.fuse_add || c.k != 1 || c.stride != 1 || c.pad != 0 || c.Cin_p != 256 || c.Kp != 256 || c.Cout_p != 128 || !c.fast_requant || c.c4 || !c.wfrag)
+            continue;
+        const int rq = a.conv.rq & a.conv2.rq & a.conv3.rq;
+        if ((rq & c.rq) != rq) continue;   // the kernel has one form for all its convolutions: not a longer one for this
+        bool others = false, sparse = true;
+        for (size_t j = i + 2; j < ops.size(); ++j) {
+            if (ops[j].b == a.out) { others = true; sparse = false; }
+            if (ops[j].a == a.out) {
+                others = true;
+                sparse = sparse && ops[j].type == OP_CONV && ops[j].conv.k == 1 && ops[j].conv.stride == 2 && ops[j].conv.pad == 0 && !ops[j].bneck && !ops[j].narrow;
+            }
+        }
+        a.reduce = 1;
+        a.sparse = others && sparse && a.conv.H % 2 == 0;
+        a.conv4 = c;
+        a.out2 = b.out;
+        a.ops_per_sample += b.ops_per_sample;
+        a.bytes_per_sample += (double)pm.tensors[b.out].C * c.H * c.W - (a.sparse ? 0.75 : 0.0) * pm.tensors[a.out].C * c.H * c.W;
+        ops.erase(ops.begin() + i + 1);
+    }
+}
+
+}  // namespace
+
 void build_fused_plan(const ParsedModel &pm, const std::vector<DevOp> &plain, std::vector<DevOp> &fused, bool wide_bottlenecks) {
     fuse_adds(pm, plain, fused);
     fuse_stem_pool(pm, fused);
@@ -708,6 +743,7 @@ void build_fused_plan(const ParsedModel &pm, const std::vector<DevOp> &plain, st
     fuse_narrow(pm, fused);
     fuse_bottlenecks(pm, fused, wide_bottlenecks);
     fuse_expand_reduce(pm, fused);
+    fuse_block_and_next(pm, fused);
 }
 
 }  // namespace isr

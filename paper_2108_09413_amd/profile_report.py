@@ -27,7 +27,7 @@ BENCH_STATS = "python bench.py --steps 2 --warmup 1 --no-cpu-baseline --no-other
 BENCH_PMC = ("python bench.py --steps 1 --warmup 0 --n 1236 --no-cpu-baseline --no-other-configs --no-comparison-systems "
              "--profile-every 0")
 BENCH_FP = "python bench.py --system fp --steps 1"
-MODES = {"0": "head", "1": "block", "2": "block + projection"}
+MODES = {"0": "head", "1": "block", "2": "block + projection", "3": "block + next"}
 
 
 def sources_sha256() -> str:

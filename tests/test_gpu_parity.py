@@ -864,6 +864,29 @@ def test_3x3_layers_with_staged_pixel_rows_against_the_oracle(isr, in_shape, str
     m.close()
 
 
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("shape,first", [((32, 56), 2), ((20, 60), 2), ((36, 124), 4)])   # 16 x 28, 10 x 30, 9 x 31
+def test_identity_block_with_the_next_stages_first_convolution(isr, shape, first, stride):
+    """The sum of a 256-channel block feeds the next 1x1 convolution from LDS; with a stride-2 projection as its only other
+    reader (and an even height) only its even pixels are written.  Whole and ragged tiles, odd sizes."""
+    _say(f"block + next 1x1 {shape} stride {stride}")
+    b = NetBuilder(rng=np.random.default_rng(83), in_shape=(3,) + shape, num_classes=9)
+    t = b.conv(b.conv(b.tensor(3, *shape, 0, 74.0), 64, 3, first, 1, True), 256, 1, 1, 0, True)
+    u = b.conv(b.conv(b.conv(t, 64, 1, 1, 0, True), 64, 3, 1, 1, True), 256, 1, 1, 0, False)
+    y = b.add(t, u, True)
+    u = b.conv(b.conv(y, 128, 1, 1, 0, True), 128, 3, stride, 1, True)
+    t = b.add(b.conv(y, 512, 1, stride, 0, False), b.conv(u, 512, 1, 1, 0, False), True)
+    b.fc(b.conv(t, 16, 1, 1, 0, True), 9)
+    blob = b.blob()
+    x = np.random.default_rng(84).integers(0, 256, size=(3,) + shape).astype(np.uint8)
+    m = _load(isr, blob, 5)
+    lg, am, cnt = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 3, 5)
+    olg, oam, ocnt = oracle.Model(blob).mc(x, 64, 2, 1, 1, 3, 5)
+    assert np.array_equal(lg, olg) and np.array_equal(am, oam) and np.array_equal(cnt, ocnt)
+    m.close()
+    _check_all_tensors(isr, blob, x, 64)
+
+
 @pytest.mark.parametrize("copies", [1, 9, 82, 84, 165, 168])
 def test_staged_rows_in_launches_of_few_and_many_tiles(isr, copies):
     """63 tiles of 256 pixels x 256 channels and fewer (64 channels a workgroup, weights three K steps ahead), 65 to 127
