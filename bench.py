@@ -412,7 +412,7 @@ def bench_noise_bank(args, isr, torch):
                "sample": f"{sample} tensors of {d} draws ({cdt:.1f} s, one thread)", "host": host_cpu_info()}
     # executed VALU instructions per 4 draws of one lane, from the committed rocprofv3 counter run
     # (SQ_INSTS_VALU / (draws / 4 / 64), profiles/noise_bank_kernel.md); peak = 256 CUs x 64 lanes x 2.4 GHz
-    valu_per_group, alu_peak = 137.0, 256 * 64 * 2.4e9 / 1e12
+    valu_per_group, alu_peak = 113.0, 256 * 64 * 2.4e9 / 1e12
     tops = values / 4 * valu_per_group / dt / 1e12
     print(json.dumps({
         "metric": "stored discrete-Gaussian noise draws/sec", "value": round(values / dt, 1), "unit": "draws/s",
@@ -422,7 +422,7 @@ def bench_noise_bank(args, isr, torch):
                                f"(table build + upload + kernel + synchronisation)"},
         "roofline": {"bound": "alu", "kernel": "noise_bank_kernel", "achieved": round(tops, 2), "peak": round(alu_peak, 2),
                      "unit": "T lane-instructions/s", "frac": round(tops / alu_peak, 4), "traffic": None,
-                     "note": "137 executed VALU instructions per lane per 4 draws (rocprofv3 SQ_INSTS_VALU) over the "
+                     "note": "113 executed VALU instructions per lane per 4 draws (rocprofv3 SQ_INSTS_VALU) over the "
                              "whole-call time; the 2 bytes written per draw are "
                              f"{values * 2 / dt / 1e9:.0f} GB/s"},
         "cpu_baseline": cpu}))

@@ -248,9 +248,9 @@ def main():
                  "rocprofv3 --kernel-trace --stats -d " + RAW + "/stats -o r50 --output-format csv -- " + BENCH_STATS,
                  "stats.log", 5000, "TOP/s")
     kernel_stats(args.raw, "fp_stats", "fconv_resnet50_floatrs_fp_kernel_stats.md",
-                 "rocprofv3 kernel statistics: ResNet-50 FloatRS-fp comparison system (fp32 network on the fp32 MFMA)",
+                 "rocprofv3 kernel statistics: ResNet-50 FloatRS-fp comparison system (fp32 network, exactly split operands on the bfloat16 MFMA)",
                  "rocprofv3 --kernel-trace --stats -d " + RAW + "/fp_stats -o fp --output-format csv -- " + BENCH_FP,
-                 "fp_stats.log", 157.3, "TFLOP/s")
+                 "fp_stats.log", 833, "TFLOP/s")
     hbm_traffic(args.raw)
     mfma_utilisation(args.raw)
 
