@@ -179,8 +179,11 @@ size_t isr_noise_bank_static_capacity(void);
  *                      the ends of the int8 range (a ReLU clamp at the zero-point stays as r >= 0):
  *                      CONV r_out = act(M (bias + sum r_in w)), M = M0 2^-(31 + shift);
  *                      ADD act((Ma r_a + Mb r_b) 2^-shift); MAXPOOL; GAP M sum r_in; FC bias + sum r_in w;
- *                      input r_0 = x + sigma z - 128 - z_0.  Arithmetic: fp32 operands, exact
- *                      products, fp32 accumulation on the matrix cores.
+ *                      input r_0 = x + sigma z - 128 - z_0.  Arithmetic: fp32 operands and
+ *                      accumulation on the matrix cores: every operand enters with its 24 bits, the
+ *                      products of 8 channels are cut at 2^-24 of the largest and rounded together.
+ *                      On the evaluation's networks the logits are no further from the exact ones
+ *                      than those of an fp32 multiply-add per product.
  * Both run Alg. 1 as isr_certify does (same two loops, same decision on the tallies).  The noise of
  * copy s, logical element p = (c*H + y)*W + x, is sigma * z with z the binary32 standard-normal draw
  * of Philox4x32-10 counter (p >> 2, s, image_id, 8 + phase), key = seed, element p & 3: words

@@ -62,9 +62,9 @@ int mfma_row_of_channel(int c) {
     return 8 * a + 4 * h + b;
 }
 
-// the upper half of the fp32 number: exact for 8-bit integers
-uint16_t bf16_of_int8(int8_t v) {
-    const float f = v;
+// the upper half of the fp32 number: exact for whole numbers of at most 8 bits
+uint16_t bf16_of_int(int v) {
+    const float f = (float)v;
     uint32_t bits;
     std::memcpy(&bits, &f, 4);
     return (uint16_t)(bits >> 16);
@@ -77,9 +77,11 @@ size_t put(std::vector<uint8_t> &arena, const void *src, size_t bytes) {
     return off;
 }
 
-// Weights, per-channel constants and the K table of one convolution (k x k taps over a [H][W][Cin_p] input).
-int build_conv(const ParsedModel &pm, const HostOp &o, int k, int stride, int pad, bool fc, std::vector<uint8_t> &arena,
-               FloatOp &f) {
+// Weights, per-channel constants and the K table of one convolution (k x k taps over a [H][W][Cin_p] input).  Every other
+// channel is computed with its sign reversed (weights, bias and scale negated: the same numbers), beginning with channel
+// `first_negated`: the matrix unit's sums are a little too low on average (float_path.hip).
+int build_conv(const ParsedModel &pm, const HostOp &o, int k, int stride, int pad, bool fc, int first_negated,
+               std::vector<uint8_t> &arena, FloatOp &f) {
     const TensorDesc &ti = pm.tensors[o.a], &to = pm.tensors[o.out];
     if (k > 127) return ISR_ERR_UNSUPPORTED;
     FConvParams &c = f.conv;
@@ -99,13 +101,14 @@ int build_conv(const ParsedModel &pm, const HostOp &o, int k, int stride, int pa
     }
     for (int oc = 0; oc < to.C; ++oc) {
         const int row = (oc / 32) * 32 + mfma_row_of_channel(oc % 32);
+        const int sign = (oc ^ first_negated) & 1 ? 1 : -1;
         for (int ic = 0; ic < ti.C; ++ic)
             for (int t = 0; t < k * k; ++t) {
                 const int kidx = t * ti.Cp + ic;
-                w[((size_t)(kidx / 32) * c.Cout_pp + row) * 32 + kidx % 32] = bf16_of_int8(o.w[((size_t)oc * ti.C + ic) * k * k + t]);
+                w[((size_t)(kidx / 32) * c.Cout_pp + row) * 32 + kidx % 32] = bf16_of_int(sign * o.w[((size_t)oc * ti.C + ic) * k * k + t]);
             }
-        bias[oc] = (float)o.bias[oc];
-        scale[oc] = fc ? 1.f : (float)std::ldexp((double)o.M0[oc], -(31 + o.shift[oc]));
+        bias[oc] = (float)sign * (float)o.bias[oc];
+        scale[oc] = (float)sign * (fc ? 1.f : (float)std::ldexp((double)o.M0[oc], -(31 + o.shift[oc])));
     }
     // offsets now, pointers after the upload
     c.w = (const uint16_t *)put(arena, w.data(), w.size() * 2);
@@ -128,19 +131,21 @@ int build_float_net(isr_model *m) {
         if (o.b >= 0) uses[o.b]++;
     }
     std::vector<uint8_t> arena(256, 0);
+    int adds = 0;   // the channels with reversed sign change from one residual block to the next
     for (const HostOp &o : pm.ops) {
         FloatOp f;
         f.type = o.type; f.a = o.a; f.b = o.b; f.out = o.out;
         const TensorDesc &ti = pm.tensors[o.a], &to = pm.tensors[o.out];
         switch (o.type) {
         case OP_CONV:
-            if ((net->status = build_conv(pm, o, o.k, o.stride, o.pad, false, arena, f)) != ISR_OK) return net->status;
+            if ((net->status = build_conv(pm, o, o.k, o.stride, o.pad, false, adds & 1, arena, f)) != ISR_OK) return net->status;
             break;
         case OP_FC:
             if (ti.H != ti.W) return net->status = ISR_ERR_UNSUPPORTED;
-            if ((net->status = build_conv(pm, o, ti.H, 1, 0, true, arena, f)) != ISR_OK) return net->status;
+            if ((net->status = build_conv(pm, o, ti.H, 1, 0, true, adds & 1, arena, f)) != ISR_OK) return net->status;
             break;
         case OP_ADD: {
+            ++adds;
             f.ma = (float)std::ldexp((double)o.Ma, -o.sh);
             f.mb = (float)std::ldexp((double)o.Mb, -o.sh);
             f.relu = o.relu;
