@@ -80,14 +80,23 @@ uint32_t float_bits(uint32_t x) {
 // Guide tables: `mant` leading mantissa bits and the low `expo` exponent bits make the index; the exponent of the
 // largest x is 157 and `first`, that of the lowest buckets, differs from it in those bits only.
 struct GuideShape {
-    uint32_t mant, expo, first;
+    uint32_t mant, expo, first, most;   // most: the largest sigma up to which no bucket holds two thresholds
     size_t words() const { return (size_t)((157u & ((1u << expo) - 1)) + 1) << mant; }
 };
 // More buckets per octave as sigma grows.  Five exponent bits put x below `lo` at 2^-21 of the draws; tables of the large
 // sigmas keep to four (57 KB of LDS at sigma 1024, x below 2^18 in 2^-13 of the draws).
-const GuideShape BANK_SHAPES[] = {{6, 5, 137}, {7, 5, 137}, {8, 5, 137}, {9, 4, 145}, {10, 4, 145}};
+const GuideShape BANK_SHAPES[] = {{6, 5, 137, 86}, {7, 5, 137, 169}, {8, 5, 137, 332}, {9, 4, 145, 661}, {10, 4, 145, 1024}};
 // Pixels need the thresholds of draws within 255 only: a large sigma has none far out in the tail.
-const GuideShape PIXEL_SHAPES[] = {{6, 5, 137}, {7, 4, 144}, {8, 3, 152}, {9, 2, 156}, {10, 0, 157}};
+const GuideShape PIXEL_SHAPES[] = {{6, 5, 137, 86}, {7, 4, 144, 169}, {8, 3, 152, 332}, {9, 2, 156, 782}, {10, 0, 157, 1024}};
+
+// By sigma: filling one shape after the other until one takes the thresholds makes a build up to twenty times as long (sigma
+// 256: 44 us instead of 8 for the bank's table, 16 instead of 1 for the pixels'; sigma 1000: 138 / 26 and 22 / 1).
+template <size_t N>
+const GuideShape &shape_of(const GuideShape (&shapes)[N], uint32_t sigma) {
+    size_t k = 0;
+    while (k + 1 < N && sigma > shapes[k].most) ++k;
+    return shapes[k];
+}
 
 // The largest float below the lowest buckets' exponent: x below them is clamped to it.  Where there are thresholds down
 // there, its guide word holds a threshold of the same mantissa, and the draw is looked up.
@@ -107,29 +116,30 @@ NoiseSampler sampler_of(const GuideShape &g, uint32_t reach, bool below) {
     return s;
 }
 
-// false: two thresholds in one bucket
+// From threshold to threshold, into words that hold zeros; false: two thresholds in one bucket.
 bool fill_guide(const GuideShape &g, const uint64_t *T, uint32_t reach, uint32_t *guide) {
-    const uint32_t rest = 23 - g.mant, index_mask = (1u << (g.mant + g.expo)) - 1, ones = (1u << rest) - 1;
-    auto bits = [&](uint32_t j) { return float_bits((uint32_t)(T[j] >> 32)); };
-    auto put = [&](uint32_t bucket, uint32_t thr, uint32_t count) {
-        guide[bucket & index_mask] = bucket << 31 | thr << (8 + g.mant) | (reach - count);
+    const uint32_t rest = 23 - g.mant, index_mask = (1u << (g.mant + g.expo)) - 1, ones = (1u << rest) - 1, end = 158u << g.mant;
+    auto put = [&](uint32_t from, uint32_t to, uint32_t thr, uint32_t count) {   // buckets [from, to): consecutive words
+        uint32_t *word = guide + (from & index_mask);
+        const uint32_t key = thr << (8 + g.mant) | (reach - count);
+#pragma clang loop vectorize(disable) unroll(disable)   // most runs are a bucket or two
+        for (uint32_t b = from; b < to; ++b) *word++ = b << 31 | key;
     };
-    for (size_t i = 0; i < g.words(); ++i) guide[i] = 0;
-    uint32_t j = 0;
-    while (j < reach && bits(j) < g.first << 23) ++j;
-    if (j) {
-        const uint32_t b = (g.first << g.mant) - 1;   // the bucket of floor_of
-        if ((b & index_mask) >= g.words()) return false;
-        put(b, ones, j - 1);
+    uint32_t j = 0, next = g.first << g.mant;
+    while (j < reach && float_bits((uint32_t)(T[j] >> 32)) < g.first << 23) ++j;
+    if (j) {   // the bucket of floor_of
+        if (((next - 1) & index_mask) >= g.words()) return false;
+        put(next - 1, next, ones, j - 1);
     }
-    for (uint32_t b = g.first << g.mant; b < 158u << g.mant; ++b) {
-        const uint32_t count = j;
-        uint32_t thr = ones;
-        if (j < reach && bits(j) >> rest == b) thr = bits(j++) & ones;
-        if (j < reach && bits(j) >> rest == b) return false;
-        put(b, thr, count);
+    for (; j < reach; ++j) {
+        const uint32_t bits = float_bits((uint32_t)(T[j] >> 32)), b = bits >> rest;
+        if (b < next || b >= end) return false;
+        put(next, b, ones, j);
+        put(b, b + 1, bits & ones, j);
+        next = b + 1;
     }
-    return j == reach;
+    put(next, end, ones, reach);
+    return true;
 }
 
 }  // namespace
@@ -143,9 +153,10 @@ bool build_device_table(uint32_t sigma, DeviceNoiseTable &out) {
     const uint64_t *T = tab->T.data() + (tab->R - reach);
     std::memset(&out, 0, sizeof(out));
     for (uint32_t j = 0; j < reach; ++j) { out.hi[j] = (uint32_t)(T[j] >> 32); out.lo[j] = (uint32_t)T[j]; }
-    for (const GuideShape &g : PIXEL_SHAPES)
-        if (g.words() <= NOISE_GUIDE_MAX && fill_guide(g, T, reach, out.guide)) { out.s = sampler_of(g, reach, has_below(g, T, reach)); return true; }
-    return false;
+    const GuideShape &g = shape_of(PIXEL_SHAPES, sigma);
+    if (g.words() > NOISE_GUIDE_MAX || !fill_guide(g, T, reach, out.guide)) return false;
+    out.s = sampler_of(g, reach, has_below(g, T, reach));
+    return true;
 }
 
 bool build_bank_table(uint32_t sigma, std::vector<uint32_t> &words, uint32_t &n_out, uint32_t &R_out) {
@@ -153,15 +164,13 @@ bool build_bank_table(uint32_t sigma, std::vector<uint32_t> &words, uint32_t &n_
     if (!tab) return false;
     const uint64_t *T = tab->T.data();
     const size_t R = tab->R;
-    for (const GuideShape &g : BANK_SHAPES) {
-        words.assign(2 * R + g.words(), 0);
-        if (!fill_guide(g, T, (uint32_t)R, words.data())) continue;
-        uint32_t *hi = words.data() + g.words(), *lo = hi + R;
-        for (size_t j = 0; j < R; ++j) { hi[j] = (uint32_t)(T[j] >> 32); lo[j] = (uint32_t)T[j]; }
-        n_out = R_out = (uint32_t)R;
-        return true;
-    }
-    return false;
+    const GuideShape &g = shape_of(BANK_SHAPES, sigma);
+    words.assign(2 * R + g.words(), 0);
+    if (!fill_guide(g, T, (uint32_t)R, words.data())) return false;
+    uint32_t *hi = words.data() + g.words(), *lo = hi + R;
+    for (size_t j = 0; j < R; ++j) { hi[j] = (uint32_t)(T[j] >> 32); lo[j] = (uint32_t)T[j]; }
+    n_out = R_out = (uint32_t)R;
+    return true;
 }
 
 void set_bank_table(NoiseBankParams &p, const uint32_t *dev, size_t words, uint32_t R) {
