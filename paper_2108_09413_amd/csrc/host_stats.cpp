@@ -65,7 +65,9 @@ double rough_normal_quantile(double q) {
     return t - (2.515517 + t * (0.802853 + t * 0.010328)) / (1.0 + t * (1.432788 + t * (0.189269 + t * 0.001308)));
 }
 
-// One safeguarded Newton phase of isr_cp_lower; a step of `accept` p or less is the last.
+// One safeguarded Newton phase of isr_cp_lower.  Convergence is quadratic: behind a step the next is about its square times
+// half the logarithmic slope of the density (not less than over the law's width, for the slope is 0 at the mode).  A
+// step whose next would be `accept` p or less is the last.
 template <class F>
 F cp_newton(F a, F b, F target, F log_beta, F p, F accept) {
     F lo = 0, hi = 1;
@@ -75,7 +77,8 @@ F cp_newton(F a, F b, F target, F log_beta, F p, F accept) {
         if (f > 0) hi = p; else lo = p;
         const bool newton = dens > 0 && std::isfinite((double)(f / dens));
         F next = newton ? p - f / dens : (lo + hi) / 2;
-        if (newton && std::fabs(next - p) <= accept * p) return next;
+        const F slope = std::fabs((a - 1) / p - (b - 1) / (1 - p)) / 2 + std::sqrt((a + b) / (p * (1 - p))), step = next - p;
+        if (newton && step * step * slope <= accept * p) return next;
         if (!(next > lo && next < hi)) next = (lo + hi) / 2;
         p = next;
         if (hi - lo <= (F)1e-19L * hi) break;
@@ -108,14 +111,14 @@ extern "C" int isr_cp_lower(uint32_t k, uint32_t n, double alpha, double *p_lowe
     if (k == 0) { *p_lower = 0.0; return ISR_OK; }
     if (k == n) { *p_lower = (double)expl(logl((ld)alpha) / (ld)n); return ISR_OK; }
     // Root in p of P[Bin(n, p) >= k] = I_p(k, n-k+1) = alpha: safeguarded Newton from the normal approximation with the
-    // score interval, in double first (most of the steps at a fraction of their cost), then in long double.  Its
-    // convergence is quadratic: behind a step of 1e-12 p the next would be below the last place of p.
+    // score interval, in double first (most of the steps at a fraction of their cost), then in long double until the next
+    // step would be far below the last place of p.
     const ld a = k, b = (ld)n - k + 1.0L, log_beta = log_beta_fn(a, b);
     const double ph = (double)k / n, z = rough_normal_quantile(alpha < 0.5 ? alpha : 0.5), zz = z * z / n;
     double p0 = (ph + zz / 2 - z * std::sqrt(ph * (1 - ph) / n + zz / (4.0 * n))) / (1 + zz);
     if (!(p0 > 0.0 && p0 < 1.0)) p0 = ph * 0.5;
-    p0 = cp_newton<double>((double)a, (double)b, alpha, (double)log_beta, p0, 1e-7);
-    const ld p = cp_newton<ld>(a, b, alpha, log_beta, p0 > 0.0 && p0 < 1.0 ? (ld)p0 : ph * 0.5L, 1e-12L);
+    p0 = cp_newton<double>((double)a, (double)b, alpha, (double)log_beta, p0, 1e-11);
+    const ld p = cp_newton<ld>(a, b, alpha, log_beta, p0 > 0.0 && p0 < 1.0 ? (ld)p0 : ph * 0.5L, 1e-18L);
     *p_lower = (double)p;
     return ISR_OK;
 }
@@ -127,7 +130,8 @@ extern "C" int isr_normal_quantile(double p, double *z) {
     const bool upper = p > 0.5;
     const ld q = upper ? (ld)1.0 - (ld)p : (ld)p;  // exact in long double
     const ld lq = logl(q);
-    // double first, then long double; quadratic convergence as above
+    // double first, then long double; the convergence is quadratic: behind a step of 1e-12 x the next would be below the last
+    // place of x
     double x0 = rough_normal_quantile((double)q);
     if (!(x0 > 0.0)) x0 = (0.5 - (double)q) * 2.5066282746310005024;
     if ((double)q > 1e-290) x0 = quantile_newton<double>((double)lq, x0, 1e-8);

@@ -59,6 +59,26 @@ def test_cp_and_radius_against_golden_values(golden_dir):
             assert res.cls == 1 and res.radius / 64.0 == pytest.approx(float(r_txt), rel=tol)
 
 
+@pytest.mark.parametrize("n,misses,alpha", [(4_200_000_000, 160, 1e-12), (2 ** 32 - 1, 3, 1e-3), (10 ** 9, 160, 1e-12), (100_000, 50, 1e-3)])
+def test_cp_bound_with_few_misses_in_many_trials(n, misses, alpha):
+    """The law is narrow there (3e-9 of p), so Newton's last step has to be that much smaller.  By the tail of the misses,
+    P[Bin(n, q) <= misses] = alpha at p = 1 - q, summed in 60 digits; within the last place of p (half a place for its
+    rounding, the rest for the long double evaluation)."""
+    import mpmath as mp
+    with mp.workdps(60):
+        p = mp.mpf(isr.isr_cp_lower(n - misses, n, alpha))
+
+        def tail(q):
+            term = total = mp.exp(n * mp.log1p(-q))
+            for j in range(1, misses + 1):
+                term *= q / (1 - q) * (n - j + 1) / j
+                total += term
+            return total
+
+        ulp = mp.mpf(2) ** -53
+        assert tail(1 - p - ulp) > alpha > tail(1 - p + ulp)
+
+
 def test_statistics_agree_with_oracle_on_random_counts():
     rng = np.random.default_rng(3)
     for _ in range(300):
