@@ -705,8 +705,12 @@ hipError_t launch_narrow(const NarrowParams &p, int channels, hipStream_t st) {
                    p.classes_p < p.classes || (channels == 64 && p.nblocks == 0)))
         return hipErrorInvalidValue;
     if (p.head && p.counts && !valid_slots(p.slots)) return hipErrorInvalidValue;
-    // images per workgroup: as few as let every workgroup of the launch run at once (two per CU); beyond, as many as fit,
-    // to share the weights
+    // Images per workgroup: one while there is a CU for each; two while all workgroups run at once (two per CU); beyond, as many
+    // as fit, to share the weights.  A second image in a workgroup costs about what a second workgroup on its CU costs with
+    // 32 channels, and less with 64: us of the two stages of ResNet-20 with one / two / most images a workgroup
+    //   copies        256              384              512              768              1024             1536
+    //   32 channels   13 / 18 / 21     17 / 18 / 21     18 / 18 / 21     22 / 24 / 22     27 / 24 / 29     36 / 35 / 31
+    //   64 channels   15 / 15 / 24     19 / 16 / 24     20 / 17 / 24     27 / 20 / 25     32 / 21 / 25     45 / 29 / 27
     const bool one = p.B <= 256, two = p.B <= 1024;
     if (channels == 16) return launch_stage<16, 32, 1>(p, st);
     if (channels == 32) return one ? launch_stage<32, 16, 1>(p, st) : two ? launch_stage<32, 16, 2>(p, st) : launch_stage<32, 16, 3>(p, st);
