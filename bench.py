@@ -32,7 +32,7 @@ INT8_MFMA_PEAK_TOPS = 5000.0   # MI355X dense int8, published
 HBM_PEAK_GBS = 8000.0
 
 WORKLOADS = {
-    # name: (config number, default chunk, oracle samples for the CPU baseline)
+    # name: (config number, default chunk_samples of isr_set_workspace, oracle samples for the CPU baseline)
     # 668 samples x 14x14 pixels = 512 output tiles of 256 pixels: the deep layers fill the 256 CUs twice
     "resnet50": (4, 668, 48),
     "resnet20": (1, 8192, 2048),
@@ -419,7 +419,7 @@ def bench_noise_bank(args, isr, torch):
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(dt / args.steps * 1e3, 3),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "int16", "data": "synthetic",
         "config": {"workload": f"noise bank: {count} tensors x {d} draws (3x32x32), sigma {sigma}, int16, whole call "
-                               f"(table build + upload + kernel + synchronisation)"},
+                               f"(kernel + synchronisation; the table stays on the device between calls)"},
         "roofline": {"bound": "alu", "kernel": "noise_bank_kernel", "achieved": round(tops, 2), "peak": round(alu_peak, 2),
                      "unit": "T lane-instructions/s", "frac": round(tops / alu_peak, 4), "traffic": None,
                      "note": "113 executed VALU instructions per lane per 4 draws (rocprofv3 SQ_INSTS_VALU) over the "

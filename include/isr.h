@@ -19,6 +19,9 @@
  *     = one step of the 8-bit grid); 1 <= sigma <= 1024.
  *   - Results are a pure function of (model, x, sigma, n0, n, alpha, seed,
  *     image_id): independent of the chunk size and of kernel choices.
+ *   - A chunk is the run of noisy copies that goes through the network together:
+ *     the chunk_samples of isr_set_workspace, or more where more fit into the
+ *     workspace (below).
  *   - Calls on one isr_model must not overlap in time (one workspace).
  */
 #ifndef ISR_H
@@ -88,7 +91,11 @@ int isr_model_info(const isr_model *m, int *C, int *H, int *W, int *num_classes)
 /* Device scratch for activations of `chunk_samples` noisy copies processed at a
  * time.  The caller allocates it (e.g. a torch uint8 tensor), keeps it alive
  * while the model uses it, and passes the HIP stream all work is enqueued on
- * (NULL = the default stream). */
+ * (NULL = the default stream).  isr_workspace_bytes is what every plan of the model
+ * needs for that many copies, the one that stores each tensor among them.  A network
+ * whose stages each run in one kernel (32 x 32 images) stores a fraction of the
+ * tensors: while fusion is enabled it takes as many copies at a time as the `bytes`
+ * given hold, chunk_samples at the least, and cuts longer runs into equal parts. */
 size_t isr_workspace_bytes(const isr_model *m, uint32_t chunk_samples);
 int isr_set_workspace(isr_model *m, void *workspace_device, size_t bytes, uint32_t chunk_samples,
                       void *hip_stream);
@@ -130,8 +137,8 @@ typedef struct isr_item {
  * optional uint32 [n_items][classes] vote arrays (host), are exactly what
  * isr_certify / isr_predict return for (x[items[i].image], items[i].sigma, n0, n,
  * alpha, seed, items[i].image_id).  The sample slots of all pairs form one list
- * that is cut into chunks of chunk_samples regardless of pair boundaries, so a
- * call with small n per pair still launches full chunks.  ISR_ERR_ARG for an
+ * that is cut into chunks regardless of pair boundaries, so a call with small n
+ * per pair still launches full chunks.  ISR_ERR_ARG for an
  * image index or sigma out of range, more than 8 distinct sigmas, n_items == 0. */
 int isr_certify_batch(isr_model *m, const uint8_t *x_device, uint32_t n_images, const isr_item *items_host,
                       uint32_t n_items, uint32_t n0, uint32_t n, double alpha, uint64_t seed,
@@ -158,7 +165,7 @@ int isr_noise_bank(uint32_t sigma, uint64_t seed, uint32_t bank_id, uint32_t fir
  * set-up, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same draws, same
  * error behaviour as isr_noise_bank, but the sampler's table goes into a fixed array in device
  * memory that is part of the library's code object (isr_noise_bank_static_capacity() bytes, 64 KiB:
- * room for every sigma up to about 420; each GPU the library runs on holds its own copy for the
+ * room for every sigma up to 543; each GPU the library runs on holds its own copy for the
  * life of the process) and the call performs no hipMalloc / hipFree.  ISR_ERR_WORKSPACE when the
  * table of this sigma does not fit the array.  All calls on one GPU share that array: calls that
  * overlap in time on one GPU, from any thread or stream, race -- serialise them.  A call leaves
@@ -199,6 +206,8 @@ size_t isr_noise_bank_static_capacity(void);
 #define ISR_FLOATRS_QUANT 1
 #define ISR_FLOATRS_FP 2
 size_t isr_float_workspace_bytes(isr_model *m, uint32_t chunk_samples, int system);
+/* ISR_FLOATRS_FP: the copies per chunk.  ISR_FLOATRS_QUANT: the chunk_samples of isr_set_workspace; its
+ * chunks are those of the int8 network.  0 without a workspace. */
 uint32_t isr_float_chunk(const isr_model *m, int system);
 int isr_float_certify(isr_model *m, const uint8_t *x_device, float sigma, uint32_t n0, uint32_t n, double alpha,
                       uint64_t seed, uint32_t image_id, int system, isr_result *out, uint32_t *counts0_host,
@@ -326,7 +335,7 @@ typedef struct isr_kernel_stat {
 } isr_kernel_stat;
 
 /* every_chunks > 0: bracket every kernel launch of each every_chunks-th chunk
- * with HIP events and accumulate per kernel instance (the chunk is followed by a
+ * (as processed: see isr_set_workspace) with HIP events and accumulate per kernel instance (the chunk is followed by a
  * stream synchronisation); 0 switches timing off.  Either call resets the
  * accumulators. */
 int isr_profile(isr_model *m, uint32_t every_chunks);
