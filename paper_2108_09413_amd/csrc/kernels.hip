@@ -79,10 +79,10 @@ hipError_t launch_noise(const NoiseParams &p, hipStream_t st) {
 // above with the tensor index in the sample word, the bank id in the image word and phase 2.  The guide table (7.5 KB up
 // to sigma 86, 57 KB at sigma 1024) is staged into LDS; the thresholds stay in memory, for the few draws that it leaves open.
 //
-// Bound by the issue of the generator's and the sampler's integer arithmetic, about 100 instructions per four draws (two
+// Bound by the issue of the generator's and the sampler's integer arithmetic, 113 instructions per four draws (two
 // blocks at a time, for more independent instructions, measured the same).  A search in buckets of equal width left a
 // wave in three (sigma 32) or nearly every one (sigma 256) a draw in the tail to search for, and divided 64-bit indices per
-// draw: 50 000 x 3072 draws took 212 us at sigma 32 and 280 at sigma 1000, now 129 and 145.
+// draw: 50 000 x 3072 draws took 212 us at sigma 32 and 280 at sigma 1000, now 130 and 140.
 __global__ __launch_bounds__(1024) void noise_bank_kernel(const NoiseBankParams p) {
     extern __shared__ __attribute__((aligned(16))) uint32_t guide[];
     const uint32_t threads = blockDim.x;

@@ -9,8 +9,8 @@
 
 namespace {
 
-// Room for the table of every sigma up to about 500 grid units (8 bytes per threshold, R = about
-// 9 sigma thresholds, plus a guide table of 7.5 to 28 KB).  Every GPU the library runs on holds its
+// Room for the table of every sigma up to 543 grid units (8 bytes per threshold, R = about
+// 8.5 sigma thresholds, plus a guide table of 7.5 to 30 KB).  Every GPU the library runs on holds its
 // own copy of this array until the process ends.
 constexpr size_t SCRATCH_BYTES = 64 * 1024;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
