@@ -1,7 +1,7 @@
 """Writes the text summaries under profiles/ from raw rocprofv3 output.
 
 The raw output (CSV files of `rocprofv3 --kernel-trace --stats` and `--pmc` runs of bench.py) is
-produced on the GPU machine by the commands that each summary quotes; this script only reads those
+produced on the machine with the GPU by the commands that each summary quotes; this script only reads those
 files and the JSON line bench.py printed in the same run.  Usage, from the repository root:
 
     python -m paper_2108_09413_amd.profile_report --raw <directory>
@@ -105,7 +105,7 @@ def kernel_stats(raw, sub, out_name, title, command, bench_log, peak, unit):
         return
     rows = list(csv.DictReader(open(path)))
     bench = last_json(os.path.join(raw, bench_log))
-    lines = ["# " + title, "", "Command (on the MI355X box, from the repository root):", "",
+    lines = ["# " + title, "", "Command (on the MI355X machine, from the repository root):", "",
              "    " + PRE + command, "", "sources_sha256: " + sources_sha256(), "",
              "| kernel (profiler name) | name in the library's timing report | calls | total ms | avg us | % |", "|---|---|---|---|---|---|"]
     for r in rows:
