@@ -703,6 +703,7 @@ int isr_noise_bank(uint32_t sigma, uint64_t seed, uint32_t bank_id, uint32_t fir
             return ISR_ERR_ARG;
         }
         t.words = words.size();
+        bank_guide(words, t.R);
         std::memcpy(t.host, words.data(), t.words * 4);
         e = hipMemcpyAsync(t.dev, t.host, t.words * 4, hipMemcpyHostToDevice, st);
     }

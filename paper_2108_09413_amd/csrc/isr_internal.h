@@ -49,6 +49,9 @@ bool build_bank_table(uint32_t sigma, std::vector<uint32_t> &words, uint32_t &n_
 struct NoiseBankParams;
 // The table arguments of a launch from such a block in device memory (16-byte aligned).
 void set_bank_table(NoiseBankParams &p, const uint32_t *dev, size_t words, uint32_t R);
+// The guide words of a block into the form that noise_bank_kernel reads: |draw| left of the bucket's threshold << 16 | the 16 lowest
+// float bits of the threshold.
+void bank_guide(std::vector<uint32_t> &words, uint32_t R);
 // Records the hipError_t that isr_last_device_error() reports on this thread.
 void set_last_device_error(int hip_error);
 bool build_device_table(uint32_t sigma, DeviceNoiseTable &out);

@@ -76,47 +76,107 @@ hipError_t launch_noise(const NoiseParams &p, hipStream_t st) {
 // ---------------------------------------------------------------------------
 // Noise bank: the discrete-Gaussian draws themselves (no image, no saturation), int16, for
 // noise that is sampled ahead of training and stored.  Same generator and counter layout as
-// above with the tensor index in the sample word, the bank id in the image word and phase 2.  The guide table (7.5 KB up
-// to sigma 86, 57 KB at sigma 1024) is staged into LDS; the thresholds stay in memory, for the few draws that it leaves open.
+// above with the tensor index in the sample word, the bank id in the image word and phase 2.  The guide table (15 KB up
+// to sigma 169, 57 KB at sigma 1024) is staged into LDS; the thresholds stay in memory, for the few draws that it leaves open.
 //
-// Bound by the issue of the generator's and the sampler's integer arithmetic, 113 instructions per four draws (two
-// blocks at a time, for more independent instructions, measured the same).  A search in buckets of equal width left a
-// wave in three (sigma 32) or nearly every one (sigma 256) a draw in the tail to search for, and divided 64-bit indices per
-// draw: 50 000 x 3072 draws took 212 us at sigma 32 and 280 at sigma 1000, now 130 and 140.
-__global__ __launch_bounds__(1024) void noise_bank_kernel(const NoiseBankParams p) {
-    extern __shared__ __attribute__((aligned(16))) uint32_t guide[];
-    const uint32_t threads = blockDim.x;
-    for (uint32_t i = threadIdx.x; i < p.guide_words / 4; i += threads) ((uint4 *)guide)[i] = ((const uint4 *)p.guide)[i];
+// Bound by the issue of the generator's and the sampler's integer arithmetic.  A draw is one LDS read and seven instructions up to
+// its word t, two and a half from there on: the guide word (bank_guide) has |draw| left of its bucket's threshold on top of the
+// threshold's 16 lowest float bits, so subtracting the draw's own bits borrows one where x lies behind the threshold and
+// leaves zeros below where that is open; sign and packing go by halves of a register.  81 instructions per four draws instead of
+// 113 with noise_draw4, which keeps to guides of half the size up to sigma 86: there is less to stage for workgroups that draw
+// few pixels a thread (a net's first kernel on 32 x 32 images got 1 % slower with the words used here, and a new sigma's first
+// call 10 us).
+// WHOLE: tensors of whole waves (d a multiple of 256).  A wave's draws then lie in one tensor, and what depends on the tensor
+// alone -- a quarter of the first two rounds of the generator, indices, addresses -- is scalar arithmetic.
+// 50 000 x 3072 draws, calls in a row: 130 -> 108 us at sigma 32; one call alone 149 -> 121 at sigma 256, 148 -> 129 at 1000.
+
+typedef short v2s __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ v2s upper_halves(uint32_t a, uint32_t b) { return __builtin_bit_cast(v2s, __builtin_amdgcn_perm(b, a, 0x07060302u)); }
+
+// The four draws of the Philox block of counter (grp, c1, c2, c3), two to a register.
+__device__ __forceinline__ void bank_draw4(const uint32_t *guide, const NoiseSampler &s, const uint32_t *thi, const uint32_t *tlo,
+                                           uint32_t grp, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t key0, uint32_t key1, v2s (&d)[2]) {
+    uint32_t u[4], t[4];
+    philox4x32_10(grp, c1, c2, c3, key0, key1, u);
+    auto bits_of = [&](int j) { return __float_as_uint(__builtin_amdgcn_fmed3f((float)(u[j] ^ (uint32_t)((int)u[j] >> 31)), s.lo, s.hi)); };
+    auto word = [&](uint32_t bits) { return *(const uint32_t *)((const uint8_t *)guide + ((bits >> s.shift) & s.mask)); };
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t bits = bits_of(j);
+        t[j] = word(bits) - (bits & 0xFFFF);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {   // with m = |draw| and r = -1 right of the centre, 0 left of it: r - (m ^ r)
+        const v2s r = upper_halves(u[2 * j], u[2 * j + 1]) >> 15;
+        d[j] = r - (upper_halves(t[2 * j], t[2 * j + 1]) ^ r);
+    }
+    const uint16_t low[4] = {(uint16_t)t[0], (uint16_t)t[1], (uint16_t)t[2], (uint16_t)t[3]};
+    if (min(min(low[0], low[1]), min(low[2], low[3])) == 0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (low[j] == 0)
+                d[j >> 1][j & 1] = (short)noise_draw_slow(thi, tlo, s, u[j], s.reach - (word(bits_of(j)) >> 16), grp, c1, c2, c3, key0, key1, j);
+    }
+}
+
+template <int WORDS, int THREADS, bool WHOLE>
+__global__ __launch_bounds__(THREADS) void noise_bank_kernel(const NoiseBankParams p) {
+    __shared__ __attribute__((aligned(16))) uint32_t guide[WORDS];
+    for (uint32_t i = threadIdx.x; i < p.guide_words / 4; i += THREADS) ((uint4 *)guide)[i] = ((const uint4 *)p.guide)[i];
     __syncthreads();
     const uint32_t groups_per_tensor = p.d >> 2;
-    const uint64_t total = (uint64_t)groups_per_tensor * p.count, step = (uint64_t)gridDim.x * threads;
-    const uint32_t dt = (uint32_t)(step / groups_per_tensor), dg = (uint32_t)(step % groups_per_tensor);
-    uint64_t g = (uint64_t)blockIdx.x * threads;
-    uint32_t t = (uint32_t)((g + threadIdx.x) / groups_per_tensor), grp = (uint32_t)(g + threadIdx.x - (uint64_t)t * groups_per_tensor);
-    for (; g < total; g += step) {   // uniform
-        int d[4];
-        noise_draw4(guide, p.s, p.thi, p.tlo, grp, p.first + t, p.bank, 4u, p.key0, p.key1, d);
-        const uint32_t w0 = __builtin_amdgcn_perm((uint32_t)d[1], (uint32_t)d[0], 0x05040100u), w1 = __builtin_amdgcn_perm((uint32_t)d[3], (uint32_t)d[2], 0x05040100u);
-        if (threadIdx.x < total - g) ((uint2 *)(p.out + 4 * g))[threadIdx.x] = make_uint2(w0, w1);
-        t += dt;
-        grp += dg;
-        if (grp >= groups_per_tensor) { grp -= groups_per_tensor; ++t; }
+    auto draw = [&](uint32_t grp, uint32_t t) {
+        v2s d[2];
+        bank_draw4(guide, p.s, p.thi, p.tlo, grp, p.first + t, p.bank, 4u, p.key0, p.key1, d);
+        return make_uint2(__builtin_bit_cast(uint32_t, d[0]), __builtin_bit_cast(uint32_t, d[1]));
+    };
+    if constexpr (WHOLE) {
+        const uint32_t lane = threadIdx.x & 63, runs = groups_per_tensor >> 6;   // of 64 groups, one per wave and step
+        const uint64_t total = (uint64_t)runs * p.count, step = (uint64_t)gridDim.x * (THREADS / 64);
+        const uint32_t dt = (uint32_t)(step / runs), dr = (uint32_t)(step % runs);
+        uint64_t q = (uint64_t)blockIdx.x * (THREADS / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        uint32_t t = (uint32_t)(q / runs), r = (uint32_t)(q - (uint64_t)t * runs);
+        for (; q < total; q += step) {
+            ((uint2 *)p.out + q * 64)[lane] = draw(r * 64 + lane, t);
+            t += dt;
+            r += dr;
+            if (r >= runs) { r -= runs; ++t; }
+        }
+    } else {
+        const uint64_t total = (uint64_t)groups_per_tensor * p.count, step = (uint64_t)gridDim.x * THREADS;
+        const uint32_t dt = (uint32_t)(step / groups_per_tensor), dg = (uint32_t)(step % groups_per_tensor);
+        uint64_t g = (uint64_t)blockIdx.x * THREADS;
+        uint32_t t = (uint32_t)((g + threadIdx.x) / groups_per_tensor), grp = (uint32_t)(g + threadIdx.x - (uint64_t)t * groups_per_tensor);
+        for (; g < total; g += step) {   // uniform
+            const uint2 w = draw(grp, t);
+            if (threadIdx.x < total - g) ((uint2 *)p.out + g)[threadIdx.x] = w;
+            t += dt;
+            grp += dg;
+            if (grp >= groups_per_tensor) { grp -= groups_per_tensor; ++t; }
+        }
     }
+}
+
+template <int WORDS, int THREADS>
+static hipError_t launch_noise_bank_guide(const NoiseBankParams &p, hipStream_t st) {
+    const uint64_t total = (uint64_t)(p.d >> 2) * p.count;
+    uint64_t blocks = (total + THREADS - 1) / THREADS;
+    if (blocks > 256 * (2048 / THREADS)) blocks = 256 * (2048 / THREADS);   // a full chip
+    set_kernel_name("noise_bank_kernel");
+    const dim3 grid((unsigned)blocks), block(THREADS);
+    if (p.d % 256 == 0) hipLaunchKernelGGL((noise_bank_kernel<WORDS, THREADS, true>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((noise_bank_kernel<WORDS, THREADS, false>), grid, block, 0, st, p);
+    return hipGetLastError();
 }
 
 hipError_t launch_noise_bank(const NoiseBankParams &p, hipStream_t st) {
     if (p.count == 0) return hipSuccess;
     if (p.d == 0 || (p.d & 3) != 0 || p.s.reach < 1 || p.s.reach > 16384 || !p.thi || !p.tlo || !p.guide || !p.out) return hipErrorInvalidValue;
-    const size_t lds = (size_t)p.guide_words * 4;
-    if (lds <= (p.s.mask >> 1) || lds > 64 * 1024 || (p.guide_words & 3)) return hipErrorInvalidValue;   // the index's leading exponent bit is set for the largest x
+    if (p.guide_words * 4 <= (p.s.mask >> 1) || p.guide_words > 14336 || (p.guide_words & 3)) return hipErrorInvalidValue;   // the index's leading exponent bit is set for the largest x
     // the waves of a workgroup share a guide: large ones where eight workgroups' guides would not fit a CU
-    const unsigned threads = lds > 16 * 1024 ? 1024 : 256;
-    const uint64_t total = (uint64_t)(p.d >> 2) * p.count;
-    uint64_t blocks = (total + threads - 1) / threads;
-    if (blocks > 256 * (2048 / threads)) blocks = 256 * (2048 / threads);   // a full chip
-    set_kernel_name("noise_bank_kernel");
-    hipLaunchKernelGGL(noise_bank_kernel, dim3((unsigned)blocks), dim3(threads), lds, st, p);
-    return hipGetLastError();
+    if (p.guide_words <= 3840) return launch_noise_bank_guide<3840, 256>(p, st);
+    if (p.guide_words <= 7680) return launch_noise_bank_guide<7680, 1024>(p, st);
+    return launch_noise_bank_guide<14336, 1024>(p, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -10,7 +10,7 @@
 namespace {
 
 // Room for the table of every sigma up to 543 grid units (8 bytes per threshold, R = about
-// 8.5 sigma thresholds, plus a guide table of 7.5 to 30 KB).  Every GPU the library runs on holds its
+// 8.5 sigma thresholds, plus a guide table of 15 to 30 KB).  Every GPU the library runs on holds its
 // own copy of this array until the process ends.
 constexpr size_t SCRATCH_BYTES = 64 * 1024;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
@@ -52,6 +52,7 @@ extern "C" int isr_noise_bank_static(uint32_t sigma, uint64_t seed, uint32_t ban
     uint32_t n = 0, R = 0;
     if (!build_bank_table(sigma, host, n, R)) return ISR_ERR_ARG;
     if (host.size() * 4 > SCRATCH_BYTES) return ISR_ERR_WORKSPACE;   // this sigma's table does not fit the fixed array
+    bank_guide(host, R);
     void *ptr = nullptr;
     hipError_t e = scratch_address(&ptr);
     hipStream_t st = (hipStream_t)hip_stream;

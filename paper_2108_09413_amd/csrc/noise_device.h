@@ -19,7 +19,8 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
     for (int r = 0; r < 10; ++r) {
         uint64_t p0 = (uint64_t)0xD2511F53u * c0;   // one 32x32->64 multiply gives both halves
         uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-        c0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+        c0 = r == 0 ? (uint32_t)(p1 >> 32) ^ c1 ^ k0   // scalar where image and sample are uniform
+                    : xor3((uint32_t)(p1 >> 32), c1, k0);
         c1 = (uint32_t)p1;
         c2 = xor3((uint32_t)(p0 >> 32), c3, k1);
         c3 = (uint32_t)p0;

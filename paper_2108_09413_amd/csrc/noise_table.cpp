@@ -84,8 +84,9 @@ struct GuideShape {
     size_t words() const { return (size_t)((157u & ((1u << expo) - 1)) + 1) << mant; }
 };
 // More buckets per octave as sigma grows.  Five exponent bits put x below `lo` at 2^-21 of the draws; tables of the large
-// sigmas keep to four (57 KB of LDS at sigma 1024, x below 2^18 in 2^-13 of the draws).
-const GuideShape BANK_SHAPES[] = {{6, 5, 137, 86}, {7, 5, 137, 169}, {8, 5, 137, 332}, {9, 4, 145, 661}, {10, 4, 145, 1024}};
+// sigmas keep to four (57 KB of LDS at sigma 1024, x below 2^18 in 2^-13 of the draws).  At least 2^7 buckets: the 16 lowest bits
+// of a float then hold all below its bucket (bank_guide).
+const GuideShape BANK_SHAPES[] = {{7, 5, 137, 169}, {8, 5, 137, 332}, {9, 4, 145, 661}, {10, 4, 145, 1024}};
 // Pixels need the thresholds of draws within 255 only: a large sigma has none far out in the tail.
 const GuideShape PIXEL_SHAPES[] = {{6, 5, 137, 86}, {7, 4, 144, 169}, {8, 3, 152, 332}, {9, 2, 156, 782}, {10, 0, 157, 1024}};
 
@@ -171,6 +172,16 @@ bool build_bank_table(uint32_t sigma, std::vector<uint32_t> &words, uint32_t &n_
     for (size_t j = 0; j < R; ++j) { hi[j] = (uint32_t)(T[j] >> 32); lo[j] = (uint32_t)T[j]; }
     n_out = R_out = (uint32_t)R;
     return true;
+}
+
+void bank_guide(std::vector<uint32_t> &words, uint32_t R) {
+    const size_t n = words.size() - 2 * (size_t)R;
+    for (const GuideShape &g : BANK_SHAPES)
+        if (g.words() == n) {
+            const uint32_t rest = 23 - g.mant, ones = (1u << rest) - 1, key_shift = 8 + g.mant;
+            for (uint32_t i = 0; i < n; ++i)   // a word holds one of its index bits: the others are where it stands
+                words[i] = (words[i] & NOISE_DRAW_MASK) << 16 | ((i << rest | (words[i] >> key_shift & ones)) & 0xFFFF);
+        }
 }
 
 void set_bank_table(NoiseBankParams &p, const uint32_t *dev, size_t words, uint32_t R) {

@@ -107,6 +107,16 @@ def test_sampler_guide_tables_of_every_resolution(isr, sigma):
     m.close()
 
 
+@pytest.mark.parametrize("d,count", [(252, 300), (256, 1), (256, 9000), (260, 300), (512, 4100), (768, 2800), (3072, 700)])
+def test_noise_bank_tensors_of_whole_and_of_ragged_waves(isr, d, count):
+    """Tensors of a multiple of 256 draws (a wave's draws lie in one tensor) and others; more waves than one launch holds at
+    once, so that each goes on to further tensors: every draw, for a guide table of each workgroup size."""
+    _say(f"noise bank d={d} count={count}")
+    for sigma in (32, 200, 1000):
+        got = isr.isr_noise_bank(sigma, 5, 11, 1000, count, d).cpu().numpy()
+        assert np.array_equal(got, oracle.noise_bank(sigma, 5, 11, 1000, count, d)), sigma
+
+
 @pytest.mark.parametrize("sigma", [2, 32])
 def test_device_sampler_law_at_scale(isr, sigma):
     """1.5e8 draws of the device sampler (a full stored-noise bank) against Def. 3.3 itself:
