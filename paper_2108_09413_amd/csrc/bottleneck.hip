@@ -6,7 +6,7 @@
 // 32-pixel MFMA fragments (no padding columns in the two later convolutions, whose requantisation
 // arithmetic is what bounds this kernel), 10 x 30 = 300 halo pixels = ten fragments for the first.
 //   1. The first convolution runs as a GEMM over the halo pixels (wave = 32 channels x 3 or 2 fragments):
-//      K steps of 64 input channels go from global memory straight into two LDS stages.
+//      K steps of 64 input channels go from global memory straight into three LDS stages.
 //      Recomputing the halo costs a third more of this (cheap) GEMM and saves writing and
 //      re-reading t1.
 //   2. Its int8 result goes into an LDS tile [halo pixel][64 channels]; halo pixels outside the
@@ -24,10 +24,14 @@
 // x is read once (plus halo, mostly cache hits), t1 and t2 never leave the CU.
 //
 // Bounds, 668 images of 56 x 56 x 256 (identity block): memory 1.07 GB = 210 us at the rate of a large copy, issue of the
-// requantisation and its data movement about 200 us, matrix unit 60 us, in phases that barriers separate.
+// requantisation and its data movement about 180 us, matrix unit 75 us, in phases that barriers separate.
 // Two workgroups of eight waves a CU instead of two of four: 344 -> 322 us (projection block 360 -> 340).
+// All operands of step 1 on their way at once, the weights of steps 3 and 4 fetched a step early, the residual's and the
+// output's places in a table (224 divisions by the tile's width instead of one per wave and fragment), t1 and t2 at 80 bytes a
+// pixel (taps as immediate offsets): 1640 -> 1350 vector instructions a wave, 354 -> 327 us; projection block 382 -> 344,
+// block + next 486 -> 428 (one card).
 // With the next stage's 1x1 convolution (256 -> 128) in the kernel the sum is not read back and, under a stride-2
-// projection, three quarters of it are not written: 441 us against 322 + 157 for two kernels.
+// projection, three quarters of it are not written: when added 441 us against 322 + 157 for two kernels.
 #include "conv_device.h"
 
 namespace isr {
@@ -45,17 +49,26 @@ constexpr int NH_FR = 10;                      // fragments (of 32 GEMM columns)
 constexpr int NP_FR = 7;                       // fragments covering the 224 output pixels, all full
 constexpr int RN = 128;                        // outputs of the next stage's first convolution
 constexpr int W2_CHUNKS = 37;                  // 16-byte chunks per 3x3 weight row in LDS: 36 + 1 pad (bank spread)
+constexpr int NROWS = (NHALO + 15) / 16 * 16;  // pixel rows of a stage: whole loads of a wave
+constexpr int TP = 80;                         // bytes per pixel of t1 and t2 in LDS: 64 + 16 (bank spread without a swizzle, so that taps are immediate offsets)
 
 // MODE 0: head (t2 stored); 1: whole identity block (residual = x); 2: whole first block of a stage --
 // the residual is itself a 1x1 convolution of x (projection shortcut, Cin = 64), computed here as well; 3: an identity
-// block of 256 channels and the 1x1 convolution into 128 channels that reads its sum (the next stage's first).
+// block of 256 channels and the 1x1 convolution into 128 channels that reads its sum (the next stage's first); 4: an
+// identity block of 256 channels.
 template <int MODE, int RQ, int RQA>
 __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p) {
-    constexpr bool TAIL = MODE != 0, PROJ = MODE == 2, IDENTITY = MODE == 1 || MODE == 3, REDUCE = MODE == 3;
-    constexpr int KB = 64, STAGE = (64 + 32 * NH_FR) * KB;            // 64 weight rows + 320 pixel rows per stage
-    static_assert(64 * W2_CHUNKS * 16 <= 2 * STAGE, "3x3 weights fit the operand stages");
-    __shared__ __attribute__((aligned(16))) int8_t Ls[2 * STAGE];     // step 1: two stages (A rows, then B rows); step 3: 3x3 weights
-    __shared__ __attribute__((aligned(16))) int8_t T[32 * NH_FR * 64]; // t1: [halo pixel][channel chunk ^ swizzle]; later t2: [output pixel][...]
+    constexpr bool TAIL = MODE != 0, PROJ = MODE == 2, IDENTITY = MODE == 1 || MODE >= 3, REDUCE = MODE == 3;
+    constexpr int NK = MODE == 2 ? 1 : MODE >= 3 ? 4 : 0;              // K steps of the first convolution, 0: any number
+    constexpr int KB = 64, STAGE = (64 + NROWS) * KB;                 // 64 weight rows, then the pixel rows
+    constexpr int TBYTES = NHALO * TP;                                // t1: [halo pixel][64 channels]; later t2: [output pixel][64 channels]
+    constexpr int WBYTES = 64 * W2_CHUNKS * 16;                       // 3x3 weights
+    constexpr int FRONT = NK == 1 ? WBYTES : 2 * STAGE;
+    static_assert(FRONT >= WBYTES && FRONT >= STAGE && STAGE <= TBYTES, "regions");
+    // step 1: three stages; from step 2 on the 3x3 weights in the space of the first two, t1 in that of the third
+    __shared__ __attribute__((aligned(16))) int8_t Ls[FRONT + TBYTES];
+    int8_t *const T = Ls + FRONT;
+    __shared__ __attribute__((aligned(8))) uint2 at_s[32 * NP_FR];   // per output pixel: index (image, row, column) or ~0 (outside the image, not stored); byte offset of its row in a stage
     __shared__ int prm[2][4][64];                                     // bias, M0, chi, shift-1 of the first two convolutions
     __shared__ __attribute__((aligned(16))) int prm3[TAIL ? 4 : 1][TAIL ? 256 : 4];
     __shared__ __attribute__((aligned(16))) int prmp[PROJ ? 4 : 1][PROJ ? 256 : 4];   // the same for the projection
@@ -78,29 +91,34 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
     // ---- step 1: t1 accumulators over the halo, K = Cin_p in steps of 64 ----
     // LDS position (row, col) of a stage holds K chunk col ^ swz(row); a lane fetches the same
     // chunk `cl` for all its rows (their numbers differ by multiples of 128): the weight row tid / 4 (waves 0 .. 3) or
-    // pixel row tid / 4 - 64, and two more pixel rows
+    // pixel row tid / 4 - 64, and two more pixel rows (the last wave has one: it fetches that twice)
     const int col = tid & 3, row0 = tid >> 2, cl = col ^ swz<4>(row0);
+    const bool short_wave = wave == 7;
+    static_assert(64 + NROWS == 2 * 128 + 7 * 16, "the last wave's third rows do not exist");
     const int8_t *row[3];
     bool inside[3];
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        const int h = row0 + 128 * j - 64, hy = h / HW, hx = h - hy * HW, y = y0 + hy, x = x0 + hx;
+        const int h = row0 + 128 * (j == 2 && short_wave ? 1 : j) - 64, hy = h / HW, hx = h - hy * HW, y = y0 + hy, x = x0 + hx;
         inside[j] = h >= 0 && h < NHALO && (unsigned)y < (unsigned)p.H && (unsigned)x < (unsigned)p.W;
         row[j] = p.in + (((long)b * p.H + y) * p.W + x) * p.Cin_p + cl * 16;
         if (j == 0 && wave < 4) { inside[j] = true; row[j] = p.w1 + (long)row0 * p.Cin_p + cl * 16; }
-        // halo pixels outside the image (and the 20 columns past the halo): any readable bytes,
+        // halo pixels outside the image (and the 4 rows past the halo): any readable bytes,
         // their results are replaced in step 2 or never used
         if (!inside[j]) row[j] = p.zpad;
     }
+    const uint32_t lds0 = lds_address(Ls);
     auto issue = [&](int ks, int buf) {
 #pragma unroll
         for (int j = 0; j < 3; ++j)
-            ISR_GLOBAL_TO_LDS16(row[j] + (inside[j] ? ks * KB : 0), &Ls[buf * STAGE + j * 8192 + wave * 1024]);
+            ISR_GLOBAL_TO_LDS16_AT(row[j] + (inside[j] ? ks * KB : 0), lds0 + (buf == 2 ? FRONT : buf * STAGE) + (j == 2 && short_wave ? 1 : j) * 8192 + wave * 1024);
     };
-    const int nk = p.Cin_p / KB;
+    // With 256 input channels every operand is on its way before any is waited for: steps 0 and 1, the constants behind them,
+    // step 2 and, in registers until a stage is free, step 3.
+    const int nk = NK ? NK : p.Cin_p / KB;
     issue(0, 0);
-    if (nk > 1) issue(1, 1);            // both stages are free at the start
-    // the constants, all on their way behind the first operands before any is waited for
+    if (NK != 1 && nk > 1) issue(1, 1);
+    v4i late[3];
     {
         const int cv = (tid >> 6) & 1, c = tid & 63, ct = tid < p.Cout_p ? tid : 0;
         const RqRaw r12 = cv ? rq_fetch(p.bias2, p.m0s2, p.chi2, p.shm12, c) : rq_fetch(p.bias1, p.m0s1, p.chi1, p.shm11, c);
@@ -108,6 +126,16 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
         if constexpr (TAIL) r3 = rq_fetch(p.bias3, p.m0s3, p.chi3, p.shm13, ct);
         if constexpr (PROJ) rp = rq_fetch(p.biasp, p.m0sp, p.chip, p.shm1p, ct);
         if constexpr (REDUCE) rp = rq_fetch(p.biasp, p.m0sp, p.chip, p.shm1p, tid & (RN - 1));
+        asm volatile("" ::: "memory");   // the loads above come first
+        if (NK != 1 && nk > 2) issue(2, 2);
+        if constexpr (NK == 4)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) late[j] = *(const v4i *)(row[j] + (inside[j] ? 3 * KB : 0));
+        if (tid < 32 * NP_FR) {
+            const int oy = tid / TW, ox = tid - oy * TW, hp = (oy + 1) * HW + ox + 1;   // the output pixel's own halo position
+            const bool store = oy0 + oy < p.H && ox0 + ox < p.W && !(REDUCE && p.sparse && ((oy | ox) & 1));   // (a tile starts at an even pixel)
+            at_s[tid] = make_uint2(store ? (uint32_t)((b * p.H + oy0 + oy) * p.W + ox0 + ox) : ~0u, (uint32_t)(64 * KB + hp * KB + (swz<4>(hp) << 4)));
+        }
         if (tid < 128) rq_store<RQ>(prm[cv], r12, c);
         if constexpr (TAIL)
             if (tid < p.Cout_p) {
@@ -117,20 +145,20 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
         if constexpr (REDUCE)
             if (tid < RN) rq_store<RQ>(prmr, rp, tid);
     }
+    if constexpr (NK == 4) wait_vmcnt<6>();   // steps 0 and 1 landed
+    else if (nk > 2) wait_vmcnt<3>();
+    else wait_vmcnt<0>();
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();       // prm visible (the operands need not have landed)
+    __builtin_amdgcn_s_barrier();       // they and the constants are visible
     asm volatile("" ::: "memory");
 
     const int c16 = wm * 32 + 16 * half;   // first of the lane's 16 channels in the first two convolutions
     const int f1 = wn * 3 - (wn == 3), n1 = wn < 2 ? 3 : 2;   // first fragment and their number: 3, 3, 2, 2
     v16i acc[3];
-    {
-        v16i init;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) init[i] = prm[0][0][c16 + i];
+    for (int f = 0; f < 3; ++f)
 #pragma unroll
-        for (int f = 0; f < 3; ++f) acc[f] = init;
-    }
+        for (int i = 0; i < 16; ++i) acc[f][i] = prm[0][0][c16 + i];
     // TAIL: the residual of the closing add is x itself.  Wave w will own output channels [32 w, 32 w + 32) there,
     // input channels of K step w / 2 of this GEMM: while that step's pixel rows sit in the LDS stage the wave copies
     // its residual values (its 32 channels of the seven fragments' pixels) into registers, so x is not read from memory
@@ -151,19 +179,12 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
                 boffs[ksub][f] = 64 * KB + rb * KB + ((c ^ swz<4>(rb)) << 4);
             }
         }
-        for (int ks = 0; ks < nk; ++ks) {
-            if (ks == 0 && nk > 1) wait_vmcnt<3>();   // step 0 landed; the 3 loads of step 1 may still be in flight
-            else wait_vmcnt<0>();
-            __builtin_amdgcn_s_barrier();   // every wave's loads of step ks landed; every wave is done with step ks - 1
-            if (ks >= 1 && ks + 1 < nk) issue(ks + 1, (ks + 1) & 1);
-            const int8_t *base = &Ls[(ks & 1) * STAGE];
+        auto compute = [&](int ks, int buf) {
+            const int8_t *base = buf == 2 ? T : Ls + buf * STAGE;
             if constexpr (IDENTITY) {
                 if (ks == wave >> 1) {   // wave-uniform
 #pragma unroll
-                    for (int f = 0; f < NP_FR; ++f) {
-                        const int o = f * 32 + l, oy = o / TW, ox = o - oy * TW, hp = (oy + 1) * HW + ox + 1;   // the output pixel's own halo position
-                        resid[f] = *(const v4i *)(base + 64 * KB + hp * KB + (((wm * 2 + half) ^ swz<4>(hp)) << 4));
-                    }
+                    for (int f = 0; f < NP_FR; ++f) resid[f] = *(const v4i *)(base + (at_s[f * 32 + l].y ^ (uint32_t)((wm * 2 + half) << 4)));
                 }
             }
 #pragma unroll
@@ -176,6 +197,33 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
                 for (int f = 0; f < 3; ++f)
                     if (f < 2 || n1 == 3) acc[f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa, fb[f], acc[f], 0, 0, 0);
             }
+        };
+        auto lds_barrier = [&]() {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        };
+        if constexpr (NK == 4) {
+            compute(0, 0);
+            compute(1, 1);
+            wait_vmcnt<3>();
+            lds_barrier();   // step 2 landed; every wave is done with step 0
+#pragma unroll
+            for (int j = 0; j < 3; ++j) *(v4i *)(Ls + (j == 2 && short_wave ? 1 : j) * 8192 + tid * 16) = late[j];
+            compute(2, 2);
+            lds_barrier();
+            compute(3, 0);
+        } else {
+            for (int ks = 0, buf = 0; ks < nk; ++ks) {   // buffer: ks mod 3
+                if (ks > 0) {
+                    if (ks + 1 < nk) wait_vmcnt<3>();
+                    else wait_vmcnt<0>();
+                    lds_barrier();   // every wave's loads of step ks landed; every wave is done with step ks - 1
+                    if (ks + 2 < nk) issue(ks + 2, buf == 0 ? 2 : buf - 1);
+                }
+                compute(ks, buf);
+                buf = buf == 2 ? 0 : buf + 1;
+            }
         }
     }
     __syncthreads();   // every wave is done with the operand stages
@@ -187,7 +235,7 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
         for (int pass = 0; pass < (TOTAL + 511) / 512; ++pass) {
             if (pass * 512 + wave * 64 < TOTAL) {        // wave-uniform
                 const int q = pass * 512 + tid, r = q / W2_CHUNKS, c = q % W2_CHUNKS;
-                ISR_GLOBAL_TO_LDS16(p.w2 + (long)r * 576 + (c < 36 ? c : 0) * 16, &Ls[(pass * 512 + wave * 64) * 16]);
+                ISR_GLOBAL_TO_LDS16_AT(p.w2 + (long)r * 576 + (c < 36 ? c : 0) * 16, lds0 + (pass * 512 + wave * 64) * 16);
             }
         }
     }
@@ -208,21 +256,32 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
             for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(acc[f][i], mm[i], ch[i], ss[i], p.lo1);
             v4i v = rq_pack16<RQ>(q);
             if (!ok) v = v4i{(int)zt, (int)zt, (int)zt, (int)zt};
-            *(v4i *)(&T[h * 64 + (((wm * 2 + half) ^ swz<4>(h)) << 4)]) = v;
+            if (h < NHALO) *(v4i *)(T + h * TP + (wm * 2 + half) * 16) = v;
         }
     }
     wait_vmcnt<0>();
     __syncthreads();   // t1 tile and 3x3 weights in LDS
 
+    // the lane's weights of the 1x1 convolutions to come: on their way while the 3x3 runs
+    auto rows64 = [&](const int8_t *w, v4i (&fa)[2]) {
+#pragma unroll
+        for (int ksub = 0; ksub < 2; ++ksub) fa[ksub] = *(const v4i *)(w + (wave * 32 + l) * 64 + ksub * 32 + half * 16);
+    };
+    v4i f3[2], fp[2], fr[4];
+    if (TAIL && wave * 32 < p.Cout_p) {
+        rows64(p.w3, f3);
+        if constexpr (PROJ) rows64(p.wp, fp);
+    }
+
     // ---- step 3: 3x3 convolution from LDS: this wave's 32 channels x its 2 (wn < 3) or 1 fragments ----
     const int nfr = wn < 3 ? 2 : 1;   // wave-uniform
-    int hb[2];                            // halo pixel of tap (0, 0) of the lane's output pixel in fragment f
+    const int8_t *tb[2];                  // the lane's chunk of halo pixel (0, 0) of the taps of its output pixel in fragment f
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
-        const int o = (wn * 2 + f) * 32 + l;
-        const int oo = o < TH * TW ? o : 0, oy = oo / TW, ox = oo - oy * TW;
-        hb[f] = oy * HW + ox;
+        const int o = (wn * 2 + f) * 32 + l, oo = o < TH * TW ? o : 0, oy = oo / TW, ox = oo - oy * TW;
+        tb[f] = T + (oy * HW + ox) * TP + half * 16;
     }
+    const int8_t *wb = Ls + ((wm * 32 + l) * W2_CHUNKS + half) * 16;
     {
         v16i init;
 #pragma unroll
@@ -232,14 +291,11 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
     }
 #pragma unroll
     for (int ks = 0; ks < 18; ++ks) {
-        const int tap = ks >> 1, ky = tap / 3, kx = tap % 3, cc = (ks & 1) * 2 + half;
-        const v4i fa = *(const v4i *)(&Ls[((wm * 32 + l) * W2_CHUNKS + 2 * ks + half) * 16]);
+        const int tap = ks >> 1, ky = tap / 3, kx = tap % 3;
+        const v4i fa = *(const v4i *)(wb + ks * 32);
         v4i fb[2];
 #pragma unroll
-        for (int f = 0; f < 2; ++f) {
-            const int hp = hb[f] + ky * HW + kx;
-            fb[f] = *(const v4i *)(&T[hp * 64 + ((cc ^ swz<4>(hp)) << 4)]);
-        }
+        for (int f = 0; f < 2; ++f) fb[f] = *(const v4i *)(tb[f] + (ky * HW + kx) * TP + (ks & 1) * 32);
 #pragma unroll
         for (int f = 0; f < 2; ++f)
             if (f < 1 || nfr == 2) acc[f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa, fb[f], acc[f], 0, 0, 0);
@@ -274,9 +330,13 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
         for (int f = 0; f < 2; ++f) {
             if (f == 1 && nfr != 2) continue;
             const int o = (wn * 2 + f) * 32 + l;
-            *(v4i *)(&T[o * 64 + (((wm * 2 + half) ^ swz<4>(o)) << 4)]) = t2[f];
+            *(v4i *)(T + o * TP + (wm * 2 + half) * 16) = t2[f];
         }
         __syncthreads();   // the t2 tile is complete
+
+        if constexpr (REDUCE)
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) fr[ks] = *(const v4i *)(p.wp + ((wave * 4 + ks) * 64 + lane) * 16);
 
         // ---- last 1x1 convolution + residual add: this wave's 32 output channels, all seven pixel fragments ----
         // Registers are short: one fragment at a time, its accumulators start from the bias in LDS, and the forms of the
@@ -284,19 +344,10 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
         if (wave * 32 >= p.Cout_p) return;   // no barrier follows
         const AddConst ac = add_const<RQA>(p);
         const int m0 = wave * 32, c0 = m0 + 16 * half;   // the lane's 16 channels
-        // index (image, row, column) of the lane's pixel of fragment f; -1: outside the image
-        auto pixel = [&](int f) {
-            int o = f * 32 + l;
-            asm volatile("" : "+v"(o));   // worked out where it is used, not kept
-            const int oy = o / TW, ox = o - oy * TW;
-            return oy0 + oy < p.H && ox0 + ox < p.W ? (b * p.H + oy0 + oy) * p.W + ox0 + ox : -1;
-        };
+        auto pixel = [&](int f) { return at_s[f * 32 + l].x; };
         // the fragments of one 1x1 convolution from 64 channels: operand(f, K half), then use(f, requantised values)
-        auto conv64 = [&](const int8_t *w, const auto &prm, int lo, auto first, auto end, auto operand, auto use) {
+        auto conv64 = [&](const v4i (&fa)[2], const auto &prm, int lo, auto first, auto end, auto operand, auto use) {
             asm volatile("" ::: "memory");
-            v4i fa[2];
-#pragma unroll
-            for (int ksub = 0; ksub < 2; ++ksub) fa[ksub] = *(const v4i *)(w + (long)(m0 + l) * 64 + ksub * 32 + half * 16);
             int mm[16], ch[16], ss[16];
             auto constants = [&]() {
 #pragma unroll
@@ -324,12 +375,12 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
             // ahead (pixels outside the image read pixel 0: in bounds, unused)
             v4i xn[2], x[2];
             auto fetch = [&](int f) {
-                const int px = pixel(f);
+                const uint32_t px = pixel(f);
 #pragma unroll
-                for (int ksub = 0; ksub < 2; ++ksub) xn[ksub] = *(const v4i *)(p.in + (long)(px >= 0 ? px : 0) * 64 + ksub * 32 + half * 16);
+                for (int ksub = 0; ksub < 2; ++ksub) xn[ksub] = *(const v4i *)(p.in + (uint64_t)(px != ~0u ? px : 0) * 64 + ksub * 32 + half * 16);
             };
             fetch(0);
-            conv64(p.wp, prmp, p.lop, Frag<0>{}, Frag<NP_FR>{}, [&](int f, int ksub) {
+            conv64(fp, prmp, p.lop, Frag<0>{}, Frag<NP_FR>{}, [&](int f, int ksub) {
                 if (ksub == 0) {
                     x[0] = xn[0]; x[1] = xn[1];
                     if (f + 1 < NP_FR) fetch(f + 1);
@@ -341,8 +392,7 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
             });
         }
         auto t2_operand = [&](int f, int ksub) {
-            const int o = f * 32 + l;
-            return *(const v4i *)(&T[o * 64 + (((ksub * 2 + half) ^ swz<4>(o)) << 4)]);
+            return *(const v4i *)(T + (f * 32 + l) * TP + (ksub * 2 + half) * 16);
         };
         auto sum = [&](int f, const int (&qc)[16]) {
             int q[16];
@@ -351,10 +401,10 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
             return rq_pack16<RQA>(q);
         };
         if constexpr (!REDUCE) {
-            conv64(p.w3, prm3, p.lo3, Frag<0>{}, Frag<NP_FR>{}, t2_operand, [&](int f, const int (&qc)[16]) {
+            conv64(f3, prm3, p.lo3, Frag<0>{}, Frag<NP_FR>{}, t2_operand, [&](int f, const int (&qc)[16]) {
                 const v4i y = sum(f, qc);
-                const int px = pixel(f);
-                if (px >= 0) *(v4i *)(p.out + (long)px * p.Cout_p + c0) = y;
+                const uint32_t px = pixel(f);
+                if (px != ~0u) *(v4i *)(p.out + c0 + (uint64_t)px * (uint32_t)p.Cout_p) = y;
             });
         } else {
             // The sum goes to memory (only its even pixels where nothing but a stride-2 projection reads it) and, three, two
@@ -364,21 +414,16 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
             auto group = [&](auto first, auto end, int region) {
                 constexpr int F0 = decltype(first)::value, F1 = decltype(end)::value;
                 const int ln = lane & 15, g = lane >> 4, oc = wave * 16 + 4 * g;
-                v4i fr[4];
-                auto weights = [&]() {
-#pragma unroll
-                    for (int ks = 0; ks < 4; ++ks) fr[ks] = *(const v4i *)(p.wp + ((wave * 4 + ks) * 64 + lane) * 16);
-                };
-                if constexpr (F0 > 0) weights();   // (the first group's residual leaves no registers for them yet)
-                conv64(p.w3, prm3, p.lo3, first, end, t2_operand, [&](int f, const int (&qc)[16]) {
+                conv64(f3, prm3, p.lo3, first, end, t2_operand, [&](int f, const int (&qc)[16]) {
                     const v4i y = sum(f, qc);
-                    const int px = pixel(f), i = (f - F0) * 32 + l;
+                    const uint32_t px = pixel(f);
+                    const int i = (f - F0) * 32 + l;
+                    if (f == 0)   // no wait for a store behind them
+#pragma unroll
+                        for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(fr[ks]));
                     *(v4i *)(&Ls[region + i * 256 + (((2 * wave + half) ^ (i & 15)) << 4)]) = y;
-                    const int o = f * 32 + l, odd = (o / TW | o % TW) & 1;   // a tile starts at an even pixel
-                    const bool store = px >= 0 && !(p.sparse && odd);
-                    if (store) *(v4i *)(p.out + (long)px * 256 + c0) = y;
+                    if (px != ~0u) *(v4i *)(p.out + c0 + (uint64_t)px * 256) = y;
                 });
-                if constexpr (F0 == 0) weights();
                 int bias[4], mm[4], ch[4], ss[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) { bias[i] = prmr[0][oc + i]; mm[i] = prmr[1][oc + i]; ch[i] = prmr[2][oc + rq_chi_at<RQ>(i)]; ss[i] = prmr[3][oc + i]; }
@@ -403,7 +448,7 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
                         *(uint32_t *)(p.out2 + (at * RN + (uint32_t)oc)) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
                 }
             };
-            static_assert(5 * 32 * 256 <= 2 * STAGE && 3 + 2 + 2 == NP_FR, "regions");
+            static_assert(5 * 32 * 256 <= FRONT && 3 + 2 + 2 == NP_FR, "regions");
             group(Frag<0>{}, Frag<3>{}, 0);
             group(Frag<3>{}, Frag<5>{}, 3 * 32 * 256);
             group(Frag<5>{}, Frag<7>{}, 0);   // every wave is done with the first group: it has passed the second's barrier
@@ -442,6 +487,7 @@ hipError_t launch_bottleneck(const BneckParams &p, hipStream_t st) {
         constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
         if (mode == 3) hipLaunchKernelGGL((bottleneck_kernel<3, RQ, RQA>), grid, block, 0, st, p);
         else if (mode == 2) hipLaunchKernelGGL((bottleneck_kernel<2, RQ, RQA>), grid, block, 0, st, p);
+        else if (mode == 1 && p.Cin_p == 256) hipLaunchKernelGGL((bottleneck_kernel<4, RQ, RQA>), grid, block, 0, st, p);
         else if (mode == 1) hipLaunchKernelGGL((bottleneck_kernel<1, RQ, RQA>), grid, block, 0, st, p);
         else hipLaunchKernelGGL((bottleneck_kernel<0, RQ, RQA>), grid, block, 0, st, p);
     });

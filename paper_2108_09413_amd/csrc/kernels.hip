@@ -84,8 +84,7 @@ hipError_t launch_noise(const NoiseParams &p, hipStream_t st) {
 // threshold's 16 lowest float bits, so subtracting the draw's own bits borrows one where x lies behind the threshold and
 // leaves zeros below where that is open; sign and packing go by halves of a register.  81 instructions per four draws instead of
 // 113 with noise_draw4, which keeps to guides of half the size up to sigma 86: there is less to stage for workgroups that draw
-// few pixels a thread (a net's first kernel on 32 x 32 images got 1 % slower with the words used here, and a new sigma's first
-// call 10 us).
+// few pixels a thread (a net's first kernel on 32 x 32 images got 1 % slower with the words used here).
 // WHOLE: tensors of whole waves (d a multiple of 256).  A wave's draws then lie in one tensor, and what depends on the tensor
 // alone -- a quarter of the first two rounds of the generator, indices, addresses -- is scalar arithmetic.
 // 50 000 x 3072 draws, calls in a row: 130 -> 108 us at sigma 32; one call alone 149 -> 121 at sigma 256, 148 -> 129 at 1000.
