@@ -3,7 +3,7 @@
 //   identity blocks  t = conv3x3(x), x = add(conv3x3(t), x)         any number
 //   [down-sampling block into the next stage, or its first convolution alone]
 //   [global average pooling, fully connected layer, argmax, vote]
-// A workgroup of four waves keeps NI whole images in LDS from the first of these to the last: x and t as (S+2) x (S+2) x C
+// A workgroup of four waves (eight: see launch_narrow) keeps NI whole images in LDS from the first of these to the last: x and t as (S+2) x (S+2) x C
 // int8 tiles whose border holds the tensor's zero-point, so that taps need no bounds checks and contribute 0.  The sum of
 // a block replaces x in place (a lane reads the residual at its own pixel and writes there; the second convolution
 // reads only t).  Memory sees the noise table, the stage's result and the weights (L2-resident, a few KiB a convolution).
@@ -22,9 +22,12 @@
 // of 2.4 GHz.  So the three have to overlap: the arithmetic of a fragment stands between the MFMAs of the next.  Four
 // workgroups share a CU at 16 channels, two at 32 and 64, where the operands in flight take the registers of a third (two
 // with pairs of fragments measured 1.81 / 1.40 / 1.11 ms for the stages of a 110-layer net on 16 700 images, three without
-// 1.88 / 1.45 / 1.23 ms).  More images per workgroup amortise the weight and constant loads of a convolution at 32 and 64
+// 1.88 / 1.45 / 1.23 ms).  With one workgroup on a CU there is nothing to overlap with: descriptors, weights and constants of
+// a convolution are fetched while the one before runs, and 16 channels take eight waves (predictions with 100 copies: ResNet-20
+// 52.3 -> 50.0 us, ResNet-110 171 -> 153, the two-convolution net 24.5 -> 23.8).  More images per workgroup amortise the weight and constant loads of a convolution at 32 and 64
 // channels, where a wave has one or two fragments per image.  The certification of the 110-layer net at 100 000 samples took
 // 43.3 ms with one launch per block, 31.6 with one per stage, 27.0 with the overlap.
+#include <cstddef>
 #include <string>
 
 #include "conv_device.h"
@@ -62,11 +65,11 @@ __device__ __forceinline__ void border_pixel(int b, int &y, int &x) {
     else if (b < 3 * P - 2) { y = b - 2 * P + 1; x = 0; }
     else { y = b - (3 * P - 2) + 1; x = P - 1; }
 }
-template <int C, int S, int NI>
+template <int C, int S, int NI, int NT>
 __device__ __forceinline__ void fill_ring(int8_t *tile, int zp, int tid) {
     constexpr int CH = C / 16, N = (4 * (S + 2) - 4) * CH;
     const int z = (int)((uint32_t)(zp & 0xFF) * 0x01010101u);
-    for (int i = tid; i < NI * N; i += 256) {
+    for (int i = tid; i < NI * N; i += NT) {
         const int im = i / N, j = i % N;
         int y, x;
         border_pixel<S>(j / CH, y, x);
@@ -256,15 +259,15 @@ __device__ __forceinline__ void with_form(int form, F f) {
 }
 
 // Global average pooling of NI tiles, fully connected layer, argmax and votes.  `scratch` is LDS that nothing else uses.
-template <int C, int S, int NI>
+template <int C, int S, int NI, int NT>
 __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t *tile, int8_t *scratch, long img0, int tid) {
-    constexpr int WORDS = C / 4, ITEMS = NI * WORDS, PARTS = 256 / ITEMS, PPP = S * S / PARTS;   // pixels per part
-    static_assert(ITEMS <= 256 && S * S % PARTS == 0, "one part per thread");
+    constexpr int WORDS = C / 4, ITEMS = NI * WORDS, PARTS = NT / ITEMS, PPP = S * S / PARTS;   // pixels per part
+    static_assert(ITEMS <= NT && S * S % PARTS == 0, "one part per thread");
     int *sums = (int *)scratch;                       // [NI][C]
     int8_t *feat = scratch + NI * C * 4;              // [NI][C]
     int *best_of = (int *)(feat + NI * C);            // [NI]
     const int lane = tid & 63, wave = tid >> 6;
-    for (int i = tid; i < NI * C; i += 256) sums[i] = 0;
+    for (int i = tid; i < NI * C; i += NT) sums[i] = 0;
     lds_barrier();
     if (tid < ITEMS * PARTS) {
         const int item = tid % ITEMS, part = tid / ITEMS, im = item / WORDS, word = item % WORDS;
@@ -280,7 +283,7 @@ __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t 
         for (int e = 0; e < 4; ++e) atomicAdd(&sums[im * C + word * 4 + e], s[e]);
     }
     lds_barrier();
-    for (int i = tid; i < NI * C; i += 256) {
+    for (int i = tid; i < NI * C; i += NT) {
         // RHA of the scaled sum, as the pooling kernel
         const long v = (long)(sums[i] - S * S * p.gap_zp_in) * p.gap_M0;
         const int sh = 31 + p.gap_sh;
@@ -290,7 +293,7 @@ __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t 
         feat[i] = (int8_t)(r < -128 ? -128 : (r > 127 ? 127 : r));
     }
     lds_barrier();
-    for (int im = wave; im < NI; im += 4) {
+    for (int im = wave; im < NI; im += NT / 64) {
         const long g = img0 + im;
         int best = INT32_MIN, best_idx = 0x7FFFFFFF;
         for (int c = lane; c < p.classes; c += 64) {
@@ -331,11 +334,49 @@ __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t 
     }
 }
 
-template <int C, int S, int NI>
-__global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const NarrowParams p) {
+// A block's descriptor.  AHEAD: dword by dword in the lanes of a register, by a vector load two blocks ahead; else by scalar loads
+// where its fields are used, which other workgroups of the CU cover.
+template <bool AHEAD>
+struct Block {
+    int lanes;
+    const __attribute__((address_space(4))) NarrowBlock *at;
+    __device__ __forceinline__ Block(const NarrowParams &p, int blk, int lane) {
+        constexpr int N = sizeof(NarrowBlock) / 4;
+        const NarrowBlock *b = p.blocks + (blk < p.nblocks ? blk : p.nblocks ? p.nblocks - 1 : 0);
+        at = (const __attribute__((address_space(4))) NarrowBlock *)(uintptr_t)b;
+        lanes = 0;
+        if (AHEAD && p.nblocks) lanes = ((const int *)b)[lane < N ? lane : N - 1];
+    }
+    __device__ __forceinline__ int field(size_t offset) const { return __builtin_amdgcn_readlane(lanes, (int)(offset / 4)); }
+    template <class T>
+    __device__ __forceinline__ const T *pointer(size_t offset) const {
+        typedef const __attribute__((address_space(1))) T *global;
+        return (const T *)(global)(uintptr_t)((uint64_t)(uint32_t)field(offset) | (uint64_t)(uint32_t)field(offset + 4) << 32);
+    }
+#define ISR_FIELD(name) (AHEAD ? field(offsetof(NarrowBlock, name)) : at->name)
+    __device__ __forceinline__ const int8_t *w1() const { return AHEAD ? pointer<int8_t>(offsetof(NarrowBlock, w1)) : at->w1; }
+    __device__ __forceinline__ const int8_t *w2() const { return AHEAD ? pointer<int8_t>(offsetof(NarrowBlock, w2)) : at->w2; }
+    __device__ __forceinline__ const int *prm1() const { return AHEAD ? pointer<int>(offsetof(NarrowBlock, prm1)) : at->prm1; }
+    __device__ __forceinline__ const int *prm2() const { return AHEAD ? pointer<int>(offsetof(NarrowBlock, prm2)) : at->prm2; }
+    __device__ __forceinline__ int zp_x() const { return ISR_FIELD(zp_x); }
+    __device__ __forceinline__ int zp_t() const { return ISR_FIELD(zp_t); }
+    __device__ __forceinline__ int lo1() const { return ISR_FIELD(lo1); }
+    __device__ __forceinline__ int lo2() const { return ISR_FIELD(lo2); }
+    __device__ __forceinline__ int form() const { return ISR_FIELD(form); }
+    __device__ __forceinline__ AddConst add() const { return {ISR_FIELD(add.ms), ISR_FIELD(add.mr), ISR_FIELD(add.c0), ISR_FIELD(add.k), ISR_FIELD(add.sh), ISR_FIELD(add.lo)}; }
+#undef ISR_FIELD
+};
+
+template <int C, int S, int NI, int NW>
+__global__ __launch_bounds__(64 * NW, C == 16 ? 4 : 2) void narrow_kernel(const NarrowParams p) {
+    constexpr int NT = 64 * NW;                      // threads
     constexpr int P = S + 2, CH = C / 16, C2 = 2 * C, S2 = S / 2;
     constexpr int TB = tile_bytes<C, S>();
     constexpr bool TAIL = C < 64;                    // there is a next stage
+    constexpr int R = 64 / NW;                       // 16 channels: rows of a wave's strip of 16 columns
+    // One workgroup on a CU: nothing else runs while a convolution waits for its descriptor, its weights and its constants, which
+    // are therefore all fetched while the one before runs.
+    constexpr bool AHEAD = NI == 1 && (C > 16 || NW > 4);
     static_assert((C == 16 && S == 32 && NI == 1) || (C == 32 && S == 16) || (C == 64 && S == 8), "shape");
     __shared__ __attribute__((aligned(256))) int8_t X[NI * TB];
     __shared__ __attribute__((aligned(256))) int8_t T[NI * TB];
@@ -350,12 +391,12 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
     // ---- the stage's input ----
     // constants, the sampler's table and the first weights are all on their way before any of them is waited for
     constexpr bool WIDE = C > 16;
-    constexpr int NTP = TAIL ? (3 * 4 * C2 + 255) / 256 : 1;
+    constexpr int NTP = TAIL ? (3 * 4 * C2 + NT - 1) / NT : 1;
     static_assert(4 * C <= 256, "one constant a thread");
     const bool from_image = C == 16 && p.stem;
     int v0 = 0, v1 = 0, vt[NTP] = {};
     v4i fa0 = {0, 0, 0, 0};
-    NoiseStage vn;
+    NoiseStage<NT> vn;
     const uint8_t *xim = nullptr;
     const DeviceNoiseTable *table = nullptr;
     uint32_t image_id = 0;
@@ -365,26 +406,38 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
         fa0 = *(const v4i *)(p.w0 + (lane & 15) * 64 + (lane >> 4) * 16);
         if (p.fused_noise) {
             use = resolve_noise_source(p.noise, img0, xim, table, image_id);
-            vn = fetch_noise_table(table, tid);
+            vn = fetch_noise_table<NT>(table, tid);
         }
     }
     if (p.nblocks && tid < 4 * C) v0 = blocks[0].prm1[tid];
     if (TAIL && p.tail)
 #pragma unroll
         for (int j = 0; j < NTP; ++j)
-            if (tid + 256 * j < 3 * 4 * C2) vt[j] = p.tprm[tid + 256 * j];
-    v4i fa[WIDE ? WideConv<WIDE ? C : 32, WIDE ? S : 16>::KS : 1];   // weights of the convolution to come
-    if constexpr (WIDE)
-        if (p.nblocks) WideConv<C, S>(lane, wave).load_weights(blocks[0].w1, fa);
+            if (tid + NT * j < 3 * 4 * C2) vt[j] = p.tprm[tid + NT * j];
+    v4i fa[WIDE ? WideConv<WIDE ? C : 32, WIDE ? S : 16>::KS : 3];   // weights of the convolution to come
+    // 16 channels: a lane's weights, by kernel row; the fourth lane group's are the zeros behind the nine taps
+    auto narrow_weights = [&](const int8_t *w, v4i (&f)[3]) {
+        constexpr int KP = (9 * 16 + 63) / 64 * 64;
+        const int kg = lane >> 4;
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky) f[ky] = *(const v4i *)(w + (lane & 15) * KP + (kg < 3 ? ky * 3 + kg : 9 + ky) * 16);
+    };
+    int vp = 0;   // AHEAD: constants of the convolution after the next
+    Block<AHEAD> cur(p, 0, lane), nxt(p, 1, lane);
+    if (p.nblocks) {
+        if constexpr (WIDE) WideConv<C, S>(lane, wave).load_weights(blocks[0].w1, fa);
+        else if constexpr (AHEAD) narrow_weights(blocks[0].w1, fa);
+        if (AHEAD && tid < 4 * C) vp = blocks[0].prm2[tid];
+    }
     auto store_constants = [&]() {
         if (p.nblocks && tid < 4 * C) prm[0][tid] = v0;
         if (TAIL && p.tail)
 #pragma unroll
             for (int j = 0; j < NTP; ++j)
-                if (tid + 256 * j < 3 * 4 * C2) tprm[tid + 256 * j] = vt[j];
+                if (tid + NT * j < 3 * 4 * C2) tprm[tid + NT * j] = vt[j];
     };
-    if (p.nblocks) fill_ring<C, S, NI>(X, blocks[0].zp_x, tid);
-    else if (p.tail) fill_ring<C, S, NI>(X, p.tzp_x, tid);
+    if (p.nblocks) fill_ring<C, S, NI, NT>(X, blocks[0].zp_x, tid);
+    else if (p.tail) fill_ring<C, S, NI, NT>(X, p.tzp_x, tid);
     if (from_image) {
         if constexpr (C == 16) {
             // the noisy image as NHWC4 words, one pixel of padding left, three right; behind it the sampler's table
@@ -393,41 +446,53 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
             NoiseLds *tab = (NoiseLds *)(T + (S + 2) * PW * 4);
             static_assert((S + 2) * PW * 4 % 16 == 0 && (S + 2) * PW * 4 + sizeof(NoiseLds) <= sizeof(T), "image and table fit");
             const int zb = (int)((uint32_t)(p.zp_in & 0xFF) * 0x01010101u);
-            for (int i = tid; i < 2 * PW + 4 * S; i += 256) {
+            for (int i = tid; i < 2 * PW + 4 * S; i += NT) {
                 int y, x;
                 if (i < PW) { y = 0; x = i; }
                 else if (i < 2 * PW) { y = S + 1; x = i - PW; }
                 else { y = 1 + ((i - 2 * PW) >> 2); x = (i & 3) == 0 ? 0 : S + (i & 3); }
                 img[y * PW + x] = zb;
             }
-            const int y = tid / (S / 4), x4 = tid % (S / 4);   // one quad of pixels per thread
-            uint32_t v[4];
+            static_assert(S * S / 4 == 256, "one quad of pixels per thread of the first four waves");
+            const int y = (tid & 255) / (S / 4), x4 = tid % (S / 4);
+            int *dst = img + (y + 1) * PW + 1 + 4 * x4;
             if (p.fused_noise) {
-                store_noise_table(*tab, vn, tid);
+                store_noise_table<NT>(*tab, vn, tid);
                 const NoiseSampler smp = table->s;
                 lds_barrier();
-                noisy_quad(*tab, smp, table, xim, p.noise.C, S, S, y, x4, use.sample, image_id, use.phase, p.noise.key0, p.noise.key1, v);
-            } else {
+                if constexpr (NW == 4) {
+                    uint32_t v[4];
+                    noisy_quad(*tab, smp, table, xim, p.noise.C, S, S, y, x4, use.sample, image_id, use.phase, p.noise.key0, p.noise.key1, v);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) dst[j] = (int)v[j];
+                } else {   // a channel of a quad at a time (the fourth byte of a pixel meets zero weights)
+                    for (int c = tid >> 8; c < 3; c += NT / 256) {
+                        int v[4];
+                        noisy_values(*tab, smp, table, xim, c < p.noise.C, (uint32_t)((c * S + y) * S + x4 * 4), use.sample, image_id, use.phase, p.noise.key0,
+                                     p.noise.key1, v);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) ((int8_t *)(dst + j))[c] = (int8_t)v[j];
+                    }
+                }
+            } else if (tid < 256) {
                 const v4i w = *(const v4i *)(p.in + ((img0 * S + y) * S + 4 * x4) * 4);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] = (uint32_t)w[j];
+                for (int j = 0; j < 4; ++j) dst[j] = w[j];
             }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) img[(y + 1) * PW + 1 + 4 * x4 + j] = (int)v[j];
             if (tid < 64) prm[1][tid] = v1;
             store_constants();
             lds_barrier();
             // one v_mfma_i32_16x16x64_i8 per 16 pixels: lane group ky reads the 16 contiguous bytes of kernel row ky (4 pixels x
             // 4 stored channels, the fourth pixel and channel meeting zero weights), the fourth group zero weights
             const int l = lane & 15, kg = lane >> 4, kr = kg < 3 ? kg : 0;
-            const int x = 16 * (wave & 1) + l, row0 = 16 * (wave >> 1);
+            const int x = 16 * (wave & 1) + l, row0 = R * (wave >> 1);
             with_form<RQ_TOP>(p.form0, [&](auto rq, auto) {
                 constexpr int RQ = decltype(rq)::value;
                 const LaneConsts<4, RQ> k(prm[1], 16, 4 * kg);
                 const int *src = img + (row0 + kr) * PW + x;
                 int8_t *dst = X + ((row0 + 1) * P + x + 1) * 16 + 4 * kg;
 #pragma unroll 4
-                for (int r = 0; r < 16; ++r) {
+                for (int r = 0; r < R; ++r) {
                     const v4i fb = {src[r * PW], src[r * PW + 1], src[r * PW + 2], src[r * PW + 3]};
                     k.fragment();
                     const v4acc acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa0, fb, bias_vector<4, RQ>(k), 0, 0, 0);
@@ -437,7 +502,7 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
             });
         }
     } else {
-        for (int i = tid; i < NI * S * S * CH; i += 256) {
+        for (int i = tid; i < NI * S * S * CH; i += NT) {
             const int im = i / (S * S * CH), j = i % (S * S * CH), pix = j / CH, c = j % CH;
             long g = img0 + im;
             if (g >= p.B) g = p.B - 1;                   // images past the end repeat the last one; never stored
@@ -451,33 +516,40 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
     // ---- identity blocks ----
     int zp_t = 256;   // zero-point in the border of t; none yet
     for (int blk = 0; blk < p.nblocks; ++blk) {
-        const auto &d = blocks[blk];
         const bool last = blk + 1 == p.nblocks;
+        const Block<AHEAD> after(p, blk + 2, lane);
+        const int zp_x = cur.zp_x(), zp_mid = cur.zp_t(), lo1 = cur.lo1(), lo2 = cur.lo2();
         lds_barrier();            // x, its border and the first convolution's constants are in LDS; the previous block is done with t
-        for (int i = tid; i < 4 * C; i += 256) prm[1][i] = d.prm2[i];
-        if (d.zp_t != zp_t) { fill_ring<C, S, NI>(T, d.zp_t, tid); zp_t = d.zp_t; }
+        if (tid < 4 * C) {
+            prm[1][tid] = AHEAD ? vp : cur.prm2()[tid];
+            if (AHEAD) vp = nxt.prm1()[tid];
+        }
+        if (zp_mid != zp_t) { fill_ring<C, S, NI, NT>(T, zp_mid, tid); zp_t = zp_mid; }
         // what the next user of x wants in its border (this block reads x's border in its first convolution only)
-        const int zp_next = last ? (p.tail ? p.tzp_x : d.zp_x) : blocks[last ? blk : blk + 1].zp_x;
-        with_form<RQ_TOP>(d.form, [&](auto rq, auto rqa) {
+        const int zp_next = last ? (p.tail ? p.tzp_x : zp_x) : nxt.zp_x();
+        auto second_constants = [&]() {   // between the convolutions
+            lds_barrier();
+            if (tid < 4 * C && !last) {
+                prm[0][tid] = AHEAD ? vp : nxt.prm1()[tid];
+                if (AHEAD) vp = nxt.prm2()[tid];
+            }
+            if (zp_next != zp_x) fill_ring<C, S, NI, NT>(X, zp_next, tid);
+        };
+        with_form<RQ_TOP>(cur.form(), [&](auto rq, auto rqa) {
             constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
             if constexpr (C == 16) {
                 // 16 channels: a K step of v_mfma_i32_16x16x64_i8 is one kernel row -- lane group kg holds tap (ky = step, kx = kg),
-                // the fourth group zero weights -- and a wave walks down 16 rows of a 16-pixel column strip: the operands of
+                // the fourth group zero weights -- and a wave walks down R rows of a 16-pixel column strip: the operands of
                 // rows y + 1, y + 2 of one output row are those of rows y, y + 1 of the next, one new LDS read per output fragment
-                constexpr int KP = (9 * C + 63) / 64 * 64;
                 const int l = lane & 15, kg = lane >> 4, kx = kg < 3 ? kg : 0;
-                const int x = 16 * (wave & 1) + l, row0 = 16 * (wave >> 1);
+                const int x = 16 * (wave & 1) + l, row0 = R * (wave >> 1);
                 // The MFMAs of row r + 1 stand between the elements of row r's epilogue: element(r, e, value), then finish(r).
-                auto conv = [&](const int8_t *src, const int8_t *w, const int *pr, auto make) {
-                    v4i fa[3];
-#pragma unroll
-                    for (int ky = 0; ky < 3; ++ky) {
-                        fa[ky] = *(const v4i *)(w + l * KP + (ky * 3 + kx) * 16);
-                        if (kg == 3) fa[ky] = v4i{0, 0, 0, 0};
-                    }
+                auto conv = [&](const int8_t *src, const int8_t *w, const int *pr, auto make) {   // w: AHEAD the next convolution's
+                    v4i fn[3];
+                    narrow_weights(w, AHEAD ? fn : fa);
                     const LaneConsts<4, RQ> k(pr, 16, 4 * kg);
                     const int8_t *col = src + (row0 * P + x + kx) * C;   // padded (row0, x + kx) = tap (0, kx) of output (row0, x)
-                    auto operand = [&](int y) { return *(const v4i *)(col + (y < 18 ? y : 17) * P * C); };   // tile rows of the strip: 0 .. 17
+                    auto operand = [&](int y) { return *(const v4i *)(col + (y < R + 2 ? y : R + 1) * P * C); };   // tile rows of the strip: 0 .. R + 1
                     v4i b[6];   // rows r + 1 .. r + 5 of the ring, read four rows ahead
 #pragma unroll
                     for (int y = 0; y < 6; ++y) b[y] = operand(y);
@@ -486,40 +558,40 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
                     acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[2], b[2], acc, 0, 0, 0);
                     auto row = make(k);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
+                    for (int r = 0; r < R; ++r) {
                         b[r % 6] = operand(r + 6);
                         k.fragment();
                         v4acc next = acc;
-                        // (no row 16: the last step has no MFMAs)
-                        if (r < 15) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[0], b[(r + 1) % 6], bias_vector<4, RQ>(k), 0, 0, 0);
+                        // (no row R: the last step has no MFMAs)
+                        if (r < R - 1) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[0], b[(r + 1) % 6], bias_vector<4, RQ>(k), 0, 0, 0);
                         row(r, 0, acc[0]);
                         row(r, 1, acc[1]);
                         if (RQ == RQ_TOP) __builtin_amdgcn_sched_barrier(0);
-                        if (r < 15) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[1], b[(r + 2) % 6], next, 0, 0, 0);
+                        if (r < R - 1) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[1], b[(r + 2) % 6], next, 0, 0, 0);
                         row(r, 2, acc[2]);
                         if (RQ == RQ_TOP) __builtin_amdgcn_sched_barrier(0);
-                        if (r < 15) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[2], b[(r + 3) % 6], next, 0, 0, 0);
+                        if (r < R - 1) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[2], b[(r + 3) % 6], next, 0, 0, 0);
                         row(r, 3, acc[3]);
                         if (RQ == RQ_TOP) __builtin_amdgcn_sched_barrier(0);
                         acc = next;
                     }
+                    if (AHEAD)
+#pragma unroll
+                        for (int ky = 0; ky < 3; ++ky) fa[ky] = fn[ky];
                 };
                 const int at = ((row0 + 1) * P + x + 1) * 16 + 4 * kg;      // the lane's four channels of its pixel in row 0
-                conv(X, d.w1, prm[0], [&](const LaneConsts<4, RQ> &k) {
+                conv(X, AHEAD ? cur.w2() : cur.w1(), prm[0], [&](const LaneConsts<4, RQ> &k) {
                     return [&, q = v4acc{}](int r, int e, int a) mutable {
-                        q[e] = k.conv(a, e, d.lo1);
+                        q[e] = k.conv(a, e, lo1);
                         if (e == 3) *(uint32_t *)(T + at + r * P * 16) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
                     };
                 });
-                lds_barrier();
-                if (!last)
-                    for (int i = tid; i < 4 * C; i += 256) prm[0][i] = blocks[blk + 1].prm1[i];
-                if (zp_next != d.zp_x) fill_ring<C, S, NI>(X, zp_next, tid);
-                const AddConst ac = {d.add.ms, d.add.mr, d.add.c0, d.add.k, d.add.sh, d.add.lo};
-                conv(T, d.w2, prm[1], [&](const LaneConsts<4, RQ> &k) {
-                    auto residual = [&](int r) { return *(const uint32_t *)(X + at + (r < 16 ? r : 15) * P * 16); };
+                second_constants();
+                const AddConst ac = cur.add();
+                conv(T, AHEAD ? nxt.w1() : cur.w2(), prm[1], [&](const LaneConsts<4, RQ> &k) {
+                    auto residual = [&](int r) { return *(const uint32_t *)(X + at + (r < R ? r : R - 1) * P * 16); };
                     return [&, residual, q = v4acc{}, rw0 = residual(0), rw1 = residual(1), rw2 = residual(2)](int r, int e, int a) mutable {
-                        q[e] = rq_add<RQ, RQA>(k.conv(a, e, d.lo2), rw0, e, ac);
+                        q[e] = rq_add<RQ, RQA>(k.conv(a, e, lo2), rw0, e, ac);
                         if (e == 3) {
                             *(uint32_t *)(X + at + r * P * 16) = rq_pack<RQA>(q[0], q[1], q[2], q[3]);
                             rw0 = rw1; rw1 = rw2; rw2 = residual(r + 3);   // read three rows ahead
@@ -528,8 +600,8 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
                 });
             } else {
                 typedef WideConv<C, S> Wide;
-                constexpr int MF = Wide::MF, NF = Wide::NF, FRAGS = NI * NF * MF / 4;   // fragments per wave
-                auto offset = [&](int i) { const int f = wave / MF + i * (4 / MF); return (f / NF) * TB + (f % NF) * Wide::FRAG; };
+                constexpr int MF = Wide::MF, NF = Wide::NF, FRAGS = NI * NF * MF / NW;   // fragments per wave
+                auto offset = [&](int i) { const int f = wave / MF + i * (NW / MF); return (f / NF) * TB + (f % NF) * Wide::FRAG; };
                 // a lane's addresses are worked out anew for each convolution: kept across them they would be spilled
                 int ln = lane;
                 asm volatile("" : "+v"(ln));
@@ -538,34 +610,33 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
                     const LaneConsts<16, RQ> k(prm[0], C, wc.mf * 32 + wc.half * 16);
                     int q[4];
                     v4i o;
-                    wide_fragments<FRAGS, RQ, true>(wc, fa, k, d.w2, [&](int i) { return X + offset(i); }, [](int) {},
+                    wide_fragments<FRAGS, RQ, true>(wc, fa, k, cur.w2(), [&](int i) { return X + offset(i); }, [](int) {},
                         [&](int, int e, int a) {
-                            q[e & 3] = k.conv(a, e, d.lo1);
+                            q[e & 3] = k.conv(a, e, lo1);
                             if ((e & 3) == 3) o[e >> 2] = (int)rq_pack<RQ>(q[0], q[1], q[2], q[3]);
                         },
                         [&](int i) { *(v4i *)(T + offset(i) + wc.out) = o; });
                 }
                 asm volatile("" : "+v"(ln));
-                lds_barrier();
-                if (!last)
-                    for (int i = tid; i < 4 * C; i += 256) prm[0][i] = blocks[blk + 1].prm1[i];
-                if (zp_next != d.zp_x) fill_ring<C, S, NI>(X, zp_next, tid);
-                const AddConst ac = {d.add.ms, d.add.mr, d.add.c0, d.add.k, d.add.sh, d.add.lo};
+                second_constants();
+                const AddConst ac = cur.add();
                 const Wide wc(ln, wave);
                 const LaneConsts<16, RQ> k(prm[1], C, wc.mf * 32 + wc.half * 16);
                 // a lane writes where it, or the lane with the other half of its pixel in this wave, has read
                 const int dst = last && p.tail ? wc.out_strided : wc.out;
                 int q[4];
                 v4i o, rv[2];   // residuals of the two fragments of a group
-                wide_fragments<FRAGS, RQ, RQA == RQ_TOP>(wc, fa, k, last ? d.w2 : blocks[blk + 1].w1, [&](int i) { return T + offset(i); },
+                wide_fragments<FRAGS, RQ, RQA == RQ_TOP>(wc, fa, k, nxt.w1(), [&](int i) { return T + offset(i); },
                     [&](int i) { rv[i & 1] = *(const v4i *)(X + offset(i) + wc.out); },
                     [&](int i, int e, int a) {
-                        q[e & 3] = rq_add<RQ, RQA>(k.conv(a, e, d.lo2), (uint32_t)rv[i & 1][e >> 2], e & 3, ac);
+                        q[e & 3] = rq_add<RQ, RQA>(k.conv(a, e, lo2), (uint32_t)rv[i & 1][e >> 2], e & 3, ac);
                         if ((e & 3) == 3) o[e >> 2] = (int)rq_pack<RQA>(q[0], q[1], q[2], q[3]);
                     },
                     [&](int i) { *(v4i *)(X + offset(i) + dst) = o; });
             }
         });
+        cur = nxt;
+        nxt = after;
     }
 
     // ---- down-sampling into the next stage ----
@@ -574,10 +645,10 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
             constexpr int TB2 = tile_bytes<C2, S2>(), KP1 = (9 * C + 63) / 64 * 64, KS1 = (9 * C + 31) / 32;
             static_assert(NI * TB2 <= NI * TB, "the next stage's tile fits the middle tensor's");
             typedef WideConv<C2, S2> Wide;
-            constexpr int MF = Wide::MF, NF = Wide::NF, FRAGS = NI * NF * MF / 4;
+            constexpr int MF = Wide::MF, NF = Wide::NF, FRAGS = (NI * NF * MF + NW - 1) / NW;   // fragments per wave (of fewer fragments than waves: one of the first waves)
             constexpr int FRAG1 = 2 * (32 / S2) * P * C;   // input bytes from one output fragment to the next (an even number of rows)
             lds_barrier();            // x is complete, the last block is done with t
-            fill_ring<C2, S2, NI>(T, p.tzp_t, tid);
+            fill_ring<C2, S2, NI, NT>(T, p.tzp_t, tid);
             with_form<RQ_TOP_WIDE>(p.tform, [&](auto rq, auto rqa) {
                 constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
                 int ln = lane;
@@ -602,7 +673,8 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
                     const bool store = p.tail == 2 && !p.head;
 #pragma unroll 1
                     for (int i = 0; i < FRAGS; ++i) {
-                        const int f = wave / MF + i * (4 / MF), im = f / NF;
+                        const int f = wave / MF + i * (NW / MF), im = f / NF;
+                        if (NI * NF * MF < NW && f >= NI * NF) break;
                         const int8_t *src = X + im * TB + (f % NF) * FRAG1;
                         k.fragment();
                         v16i a = bias_vector<16, RQ>(k);
@@ -630,7 +702,8 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
                     lds_barrier();
 #pragma unroll 1
                     for (int i = 0; i < FRAGS; ++i) {
-                        const int f = wave / MF + i * (4 / MF), im = f / NF;
+                        const int f = wave / MF + i * (NW / MF), im = f / NF;
+                        if (NI * NF * MF < NW && f >= NI * NF) break;
                         asm volatile("" ::: "memory");   // one convolution's constants at a time
                         int r[16], q[16];
                         {
@@ -656,28 +729,28 @@ __global__ __launch_bounds__(256, C == 16 ? 4 : 2) void narrow_kernel(const Narr
             });
             if (p.head) {   // tail == 2: the pooling reads the convolution just computed
                 lds_barrier();
-                if constexpr (C == 16) narrow_head<C2, S2, NI>(p, T, X, img0, tid);
+                if constexpr (C == 16) narrow_head<C2, S2, NI, NT>(p, T, X, img0, tid);
             }
             return;
         }
     }
     lds_barrier();
     if (!p.head) {   // the stage's result
-        for (int i = tid; i < NI * S * S * CH; i += 256) {
+        for (int i = tid; i < NI * S * S * CH; i += NT) {
             const int im = i / (S * S * CH), j = i % (S * S * CH), pix = j / CH, c = j % CH;
             const long g = img0 + im;
             if (g < p.B) *(v4i *)(p.out + (g * S * S + pix) * C + c * 16) = *(const v4i *)(X + im * TB + tile_at<C, S>(pix / S + 1, pix % S + 1, c));
         }
     } else {
-        if constexpr (C == 64) narrow_head<C, S, NI>(p, X, T, img0, tid);
+        if constexpr (C == 64) narrow_head<C, S, NI, NT>(p, X, T, img0, tid);
     }
 }
 
-template <int C, int S, int NI>
+template <int C, int S, int NI, int NW>
 hipError_t launch_stage(const NarrowParams &p, hipStream_t st) {
-    static const std::string name = "narrow_kernel<" + std::to_string(C) + ", " + std::to_string(S) + ", " + std::to_string(NI) + ">";
+    static const std::string name = "narrow_kernel<" + std::to_string(C) + ", " + std::to_string(S) + ", " + std::to_string(NI) + (NW == 4 ? "" : ", " + std::to_string(NW) + " waves") + ">";
     set_kernel_name(name.c_str());
-    hipLaunchKernelGGL((narrow_kernel<C, S, NI>), dim3((unsigned)((p.B + NI - 1) / NI)), dim3(256), 0, st, p);
+    hipLaunchKernelGGL((narrow_kernel<C, S, NI, NW>), dim3((unsigned)((p.B + NI - 1) / NI)), dim3(64 * NW), 0, st, p);
     return hipGetLastError();
 }
 
@@ -712,9 +785,12 @@ hipError_t launch_narrow(const NarrowParams &p, int channels, hipStream_t st) {
     //   32 channels   13 / 18 / 21     17 / 18 / 21     18 / 18 / 21     22 / 24 / 22     27 / 24 / 29     36 / 35 / 31
     //   64 channels   15 / 15 / 24     19 / 16 / 24     20 / 17 / 24     27 / 20 / 25     32 / 21 / 25     45 / 29 / 27
     const bool one = p.B <= 256, two = p.B <= 1024;
-    if (channels == 16) return launch_stage<16, 32, 1>(p, st);
-    if (channels == 32) return one ? launch_stage<32, 16, 1>(p, st) : two ? launch_stage<32, 16, 2>(p, st) : launch_stage<32, 16, 3>(p, st);
-    if (channels == 64) return one ? launch_stage<64, 8, 1>(p, st) : two ? launch_stage<64, 8, 2>(p, st) : launch_stage<64, 8, 6>(p, st);
+    // Waves: eight for 16 channels while every image has a CU for itself, where a convolution is a chain of latencies (first kernel of
+    // ResNet-20 / -110 at 100 copies 2.1 / 11 us shorter; from two workgroups a CU on the same or longer: 300 copies + 0.2,
+    // 1000 + 2).  At 32 channels four waves stay ahead at all sizes: each fetches the whole weight matrix (3 us more for 9 blocks).
+    if (channels == 16) return one ? launch_stage<16, 32, 1, 8>(p, st) : launch_stage<16, 32, 1, 4>(p, st);
+    if (channels == 32) return one ? launch_stage<32, 16, 1, 4>(p, st) : two ? launch_stage<32, 16, 2, 4>(p, st) : launch_stage<32, 16, 3, 4>(p, st);
+    if (channels == 64) return one ? launch_stage<64, 8, 1, 4>(p, st) : two ? launch_stage<64, 8, 2, 4>(p, st) : launch_stage<64, 8, 6, 4>(p, st);
     return hipErrorInvalidValue;
 }
 

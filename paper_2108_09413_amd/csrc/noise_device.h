@@ -85,19 +85,48 @@ struct NoiseLds {
     uint32_t guide[NOISE_GUIDE_MAX];
 };
 
-// A workgroup of 256 threads stages a table into LDS: the loads, and later the stores (followed by a barrier at the caller).
+// A workgroup of NT threads stages a table into LDS: the loads, and later the stores (followed by a barrier at the caller).
+template <int NT>
 struct NoiseStage {
-    uint4 v[2];
+    static constexpr int N = NOISE_GUIDE_MAX / 4, LOADS = (N + NT - 1) / NT;
+    uint4 v[LOADS];
 };
-__device__ __forceinline__ NoiseStage fetch_noise_table(const DeviceNoiseTable *tab, int tid) {
-    constexpr int N = NOISE_GUIDE_MAX / 4;
-    static_assert(N > 256 && N <= 512, "two loads a thread");
+template <int NT = 256>
+__device__ __forceinline__ NoiseStage<NT> fetch_noise_table(const DeviceNoiseTable *tab, int tid) {
+    typedef NoiseStage<NT> Stage;
     const uint4 *src = (const uint4 *)tab->guide;
-    return {{src[tid], src[tid + 256 < N ? tid + 256 : tid]}};
+    Stage s;
+#pragma unroll
+    for (int j = 0; j < Stage::LOADS; ++j) s.v[j] = src[tid + j * NT < Stage::N ? tid + j * NT : 0];
+    return s;
 }
-__device__ __forceinline__ void store_noise_table(NoiseLds &t, const NoiseStage &s, int tid) {
-    ((uint4 *)t.guide)[tid] = s.v[0];
-    if (tid + 256 < (int)NOISE_GUIDE_MAX / 4) ((uint4 *)t.guide)[tid + 256] = s.v[1];
+template <int NT = 256>
+__device__ __forceinline__ void store_noise_table(NoiseLds &t, const NoiseStage<NT> &s, int tid) {
+    typedef NoiseStage<NT> Stage;
+#pragma unroll
+    for (int j = 0; j < Stage::LOADS; ++j)
+        if (tid + j * NT < Stage::N) ((uint4 *)t.guide)[tid + j * NT] = s.v[j];
+}
+
+// Channel values of four horizontally adjacent noisy pixels, not yet saturated: x + delta of logical elements pix .. pix + 3; 128
+// where the image lacks the channel, so that it holds 0 after the recentring.
+__device__ __forceinline__ void noisy_sums(const NoiseLds &t, const NoiseSampler &s, const DeviceNoiseTable *tab, const uint8_t *xim, bool there,
+                                           uint32_t pix, uint32_t sample, uint32_t image_id, uint32_t phase, uint32_t key0, uint32_t key1, int (&v)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = 128;
+    if (there) {
+        const uint32_t px4 = *(const uint32_t *)(xim + pix);   // pix is a multiple of 4
+        noise_draw4(t.guide, s, tab->hi, tab->lo, pix >> 2, sample, image_id, phase * 2u, key0, key1, v);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] += (int)((px4 >> (8 * j)) & 0xFF);
+    }
+}
+// the same as int8 codes: clamp(x + delta, 0, 255) - 128
+__device__ __forceinline__ void noisy_values(const NoiseLds &t, const NoiseSampler &s, const DeviceNoiseTable *tab, const uint8_t *xim, bool there,
+                                             uint32_t pix, uint32_t sample, uint32_t image_id, uint32_t phase, uint32_t key0, uint32_t key1, int (&v)[4]) {
+    noisy_sums(t, s, tab, xim, there, pix, sample, image_id, phase, key0, key1, v);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = min(max(v[j], 0), 255) - 128;
 }
 
 // Four horizontally adjacent noisy pixels (x4 * 4 .. x4 * 4 + 3 of row y) of one copy as NHWC4 words:
@@ -107,17 +136,8 @@ __device__ __forceinline__ void noisy_quad(const NoiseLds &t, const NoiseSampler
                                            uint32_t key1, uint32_t packed[4]) {
     int v[3][4];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[c][j] = 128;   // channels the image has not hold 0 after the recentring
-        if (c < C) {
-            const uint32_t pix = (uint32_t)((c * H + y) * W + x4 * 4);   // multiple of 4
-            const uint32_t px4 = *(const uint32_t *)(xim + pix);
-            noise_draw4(t.guide, s, tab->hi, tab->lo, pix >> 2, sample, image_id, phase * 2u, key0, key1, v[c]);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[c][j] += (int)((px4 >> (8 * j)) & 0xFF);
-        }
-    }
+    for (int c = 0; c < 3; ++c)
+        noisy_sums(t, s, tab, xim, c < C, (uint32_t)((c * H + y) * W + x4 * 4), sample, image_id, phase, key0, key1, v[c]);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {   // saturation of two 16-bit values to bytes at once
         uint32_t lo = __builtin_amdgcn_perm((uint32_t)v[1][j], (uint32_t)v[0][j], 0x05040100u), hi = (uint32_t)v[2][j];

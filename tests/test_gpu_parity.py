@@ -384,6 +384,31 @@ def test_stages_of_the_nets_on_32x32_images(isr, net, copies):
     m.close()
 
 
+@pytest.mark.parametrize("channels", [1, 2, 3])
+def test_noise_of_few_copies_is_drawn_by_channel(isr, channels):
+    """Eight waves an image draw a channel of a quad of pixels at a time: images of one to three channels, few copies (eight
+    waves) and many (four), blocks whose descriptors are fetched ahead in every stage."""
+    _say(f"narrow stages of {channels}-channel images")
+    b = NetBuilder(rng=np.random.default_rng(92), in_shape=(channels, 32, 32), num_classes=7)
+    t = b.conv(b.tensor(channels, 32, 32, 0, 74.0), 16, 3, 1, 1, True)
+    for ch in (16, 32, 64):
+        if ch > 16:
+            u = b.conv(b.conv(t, ch, 3, 2, 1, True), ch, 3, 1, 1, False)
+            t = b.add(b.conv(t, ch, 1, 2, 0, False), u, True)
+        for zo in (-128, -70, -128):
+            t = b.add(t, b.conv(b.conv(t, ch, 3, 1, 1, True), ch, 3, 1, 1, False), True, zp_out=zo)
+    b.fc(b.gap(t), 7)
+    blob = b.blob()
+    om = oracle.Model(blob)
+    x = np.random.default_rng(13).integers(0, 256, size=(channels, 32, 32)).astype(np.uint8)
+    olg, oam, _ = om.mc(x, 64, 2, 1, 1, 100, 4)
+    m = _load(isr, blob, 300)
+    for copies in (4, 300):
+        lg, am, _ = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 100, copies)
+        assert np.array_equal(lg[:4], olg) and np.array_equal(am[:4], oam), copies
+    m.close()
+
+
 @pytest.mark.parametrize("first", ["16 channels", "7x7 and pooling", "noise launch"])
 def test_both_phases_of_a_certification_in_one_list(isr, first):
     """Chunks and launches that end inside either phase and inside a pair: tallies against those of the phases alone, for first
@@ -455,6 +480,26 @@ def test_bottleneck_blocks_in_one_kernel(isr, shape):
     om = oracle.Model(blob)
     lg, am, cnt = isr.isr_debug_forward(m, x, 64, 3, 1, 1, 50, 5)
     olg, oam, ocnt = om.mc(x, 64, 3, 1, 1, 50, 5)
+    assert np.array_equal(lg, olg) and np.array_equal(cnt, ocnt)
+    m.close()
+
+
+@pytest.mark.parametrize("cin", [192, 256, 320, 512])
+def test_bottleneck_heads_of_three_to_eight_k_steps(isr, cin):
+    """The opening 1x1 and the 3x3 convolution (64 middle channels) in one kernel for wider inputs than a block's own: more K
+    steps than operand stages, against the oracle."""
+    _say(f"bottleneck head {cin} input channels")
+    b = NetBuilder(rng=np.random.default_rng(83), in_shape=(3, 10, 32), num_classes=5)
+    t = b.conv(b.tensor(3, 10, 32, 0, 74.0), cin, 3, 1, 1, True)
+    u = b.conv(b.conv(t, 64, 1, 1, 0, True, zp_out=-90), 64, 3, 1, 1, True, zp_out=7)
+    u = b.conv(u, 256, 1, 1, 0, False)
+    b.fc(b.gap(b.add(b.conv(t, 256, 1, 1, 0, False), u, True)), 5)
+    blob = b.blob()
+    x = np.random.default_rng(12).integers(0, 256, size=(3, 10, 32)).astype(np.uint8)
+    _check_all_tensors(isr, blob, x, 64, sample=2, chunk=3)
+    m = _load(isr, blob, 5)
+    lg, _, cnt = isr.isr_debug_forward(m, x, 64, 3, 1, 1, 50, 5)
+    olg, _, ocnt = oracle.Model(blob).mc(x, 64, 3, 1, 1, 50, 5)
     assert np.array_equal(lg, olg) and np.array_equal(cnt, ocnt)
     m.close()
 
