@@ -30,6 +30,8 @@ struct FloatOp {
     int a = -1, b = -1, out = -1;
     FConvParams conv{};            // CONV and FC (an FC layer is a convolution over the whole input)
     int res = -1;                  // tensor read by the residual add folded into the convolution, or -1
+    int pair = -1;                 // the op before, whose result is that tensor, runs in this op's kernel: its input tensor
+    int paired = 0;                // this op runs in the next one's kernel (alone only where its own result is asked for)
     float ma = 0.f, mb = 0.f;      // ADD
     int relu = 0;
     FPoolParams pool{};
@@ -188,9 +190,24 @@ int build_float_net(isr_model *m) {
             c.scale = (const float *)(net->dconst + (size_t)c.scale);
             c.ktab = (const int32_t *)(net->dconst + (size_t)c.ktab);
         }
+    // the residual of a folded add that the convolution before computes for it alone: both in one kernel
+    for (size_t i = 1; i < net->ops.size(); ++i) {
+        FloatOp &f = net->ops[i], &q = net->ops[i - 1];
+        if (f.type != OP_CONV || q.type != OP_CONV || f.res < 0 || f.res != q.out || q.res >= 0 || uses[q.out] != 1 || f.a == q.out ||
+            !fconv_pair_supported(f.conv, q.conv))
+            continue;
+        f.pair = q.a;
+        q.paired = 1;
+        f.flops += q.flops;
+        f.bytes += q.bytes - 8.0 * f.conv.Ho * f.conv.Wo * pm.tensors[f.out].C;   // the residual is neither written nor read
+        FConvParams &c = f.conv;
+        c.w2 = q.conv.w; c.bias2 = q.conv.bias; c.scale2 = q.conv.scale;
+        c.H2 = q.conv.H; c.W2 = q.conv.W; c.Cin2_p = q.conv.Cin_p; c.stride2 = q.conv.stride; c.relu2 = q.conv.relu;
+    }
     for (const FloatOp &f : net->ops) {   // what the planner looks at: op type and tensor ids
+        if (f.paired) continue;
         DevOp d{};
-        d.type = f.type; d.a = f.a; d.b = f.res >= 0 ? f.res : f.b; d.out = f.out;
+        d.type = f.type; d.a = f.a; d.b = f.pair >= 0 ? f.pair : f.res >= 0 ? f.res : f.b; d.out = f.out;
         net->plan.ops.push_back(d);
     }
     return net->status = ISR_OK;
@@ -201,6 +218,9 @@ int plan_float_net(isr_model *m, uint32_t chunk_samples) {
     FloatNet &net = *m->fnet;
     if (net.planned_chunk != chunk_samples) {
         plan_workspace(m->pm, chunk_samples, net.plan);
+        // a result that is stored only where it is asked for lies where the op that else computes it will put its own
+        for (const FloatOp &f : net.ops)
+            if (f.pair >= 0) net.plan.toff[f.res] = net.plan.toff[f.out];
         net.planned_chunk = chunk_samples;
     }
     return ISR_OK;
@@ -258,6 +278,7 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
         bool whole = !raw_noise && stop_tensor != 0;
         if (whole) {
             for (const FloatOp &f : net.ops) {
+                if (f.paired && f.out != stop_tensor) continue;
                 if ((rc = mark()) != ISR_OK) return rc;
                 const TensorDesc &ti = pm.tensors[f.a], &to = pm.tensors[f.out];
                 switch (f.type) {
@@ -266,7 +287,8 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
                     FConvParams c = f.conv;
                     c.in = tptr(f.a);
                     c.out = f.type == OP_FC ? dlogits : tptr(f.out);
-                    c.res = f.res >= 0 ? tptr(f.res) : nullptr;
+                    if (f.pair >= 0) c.in2 = tptr(f.pair);
+                    else c.res = f.res >= 0 ? tptr(f.res) : nullptr;
                     c.npix = (int32_t)(bn * c.Ho * c.Wo);
                     HIP_TRY(launch_fconv(c, m->stream));
                     break; }

@@ -168,15 +168,19 @@ __global__ __launch_bounds__(256) void float_noise_kernel(const FloatNoiseParams
 // 32 cycles per 8 of them.
 //
 // ResNet-50 at 224 x 224, 668 copies: 58 -> 26.8 ms for all layers (1x1 layers at 56 x 56 within 1.05 - 1.6 of a copy at
-// 5 TB/s, 3x3 layers 2.0 - 2.8 times the matrix time: the split and the loads), 96 -> 213 TFLOP/s on 128-channel tiles.
+// 5 TB/s, 3x3 layers 2.0 - 2.8 times the matrix time: the split and the loads; now 24.0), 96 -> 213 TFLOP/s on 128-channel tiles.
 // Error of the logits against binary64 (2-norm), fp32 instruction -> this kernel: tiny net 3.5e-7 -> 3.3e-7, ResNet-20
 // 2.0e-7 -> 1.55e-7, ResNet-110 3.1e-7 -> 2.5e-7, ResNet-50 at 96 to 224 pixels 8.1 .. 9.5e-7 -> 4.9 .. 5.8e-7.
 //
 // FLAT: 1x1 stride-1 layers; else TABLE: K chunks of 4 channels looked up in ktab (a tap changes inside a step), else a
-// step lies inside one tap (Cin a multiple of 32) and its tap is counted along.
+// step lies inside one tap (Cin a multiple of 32) and its tap is counted along.  PAIR: a 1x1 layer of any stride whose residual is
+// another one's result that nothing else reads (the first block of a stage: closing convolution and projection).  The kernel
+// computes that one first and keeps it in registers, with the same operations on the same numbers; three stages, because such
+// layers have few steps (two: 1407 / 1086 / 729 / 605 us).  668 copies, two kernels -> one, at 56 / 28 / 14 / 7 pixels: 1881 -> 919,
+// 1220 -> 771, 866 -> 646, 665 -> 562 us.
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-enum FAddress { F_FLAT, F_TAP, F_TABLE };
+enum FAddress { F_FLAT, F_TAP, F_TABLE, F_PAIR };
 
 // the three bfloat16 parts of 8 floats, 8 to a register quadruple
 __device__ __forceinline__ void split_bf16(const v4f &lo, const v4f &hi, v4i (&part)[3]) {
@@ -199,7 +203,10 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
     constexpr int BM = 32 * MT, BN = 128 * NT;
     constexpr int ASTAGE = BM * 64, STAGE = ASTAGE + BN * 128;   // bytes
     constexpr int NA = (BM + 63) / 64, NB = BN / 32;             // direct-to-LDS loads per lane and step
-    __shared__ __attribute__((aligned(256))) int8_t lds[2 * STAGE];
+    constexpr bool PAIR = ADDR == F_PAIR;
+    constexpr int NST = PAIR ? 3 : 2;                            // stages; the steps after the current one are on their way to the others
+    __shared__ __attribute__((aligned(256))) int8_t lds[NST * STAGE];
+    __shared__ __attribute__((aligned(16))) float consts[PAIR ? 4 * BM : 1];                  // PAIR: bias, scale of the other layer, then of this one
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
@@ -222,6 +229,7 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
     const uint8_t *wsrc = (const uint8_t *)p.w + ((size_t)(ch0 + arow) * 64 + ac * 16);
     const uint8_t *in = (const uint8_t *)p.in;
     uint32_t boff[NB];          // byte offset of tap (0, 0) of the lane's pixel (of the pixel itself: FLAT), wrapping below 0
+    uint32_t boff2[ADDR == F_PAIR ? NB : 1];
     int iy0[NB], ix0[NB];
     const int hw_o = p.Ho * p.Wo;
 #pragma unroll
@@ -230,6 +238,10 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
         const int n = (int)(P < p.npix ? P : p.npix - 1);      // pixels past the end repeat the last one; never stored
         if constexpr (ADDR == F_FLAT) {
             boff[j] = (uint32_t)n * (uint32_t)(p.Cin_p * 4) + (uint32_t)(bc * 16);
+        } else if constexpr (ADDR == F_PAIR) {
+            const int b = n / hw_o, r = n - b * hw_o, oy = r / p.Wo, ox = r - oy * p.Wo;
+            boff[j] = (uint32_t)((b * p.H + oy * p.stride) * p.W + ox * p.stride) * (uint32_t)(p.Cin_p * 4) + (uint32_t)(bc * 16);
+            boff2[j] = (uint32_t)((b * p.H2 + oy * p.stride2) * p.W2 + ox * p.stride2) * (uint32_t)(p.Cin2_p * 4) + (uint32_t)(bc * 16);
         } else {
             const int b = n / hw_o, r = n - b * hw_o, oy = r / p.Wo, ox = r - oy * p.Wo;
             const int y = oy * p.stride - p.pad, x = ox * p.stride - p.pad;
@@ -247,7 +259,7 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
         for (int j = 0; j < NA; ++j)
             if (BM >= 64 || wave < 2)
                 ISR_GLOBAL_TO_LDS16_AT(wsrc + (size_t)step * p.Cout_pp * 64 + j * 4096, a + j * 4096);
-        if constexpr (ADDR == F_FLAT) {
+        if constexpr (ADDR == F_FLAT || ADDR == F_PAIR) {
 #pragma unroll
             for (int j = 0; j < NB; ++j) ISR_GLOBAL_TO_LDS16_AT(in + (boff[j] + (uint32_t)step * 128u), b + j * 4096);
         } else {
@@ -278,22 +290,27 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
     // one constant of the epilogue per thread: bias [BM], scale [BM]
     static_assert(2 * BM <= 256 && 8 * BM <= STAGE, "one constant a thread, into one stage");
     float bias_or_scale = 0.0f;
-    if (tid < 2 * BM) bias_or_scale = (tid < BM ? p.bias : p.scale)[ch0 + (tid < BM ? tid : tid - BM)];
+    if (tid < 2 * BM) {
+        const int ch = ch0 + (tid < BM ? tid : tid - BM);
+        bias_or_scale = (tid < BM ? p.bias : p.scale)[ch];
+        if constexpr (PAIR) {
+            consts[tid] = (tid < BM ? p.bias2 : p.scale2)[ch];
+            consts[2 * BM + tid] = bias_or_scale;
+        }
+    }
 
     v16f acc[MT][NT];
+    auto clear = [&]() {
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+            for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-
-    issue(0, 0);
-    for (int step = 0; step < nsteps; ++step) {
-        wait_vmcnt<0>();
-        __builtin_amdgcn_s_barrier();   // every wave's loads of this step landed; every wave is done reading the other buffer
-        if (step + 1 < nsteps) issue(step + 1, (step + 1) & 1);
-        const int8_t *A = lds + (step & 1) * STAGE, *B = A + ASTAGE;
+                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+    };
+    clear();
+    auto multiply = [&](int buf) {
+        const int8_t *A = lds + buf * STAGE, *B = A + ASTAGE;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             v4i af[MT];
@@ -316,17 +333,71 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
                                                                              acc[i][j], 0, 0, 0);
             }
         }
+    };
+
+    v16f other[PAIR ? MT : 1][PAIR ? NT : 1];   // PAIR: the residual
+    const float *bs = consts + 2 * BM;          // bias, scale
+    if constexpr (!PAIR) {
+        issue(0, 0);
+        for (int step = 0; step < nsteps; ++step) {
+            wait_vmcnt<0>();
+            __builtin_amdgcn_s_barrier();   // every wave's loads of this step landed; every wave is done reading the other buffer
+            if (step + 1 < nsteps) issue(step + 1, (step + 1) & 1);
+            multiply(step & 1);
+        }
+        float *idle = (float *)(lds + (nsteps & 1) * STAGE);   // the stage that the last step did not use
+        if (tid < 2 * BM) idle[tid] = bias_or_scale;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        bs = idle;
+    } else {
+        // the steps of both layers are one sequence; these layers have few, and wait for memory with one of them ahead
+        const uint8_t *wsrc2 = (const uint8_t *)p.w2 + ((size_t)(ch0 + arow) * 64 + ac * 16), *in2 = (const uint8_t *)p.in2;
+        const int steps2 = p.Cin2_p >> 5, all = steps2 + nsteps;
+        auto fetch = [&](int s, int buf) {
+            const uint32_t a = lds0 + buf * STAGE + wave * 1024, b = lds0 + buf * STAGE + ASTAGE + wave * 1024;
+            const bool own = s >= steps2;
+            const int step = own ? s - steps2 : s;
+            const uint8_t *w = (own ? wsrc : wsrc2) + (size_t)step * p.Cout_pp * 64, *x = (own ? in : in2) + step * 128;
+#pragma unroll
+            for (int j = 0; j < NA; ++j) ISR_GLOBAL_TO_LDS16_AT(w + j * 4096, a + j * 4096);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) ISR_GLOBAL_TO_LDS16_AT(x + (own ? boff[j] : boff2[j]), b + j * 4096);
+        };
+        fetch(0, 0);
+        fetch(1, 1);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the constants are stored
+        int buf = 0;
+        for (int s = 0; s < all; ++s) {
+            if (s + 1 < all) wait_vmcnt<NA + NB>();   // only the next step's loads may be in flight
+            else wait_vmcnt<0>();
+            __builtin_amdgcn_s_barrier();
+            if (s + 2 < all) fetch(s + 2, buf == 0 ? 2 : buf - 1);
+            multiply(buf);
+            buf = buf == 2 ? 0 : buf + 1;
+            if (s + 1 == steps2) {
+                const float lo = p.relu2 ? 0.0f : -INFINITY;
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            const int ch = i * 32 + 16 * half + 4 * g;
+                            const v4f bias = *(const v4f *)(consts + ch), scale = *(const v4f *)(consts + BM + ch);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) other[i][j][4 * g + e] = fmaxf((acc[i][j][4 * g + e] + bias[e]) * scale[e], lo);
+                        }
+                clear();
+            }
+        }
     }
 
     // Epilogue: with the weight rows in MFMA row order a lane holds 16 consecutive channels of one pixel.  Bias and scale come
     // from LDS (the stage that the last step did not use), the residual is read three groups of 16 channels ahead: a load
     // waits for the stores issued before it, and with bias, scale and residual loaded where they are used each of the 8 MT
     // stores of a wave was waited for in turn (64 -> 256 with residual, 668 copies of 56 x 56: 1285 -> 1140 us).
-    float *bs = (float *)(lds + (nsteps & 1) * STAGE);
-    if (tid < 2 * BM) bs[tid] = bias_or_scale;
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
     const float lo = p.relu ? 0.0f : -INFINITY, add_lo = p.add_relu ? 0.0f : -INFINITY;
     auto finish = [&](auto full, auto with_res) {
         constexpr bool FULL = decltype(full)::value, RES = decltype(with_res)::value;   // FULL: every pixel and channel of the tile exists
@@ -341,19 +412,20 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
         }
         // Cout_p is a multiple of 16: the run of a lane is stored whole or not at all
         auto there = [&](int u) { return FULL || (ok[u / MT] && ch0 + (u % MT) * 32 + 16 * half < p.Cout_p); };
-        v4f r[RES ? AHEAD + 1 : 1][4];
+        constexpr bool LOADED = RES && ADDR != F_PAIR;
+        v4f r[LOADED ? AHEAD + 1 : 1][4];
         auto fetch = [&](int u) {
             const float *src = p.res + (there(u) ? at[u / MT] + (u % MT) * 32 : 0);
 #pragma unroll
-            for (int g = 0; g < 4; ++g) r[RES ? u % (AHEAD + 1) : 0][g] = *(const v4f *)(src + 4 * g);
+            for (int g = 0; g < 4; ++g) r[LOADED ? u % (AHEAD + 1) : 0][g] = *(const v4f *)(src + 4 * g);
         };
-        if constexpr (RES)
+        if constexpr (LOADED)
 #pragma unroll
             for (int u = 0; u < AHEAD && u < U; ++u) fetch(u);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = u % MT, j = u / MT, ch = i * 32 + 16 * half;
-            if constexpr (RES)
+            if constexpr (LOADED)
                 if (u + AHEAD < U) fetch(u + AHEAD);
             __builtin_amdgcn_sched_barrier(0);
             v4f t[4];
@@ -363,7 +435,8 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     t[g][e] = fmaxf((acc[i][j][4 * g + e] + bias[e]) * scale[e], lo);
-                    if constexpr (RES) t[g][e] = fmaxf(p.ma * t[g][e] + p.mb * r[u % (AHEAD + 1)][g][e], add_lo);
+                    if constexpr (LOADED) t[g][e] = fmaxf(p.ma * t[g][e] + p.mb * r[u % (AHEAD + 1)][g][e], add_lo);
+                    else if constexpr (RES) t[g][e] = fmaxf(p.ma * t[g][e] + p.mb * other[i][j][4 * g + e], add_lo);
                 }
             }
             if (there(u))
@@ -372,7 +445,7 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
         }
     };
     const bool full = px0 + BN <= p.npix && ch0 + BM <= p.Cout_p;
-    if (p.res) {
+    if (ADDR == F_PAIR || p.res) {
         if (full) finish(std::true_type{}, std::true_type{});
         else finish(std::false_type{}, std::true_type{});
     } else {
@@ -497,6 +570,24 @@ static hipError_t launch_fconv_tile(const FConvParams &p, hipStream_t st) {
     return hipGetLastError();
 }
 
+// Two 1x1 layers of one kernel (F_PAIR): the same output tensor, channels in whole steps, stored channels in whole tiles' runs.
+bool fconv_pair_supported(const FConvParams &p, const FConvParams &q) {
+    return p.k == 1 && q.k == 1 && p.pad == 0 && q.pad == 0 && p.Cin_p % 32 == 0 && q.Cin_p % 32 == 0 && p.Cout_p == q.Cout_p && p.Cout_pp == q.Cout_pp &&
+           p.Ho == q.Ho && p.Wo == q.Wo && p.Cout_pp % 128 == 0;
+}
+
+static hipError_t launch_fconv_pair(const FConvParams &p, hipStream_t st) {
+    if (p.k != 1 || p.pad != 0 || p.Cin_p % 32 || p.Cin2_p <= 0 || p.Cin2_p % 32 || p.Cout_pp % 128 || !p.w2 || !p.bias2 || !p.scale2 || p.stride < 1 ||
+        p.stride2 < 1 || (p.Ho - 1) * p.stride >= p.H || (p.Wo - 1) * p.stride >= p.W || (p.Ho - 1) * p.stride2 >= p.H2 || (p.Wo - 1) * p.stride2 >= p.W2 ||
+        (long)p.npix / ((long)p.Ho * p.Wo) * p.H2 * p.W2 * p.Cin2_p >= (1L << 30))
+        return hipErrorInvalidValue;
+    const long blocks = (((long)p.npix + 127) / 128) * (p.Cout_pp / 128);
+    if (blocks > 0x7FFFFFFFL) return hipErrorInvalidValue;
+    set_kernel_name("fconv_kernel<128 x 128, pair>");
+    hipLaunchKernelGGL((fconv_kernel<4, 1, F_PAIR>), dim3((unsigned)blocks), dim3(256), 0, st, p);
+    return hipGetLastError();
+}
+
 hipError_t launch_fconv(const FConvParams &p, hipStream_t st) {
     if (p.npix <= 0) return hipSuccess;
     const int bm = fconv_tile_m(p.Cout_p);
@@ -504,6 +595,7 @@ hipError_t launch_fconv(const FConvParams &p, hipStream_t st) {
     if (p.Kq <= 0 || (p.Kq & 7) || p.Cout_pp % bm != 0 || p.Cout_p > p.Cout_pp || (p.Cout_p & 15) || (p.Cin_p & 3) || !p.zeros ||
         (long)p.npix / ((long)p.Ho * p.Wo) * p.H * p.W * p.Cin_p >= (1L << 30))
         return hipErrorInvalidValue;
+    if (p.in2) return launch_fconv_pair(p, st);
     // The largest tile (fewest bytes into LDS and fewest splits per multiply) that still gives every CU its two
     // workgroups; launches with few pixels take smaller ones.
     auto tiles = [&](int m, int n) { return (((long)p.npix + n - 1) / n) * (p.Cout_pp / m); };

@@ -383,6 +383,11 @@ struct FConvParams {
     int32_t npix;            // B * Ho * Wo
     int32_t relu, add_relu;
     float ma, mb;
+    // in2 != null: the residual is not stored but another 1x1 convolution's result, computed in the kernel (this one is 1x1 as well)
+    const float *in2;        // [B][H2][W2][Cin2_p]
+    const uint16_t *w2;
+    const float *bias2, *scale2;
+    int32_t H2, W2, Cin2_p, stride2, relu2;
 };
 struct FAddParams { const float *a, *b; float *out; float ma, mb; int32_t relu; int64_t n4; };
 struct FPoolParams { const float *in; float *out; int32_t H, W, Cp, Ho, Wo, k, stride, pad, B; };
@@ -390,6 +395,7 @@ struct FGapParams { const float *in; float *out; int32_t HW, Cp, B; float scale;
 struct FVoteParams { const float *logits; int32_t classes, stride, B; int32_t *argmax; uint32_t *counts; };
 hipError_t launch_float_noise(const FloatNoiseParams &p, hipStream_t st);
 hipError_t launch_fconv(const FConvParams &p, hipStream_t st);
+bool fconv_pair_supported(const FConvParams &p, const FConvParams &q);   // q's result as p's residual in one kernel
 int fconv_tile_m(int cout_p);   // channels per output tile chosen for a layer (Cout_pp is a multiple of it)
 hipError_t launch_fadd(const FAddParams &p, hipStream_t st);
 hipError_t launch_fmaxpool(const FPoolParams &p, hipStream_t st);

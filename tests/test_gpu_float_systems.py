@@ -183,6 +183,46 @@ def test_floatrs_fp_every_tile_and_addressing_form(isr, copies):
     m.close()
 
 
+@pytest.mark.parametrize("copies", [1, 60])
+@pytest.mark.parametrize("closing_first", [False, True])
+def test_floatrs_fp_residual_computed_in_the_kernel(isr, closing_first, copies):
+    """First blocks of a stage, whose residual is a projection that only their add reads: closing convolution and projection in
+    one kernel, in either order, with 1 to 5 steps each (fewer and more than stages), strides 1 and 2, channels that fill no tile,
+    ReLU on the inner convolution; the results that are no longer stored remain to be had one by one."""
+    _say(f"FloatRS-fp paired 1x1 layers, {copies} copies")
+    from synth.models import NetBuilder
+    b = NetBuilder(rng=np.random.default_rng(84), in_shape=(3, 29, 28), num_classes=6)
+    t = b.conv(b.tensor(3, 29, 28, 0, 74.0), 32, 3, 1, 1, True)
+    inner = []
+    for mid, out, stride, relu in ((32, 128, 1, False), (160, 144, 2, True), (64, 400, 1, False)):
+        u = b.conv(t, mid, 3, stride, 1, True)
+        if closing_first:
+            u = b.conv(u, out, 1, 1, 0, relu)
+            inner.append(u)
+            t = b.add(u, b.conv(t, out, 1, stride, 0, False), True)
+        else:
+            r = b.conv(t, out, 1, stride, 0, relu)
+            inner.append(r)
+            t = b.add(b.conv(u, out, 1, 1, 0, False), r, True)
+        t = b.conv(t, 96, 1, 1, 0, True)
+    b.fc(b.gap(t), 6)
+    blob = b.blob()
+    m = _load(isr, blob, 4 * copies)
+    om = oracle.Model(blob)
+    x = np.random.default_rng(5).integers(0, 256, size=(3, 29, 28)).astype(np.uint8)
+    lg, am, cnt = isr.isr_float_debug_forward(m, x, 63.75, 3, 1, 1, 50, copies, FP)
+    k = min(copies, 3)
+    wl = om.mc_float(x, 63.75, 3, 1, 1, 50 + copies - k, k, FP)[0]
+    _check_fp_logits(lg[-k:], wl, am[-k:])
+    assert cnt.sum() == copies
+    _, want = om.forward_float(oracle.noisy_float(x, 63.75, 3, 1, 1, 50))
+    for tid in inner:
+        c, h, w, _ = om.tensor_shape(tid)
+        got = isr.isr_float_debug_tensor(m, x, 63.75, 3, 1, 1, 50, tid, (c, h, w))
+        assert np.all(np.abs(got.astype(np.float64) - want[tid]) <= REL * np.abs(want[tid]).max()), tid
+    m.close()
+
+
 # 2-norm error of the logits that one rounding per product gives (the fp32 matrix instruction, a chain of fused
 # multiply-adds), measured over 768 copies: 2.0e-7 and 3.1e-7.  The kernel rounds less often (1.55e-7 and 2.5e-7); the bounds
 # are the chain's error plus 15 % for the spread of 24 copies.  Sums that all err to the same side, as the matrix unit's do
