@@ -1,6 +1,7 @@
 // C ABI: model loading, workspace planning and the Monte-Carlo driver that
 // enqueues noise -> layers -> vote kernels for chunks of sample indices.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -542,9 +543,29 @@ int isr::open_counts(isr_model *m) {
     m->counts_clean = false;
     return ISR_OK;
 }
+// Tallies to the host and zeros on the device, by the last kernel of a call: nothing that the call was given is in use when its
+// flag has arrived, only the kernel's own end is still to come.  Waits of more than 2 ms, and what goes wrong, are the runtime's.
+static int publish(isr_model *m, uint32_t *counts, uint32_t *host_dev, size_t n) {
+    if (n > PUBLISH_WATCHED) {
+        HIP_TRY(launch_publish(counts, host_dev, n, nullptr, 0, m->stream));
+        HIP_TRY(hipStreamSynchronize(m->stream));
+        return ISR_OK;
+    }
+    const uint32_t seq = ++m->published;
+    HIP_TRY(launch_publish(counts, host_dev, n, m->hflag_dev, seq, m->stream));
+    const auto patience = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+    for (uint32_t spins = 1; __atomic_load_n(m->hflag, __ATOMIC_ACQUIRE) != seq; ++spins) {
+        if (spins % 64 == 0 && std::chrono::steady_clock::now() > patience) {
+            HIP_TRY(hipStreamSynchronize(m->stream));
+            break;
+        }
+        __builtin_ia32_pause();
+    }
+    return ISR_OK;
+}
 int isr::close_counts(isr_model *m, uint32_t phases) {
-    HIP_TRY(launch_publish(m->dcounts, m->hcounts_dev, (size_t)phases * m->pm.classes, m->stream));
-    HIP_TRY(hipStreamSynchronize(m->stream));
+    const int rc = publish(m, m->dcounts, m->hcounts_dev, (size_t)phases * m->pm.classes);
+    if (rc != ISR_OK) return rc;
     m->counts_clean = true;
     return ISR_OK;
 }
@@ -606,7 +627,7 @@ int prepare_batch(isr_model *m, const void *x, uint32_t n_images, const isr_item
         HIP_TRY(hipMalloc((void **)&m->ditems, sizeof(NoiseItem) * cap));
         HIP_TRY(hipHostMalloc((void **)&m->hitems, sizeof(NoiseItem) * cap, hipHostMallocDefault));
         HIP_TRY(hipMalloc((void **)&m->dcounts_b, sizeof(uint32_t) * 2 * cap * C));
-        HIP_TRY(hipHostMalloc((void **)&m->hcounts_b, sizeof(uint32_t) * 2 * cap * C, hipHostMallocDefault));
+        HIP_TRY(hipHostMalloc((void **)&m->hcounts_b, sizeof(uint32_t) * 2 * cap * C, hipHostMallocCoherent));
         HIP_TRY(hipHostGetDevicePointer((void **)&m->hcounts_b_dev, m->hcounts_b, 0));
         m->items_cap = cap;
         m->counts_b_clean = false;
@@ -623,8 +644,8 @@ int prepare_batch(isr_model *m, const void *x, uint32_t n_images, const isr_item
 
 // The tallies of a batched call on the host, zeros on the device (as close_counts).
 int finish_batch(isr_model *m, size_t words) {
-    HIP_TRY(launch_publish(m->dcounts_b, m->hcounts_b_dev, words, m->stream));
-    HIP_TRY(hipStreamSynchronize(m->stream));
+    const int rc = publish(m, m->dcounts_b, m->hcounts_b_dev, words);
+    if (rc != ISR_OK) return rc;
     m->counts_b_clean = true;
     return ISR_OK;
 }
@@ -659,12 +680,16 @@ int isr_load_model(const void *blob_host, size_t bytes, isr_model **out) {
     const size_t narrow_off = round_256(arena.host.size()), tables_off = round_256(narrow_off + narrow_ops_room(m->ops));
     const size_t tables_bytes = round_256(sizeof(DeviceNoiseTable) * TABLE_SLOTS), counts_bytes = sizeof(uint32_t) * 2 * m->pm.classes;
     hipError_t e = hipMalloc((void **)&m->dconst, tables_off + tables_bytes + counts_bytes);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&m->htables, tables_bytes + counts_bytes, hipHostMallocDefault);
+    const size_t flag_off = round_256(tables_bytes + counts_bytes);
+    if (e == hipSuccess) e = hipHostMalloc((void **)&m->htables, flag_off + 64, hipHostMallocCoherent);   // the host watches the flag while a kernel runs
     if (e == hipSuccess) {
         m->dtables = (DeviceNoiseTable *)(m->dconst + tables_off);
         m->dcounts = (uint32_t *)(m->dconst + tables_off + tables_bytes);
         m->hcounts = (uint32_t *)((uint8_t *)m->htables + tables_bytes);
+        m->hflag = (uint32_t *)((uint8_t *)m->htables + flag_off);
+        *m->hflag = m->published;
         e = hipHostGetDevicePointer((void **)&m->hcounts_dev, m->hcounts, 0);
+        if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&m->hflag_dev, m->hflag, 0);
     }
     if (e != hipSuccess) { g_last_hip_error = (int)e; return cleanup(ISR_ERR_DEVICE); }
     rebase_device_ops(m->ops, m->dconst);

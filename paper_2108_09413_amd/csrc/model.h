@@ -31,6 +31,8 @@ struct isr_model {
     int table_next = 0;
     uint32_t *dcounts = nullptr;        // 2 * classes
     uint32_t *hcounts = nullptr, *hcounts_dev = nullptr;   // pinned, 2 * classes, and its address for kernels
+    uint32_t *hflag = nullptr, *hflag_dev = nullptr;       // one word in the same pinned allocation: number of the last call whose tallies arrived
+    uint32_t published = 0;                                // of the last call that published some
     bool counts_clean = false, counts_b_clean = false;     // dcounts, dcounts_b hold zeros
     // batched calls: item descriptors and per-item vote counters, grown on demand
     NoiseItem *ditems = nullptr, *hitems = nullptr;

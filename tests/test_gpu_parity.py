@@ -1126,6 +1126,23 @@ def test_batched_pairs_with_the_noise_drawn_inside_the_first_layer(isr, chunk):
     m.close()
 
 
+def test_tallies_of_every_size_reach_the_host(isr):
+    """The last kernel's hand-over of the tallies: few, the most that the host watches for, more than that; call after call on one
+    handle, so that each finds zeroed counters."""
+    _say("hand-over of the tallies")
+    blob = synth.build_model(0)
+    m = _load(isr, blob, 256)
+    om = oracle.Model(blob)
+    x = synth.make_image(0, 1)
+    for items in (1, 25, 26, 410, 25, 26, 1):
+        pairs = [(0, 32, 7 + i) for i in range(items)]
+        _, counts = isr.isr_predict_batch(m, x[None], pairs, 3, ALPHA, seed=items)
+        assert counts.shape == (items, 10) and np.all(counts.sum(axis=1) == 3)
+        for i in (0, items // 2, items - 1):
+            assert np.array_equal(counts[i], om.mc(x, 32, items, 7 + i, 0, 0, 3)[2]), (items, i)
+    m.close()
+
+
 def test_batched_call_argument_errors(isr):
     blob = synth.build_model(0)
     m = _load(isr, blob, 32)
