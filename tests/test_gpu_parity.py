@@ -272,6 +272,13 @@ def test_first_layer_fused_with_max_pooling(isr, shape):
     _check_all_tensors(isr, b.blob(), x, 64, sample=3, chunk=5)
 
 
+@pytest.mark.parametrize("shape", [(150, 100), (67, 124), (100, 160), (35, 224), (3, 128)])
+def test_first_layer_fused_with_max_pooling_in_several_bands(isr, shape):
+    """Images of more pooled rows than a workgroup makes, in one strip of columns (16 rows) and in two (8), whose last band and
+    last wave are partly or wholly outside the image."""
+    test_first_layer_fused_with_max_pooling(isr, shape)
+
+
 def test_identity_residual_blocks_in_one_kernel(isr):
     """conv3x3 -> conv3x3 -> add with the block input, at the three shapes that run as one
     LDS-resident kernel (16 channels at 32x32, 32 at 16x16, 64 at 8x8): non-trivial zero-points
