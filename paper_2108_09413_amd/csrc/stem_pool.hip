@@ -21,7 +21,8 @@
 // Bound by the issue of integer arithmetic, half of it the noise.  Bands of 8 pooled rows draw 39 rows of noise for 32 (bands of
 // 4: 23 for 16), waves of 4 pooled rows compute 9 convolution rows for 8 (waves of 2: 5 for 4), the bias joins the maxima
 // and not the accumulators, and a column outside the image is replaced by one of the same window instead of being masked:
-// 668 copies of 224 x 224 302 -> 270 us by the bands and waves, 291 -> 246 with the rest (another card).
+// 668 copies of 224 x 224 303 -> 269 us by the bands, the waves and the bias, 291 -> 246 us with the columns as well (each pair
+// on a card of its own).
 #include <climits>
 
 #include "conv_device.h"
