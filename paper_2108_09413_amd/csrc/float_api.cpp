@@ -32,6 +32,7 @@ struct FloatOp {
     int res = -1;                  // tensor read by the residual add folded into the convolution, or -1
     int pair = -1;                 // the op before, whose result is that tensor, runs in this op's kernel: its input tensor
     int paired = 0;                // this op runs in the next one's kernel (alone only where its own result is asked for)
+    int next = 0;                  // the next op, which reads this one's sum, can run in this op's kernel
     float ma = 0.f, mb = 0.f;      // ADD
     int relu = 0;
     FPoolParams pool{};
@@ -41,7 +42,9 @@ struct FloatOp {
 
 struct FloatNet {
     std::vector<FloatOp> ops;
-    Plan plan;                     // tensor placement: the ops' tensor ids with the int8 planner, whose bytes for B copies hold B / 4 fp32 copies
+    // tensor placement: the ops' tensor ids with the int8 planner, whose bytes for B copies hold B / 4 fp32 copies; `merged` with the
+    // results of ops that can run in one kernel placed together, which takes more, and is used where the workspace has it
+    Plan plan, merged;
     uint32_t planned_chunk = 0;
     uint8_t *dconst = nullptr;
     int status = ISR_OK;           // ISR_ERR_UNSUPPORTED when an op has no float kernel
@@ -204,11 +207,23 @@ int build_float_net(isr_model *m) {
         c.w2 = q.conv.w; c.bias2 = q.conv.bias; c.scale2 = q.conv.scale;
         c.H2 = q.conv.H; c.W2 = q.conv.W; c.Cin2_p = q.conv.Cin_p; c.stride2 = q.conv.stride; c.relu2 = q.conv.relu;
     }
-    for (const FloatOp &f : net->ops) {   // what the planner looks at: op type and tensor ids
+    // a closing convolution with its add and the convolution issued next, which reads the sum: one kernel writes both results
+    for (size_t i = 0; i + 1 < net->ops.size(); ++i) {
+        FloatOp &f = net->ops[i], &g = net->ops[i + 1];
+        f.next = f.type == OP_CONV && g.type == OP_CONV && f.res >= 0 && !f.paired && g.a == f.out && g.res < 0 && g.pair < 0 && !g.paired &&
+                 fexpand_supported(f.conv, g.conv);
+    }
+    for (size_t i = 0; i < net->ops.size(); ++i) {   // what the planner looks at: op type and tensor ids
+        const FloatOp &f = net->ops[i];
         if (f.paired) continue;
         DevOp d{};
         d.type = f.type; d.a = f.a; d.b = f.pair >= 0 ? f.pair : f.res >= 0 ? f.res : f.b; d.out = f.out;
         net->plan.ops.push_back(d);
+        if (i && net->ops[i - 1].next) {
+            net->merged.ops.back().out2 = f.out;
+            continue;
+        }
+        net->merged.ops.push_back(d);
     }
     return net->status = ISR_OK;
 }
@@ -217,14 +232,19 @@ int build_float_net(isr_model *m) {
 int plan_float_net(isr_model *m, uint32_t chunk_samples) {
     FloatNet &net = *m->fnet;
     if (net.planned_chunk != chunk_samples) {
-        plan_workspace(m->pm, chunk_samples, net.plan);
-        // a result that is stored only where it is asked for lies where the op that else computes it will put its own
-        for (const FloatOp &f : net.ops)
-            if (f.pair >= 0) net.plan.toff[f.res] = net.plan.toff[f.out];
+        for (Plan *pl : {&net.plan, &net.merged}) {
+            plan_workspace(m->pm, chunk_samples, *pl);
+            // a result that is stored only where it is asked for lies where the op that else computes it will put its own
+            for (const FloatOp &f : net.ops)
+                if (f.pair >= 0) pl->toff[f.res] = pl->toff[f.out];
+        }
         net.planned_chunk = chunk_samples;
     }
     return ISR_OK;
 }
+
+// The placement that the workspace has room for.
+const Plan &float_plan(const isr_model *m) { return m->fnet->merged.bytes <= m->ws_bytes ? m->fnet->merged : m->fnet->plan; }
 
 // Copies per chunk of the fp32 network: tensors sit at the offsets of the op-by-op int8 plan, four
 // bytes per element, so a quarter of the int8 chunk fits (less when the padded logits need more).
@@ -240,8 +260,9 @@ uint32_t float_chunk(const isr_model *m) {
 int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uint32_t image, uint32_t phase, uint32_t begin,
                  uint64_t count, float *logits_host, int32_t *argmax_host, uint32_t *dcounts, bool raw_noise, int stop_tensor = -1) {
     const ParsedModel &pm = m->pm;
-    const Plan &pl = m->fnet->plan;
     const FloatNet &net = *m->fnet;
+    const Plan &pl = float_plan(m);
+    const bool merged = &pl == &net.merged;
     const uint32_t chunk = float_chunk(m);
     if (chunk == 0) return ISR_ERR_WORKSPACE;
     auto tptr = [&](int t) { return (float *)(m->ws + pl.toff[t]); };
@@ -277,10 +298,12 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
         work.push_back({last_kernel_name(), 0, 0.0, (double)bn * pm.H * pm.W * 16});
         bool whole = !raw_noise && stop_tensor != 0;
         if (whole) {
-            for (const FloatOp &f : net.ops) {
+            for (size_t i = 0; i < net.ops.size(); ++i) {
+                const FloatOp &f = net.ops[i];
                 if (f.paired && f.out != stop_tensor) continue;
                 if ((rc = mark()) != ISR_OK) return rc;
                 const TensorDesc &ti = pm.tensors[f.a], &to = pm.tensors[f.out];
+                const FloatOp *last = &f;   // of this launch
                 switch (f.type) {
                 case OP_CONV:
                 case OP_FC: {
@@ -290,6 +313,14 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
                     if (f.pair >= 0) c.in2 = tptr(f.pair);
                     else c.res = f.res >= 0 ? tptr(f.res) : nullptr;
                     c.npix = (int32_t)(bn * c.Ho * c.Wo);
+                    if (merged && f.next && f.out != stop_tensor && fexpand_wanted(c, net.ops[i + 1].conv)) {
+                        const FloatOp &g = net.ops[++i];
+                        FConvParams r = g.conv;
+                        r.out = tptr(g.out);
+                        HIP_TRY(launch_fexpand(c, r, m->stream));
+                        last = &g;
+                        break;
+                    }
                     HIP_TRY(launch_fconv(c, m->stream));
                     break; }
                 case OP_ADD: {
@@ -307,7 +338,11 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
                     break; }
                 }
                 work.push_back({last_kernel_name(), f.type == OP_CONV || f.type == OP_FC, f.flops * bn, f.bytes * bn});
-                if (f.out == stop_tensor) { whole = false; break; }
+                if (last != &f) {   // the sum is not read back
+                    work.back().ops += last->flops * bn;
+                    work.back().bytes += (last->bytes - 4.0 * ti.H * ti.W * to.C) * bn;
+                }
+                if (last->out == stop_tensor) { whole = false; break; }
             }
         }
         if (whole) {
@@ -431,7 +466,7 @@ int isr_float_debug_noisy(isr_model *m, const uint8_t *x_device, float sigma, ui
     }
     if ((rc = run_fp_range(m, x_device, sigma, seed, image_id, phase, sample_begin, count, nullptr, nullptr, nullptr, true)) != ISR_OK) return rc;
     std::vector<float> tmp(count * hw * 4);
-    HIP_TRY(hipMemcpyAsync(tmp.data(), m->ws + m->fnet->plan.toff[0], tmp.size() * 4, hipMemcpyDeviceToHost, m->stream));
+    HIP_TRY(hipMemcpyAsync(tmp.data(), m->ws + float_plan(m).toff[0], tmp.size() * 4, hipMemcpyDeviceToHost, m->stream));
     HIP_TRY(hipStreamSynchronize(m->stream));
     float *o = (float *)out_host;
     for (uint32_t s = 0; s < count; ++s)
@@ -474,7 +509,7 @@ int isr_float_debug_tensor(isr_model *m, const uint8_t *x_device, float sigma, u
     const TensorDesc &t = pm.tensors[tensor_id];
     const size_t hw = (size_t)t.H * t.W;
     std::vector<float> tmp(hw * t.Cp);
-    HIP_TRY(hipMemcpyAsync(tmp.data(), m->ws + m->fnet->plan.toff[tensor_id], tmp.size() * 4, hipMemcpyDeviceToHost, m->stream));
+    HIP_TRY(hipMemcpyAsync(tmp.data(), m->ws + float_plan(m).toff[tensor_id], tmp.size() * 4, hipMemcpyDeviceToHost, m->stream));
     HIP_TRY(hipStreamSynchronize(m->stream));
     for (int c = 0; c < t.C; ++c)
         for (size_t i = 0; i < hw; ++i) out_host[(size_t)c * hw + i] = tmp[i * t.Cp + c];

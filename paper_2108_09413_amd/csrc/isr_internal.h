@@ -396,6 +396,9 @@ struct FVoteParams { const float *logits; int32_t classes, stride, B; int32_t *a
 hipError_t launch_float_noise(const FloatNoiseParams &p, hipStream_t st);
 hipError_t launch_fconv(const FConvParams &p, hipStream_t st);
 bool fconv_pair_supported(const FConvParams &p, const FConvParams &q);   // q's result as p's residual in one kernel
+bool fexpand_supported(const FConvParams &p, const FConvParams &q);      // p with its add, and q that reads the sum, in one kernel ...
+bool fexpand_wanted(const FConvParams &p, const FConvParams &q);         // ... for this number of pixels
+hipError_t launch_fexpand(const FConvParams &p, const FConvParams &q, hipStream_t st);
 int fconv_tile_m(int cout_p);   // channels per output tile chosen for a layer (Cout_pp is a multiple of it)
 hipError_t launch_fadd(const FAddParams &p, hipStream_t st);
 hipError_t launch_fmaxpool(const FPoolParams &p, hipStream_t st);

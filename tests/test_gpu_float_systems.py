@@ -223,6 +223,45 @@ def test_floatrs_fp_residual_computed_in_the_kernel(isr, closing_first, copies):
     m.close()
 
 
+@pytest.mark.parametrize("copies", [150, 305])
+@pytest.mark.parametrize("mid,out,reduced,pair", [(64, 128, 64, 0), (96, 512, 64, 0), (64, 384, 128, 0), (256, 512, 128, 0), (64, 128, 256, 0), (64, 384, 256, 0), (160, 1024, 256, 0),
+                                                  (32, 128, 64, 1), (96, 512, 64, 2), (64, 512, 128, 1), (160, 256, 128, 2)])
+def test_floatrs_fp_closing_layer_and_the_reader_of_its_sum(isr, mid, out, reduced, pair, copies):
+    """A block's closing 1x1 layer with its add and the 1x1 layer that reads the sum: one kernel for many copies (nearly a round of
+    workgroups and nearly two, whose pixels fill no tile; one and more steps of the first layer, one to eight times 128 channels), two for one copy.  pair: the residual is a
+    projection of that stride, computed in the kernel as well.  Where 256 channels of result next to a sum of 128 are more than the
+    workspace was ever asked for, two kernels.  The logits are the same to the bit and near the oracle's."""
+    _say(f"FloatRS-fp closing layer {mid} -> {out} -> {reduced}, projection {pair}, {copies} copies")
+    from synth.models import NetBuilder
+    b = NetBuilder(rng=np.random.default_rng(85), in_shape=(3, 29, 28), num_classes=6)
+    t = b.conv(b.tensor(3, 29, 28, 0, 74.0), 32, 3, 1 if pair == 2 else 2, 1, True)
+    if pair:
+        r = b.conv(t, out, 1, pair, 0, True)
+        t = b.add(b.conv(b.conv(t, mid, 3, pair, 1, True), out, 1, 1, 0, False), r, True)
+    else:
+        t = b.conv(t, out, 1, 1, 0, True)
+        t = b.add(b.conv(b.conv(t, mid, 1, 1, 0, True), out, 1, 1, 0, False), t, True)
+    u = b.conv(t, reduced, 1, 1, 0, True)                      # reads the sum, as the next add does
+    t = b.add(b.conv(u, out, 1, 1, 0, True), t, False)
+    t = b.conv(t, reduced, 1, 1, 0, False)
+    b.fc(b.gap(t), 6)
+    blob = b.blob()
+    m = _load(isr, blob, 4 * copies)
+    om = oracle.Model(blob)
+    x = np.random.default_rng(5).integers(0, 256, size=(3, 29, 28)).astype(np.uint8)
+    isr.isr_profile(m, 1)
+    lg, am, cnt = isr.isr_float_debug_forward(m, x, 63.75, 3, 1, 1, 50, copies, FP)
+    merged = any(k["name"].startswith("fexpand_kernel") for k in isr.isr_profile_read(m))
+    assert merged == (reduced <= out and (reduced < 256 or copies > 300))
+    for i in (0, 1, copies // 2, copies - 1):
+        assert np.array_equal(isr.isr_float_debug_forward(m, x, 63.75, 3, 1, 1, 50 + i, 1, FP)[0][0], lg[i]), i
+    k = 2
+    wl = om.mc_float(x, 63.75, 3, 1, 1, 50 + copies - k, k, FP)[0]
+    _check_fp_logits(lg[-k:], wl, am[-k:])
+    assert cnt.sum() == copies
+    m.close()
+
+
 # 2-norm error of the logits that one rounding per product gives (the fp32 matrix instruction, a chain of fused
 # multiply-adds), measured over 768 copies: 2.0e-7 and 3.1e-7.  The kernel rounds less often (1.55e-7 and 2.5e-7); the bounds
 # are the chain's error plus 15 % for the spread of 24 copies.  Sums that all err to the same side, as the matrix unit's do
