@@ -167,13 +167,13 @@ __global__ __launch_bounds__(256) void float_noise_kernel(const FloatNoiseParams
 // 32 NT pixels, so a pixel fragment is split in registers by one wave only: 5.5 instructions an element, for MT MFMAs of
 // 32 cycles per 8 of them.
 //
-// ResNet-50 at 224 x 224, 668 copies: 58 -> 26.8 ms for all layers (1x1 layers at 56 x 56 within 1.05 - 1.6 of a copy at
-// 5 TB/s, 3x3 layers 2.0 - 2.8 times the matrix time: the split and the loads; now 24.0), 96 -> 213 TFLOP/s on 128-channel tiles.
+// ResNet-50 at 224 x 224, 668 copies: 58 -> 26.8 ms for all layers by these products, 96 -> 213 TFLOP/s on 128-channel tiles; 19.6 ms
+// with the fused and the 3x3 kernels below.
 // Error of the logits against binary64 (2-norm), fp32 instruction -> this kernel: tiny net 3.5e-7 -> 3.3e-7, ResNet-20
-// 2.0e-7 -> 1.55e-7, ResNet-110 3.1e-7 -> 2.5e-7, ResNet-50 at 96 to 224 pixels 8.1 .. 9.5e-7 -> 4.9 .. 5.8e-7.
+// 2.0e-7 -> 1.55e-7, ResNet-110 3.1e-7 -> 2.4e-7, ResNet-50 at 96 to 224 pixels 8.1 .. 9.5e-7 -> 4.9 .. 5.9e-7.
 //
 // FLAT: 1x1 stride-1 layers; else TABLE: K chunks of 4 channels looked up in ktab (a tap changes inside a step), else a
-// step lies inside one tap (Cin a multiple of 32) and its tap is counted along.  PAIR: a 1x1 layer of any stride whose residual is
+// step lies inside one tap (Cin a multiple of 32) and its tap is counted along, all taps of 32 channels before the next 32.  PAIR: a 1x1 layer of any stride whose residual is
 // another one's result that nothing else reads (the first block of a stage: closing convolution and projection).  The kernel
 // computes that one first and keeps it in registers, with the same operations on the same numbers; three stages, because such
 // layers have few steps (two: 1407 / 1086 / 729 / 605 us).  668 copies, two kernels -> one, at 56 / 28 / 14 / 7 pixels: 1881 -> 919,
@@ -195,6 +195,72 @@ __device__ __forceinline__ void split_bf16(const v4f &lo, const v4f &hi, v4i (&p
                 b = b - __uint_as_float(__float_as_uint(b) & 0xFFFF0000u);
             }
         }
+    }
+}
+
+// Epilogue of a tile of 32 MT channels by 32 NT pixels a wave: with the weight rows in MFMA row order a lane holds 16 consecutive
+// channels of one pixel.  Bias and scale come from LDS (`bs`, a stage that the last step did not use), the residual is read three groups
+// of 16 channels ahead: a load waits for the stores issued before it, and with bias, scale and residual loaded where they are used
+// each of the 8 MT stores of a wave was waited for in turn (64 -> 256 with residual, 668 copies of 56 x 56: 1285 -> 1140 us).
+// PAIR: the residual is in `other`.  FULL: every pixel and channel of the tile exists.
+template <bool FULL, bool RES, bool PAIR, int MT, int NT, class Other>
+__device__ __forceinline__ void fconv_finish(const FConvParams &p, const v16f (&acc)[MT][NT], const Other &other, const float *bs, long px, int ch0, int lane) {
+    constexpr int BM = 32 * MT, U = NT * MT, AHEAD = 3;
+    const int half = lane >> 5, l32 = lane & 31;
+    const float lo = p.relu ? 0.0f : -INFINITY, add_lo = p.add_relu ? 0.0f : -INFINITY;
+    long at[NT];
+    bool ok[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const long P = px + j * 32 + l32;
+        ok[j] = FULL || P < p.npix;
+        at[j] = (ok[j] ? P : 0) * p.Cout_p + ch0 + 16 * half;
+    }
+    // Cout_p is a multiple of 16: the run of a lane is stored whole or not at all
+    auto there = [&](int u) { return FULL || (ok[u / MT] && ch0 + (u % MT) * 32 + 16 * half < p.Cout_p); };
+    constexpr bool LOADED = RES && !PAIR;
+    v4f r[LOADED ? AHEAD + 1 : 1][4];
+    auto fetch = [&](int u) {
+        const float *src = p.res + (there(u) ? at[u / MT] + (u % MT) * 32 : 0);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) r[LOADED ? u % (AHEAD + 1) : 0][g] = *(const v4f *)(src + 4 * g);
+    };
+    if constexpr (LOADED)
+#pragma unroll
+        for (int u = 0; u < AHEAD && u < U; ++u) fetch(u);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = u % MT, j = u / MT, ch = i * 32 + 16 * half;
+        if constexpr (LOADED)
+            if (u + AHEAD < U) fetch(u + AHEAD);
+        __builtin_amdgcn_sched_barrier(0);
+        v4f t[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const v4f bias = *(const v4f *)(bs + ch + 4 * g), scale = *(const v4f *)(bs + BM + ch + 4 * g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                t[g][e] = fmaxf((acc[i][j][4 * g + e] + bias[e]) * scale[e], lo);
+                if constexpr (LOADED) t[g][e] = fmaxf(p.ma * t[g][e] + p.mb * r[u % (AHEAD + 1)][g][e], add_lo);
+                else if constexpr (RES) t[g][e] = fmaxf(p.ma * t[g][e] + p.mb * other[i][j][4 * g + e], add_lo);
+            }
+        }
+        if (there(u))
+#pragma unroll
+            for (int g = 0; g < 4; ++g) *(v4f *)(p.out + at[j] + i * 32 + 4 * g) = t[g];
+    }
+}
+template <bool PAIR, int MT, int NT, class Other>
+__device__ __forceinline__ void fconv_finish_tile(const FConvParams &p, const v16f (&acc)[MT][NT], const Other &other, const float *bs, long px0, int ch0,
+                                                  int wave, int lane, int waves) {
+    const bool full = px0 + waves * 32 * NT <= p.npix && ch0 + 32 * MT <= p.Cout_p;
+    const long px = px0 + wave * NT * 32;
+    if (PAIR || p.res) {
+        if (full) fconv_finish<true, true, PAIR>(p, acc, other, bs, px, ch0, lane);
+        else fconv_finish<false, true, PAIR>(p, acc, other, bs, px, ch0, lane);
+    } else {
+        if (full) fconv_finish<true, false, PAIR>(p, acc, other, bs, px, ch0, lane);
+        else fconv_finish<false, false, PAIR>(p, acc, other, bs, px, ch0, lane);
     }
 }
 
@@ -258,7 +324,7 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
 #pragma unroll
         for (int j = 0; j < NA; ++j)
             if (BM >= 64 || wave < 2)
-                ISR_GLOBAL_TO_LDS16_AT(wsrc + (size_t)step * p.Cout_pp * 64 + j * 4096, a + j * 4096);
+                ISR_GLOBAL_TO_LDS16_AT(wsrc + (size_t)(ADDR == F_TAP ? (dy * p.k + dx) * (p.Cin_p >> 5) + (c0 >> 5) : step) * p.Cout_pp * 64 + j * 4096, a + j * 4096);
         if constexpr (ADDR == F_FLAT || ADDR == F_PAIR) {
 #pragma unroll
             for (int j = 0; j < NB; ++j) ISR_GLOBAL_TO_LDS16_AT(in + (boff[j] + (uint32_t)step * 128u), b + j * 4096);
@@ -281,8 +347,7 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
                 ISR_GLOBAL_TO_LDS16_AT(ok ? src : (const uint8_t *)p.zeros, b + j * 4096);
             }
             if constexpr (ADDR == F_TAP) {
-                c0 += 32;
-                if (c0 == p.Cin_p) { c0 = 0; if (++dx == p.k) { dx = 0; ++dy; } }
+                if (++dx == p.k) { dx = 0; if (++dy == p.k) { dy = 0; c0 += 32; } }
             }
         }
     };
@@ -394,64 +459,150 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
         }
     }
 
-    // Epilogue: with the weight rows in MFMA row order a lane holds 16 consecutive channels of one pixel.  Bias and scale come
-    // from LDS (the stage that the last step did not use), the residual is read three groups of 16 channels ahead: a load
-    // waits for the stores issued before it, and with bias, scale and residual loaded where they are used each of the 8 MT
-    // stores of a wave was waited for in turn (64 -> 256 with residual, 668 copies of 56 x 56: 1285 -> 1140 us).
-    const float lo = p.relu ? 0.0f : -INFINITY, add_lo = p.add_relu ? 0.0f : -INFINITY;
-    auto finish = [&](auto full, auto with_res) {
-        constexpr bool FULL = decltype(full)::value, RES = decltype(with_res)::value;   // FULL: every pixel and channel of the tile exists
-        constexpr int U = NT * MT, AHEAD = 3;
-        long at[NT];
-        bool ok[NT];
+    fconv_finish_tile<PAIR>(p, acc, other, bs, px0, ch0, wave, lane, 4);
+}
+
+// 3x3 layers of stride 1 with a border of one pixel: the nine taps of 128 consecutive pixels lie in one run of 130 + 2 W pixels.  The
+// workgroup splits 32 channels of that run once into three planes of bfloat16 in LDS, from which all nine taps read their
+// operands; tap by tap through fconv_kernel every pixel was fetched and split nine times, 44 instructions for 3 MT matrix instructions,
+// which left the matrix unit idle for half of the time.  Taps outside the image read a row of zeros.  The weights
+// of a tap come through three stages, two steps ahead; the next channels of the run are fetched into registers during the second to
+// ninth tap.  Products are added in the order of fconv_kernel.  668 copies of ResNet-50's layers of 64 channels at
+// 56 x 56, 128 at 28 x 28, 256 at 14 x 14, 512 at 7 x 7, tap by tap -> from the run: 600 -> 450, 464 -> 372, 410 -> 333, 387 -> 320 us
+// (0.21 ms at the nominal rate of the matrix unit); 16 copies at 56 x 56: 27 -> 21 us.
+template <int MT, int NL>   // NL: rows of 32 pixels of the run, 130 + 2 W <= 32 NL
+__global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
+    constexpr int BM = 32 * MT, BN = 128, NST = 3, ASTAGE = BM * 64, NA = (BM + 63) / 64, ZERO = 32 * NL, PLANE = (32 * NL + 1) * 64;
+    __shared__ __attribute__((aligned(256))) int8_t wt[NST * ASTAGE];
+    __shared__ __attribute__((aligned(256))) int8_t run[3 * PLANE];
+    static_assert(sizeof(wt) + sizeof(run) <= 80 * 1024 && 2 * BM <= 256 && 8 * BM <= ASTAGE, "two workgroups a CU; the constants fit a stage");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const int mtiles = p.Cout_pp / BM;
+    const long nb = gridDim.x, per = nb >> 3, rem = nb & 7, xcd = blockIdx.x & 7;
+    const long bid = xcd * per + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3);   // as fconv_kernel
+    const int ch0 = (int)(bid % mtiles) * BM;
+    const int px0 = (int)(bid / mtiles) * BN;
+    const uint32_t lds0 = lds_address(wt) + wave * 1024;
+    const int nblk = p.Cin_p >> 5, arow = tid >> 2, ac = (tid & 3) ^ swz<4>(arow);
+    const uint32_t wlane = (uint32_t)((ch0 + arow) * 64 + ac * 16);
+
+    int ft = 0, fb = 0, fbuf = 0;   // tap, block of 32 channels and stage of the next weights to fetch
+    auto weights = [&]() {
+        if (fb >= nblk) return;
+        const uint8_t *w = (const uint8_t *)p.w + (size_t)(ft * nblk + fb) * p.Cout_pp * 64;
 #pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            const long P = px0 + (wave * NT + j) * 32 + l32;
-            ok[j] = FULL || P < p.npix;
-            at[j] = (ok[j] ? P : 0) * p.Cout_p + ch0 + 16 * half;
-        }
-        // Cout_p is a multiple of 16: the run of a lane is stored whole or not at all
-        auto there = [&](int u) { return FULL || (ok[u / MT] && ch0 + (u % MT) * 32 + 16 * half < p.Cout_p); };
-        constexpr bool LOADED = RES && ADDR != F_PAIR;
-        v4f r[LOADED ? AHEAD + 1 : 1][4];
-        auto fetch = [&](int u) {
-            const float *src = p.res + (there(u) ? at[u / MT] + (u % MT) * 32 : 0);
+        for (int j = 0; j < NA; ++j)
+            if (BM >= 64 || wave < 2) ISR_GLOBAL_TO_LDS16_AT(w + (wlane + (uint32_t)(j * 4096)), lds0 + fbuf * ASTAGE + j * 4096);
+        fbuf = fbuf == NST - 1 ? 0 : fbuf + 1;
+        if (++ft == 9) { ft = 0; ++fb; }
+    };
+    // a thread's four channels of NL pixels of the run; pixels outside the tensor are never read from LDS
+    const int rrow = tid >> 3, rc = tid & 7;
+    v4f next[NL];
+    auto fetch = [&](int blk) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) r[LOADED ? u % (AHEAD + 1) : 0][g] = *(const v4f *)(src + 4 * g);
-        };
-        if constexpr (LOADED)
-#pragma unroll
-            for (int u = 0; u < AHEAD && u < U; ++u) fetch(u);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = u % MT, j = u / MT, ch = i * 32 + 16 * half;
-            if constexpr (LOADED)
-                if (u + AHEAD < U) fetch(u + AHEAD);
-            __builtin_amdgcn_sched_barrier(0);
-            v4f t[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const v4f bias = *(const v4f *)(bs + ch + 4 * g), scale = *(const v4f *)(bs + BM + ch + 4 * g);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    t[g][e] = fmaxf((acc[i][j][4 * g + e] + bias[e]) * scale[e], lo);
-                    if constexpr (LOADED) t[g][e] = fmaxf(p.ma * t[g][e] + p.mb * r[u % (AHEAD + 1)][g][e], add_lo);
-                    else if constexpr (RES) t[g][e] = fmaxf(p.ma * t[g][e] + p.mb * other[i][j][4 * g + e], add_lo);
-                }
-            }
-            if (there(u))
-#pragma unroll
-                for (int g = 0; g < 4; ++g) *(v4f *)(p.out + at[j] + i * 32 + 4 * g) = t[g];
+        for (int j = 0; j < NL; ++j) {
+            int n = px0 - p.W - 1 + rrow + 32 * j;
+            n = n < 0 ? 0 : (n < p.npix ? n : p.npix - 1);
+            next[j] = *(const v4f *)((const uint8_t *)p.in + ((uint32_t)n * (uint32_t)(p.Cin_p * 4) + (uint32_t)(blk * 128 + rc * 16)));
         }
     };
-    const bool full = px0 + BN <= p.npix && ch0 + BM <= p.Cout_p;
-    if (ADDR == F_PAIR || p.res) {
-        if (full) finish(std::true_type{}, std::true_type{});
-        else finish(std::false_type{}, std::true_type{});
-    } else {
-        if (full) finish(std::true_type{}, std::false_type{});
-        else finish(std::false_type{}, std::false_type{});
-    }
+    auto store = [&]() {
+        int8_t *dst = run + rrow * 64 + (((rc >> 1) ^ swz<4>(rrow)) << 4) + (rc & 1) * 8;
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            float x[4] = {next[j][0], next[j][1], next[j][2], next[j][3]};
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                uint2 part;
+                part.x = __builtin_amdgcn_perm(__float_as_uint(x[1]), __float_as_uint(x[0]), 0x07060302u);
+                part.y = __builtin_amdgcn_perm(__float_as_uint(x[3]), __float_as_uint(x[2]), 0x07060302u);
+                *(uint2 *)(dst + k * PLANE + j * 2048) = part;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (k < 2) x[e] = x[e] - __uint_as_float(__float_as_uint(x[e]) & 0xFFFF0000u);   // exact
+            }
+        }
+    };
+    float bias_or_scale = 0.0f;
+    if (tid < 2 * BM) bias_or_scale = (tid < BM ? p.bias : p.scale)[ch0 + (tid < BM ? tid : tid - BM)];
+    fetch(0);
+    if (tid < 12) *(v4i *)(run + (tid >> 2) * PLANE + ZERO * 64 + (tid & 3) * 16) = v4i{0, 0, 0, 0};
+
+    // the lane's pixel: which taps are inside the image
+    const int P = px0 + wave * 32 + l32, n = P < p.npix ? P : p.npix - 1;
+    const int x = n % p.W, y = n / p.W % p.H;
+    const int centre = wave * 32 + l32 + p.W + 1;
+    v16f acc[MT][1];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][0][e] = 0.0f;
+
+    store();
+    weights();
+    weights();
+    int buf = 0;
+    auto block = [&](int blk, auto not_last) {
+        constexpr bool more = decltype(not_last)::value;
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+            // what may be left of what this thread has issued since this step's weights: those of the next step, and the run's channels,
+            // fetched in step 0
+            if (tap == 8 && !more) wait_vmcnt<0>();
+            else if ((tap == 1 || tap == 2) && more) wait_vmcnt<NA + NL>();
+            else wait_vmcnt<NA>();
+            if (tap == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the run is stored
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            weights();
+            if (tap == 0 && more) {
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+                fetch(blk + 1);
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const int dy = tap / 3 - 1, dx = tap % 3 - 1;
+            const bool ok = (unsigned)(y + dy) < (unsigned)p.H && (unsigned)(x + dx) < (unsigned)p.W;
+            const int row = ok ? centre + dy * p.W + dx : ZERO;
+            const int at = row * 64 + ((half ^ swz<4>(row)) << 4);
+            const int8_t *A = wt + buf * ASTAGE;
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                v4i af[MT], part[3];
+#pragma unroll
+                for (int i = 0; i < MT; ++i) {
+                    const int r = i * 32 + l32;
+                    af[i] = *(const v4i *)(A + r * 64 + (((2 * ks + half) ^ swz<4>(r)) << 4));
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k) part[k] = *(const v4i *)(run + k * PLANE + (at ^ (32 * ks)));
+#pragma unroll
+                for (int k = 2; k >= 0; --k)
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+                        acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, af[i]), __builtin_bit_cast(v8bf, part[k]), acc[i][0], 0, 0, 0);
+            }
+            buf = buf == NST - 1 ? 0 : buf + 1;
+        }
+        if (more) {
+            __builtin_amdgcn_s_barrier();   // every wave has read the run
+            asm volatile("" ::: "memory");
+            store();
+        }
+    };
+    for (int blk = 0; blk + 1 < nblk; ++blk) block(blk, std::true_type{});
+    block(nblk - 1, std::false_type{});
+    __builtin_amdgcn_s_barrier();
+    float *bs = (float *)wt;
+    if (tid < 2 * BM) bs[tid] = bias_or_scale;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    fconv_finish_tile<false>(p, acc, 0, bs, px0, ch0, wave, lane, 4);
 }
 
 // A closing 1x1 layer with its residual add, and the 1x1 layer that reads the sum, in one kernel.  Both are bound by memory, by
@@ -822,6 +973,19 @@ static hipError_t launch_fconv_pair(const FConvParams &p, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <int MT>
+static hipError_t launch_fpatch(const FConvParams &p, hipStream_t st) {
+    const long blocks = (((long)p.npix + 127) / 128) * (p.Cout_pp / (32 * MT));
+    if (blocks > 0x7FFFFFFFL || 130 + 2 * p.W > 256) return hipErrorInvalidValue;
+    static const std::string name = "fpatch_kernel<" + std::to_string(32 * MT) + ">";
+    set_kernel_name(name.c_str());
+    const dim3 grid((unsigned)blocks), block(256);
+    if (130 + 2 * p.W <= 160) hipLaunchKernelGGL((fpatch_kernel<MT, 5>), grid, block, 0, st, p);
+    else if (130 + 2 * p.W <= 192) hipLaunchKernelGGL((fpatch_kernel<MT, 6>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((fpatch_kernel<MT, 8>), grid, block, 0, st, p);
+    return hipGetLastError();
+}
+
 hipError_t launch_fconv(const FConvParams &p, hipStream_t st) {
     if (p.npix <= 0) return hipSuccess;
     const int bm = fconv_tile_m(p.Cout_p);
@@ -834,6 +998,11 @@ hipError_t launch_fconv(const FConvParams &p, hipStream_t st) {
     // workgroups; launches with few pixels take smaller ones.
     auto tiles = [&](int m, int n) { return (((long)p.npix + n - 1) / n) * (p.Cout_pp / m); };
     constexpr long FULL = 512;
+    if (p.k == 3 && p.stride == 1 && p.pad == 1 && p.Cin_p % 32 == 0 && p.W <= 63 && p.Ho == p.H && p.Wo == p.W) {
+        if (bm == 128 && tiles(128, 128) >= FULL) return launch_fpatch<4>(p, st);
+        if (bm >= 64 && tiles(64, 128) >= FULL) return launch_fpatch<2>(p, st);
+        return launch_fpatch<1>(p, st);
+    }
     if (bm == 128) {
         if (tiles(128, 256) >= FULL) return launch_fconv_tile<4, 2>(p, st);
         if (tiles(128, 128) >= FULL) return launch_fconv_tile<4, 1>(p, st);

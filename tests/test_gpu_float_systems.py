@@ -262,6 +262,35 @@ def test_floatrs_fp_closing_layer_and_the_reader_of_its_sum(isr, mid, out, reduc
     m.close()
 
 
+@pytest.mark.parametrize("h,w,copies", [(9, 63, 5), (9, 64, 5), (3, 32, 9), (40, 31, 2), (17, 16, 9), (15, 15, 300), (16, 15, 3), (1, 15, 40), (5, 1, 40), (1, 1, 3)])
+def test_floatrs_fp_3x3_layers_from_one_run_of_pixels(isr, h, w, copies):
+    """3x3 layers whose nine taps are read from one run of pixels in LDS: the widest maps of each size of run (15, 31, 63) and the next
+    (64: tap by tap), single rows, columns and pixels, tiles that span images, 32 to 160 channels in and out, few tiles and many,
+    with a residual and without, against the oracle."""
+    _say(f"FloatRS-fp 3x3 layers on {h} x {w}, {copies} copies")
+    from synth.models import NetBuilder
+    k = 4 - (w - 1) % 4                                         # inputs are a multiple of 4 pixels wide
+    b = NetBuilder(rng=np.random.default_rng(86), in_shape=(3, h + k - 1, w + k - 1), num_classes=6)
+    t = b.conv(b.tensor(3, h + k - 1, w + k - 1, 0, 74.0), 32, k, 1, 0, True)
+    t = b.conv(t, 96, 3, 1, 1, True)
+    u = b.conv(t, 64, 3, 1, 1, True)
+    t = b.add(b.conv(u, 96, 3, 1, 1, False), t, True)
+    t = b.conv(t, 160, 3, 1, 1, True)
+    t = b.conv(t, 32, 3, 1, 1, False)
+    b.fc(b.gap(t), 6)
+    blob = b.blob()
+    m = _load(isr, blob, 4 * copies)
+    om = oracle.Model(blob)
+    x = np.random.default_rng(5).integers(0, 256, size=(3, h + k - 1, w + k - 1)).astype(np.uint8)
+    lg, am, cnt = isr.isr_float_debug_forward(m, x, 63.75, 3, 1, 1, 50, copies, FP)
+    n = min(copies, 3)
+    wl = om.mc_float(x, 63.75, 3, 1, 1, 50 + copies - n, n, FP)[0]
+    _check_fp_logits(lg[-n:], wl, am[-n:])
+    assert np.array_equal(isr.isr_float_debug_forward(m, x, 63.75, 3, 1, 1, 50 + copies // 2, 1, FP)[0][0], lg[copies // 2])
+    assert cnt.sum() == copies
+    m.close()
+
+
 # 2-norm error of the logits that one rounding per product gives (the fp32 matrix instruction, a chain of fused
 # multiply-adds), measured over 768 copies: 2.0e-7 and 3.1e-7.  The kernel rounds less often (1.55e-7 and 2.5e-7); the bounds
 # are the chain's error plus 15 % for the spread of 24 copies.  Sums that all err to the same side, as the matrix unit's do
