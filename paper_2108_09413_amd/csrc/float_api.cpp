@@ -43,7 +43,7 @@ struct FloatOp {
 struct FloatNet {
     std::vector<FloatOp> ops;
     // tensor placement: the ops' tensor ids with the int8 planner, whose bytes for B copies hold B / 4 fp32 copies; `merged` with the
-    // results of ops that can run in one kernel placed together, which takes more, and is used where the workspace has it
+    // results of ops that can run in one kernel placed together, which can take more, and is used where the workspace has it
     Plan plan, merged;
     uint32_t planned_chunk = 0;
     uint8_t *dconst = nullptr;
@@ -94,22 +94,25 @@ int build_conv(const ParsedModel &pm, const HostOp &o, int k, int stride, int pa
     const int bm = fconv_tile_m(c.Cout_p);
     c.Cout_pp = (c.Cout_p + bm - 1) / bm * bm;
     c.k = k; c.stride = stride; c.pad = pad;
-    const int kq_real = k * k * ti.Cp / 4;
+    // quads of K of a kernel row; the 7x7 layers on images leave the last of eight empty (fstem_pool_kernel reads pairs of pixels)
+    const int row_quads = k * ti.Cp / 4 + (k == 7 && ti.Cp == 4 ? 1 : 0), kq_real = k * row_quads;
     c.Kq = (kq_real + 7) & ~7;
     c.relu = fc ? 0 : o.relu;
     std::vector<uint16_t> w((size_t)c.Kq * c.Cout_pp * 4, 0);
     std::vector<float> bias(c.Cout_pp, 0.f), scale(c.Cout_pp, 0.f);
     std::vector<int32_t> ktab(c.Kq, -1);
     for (int kq = 0; kq < kq_real; ++kq) {
-        const int tap = 4 * kq / ti.Cp, coff = 4 * kq % ti.Cp;
-        ktab[kq] = ((tap / k) << 24) | ((tap % k) << 16) | coff;
+        const int kx = kq % row_quads * 4 / ti.Cp, coff = kq % row_quads * 4 % ti.Cp;
+        if (kx < k) ktab[kq] = ((kq / row_quads) << 24) | (kx << 16) | coff;
     }
+    std::vector<uint32_t> first_k(k * k);   // place in K of a tap's first channel
+    for (int t = 0; t < k * k; ++t) first_k[t] = (uint32_t)(t / k * row_quads * 4 + t % k * ti.Cp);
     for (int oc = 0; oc < to.C; ++oc) {
         const int row = (oc / 32) * 32 + mfma_row_of_channel(oc % 32);
         const int sign = (oc ^ first_negated) & 1 ? 1 : -1;
         for (int ic = 0; ic < ti.C; ++ic)
             for (int t = 0; t < k * k; ++t) {
-                const int kidx = t * ti.Cp + ic;
+                const uint32_t kidx = first_k[t] + (uint32_t)ic;
                 w[((size_t)(kidx / 32) * c.Cout_pp + row) * 32 + kidx % 32] = bf16_of_int(sign * o.w[((size_t)oc * ti.C + ic) * k * k + t]);
             }
         bias[oc] = (float)sign * (float)o.bias[oc];
@@ -210,6 +213,10 @@ int build_float_net(isr_model *m) {
     // a closing convolution with its add and the convolution issued next, which reads the sum: one kernel writes both results
     for (size_t i = 0; i + 1 < net->ops.size(); ++i) {
         FloatOp &f = net->ops[i], &g = net->ops[i + 1];
+        if (f.type == OP_CONV && g.type == OP_MAXPOOL) {   // a first layer and its pooling, which alone reads it: its result is not stored
+            f.next = f.res < 0 && g.a == f.out && uses[f.out] == 1 && fstem_pool_supported(f.conv, g.pool);
+            continue;
+        }
         f.next = f.type == OP_CONV && g.type == OP_CONV && f.res >= 0 && !f.paired && g.a == f.out && g.res < 0 && g.pair < 0 && !g.paired &&
                  fexpand_supported(f.conv, g.conv);
     }
@@ -220,7 +227,8 @@ int build_float_net(isr_model *m) {
         d.type = f.type; d.a = f.a; d.b = f.pair >= 0 ? f.pair : f.res >= 0 ? f.res : f.b; d.out = f.out;
         net->plan.ops.push_back(d);
         if (i && net->ops[i - 1].next) {
-            net->merged.ops.back().out2 = f.out;
+            DevOp &both = net->merged.ops.back();
+            (f.type == OP_MAXPOOL ? both.out : both.out2) = f.out;
             continue;
         }
         net->merged.ops.push_back(d);
@@ -243,8 +251,11 @@ int plan_float_net(isr_model *m, uint32_t chunk_samples) {
     return ISR_OK;
 }
 
-// The placement that the workspace has room for.
-const Plan &float_plan(const isr_model *m) { return m->fnet->merged.bytes <= m->ws_bytes ? m->fnet->merged : m->fnet->plan; }
+// The placement for forwards that end at `stop_tensor` (-1: at the votes): `merged` where the workspace has room and that tensor a place.
+const Plan &float_plan(const isr_model *m, int stop_tensor) {
+    const FloatNet &net = *m->fnet;
+    return net.merged.bytes <= m->ws_bytes && (stop_tensor < 0 || net.merged.has[stop_tensor]) ? net.merged : net.plan;
+}
 
 // Copies per chunk of the fp32 network: tensors sit at the offsets of the op-by-op int8 plan, four
 // bytes per element, so a quarter of the int8 chunk fits (less when the padded logits need more).
@@ -261,7 +272,7 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
                  uint64_t count, float *logits_host, int32_t *argmax_host, uint32_t *dcounts, bool raw_noise, int stop_tensor = -1) {
     const ParsedModel &pm = m->pm;
     const FloatNet &net = *m->fnet;
-    const Plan &pl = float_plan(m);
+    const Plan &pl = float_plan(m, stop_tensor);
     const bool merged = &pl == &net.merged;
     const uint32_t chunk = float_chunk(m);
     if (chunk == 0) return ISR_ERR_WORKSPACE;
@@ -313,6 +324,14 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
                     if (f.pair >= 0) c.in2 = tptr(f.pair);
                     else c.res = f.res >= 0 ? tptr(f.res) : nullptr;
                     c.npix = (int32_t)(bn * c.Ho * c.Wo);
+                    if (merged && f.next && net.ops[i + 1].type == OP_MAXPOOL) {
+                        const FloatOp &g = net.ops[++i];
+                        FPoolParams q = g.pool;
+                        q.out = tptr(g.out); q.B = (int32_t)bn;
+                        HIP_TRY(launch_fstem_pool(c, q, m->stream));
+                        last = &g;
+                        break;
+                    }
                     if (merged && f.next && f.out != stop_tensor && fexpand_wanted(c, net.ops[i + 1].conv)) {
                         const FloatOp &g = net.ops[++i];
                         FConvParams r = g.conv;
@@ -338,9 +357,10 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
                     break; }
                 }
                 work.push_back({last_kernel_name(), f.type == OP_CONV || f.type == OP_FC, f.flops * bn, f.bytes * bn});
-                if (last != &f) {   // the sum is not read back
+                if (last != &f) {   // what lies between the two is not read back, and stored only if it is a sum
+                    const double between = 4.0 * to.C * to.H * to.W;
                     work.back().ops += last->flops * bn;
-                    work.back().bytes += (last->bytes - 4.0 * ti.H * ti.W * to.C) * bn;
+                    work.back().bytes += (last->bytes - (last->type == OP_MAXPOOL ? 2.0 : 1.0) * between) * bn;
                 }
                 if (last->out == stop_tensor) { whole = false; break; }
             }
@@ -466,7 +486,7 @@ int isr_float_debug_noisy(isr_model *m, const uint8_t *x_device, float sigma, ui
     }
     if ((rc = run_fp_range(m, x_device, sigma, seed, image_id, phase, sample_begin, count, nullptr, nullptr, nullptr, true)) != ISR_OK) return rc;
     std::vector<float> tmp(count * hw * 4);
-    HIP_TRY(hipMemcpyAsync(tmp.data(), m->ws + float_plan(m).toff[0], tmp.size() * 4, hipMemcpyDeviceToHost, m->stream));
+    HIP_TRY(hipMemcpyAsync(tmp.data(), m->ws + float_plan(m, -1).toff[0], tmp.size() * 4, hipMemcpyDeviceToHost, m->stream));
     HIP_TRY(hipStreamSynchronize(m->stream));
     float *o = (float *)out_host;
     for (uint32_t s = 0; s < count; ++s)
@@ -509,7 +529,7 @@ int isr_float_debug_tensor(isr_model *m, const uint8_t *x_device, float sigma, u
     const TensorDesc &t = pm.tensors[tensor_id];
     const size_t hw = (size_t)t.H * t.W;
     std::vector<float> tmp(hw * t.Cp);
-    HIP_TRY(hipMemcpyAsync(tmp.data(), m->ws + float_plan(m).toff[tensor_id], tmp.size() * 4, hipMemcpyDeviceToHost, m->stream));
+    HIP_TRY(hipMemcpyAsync(tmp.data(), m->ws + float_plan(m, tensor_id).toff[tensor_id], tmp.size() * 4, hipMemcpyDeviceToHost, m->stream));
     HIP_TRY(hipStreamSynchronize(m->stream));
     for (int c = 0; c < t.C; ++c)
         for (size_t i = 0; i < hw; ++i) out_host[(size_t)c * hw + i] = tmp[i * t.Cp + c];

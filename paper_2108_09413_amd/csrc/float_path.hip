@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256) void float_noise_kernel(const FloatNoiseParams
 // 32 NT pixels, so a pixel fragment is split in registers by one wave only: 5.5 instructions an element, for MT MFMAs of
 // 32 cycles per 8 of them.
 //
-// ResNet-50 at 224 x 224, 668 copies: 58 -> 26.8 ms for all layers by these products, 96 -> 213 TFLOP/s on 128-channel tiles; 19.6 ms
+// ResNet-50 at 224 x 224, 668 copies: 58 -> 26.8 ms for all layers by these products, 96 -> 213 TFLOP/s on 128-channel tiles; 18.6 ms
 // with the fused and the 3x3 kernels below.
 // Error of the logits against binary64 (2-norm), fp32 instruction -> this kernel: tiny net 3.5e-7 -> 3.3e-7, ResNet-20
 // 2.0e-7 -> 1.55e-7, ResNet-110 3.1e-7 -> 2.4e-7, ResNet-50 at 96 to 224 pixels 8.1 .. 9.5e-7 -> 4.9 .. 5.9e-7.
@@ -261,6 +261,19 @@ __device__ __forceinline__ void fconv_finish_tile(const FConvParams &p, const v1
     } else {
         if (full) fconv_finish<true, false, PAIR>(p, acc, other, bs, px, ch0, lane);
         else fconv_finish<false, false, PAIR>(p, acc, other, bs, px, ch0, lane);
+    }
+}
+
+// of 4 floats, 4 to a pair
+__device__ __forceinline__ void split_bf16_4(const v4f &v, uint2 (&part)[3]) {
+    float x[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        part[k].x = __builtin_amdgcn_perm(__float_as_uint(x[1]), __float_as_uint(x[0]), 0x07060302u);
+        part[k].y = __builtin_amdgcn_perm(__float_as_uint(x[3]), __float_as_uint(x[2]), 0x07060302u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (k < 2) x[e] = x[e] - __uint_as_float(__float_as_uint(x[e]) & 0xFFFF0000u);   // exact
     }
 }
 
@@ -512,17 +525,10 @@ __global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
         int8_t *dst = run + rrow * 64 + (((rc >> 1) ^ swz<4>(rrow)) << 4) + (rc & 1) * 8;
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
-            float x[4] = {next[j][0], next[j][1], next[j][2], next[j][3]};
+            uint2 part[3];
+            split_bf16_4(next[j], part);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                uint2 part;
-                part.x = __builtin_amdgcn_perm(__float_as_uint(x[1]), __float_as_uint(x[0]), 0x07060302u);
-                part.y = __builtin_amdgcn_perm(__float_as_uint(x[3]), __float_as_uint(x[2]), 0x07060302u);
-                *(uint2 *)(dst + k * PLANE + j * 2048) = part;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (k < 2) x[e] = x[e] - __uint_as_float(__float_as_uint(x[e]) & 0xFFFF0000u);   // exact
-            }
+            for (int k = 0; k < 3; ++k) *(uint2 *)(dst + k * PLANE + j * 2048) = part[k];
         }
     };
     float bias_or_scale = 0.0f;
@@ -603,6 +609,127 @@ __global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     fconv_finish_tile<false>(p, acc, 0, bs, px0, ch0, wave, lane, 4);
+}
+
+// First layer (7x7, stride 2, border 3, 4 stored channels in, 64 out) with the 3x3 / 2 max pooling that alone reads it.  The layer's
+// result is four times the pooled one, and writing it and reading it back took as long as all its products should; here it
+// never leaves the registers.  A workgroup makes 4 pooled rows x 31 pooled columns: the 23 x 136 pixels that this takes are split
+// once into three planes of bfloat16 in LDS; a wave computes 32 channels of 2 pooled rows, row of the layer by row, the 32
+// even columns 2 px and the 32 odd ones 2 px - 1 of a row as one fragment each, with its weights in registers.  The right
+// neighbour of a pooled pixel is the next lane's odd column.  A fragment's operand is two pixels (16 bytes) of one kernel row, eight
+// taps of which the last has zero weights; the pairs of pixels of a row of LDS lie by parity, so that lanes, two pairs apart, read
+// neighbouring places.  Eight taps of a row are four groups of products to add instead of three and a half, and each rounds; the small
+// parts of the pixels, two thirds of the products, therefore have a sum of their own, whose roundings are too small to count.  224 x 224, the two / this one: 668 copies
+// 1272 + 581 -> 800 us, 96 copies 188 + 84 -> 124, 16 copies 44 + 16 -> 27 (42, 7 and 2 us less with one sum).  Bound by the reads of the planes (3 KB for two
+// matrix instructions a wave) and the products themselves (five rows for four).
+constexpr int FS_ROWS = 2, FS_BAND = 4, FS_COLS = 31, FS_IN = 4 * FS_BAND + 7, FS_HALF = 34, FS_PITCH = 2 * FS_HALF * 16;
+__global__ __launch_bounds__(256, 2) void fstem_pool_kernel(const FConvParams p, const int Hp, const int Wp, float *const out) {
+    constexpr int PLANE = FS_IN * FS_PITCH;
+    __shared__ __attribute__((aligned(256))) int8_t img[3 * PLANE];
+    __shared__ __attribute__((aligned(16))) float consts[128];   // bias, scale
+    static_assert(sizeof(img) + sizeof(consts) <= 80 * 1024, "two workgroups a CU");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const int bands = (Hp + FS_BAND - 1) / FS_BAND, strips = (Wp + FS_COLS - 1) / FS_COLS;
+    const int strip = blockIdx.x % strips, band = blockIdx.x / strips % bands, b = blockIdx.x / (strips * bands);
+    const int py0 = band * FS_BAND, px0 = strip * FS_COLS;
+    const float *in = p.in + (size_t)b * p.H * p.W * 4;
+
+    const int mf = wave & 1, group = wave >> 1;
+    v4i af[14];   // [kernel row][half of its eight taps]
+#pragma unroll
+    for (int s = 0; s < 14; ++s) af[s] = *(const v4i *)((const uint8_t *)p.w + ((s >> 1) * 64 + mf * 32 + l32) * 64 + (2 * (s & 1) + half) * 16);
+    if (tid < 128) consts[tid] = tid < 64 ? p.bias[tid] : p.scale[tid - 64];
+    // input pixel (4 py0 - 5 + r, 4 px0 - 5 + x) -> row r, pair x / 2; zeros outside the image
+    constexpr int PIX = FS_IN * 4 * FS_HALF, PER = (PIX + 255) / 256;
+    v4f v4[PER];
+    auto place = [&](int j, int &r, int &x) {
+        const int i = tid + 256 * j;
+        r = i / (4 * FS_HALF);
+        x = i % (4 * FS_HALF);
+        return i < PIX;
+    };
+    auto inside = [&](int r, int x) { return (unsigned)(4 * py0 - 5 + r) < (unsigned)p.H && (unsigned)(4 * px0 - 5 + x) < (unsigned)p.W; };
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {   // all on their way before the first is waited for
+        int r, x;
+        place(j, r, x);
+        v4[j] = *(const v4f *)(in + (inside(r, x) ? (4 * py0 - 5 + r) * p.W + 4 * px0 - 5 + x : 0) * 4);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        int r, x;
+        if (!place(j, r, x)) break;
+        const bool ok = inside(r, x);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v4[j][e] = ok ? v4[j][e] : 0.0f;
+        uint2 part[3];
+        split_bf16_4(v4[j], part);
+        const int q = x >> 1;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) *(uint2 *)(img + k * PLANE + r * FS_PITCH + ((q & 1) * FS_HALF + (q >> 1)) * 16 + (x & 1) * 8) = part[k];
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+
+    const int py = py0 + group * FS_ROWS, px = px0 + l32;
+    if (py >= Hp) return;
+    // pairs of the odd column: 2 l + 2 ks + half, of the even one: one further
+    const int8_t *odd = img + 4 * group * FS_ROWS * FS_PITCH + (half * FS_HALF + l32) * 16;
+    const int8_t *even = img + 4 * group * FS_ROWS * FS_PITCH + (half ? l32 + 1 : FS_HALF + l32) * 16;
+    const bool odd_ok = 2 * px - 1 >= 0 && 2 * px - 1 < p.Wo, store = l32 < FS_COLS && px < Wp;
+    const int c0 = mf * 32 + 16 * half;
+    const float lo = p.relu ? 0.0f : -INFINITY;
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 2 * FS_ROWS + 1; ++i) {
+        const int cy = 2 * py - 1 + i;
+        float h[16];
+        if ((unsigned)cy < (unsigned)p.Ho) {
+            v16f ae, ao, se, so;   // sums of the leading parts, of the two small ones
+#pragma unroll
+            for (int e = 0; e < 16; ++e) ae[e] = ao[e] = se[e] = so[e] = 0.0f;
+#pragma unroll
+            for (int s = 0; s < 14; ++s) {
+                const int at = (2 * i + (s >> 1)) * FS_PITCH + (s & 1) * 16;
+#pragma unroll
+                for (int k = 2; k >= 0; --k) {
+                    const v4i xe = *(const v4i *)(even + k * PLANE + at), xo = *(const v4i *)(odd + k * PLANE + at);
+                    v16f &e = k ? se : ae, &o = k ? so : ao;
+                    e = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, af[s]), __builtin_bit_cast(v8bf, xe), e, 0, 0, 0);
+                    o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, af[s]), __builtin_bit_cast(v8bf, xo), o, 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const v4f bias = *(const v4f *)(consts + c0 + 4 * g), scale = *(const v4f *)(consts + 64 + c0 + 4 * g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float te = fmaxf(((ae[4 * g + e] + se[4 * g + e]) + bias[e]) * scale[e], lo);
+                    const float to = odd_ok ? fmaxf(((ao[4 * g + e] + so[4 * g + e]) + bias[e]) * scale[e], lo) : -INFINITY;
+                    // wave_shl:1 reads the next lane (the last one, which has none, makes no pixel)
+                    const float right = __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(to), 0x130, 0xf, 0xf, true));
+                    h[4 * g + e] = fmaxf(fmaxf(te, to), right);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) h[e] = -INFINITY;
+        }
+        // pooled row j takes rows 2 j, 2 j + 1, 2 j + 2 of these
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = i == 0 ? h[e] : fmaxf(v[e], h[e]);
+        if (i > 0 && (i & 1) == 0) {
+            const int y = py + i / 2 - 1;
+            if (store && y < Hp)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) *(v4f *)(out + (((size_t)b * Hp + y) * Wp + px) * 64 + c0 + 4 * g) = v4f{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = h[e];
+        }
+    }
 }
 
 // A closing 1x1 layer with its residual add, and the 1x1 layer that reads the sum, in one kernel.  Both are bound by memory, by
@@ -1063,6 +1190,20 @@ hipError_t launch_fexpand(const FConvParams &e, const FConvParams &r, hipStream_
     if (r.Cout_p == 64) return launch_fexpand_tile<2, 4, false>(p, st);
     if (r.Cout_p == 128) return launch_fexpand_tile<4, 4, false>(p, st);
     return launch_fexpand_tile<8, 8, false>(p, st);
+}
+
+bool fstem_pool_supported(const FConvParams &p, const FPoolParams &q) {
+    return p.k == 7 && p.stride == 2 && p.pad == 3 && p.Cin_p == 4 && p.Cout_p == 64 && p.Cout_pp == 64 && q.k == 3 && q.stride == 2 && q.pad == 1 && q.Cp == 64 &&
+           q.H == p.Ho && q.W == p.Wo && p.Ho == (p.H - 1) / 2 + 1 && p.Wo == (p.W - 1) / 2 + 1 && q.Ho == (q.H - 1) / 2 + 1 && q.Wo == (q.W - 1) / 2 + 1;
+}
+
+hipError_t launch_fstem_pool(const FConvParams &p, const FPoolParams &q, hipStream_t st) {
+    if (!fstem_pool_supported(p, q) || !p.in || !q.out || p.res || p.in2 || q.B <= 0) return hipErrorInvalidValue;
+    const long blocks = (long)((q.Ho + FS_BAND - 1) / FS_BAND) * ((q.Wo + FS_COLS - 1) / FS_COLS) * q.B;
+    if (blocks > 0x7FFFFFFFL) return hipErrorInvalidValue;
+    set_kernel_name("fstem_pool_kernel");
+    hipLaunchKernelGGL(fstem_pool_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p, q.Ho, q.Wo, q.out);
+    return hipGetLastError();
 }
 
 hipError_t launch_fadd(const FAddParams &p, hipStream_t st) {

@@ -399,6 +399,8 @@ bool fconv_pair_supported(const FConvParams &p, const FConvParams &q);   // q's 
 bool fexpand_supported(const FConvParams &p, const FConvParams &q);      // p with its add, and q that reads the sum, in one kernel ...
 bool fexpand_wanted(const FConvParams &p, const FConvParams &q);         // ... for this number of pixels
 hipError_t launch_fexpand(const FConvParams &p, const FConvParams &q, hipStream_t st);
+bool fstem_pool_supported(const FConvParams &p, const FPoolParams &q);   // p and the pooling q of its result in one kernel
+hipError_t launch_fstem_pool(const FConvParams &p, const FPoolParams &q, hipStream_t st);   // p.out and q.in are not used
 int fconv_tile_m(int cout_p);   // channels per output tile chosen for a layer (Cout_pp is a multiple of it)
 hipError_t launch_fadd(const FAddParams &p, hipStream_t st);
 hipError_t launch_fmaxpool(const FPoolParams &p, hipStream_t st);

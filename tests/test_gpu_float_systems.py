@@ -291,6 +291,39 @@ def test_floatrs_fp_3x3_layers_from_one_run_of_pixels(isr, h, w, copies):
     m.close()
 
 
+@pytest.mark.parametrize("h,w,copies", [(224, 224, 2), (64, 64, 5), (37, 28, 3), (30, 44, 3), (9, 8, 4), (150, 124, 2), (17, 128, 2), (3, 4, 2), (33, 252, 2)])
+def test_floatrs_fp_first_layer_with_its_pooling(isr, h, w, copies):
+    """7x7 / 2 layer into 64 channels and 3x3 / 2 pooling in one kernel: bands and strips that end inside the image and beside it, odd
+    sizes, images smaller than a window; the pooled tensor and the layer's own (which the kernel does not store) against the oracle."""
+    _say(f"FloatRS-fp first layer with pooling {h} x {w}, {copies} copies")
+    from synth.models import NetBuilder
+    b = NetBuilder(rng=np.random.default_rng(87), in_shape=(3, h, w), num_classes=6)
+    c = b.conv(b.tensor(3, h, w, 0, 74.0), 64, 7, 2, 3, w != 44)
+    t = b.maxpool(c, 3, 2, 1)
+    u = b.conv(t, 64, 1, 1, 0, True)
+    b.fc(b.gap(u), 6)
+    blob = b.blob()
+    m = _load(isr, blob, 4 * copies)
+    om = oracle.Model(blob)
+    x = np.random.default_rng(5).integers(0, 256, size=(3, h, w)).astype(np.uint8)
+    isr.isr_profile(m, 1)
+    lg, am, cnt = isr.isr_float_debug_forward(m, x, 63.75, 3, 1, 1, 50, copies, FP)
+    assert any(k["name"] == "fstem_pool_kernel" for k in isr.isr_profile_read(m))
+    wl = om.mc_float(x, 63.75, 3, 1, 1, 50, copies, FP)[0]
+    _check_fp_logits(lg, wl, am)
+    _, want = om.forward_float(oracle.noisy_float(x, 63.75, 3, 1, 1, 50))
+    got = [isr.isr_float_debug_tensor(m, x, 63.75, 3, 1, 1, 50, tid, om.tensor_shape(tid)[:3]) for tid in (c, t)]
+    for tid, g in zip((c, t), got):
+        assert np.all(np.abs(g.astype(np.float64) - want[tid]) <= REL * np.abs(want[tid]).max()), tid
+    rows, cols = got[1].shape[1:]
+    padded = np.full((64, 2 * rows + 1, 2 * cols + 1), -np.inf, np.float32)
+    padded[:, 1:got[0].shape[1] + 1, 1:got[0].shape[2] + 1] = got[0]
+    pooled = np.max([padded[:, i:i + 2 * rows:2, j:j + 2 * cols:2] for i in range(3) for j in range(3)], axis=0)
+    # the layer's own kernel adds the same products in another order: a few roundings of the largest sum
+    assert np.abs(pooled - got[1]).max() <= 2.0 ** -20 * np.abs(pooled).max()
+    m.close()
+
+
 # 2-norm error of the logits that one rounding per product gives (the fp32 matrix instruction, a chain of fused
 # multiply-adds), measured over 768 copies: 2.0e-7 and 3.1e-7.  The kernel rounds less often (1.55e-7 and 2.5e-7); the bounds
 # are the chain's error plus 15 % for the spread of 24 copies.  Sums that all err to the same side, as the matrix unit's do
