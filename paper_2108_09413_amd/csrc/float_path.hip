@@ -170,7 +170,8 @@ __global__ __launch_bounds__(256) void float_noise_kernel(const FloatNoiseParams
 // ResNet-50 at 224 x 224, 668 copies: 58 -> 26.8 ms for all layers by these products, 96 -> 213 TFLOP/s on 128-channel tiles; 18.6 ms
 // with the fused and the 3x3 kernels below.
 // Error of the logits against binary64 (2-norm), fp32 instruction -> this kernel: tiny net 3.5e-7 -> 3.3e-7, ResNet-20
-// 2.0e-7 -> 1.55e-7, ResNet-110 3.1e-7 -> 2.4e-7, ResNet-50 at 96 to 224 pixels 8.1 .. 9.5e-7 -> 4.9 .. 5.9e-7.
+// 2.0e-7 -> 1.55e-7, ResNet-110 3.1e-7 -> 2.5e-7, ResNet-50 at 96 to 224 pixels 8.1 .. 9.5e-7 -> 4.9 .. 5.8e-7; with the sums that
+// fpatch_kernel and fstem_pool_kernel keep apart 3.3e-7, 1.3e-7, 2.2e-7 and 4.8 .. 5.3e-7.
 //
 // FLAT: 1x1 stride-1 layers; else TABLE: K chunks of 4 channels looked up in ktab (a tap changes inside a step), else a
 // step lies inside one tap (Cin a multiple of 32) and its tap is counted along, all taps of 32 channels before the next 32.  PAIR: a 1x1 layer of any stride whose residual is
@@ -480,8 +481,10 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
 // operands; tap by tap through fconv_kernel every pixel was fetched and split nine times, 44 instructions for 3 MT matrix instructions,
 // which left the matrix unit idle for half of the time.  Taps outside the image read a row of zeros.  The weights
 // of a tap come through three stages, two steps ahead; the next channels of the run are fetched into registers during the second to
-// ninth tap.  Products are added in the order of fconv_kernel.  668 copies of ResNet-50's layers of 64 channels at
-// 56 x 56, 128 at 28 x 28, 256 at 14 x 14, 512 at 7 x 7, tap by tap -> from the run: 600 -> 450, 464 -> 372, 410 -> 333, 387 -> 320 us
+// ninth tap.  Products are added in the order of fconv_kernel.  Where registers allow (maps of at most 31 pixels a row), the two small
+// parts of the pixels have a sum of their own, whose roundings are too small to count: 12 us of 333 at 14 x 14 for up to a fifth
+// of the error of the logits.  668 copies of ResNet-50's layers of 64 channels at
+// 56 x 56, 128 at 28 x 28, 256 at 14 x 14, 512 at 7 x 7, tap by tap -> from the run: 600 -> 450, 464 -> 374, 410 -> 345, 387 -> 331 us
 // (0.21 ms at the nominal rate of the matrix unit); 16 copies at 56 x 56: 27 -> 21 us.
 template <int MT, int NL>   // NL: rows of 32 pixels of the run, 130 + 2 W <= 32 NL
 __global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
@@ -540,11 +543,15 @@ __global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
     const int P = px0 + wave * 32 + l32, n = P < p.npix ? P : p.npix - 1;
     const int x = n % p.W, y = n / p.W % p.H;
     const int centre = wave * 32 + l32 + p.W + 1;
-    v16f acc[MT][1];
+    constexpr bool TWO = NL <= 6;
+    v16f acc[MT][1], small[TWO ? MT : 1];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][0][e] = 0.0f;
+        for (int e = 0; e < 16; ++e) {
+            acc[i][0][e] = 0.0f;
+            if (TWO) small[TWO ? i : 0][e] = 0.0f;
+        }
 
     store();
     weights();
@@ -589,8 +596,10 @@ __global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
 #pragma unroll
                 for (int k = 2; k >= 0; --k)
 #pragma unroll
-                    for (int i = 0; i < MT; ++i)
-                        acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, af[i]), __builtin_bit_cast(v8bf, part[k]), acc[i][0], 0, 0, 0);
+                    for (int i = 0; i < MT; ++i) {
+                        v16f &sum = TWO && k ? small[TWO ? i : 0] : acc[i][0];
+                        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, af[i]), __builtin_bit_cast(v8bf, part[k]), sum, 0, 0, 0);
+                    }
             }
             buf = buf == NST - 1 ? 0 : buf + 1;
         }
@@ -602,6 +611,9 @@ __global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
     };
     for (int blk = 0; blk + 1 < nblk; ++blk) block(blk, std::true_type{});
     block(nblk - 1, std::false_type{});
+    if constexpr (TWO)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[i][0] += small[i];
     __builtin_amdgcn_s_barrier();
     float *bs = (float *)wt;
     if (tid < 2 * BM) bs[tid] = bias_or_scale;

@@ -325,7 +325,7 @@ def test_floatrs_fp_first_layer_with_its_pooling(isr, h, w, copies):
 
 
 # 2-norm error of the logits that one rounding per product gives (the fp32 matrix instruction, a chain of fused
-# multiply-adds), measured over 768 copies: 2.0e-7 and 3.1e-7.  The kernel rounds less often (1.55e-7 and 2.5e-7); the bounds
+# multiply-adds), measured over 768 copies: 2.0e-7 and 3.1e-7.  The kernels round less often (1.3e-7 and 2.2e-7); the bounds
 # are the chain's error plus 15 % for the spread of 24 copies.  Sums that all err to the same side, as the matrix unit's do
 # by themselves, add up over the blocks of the deep net: 5.3e-7.
 @pytest.mark.parametrize("cfg,bound", [(1, 2.3e-7), (2, 3.6e-7)])
