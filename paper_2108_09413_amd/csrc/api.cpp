@@ -319,6 +319,30 @@ int run_slots(isr_model *m, const Plan &pl, const Draw &draw, int32_t *logits_ho
             }
             return ISR_OK;
         };
+        auto narrow_params = [&](const DevOp &d, uint32_t j0, uint32_t bn) {
+            NarrowParams np = d.np;
+            np.in = (const int8_t *)tptr(d.a, j0);
+            np.out = d.head ? nullptr : (int8_t *)tptr(d.out, j0);
+            np.B = (int32_t)bn;
+            np.fused_noise = d.noise_fused && m->quant_sigma < 0.f;
+            if (np.fused_noise) np.noise = noise_source(j0);
+            if (d.head) {
+                np.logits = logits_host ? (int32_t *)(ws + pl.logits_off) + (size_t)j0 * pm.classes : nullptr;
+                np.argmax = argmax_host ? (int32_t *)(ws + pl.argmax_off) + j0 : nullptr;
+                np.counts = dcounts;
+                np.slots = slots_at(j0);
+            }
+            return np;
+        };
+        // copies [j0, j0 + bn) of the chunk through the three stages of a net on 32x32 images, one launch
+        auto run_chain = [&](const DevOp *d, uint32_t j0, uint32_t bn) -> int {
+            if ((prc = mark()) != ISR_OK) return prc;
+            HIP_TRY(launch_narrow_chain(narrow_params(d[0], j0, bn), narrow_params(d[1], j0, bn), narrow_params(d[2], j0, bn), m->stream));
+            if (timed)
+                ev_work.push_back({last_kernel_name(), 1, (d[0].ops_per_sample + d[1].ops_per_sample + d[2].ops_per_sample) * bn,
+                                   (d[0].bytes_per_sample + d[1].bytes_per_sample + d[2].bytes_per_sample) * bn});
+            return ISR_OK;
+        };
         // copies [j0, j0 + bn) of the chunk through one op of the plan
         auto run_op = [&](const DevOp &d, uint32_t j0, uint32_t bn) -> int {
             if ((prc = mark()) != ISR_OK) return prc;
@@ -350,19 +374,7 @@ int run_slots(isr_model *m, const Plan &pl, const Draw &draw, int32_t *logits_ho
                     break;
                 }
                 if (d.narrow) {
-                    NarrowParams np = d.np;
-                    np.in = (const int8_t *)tptr(d.a, j0);
-                    np.out = d.head ? nullptr : (int8_t *)tptr(d.out, j0);
-                    np.B = (int32_t)bn;
-                    np.fused_noise = d.noise_fused && m->quant_sigma < 0.f;
-                    if (np.fused_noise) np.noise = noise_source(j0);
-                    if (d.head) {
-                        np.logits = logits_host ? (int32_t *)(ws + pl.logits_off) + (size_t)j0 * pm.classes : nullptr;
-                        np.argmax = argmax_host ? (int32_t *)(ws + pl.argmax_off) + j0 : nullptr;
-                        np.counts = dcounts;
-                        np.slots = slots_at(j0);
-                    }
-                    HIP_TRY(launch_narrow(np, d.narrow, m->stream));
+                    HIP_TRY(launch_narrow(narrow_params(d, j0, bn), d.narrow, m->stream));
                     break;
                 }
                 if (d.bneck) {
@@ -489,8 +501,13 @@ int run_slots(isr_model *m, const Plan &pl, const Draw &draw, int32_t *logits_ho
             for (uint32_t j0 = 0; j0 < cnt; j0 += sub) {
                 const uint32_t bn = std::min(sub, cnt - j0);
                 if (!noise_done && !own_noise && (prc = run_noise(j0, bn)) != ISR_OK) return prc;
-                for (size_t i = op0; i < op1; ++i)
-                    if ((prc = run_op(pl.ops[i], j0, bn)) != ISR_OK) return prc;
+                for (size_t i = op0; i < op1; ++i) {
+                    const DevOp *d = &pl.ops[i];
+                    const bool chain = op1 - i >= 3 && d[0].narrow == 16 && d[1].narrow == 32 && d[2].narrow == 64 && d[0].np.tail == 1 && d[1].np.tail == 1 &&
+                                       d[1].a == d[0].out && d[2].a == d[1].out && narrow_chain_wanted((int)bn);
+                    if ((prc = chain ? run_chain(d, j0, bn) : run_op(*d, j0, bn)) != ISR_OK) return prc;
+                    if (chain) i += 2;
+                }
             }
             noise_done = true;
             op0 = op1;

@@ -425,6 +425,8 @@ bool stem_pool_supported(int k, int stride, int pad, int cout_p, int H, int W, i
 hipError_t launch_stem16(const Stem16Params &p, hipStream_t st);
 bool stem16_supported(int k, int stride, int pad, int cout_p, int H, int W, int fast_requant);
 hipError_t launch_narrow(const NarrowParams &p, int channels, hipStream_t st);   // narrow_net.hip
+bool narrow_chain_wanted(int copies);   // all three stages in one launch
+hipError_t launch_narrow_chain(const NarrowParams &s16, const NarrowParams &s32, const NarrowParams &s64, hipStream_t st);
 bool basic_block_supported(int channels, int size);
 hipError_t launch_bottleneck(const BneckParams &p, hipStream_t st);
 bool bottleneck_supported(int cin_p, int cmid_p, int cout_p, int tail);

@@ -1,4 +1,4 @@
-// The nets on 32 x 32 images (stages of 16 channels at 32 x 32, 32 at 16 x 16, 64 at 8 x 8 pixels), one launch per stage:
+// The nets on 32 x 32 images (stages of 16 channels at 32 x 32, 32 at 16 x 16, 64 at 8 x 8 pixels), one launch per stage (of few copies one for all):
 //   [first layer: noise draws + 3x3 convolution into 16 channels]   stage 16 only; else the stage's input is loaded
 //   identity blocks  t = conv3x3(x), x = add(conv3x3(t), x)         any number
 //   [down-sampling block into the next stage, or its first convolution alone]
@@ -24,7 +24,7 @@
 // with pairs of fragments measured 1.81 / 1.40 / 1.11 ms for the stages of a 110-layer net on 16 700 images, three without
 // 1.88 / 1.45 / 1.23 ms).  With one workgroup on a CU there is nothing to overlap with: descriptors, weights and constants of
 // a convolution are fetched while the one before runs, and 16 channels take eight waves (predictions with 100 copies: ResNet-20
-// 52.3 -> 50.0 us, ResNet-110 171 -> 153, the two-convolution net 24.5 -> 23.8).  More images per workgroup amortise the weight and constant loads of a convolution at 32 and 64
+// 52.3 -> 50.0 us, ResNet-110 171 -> 153, the two-convolution net 24.5 -> 23.8; before the stages shared a launch and the host watched for the tallies).  More images per workgroup amortise the weight and constant loads of a convolution at 32 and 64
 // channels, where a wave has one or two fragments per image.  The certification of the 110-layer net at 100 000 samples took
 // 43.3 ms with one launch per block, 31.6 with one per stage, 27.0 with the overlap.
 #include <cstddef>
@@ -368,7 +368,7 @@ struct Block {
 };
 
 template <int C, int S, int NI, int NW>
-__global__ __launch_bounds__(64 * NW, C == 16 ? 4 : 2) void narrow_kernel(const NarrowParams p) {
+__device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
     constexpr int NT = 64 * NW;                      // threads
     constexpr int P = S + 2, CH = C / 16, C2 = 2 * C, S2 = S / 2;
     constexpr int TB = tile_bytes<C, S>();
@@ -747,6 +747,21 @@ __global__ __launch_bounds__(64 * NW, C == 16 ? 4 : 2) void narrow_kernel(const 
 }
 
 template <int C, int S, int NI, int NW>
+__global__ __launch_bounds__(64 * NW, C == 16 ? 4 : 2) void narrow_kernel(const NarrowParams p) { narrow_stage<C, S, NI, NW>(p); }
+
+// The three stages of a net in one launch (narrow_chain_wanted): a workgroup reads back only what it has written, so that nothing but
+// its barrier orders the stages.  The waves that the later ones do not take end early.
+struct NarrowChain { NarrowParams stage[3]; };
+__global__ __launch_bounds__(512, 2) void narrow_chain_kernel(const NarrowChain c) {
+    narrow_stage<16, 32, 1, 8>(c.stage[0]);
+    __syncthreads();   // the stage's result is stored
+    if (threadIdx.x >= 256) return;
+    narrow_stage<32, 16, 1, 4>(c.stage[1]);
+    __syncthreads();
+    narrow_stage<64, 8, 1, 4>(c.stage[2]);
+}
+
+template <int C, int S, int NI, int NW>
 hipError_t launch_stage(const NarrowParams &p, hipStream_t st) {
     static const std::string name = "narrow_kernel<" + std::to_string(C) + ", " + std::to_string(S) + ", " + std::to_string(NI) + (NW == 4 ? "" : ", " + std::to_string(NW) + " waves") + ">";
     set_kernel_name(name.c_str());
@@ -763,21 +778,26 @@ bool basic_block_supported(int channels, int size) {
 }
 bool trans_block_supported(int cout, int size_out) { return (cout == 32 && size_out == 16) || (cout == 64 && size_out == 8); }
 
-hipError_t launch_narrow(const NarrowParams &p, int channels, hipStream_t st) {
-    if (p.B <= 0) return hipSuccess;
+static bool narrow_valid(const NarrowParams &p, int channels) {
     const bool from_image = channels == 16 && p.stem;
     if ((p.nblocks > 0 && !p.blocks) || p.nblocks < 0 || (p.nblocks == 0 && !p.tail && !from_image) || (!p.head && !p.out) ||
         (from_image ? !p.w0 || !p.prm0 || (!p.fused_noise && !p.in) : !p.in || p.stem))
-        return hipErrorInvalidValue;
+        return false;
     if (p.fused_noise) {
         const NoiseSource &ns = p.noise;
-        if (!from_image || !ns.x || !ns.table || ns.C < 1 || ns.C > 3 || ns.H != 32 || ns.W != 32 || !valid_slots(ns.slots)) return hipErrorInvalidValue;
+        if (!from_image || !ns.x || !ns.table || ns.C < 1 || ns.C > 3 || ns.H != 32 || ns.W != 32 || !valid_slots(ns.slots)) return false;
     }
-    if (p.tail && (channels == 64 || !p.tw1 || !p.tprm || (p.tail == 1 && (!p.tw2 || !p.twp)) || p.tail > 2)) return hipErrorInvalidValue;
+    if (p.tail && (channels == 64 || !p.tw1 || !p.tprm || (p.tail == 1 && (!p.tw2 || !p.twp)) || p.tail > 2)) return false;
     if (p.head && (!(channels == 64 || (channels == 16 && p.tail == 2)) || (p.tail && channels == 64) || !p.fc_w || !p.fc_bias || p.classes < 1 ||
                    p.classes_p < p.classes || (channels == 64 && p.nblocks == 0)))
-        return hipErrorInvalidValue;
-    if (p.head && p.counts && !valid_slots(p.slots)) return hipErrorInvalidValue;
+        return false;
+    if (p.head && p.counts && !valid_slots(p.slots)) return false;
+    return true;
+}
+
+hipError_t launch_narrow(const NarrowParams &p, int channels, hipStream_t st) {
+    if (p.B <= 0) return hipSuccess;
+    if (!narrow_valid(p, channels)) return hipErrorInvalidValue;
     // Images per workgroup: one while there is a CU for each; two while all workgroups run at once (two per CU); beyond, as many
     // as fit, to share the weights.  A second image in a workgroup costs about what a second workgroup on its CU costs with
     // 32 channels, and less with 64: us of the two stages of ResNet-20 with one / two / most images a workgroup
@@ -792,6 +812,21 @@ hipError_t launch_narrow(const NarrowParams &p, int channels, hipStream_t st) {
     if (channels == 32) return one ? launch_stage<32, 16, 1, 4>(p, st) : two ? launch_stage<32, 16, 2, 4>(p, st) : launch_stage<32, 16, 3, 4>(p, st);
     if (channels == 64) return one ? launch_stage<64, 8, 1, 4>(p, st) : two ? launch_stage<64, 8, 2, 4>(p, st) : launch_stage<64, 8, 6, 4>(p, st);
     return hipErrorInvalidValue;
+}
+
+// All stages in one launch while every image has a CU for itself: predictions with 100 copies 45.8 -> 42.6 us (ResNet-20), 148 -> 145
+// (ResNet-110), with 250 47.6 -> 44.0.  The kernel takes the registers of the widest stage, one workgroup a CU: a 257th image
+// would wait for a whole round, where three launches share the CUs (300 copies 60 us).
+bool narrow_chain_wanted(int copies) { return copies <= 256; }
+
+hipError_t launch_narrow_chain(const NarrowParams &s16, const NarrowParams &s32, const NarrowParams &s64, hipStream_t st) {
+    if (s16.B <= 0) return hipSuccess;
+    if (!narrow_valid(s16, 16) || !narrow_valid(s32, 32) || !narrow_valid(s64, 64) || s16.B != s32.B || s16.B != s64.B || s16.tail != 1 || s32.tail != 1 || s16.head ||
+        s16.out != s32.in || s32.out != s64.in)
+        return hipErrorInvalidValue;
+    set_kernel_name("narrow_chain_kernel");
+    hipLaunchKernelGGL(narrow_chain_kernel, dim3((unsigned)s16.B), dim3(512), 0, st, NarrowChain{{s16, s32, s64}});
+    return hipGetLastError();
 }
 
 }  // namespace isr

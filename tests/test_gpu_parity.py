@@ -416,6 +416,39 @@ def test_noise_of_few_copies_is_drawn_by_channel(isr, channels):
     m.close()
 
 
+@pytest.mark.parametrize("copies", [1, 256, 257])
+@pytest.mark.parametrize("blocks", [(0, 0, 0), (1, 0, 2), (0, 3, 1), (2, 1, 0)])
+def test_three_stages_of_few_copies_in_one_launch(isr, blocks, copies):
+    """Nets on 32x32 images whose stages run in one launch up to 256 copies and in three beyond, with no and several identity blocks a
+    stage: logits against the oracle, all copies against the op-by-op kernels, and which launch it was."""
+    _say(f"narrow stages of {blocks} blocks, {copies} copies")
+    b = NetBuilder(rng=np.random.default_rng(93), in_shape=(3, 32, 32), num_classes=7)
+    t = b.conv(b.tensor(3, 32, 32, 0, 74.0), 16, 3, 1, 1, True)
+    for ch, n in zip((16, 32, 64), blocks):
+        if ch > 16:
+            u = b.conv(b.conv(t, ch, 3, 2, 1, True), ch, 3, 1, 1, False)
+            t = b.add(b.conv(t, ch, 1, 2, 0, False), u, True)
+        for i in range(n):
+            t = b.add(t, b.conv(b.conv(t, ch, 3, 1, 1, True), ch, 3, 1, 1, False), True, zp_out=-128 + 30 * i)
+    b.fc(b.gap(t), 7)
+    blob = b.blob()
+    om = oracle.Model(blob)
+    x = np.random.default_rng(13).integers(0, 256, size=(3, 32, 32)).astype(np.uint8)
+    n = min(copies, 4)
+    olg, oam, _ = om.mc(x, 64, 2, 1, 1, 100, n)
+    m = _load(isr, blob, 300)
+    isr.isr_profile(m, 1)
+    lg, am, cnt = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 100, copies)
+    names = [k["name"] for k in isr.isr_profile_read(m)]
+    whole = blocks[2] > 0          # without blocks the last stage has no kernel of its own
+    assert ("narrow_chain_kernel" in names) == (whole and copies <= 256), names
+    assert np.array_equal(lg[:n], olg) and np.array_equal(am[:n], oam)
+    isr.isr_set_fusion(m, 0)
+    plain = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 100, copies)
+    assert np.array_equal(lg, plain[0]) and np.array_equal(am, plain[1]) and np.array_equal(cnt, plain[2])
+    m.close()
+
+
 @pytest.mark.parametrize("first", ["16 channels", "7x7 and pooling", "noise launch"])
 def test_both_phases_of_a_certification_in_one_list(isr, first):
     """Chunks and launches that end inside either phase and inside a pair: tallies against those of the phases alone, for first
