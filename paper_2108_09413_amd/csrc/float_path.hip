@@ -77,12 +77,22 @@ __device__ __forceinline__ void cos_sin_turn24(uint32_t t, float &co, float &si)
     si = __uint_as_float(__float_as_uint(quarter ? p : q) ^ ((t << 8) & 0x80000000u));
 }
 
+// The correctly rounded root of x >= 0 (0, or far from the ends of the range).  The root instruction is off by at most one unit u, in a
+// sixth of the draws.  The root lies below the middle of s - u and s where x < (s - u/2)^2 = s (s - u) + u^2/4; x - s (s - u) is a
+// multiple of u^2, so that is where it is not positive, and one fused multiply-add has its sign.  The same above s.  Checked
+// against the binary64 root for all 2^24 arguments of the sampler; with that root, rounded once more, a certification of ResNet-20 on
+// rounded noise (10 100 copies) took 606.6 us, now 600.9.
+__device__ __forceinline__ float sqrt_rn(float x) {
+    const float s = __builtin_amdgcn_sqrtf(x);
+    const float below = __uint_as_float(__float_as_uint(s) - 1u), above = __uint_as_float(__float_as_uint(s) + 1u);   // of 0: NaN, which is neither
+    const float r = __builtin_fmaf(-below, s, x) <= 0.0f ? below : s;
+    return __builtin_fmaf(-above, s, x) > 0.0f ? above : r;
+}
+
 __device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float &za, float &zb) {
 #pragma clang fp contract(off)
     const float l = neg_log_u24((wa >> 8) + 1u);
-    // the correctly rounded binary32 root: the binary64 root rounded once more (53 >= 2 * 24 + 2 bits make the
-    // second rounding harmless); the fast binary32 root instruction alone is off by one unit in a sixth of the draws
-    const float r = (float)sqrt((double)(2.0f * l));
+    const float r = sqrt_rn(2.0f * l);
     float c, s;
     cos_sin_turn24(wb >> 8, c, s);
     za = r * c;
