@@ -209,7 +209,7 @@ struct Stem16Params {
     int32_t H, W, B, zp_in, lo, tie_free;
 };
 
-// The nets on 32 x 32 images with 16 / 32 / 64 channels at 32 / 16 / 8 pixels, one launch per stage (narrow_net.hip).
+// The nets on 32 x 32 images with 16 / 32 / 64 channels at 32 / 16 / 8 pixels, one launch per stage, or of few copies one for all (narrow_net.hip).
 // Per-channel constants come packed, int32 [4][C]: bias, M0, chi, shift-1 (top form: addend and multiplier, see rq_chi).
 struct NarrowBlock {         // identity residual block, stored in device memory
     const int8_t *w1, *w2;   // [>= C][Kp] each, K = (tap, channel), Kp = 9 C rounded up to 64

@@ -27,7 +27,7 @@ BENCH_STATS = "python bench.py --steps 2 --warmup 1 --no-cpu-baseline --no-other
 BENCH_PMC = ("python bench.py --steps 1 --warmup 0 --n 1236 --no-cpu-baseline --no-other-configs --no-comparison-systems "
              "--profile-every 0")
 BENCH_FP = "python bench.py --system fp --steps 1"
-MODES = {"0": "head", "1": "block", "2": "block + projection", "3": "block + next"}
+MODES = {"0": "head", "1": "block", "2": "block + projection", "3": "block + next", "4": "block"}
 
 
 def sources_sha256() -> str:
@@ -70,9 +70,15 @@ def library_name(profiler_name: str) -> str:
     if m:
         mt, nt, wm, wn = map(int, m.groups())
         return "fconv_kernel<%d x %d>" % (32 * mt * wm, 32 * nt * wn)
-    m = re.match(r"fconv_kernel<(\d), (\d), \d>", n)
+    m = re.match(r"fconv_kernel<(\d), (\d), (\d)>", n)
     if m:
-        return "fconv_kernel<%d x %d>" % (32 * int(m.group(1)), 128 * int(m.group(2)))
+        return "fconv_kernel<%d x %d%s>" % (32 * int(m.group(1)), 128 * int(m.group(2)), ", pair" if m.group(3) == "3" else "")
+    m = re.match(r"fexpand_kernel<(\d), \d, (true|false)>", n)
+    if m:
+        return "fexpand_kernel<%d%s>" % (32 * int(m.group(1)), ", pair" if m.group(2) == "true" else "")
+    m = re.match(r"fpatch_kernel<(\d), \d>", n)
+    if m:
+        return "fpatch_kernel<%d>" % (32 * int(m.group(1)))
     n = re.sub(r"^stem_pool_kernel<\d>$", "stem_pool_kernel", n)
     if n == "stem_pool_kernel":
         return "stem_pool_kernel (+noise)"      # the default plan of the 224 x 224 workload draws the noise in this kernel
@@ -80,7 +86,8 @@ def library_name(profiler_name: str) -> str:
 
 
 def is_conv(name: str) -> bool:
-    return name.startswith(("conv_dma_kernel", "conv_patch_kernel", "expand_reduce_kernel", "proj_expand_reduce_kernel", "bottleneck_kernel", "stem_pool_kernel", "fconv_kernel"))
+    return name.startswith(("conv_dma_kernel", "conv_patch_kernel", "expand_reduce_kernel", "proj_expand_reduce_kernel", "bottleneck_kernel", "stem_pool_kernel", "fconv_kernel",
+                            "fexpand_kernel", "fpatch_kernel", "fstem_pool_kernel"))
 
 
 def last_json(path):

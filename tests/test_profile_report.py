@@ -33,6 +33,17 @@ def test_profiler_names_map_to_the_librarys_instance_names():
     assert profile_report.is_conv("fconv_kernel<64 x 128>") and not profile_report.is_conv("gap_kernel")
 
 
+def test_profiler_names_of_the_fused_fp32_kernels():
+    f = profile_report.library_name
+    assert f("void isr::(anonymous namespace)::fconv_kernel<4, 2, 1>(isr::FConvParams)") == "fconv_kernel<128 x 256>"
+    assert f("void isr::(anonymous namespace)::fconv_kernel<4, 1, 3>(isr::FConvParams)") == "fconv_kernel<128 x 128, pair>"
+    assert f("void isr::(anonymous namespace)::fexpand_kernel<2, 4, false>(isr::(anonymous namespace)::FExpandParams)") == "fexpand_kernel<64>"
+    assert f("void isr::(anonymous namespace)::fexpand_kernel<4, 4, true>(isr::(anonymous namespace)::FExpandParams)") == "fexpand_kernel<128, pair>"
+    assert f("void isr::(anonymous namespace)::fpatch_kernel<4, 5>(isr::FConvParams)") == "fpatch_kernel<128>"
+    assert f("void isr::(anonymous namespace)::bottleneck_kernel<4, 2, 2>(isr::BneckParams)").startswith("bottleneck_kernel<block, ")
+    assert all(profile_report.is_conv(n) for n in ("fexpand_kernel<64>", "fpatch_kernel<128>", "fstem_pool_kernel"))
+
+
 def test_committed_traffic_summary_parses_and_names_instances_as_the_library_does():
     import bench
     path = os.path.join(ROOT, "profiles", "resnet50_certify_hbm_traffic.md")
