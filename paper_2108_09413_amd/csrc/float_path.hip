@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) void float_noise_kernel(const FloatNoiseParams
 // with the fused and the 3x3 kernels below.
 // Error of the logits against binary64 (2-norm), fp32 instruction -> this kernel: tiny net 3.5e-7 -> 3.3e-7, ResNet-20
 // 2.0e-7 -> 1.55e-7, ResNet-110 3.1e-7 -> 2.5e-7, ResNet-50 at 96 to 224 pixels 8.1 .. 9.5e-7 -> 4.9 .. 5.8e-7; with the sums that
-// fpatch_kernel and fstem_pool_kernel keep apart 3.3e-7, 1.3e-7, 2.2e-7 and 4.8 .. 5.3e-7.
+// fpatch_kernel, fpatch16_kernel and fstem_pool_kernel keep apart 3.3e-7, 1.45e-7, 2.1e-7 and 4.8 .. 5.4e-7.
 //
 // FLAT: 1x1 stride-1 layers; else TABLE: K chunks of 4 channels looked up in ktab (a tap changes inside a step), else a
 // step lies inside one tap (Cin a multiple of 32) and its tap is counted along, all taps of 32 channels before the next 32.  PAIR: a 1x1 layer of any stride whose residual is
@@ -630,6 +630,106 @@ __global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    fconv_finish_tile<false>(p, acc, 0, bs, px0, ch0, wave, lane, 4);
+}
+
+// The same for inputs of an odd multiple of 16 channels (fpatch_kernel's steps are of 32): the run of 256 pixels, 16 channels of it, and the
+// weights of all nine taps fit LDS together, so that the taps follow one another without a barrier.  Rows of LDS are 32 bytes, the two
+// chunks of every other group of eight rows exchanged, which keeps the rows that are read together in different banks.  Through the table
+// these layers were half of the fp32 nets on 32 x 32 images: largest launches of ResNet-110 on 1024 copies 421 -> 250 us, its
+// certification at n = 10 000 45.9 -> 32.8 ms (three workgroups a CU; 35.1 with two), ResNet-20's at 20 000 17.1 -> 12.7.
+template <int MT, int NL>   // 258 + 2 W <= 32 NL
+__global__ __launch_bounds__(256, MT == 1 ? 3 : 2) void fpatch16_kernel(const FConvParams p) {
+    constexpr int BM = 32 * MT, NT = 2, BN = 128 * NT, ROWS = 32 * NL, ZERO = ROWS, PLANE = (ROWS + 1) * 32, TAP = BM * 32;
+    constexpr int NX = (4 * ROWS + 255) / 256, NW = (18 * BM + 255) / 256;   // chunks of pixels, of weights a thread
+    __shared__ __attribute__((aligned(256))) int8_t wt[9 * TAP];
+    __shared__ __attribute__((aligned(256))) int8_t run[3 * PLANE];
+    __shared__ __attribute__((aligned(16))) float bs[2 * BM];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const int mtiles = p.Cout_pp / BM;
+    const long nb = gridDim.x, per = nb >> 3, rem = nb & 7, xcd = blockIdx.x & 7;
+    const long bid = xcd * per + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3);   // as fconv_kernel
+    const int ch0 = (int)(bid % mtiles) * BM;
+    const int px0 = (int)(bid / mtiles) * BN;
+    const int nblk = p.Cin_p >> 4;
+    auto place = [](int row, int chunk) { return row * 32 + ((chunk ^ (row >> 3 & 1)) << 4); };
+
+    if (tid < 2 * BM) bs[tid] = (tid < BM ? p.bias : p.scale)[ch0 + (tid < BM ? tid : tid - BM)];
+    if (tid < 6) *(v4i *)(run + (tid >> 1) * PLANE + ZERO * 32 + (tid & 1) * 16) = v4i{0, 0, 0, 0};
+    int x[NT], y[NT], centre[NT];
+    v16f acc[MT][NT], small[MT][NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int r = (wave * NT + j) * 32 + l32, n = px0 + r < p.npix ? px0 + r : p.npix - 1;
+        x[j] = n % p.W;
+        y[j] = n / p.W % p.H;
+        centre[j] = r + p.W + 1;
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = small[i][j][e] = 0.0f;
+    }
+    for (int blk = 0; blk < nblk; ++blk) {
+        v4f px[NX];
+        v4i wv[NW];
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+            int n = px0 - p.W - 1 + ((tid + 256 * j) >> 2);
+            n = n < 0 ? 0 : (n < p.npix ? n : p.npix - 1);
+            px[j] = *(const v4f *)((const uint8_t *)p.in + ((uint32_t)n * (uint32_t)(p.Cin_p * 4) + (uint32_t)(blk * 64 + (tid & 3) * 16)));
+        }
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+            int i = tid + 256 * j;
+            if (i >= 18 * BM) i = 18 * BM - 1;
+            const int row = (i >> 1) % BM, k16 = (i >> 1) / BM * nblk + blk;
+            wv[j] = *(const v4i *)((const uint8_t *)p.w + ((size_t)(k16 >> 1) * p.Cout_pp + ch0 + row) * 64 + (k16 & 1) * 32 + (i & 1) * 16);
+        }
+        if (blk > 0) __syncthreads();   // every wave has read what this one replaces
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+            const int row = (tid + 256 * j) >> 2, c = tid & 3;
+            uint2 part[3];
+            split_bf16_4(px[j], part);
+            if (row < ROWS)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) *(uint2 *)(run + k * PLANE + place(row, c >> 1) + (c & 1) * 8) = part[k];
+        }
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+            const int i = tid + 256 * j, row = (i >> 1) % BM;
+            if (i < 18 * BM) *(v4i *)(wt + (i >> 1) / BM * TAP + place(row, i & 1)) = wv[j];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+            const int dy = tap / 3 - 1, dx = tap % 3 - 1;
+            v4i af[MT], part[NT][3];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) af[i] = *(const v4i *)(wt + tap * TAP + place(i * 32 + l32, half));
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const bool ok = (unsigned)(y[j] + dy) < (unsigned)p.H && (unsigned)(x[j] + dx) < (unsigned)p.W;
+                const int at = place(ok ? centre[j] + dy * p.W + dx : ZERO, half);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) part[j][k] = *(const v4i *)(run + k * PLANE + at);
+            }
+#pragma unroll
+            for (int k = 2; k >= 0; --k)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int i = 0; i < MT; ++i) {
+                        v16f &sum = k ? small[i][j] : acc[i][j];
+                        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, af[i]), __builtin_bit_cast(v8bf, part[j][k]), sum, 0, 0, 0);
+                    }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] += small[i][j];
     fconv_finish_tile<false>(p, acc, 0, bs, px0, ch0, wave, lane, 4);
 }
 
@@ -1135,6 +1235,18 @@ static hipError_t launch_fpatch(const FConvParams &p, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <int MT>
+static hipError_t launch_fpatch16(const FConvParams &p, hipStream_t st) {
+    const long blocks = (((long)p.npix + 255) / 256) * (p.Cout_pp / (32 * MT));
+    if (blocks > 0x7FFFFFFFL || 258 + 2 * p.W > 352) return hipErrorInvalidValue;
+    static const std::string name = "fpatch16_kernel<" + std::to_string(32 * MT) + ">";
+    set_kernel_name(name.c_str());
+    const dim3 grid((unsigned)blocks), block(256);
+    if (258 + 2 * p.W <= 288) hipLaunchKernelGGL((fpatch16_kernel<MT, 9>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((fpatch16_kernel<MT, 11>), grid, block, 0, st, p);
+    return hipGetLastError();
+}
+
 hipError_t launch_fconv(const FConvParams &p, hipStream_t st) {
     if (p.npix <= 0) return hipSuccess;
     const int bm = fconv_tile_m(p.Cout_p);
@@ -1152,6 +1264,8 @@ hipError_t launch_fconv(const FConvParams &p, hipStream_t st) {
         if (bm >= 64 && tiles(64, 128) >= FULL) return launch_fpatch<2>(p, st);
         return launch_fpatch<1>(p, st);
     }
+    if (p.k == 3 && p.stride == 1 && p.pad == 1 && p.Cin_p % 32 == 16 && p.W <= 47 && p.Ho == p.H && p.Wo == p.W)
+        return bm == 32 ? launch_fpatch16<1>(p, st) : launch_fpatch16<2>(p, st);
     if (bm == 128) {
         if (tiles(128, 256) >= FULL) return launch_fconv_tile<4, 2>(p, st);
         if (tiles(128, 128) >= FULL) return launch_fconv_tile<4, 1>(p, st);

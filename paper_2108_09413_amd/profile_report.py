@@ -76,9 +76,9 @@ def library_name(profiler_name: str) -> str:
     m = re.match(r"fexpand_kernel<(\d), \d, (true|false)>", n)
     if m:
         return "fexpand_kernel<%d%s>" % (32 * int(m.group(1)), ", pair" if m.group(2) == "true" else "")
-    m = re.match(r"fpatch_kernel<(\d), \d>", n)
+    m = re.match(r"(fpatch|fpatch16)_kernel<(\d), \d+>", n)
     if m:
-        return "fpatch_kernel<%d>" % (32 * int(m.group(1)))
+        return "%s_kernel<%d>" % (m.group(1), 32 * int(m.group(2)))
     n = re.sub(r"^stem_pool_kernel<\d>$", "stem_pool_kernel", n)
     if n == "stem_pool_kernel":
         return "stem_pool_kernel (+noise)"      # the default plan of the 224 x 224 workload draws the noise in this kernel
@@ -87,7 +87,7 @@ def library_name(profiler_name: str) -> str:
 
 def is_conv(name: str) -> bool:
     return name.startswith(("conv_dma_kernel", "conv_patch_kernel", "expand_reduce_kernel", "proj_expand_reduce_kernel", "bottleneck_kernel", "stem_pool_kernel", "fconv_kernel",
-                            "fexpand_kernel", "fpatch_kernel", "fstem_pool_kernel"))
+                            "fexpand_kernel", "fpatch_kernel", "fpatch16_kernel", "fstem_pool_kernel"))
 
 
 def last_json(path):

@@ -40,6 +40,7 @@ def test_profiler_names_of_the_fused_fp32_kernels():
     assert f("void isr::(anonymous namespace)::fexpand_kernel<2, 4, false>(isr::(anonymous namespace)::FExpandParams)") == "fexpand_kernel<64>"
     assert f("void isr::(anonymous namespace)::fexpand_kernel<4, 4, true>(isr::(anonymous namespace)::FExpandParams)") == "fexpand_kernel<128, pair>"
     assert f("void isr::(anonymous namespace)::fpatch_kernel<4, 5>(isr::FConvParams)") == "fpatch_kernel<128>"
+    assert f("void isr::(anonymous namespace)::fpatch16_kernel<1, 11>(isr::FConvParams)") == "fpatch16_kernel<32>"
     assert f("void isr::(anonymous namespace)::bottleneck_kernel<4, 2, 2>(isr::BneckParams)").startswith("bottleneck_kernel<block, ")
     assert all(profile_report.is_conv(n) for n in ("fexpand_kernel<64>", "fpatch_kernel<128>", "fstem_pool_kernel"))
 
