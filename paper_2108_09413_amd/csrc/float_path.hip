@@ -614,13 +614,15 @@ __global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
             buf = buf == NST - 1 ? 0 : buf + 1;
         }
         if (more) {
-            __builtin_amdgcn_s_barrier();   // every wave has read the run
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave has read the run
+            __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             store();
         }
     };
     for (int blk = 0; blk + 1 < nblk; ++blk) block(blk, std::true_type{});
     block(nblk - 1, std::false_type{});
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave has read its last step, whose stage may be the one that follows
     if constexpr (TWO)
 #pragma unroll
         for (int i = 0; i < MT; ++i) acc[i][0] += small[i];
@@ -1068,7 +1070,8 @@ __global__ __launch_bounds__(64 * NW, 2) void fexpand_kernel(const FExpandParams
             buf = buf == NST - 1 ? 0 : buf + 1;
         }
     }
-    __builtin_amdgcn_s_barrier();   // the last step is read, nothing is on its way: its stage takes the second layer's constants
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave has read its last step; nothing is on its way
+    __builtin_amdgcn_s_barrier();                        // any stage is free: the first one takes the second layer's constants
     float *c2 = (float *)lds;
     if (tid < 2 * COUT) c2[tid] = constant2;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
