@@ -148,9 +148,7 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
     if constexpr (NK == 4) wait_vmcnt<6>();   // steps 0 and 1 landed
     else if (nk > 2) wait_vmcnt<3>();
     else wait_vmcnt<0>();
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();       // they and the constants are visible
-    asm volatile("" ::: "memory");
+    lds_barrier();   // they and the constants are visible
 
     const int c16 = wm * 32 + 16 * half;   // first of the lane's 16 channels in the first two convolutions
     const int f1 = wn * 3 - (wn == 3), n1 = wn < 2 ? 3 : 2;   // first fragment and their number: 3, 3, 2, 2
@@ -197,11 +195,6 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
                 for (int f = 0; f < 3; ++f)
                     if (f < 2 || n1 == 3) acc[f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa, fb[f], acc[f], 0, 0, 0);
             }
-        };
-        auto lds_barrier = [&]() {
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
         };
         if constexpr (NK == 4) {
             compute(0, 0);
@@ -427,9 +420,7 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
                 int bias[4], mm[4], ch[4], ss[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) { bias[i] = prmr[0][oc + i]; mm[i] = prmr[1][oc + i]; ch[i] = prmr[2][oc + rq_chi_at<RQ>(i)]; ss[i] = prmr[3][oc + i]; }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                __builtin_amdgcn_s_barrier();   // the group's sums are complete
-                asm volatile("" ::: "memory");
+                lds_barrier();   // the group's sums are complete
                 const bool full = oy0 + TH <= p.H && ox0 + TW <= p.W;
 #pragma unroll
                 for (int nb = 0; nb < 2 * (F1 - F0); ++nb) {

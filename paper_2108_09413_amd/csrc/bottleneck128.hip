@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256, 2) void bottleneck128_kernel(const BneckParams
         for (int ks = 0; ks < nk; ++ks) {
             if (ks == 0 && nk > 1) wait_vmcnt<6>();   // step 0 landed; the 6 loads of step 1 may still be in flight
             else wait_vmcnt<0>();
-            __builtin_amdgcn_s_barrier();   // every wave's loads of step ks landed; every wave is done with step ks - 1
+            lds_barrier();   // every wave's loads of step ks landed; every wave is done with step ks - 1
             if (ks >= 1 && ks + 1 < nk) issue1(ks + 1, (ks + 1) & 1);
             const int8_t *base = &Ls[(ks & 1) * STAGE1];
 #pragma unroll
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(256, 2) void bottleneck128_kernel(const BneckParams
             else if (ks + 1 < STEPS) wait_vmcnt<2>();
             else wait_vmcnt<0>();
             if (ks == 0) __syncthreads();           // also: every wave's part of the t1 tile is written
-            else __builtin_amdgcn_s_barrier();      // every wave's loads of step ks landed; every wave is done with step ks - 1
+            else lds_barrier();                     // every wave's loads of step ks landed; every wave is done with step ks - 1
             if (ks >= 1 && ks + 2 < STEPS) issue2(ks + 2, cur == 0 ? 2 : cur - 1);   // into the stage of step ks - 1
             const int tap = ks >> 1, ky = tap / 3, kx = tap - 3 * ky, chalf = (ks & 1) * 4;
             const int8_t *wbase = &W2s[cur * W2_STAGE];

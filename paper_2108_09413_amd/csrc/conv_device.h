@@ -234,6 +234,13 @@ __device__ __forceinline__ uint32_t lds_address(const void *p) {
 // The compiler does not order LDS reads after loads that write LDS; this wait does.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// The workgroup's barrier for tiles in LDS; loads from memory stay in flight.  This wave's LDS operations are complete before it, not
+// only issued: others may overwrite behind it what this wave has read, be it with stores or with loads straight into LDS.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
 
 }  // namespace isr
 

@@ -252,7 +252,7 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
                 else wait_vmcnt<0>();
             } else if (NST == 3 && ks + 1 < steps) wait_vmcnt<L>();
             else wait_vmcnt<0>();
-            __builtin_amdgcn_s_barrier();   // every wave's loads of step ks landed; every wave is done with step ks - 1
+            lds_barrier();   // every wave's loads of step ks landed; every wave is done with step ks - 1
             if (ks >= 1) {
                 if (ks + NST - 1 < steps) fetch(ks + NST - 1, fill);
                 else if (FUSE == 1 && with_residual_tile && ks + 1 == steps && res_buf < 0) { res_buf = fill; issue_residual(fill); }
@@ -299,7 +299,7 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
         }
         if (steps >= 2) wait_vmcnt<L>();
         else wait_vmcnt<0>();
-        __builtin_amdgcn_s_barrier();   // every wave's loads of step 0 landed
+        lds_barrier();   // every wave's loads of step 0 landed
         v4i fa[2][FM], fb[2][FN];
         auto read_fragments = [&](const int8_t *base, int ksub, int slot) {
 #pragma unroll
@@ -321,8 +321,7 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
                     // only the loads of step ks + 1 are in flight (those of step ks + 2 are issued below);
                     // this wave's reads of the current buffer are complete before any wave refills it
                     wait_vmcnt<0>();
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                    __builtin_amdgcn_s_barrier();
+                    lds_barrier();
                     if (ks + 2 < steps) fetch(ks + 2, cur);
                     read_fragments(Ls[nxt], 0, slot ^ 1);
                 }

@@ -246,7 +246,7 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     constexpr int PENDING = DUTY ? (NAB - 2) / NG * LA : (NAB - 2) * NA;
     if (!DUTY) wait_vmcnt<(NAB - 1) * NA>();
     else wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();   // step 0 landed
+    lds_barrier();   // step 0 landed
     refill(0, 0, 0);
     tap_rows(0, brow);
     read_fragments(As[0], Bs[0], brow, 0, 0);
@@ -259,10 +259,9 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
             if (ksub + 1 < KS) {
                 read_fragments(abase, bbase, brow, ksub + 1, slot ^ 1);
             } else if (t + 1 < nk) {
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of step t are complete
                 if (PENDING > 0 && t + NAB - 1 < nk) wait_vmcnt<PENDING>();
                 else wait_vmcnt<0>();
-                __builtin_amdgcn_s_barrier();   // every wave's loads of step t + 1 landed; every wave is done reading step t
+                lds_barrier();   // every wave's loads of step t + 1 landed; every wave is done reading step t
                 if (++tap == 9) { tap = 0; ++slice; }
                 refill(t + 1, slice, tap);
                 tap_rows(tap, brow);

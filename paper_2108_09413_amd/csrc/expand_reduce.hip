@@ -117,7 +117,7 @@ __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p)
             } else {
                 wait_vmcnt<0>();
             }
-            __builtin_amdgcn_s_barrier();    // every wave's loads of this tile landed; every wave is done with the previous tile's buffers
+            lds_barrier();   // every wave's loads of this tile landed; every wave is done with the previous tile's buffers
         }
         if (prefetch) issue_tile(tile + 2 * G, buf >= 1 ? buf - 1 : XNB - 1);   // the buffer of the previous tile
 
@@ -153,8 +153,7 @@ __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p)
             *(v4i *)cell = yv;
             if (n1 < p.npix) *(v4i *)(p.y + n1 * XC + oc) = yv;
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's part of the y tile is in LDS (its stores to memory may still be under way)
-        __builtin_amdgcn_s_barrier();                         // the y tile is complete
+        lds_barrier();   // the y tile is complete (its stores to memory may still be under way)
         asm volatile("" ::: "memory");
 
         // ---- reduce: 16 channels x 32 pixels per wave, K = 512 channels of the y tile ----
@@ -265,7 +264,7 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
             } else {
                 wait_vmcnt<0>();
             }
-            __builtin_amdgcn_s_barrier();    // every wave's loads of this tile landed; every wave is done with the previous tile
+            lds_barrier();   // every wave's loads of this tile landed; every wave is done with the previous tile
         }
         if (prefetch) issue_tile(tile + 2 * G, buf >= 1 ? buf - 1 : XNB - 1);
 
@@ -326,8 +325,7 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
             const long n1 = (long)n0 + px1;
             if (n1 < p.npix) *(v4i *)(p.y + n1 * XC + oc) = yv;
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's part of the y tile is in LDS
-        __builtin_amdgcn_s_barrier();                         // the y tile is complete
+        lds_barrier();   // the y tile is complete
         asm volatile("" ::: "memory");
 
         // ---- reduce: wave w computes channels 16 (w / 2) .. + 15 of pixels 16 (w % 2) .. + 15 ----
@@ -422,7 +420,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
             } else {
                 wait_vmcnt<0>();
             }
-            __builtin_amdgcn_s_barrier();    // every wave's loads of this tile landed; every wave is done with the previous tile
+            lds_barrier();   // every wave's loads of this tile landed; every wave is done with the previous tile
         }
         if (prefetch) issue_tile(tile + 2 * G, buf >= 1 ? buf - 1 : XNB - 1);
 
@@ -463,8 +461,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
             const long n1 = (long)n0 + px1;
             if (n1 < p.npix) *(v4i *)(p.y + n1 * XC + oc) = yv;
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's part of the y tile is in LDS
-        __builtin_amdgcn_s_barrier();                         // the y tile is complete
+        lds_barrier();   // the y tile is complete
         asm volatile("" ::: "memory");
 
         // ---- reduce: wave w computes channels 16 w .. 16 w + 15 of the 32 pixels ----
@@ -571,7 +568,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
             // loads, which were issued after the loads of this tile: all that may still be under way are the two stores that
             // ended the previous tile.
             wait_vmcnt<2>();
-            __builtin_amdgcn_s_barrier();    // every wave's loads of this tile landed; every wave is done with the previous tile
+            lds_barrier();   // every wave's loads of this tile landed; every wave is done with the previous tile
         }
         if (prefetch) issue_tile(tile + 2 * G, buf >= 1 ? buf - 1 : XNB - 1);
         int l = lane;
@@ -617,8 +614,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
         v4i a2c[2][GK];
 #pragma unroll
         for (int i = 0; i < GK; ++i) a2c[0][i] = *(const v4i *)(a2w + ((uint32_t)l * 16 + (uint32_t)(i * 1024)));
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's part of the y tile is in LDS
-        __builtin_amdgcn_s_barrier();                         // the y tile is complete
+        lds_barrier();   // the y tile is complete
         asm volatile("" ::: "memory");
 
         // ---- reduce: wave w computes channels 16 w .. 16 w + 15 of the 32 pixels, K = 1024 ----

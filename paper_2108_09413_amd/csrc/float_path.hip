@@ -430,15 +430,13 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
         issue(0, 0);
         for (int step = 0; step < nsteps; ++step) {
             wait_vmcnt<0>();
-            __builtin_amdgcn_s_barrier();   // every wave's loads of this step landed; every wave is done reading the other buffer
+            lds_barrier();   // every wave's loads of this step landed; every wave is done reading the other buffer
             if (step + 1 < nsteps) issue(step + 1, (step + 1) & 1);
             multiply(step & 1);
         }
         float *idle = (float *)(lds + (nsteps & 1) * STAGE);   // the stage that the last step did not use
         if (tid < 2 * BM) idle[tid] = bias_or_scale;
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+        lds_barrier();
         bs = idle;
     } else {
         // the steps of both layers are one sequence; these layers have few, and wait for memory with one of them ahead
@@ -461,7 +459,7 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
         for (int s = 0; s < all; ++s) {
             if (s + 1 < all) wait_vmcnt<NA + NB>();   // only the next step's loads may be in flight
             else wait_vmcnt<0>();
-            __builtin_amdgcn_s_barrier();
+            lds_barrier();
             if (s + 2 < all) fetch(s + 2, buf == 0 ? 2 : buf - 1);
             multiply(buf);
             buf = buf == 2 ? 0 : buf + 1;
@@ -576,9 +574,7 @@ __global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
             if (tap == 8 && !more) wait_vmcnt<0>();
             else if ((tap == 1 || tap == 2) && more) wait_vmcnt<NA + NL>();
             else wait_vmcnt<NA>();
-            if (tap == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the run is stored
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
+            lds_barrier();   // the run is stored (tap 0); every wave is done with the step before
             __builtin_amdgcn_sched_barrier(0);
             weights();
             if (tap == 0 && more) {
@@ -614,24 +610,19 @@ __global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
             buf = buf == NST - 1 ? 0 : buf + 1;
         }
         if (more) {
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave has read the run
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
+            lds_barrier();   // every wave has read the run
             store();
         }
     };
     for (int blk = 0; blk + 1 < nblk; ++blk) block(blk, std::true_type{});
     block(nblk - 1, std::false_type{});
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave has read its last step, whose stage may be the one that follows
     if constexpr (TWO)
 #pragma unroll
         for (int i = 0; i < MT; ++i) acc[i][0] += small[i];
-    __builtin_amdgcn_s_barrier();
+    lds_barrier();   // every wave has read its last step, whose stage may be the one that follows
     float *bs = (float *)wt;
     if (tid < 2 * BM) bs[tid] = bias_or_scale;
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    lds_barrier();
     fconv_finish_tile<false>(p, acc, 0, bs, px0, ch0, wave, lane, 4);
 }
 
@@ -794,9 +785,7 @@ __global__ __launch_bounds__(256, 2) void fstem_pool_kernel(const FConvParams p,
 #pragma unroll
         for (int k = 0; k < 3; ++k) *(uint2 *)(img + k * PLANE + r * FS_PITCH + ((q & 1) * FS_HALF + (q >> 1)) * 16 + (x & 1) * 8) = part[k];
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    lds_barrier();
 
     const int py = py0 + group * FS_ROWS, px = px0 + l32;
     if (py >= Hp) return;
@@ -965,8 +954,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fexpand_kernel(const FExpandParams
     };
     auto weights = [&](const int8_t *A, int i, int r, int ks) { return *(const v4i *)(A + (i * 32 + r) * 64 + (((2 * ks + half) ^ swz<4>(r)) << 4)); };
     auto begin = [&]() {   // after the wait for this wave's loads of the step
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+        lds_barrier();
         __builtin_amdgcn_sched_barrier(0);
         fetch();
     };
@@ -1070,13 +1058,10 @@ __global__ __launch_bounds__(64 * NW, 2) void fexpand_kernel(const FExpandParams
             buf = buf == NST - 1 ? 0 : buf + 1;
         }
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave has read its last step; nothing is on its way
-    __builtin_amdgcn_s_barrier();                        // any stage is free: the first one takes the second layer's constants
+    lds_barrier();   // every wave has read its last step, nothing is on its way: the first stage takes the second layer's constants
     float *c2 = (float *)lds;
     if (tid < 2 * COUT) c2[tid] = constant2;
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    lds_barrier();
     const float lo2 = p.relu2 ? 0.0f : -INFINITY;
     float *const out = p.out + pix * COUT + 16 * half;
 #pragma unroll

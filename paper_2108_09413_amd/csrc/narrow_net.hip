@@ -49,13 +49,6 @@ __device__ __forceinline__ int tile_at(int y, int x, int chunk) {
 template <int C, int S>
 constexpr int tile_bytes() { return (S + 2) * (S + 2) * C; }
 
-// this wave's LDS operations are complete, then the workgroup's barrier; loads from memory stay in flight
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
 // border pixel b of a padded (S+2) x (S+2) tile: top row, bottom row, left and right columns without the corners
 template <int S>
 __device__ __forceinline__ void border_pixel(int b, int &y, int &x) {

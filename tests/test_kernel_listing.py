@@ -1,0 +1,87 @@
+"""The machine code of the library's own kernels, read back from the built libisr.so: properties that the kernels rely on
+and that neither the compiler nor a run on a GPU would show to be lost."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2108_09413_amd as isr
+from paper_2108_09413_amd.build import LIB
+
+LLVM = "/opt/rocm/llvm/bin"
+
+
+def _parse(listing):
+    """{kernel: [(address, instruction, branch target or None)]}"""
+    code, base, kernels = None, 0, {}
+    for line in listing.splitlines():
+        head = re.match(r"([0-9a-f]+) <(.+)>:$", line)
+        if head:
+            base, code = int(head.group(1), 16), kernels.setdefault(head.group(2), [])
+        elif line.startswith("\t") and code is not None and "//" in line:
+            text, _, rest = line.strip().partition("//")
+            target = re.search(r"<.*\+0x([0-9a-f]+)>", rest)
+            code.append((int(rest.split(":")[0], 16), text.strip(), base + int(target.group(1), 16) if target else None))
+    return kernels
+
+
+@pytest.fixture(scope="module")
+def code_objects(tmp_path_factory):
+    if not os.path.exists(os.path.join(LLVM, "llvm-objdump")):
+        pytest.skip("no llvm-objdump")
+    isr.lib()
+    out = str(tmp_path_factory.mktemp("listing"))
+    shutil.copy(LIB, out)
+    subprocess.check_call([os.path.join(LLVM, "llvm-objdump"), "--offloading", "libisr.so"], cwd=out, stdout=subprocess.DEVNULL)
+    return [os.path.join(out, f) for f in sorted(os.listdir(out)) if f.endswith("gfx950")]
+
+
+@pytest.fixture(scope="module")
+def kernels(code_objects):
+    found = {}
+    for f in code_objects:
+        found.update(_parse(subprocess.check_output([os.path.join(LLVM, "llvm-objdump"), "-d", f], text=True)))
+    assert len(found) > 100
+    return found
+
+
+def _open_at_barriers(code):
+    """Addresses of the barriers that some path reaches with an LDS access of this wave not known to be complete."""
+    index = {a: i for i, (a, _, _) in enumerate(code)}
+    seen, todo, bad = set(), [(0, False)], set()
+    while todo:
+        i, pending = todo.pop()
+        while i < len(code) and (i, pending) not in seen:
+            seen.add((i, pending))
+            address, text, target = code[i]
+            op = text.split()[0]
+            if op == "s_barrier" and pending:
+                bad.add(address)
+            elif op.startswith("ds_"):
+                pending = True
+            elif op == "s_waitcnt" and "lgkmcnt(0)" in text:
+                pending = False
+            elif op == "s_endpgm":
+                break
+            if target is not None and op.startswith("s_cbranch"):
+                todo.append((index[target], pending))
+            i = index[target] if op == "s_branch" else i + 1
+    return bad
+
+
+def test_a_path_with_an_open_read_is_found():
+    def code(wait):
+        return [(0, "s_cbranch_scc1 2", 12), (4, "ds_read_b128 v[0:3], v4", None), (8, wait, None), (12, "s_barrier", None), (16, "s_endpgm", None)]
+    assert _open_at_barriers(code("s_nop 0")) == {12}
+    assert _open_at_barriers(code("s_waitcnt lgkmcnt(1)")) == {12}
+    assert _open_at_barriers(code("s_waitcnt lgkmcnt(0)")) == set()
+
+
+def test_lds_accesses_are_complete_at_every_barrier(kernels):
+    """Behind a barrier other waves overwrite what this one has read, with stores or with loads straight into LDS: its reads have to be
+    done by then, not only issued, on every path."""
+    assert sum(t.startswith("s_barrier") for code in kernels.values() for _, t, _ in code) > 500
+    bad = {name: len(at) for name, code in kernels.items() if (at := _open_at_barriers(code))}
+    assert not bad
