@@ -856,7 +856,7 @@ __global__ __launch_bounds__(256, 2) void fstem_pool_kernel(const FConvParams p,
 //
 // Three stages.  Loads and stores end in order, so a step waits until only what was issued after its loads is left: the loads of
 // the next step and the stores of the two steps before.  Pixels past the end repeat the last one and store the same values to
-// the same place, so that the number of stores is always the same.
+// the same place, so that the number of stores is always the same; tests/test_kernel_listing.py counts them in the machine code.
 //
 // PAIR: the residual is another 1x1 layer's result, as F_PAIR: its steps come before the first layer's, its sums stay in registers.
 struct FExpandParams {

@@ -85,3 +85,26 @@ def test_lds_accesses_are_complete_at_every_barrier(kernels):
     assert sum(t.startswith("s_barrier") for code in kernels.values() for _, t, _ in code) > 500
     bad = {name: len(at) for name, code in kernels.items() if (at := _open_at_barriers(code))}
     assert not bad
+
+
+def test_fexpand_stores_are_what_its_waits_count(kernels):
+    """fexpand_kernel waits until only what was issued after a step's loads is left, four stores a step of its second kind among it: a
+    store that the compiler merged, dropped or moved to another step would let a stage be read before it has landed."""
+    checked = 0
+    for name, code in kernels.items():
+        tiles = re.search(r"fexpand_kernelILi(\d+)E", name)
+        if not tiles:
+            continue
+        steps, stores = [0], {"global_store_dwordx4"}
+        for _, text, _ in code:
+            op = text.split()[0]
+            if op == "s_barrier":
+                steps.append(0)
+            elif "store" in op and not op.startswith("scratch_"):   # scratch only adds to what is waited for
+                stores.add(op)
+                steps[-1] += 1
+        assert stores == {"global_store_dwordx4"}
+        # four steps of the second kind in the loop; behind the last barrier the second layer's result, four stores for 32 channels
+        assert steps[-1] == 4 * int(tiles.group(1)) and sorted(n for n in steps[:-1] if n) == [4] * 4, (name, steps)
+        checked += 1
+    assert checked == 5
