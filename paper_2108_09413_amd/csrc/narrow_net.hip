@@ -186,8 +186,8 @@ __device__ __forceinline__ auto bias_vector(const LaneConsts<N, RQ> &k) {
 }
 
 // FRAGS fragments of one convolution of a wave, weights in `fa`, which afterwards holds those at `next`: source(i) is
-// fragment i's tile address; element(i, e, value) consumes the accumulator of element e (in the order of e), after
-// start(i) and before finish(i).
+// fragment i's tile address; element(i, q, e, value) consumes the accumulator of element e (in the order of e), after
+// start(i, q) and before finish(i); q: which of a group's fragments, a constant wherever it indexes registers.
 template <int FRAGS, int RQ, bool PAIRS, int C, int S, class Source, class Start, class Element, class Finish>
 __device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&fa)[WideConv<C, S>::KS], const LaneConsts<16, RQ> &k, const int8_t *next,
                                                Source source, Start start, Element element, Finish finish) {
@@ -210,12 +210,12 @@ __device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&f
         for (int g = 1; g < G; ++g) {
             v16i prev[P];
 #pragma unroll
-            for (int q = 0; q < P; ++q) { prev[q] = acc[q]; start((g - 1) * P + q); }
+            for (int q = 0; q < P; ++q) { prev[q] = acc[q]; start((g - 1) * P + q, q); }
             const int8_t *src[P];
             begin(g, src);
             auto elem = [&](int e) {
                 const int i = (g - 1) * P + e / 16;
-                element(i, e & 15, prev[e / 16][e & 15]);
+                element(i, e / 16, e & 15, prev[e / 16][e & 15]);
                 if ((e & 15) == 15) finish(i);
             };
             if (g + 1 < G) wide_group<P, true, false>(wc, src, fa, acc, row, elem);
@@ -223,9 +223,9 @@ __device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&f
         }
 #pragma unroll
         for (int q = 0; q < P; ++q) {
-            start((G - 1) * P + q);
+            start((G - 1) * P + q, q);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) element((G - 1) * P + q, e, acc[q][e]);
+            for (int e = 0; e < 16; ++e) element((G - 1) * P + q, q, e, acc[q][e]);
             finish((G - 1) * P + q);
         }
     } else {
@@ -233,9 +233,9 @@ __device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&f
         for (int i = 0; i < FRAGS; ++i) {
             k.fragment();
             const v16i acc = wc.run(source(i), fa, bias_vector<16, RQ>(k));
-            start(i);
+            start(i, 0);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) element(i, e, acc[e]);
+            for (int e = 0; e < 16; ++e) element(i, 0, e, acc[e]);
             finish(i);
         }
         wc.load_weights(next, fa);
@@ -328,7 +328,8 @@ __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t 
 }
 
 // A block's descriptor.  AHEAD: dword by dword in the lanes of a register, by a vector load two blocks ahead; else by scalar loads
-// where its fields are used, which other workgroups of the CU cover.
+// where its fields are used, which other workgroups of the CU cover; it is then made anew for each block, since what is alive across
+// the convolutions costs these kernels their last registers (256 with 2 spilled instead of 253).
 template <bool AHEAD>
 struct Block {
     int lanes;
@@ -510,7 +511,11 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
     int zp_t = 256;   // zero-point in the border of t; none yet
     for (int blk = 0; blk < p.nblocks; ++blk) {
         const bool last = blk + 1 == p.nblocks;
-        const Block<AHEAD> after(p, blk + 2, lane);
+        if constexpr (!AHEAD) {   // nothing of a descriptor is kept across the convolutions
+            cur = Block<AHEAD>(p, blk, lane);
+            nxt = Block<AHEAD>(p, last ? blk : blk + 1, lane);
+        }
+        const Block<AHEAD> after(p, AHEAD ? blk + 2 : 0, lane);
         const int zp_x = cur.zp_x(), zp_mid = cur.zp_t(), lo1 = cur.lo1(), lo2 = cur.lo2();
         lds_barrier();            // x, its border and the first convolution's constants are in LDS; the previous block is done with t
         if (tid < 4 * C) {
@@ -603,8 +608,8 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                     const LaneConsts<16, RQ> k(prm[0], C, wc.mf * 32 + wc.half * 16);
                     int q[4];
                     v4i o;
-                    wide_fragments<FRAGS, RQ, true>(wc, fa, k, cur.w2(), [&](int i) { return X + offset(i); }, [](int) {},
-                        [&](int, int e, int a) {
+                    wide_fragments<FRAGS, RQ, true>(wc, fa, k, cur.w2(), [&](int i) { return X + offset(i); }, [](int, int) {},
+                        [&](int, int, int e, int a) {
                             q[e & 3] = k.conv(a, e, lo1);
                             if ((e & 3) == 3) o[e >> 2] = (int)rq_pack<RQ>(q[0], q[1], q[2], q[3]);
                         },
@@ -620,16 +625,18 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 int q[4];
                 v4i o, rv[2];   // residuals of the two fragments of a group
                 wide_fragments<FRAGS, RQ, RQA == RQ_TOP>(wc, fa, k, nxt.w1(), [&](int i) { return T + offset(i); },
-                    [&](int i) { rv[i & 1] = *(const v4i *)(X + offset(i) + wc.out); },
-                    [&](int i, int e, int a) {
-                        q[e & 3] = rq_add<RQ, RQA>(k.conv(a, e, lo2), (uint32_t)rv[i & 1][e >> 2], e & 3, ac);
+                    [&](int i, int j) { rv[j] = *(const v4i *)(X + offset(i) + wc.out); },
+                    [&](int, int j, int e, int a) {
+                        q[e & 3] = rq_add<RQ, RQA>(k.conv(a, e, lo2), (uint32_t)rv[j][e >> 2], e & 3, ac);
                         if ((e & 3) == 3) o[e >> 2] = (int)rq_pack<RQA>(q[0], q[1], q[2], q[3]);
                     },
                     [&](int i) { *(v4i *)(X + offset(i) + dst) = o; });
             }
         });
-        cur = nxt;
-        nxt = after;
+        if constexpr (AHEAD) {
+            cur = nxt;
+            nxt = after;
+        }
     }
 
     // ---- down-sampling into the next stage ----

@@ -108,3 +108,16 @@ def test_fexpand_stores_are_what_its_waits_count(kernels):
         assert steps[-1] == 4 * int(tiles.group(1)) and sorted(n for n in steps[:-1] if n) == [4] * 4, (name, steps)
         checked += 1
     assert checked == 5
+
+
+def test_stage_kernels_keep_to_their_registers(code_objects):
+    """The kernels of the nets on 32 x 32 images, whose rates rest on two workgroups a CU with everything in registers."""
+    seen = 0
+    for f in code_objects:
+        notes = subprocess.check_output([os.path.join(LLVM, "llvm-readelf"), "--notes", f], text=True)
+        for kernel in notes.split("  - .agpr_count:")[1:]:
+            field = {k: re.search(rf"\.{k}:\s+(\S+)", kernel).group(1) for k in ("name", "vgpr_spill_count", "private_segment_fixed_size")}
+            if "narrow_" in field["name"]:
+                assert (field["vgpr_spill_count"], field["private_segment_fixed_size"]) == ("0", "0"), field
+                seen += 1
+    assert seen == 9
