@@ -95,7 +95,10 @@ int isr_model_info(const isr_model *m, int *C, int *H, int *W, int *num_classes)
  * needs for that many copies, the one that stores each tensor among them.  A network
  * whose stages each run in one kernel (32 x 32 images) stores a fraction of the
  * tensors: while fusion is enabled it takes as many copies at a time as the `bytes`
- * given hold, chunk_samples at the least, and cuts longer runs into equal parts. */
+ * given hold, chunk_samples at the least, and cuts longer runs into equal parts.
+ * A call returns when its results are on the host and nothing that it was given is read
+ * or written any more; the stream may for some microseconds still be ending the last
+ * kernel, and then reports so if it is asked. */
 size_t isr_workspace_bytes(const isr_model *m, uint32_t chunk_samples);
 int isr_set_workspace(isr_model *m, void *workspace_device, size_t bytes, uint32_t chunk_samples,
                       void *hip_stream);

@@ -40,14 +40,23 @@ const char *isr::last_kernel_name() { return g_kernel_name; }
 
 namespace {
 
+// The pinned staging memory before it is written anew: copies out of it of an earlier call have ended.  Published tallies say so;
+// after a call that published none, or failed on its way, the stream's end does.
+int free_staging(isr_model *m) {
+    if (m->staging_busy) HIP_TRY(hipStreamSynchronize(m->stream));
+    m->staging_busy = false;
+    return ISR_OK;
+}
+
 int get_table(isr_model *m, uint32_t sigma, const DeviceNoiseTable **out) {
+    int rc;
     for (int i = 0; i < TABLE_SLOTS; ++i)
         if (m->table_sigma[i] == sigma) { *out = m->dtables + i; return ISR_OK; }
     int slot = m->table_next;
     m->table_next = (slot + 1) % TABLE_SLOTS;
-    // the staging slot may still be in flight from an earlier call on this stream
-    HIP_TRY(hipStreamSynchronize(m->stream));
+    if ((rc = free_staging(m)) != ISR_OK) return rc;
     if (!build_device_table(sigma, m->htables[slot])) return ISR_ERR_ARG;
+    m->staging_busy = true;
     HIP_TRY(hipMemcpyAsync(m->dtables + slot, m->htables + slot, sizeof(DeviceNoiseTable), hipMemcpyHostToDevice, m->stream));
     m->table_sigma[slot] = sigma;
     *out = m->dtables + slot;
@@ -261,6 +270,7 @@ int run_slots(isr_model *m, const Plan &pl, const Draw &draw, int32_t *logits_ho
         const bool timed = m->profile_every && (m->chunk_counter++ % m->profile_every) == 0;
         size_t ev = 0;
         auto mark = [&]() -> int {   // event before a launch / after the last one
+            ++m->launches;
             if (!timed) return ISR_OK;
             if (ev == m->events.size()) {
                 hipEvent_t e;
@@ -562,14 +572,35 @@ int isr::open_counts(isr_model *m) {
 }
 // Tallies to the host and zeros on the device, by the last kernel of a call: nothing that the call was given is in use when its
 // flag has arrived, only the kernel's own end is still to come.  Waits of more than 2 ms, and what goes wrong, are the runtime's.
+//
+// The event behind the kernel has the stream's end on its way while the host watches; without it whoever synchronises next only
+// then asks for it, and waits longer than the flag has saved.  Behind more than five launches and this one a synchronisation
+// that comes after the end takes 28 us, whatever they are, where one that waits for the end takes 2, so such a call waits for the stream
+// itself.  us of calls in a row / of a call and a synchronisation of the device behind it, prediction with 100 copies or
+// (two-convolution net, one launch) certification with 1000:
+//                                    stream's end      flag alone       flag and event
+//   two-convolution net              38.7 / 41.1       34.8 / 45.0      34.6 / 39.0
+//   ResNet-20                        47.0 / 49.5       42.6 / 53.0      42.1 / 46.5
+//   ResNet-50, 36 launches            956 /  960        948 /  981       947 /  980
+//   two-convolution net, 5 launches   81.6 / 83.8                        77.2 / 81.6
+//   two-convolution net, 6 launches   94.3 / 96.7                        90.0 / 118.4
+//   ResNet-20, 5 launches           179.6 / 181.4                      174.6 / 178.9
+//   ResNet-20, 6 launches           210.6 / 213.0                      205.9 / 233.9
+//   20 pairs of 10 classes           58.7 / 60.7       62.9 / 63.7      54.5 / 56.5
+//   256 pairs of 10 classes         265.8 / 268.1     274.7 / 270.8    260.6 / 262.3
+constexpr uint32_t WATCHED_LAUNCHES = 5;
 static int publish(isr_model *m, uint32_t *counts, uint32_t *host_dev, size_t n) {
-    if (n > PUBLISH_WATCHED) {
+    const bool watch = n <= PUBLISH_WATCHED && m->launches <= WATCHED_LAUNCHES;
+    m->launches = 0;
+    if (!watch) {
         HIP_TRY(launch_publish(counts, host_dev, n, nullptr, 0, m->stream));
         HIP_TRY(hipStreamSynchronize(m->stream));
+        m->staging_busy = false;
         return ISR_OK;
     }
     const uint32_t seq = ++m->published;
     HIP_TRY(launch_publish(counts, host_dev, n, m->hflag_dev, seq, m->stream));
+    HIP_TRY(hipEventRecord(m->end, m->stream));
     const auto patience = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
     for (uint32_t spins = 1; __atomic_load_n(m->hflag, __ATOMIC_ACQUIRE) != seq; ++spins) {
         if (spins % 64 == 0 && std::chrono::steady_clock::now() > patience) {
@@ -578,6 +609,7 @@ static int publish(isr_model *m, uint32_t *counts, uint32_t *host_dev, size_t n)
         }
         __builtin_ia32_pause();
     }
+    m->staging_busy = false;
     return ISR_OK;
 }
 int isr::close_counts(isr_model *m, uint32_t phases) {
@@ -590,13 +622,12 @@ int isr::close_counts(isr_model *m, uint32_t phases) {
 namespace {
 
 // Makes the tables of every sigma in `sigmas` resident at once (at most TABLE_SLOTS
-// distinct values) and returns the slot of each.
+// distinct values) and returns the slot of each.  The staging memory is free (free_staging).
 int get_tables(isr_model *m, const std::vector<uint32_t> &sigmas, std::vector<uint32_t> &slots) {
     std::vector<uint32_t> distinct;
     for (uint32_t s : sigmas)
         if (std::find(distinct.begin(), distinct.end(), s) == distinct.end()) distinct.push_back(s);
     if ((int)distinct.size() > TABLE_SLOTS) return ISR_ERR_ARG;
-    bool synced = false;
     for (uint32_t s : distinct) {
         bool have = false;
         for (int i = 0; i < TABLE_SLOTS; ++i) have = have || m->table_sigma[i] == s;
@@ -608,8 +639,8 @@ int get_tables(isr_model *m, const std::vector<uint32_t> &sigmas, std::vector<ui
         }
         if (slot < 0) return ISR_ERR_ARG;   // cannot happen: fewer needed tables than slots
         m->table_next = (slot + 1) % TABLE_SLOTS;
-        if (!synced) { HIP_TRY(hipStreamSynchronize(m->stream)); synced = true; }   // staging slots may be in flight
         if (!build_device_table(s, m->htables[slot])) return ISR_ERR_ARG;
+        m->staging_busy = true;
         HIP_TRY(hipMemcpyAsync(m->dtables + slot, m->htables + slot, sizeof(DeviceNoiseTable), hipMemcpyHostToDevice, m->stream));
         m->table_sigma[slot] = s;
     }
@@ -649,10 +680,10 @@ int prepare_batch(isr_model *m, const void *x, uint32_t n_images, const isr_item
         m->items_cap = cap;
         m->counts_b_clean = false;
     }
-    int rc = get_tables(m, sigmas, slots);
-    if (rc != ISR_OK) return rc;
-    HIP_TRY(hipStreamSynchronize(m->stream));   // the pinned descriptors of an earlier call may still be in flight
+    int rc = free_staging(m);
+    if (rc != ISR_OK || (rc = get_tables(m, sigmas, slots)) != ISR_OK) return rc;
     for (uint32_t i = 0; i < n_items; ++i) m->hitems[i] = NoiseItem{items[i].image, slots[i], items[i].image_id};
+    m->staging_busy = true;
     HIP_TRY(hipMemcpyAsync(m->ditems, m->hitems, sizeof(NoiseItem) * n_items, hipMemcpyHostToDevice, m->stream));
     if (!m->counts_b_clean) HIP_TRY(launch_fill_u32(m->dcounts_b, 0, (size_t)2 * m->items_cap * C, m->stream));
     m->counts_b_clean = false;
@@ -707,6 +738,7 @@ int isr_load_model(const void *blob_host, size_t bytes, isr_model **out) {
         *m->hflag = m->published;
         e = hipHostGetDevicePointer((void **)&m->hcounts_dev, m->hcounts, 0);
         if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&m->hflag_dev, m->hflag, 0);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&m->end, hipEventDisableTiming);
     }
     if (e != hipSuccess) { g_last_hip_error = (int)e; return cleanup(ISR_ERR_DEVICE); }
     rebase_device_ops(m->ops, m->dconst);
@@ -792,6 +824,7 @@ int isr_profile_read(const isr_model *m, isr_kernel_stat *out_host, uint32_t cap
 int isr_free_model(isr_model *m) {
     if (!m) return ISR_OK;
     for (hipEvent_t e : m->events) (void)hipEventDestroy(e);
+    if (m->end) (void)hipEventDestroy(m->end);
     if (m->dconst) (void)hipFree(m->dconst);
     if (m->htables) (void)hipHostFree(m->htables);
     if (m->ditems) (void)hipFree(m->ditems);

@@ -288,6 +288,7 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
         struct Work { const char *kernel; int conv; double ops, bytes; };
         std::vector<Work> work;
         auto mark = [&]() -> int {
+            ++m->launches;
             if (!timed) return ISR_OK;
             if (ev == m->events.size()) {
                 hipEvent_t e;

@@ -442,7 +442,7 @@ hipError_t launch_maxpool(const PoolParams &p, hipStream_t st);
 hipError_t launch_gap(const GapParams &p, hipStream_t st);
 hipError_t launch_fc(const FcParams &p, hipStream_t st);
 // flag != null (at most PUBLISH_WATCHED tallies): `seq` is stored there when the tallies are on the host
-constexpr size_t PUBLISH_WATCHED = 256;
+constexpr size_t PUBLISH_WATCHED = 2560;
 hipError_t launch_publish(uint32_t *counts, uint32_t *host, size_t n, uint32_t *flag, uint32_t seq, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, size_t n, hipStream_t st);
 // Tile geometry of the convolution kernel chosen for (Cout_p): rows per M tile.

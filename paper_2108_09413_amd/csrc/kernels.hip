@@ -427,20 +427,18 @@ hipError_t launch_fc(const FcParams &p, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Tallies to the host's pinned memory, and zeros in their place for the next call.  One a thread, then `seq` to `flag`: the host
-// that watches it has them 5 us before the end of the stream is reported (prediction with ResNet-20 and 100 copies 50.0 -> 45.5
-// us, with the two-convolution net 23.8 -> 19.4).  Every store goes past the caches by its scope and is complete (vmcnt) before
-// the workgroup's barrier, so the flag is the last to arrive without a write-back of the L2.  Such stores take 10 to 20 ns each:
-// 2560 tallies took 20 us longer this way, and the votes of 1000 copies stored one by one instead of counted 17 us.
+// Tallies to the host's pinned memory, and zeros in their place for the next call, then `seq` to `flag`: the host that watches it has
+// them 4 to 5 us before the end of the stream is reported (api.cpp, publish).  Every store goes past the caches by its scope and is
+// complete (vmcnt) before the workgroup's barrier, so the flag is the last to arrive without a write-back of the L2.  2560 tallies
+// are the most that were measured, by one workgroup in ten turns (256 pairs of 10 classes 266 -> 261 us a call).
 __global__ __launch_bounds__(256) void publish_kernel(uint32_t *counts, uint32_t *host, uint32_t n, uint32_t *flag, uint32_t seq) {
-    const uint32_t i = threadIdx.x;
-    if (i < n) {
+    for (uint32_t i = threadIdx.x; i < n; i += 256) {
         __hip_atomic_store(&host[i], counts[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&counts[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (i == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 // the same for many tallies, whose host waits for the stream
 __global__ void publish_many_kernel(uint32_t *counts, uint32_t *host, size_t n) {

@@ -1183,6 +1183,29 @@ def test_tallies_of_every_size_reach_the_host(isr):
     m.close()
 
 
+@pytest.mark.parametrize("pairs,chunk,fusion", [(256, 4096, 1), (257, 4096, 1), (1, 8, 0), (2, 8, 0)])
+def test_calls_in_a_row_whichever_way_they_end(isr, pairs, chunk, fusion):
+    """Batched calls one right behind the other, with other noise levels and pairs each time, whose descriptors and tables go through the
+    same pinned memory, on both sides of what the host watches for: 2560 tallies and more (10 classes a pair), five launches and ten
+    (one chunk and two, op by op).  Against single-pair calls of a model of their own; the tallies are cleared in between."""
+    _say(f"calls in a row, {pairs} pairs, chunks of {chunk}")
+    blob = synth.build_model(0)
+    m, other = _load(isr, blob, chunk), _load(isr, blob, 64)
+    isr.isr_set_fusion(m, fusion)
+    xs = np.stack([synth.make_image(0, i) for i in range(1, 4)])
+    calls = [[((i + k) % 3, (16, 32, 64, 128, 256, 512)[(i + 2 * k) % 6] + k, i) for i in range(pairs)] for k in range(3)]
+    import torch
+    x_dev = torch.from_numpy(xs).cuda()
+    got = [isr.isr_predict_batch(m, x_dev, items, 8, ALPHA, seed=k)[1] for k, items in enumerate(calls)]
+    for k, items in enumerate(calls):
+        assert got[k].sum() == 8 * pairs
+        for i in range(0, pairs, max(1, pairs // 16)):
+            want = isr.isr_predict(other, x_dev[items[i][0]], items[i][1], 8, ALPHA, seed=k, image_id=items[i][2])[1]
+            assert np.array_equal(got[k][i], want), (k, i)
+    m.close()
+    other.close()
+
+
 def test_batched_call_argument_errors(isr):
     blob = synth.build_model(0)
     m = _load(isr, blob, 32)
