@@ -77,12 +77,13 @@ hipError_t launch_noise(const NoiseParams &p, hipStream_t st) {
 // Noise bank: the discrete-Gaussian draws themselves (no image, no saturation), int16, for
 // noise that is sampled ahead of training and stored.  Same generator and counter layout as
 // above with the tensor index in the sample word, the bank id in the image word and phase 2.  The guide table (15 KB up
-// to sigma 169, 57 KB at sigma 1024) is staged into LDS; the thresholds stay in memory, for the few draws that it leaves open.
+// to sigma 169, 57 KB at sigma 1024) is staged into LDS, except for small banks (launch_noise_bank); the thresholds stay in memory,
+// for the few draws that it leaves open.
 //
 // Bound by the issue of the generator's and the sampler's integer arithmetic.  A draw is one LDS read and seven instructions up to
 // its word t, two and a half from there on: the guide word (bank_guide) has |draw| left of its bucket's threshold on top of the
 // threshold's 16 lowest float bits, so subtracting the draw's own bits borrows one where x lies behind the threshold and
-// leaves zeros below where that is open; sign and packing go by halves of a register.  81 instructions per four draws instead of
+// leaves zeros below where that is open; sign and packing go by halves of a register.  84 instructions per four draws instead of
 // 113 with noise_draw4, which keeps to guides of half the size up to sigma 86: there is less to stage for workgroups that draw
 // few pixels a thread (a net's first kernel on 32 x 32 images got 1 % slower with the words used here).
 // WHOLE: tensors of whole waves (d a multiple of 256).  A wave's draws then lie in one tensor, and what depends on the tensor
@@ -118,11 +119,15 @@ __device__ __forceinline__ void bank_draw4(const uint32_t *guide, const NoiseSam
     }
 }
 
+// WORDS == 0: the guide stays in memory (launch_noise_bank).
 template <int WORDS, int THREADS, bool WHOLE>
 __global__ __launch_bounds__(THREADS) void noise_bank_kernel(const NoiseBankParams p) {
-    __shared__ __attribute__((aligned(16))) uint32_t guide[WORDS];
-    for (uint32_t i = threadIdx.x; i < p.guide_words / 4; i += THREADS) ((uint4 *)guide)[i] = ((const uint4 *)p.guide)[i];
-    __syncthreads();
+    __shared__ __attribute__((aligned(16))) uint32_t staged[WORDS ? WORDS : 4];
+    const uint32_t *const guide = WORDS ? staged : p.guide;
+    if constexpr (WORDS != 0) {
+        for (uint32_t i = threadIdx.x; i < p.guide_words / 4; i += THREADS) ((uint4 *)staged)[i] = ((const uint4 *)p.guide)[i];
+        __syncthreads();
+    }
     const uint32_t groups_per_tensor = p.d >> 2;
     auto draw = [&](uint32_t grp, uint32_t t) {
         v2s d[2];
@@ -172,6 +177,14 @@ hipError_t launch_noise_bank(const NoiseBankParams &p, hipStream_t st) {
     if (p.count == 0) return hipSuccess;
     if (p.d == 0 || (p.d & 3) != 0 || p.s.reach < 1 || p.s.reach > 16384 || !p.thi || !p.tlo || !p.guide || !p.out) return hipErrorInvalidValue;
     if (p.guide_words * 4 <= (p.s.mask >> 1) || p.guide_words > 14336 || (p.guide_words & 3)) return hipErrorInvalidValue;   // the index's leading exponent bit is set for the largest x
+    // Small banks: the guide is not staged.  A workgroup would wait for all of it to make one step, which reads a few lines of its upper
+    // octaves.  From the second step of a thread on, with the large guides from half a step, those reads cost more.  us of a call, not
+    // staged / staged:
+    //   groups      40 k            130 k           237 k           521 k           768 k           1536 k
+    //   sigma 32    16.42 / 16.70                   17.41 / 17.65   18.70 / 19.13   19.74 / 19.65   23.25 / 22.30
+    //   sigma 300   16.51 / 17.15   16.98 / 17.40   17.57 / 17.71   19.08 / 18.94   20.28 / 19.70   24.04 / 22.25
+    //   sigma 900   17.87 / 18.70   18.70 / 19.22   19.48 / 19.68   21.18 / 21.13   22.63 / 21.97   27.19 / 24.97
+    if ((uint64_t)(p.d >> 2) * p.count <= 256 * (p.guide_words <= 3840 ? 2048 : 512)) return launch_noise_bank_guide<0, 256>(p, st);
     // the waves of a workgroup share a guide: large ones where eight workgroups' guides would not fit a CU
     if (p.guide_words <= 3840) return launch_noise_bank_guide<3840, 256>(p, st);
     if (p.guide_words <= 7680) return launch_noise_bank_guide<7680, 1024>(p, st);

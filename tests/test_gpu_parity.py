@@ -117,6 +117,17 @@ def test_noise_bank_tensors_of_whole_and_of_ragged_waves(isr, d, count):
         assert np.array_equal(got, oracle.noise_bank(sigma, 5, 11, 1000, count, d)), sigma
 
 
+@pytest.mark.parametrize("sigma,groups", [(3, 1), (86, 524288), (86, 524289), (169, 524288), (170, 131072), (170, 131073), (1024, 131072)])
+def test_small_banks_read_their_guide_from_memory(isr, sigma, groups):
+    """Banks of one step a thread and one group of four draws more, tensors of whole waves and ragged ones: the guide is read from
+    memory up to there, from LDS beyond."""
+    _say(f"small noise bank sigma={sigma} groups={groups}")
+    for d in (4, 256 if groups % 64 == 0 else 4 * groups):
+        count = 4 * groups // d
+        got = isr.isr_noise_bank(sigma, 9, 2, 17, count, d).cpu().numpy()
+        assert np.array_equal(got, oracle.noise_bank(sigma, 9, 2, 17, count, d)), d
+
+
 @pytest.mark.parametrize("sigma", [2, 32])
 def test_device_sampler_law_at_scale(isr, sigma):
     """1.5e8 draws of the device sampler (a full stored-noise bank) against Def. 3.3 itself:
