@@ -308,11 +308,22 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
         np.quant = 0;
         HIP_TRY(launch_float_noise(np, m->stream));
         work.push_back({last_kernel_name(), 0, 0.0, (double)bn * pm.H * pm.W * 16});
+        // what runs in one kernel, for this number of pixels: op i with the one after it, and with the one before it
+        auto expand_runs = [&](size_t i) {
+            FConvParams c = net.ops[i].conv;
+            c.npix = (int32_t)(bn * c.Ho * c.Wo);
+            return merged && net.ops[i].next && net.ops[i].out != stop_tensor && fexpand_wanted(c, net.ops[i + 1].conv);
+        };
+        auto pair_runs = [&](size_t i) {
+            FConvParams c = net.ops[i].conv;
+            c.npix = (int32_t)(bn * c.Ho * c.Wo);
+            return fconv_pair_wanted(c) || expand_runs(i);
+        };
         bool whole = !raw_noise && stop_tensor != 0;
         if (whole) {
             for (size_t i = 0; i < net.ops.size(); ++i) {
                 const FloatOp &f = net.ops[i];
-                if (f.paired && f.out != stop_tensor) continue;
+                if (f.paired && f.out != stop_tensor && pair_runs(i + 1)) continue;
                 if ((rc = mark()) != ISR_OK) return rc;
                 const TensorDesc &ti = pm.tensors[f.a], &to = pm.tensors[f.out];
                 const FloatOp *last = &f;   // of this launch
@@ -322,7 +333,7 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
                     FConvParams c = f.conv;
                     c.in = tptr(f.a);
                     c.out = f.type == OP_FC ? dlogits : tptr(f.out);
-                    if (f.pair >= 0) c.in2 = tptr(f.pair);
+                    if (f.pair >= 0 && pair_runs(i)) c.in2 = tptr(f.pair);
                     else c.res = f.res >= 0 ? tptr(f.res) : nullptr;
                     c.npix = (int32_t)(bn * c.Ho * c.Wo);
                     if (merged && f.next && net.ops[i + 1].type == OP_MAXPOOL) {
@@ -333,7 +344,7 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
                         last = &g;
                         break;
                     }
-                    if (merged && f.next && f.out != stop_tensor && fexpand_wanted(c, net.ops[i + 1].conv)) {
+                    if (expand_runs(i)) {
                         const FloatOp &g = net.ops[++i];
                         FConvParams r = g.conv;
                         r.out = tptr(g.out);
@@ -358,6 +369,10 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
                     break; }
                 }
                 work.push_back({last_kernel_name(), f.type == OP_CONV || f.type == OP_FC, f.flops * bn, f.bytes * bn});
+                if (f.pair >= 0 && !pair_runs(i)) {   // the op's own part of the pair, which reads the residual
+                    work.back().ops -= net.ops[i - 1].flops * bn;
+                    work.back().bytes -= (net.ops[i - 1].bytes - 8.0 * to.C * to.H * to.W) * bn;
+                }
                 if (last != &f) {   // what lies between the two is not read back, and stored only if it is a sum
                     const double between = 4.0 * to.C * to.H * to.W;
                     work.back().ops += last->flops * bn;

@@ -630,7 +630,9 @@ __global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
 // weights of all nine taps fit LDS together, so that the taps follow one another without a barrier.  Rows of LDS are 32 bytes, the two
 // chunks of every other group of eight rows exchanged, which keeps the rows that are read together in different banks.  Through the table
 // these layers were half of the fp32 nets on 32 x 32 images: largest launches of ResNet-110 on 1024 copies 421 -> 250 us, its
-// certification at n = 10 000 45.9 -> 32.8 ms (three workgroups a CU; 35.1 with two), ResNet-20's at 20 000 17.1 -> 12.7.
+// certification at n = 10 000 45.9 -> 32.8 ms (three workgroups a CU; 35.1 with two), ResNet-20's at 20 000 17.1 -> 12.7.  Of few copies
+// as well: certifications of ResNet-20 with 1 + 4, 1 + 100, 1 + 1000 copies 395 -> 325, 457 -> 367, 1189 -> 820 us, ResNet-110 with 1 + 4
+// 1935 -> 1510.
 template <int MT, int NL>   // 258 + 2 W <= 32 NL
 __global__ __launch_bounds__(256, MT == 1 ? 3 : 2) void fpatch16_kernel(const FConvParams p) {
     constexpr int BM = 32 * MT, NT = 2, BN = 128 * NT, ROWS = 32 * NL, ZERO = ROWS, PLANE = (ROWS + 1) * 32, TAP = BM * 32;
@@ -1197,6 +1199,15 @@ bool fconv_pair_supported(const FConvParams &p, const FConvParams &q) {
     return p.k == 1 && q.k == 1 && p.pad == 0 && q.pad == 0 && p.Cin_p % 32 == 0 && q.Cin_p % 32 == 0 && p.Cout_p == q.Cout_p && p.Cout_pp == q.Cout_pp &&
            p.Ho == q.Ho && p.Wo == q.Wo && p.Cout_pp % 128 == 0;
 }
+
+// The one kernel has one tile, of 128 pixels by 128 channels; the two take smaller ones where the pixels are few.  It pays from as many
+// tiles as half of the CUs.  fp32 ResNet-50, us of a run of 1, 4, 8, 16, 32, 64 copies:
+//   always paired            896   940  1031  1282  1685  2551
+//   from 96 tiles            869   920  1021  1284  1685  2553
+//   from 192                 869   921  1020  1280  1685  2552
+//   from 384                 869   925  1026  1290  1700  2560
+//   never                    871   925  1027  1304  1739  2629
+bool fconv_pair_wanted(const FConvParams &p) { return ((long)p.npix + 127) / 128 * (p.Cout_pp / 128) >= 128; }
 
 static hipError_t launch_fconv_pair(const FConvParams &p, hipStream_t st) {
     if (p.k != 1 || p.pad != 0 || p.Cin_p % 32 || p.Cin2_p <= 0 || p.Cin2_p % 32 || p.Cout_pp % 128 || !p.w2 || !p.bias2 || !p.scale2 || p.stride < 1 ||

@@ -395,7 +395,8 @@ struct FGapParams { const float *in; float *out; int32_t HW, Cp, B; float scale;
 struct FVoteParams { const float *logits; int32_t classes, stride, B; int32_t *argmax; uint32_t *counts; };
 hipError_t launch_float_noise(const FloatNoiseParams &p, hipStream_t st);
 hipError_t launch_fconv(const FConvParams &p, hipStream_t st);
-bool fconv_pair_supported(const FConvParams &p, const FConvParams &q);   // q's result as p's residual in one kernel
+bool fconv_pair_supported(const FConvParams &p, const FConvParams &q);   // q's result as p's residual in one kernel ...
+bool fconv_pair_wanted(const FConvParams &p);                            // ... for this number of pixels
 bool fexpand_supported(const FConvParams &p, const FConvParams &q);      // p with its add, and q that reads the sum, in one kernel ...
 bool fexpand_wanted(const FConvParams &p, const FConvParams &q);         // ... for this number of pixels
 hipError_t launch_fexpand(const FConvParams &p, const FConvParams &q, hipStream_t st);

@@ -223,6 +223,27 @@ def test_floatrs_fp_residual_computed_in_the_kernel(isr, closing_first, copies):
     m.close()
 
 
+def test_floatrs_fp_pairs_of_few_tiles_run_apart(isr):
+    """A closing layer and its projection as two kernels up to 127 tiles of 128 x 128, as one beyond, which writes the same bits."""
+    _say("FloatRS-fp pairs of few tiles")
+    from synth.models import NetBuilder
+    b = NetBuilder(rng=np.random.default_rng(86), in_shape=(3, 30, 28), num_classes=6)
+    t = b.conv(b.tensor(3, 30, 28, 0, 74.0), 64, 3, 1, 1, True)
+    u = b.conv(t, 96, 3, 2, 1, True)
+    r = b.conv(t, 496, 1, 2, 0, True)
+    t = b.add(b.conv(u, 496, 1, 1, 0, False), r, True)   # 15 x 14 pixels, four tiles of channels
+    b.fc(b.gap(t), 6)
+    m = _load(isr, b.blob(), 4 * 20)
+    x = np.random.default_rng(6).integers(0, 256, size=(3, 30, 28)).astype(np.uint8)
+    logits = {}
+    for copies, together in ((1, False), (18, False), (19, True)):   # 8, 120, 128 tiles
+        isr.isr_profile(m, 1)
+        logits[copies] = isr.isr_float_debug_forward(m, x, 63.75, 3, 1, 1, 50, copies, FP)[0]
+        assert any("pair" in k["name"] for k in isr.isr_profile_read(m)) == together
+    assert np.array_equal(logits[1], logits[19][:1]) and np.array_equal(logits[18], logits[19][:18])
+    m.close()
+
+
 @pytest.mark.parametrize("copies", [150, 305])
 @pytest.mark.parametrize("mid,out,reduced,pair", [(64, 128, 64, 0), (96, 512, 64, 0), (64, 384, 128, 0), (256, 512, 128, 0), (64, 128, 256, 0), (64, 384, 256, 0), (160, 1024, 256, 0),
                                                   (32, 128, 64, 1), (96, 512, 64, 2), (64, 512, 128, 1), (160, 256, 128, 2)])
