@@ -494,8 +494,15 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
 // of the error of the logits.  668 copies of ResNet-50's layers of 64 channels at
 // 56 x 56, 128 at 28 x 28, 256 at 14 x 14, 512 at 7 x 7, tap by tap -> from the run: 600 -> 450, 464 -> 374, 410 -> 345, 387 -> 331 us
 // (0.21 ms at the nominal rate of the matrix unit); 16 copies at 56 x 56: 27 -> 21 us.
+// Workgroups a CU: as many as LDS has room for, where registers allow (left to itself the compiler takes a few more than
+// three or four of them leave: 256 copies of the fp32 ResNet-50 at 96 x 96 2206 instead of 2072 us).
+template <int MT, int NL>
+constexpr int fpatch_workgroups() {
+    constexpr int fit = 160 * 1024 / (3 * 32 * MT * 64 + 3 * (32 * NL + 1) * 64);
+    return MT == 4 || fit < 2 ? 2 : MT == 2 && fit > 3 ? 3 : fit > 4 ? 4 : fit;
+}
 template <int MT, int NL>   // NL: rows of 32 pixels of the run, 130 + 2 W <= 32 NL
-__global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
+__global__ __launch_bounds__(256, (fpatch_workgroups<MT, NL>())) void fpatch_kernel(const FConvParams p) {
     constexpr int BM = 32 * MT, BN = 128, NST = 3, ASTAGE = BM * 64, NA = (BM + 63) / 64, ZERO = 32 * NL, PLANE = (32 * NL + 1) * 64;
     __shared__ __attribute__((aligned(256))) int8_t wt[NST * ASTAGE];
     __shared__ __attribute__((aligned(256))) int8_t run[3 * PLANE];
@@ -589,24 +596,34 @@ __global__ __launch_bounds__(256, 2) void fpatch_kernel(const FConvParams p) {
             const int row = ok ? centre + dy * p.W + dx : ZERO;
             const int at = row * 64 + ((half ^ swz<4>(row)) << 4);
             const int8_t *A = wt + buf * ASTAGE;
+            // The reads of the second half are issued before the last products of the first: they are complete at the next barrier
+            // without a wait there (13 layers of one copy's fp32 ResNet-50, where nothing hides it, 325 -> 300 us).
+            v4i af[2][MT], part[2][3];
+            auto read = [&](int ks) {
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                v4i af[MT], part[3];
+                for (int k = 2; k >= 0; --k) part[ks][k] = *(const v4i *)(run + k * PLANE + (at ^ (32 * ks)));
 #pragma unroll
                 for (int i = 0; i < MT; ++i) {
                     const int r = i * 32 + l32;
-                    af[i] = *(const v4i *)(A + r * 64 + (((2 * ks + half) ^ swz<4>(r)) << 4));
+                    af[ks][i] = *(const v4i *)(A + r * 64 + (((2 * ks + half) ^ swz<4>(r)) << 4));
                 }
+            };
+            read(0);
 #pragma unroll
-                for (int k = 0; k < 3; ++k) part[k] = *(const v4i *)(run + k * PLANE + (at ^ (32 * ks)));
+            for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-                for (int k = 2; k >= 0; --k)
+                for (int k = 2; k >= 0; --k) {
+                    if (ks == 0 && k == 0) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        read(1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
 #pragma unroll
                     for (int i = 0; i < MT; ++i) {
                         v16f &sum = TWO && k ? small[TWO ? i : 0] : acc[i][0];
-                        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, af[i]), __builtin_bit_cast(v8bf, part[k]), sum, 0, 0, 0);
+                        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, af[ks][i]), __builtin_bit_cast(v8bf, part[ks][k]), sum, 0, 0, 0);
                     }
-            }
+                }
             buf = buf == NST - 1 ? 0 : buf + 1;
         }
         if (more) {
