@@ -79,7 +79,8 @@ __device__ __forceinline__ void cos_sin_turn24(uint32_t t, float &co, float &si)
 
 // The correctly rounded root of x >= 0 (0, or far from the ends of the range).  The root instruction is off by at most one unit u, in a
 // sixth of the draws.  The root lies below the middle of s - u and s where x < (s - u/2)^2 = s (s - u) + u^2/4; x - s (s - u) is a
-// multiple of u^2, so that is where it is not positive, and one fused multiply-add has its sign.  The same above s.  Checked
+// multiple of u^2, so that is where it is not positive, and one fused multiply-add has its sign.  The same above s.  This is the
+// usual correction by the residuals at the neighbours (compilers expand a correctly rounded root this way).  Checked
 // against the binary64 root for all 2^24 arguments of the sampler; with that root, rounded once more, a certification of ResNet-20 on
 // rounded noise (10 100 copies) took 606.6 us, now 600.9.
 __device__ __forceinline__ float sqrt_rn(float x) {
@@ -484,6 +485,14 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
     fconv_finish_tile<PAIR>(p, acc, other, bs, px0, ch0, wave, lane, 4);
 }
 
+// Workgroups of fpatch_kernel a CU: as many as LDS has room for, where registers allow (left to itself the compiler takes a few more than
+// three or four of them leave: 256 copies of the fp32 ResNet-50 at 96 x 96 2206 instead of 2072 us).
+template <int MT, int NL>
+constexpr int fpatch_workgroups() {
+    constexpr int fit = 160 * 1024 / (3 * 32 * MT * 64 + 3 * (32 * NL + 1) * 64);
+    return MT == 4 || fit < 2 ? 2 : MT == 2 && fit > 3 ? 3 : fit > 4 ? 4 : fit;
+}
+
 // 3x3 layers of stride 1 with a border of one pixel: the nine taps of 128 consecutive pixels lie in one run of 130 + 2 W pixels.  The
 // workgroup splits 32 channels of that run once into three planes of bfloat16 in LDS, from which all nine taps read their
 // operands; tap by tap through fconv_kernel every pixel was fetched and split nine times, 44 instructions for 3 MT matrix instructions,
@@ -494,13 +503,6 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
 // of the error of the logits.  668 copies of ResNet-50's layers of 64 channels at
 // 56 x 56, 128 at 28 x 28, 256 at 14 x 14, 512 at 7 x 7, tap by tap -> from the run: 600 -> 450, 464 -> 374, 410 -> 345, 387 -> 331 us
 // (0.21 ms at the nominal rate of the matrix unit); 16 copies at 56 x 56: 27 -> 21 us.
-// Workgroups a CU: as many as LDS has room for, where registers allow (left to itself the compiler takes a few more than
-// three or four of them leave: 256 copies of the fp32 ResNet-50 at 96 x 96 2206 instead of 2072 us).
-template <int MT, int NL>
-constexpr int fpatch_workgroups() {
-    constexpr int fit = 160 * 1024 / (3 * 32 * MT * 64 + 3 * (32 * NL + 1) * 64);
-    return MT == 4 || fit < 2 ? 2 : MT == 2 && fit > 3 ? 3 : fit > 4 ? 4 : fit;
-}
 template <int MT, int NL>   // NL: rows of 32 pixels of the run, 130 + 2 W <= 32 NL
 __global__ __launch_bounds__(256, (fpatch_workgroups<MT, NL>())) void fpatch_kernel(const FConvParams p) {
     constexpr int BM = 32 * MT, BN = 128, NST = 3, ASTAGE = BM * 64, NA = (BM + 63) / 64, ZERO = 32 * NL, PLANE = (32 * NL + 1) * 64;
