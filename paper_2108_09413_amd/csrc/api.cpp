@@ -568,6 +568,7 @@ int isr::run_quant(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, u
 int isr::open_counts(isr_model *m) {
     if (!m->counts_clean) HIP_TRY(launch_fill_u32(m->dcounts, 0, 2 * (size_t)m->pm.classes, m->stream));
     m->counts_clean = false;
+    m->launches = 0;
     return ISR_OK;
 }
 // Tallies to the host and zeros on the device, by the last kernel of a call: nothing that the call was given is in use when its
@@ -591,7 +592,6 @@ int isr::open_counts(isr_model *m) {
 constexpr uint32_t WATCHED_LAUNCHES = 5;
 static int publish(isr_model *m, uint32_t *counts, uint32_t *host_dev, size_t n) {
     const bool watch = n <= PUBLISH_WATCHED && m->launches <= WATCHED_LAUNCHES;
-    m->launches = 0;
     if (!watch) {
         HIP_TRY(launch_publish(counts, host_dev, n, nullptr, 0, m->stream));
         HIP_TRY(hipStreamSynchronize(m->stream));
@@ -687,6 +687,7 @@ int prepare_batch(isr_model *m, const void *x, uint32_t n_images, const isr_item
     HIP_TRY(hipMemcpyAsync(m->ditems, m->hitems, sizeof(NoiseItem) * n_items, hipMemcpyHostToDevice, m->stream));
     if (!m->counts_b_clean) HIP_TRY(launch_fill_u32(m->dcounts_b, 0, (size_t)2 * m->items_cap * C, m->stream));
     m->counts_b_clean = false;
+    m->launches = 0;
     return ISR_OK;
 }
 

@@ -34,7 +34,7 @@ struct isr_model {
     uint32_t *hflag = nullptr, *hflag_dev = nullptr;       // one word in the same pinned allocation: number of the last call whose tallies arrived
     uint32_t published = 0;                                // of the last call that published some
     hipEvent_t end = nullptr;           // recorded behind tallies whose arrival the host watches
-    uint32_t launches = 0;              // since tallies were published last
+    uint32_t launches = 0;              // of the call that is running
     bool staging_busy = false;          // copies out of htables or hitems may be under way
     bool counts_clean = false, counts_b_clean = false;     // dcounts, dcounts_b hold zeros
     // batched calls: item descriptors and per-item vote counters, grown on demand
