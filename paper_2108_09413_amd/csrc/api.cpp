@@ -41,9 +41,16 @@ const char *isr::last_kernel_name() { return g_kernel_name; }
 namespace {
 
 // The pinned staging memory before it is written anew: copies out of it of an earlier call have ended.  Published tallies say so;
-// after a call that published none, or failed on its way, the stream's end does.
+// after a call that published none, or failed on its way, the stream's end does.  A stream that is being captured is refused, here
+// as by the synchronisation: a copy that is only recorded would leave its table marked as resident.
 int free_staging(isr_model *m) {
-    if (m->staging_busy) HIP_TRY(hipStreamSynchronize(m->stream));
+    if (m->staging_busy) {
+        HIP_TRY(hipStreamSynchronize(m->stream));
+    } else {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        HIP_TRY(hipStreamIsCapturing(m->stream, &capture));
+        if (capture != hipStreamCaptureStatusNone) HIP_TRY(hipErrorStreamCaptureUnsupported);
+    }
     m->staging_busy = false;
     return ISR_OK;
 }

@@ -1217,6 +1217,35 @@ def test_calls_in_a_row_whichever_way_they_end(isr, pairs, chunk, fusion):
     other.close()
 
 
+def test_calls_that_upload_are_refused_on_a_stream_being_captured(isr):
+    """A noise level that is not resident, and a batch: nothing is recorded, and the tables are right in the calls afterwards."""
+    import torch
+    _say("calls under capture")
+    blob = synth.build_model(0)
+    om = oracle.Model(blob)
+    x = synth.make_image(0, 1)
+    x_dev = torch.from_numpy(x).cuda()
+    m = isr.isr_load_model(blob)
+    stream = torch.cuda.Stream()
+    isr.isr_set_workspace(m, 64, stream=stream)
+    torch.cuda.synchronize()
+    isr.isr_predict_batch(m, x_dev[None], [(0, 32, 2)], 20, ALPHA, seed=1)   # its buffers are there
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        graph.capture_begin()
+        unused = x_dev.clone()
+        for call in (lambda: isr.isr_predict(m, x_dev, 64, 20, ALPHA, seed=1, image_id=2),
+                     lambda: isr.isr_predict_batch(m, x_dev[None], [(0, 128, 2)], 20, ALPHA, seed=1)):
+            with pytest.raises(isr.IsrError):
+                call()
+        graph.capture_end()
+    torch.cuda.synchronize()
+    for sigma in (64, 128, 32):
+        assert np.array_equal(isr.isr_predict(m, x_dev, sigma, 20, ALPHA, seed=1, image_id=2)[1], om.mc(x, sigma, 1, 2, 0, 0, 20)[2]), sigma
+        assert np.array_equal(isr.isr_predict_batch(m, x_dev[None], [(0, sigma, 2)], 20, ALPHA, seed=1)[1][0], om.mc(x, sigma, 1, 2, 0, 0, 20)[2]), sigma
+    m.close()
+
+
 def test_batched_call_argument_errors(isr):
     blob = synth.build_model(0)
     m = _load(isr, blob, 32)
