@@ -521,7 +521,7 @@ int run_slots(isr_model *m, const Plan &pl, const Draw &draw, int32_t *logits_ho
                 for (size_t i = op0; i < op1; ++i) {
                     const DevOp *d = &pl.ops[i];
                     const bool chain = op1 - i >= 3 && d[0].narrow == 16 && d[1].narrow == 32 && d[2].narrow == 64 && d[0].np.tail == 1 && d[1].np.tail == 1 &&
-                                       d[1].a == d[0].out && d[2].a == d[1].out && narrow_chain_wanted((int)bn);
+                                       d[1].a == d[0].out && d[2].a == d[1].out && narrow_chain_wanted((int)bn) && images_apart(pm, pl, i);
                     if ((prc = chain ? run_chain(d, j0, bn) : run_op(*d, j0, bn)) != ISR_OK) return prc;
                     if (chain) i += 2;
                 }

@@ -750,7 +750,8 @@ template <int C, int S, int NI, int NW>
 __global__ __launch_bounds__(64 * NW, C == 16 ? 4 : 2) void narrow_kernel(const NarrowParams p) { narrow_stage<C, S, NI, NW>(p); }
 
 // The three stages of a net in one launch (narrow_chain_wanted): a workgroup reads back only what it has written, so that nothing but
-// its barrier orders the stages.  The waves that the later ones do not take end early.
+// its barrier orders the stages; other images are at other stages meanwhile, so that the tensors have to lie apart (images_apart).
+// The waves that the later stages do not take end early.
 struct NarrowChain { NarrowParams stage[3]; };
 __global__ __launch_bounds__(512, 2) void narrow_chain_kernel(const NarrowChain c) {
     narrow_stage<16, 32, 1, 8>(c.stage[0]);

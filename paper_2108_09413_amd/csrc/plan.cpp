@@ -113,6 +113,23 @@ void plan_workspace(const ParsedModel &pm, uint32_t B, Plan &pl) {
     pl.bytes = pl.argmax_off + round_up((size_t)B * 4, 256);
 }
 
+// The placement above gives a tensor's space away once its last reader has been issued, and an op's output never lies over that
+// op's own input; a later op's may.  Over the same image's bytes it may in one launch too: its workgroup has read them.
+bool images_apart(const ParsedModel &pm, const Plan &pl, size_t i) {
+    auto bytes = [&](int t) { const TensorDesc &d = pm.tensors[t]; return (size_t)d.H * d.W * d.Cp; };   // of an image
+    for (size_t w = 1; w < 3; ++w) {
+        const DevOp &o = pl.ops[i + w];
+        if (o.head || o.type == OP_FC) continue;   // writes no tensor
+        for (size_t r = 0; r < w; ++r) {
+            const int in = pl.ops[i + r].a;
+            const size_t at = pl.toff[in], to = pl.toff[o.out], n = bytes(in), m = bytes(o.out);
+            const bool same = at == to && n == m, overlap = at < to + m * pl.chunk && to < at + n * pl.chunk;
+            if (overlap && !same) return false;
+        }
+    }
+    return true;
+}
+
 uint32_t plan_copies(const ParsedModel &pm, uint32_t B, size_t bytes, const Plan &pl) {
     for (const DevOp &d : pl.ops)
         if (!d.narrow) return B;

@@ -80,6 +80,9 @@ void plan_segments(const ParsedModel &pm, uint32_t B, Plan &pl);
 uint32_t plan_copies(const ParsedModel &pm, uint32_t B, size_t bytes, const Plan &pl);
 // Offsets of every tensor of a chunk of B samples in the workspace.
 void plan_workspace(const ParsedModel &pm, uint32_t B, Plan &pl);
+// Whether ops i, i + 1, i + 2 of a placed plan, each reading the one before, can run image by image side by side: nothing that one of
+// them writes lies where another image's input of an op before it does.
+bool images_apart(const ParsedModel &pm, const Plan &pl, size_t i);
 
 }  // namespace isr
 
