@@ -32,7 +32,7 @@ struct FloatOp {
     int res = -1;                  // tensor read by the residual add folded into the convolution, or -1
     int pair = -1;                 // the op before, whose result is that tensor, runs in this op's kernel: its input tensor
     int paired = 0;                // this op runs in the next one's kernel (alone only where its own result is asked for)
-    int next = 0;                  // the next op, which reads this one's sum, can run in this op's kernel
+    int next = 0;                  // the next op, which reads this one's result, can run in this op's kernel
     float ma = 0.f, mb = 0.f;      // ADD
     int relu = 0;
     FPoolParams pool{};
@@ -40,12 +40,17 @@ struct FloatOp {
     double flops = 0.0, bytes = 0.0;   // per copy: 2 per multiply-accumulate on real channels; fp32 bytes in + out
 };
 
+// Ops that run in the kernel of the op before: none, poolings (of first layers), readers of sums as well.
+enum FloatJoin { JOIN_NONE, JOIN_POOLS, JOIN_ALL };
+
 struct FloatNet {
     std::vector<FloatOp> ops;
     // tensor placement: the ops' tensor ids with the int8 planner, whose bytes for B copies hold B / 4 fp32 copies; `merged` with the
-    // results of ops that can run in one kernel placed together, which can take more, and is used where the workspace has it
+    // results of ops that can run in one kernel placed together, which can take more: of as many kinds of them as the workspace has room for
     Plan plan, merged;
+    FloatJoin joins = JOIN_NONE;   // of `merged`
     uint32_t planned_chunk = 0;
+    size_t planned_bytes = 0;      // of the workspace that `merged` is for
     uint8_t *dconst = nullptr;
     int status = ISR_OK;           // ISR_ERR_UNSUPPORTED when an op has no float kernel
 };
@@ -220,41 +225,56 @@ int build_float_net(isr_model *m) {
         f.next = f.type == OP_CONV && g.type == OP_CONV && f.res >= 0 && !f.paired && g.a == f.out && g.res < 0 && g.pair < 0 && !g.paired &&
                  fexpand_supported(f.conv, g.conv);
     }
-    for (size_t i = 0; i < net->ops.size(); ++i) {   // what the planner looks at: op type and tensor ids
-        const FloatOp &f = net->ops[i];
-        if (f.paired) continue;
-        DevOp d{};
-        d.type = f.type; d.a = f.a; d.b = f.pair >= 0 ? f.pair : f.res >= 0 ? f.res : f.b; d.out = f.out;
-        net->plan.ops.push_back(d);
-        if (i && net->ops[i - 1].next) {
-            DevOp &both = net->merged.ops.back();
-            (f.type == OP_MAXPOOL ? both.out : both.out2) = f.out;
-            continue;
-        }
-        net->merged.ops.push_back(d);
-    }
     return net->status = ISR_OK;
 }
 
-// Places the float network's tensors for chunks of m->chunk int8-sized copies (a quarter as many fp32 copies).
-int plan_float_net(isr_model *m, uint32_t chunk_samples) {
-    FloatNet &net = *m->fnet;
-    if (net.planned_chunk != chunk_samples) {
-        for (Plan *pl : {&net.plan, &net.merged}) {
-            plan_workspace(m->pm, chunk_samples, *pl);
-            // a result that is stored only where it is asked for lies where the op that else computes it will put its own
-            for (const FloatOp &f : net.ops)
-                if (f.pair >= 0) pl->toff[f.res] = pl->toff[f.out];
-        }
-        net.planned_chunk = chunk_samples;
-    }
-    return ISR_OK;
+// Whether op i + 1 of the net is one of those.
+bool float_joined(const FloatNet &net, size_t i, FloatJoin joins) {
+    return net.ops[i].next && joins >= (net.ops[i + 1].type == OP_MAXPOOL ? JOIN_POOLS : JOIN_ALL);
 }
 
-// The placement for forwards that end at `stop_tensor` (-1: at the votes): `merged` where the workspace has room and that tensor a place.
+// Places the float network's tensors for chunks of so many int8-sized copies (a quarter as many fp32 copies), the results of joined ops together.
+void place_float_net(const isr_model *m, uint32_t chunk_samples, FloatJoin joins, Plan &pl) {
+    const FloatNet &net = *m->fnet;
+    pl.ops.clear();
+    for (size_t i = 0; i < net.ops.size(); ++i) {   // what the planner looks at: op type and tensor ids
+        const FloatOp &f = net.ops[i];
+        if (f.paired) continue;
+        if (i && float_joined(net, i - 1, joins)) {
+            DevOp &both = pl.ops.back();
+            (f.type == OP_MAXPOOL ? both.out : both.out2) = f.out;
+            continue;
+        }
+        DevOp d{};
+        d.type = f.type; d.a = f.a; d.b = f.pair >= 0 ? f.pair : f.res >= 0 ? f.res : f.b; d.out = f.out;
+        pl.ops.push_back(d);
+    }
+    plan_workspace(m->pm, chunk_samples, pl);
+    // a result that is stored only where it is asked for lies where the op that else computes it will put its own
+    for (const FloatOp &f : net.ops)
+        if (f.pair >= 0) { pl.toff[f.res] = pl.toff[f.out]; pl.has[f.res] = 1; }
+}
+
+// Both placements for a workspace of `bytes`, which hold the one op by op.  A first layer with its pooling adds its products in another
+// order than the two apart, so isr_float_workspace_bytes asks for the room that they take; what reads a sum is joined where there
+// is more, with the same bits.
+void plan_float_net(isr_model *m, uint32_t chunk_samples, size_t bytes) {
+    FloatNet &net = *m->fnet;
+    if (net.planned_chunk == chunk_samples && net.planned_bytes == bytes) return;
+    place_float_net(m, chunk_samples, JOIN_NONE, net.plan);
+    for (FloatJoin joins : {JOIN_ALL, JOIN_POOLS, JOIN_NONE}) {
+        net.joins = joins;
+        place_float_net(m, chunk_samples, joins, net.merged);
+        if (net.merged.bytes <= bytes) break;
+    }
+    net.planned_chunk = chunk_samples;
+    net.planned_bytes = bytes;
+}
+
+// The placement for forwards that end at `stop_tensor` (-1: at the votes): `merged` unless it has no place for that tensor.
 const Plan &float_plan(const isr_model *m, int stop_tensor) {
     const FloatNet &net = *m->fnet;
-    return net.merged.bytes <= m->ws_bytes && (stop_tensor < 0 || net.merged.has[stop_tensor]) ? net.merged : net.plan;
+    return stop_tensor < 0 || net.merged.has[stop_tensor] ? net.merged : net.plan;
 }
 
 // Copies per chunk of the fp32 network: tensors sit at the offsets of the op-by-op int8 plan, four
@@ -312,7 +332,7 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
         auto expand_runs = [&](size_t i) {
             FConvParams c = net.ops[i].conv;
             c.npix = (int32_t)(bn * c.Ho * c.Wo);
-            return merged && net.ops[i].next && net.ops[i].out != stop_tensor && fexpand_wanted(c, net.ops[i + 1].conv);
+            return merged && float_joined(net, i, net.joins) && net.ops[i].out != stop_tensor && fexpand_wanted(c, net.ops[i + 1].conv);
         };
         auto pair_runs = [&](size_t i) {
             FConvParams c = net.ops[i].conv;
@@ -336,7 +356,7 @@ int run_fp_range(isr_model *m, const uint8_t *x, float sigma, uint64_t seed, uin
                     if (f.pair >= 0 && pair_runs(i)) c.in2 = tptr(f.pair);
                     else c.res = f.res >= 0 ? tptr(f.res) : nullptr;
                     c.npix = (int32_t)(bn * c.Ho * c.Wo);
-                    if (merged && f.next && net.ops[i + 1].type == OP_MAXPOOL) {
+                    if (merged && float_joined(net, i, net.joins) && net.ops[i + 1].type == OP_MAXPOOL) {
                         const FloatOp &g = net.ops[++i];
                         FPoolParams q = g.pool;
                         q.out = tptr(g.out); q.B = (int32_t)bn;
@@ -428,7 +448,7 @@ int check_float_call(isr_model *m, const void *x, float sigma, int system) {
     if (system == ISR_FLOATRS_FP) {
         const int rc = build_float_net(m);
         if (rc != ISR_OK) return rc;
-        plan_float_net(m, m->chunk);
+        plan_float_net(m, m->chunk, m->ws_bytes);
         if (float_chunk(m) == 0 || m->fnet->plan.bytes > m->ws_bytes) return ISR_ERR_WORKSPACE;
     }
     return ISR_OK;
@@ -449,8 +469,13 @@ size_t isr_float_workspace_bytes(isr_model *m, uint32_t chunk_samples, int syste
     if (!m || chunk_samples == 0) return 0;
     if (system == ISR_FLOATRS_QUANT) return isr_workspace_bytes(m, chunk_samples);
     if (system != ISR_FLOATRS_FP || build_float_net(m) != ISR_OK) return 0;
-    plan_float_net(m, chunk_samples);
-    return std::max(m->fnet->plan.bytes, isr_workspace_bytes(m, chunk_samples));
+    size_t need = isr_workspace_bytes(m, chunk_samples);
+    Plan pl;
+    for (FloatJoin joins : {JOIN_NONE, JOIN_POOLS}) {
+        place_float_net(m, chunk_samples, joins, pl);
+        need = std::max(need, pl.bytes);
+    }
+    return need;
 }
 
 uint32_t isr_float_chunk(const isr_model *m, int system) {

@@ -244,6 +244,36 @@ def test_floatrs_fp_pairs_of_few_tiles_run_apart(isr):
     m.close()
 
 
+def test_floatrs_fp_joined_layers_each_where_the_workspace_has_room(isr):
+    """A first layer with its pooling, and sums one of whose readers has no room beside it (256 channels next to 128): in a workspace
+    of the size asked for the first layer and its pooling are joined alone, in twice that all; the logits are the same to the bit."""
+    _say("FloatRS-fp joined layers and the workspace")
+    import torch
+    from synth.models import NetBuilder
+    b = NetBuilder(rng=np.random.default_rng(87), in_shape=(3, 32, 28), num_classes=6)
+    t = b.maxpool(b.conv(b.tensor(3, 32, 28, 0, 74.0), 64, 7, 2, 3, True), 3, 2, 1)   # 8 x 7 pixels
+    r = b.conv(t, 128, 1, 1, 0, True)
+    t = b.add(b.conv(b.conv(r, 64, 1, 1, 0, True), 128, 1, 1, 0, False), r, True)
+    t = b.add(b.conv(b.conv(t, 128, 1, 1, 0, True), 128, 1, 1, 0, False), t, True)
+    t = b.conv(t, 256, 1, 1, 0, True)
+    b.fc(b.gap(t), 6)
+    chunk, copies = 4 * 900, 900
+    m = _load(isr, b.blob(), chunk)
+    bytes_ = isr.lib().isr_float_workspace_bytes(m.handle, chunk, FP)
+    x = torch.from_numpy(np.random.default_rng(7).integers(0, 256, size=(3, 32, 28)).astype(np.uint8)).cuda()
+    room = torch.empty(2 * bytes_ + 256, dtype=torch.uint8, device="cuda")
+    logits = []
+    for size, kernels in ((bytes_, {"fstem_pool_kernel"}), (2 * bytes_, {"fstem_pool_kernel", "fexpand_kernel<128>", "fexpand_kernel<256>"})):
+        at = (room.data_ptr() + 255) // 256 * 256
+        isr._check(isr.lib().isr_set_workspace(m.handle, ctypes.c_void_p(at), size, chunk, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)), "isr_set_workspace")
+        isr.isr_profile(m, 1)
+        logits.append(isr.isr_float_debug_forward(m, x, 63.75, 3, 1, 1, 50, copies, FP)[0])
+        names = {k["name"] for k in isr.isr_profile_read(m)}
+        assert {n for n in names if n.startswith(("fstem_pool", "fexpand"))} == kernels, names
+    assert np.array_equal(logits[0], logits[1])
+    m.close()
+
+
 @pytest.mark.parametrize("copies", [150, 305])
 @pytest.mark.parametrize("mid,out,reduced,pair", [(64, 128, 64, 0), (96, 512, 64, 0), (64, 384, 128, 0), (256, 512, 128, 0), (64, 128, 256, 0), (64, 384, 256, 0), (160, 1024, 256, 0),
                                                   (32, 128, 64, 1), (96, 512, 64, 2), (64, 512, 128, 1), (160, 256, 128, 2)])
