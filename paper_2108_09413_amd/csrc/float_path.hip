@@ -8,6 +8,7 @@
 
 #include "conv_device.h"
 #include "isr_internal.h"
+#include "nearest_root.h"
 #include "noise_device.h"
 
 namespace isr {
@@ -77,18 +78,9 @@ __device__ __forceinline__ void cos_sin_turn24(uint32_t t, float &co, float &si)
     si = __uint_as_float(__float_as_uint(quarter ? p : q) ^ ((t << 8) & 0x80000000u));
 }
 
-// The correctly rounded root of x >= 0 (0, or far from the ends of the range).  The root instruction is off by at most one unit u, in a
-// sixth of the draws.  The root lies below the middle of s - u and s where x < (s - u/2)^2 = s (s - u) + u^2/4; x - s (s - u) is a
-// multiple of u^2, so that is where it is not positive, and one fused multiply-add has its sign.  The same above s.  This is the
-// usual correction by the residuals at the neighbours (compilers expand a correctly rounded root this way).  Checked
-// against the binary64 root for all 2^24 arguments of the sampler; with that root, rounded once more, a certification of ResNet-20 on
-// rounded noise (10 100 copies) took 606.6 us, now 600.9.
-__device__ __forceinline__ float sqrt_rn(float x) {
-    const float s = __builtin_amdgcn_sqrtf(x);
-    const float below = __uint_as_float(__float_as_uint(s) - 1u), above = __uint_as_float(__float_as_uint(s) + 1u);   // of 0: NaN, which is neither
-    const float r = __builtin_fmaf(-below, s, x) <= 0.0f ? below : s;
-    return __builtin_fmaf(-above, s, x) > 0.0f ? above : r;
-}
+// The root instruction is off by at most one unit, in a sixth of the draws.  With the binary64 root, rounded once more, a certification of
+// ResNet-20 on rounded noise (10 100 copies) took 606.6 us, with this 600.9.
+__device__ __forceinline__ float sqrt_rn(float x) { return nearest_root(x, __builtin_amdgcn_sqrtf(x)); }
 
 __device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float &za, float &zb) {
 #pragma clang fp contract(off)
