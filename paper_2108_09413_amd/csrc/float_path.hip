@@ -342,7 +342,7 @@ __global__ __launch_bounds__(256, 2) void fconv_kernel(const FConvParams p) {
         for (int j = 0; j < NA; ++j)
             if (BM >= 64 || wave < 2)
                 ISR_GLOBAL_TO_LDS16_AT(wsrc + (size_t)(ADDR == F_TAP ? (dy * p.k + dx) * (p.Cin_p >> 5) + (c0 >> 5) : step) * p.Cout_pp * 64 + j * 4096, a + j * 4096);
-        if constexpr (ADDR == F_FLAT || ADDR == F_PAIR) {
+        if constexpr (ADDR == F_FLAT) {
 #pragma unroll
             for (int j = 0; j < NB; ++j) ISR_GLOBAL_TO_LDS16_AT(in + (boff[j] + (uint32_t)step * 128u), b + j * 4096);
         } else {
