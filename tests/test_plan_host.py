@@ -72,19 +72,18 @@ def test_stages_of_different_images_lie_apart(plan_host, tmp_path, last, first):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("last", ["max pooling", "convolution", "nothing"])
-def test_stages_whose_result_is_stored_run_in_launches_of_their_own(last):
-    print(f"three stages, then {last}", flush=True)
-    m = isr.isr_load_model(three_stages(last))
+@pytest.mark.parametrize("last,first,together", [("max pooling", "3x3", False), ("convolution", "3x3", False), ("nothing", "5x5", False), ("pooling", "5x5", True)])
+def test_stages_whose_result_is_stored_run_in_launches_of_their_own(last, first, together):
+    """256 copies against the op-by-op kernels; with a 5x5 first layer the first stage reads its input from memory."""
+    print(f"{first} first layer, three stages, then {last}", flush=True)
+    m = isr.isr_load_model(three_stages(last, first))
     isr.isr_set_workspace(m, 256)
     x = np.random.default_rng(13).integers(0, 256, size=(3, 32, 32)).astype(np.uint8)
-    import torch
-    x_dev = torch.from_numpy(x).cuda()
     isr.isr_profile(m, 1)
-    fused = isr.isr_debug_forward(m, x_dev, 64, 2, 1, 1, 100, 256)
+    fused = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 100, 256)
     names = [k["name"] for k in isr.isr_profile_read(m)]
-    assert sum(n.startswith("narrow_kernel") for n in names) == 3 and "narrow_chain_kernel" not in names, names
+    assert [sum(n.startswith(k) for n in names) for k in ("narrow_kernel", "narrow_chain_kernel")] == ([0, 1] if together else [3, 0]), names
     isr.isr_set_fusion(m, 0)
-    for a, b in zip(fused, isr.isr_debug_forward(m, x_dev, 64, 2, 1, 1, 100, 256)):
+    for a, b in zip(fused, isr.isr_debug_forward(m, x, 64, 2, 1, 1, 100, 256)):
         assert np.array_equal(a, b)
     m.close()
