@@ -144,39 +144,23 @@ int build_narrow_ops(isr_model *m, ConstArena &arena, size_t limit) {
     std::vector<NarrowBlock> blocks;
     std::vector<int32_t> consts;
     auto host = [&](const int32_t *dev) { return (const int32_t *)(arena.host.data() + ((const uint8_t *)dev - m->dconst)); };
-    // one shift for all channels
-    auto one_shift = [&](const ConvParams &c) {
-        const int32_t *s = host(c.shm1);
-        for (int i = 1; i < c.Cout_p; ++i)
-            if (s[i] != s[0]) return false;
-        return true;
-    };
-    auto form_of = [&](int rq, bool add_top, std::initializer_list<const ConvParams *> convs) {
-        bool uniform = true;
-        for (const ConvParams *c : convs) uniform = uniform && one_shift(*c);
-        return rq == RQ_TOP && uniform ? (add_top ? 0 : 1) : 2;
-    };
-    auto pack = [&](const ConvParams &c, int form) {   // [4][C], returns its offset
+    auto form_of = [](int rq, int add_rq) { return !(rq & RQ_PAIR) ? 2 : add_rq & RQ_PAIR ? 0 : 1; };
+    auto pack = [&](const ConvParams &c) {   // [4][C], returns its offset
         const size_t off = consts.size();
         const int C = c.Cout_p;
         consts.resize(off + 4 * C);
         int32_t *k = consts.data() + off;
         for (int i = 0; i < C; ++i) {
-            const int shm1 = host(c.shm1)[i];
             k[i] = host(c.bias)[i];
             k[C + i] = host(c.m0s)[i];
-            k[2 * C + i] = form < 2 ? (int32_t)((uint32_t)host(c.chi)[i] << (24 - shm1)) : host(c.chi)[i];
-            k[3 * C + i] = form < 2 ? 1 << (24 - shm1) : shm1;
+            k[2 * C + i] = host(c.chi)[i];
+            k[3 * C + i] = host(c.shm1)[i];
         }
         return off;
     };
-    auto add_of = [](const ConvParams &c, bool top) {
-        AddConst a{c.add_mul_self, c.add_mul_res, c.add_c0, c.add_k, c.add_sh, c.add_lo};
-        if (top) {   // as add_const of the kernels
-            const int s = 23 - c.add_sh;
-            a = AddConst{c.add_mul_self << s, c.add_mul_res << s, (c.add_c0 + c.add_k) << s, 0, 0, 0};
-        }
-        return a;
+    auto add_of = [](const ConvParams &c, bool pair) {   // as add_const of the kernels
+        return pair ? AddConst{c.add_mul_self, c.add_mul_res, c.add_c0 + c.add_k, 0, c.add_sh, 0}
+                    : AddConst{c.add_mul_self, c.add_mul_res, c.add_c0, c.add_k, c.add_sh, c.add_lo};
     };
     auto lo_of = [](const ConvParams &c) { return c.relu ? c.zp_out : -128; };
     for (int pi = 1; pi <= 2; ++pi)
@@ -188,38 +172,38 @@ int build_narrow_ops(isr_model *m, ConstArena &arena, size_t limit) {
                 const ConvParams &c1 = q.conv, &c2 = q.conv2, &cp = q.conv3;
                 if (q.stem16) {
                     np.stem = 1;
-                    np.form0 = form_of(c1.rq, true, {&c1});
+                    np.form0 = form_of(c1.rq, RQ_PAIR);
                     np.w0 = c1.w; np.zp_in = c1.zp_in; np.lo0 = lo_of(c1);
-                    np.prm0 = (const int32_t *)(pack(c1, np.form0) + 1);
+                    np.prm0 = (const int32_t *)(pack(c1) + 1);
                 } else if (q.block) {
                     np.nblocks = (int32_t)q.chain.size();
                     np.blocks = (const NarrowBlock *)(blocks.size() + 1);
                     for (const auto &blk : q.chain) {
                         const ConvParams &a = blk.first, &b = blk.second;
                         NarrowBlock nb{};
-                        nb.form = form_of(a.rq & b.rq, b.add_rq == RQ_TOP, {&a, &b});
+                        nb.form = form_of(a.rq & b.rq, b.add_rq);
                         nb.w1 = a.w; nb.w2 = b.w;
-                        nb.prm1 = (const int32_t *)pack(a, nb.form);
-                        nb.prm2 = (const int32_t *)pack(b, nb.form);
+                        nb.prm1 = (const int32_t *)pack(a);
+                        nb.prm2 = (const int32_t *)pack(b);
                         nb.zp_x = a.zp_in; nb.zp_t = a.zp_out; nb.lo1 = lo_of(a); nb.lo2 = lo_of(b);
                         nb.add = add_of(b, nb.form == 0);
                         blocks.push_back(nb);
                     }
                 } else if (q.trans) {
                     np.tail = 1;
-                    np.tform = form_of(c1.rq & c2.rq & cp.rq, rq_is_top(cp.add_rq), {&c1, &c2, &cp});
+                    np.tform = form_of(c1.rq & c2.rq & cp.rq, cp.add_rq);
                     np.tw1 = c1.w; np.tw2 = c2.w; np.twp = cp.w;
-                    np.tprm = (const int32_t *)(pack(c1, np.tform) + 1);
-                    pack(c2, np.tform);
-                    pack(cp, np.tform);
+                    np.tprm = (const int32_t *)(pack(c1) + 1);
+                    pack(c2);
+                    pack(cp);
                     np.tzp_x = c1.zp_in; np.tzp_t = c1.zp_out;
                     np.tlo1 = lo_of(c1); np.tlo2 = lo_of(c2); np.tlop = lo_of(cp);
                     np.tadd = add_of(cp, np.tform == 0);
                 } else if (q.type == OP_CONV) {
                     np.tail = 2;
-                    np.tform = form_of(c1.rq, true, {&c1});
+                    np.tform = form_of(c1.rq, RQ_PAIR);
                     np.tw1 = c1.w;
-                    np.tprm = (const int32_t *)(pack(c1, np.tform) + 1);
+                    np.tprm = (const int32_t *)(pack(c1) + 1);
                     consts.resize(consts.size() + 2 * 4 * c1.Cout_p);   // the kernel stages three convolutions' constants
                     np.tzp_x = c1.zp_in; np.tzp_t = c1.zp_out; np.tlo1 = lo_of(c1);
                 } else if (q.type == OP_GAP) {
@@ -406,7 +390,7 @@ int run_slots(isr_model *m, const Plan &pl, const Draw &draw, int32_t *logits_ho
                     bp.zp_t1 = c1.zp_out;
                     bp.lo1 = c1.relu ? c1.zp_out : -128;
                     bp.lo2 = c2.relu ? c2.zp_out : -128;
-                    bp.rq = c1.rq & c2.rq; bp.add_rq = 3;
+                    bp.rq = c1.rq & c2.rq; bp.add_rq = RQ_TOP | RQ_PAIR;
                     if (bp.tail) {
                         // the closing 1x1 convolution; with a projection shortcut (bneck == 4) conv3 carries two
                         // convolutions, and either of them may be the one that reads the block input
@@ -419,7 +403,7 @@ int run_slots(isr_model *m, const Plan &pl, const Draw &draw, int32_t *logits_ho
                         bp.add_mul_self = swap ? c3.add_mul_res : c3.add_mul_self;   // "self" in the kernel = the closing convolution
                         bp.add_mul_res = swap ? c3.add_mul_self : c3.add_mul_res;
                         bp.add_c0 = c3.add_c0; bp.add_k = c3.add_k; bp.add_sh = c3.add_sh; bp.add_lo = c3.add_lo;
-                        bp.rq &= c3.rq & (d.bneck == 4 ? c3.rq2 : 3);
+                        bp.rq &= c3.rq & (d.bneck == 4 ? c3.rq2 : ~0);
                         bp.add_rq = c3.add_rq;
                         if (d.bneck == 4) {
                             bp.proj = 1;

@@ -239,6 +239,7 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
         int mm[16], ch[16], ss[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) { mm[i] = prm[0][1][c16 + i]; ch[i] = prm[0][2][c16 + rq_chi_at<RQ>(i)]; ss[i] = prm[0][3][c16 + i]; }
+        const RqLayer L = rq_layer<RQ>(prm[0][2][0], prm[0][3][0]);
 #pragma unroll
         for (int f = 0; f < 3; ++f) {
             if (f == 2 && n1 != 3) continue;   // wave-uniform
@@ -246,8 +247,8 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
             const bool ok = h < NHALO && (unsigned)y < (unsigned)p.H && (unsigned)x < (unsigned)p.W;
             int q[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(acc[f][i], mm[i], ch[i], ss[i], p.lo1);
-            v4i v = rq_pack16<RQ>(q);
+            for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(acc[f][i], mm[i], ch[i], ss[i], p.lo1, L);
+            v4i v = rq_pack16<RQ>(q, L);
             if (!ok) v = v4i{(int)zt, (int)zt, (int)zt, (int)zt};
             if (h < NHALO) *(v4i *)(T + h * TP + (wm * 2 + half) * 16) = v;
         }
@@ -300,13 +301,14 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
         int mm[16], ch[16], ss[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) { mm[i] = prm[1][1][c16 + i]; ch[i] = prm[1][2][c16 + rq_chi_at<RQ>(i)]; ss[i] = prm[1][3][c16 + i]; }
+        const RqLayer L = rq_layer<RQ>(prm[1][2][0], prm[1][3][0]);
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
             if (f == 1 && nfr != 2) { t2[f] = v4i{0, 0, 0, 0}; continue; }
             int q[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(acc[f][i], mm[i], ch[i], ss[i], p.lo2);
-            t2[f] = rq_pack16<RQ>(q);
+            for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(acc[f][i], mm[i], ch[i], ss[i], p.lo2, L);
+            t2[f] = rq_pack16<RQ>(q, L);
         }
     }
     if constexpr (!TAIL) {
@@ -338,7 +340,8 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
         const AddConst ac = add_const<RQA>(p);
         const int m0 = wave * 32, c0 = m0 + 16 * half;   // the lane's 16 channels
         auto pixel = [&](int f) { return at_s[f * 32 + l].x; };
-        // the fragments of one 1x1 convolution from 64 channels: operand(f, K half), then use(f, requantised values)
+        // the fragments of one 1x1 convolution from 64 channels: operand(f, K half), then use(f, results of rq_conv)
+        constexpr bool KEEP = rq_is_top(RQ) || RQ == RQ_PAIR;
         auto conv64 = [&](const v4i (&fa)[2], const auto &prm, int lo, auto first, auto end, auto operand, auto use) {
             asm volatile("" ::: "memory");
             int mm[16], ch[16], ss[16];
@@ -346,7 +349,8 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) { mm[i] = prm[1][c0 + i]; ch[i] = prm[2][c0 + rq_chi_at<RQ>(i)]; ss[i] = prm[3][c0 + i]; }
             };
-            if constexpr (rq_is_top(RQ)) constants();
+            const RqLayer L = rq_layer<RQ>(prm[2][0], prm[3][0]);
+            if constexpr (KEEP) constants();
 #pragma unroll
             for (int f = decltype(first)::value; f < decltype(end)::value; ++f) {
                 asm volatile("" ::: "memory");
@@ -356,11 +360,11 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
                 for (int i = 0; i < 16; ++i) a[i] = prm[0][c0 + i];
 #pragma unroll
                 for (int ksub = 0; ksub < 2; ++ksub) a = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ksub], operand(f, ksub), a, 0, 0, 0);
-                if constexpr (!rq_is_top(RQ)) constants();
+                if constexpr (!KEEP) constants();
                 int q[16];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(a[i], mm[i], ch[i], ss[i], lo);
-                use(f, q);
+                for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(a[i], mm[i], ch[i], ss[i], lo, L);
+                use(f, q, L);
             }
         };
         if constexpr (PROJ) {
@@ -379,23 +383,23 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
                     if (f + 1 < NP_FR) fetch(f + 1);
                 }
                 return x[ksub];
-            }, [&](int f, const int (&q)[16]) {
-                resid[f] = rq_pack16<RQ>(q);
+            }, [&](int f, const int (&q)[16], const RqLayer &L) {
+                resid[f] = rq_pack16<RQ>(q, L);
                 asm volatile("" : "+v"(resid[f]));   // packed: the compiler would keep the sixteen values
             });
         }
         auto t2_operand = [&](int f, int ksub) {
             return *(const v4i *)(T + (f * 32 + l) * TP + (ksub * 2 + half) * 16);
         };
-        auto sum = [&](int f, const int (&qc)[16]) {
-            int q[16];
+        auto sum = [&](int f, const int (&q)[16], const RqLayer &L) {
+            v4i y;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) q[i] = rq_add<RQ, RQA>(qc[i], (uint32_t)resid[f][i >> 2], i & 3, ac);
-            return rq_pack16<RQA>(q);
+            for (int i = 0; i < 4; ++i) y[i] = (int)rq_add4<RQ, RQA>(q[4 * i], q[4 * i + 1], q[4 * i + 2], q[4 * i + 3], (uint32_t)resid[f][i], ac, L);
+            return y;
         };
         if constexpr (!REDUCE) {
-            conv64(f3, prm3, p.lo3, Frag<0>{}, Frag<NP_FR>{}, t2_operand, [&](int f, const int (&qc)[16]) {
-                const v4i y = sum(f, qc);
+            conv64(f3, prm3, p.lo3, Frag<0>{}, Frag<NP_FR>{}, t2_operand, [&](int f, const int (&q)[16], const RqLayer &L) {
+                const v4i y = sum(f, q, L);
                 const uint32_t px = pixel(f);
                 if (px != ~0u) *(v4i *)(p.out + c0 + (uint64_t)px * (uint32_t)p.Cout_p) = y;
             });
@@ -404,11 +408,12 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
             // and two fragments at a time, into LDS: [pixel][256 channels], chunk c of pixel p at c ^ (p & 15), in the space of
             // the 3x3 weights.  After a barrier each wave makes 16 of the next convolution's channels of those pixels
             // while the others go on to the next fragments, which have a region of their own.
+            const RqLayer Lr = rq_layer<RQ>(prmr[2][0], prmr[3][0]);
             auto group = [&](auto first, auto end, int region) {
                 constexpr int F0 = decltype(first)::value, F1 = decltype(end)::value;
                 const int ln = lane & 15, g = lane >> 4, oc = wave * 16 + 4 * g;
-                conv64(f3, prm3, p.lo3, first, end, t2_operand, [&](int f, const int (&qc)[16]) {
-                    const v4i y = sum(f, qc);
+                conv64(f3, prm3, p.lo3, first, end, t2_operand, [&](int f, const int (&q)[16], const RqLayer &L) {
+                    const v4i y = sum(f, q, L);
                     const uint32_t px = pixel(f);
                     const int i = (f - F0) * 32 + l;
                     if (f == 0)   // no wait for a store behind them
@@ -430,13 +435,13 @@ __global__ __launch_bounds__(512, 4) void bottleneck_kernel(const BneckParams p)
                         a = __builtin_amdgcn_mfma_i32_16x16x64_i8(fr[ks], *(const v4i *)(&Ls[region + (16 * nb + ln) * 256 + (((4 * ks + g) ^ ln) << 4)]), a, 0, 0, 0);
                     int q[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) q[i] = rq_conv<RQ>(a[i], mm[i], ch[i], ss[i], p.lop);
+                    for (int i = 0; i < 4; ++i) q[i] = rq_conv<RQ>(a[i], mm[i], ch[i], ss[i], p.lop, Lr);
                     // sixteen pixels of the tile from a constant one on: they lie in one row or in two
                     const int cy = (F0 * 32 + 16 * nb) / TW, cx = (F0 * 32 + 16 * nb) % TW;
                     const bool wrap = cx + ln >= TW;
                     const uint32_t at = (uint32_t)((b * p.H + oy0 + cy) * p.W + ox0 + cx) + (uint32_t)(ln + (wrap ? p.W - TW : 0));
                     if (full || (oy0 + cy + wrap < p.H && ox0 + cx + ln - (wrap ? TW : 0) < p.W))
-                        *(uint32_t *)(p.out2 + (at * RN + (uint32_t)oc)) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
+                        *(uint32_t *)(p.out2 + (at * RN + (uint32_t)oc)) = rq_pack<RQ>(q[0], q[1], q[2], q[3], Lr);
                 }
             };
             static_assert(5 * 32 * 256 <= FRONT && 3 + 2 + 2 == NP_FR, "regions");

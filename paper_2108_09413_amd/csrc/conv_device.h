@@ -94,8 +94,14 @@ __device__ __forceinline__ uint32_t pack4(int a, int b, int c, int d) {
 //                permute 4.3 - 4.5): 12 instead of 17, with a residual add 29 instead of 37.  ResNet-50, 668 copies:
 //                identity block at 56 x 56 409 -> 349 us, expand + reduce at 28 x 28 160 -> 138, at 14 x 14 120 -> 108.
 //   RQ_TOP_TIES  the same with ties (a 64-bit multiply-add instead of the multiply)
-// An add is RQ_ANY, RQ_TIE_FREE, RQ_TOP or RQ_TOP_WIDE (two signed operands, whose sum may leave int32 and saturates).
-// The forms of several convolutions combine with &.
+//   RQ_PAIR      tie-free, lower clamp -128, ONE shift for all channels of the layer (networks quantised per tensor have one; the
+//                multipliers may differ).  w = high word of acc * M0 + chi 2^32 is one v_mad_i64_i32, and v_ashr_pk_i8_i32
+//                shifts, saturates and packs two of them: 8.4 issue cycles an output against 11.7 of RQ_TOP, 26 against 32 with an
+//                add (measured rates: v_mad_i64_i32 4.24, v_ashr_pk_i8_i32 8.25, v_mul_hi 4.55, v_mad_i32_i24 4.47, v_perm 4.16).
+//                No bound on the range of w, which int32 holds.  Certification of ResNet-50, n = 10 000: 65.4 -> 63.7 ms, of the
+//                110-layer net, n = 100 000: 26.71 -> 25.68 ms, ResNet-20 5.24 -> 5.12.
+// An add is RQ_ANY, RQ_TIE_FREE, RQ_TOP, RQ_TOP_WIDE (two signed operands, whose sum may leave int32 and saturates) or RQ_PAIR.
+// The forms of several convolutions combine with & (Rq).
 // v_mad_i32_i24 with the clamp bit: sat32(a * b + c), a and b in 24 bits (no builtin reaches the clamp bit)
 __device__ __forceinline__ int mad24_sat(int a, int b, int c) {
     int r;
@@ -111,12 +117,32 @@ template <int RQ>
 __device__ __forceinline__ int rq_sh(int shm1) { return rq_is_top(RQ) ? 1 << (24 - shm1) : shm1; }
 // index of channel i's addend
 template <int RQ>
-__device__ __forceinline__ constexpr int rq_chi_at(int i) { return rq_is_top(RQ) ? 0 : i; }
+__device__ __forceinline__ constexpr int rq_chi_at(int i) { return rq_is_top(RQ) || RQ == RQ_PAIR ? 0 : i; }
 
-// requantise + clamp to [lo, 127]: the value, or in the top form a word with the value in its top byte
+// RQ_PAIR: a layer's addend and shift, in scalar registers; the other forms have theirs per channel.
+struct RqLayer {
+    long add;   // chi 2^32
+    int sh;
+};
+// from the staged constants of any real channel
 template <int RQ>
-__device__ __forceinline__ int rq_conv(int acc, int m0, int chi, int sh, int lo) {
-    if constexpr (RQ == RQ_TOP) {
+__device__ __forceinline__ RqLayer rq_layer(int chi, int sh) {
+    if constexpr (RQ == RQ_PAIR) {
+        long add = (long)((unsigned long)(uint32_t)__builtin_amdgcn_readfirstlane(chi) << 32);
+        asm("" : "+s"(add));   // a low word known to be zero would make a multiply and an add of the multiply-add
+        return {add, __builtin_amdgcn_readfirstlane(sh)};
+    } else {
+        return {0, 0};
+    }
+}
+
+// requantise + clamp to [lo, 127]: the value, in the top form a word with the value in its top byte, in the pair form one
+// that rq_pack shifts and clamps
+template <int RQ>
+__device__ __forceinline__ int rq_conv(int acc, int m0, int chi, int sh, int lo, const RqLayer &layer) {
+    if constexpr (RQ == RQ_PAIR) {
+        return (int)(((long)acc * (long)m0 + layer.add) >> 32);
+    } else if constexpr (RQ == RQ_TOP) {
         return mad24_sat(__mulhi(acc, m0), sh, chi);
     } else if constexpr (RQ == RQ_TOP_TIES) {
         const long w = (long)acc * (long)m0 + (long)(acc >> 31);   // v - [v < 0], as requant_fast
@@ -126,48 +152,21 @@ __device__ __forceinline__ int rq_conv(int acc, int m0, int chi, int sh, int lo)
     }
 }
 
-// Constants of the residual add.  Top form: everything times 2^(23 - add_sh); the saturating double of the sum has the
-// int8 result in the top byte.
-template <int RQA, class P>
-__host__ __device__ __forceinline__ AddConst add_const(const P &p) {
-    if constexpr (rq_is_top(RQA)) {
-        const int s = 23 - p.add_sh;
-        return {p.add_mul_self << s, p.add_mul_res << s, (p.add_c0 + p.add_k) << s, 0, 0, 0};
-    } else {
-        return {p.add_mul_self, p.add_mul_res, p.add_c0, p.add_k, p.add_sh, p.add_lo};
-    }
+// sat8(v >> sh) of four words -> one dword.  Each instruction writes one half of the register and keeps the other; a vector
+// instruction right behind a write of the upper half must not read it (the wait state at the end).
+__device__ __forceinline__ uint32_t pack_shifted(int a, int b, int c, int d, int sh) {
+    uint32_t r;
+    asm("v_ashr_pk_i8_i32 %0, %1, %2, %5\n\tv_ashr_pk_i8_i32 %0, %3, %4, %5 op_sel:[0,0,0,1]\n\ts_nop 0"
+        : "=&v"(r) : "v"(a), "v"(b), "v"(c), "v"(d), "s"(sh));
+    return r;
 }
 
-// Residual add of q (as rq_conv<RQ> returns it) and the int8 value r8.  A top-form add goes with a top-form convolution.
-// 24-bit multiplies: |q|, |r| <= 2^7, |multipliers| < 2^23.
-template <int RQ, int RQA>
-__device__ __forceinline__ int rq_add_value(int q, int r8, const AddConst &a) {
-    static_assert(!rq_is_top(RQA) || rq_is_top(RQ), "");
-    const int qi = rq_is_top(RQ) ? q >> 24 : q;
-    if constexpr (RQA == RQ_TOP) {
-        const int v = __mul24(qi, a.ms) + __mul24(r8, a.mr) + a.c0;
-        return __builtin_elementwise_add_sat(v, v);
-    } else if constexpr (RQA == RQ_TOP_WIDE) {
-        const int v = mad24_sat(qi, a.ms, __mul24(r8, a.mr) + a.c0);
-        return __builtin_elementwise_add_sat(v, v);
-    } else if constexpr (RQA == RQ_TIE_FREE) {
-        const int v = __mul24(qi, a.ms) + (a.c0 + a.k) + __mul24(r8, a.mr);
-        return clamp3(v >> a.sh, a.lo, 127);
-    } else {
-        const int v = __mul24(qi, a.ms) + a.c0 + __mul24(r8, a.mr);
-        return clamp3((v + a.k + (v >> 31)) >> a.sh, a.lo, 127);
-    }
-}
-// r = byte j of the residual word (the byte selections fold into the multiplies)
-template <int RQ, int RQA>
-__device__ __forceinline__ int rq_add(int q, uint32_t rword, int j, const AddConst &a) {
-    return rq_add_value<RQ, RQA>(q, (int)(int8_t)(rword >> (8 * j)), a);
-}
-
-// four results of rq_conv / rq_add -> one dword of int8
+// four results of rq_conv -> one dword of int8
 template <int RQ>
-__device__ __forceinline__ uint32_t rq_pack(int a, int b, int c, int d) {
-    if constexpr (rq_is_top(RQ)) {
+__device__ __forceinline__ uint32_t rq_pack(int a, int b, int c, int d, const RqLayer &layer) {
+    if constexpr (RQ == RQ_PAIR) {
+        return pack_shifted(a, b, c, d, layer.sh);
+    } else if constexpr (rq_is_top(RQ)) {
         const uint32_t lo = __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x0c0c0703u);
         const uint32_t hi = __builtin_amdgcn_perm((uint32_t)d, (uint32_t)c, 0x07030c0cu);
         return lo | hi;
@@ -176,15 +175,71 @@ __device__ __forceinline__ uint32_t rq_pack(int a, int b, int c, int d) {
     }
 }
 template <int RQ>
-__device__ __forceinline__ v4i rq_pack16(const int (&q)[16]) {
-    return v4i{(int)rq_pack<RQ>(q[0], q[1], q[2], q[3]), (int)rq_pack<RQ>(q[4], q[5], q[6], q[7]),
-               (int)rq_pack<RQ>(q[8], q[9], q[10], q[11]), (int)rq_pack<RQ>(q[12], q[13], q[14], q[15])};
+__device__ __forceinline__ v4i rq_pack16(const int (&q)[16], const RqLayer &layer) {
+    return v4i{(int)rq_pack<RQ>(q[0], q[1], q[2], q[3], layer), (int)rq_pack<RQ>(q[4], q[5], q[6], q[7], layer),
+               (int)rq_pack<RQ>(q[8], q[9], q[10], q[11], layer), (int)rq_pack<RQ>(q[12], q[13], q[14], q[15], layer)};
+}
+
+// Constants of the residual add.  Top form: everything times 2^(23 - add_sh); the saturating double of the sum has the
+// int8 result in the top byte.
+template <int RQA, class P>
+__host__ __device__ __forceinline__ AddConst add_const(const P &p) {
+    if constexpr (RQA == RQ_PAIR) {
+        return {p.add_mul_self, p.add_mul_res, p.add_c0 + p.add_k, 0, p.add_sh, 0};
+    } else if constexpr (rq_is_top(RQA)) {
+        const int s = 23 - p.add_sh;
+        return {p.add_mul_self << s, p.add_mul_res << s, (p.add_c0 + p.add_k) << s, 0, 0, 0};
+    } else {
+        return {p.add_mul_self, p.add_mul_res, p.add_c0, p.add_k, p.add_sh, p.add_lo};
+    }
+}
+
+// Residual add of the int8 value q and the int8 value r8: the value, or a word as rq_conv<RQA> returns.
+// 24-bit multiplies: |q|, |r| <= 2^7, |multipliers| < 2^23.
+template <int RQA>
+__device__ __forceinline__ int rq_add_value(int q, int r8, const AddConst &a) {
+    if constexpr (RQA == RQ_PAIR) {
+        return __mul24(q, a.ms) + __mul24(r8, a.mr) + a.c0;
+    } else if constexpr (RQA == RQ_TOP) {
+        const int v = __mul24(q, a.ms) + __mul24(r8, a.mr) + a.c0;
+        return __builtin_elementwise_add_sat(v, v);
+    } else if constexpr (RQA == RQ_TOP_WIDE) {
+        const int v = mad24_sat(q, a.ms, __mul24(r8, a.mr) + a.c0);
+        return __builtin_elementwise_add_sat(v, v);
+    } else if constexpr (RQA == RQ_TIE_FREE) {
+        const int v = __mul24(q, a.ms) + (a.c0 + a.k) + __mul24(r8, a.mr);
+        return clamp3(v >> a.sh, a.lo, 127);
+    } else {
+        const int v = __mul24(q, a.ms) + a.c0 + __mul24(r8, a.mr);
+        return clamp3((v + a.k + (v >> 31)) >> a.sh, a.lo, 127);
+    }
+}
+// Four channels: q as rq_conv<RQ> returns them, the residuals the bytes of rword (the byte selections fold into the
+// multiplies); the sums as one dword of int8.
+template <int RQ, int RQA>
+__device__ __forceinline__ uint32_t rq_add4(int q0, int q1, int q2, int q3, uint32_t rword, const AddConst &a, const RqLayer &layer) {
+    static_assert(RQA == RQ_ANY || RQA == RQ_TIE_FREE || (RQA == RQ_PAIR ? RQ == RQ_PAIR : rq_is_top(RQ)), "a form of the add next to one of the convolution");
+    int q[4] = {q0, q1, q2, q3}, v[4];
+    uint32_t qword = 0;
+    if constexpr (RQ == RQ_PAIR) qword = rq_pack<RQ>(q0, q1, q2, q3, layer);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int qj = RQ == RQ_PAIR ? (int)(int8_t)(qword >> (8 * j)) : rq_is_top(RQ) ? q[j] >> 24 : q[j];
+        v[j] = rq_add_value<RQA>(qj, (int)(int8_t)(rword >> (8 * j)), a);
+    }
+    return rq_pack<RQA>(v[0], v[1], v[2], v[3], RqLayer{0, a.sh});
 }
 
 // Calls f with the compile-time forms <RQ of the convolutions, RQ of the add> that serve layers of these classes.
 template <class F>
 void with_rq(int rq, int rqa, F f) {
     using std::integral_constant;
+    if (rq & rqa & RQ_PAIR) {
+        f(integral_constant<int, RQ_PAIR>{}, integral_constant<int, RQ_PAIR>{});
+        return;
+    }
+    rq &= ~RQ_PAIR;
+    rqa &= ~RQ_PAIR;
     if (rq == RQ_TOP && rqa == RQ_TOP) f(integral_constant<int, RQ_TOP>{}, integral_constant<int, RQ_TOP>{});
     else if (rq == RQ_TOP && rqa == RQ_TOP_WIDE) f(integral_constant<int, RQ_TOP>{}, integral_constant<int, RQ_TOP_WIDE>{});
     else if (rq == RQ_TOP) f(integral_constant<int, RQ_TOP>{}, integral_constant<int, RQ_ANY>{});
@@ -196,7 +251,8 @@ void with_rq(int rq, int rqa, F f) {
 template <class F>
 void with_rq(int rq, F f) {
     using std::integral_constant;
-    if (rq == RQ_TOP) f(integral_constant<int, RQ_TOP>{});
+    if (rq & RQ_PAIR) f(integral_constant<int, RQ_PAIR>{});
+    else if (rq == RQ_TOP) f(integral_constant<int, RQ_TOP>{});
     else if (rq == RQ_TOP_TIES) f(integral_constant<int, RQ_TOP_TIES>{});
     else if (rq == RQ_TIE_FREE) f(integral_constant<int, RQ_TIE_FREE>{});
     else f(integral_constant<int, RQ_ANY>{});

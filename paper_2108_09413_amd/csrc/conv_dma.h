@@ -339,6 +339,7 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
     v4i rq[FUSE == 2 ? FM : 1][FUSE == 2 ? FN : 1];
     if constexpr (FUSE == 2) {
         gemm(p.Cin2_p / KB, prm2_s[0], issue2, false, prefetched);
+        const RqLayer layer2 = rq_layer<RQ>(prm2_s[2][0], prm2_s[3][0]);
 #pragma unroll
         for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
@@ -347,9 +348,9 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
 #pragma unroll
                 for (int i = 0; i < ACC; ++i) {
                     const int c = lane_oc(fm) + i;
-                    q[i] = rq_conv<RQ>(acc[fm][fn][i], prm2_s[1][c], prm2_s[2][lane_oc(fm) + rq_chi_at<RQ>(i)], prm2_s[3][c], p.lo2);
+                    q[i] = rq_conv<RQ>(acc[fm][fn][i], prm2_s[1][c], prm2_s[2][lane_oc(fm) + rq_chi_at<RQ>(i)], prm2_s[3][c], p.lo2, layer2);
                 }
-                rq[fm][fn] = rq_pack16<RQ>(q);
+                rq[fm][fn] = rq_pack16<RQ>(q, layer2);
             }
         __syncthreads();   // every wave is done with the operand buffers before the main GEMM refills them
     }
@@ -364,6 +365,7 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
         resbuf = Ls[res_buf];
     }
     const int lo = p.relu ? p.zp_out : -128;
+    const RqLayer layer = rq_layer<RQ>(prm_s[2][0], prm_s[3][0]);
     const AddConst ac = add_const<FUSE != 0 ? RQA : (int)RQ_ANY>(p);
 #pragma unroll
     for (int fm = 0; fm < FM; ++fm) {
@@ -381,18 +383,19 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
                 if (n >= p.npix) continue;
                 int q[ACC];
 #pragma unroll
-                for (int i = 0; i < ACC; ++i) q[i] = rq_conv<RQ>(acc[fm][fn][i], mm[i], ch[i], ss[i], lo);
+                for (int i = 0; i < ACC; ++i) q[i] = rq_conv<RQ>(acc[fm][fn][i], mm[i], ch[i], ss[i], lo, layer);
+                v4i v;
                 if constexpr (FUSE != 0) {
                     const int pixel = wn * WTN + fn * MT + (lane & (MT - 1));
                     v4i rv;
                     if constexpr (FUSE == 2) rv = rq[fm][fn];
                     else rv = *(const v4i *)(resbuf + (pixel * RCH + ((lane_oc(fm) >> 4) ^ rswz(pixel))) * 16);
 #pragma unroll
-                    for (int i = 0; i < ACC; ++i) q[i] = rq_add<RQ, RQA>(q[i], (uint32_t)rv[i >> 2], i & 3, ac);
+                    for (int i = 0; i < 4; ++i) v[i] = (int)rq_add4<RQ, RQA>(q[4 * i], q[4 * i + 1], q[4 * i + 2], q[4 * i + 3], (uint32_t)rv[i], ac, layer);
+                } else {
+                    v = rq_pack16<RQ>(q, layer);
                 }
-                int8_t *dst = p.out + n * p.Cout_p + oc;
-                v4i v = rq_pack16<FUSE != 0 ? RQA : RQ>(q);
-                *(v4i *)dst = v;
+                *(v4i *)(p.out + n * p.Cout_p + oc) = v;
             }
         }
     }

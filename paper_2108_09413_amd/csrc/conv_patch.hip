@@ -277,6 +277,7 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
 
     // epilogue: requantise, clamp, pack, store (NHWC)
     const int lo = p.relu ? p.zp_out : -128;
+    const RqLayer L = rq_layer<RQ>(prm_s[2][0], prm_s[3][0]);
 #pragma unroll
     for (int fm = 0; fm < 2; ++fm) {
         const int oc = m0 + lane_oc(fm);
@@ -292,8 +293,8 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
             if (n >= p.npix) continue;
             int q[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(acc[fm][fn][i], mm[i], ch[i], ss[i], lo);
-            *(v4i *)(p.out + n * p.Cout_p + oc) = rq_pack16<RQ>(q);
+            for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(acc[fm][fn][i], mm[i], ch[i], ss[i], lo, L);
+            *(v4i *)(p.out + n * p.Cout_p + oc) = rq_pack16<RQ>(q, L);
         }
     }
 }

@@ -31,10 +31,10 @@ constexpr int XK1 = 128, XC = 512, XN2 = 128, XPX = 32, XNW = 8, XNT = XNW * 64;
 constexpr int XNB = 3;   // tile buffers: loads run two tiles ahead
 typedef int v4acc __attribute__((ext_vector_type(4)));
 
-// four channels' addends of the requantisation (one value for a whole layer in the top form)
+// four channels' addends of the requantisation (one value for a whole layer where the form has one)
 template <int RQ>
 __device__ __forceinline__ v4i rq_chi4(const int *c) {
-    if constexpr (rq_is_top(RQ)) return v4i{c[0], c[0], c[0], c[0]};
+    if constexpr (rq_chi_at<RQ>(1) == 0) return v4i{c[0], c[0], c[0], c[0]};
     else return *(const v4i *)c;
 }
 
@@ -93,6 +93,7 @@ __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p)
     if (tid < XN2) rq_store<RQ>(prm2, r2, i2);
     wait_vmcnt<0>();
     __syncthreads();   // the constants are in LDS, the first tile has landed
+    const RqLayer L1 = rq_layer<RQ>(prm1[2][0], prm1[3][0]), L2 = rq_layer<RQ>(prm2[2][0], prm2[3][0]);
 
     int buf = 0;
     for (int it = 0; tile < ntiles; tile += G, ++it) {
@@ -145,10 +146,8 @@ __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p)
                 const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = rq_chi4<RQ>(&prm1[2][oc + 4 * gi]), ss = *(const v4i *)&prm1[3][oc + 4 * gi];
                 int q[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    q[i] = rq_add<RQ, RQA>(rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1), (uint32_t)rv[gi], i, ac);
-                }
-                yv[gi] = (int)rq_pack<RQA>(q[0], q[1], q[2], q[3]);
+                for (int i = 0; i < 4; ++i) q[i] = rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1, L1);
+                yv[gi] = (int)rq_add4<RQ, RQA>(q[0], q[1], q[2], q[3], (uint32_t)rv[gi], ac, L1);
             }
             *(v4i *)cell = yv;
             if (n1 < p.npix) *(v4i *)(p.y + n1 * XC + oc) = yv;
@@ -178,9 +177,9 @@ __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int c = wave * 16 + g * 4 + i;
-                q[i] = rq_conv<RQ>(acc2[nb][i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2);
+                q[i] = rq_conv<RQ>(acc2[nb][i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2, L2);
             }
-            if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * XN2 + wave * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
+            if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * XN2 + wave * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3], L2);
         }
         buf = buf + 1 == XNB ? 0 : buf + 1;
     }
@@ -250,6 +249,8 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
     if (tid < XN2) rq_store<RQ>(prm2, r2, i2);
     wait_vmcnt<0>();
     __syncthreads();   // the constants are in LDS, the first tile has landed
+    const RqLayer L1 = rq_layer<RQ>(prm1[2][0], prm1[3][0]), L2 = rq_layer<RQ>(prm2[2][0], prm2[3][0]);
+    const RqLayer Lp = rq_layer<RQ>(prmp[2][0], prmp[3][0]);
 
     int buf = 0;
     for (int it = 0; tile < ntiles; tile += G, ++it) {
@@ -293,8 +294,8 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
                 const v4i mm = *(const v4i *)&prmp[1][oc + 4 * gi], ch = rq_chi4<RQ>(&prmp[2][oc + 4 * gi]), ss = *(const v4i *)&prmp[3][oc + 4 * gi];
                 int q[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) q[i] = rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lop);
-                rq[gi] = (int)rq_pack<RQ>(q[0], q[1], q[2], q[3]);
+                for (int i = 0; i < 4; ++i) q[i] = rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lop, Lp);
+                rq[gi] = (int)rq_pack<RQ>(q[0], q[1], q[2], q[3], Lp);
             }
         }
         // ---- expand + add ----
@@ -316,10 +317,8 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
                 const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = rq_chi4<RQ>(&prm1[2][oc + 4 * gi]), ss = *(const v4i *)&prm1[3][oc + 4 * gi];
                 int q[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    q[i] = rq_add<RQ, RQA>(rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1), (uint32_t)rq[gi], i, ac);
-                }
-                yv[gi] = (int)rq_pack<RQA>(q[0], q[1], q[2], q[3]);
+                for (int i = 0; i < 4; ++i) q[i] = rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1, L1);
+                yv[gi] = (int)rq_add4<RQ, RQA>(q[0], q[1], q[2], q[3], (uint32_t)rq[gi], ac, L1);
             }
             *(v4i *)(Y + px1 * XC + (((oc >> 4) ^ (px1 & 15)) << 4)) = yv;
             const long n1 = (long)n0 + px1;
@@ -343,10 +342,10 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int c = mb * 16 + g * 4 + i;
-                q[i] = rq_conv<RQ>(acc2[i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2);
+                q[i] = rq_conv<RQ>(acc2[i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2, L2);
             }
             const long n2 = (long)n0 + px;
-            if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * XN2 + mb * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
+            if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * XN2 + mb * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3], L2);
         }
         buf = buf + 1 == XNB ? 0 : buf + 1;
     }
@@ -406,6 +405,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
     if (tid < XN2W) rq_store<RQ>(prm2, r2, i2);
     wait_vmcnt<0>();
     __syncthreads();   // the constants are in LDS, the first tile has landed
+    const RqLayer L1 = rq_layer<RQ>(prm1[2][0], prm1[3][0]), L2 = rq_layer<RQ>(prm2[2][0], prm2[3][0]);
 
     int buf = 0;
     for (int it = 0; tile < ntiles; tile += G, ++it) {
@@ -452,10 +452,8 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
                 const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = rq_chi4<RQ>(&prm1[2][oc + 4 * gi]), ss = *(const v4i *)&prm1[3][oc + 4 * gi];
                 int q[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    q[i] = rq_add<RQ, RQA>(rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1), (uint32_t)rv[gi], i, ac);
-                }
-                yv[gi] = (int)rq_pack<RQA>(q[0], q[1], q[2], q[3]);
+                for (int i = 0; i < 4; ++i) q[i] = rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1, L1);
+                yv[gi] = (int)rq_add4<RQ, RQA>(q[0], q[1], q[2], q[3], (uint32_t)rv[gi], ac, L1);
             }
             *(v4i *)cell = yv;
             const long n1 = (long)n0 + px1;
@@ -486,9 +484,9 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int c = wave * 16 + g * 4 + i;
-                    q[i] = rq_conv<RQ>(acc2[nb][i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2);
+                    q[i] = rq_conv<RQ>(acc2[nb][i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2, L2);
                 }
-                if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * XN2W + wave * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
+                if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * XN2W + wave * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3], L2);
             }
         }
         buf = buf + 1 == XNB ? 0 : buf + 1;
@@ -558,6 +556,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
     if (tid < DN2) rq_store<RQ>(prm2, r2, i2);
     wait_vmcnt<0>();
     __syncthreads();   // the constants are in LDS, the first tile has landed
+    const RqLayer L1 = rq_layer<RQ>(prm1[2][0], prm1[3][0]), L2 = rq_layer<RQ>(prm2[2][0], prm2[3][0]);
 
     int buf = 0;
     for (int it = 0; tile < ntiles; tile += G, ++it) {
@@ -601,10 +600,8 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
                 const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = rq_chi4<RQ>(&prm1[2][oc + 4 * gi]), ss = *(const v4i *)&prm1[3][oc + 4 * gi];
                 int q[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    q[i] = rq_add<RQ, RQA>(rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1), (uint32_t)rv[gi], i, ac);
-                }
-                yv[gi] = (int)rq_pack<RQA>(q[0], q[1], q[2], q[3]);
+                for (int i = 0; i < 4; ++i) q[i] = rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1, L1);
+                yv[gi] = (int)rq_add4<RQ, RQA>(q[0], q[1], q[2], q[3], (uint32_t)rv[gi], ac, L1);
             }
             *(v4i *)cell = yv;
             if (n1 < p.npix) *(v4i *)(p.y + n1 * DC + oc) = yv;
@@ -647,9 +644,9 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int c = wave * 16 + g * 4 + i;
-                    q[i] = rq_conv<RQ>(acc2[nb][i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2);
+                    q[i] = rq_conv<RQ>(acc2[nb][i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2, L2);
                 }
-                if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * DN2 + wave * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
+                if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * DN2 + wave * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3], L2);
             }
         }
         buf = buf + 1 == XNB ? 0 : buf + 1;
@@ -691,7 +688,7 @@ void expand_reduce_params(const ConvParams &e, const ConvParams &r, const int8_t
     xp.y = y; xp.t1n = t1n;
     xp.a2 = r.wfrag; xp.bias2 = r.bias; xp.m0s2 = r.m0s; xp.chi2 = r.chi; xp.shm12 = r.shm1;
     xp.lo2 = r.relu ? r.zp_out : -128;
-    xp.rq = e.rq & r.rq & (e.fuse_add == 2 ? e.rq2 : RQ_TOP);
+    xp.rq = e.rq & r.rq & (e.fuse_add == 2 ? e.rq2 : ~0);
     xp.add_rq = e.add_rq;
     xp.add_c0 = e.add_c0; xp.add_k = e.add_k; xp.add_sh = e.add_sh; xp.add_lo = e.add_lo;
     xp.npix = copies * e.Ho * e.Wo;
@@ -721,7 +718,7 @@ void expand_reduce_params(const ConvParams &e, const ConvParams &r, const int8_t
 // the kernels serve tie-free convolutions only
 template <class F>
 static void with_tie_free_rq(const XrParams &p, F f) {
-    with_rq(p.rq, p.add_rq, [&](auto rq, auto rqa) { if constexpr ((decltype(rq)::value & RQ_TIE_FREE) != 0) f(rq, rqa); });
+    with_rq(p.rq, p.add_rq, [&](auto rq, auto rqa) { if constexpr ((decltype(rq)::value & (RQ_TIE_FREE | RQ_PAIR)) != 0) f(rq, rqa); });
 }
 
 hipError_t launch_expand_reduce(const XrParams &p, hipStream_t st) {

@@ -131,9 +131,11 @@ struct ParsedModel {
 int parse_model(const void *blob, size_t bytes, ParsedModel &out, std::string &why);
 
 // ---- device-side op descriptors -------------------------------------------
-// Forms of the requantisation and of the residual add (conv_device.h)
-enum Rq : int { RQ_ANY = 0, RQ_TIE_FREE = 1, RQ_TOP_TIES = 2, RQ_TOP = 3, RQ_TOP_WIDE = 4 };
-constexpr bool rq_is_top(int rq) { return rq >= RQ_TOP_TIES; }
+// Forms of the requantisation and of the residual add (conv_device.h).  The class of a layer or an add is one of the first
+// five values, with RQ_PAIR set beside it where that form serves it too.
+enum Rq : int { RQ_ANY = 0, RQ_TIE_FREE = 1, RQ_TOP_TIES = 2, RQ_TOP = 3, RQ_TOP_WIDE = 4, RQ_PAIR = 8 };
+constexpr int rq_form(int rq) { return rq & RQ_PAIR ? (int)RQ_PAIR : rq; }   // the form that a class takes
+constexpr bool rq_is_top(int rq) { return rq >= RQ_TOP_TIES && rq <= RQ_TOP_WIDE; }
 struct AddConst { int32_t ms, mr, c0, k, sh, lo; };   // constants of a residual add in its form
 
 struct ConvParams {
@@ -153,13 +155,13 @@ struct ConvParams {
     // never rounds an exact half and the sign correction of the rounding term is dead: the kernel then
     // takes (mulhi(acc, M0) + chi) >> (shift - 1) (decided per layer when the model is loaded)
     int32_t tie_free;
-    int32_t rq;              // Rq form of this convolution's requantisation (conv_device.h)
+    int32_t rq;              // Rq class of this convolution's requantisation (conv_device.h)
     // residual add folded into the epilogue (fuse_add != 0): with q the int8 result above,
     //   v = q * add_mul_self + res * add_mul_res + add_c0            (= (q-z)Ms + (res-zr)Mr)
     //   out = clamp((v + add_k + (v >> 31)) >> add_sh, add_lo, 127)  (add_k = 2^(sh-1) + z_o 2^sh)
     const int8_t *res;       // [B][Ho][Wo][Cout_p] other input of the add
     int32_t fuse_add, add_mul_self, add_mul_res, add_c0, add_k, add_sh, add_lo;
-    int32_t add_rq;          // Rq form of the add
+    int32_t add_rq;          // Rq class of the add
     int32_t add_tie_free;    // 1: no pair of int8 inputs makes v a negative exact half: out = clamp((v + add_k) >> add_sh)
     // fuse_add == 2: the residual is itself the output of a 1x1 stride-1 convolution (same pixels, same
     // channels) that has no other reader; the kernel computes it first, keeps it in registers and never
@@ -210,13 +212,13 @@ struct Stem16Params {
 };
 
 // The nets on 32 x 32 images with 16 / 32 / 64 channels at 32 / 16 / 8 pixels, one launch per stage, or of few copies one for all (narrow_net.hip).
-// Per-channel constants come packed, int32 [4][C]: bias, M0, chi, shift-1 (top form: addend and multiplier, see rq_chi).
+// Per-channel constants come packed, int32 [4][C]: bias, M0, chi, shift-1.
 struct NarrowBlock {         // identity residual block, stored in device memory
     const int8_t *w1, *w2;   // [>= C][Kp] each, K = (tap, channel), Kp = 9 C rounded up to 64
     const int32_t *prm1, *prm2;
     int32_t zp_x, zp_t;      // zero-points of the block input and of the middle tensor
     int32_t lo1, lo2;        // lower clamps of the two convolutions
-    int32_t form;            // 0: RQ_TOP with one shift for all channels, add RQ_TOP; 1: the same, add RQ_ANY; 2: RQ_ANY, add RQ_ANY
+    int32_t form;            // 0: RQ_PAIR, add RQ_PAIR; 1: RQ_PAIR, add RQ_ANY; 2: RQ_ANY, add RQ_ANY
     AddConst add;
     int32_t pad_;
 };
@@ -233,7 +235,7 @@ struct NarrowParams {
     int32_t nblocks;
     const NarrowBlock *blocks;
     // tail 1: down-sampling block t = conv3x3/2(x), u = conv3x3(t), r = conv1x1/2(x), y = add(r, u); 2: t alone
-    int32_t tail, tform;     // form 0: RQ_TOP, add RQ_TOP_WIDE; 1, 2 as above
+    int32_t tail, tform;     // form as above
     const int8_t *tw1, *tw2, *twp;
     const int32_t *tprm;     // [3][4][2C]: t, u, r
     int32_t tzp_x, tzp_t, tlo1, tlo2, tlop;
@@ -274,7 +276,7 @@ struct BneckParams {
     int32_t zp_t1;           // zero-point of the first convolution's output (padding value of the 3x3)
     int32_t lo1, lo2, lo3;   // lower clamps of the three int8 results
     int32_t add_mul_self, add_mul_res, add_c0, add_k, add_sh, add_lo;   // as in ConvParams
-    int32_t rq, add_rq;      // Rq form (conv_device.h) that serves every convolution of the block; that of the add
+    int32_t rq, add_rq;      // Rq class (conv_device.h) of every convolution of the block together; that of the add
 };
 
 // Closing 1x1 convolution + residual add of one bottleneck block and the opening 1x1 convolution of the next
@@ -295,7 +297,7 @@ struct XrParams {
     const int32_t *bias2, *m0s2, *chi2, *shm12;   // reducing convolution [128]
     int32_t lo1, lo2;        // lower clamps of the two convolutions' int8 results
     int32_t add_mul_self, add_mul_res, add_c0, add_k, add_sh, add_lo;   // as in ConvParams
-    int32_t rq, add_rq;      // Rq form that serves every convolution (at least tie-free); that of the add
+    int32_t rq, add_rq;      // Rq class of all convolutions together (at least tie-free); that of the add
     int32_t npix;
     int32_t n2;              // output channels of the reducing convolution: 128, or 256 (stored residual only)
     int32_t k1;              // input channels of the expanding convolution: 128 (512 block channels) or 256 (1024; stored residual, n2 = 256)

@@ -147,33 +147,34 @@ __device__ __forceinline__ void wide_group(const WideConv<C, S> &wc, const int8_
     }
 }
 
-// A lane's constants of N consecutive output channels from the packed form [4][C].  The top form keeps them in registers
-// across the fragments of a convolution; the others, for the few layers that need them, read them where they are used.
-template <int N, int RQ, bool TOP = RQ == RQ_TOP>
+// A lane's constants of N consecutive output channels from the packed form [4][C].  The pair form keeps them in registers
+// across the fragments of a convolution; the other, for the few layers that need it, reads them where they are used.
+template <int N, int RQ, bool PAIR = RQ == RQ_PAIR>
 struct LaneConsts {
-    int m0[N], chi, sh, b4[4];    // one addend and (forms in use here) one multiplier for all channels
+    int m0[N], b4[4];
+    RqLayer layer;
     const int *b;                 // 16 channels: the bias is read into the accumulator, registers are short
     __device__ __forceinline__ LaneConsts(const int *prm, int C, int c0) : b(prm + c0) {
 #pragma unroll
         for (int i = 0; i < N; ++i) m0[i] = prm[C + c0 + i];
 #pragma unroll
         for (int i = 0; i < 4; ++i) b4[i] = prm[c0 + i];
-        chi = prm[2 * C];
-        sh = prm[3 * C];
+        layer = rq_layer<RQ>(prm[2 * C], prm[3 * C]);
     }
     __device__ __forceinline__ void fragment() const { if (N == 16) asm volatile("" ::: "memory"); }   // start of a fragment: the bias is not kept
     __device__ __forceinline__ int bias(int i) const { return N == 4 ? b4[i & 3] : b[i]; }
-    __device__ __forceinline__ int conv(int acc, int i, int lo) const { return rq_conv<RQ>(acc, m0[i], chi, sh, lo); }
+    __device__ __forceinline__ int conv(int acc, int i, int lo) const { return rq_conv<RQ>(acc, m0[i], 0, 0, lo, layer); }
 };
 template <int N, int RQ>
 struct LaneConsts<N, RQ, false> {
     const int *at;
     int C;
+    RqLayer layer = {};
     __device__ __forceinline__ LaneConsts(const int *prm, int C_, int c0) : at(prm + c0), C(C_) {}
     __device__ __forceinline__ void fragment() const { asm volatile("" ::: "memory"); }   // no constant is carried over in a register
     __device__ __forceinline__ int bias(int i) const { return at[i]; }
     __device__ __forceinline__ int conv(int acc, int i, int lo) const {
-        return rq_conv<RQ>(acc, at[C + i], at[2 * C + (rq_is_top(RQ) ? 0 : i)], at[3 * C + i], lo);
+        return rq_conv<RQ>(acc, at[C + i], at[2 * C + i], at[3 * C + i], lo, layer);
     }
 };
 template <int N, int RQ>
@@ -191,7 +192,7 @@ __device__ __forceinline__ auto bias_vector(const LaneConsts<N, RQ> &k) {
 template <int FRAGS, int RQ, bool PAIRS, int C, int S, class Source, class Start, class Element, class Finish>
 __device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&fa)[WideConv<C, S>::KS], const LaneConsts<16, RQ> &k, const int8_t *next,
                                                Source source, Start start, Element element, Finish finish) {
-    if constexpr (RQ == RQ_TOP) {
+    if constexpr (RQ == RQ_PAIR) {
         constexpr int P = PAIRS && FRAGS >= 2 ? 2 : 1, G = FRAGS / P;
         static_assert(FRAGS % P == 0, "whole groups");
         const int8_t *row = wc.weight_row(next);
@@ -242,12 +243,12 @@ __device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&f
     }
 }
 
-// f with the compile-time forms of a descriptor's `form`; TOPA: the add's form next to RQ_TOP
-template <int TOPA, class F>
+// f with the compile-time forms of a descriptor's `form`
+template <class F>
 __device__ __forceinline__ void with_form(int form, F f) {
     using std::integral_constant;
-    if (form == 0) f(integral_constant<int, RQ_TOP>{}, integral_constant<int, TOPA>{});
-    else if (form == 1) f(integral_constant<int, RQ_TOP>{}, integral_constant<int, RQ_ANY>{});
+    if (form == 0) f(integral_constant<int, RQ_PAIR>{}, integral_constant<int, RQ_PAIR>{});
+    else if (form == 1) f(integral_constant<int, RQ_PAIR>{}, integral_constant<int, RQ_ANY>{});
     else f(integral_constant<int, RQ_ANY>{}, integral_constant<int, RQ_ANY>{});
 }
 
@@ -480,7 +481,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
             // 4 stored channels, the fourth pixel and channel meeting zero weights), the fourth group zero weights
             const int l = lane & 15, kg = lane >> 4, kr = kg < 3 ? kg : 0;
             const int x = 16 * (wave & 1) + l, row0 = R * (wave >> 1);
-            with_form<RQ_TOP>(p.form0, [&](auto rq, auto) {
+            with_form(p.form0, [&](auto rq, auto) {
                 constexpr int RQ = decltype(rq)::value;
                 const LaneConsts<4, RQ> k(prm[1], 16, 4 * kg);
                 const int *src = img + (row0 + kr) * PW + x;
@@ -490,7 +491,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                     const v4i fb = {src[r * PW], src[r * PW + 1], src[r * PW + 2], src[r * PW + 3]};
                     k.fragment();
                     const v4acc acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa0, fb, bias_vector<4, RQ>(k), 0, 0, 0);
-                    const uint32_t q = rq_pack<RQ>(k.conv(acc[0], 0, p.lo0), k.conv(acc[1], 1, p.lo0), k.conv(acc[2], 2, p.lo0), k.conv(acc[3], 3, p.lo0));
+                    const uint32_t q = rq_pack<RQ>(k.conv(acc[0], 0, p.lo0), k.conv(acc[1], 1, p.lo0), k.conv(acc[2], 2, p.lo0), k.conv(acc[3], 3, p.lo0), k.layer);
                     *(uint32_t *)(dst + r * P * 16) = q;
                 }
             });
@@ -533,7 +534,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
             }
             if (zp_next != zp_x) fill_ring<C, S, NI, NT>(X, zp_next, tid);
         };
-        with_form<RQ_TOP>(cur.form(), [&](auto rq, auto rqa) {
+        with_form(cur.form(), [&](auto rq, auto rqa) {
             constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
             if constexpr (C == 16) {
                 // 16 channels: a K step of v_mfma_i32_16x16x64_i8 is one kernel row -- lane group kg holds tap (ky = step, kx = kg),
@@ -564,13 +565,13 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                         if (r < R - 1) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[0], b[(r + 1) % 6], bias_vector<4, RQ>(k), 0, 0, 0);
                         row(r, 0, acc[0]);
                         row(r, 1, acc[1]);
-                        if (RQ == RQ_TOP) __builtin_amdgcn_sched_barrier(0);
+                        if (RQ == RQ_PAIR) __builtin_amdgcn_sched_barrier(0);
                         if (r < R - 1) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[1], b[(r + 2) % 6], next, 0, 0, 0);
                         row(r, 2, acc[2]);
-                        if (RQ == RQ_TOP) __builtin_amdgcn_sched_barrier(0);
+                        if (RQ == RQ_PAIR) __builtin_amdgcn_sched_barrier(0);
                         if (r < R - 1) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[2], b[(r + 3) % 6], next, 0, 0, 0);
                         row(r, 3, acc[3]);
-                        if (RQ == RQ_TOP) __builtin_amdgcn_sched_barrier(0);
+                        if (RQ == RQ_PAIR) __builtin_amdgcn_sched_barrier(0);
                         acc = next;
                     }
                     if (AHEAD)
@@ -581,7 +582,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 conv(X, AHEAD ? cur.w2() : cur.w1(), prm[0], [&](const LaneConsts<4, RQ> &k) {
                     return [&, q = v4acc{}](int r, int e, int a) mutable {
                         q[e] = k.conv(a, e, lo1);
-                        if (e == 3) *(uint32_t *)(T + at + r * P * 16) = rq_pack<RQ>(q[0], q[1], q[2], q[3]);
+                        if (e == 3) *(uint32_t *)(T + at + r * P * 16) = rq_pack<RQ>(q[0], q[1], q[2], q[3], k.layer);
                     };
                 });
                 second_constants();
@@ -589,9 +590,9 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 conv(T, AHEAD ? nxt.w1() : cur.w2(), prm[1], [&](const LaneConsts<4, RQ> &k) {
                     auto residual = [&](int r) { return *(const uint32_t *)(X + at + (r < R ? r : R - 1) * P * 16); };
                     return [&, residual, q = v4acc{}, rw0 = residual(0), rw1 = residual(1), rw2 = residual(2)](int r, int e, int a) mutable {
-                        q[e] = rq_add<RQ, RQA>(k.conv(a, e, lo2), rw0, e, ac);
+                        q[e] = k.conv(a, e, lo2);
                         if (e == 3) {
-                            *(uint32_t *)(X + at + r * P * 16) = rq_pack<RQA>(q[0], q[1], q[2], q[3]);
+                            *(uint32_t *)(X + at + r * P * 16) = rq_add4<RQ, RQA>(q[0], q[1], q[2], q[3], rw0, ac, k.layer);
                             rw0 = rw1; rw1 = rw2; rw2 = residual(r + 3);   // read three rows ahead
                         }
                     };
@@ -611,7 +612,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                     wide_fragments<FRAGS, RQ, true>(wc, fa, k, cur.w2(), [&](int i) { return X + offset(i); }, [](int, int) {},
                         [&](int, int, int e, int a) {
                             q[e & 3] = k.conv(a, e, lo1);
-                            if ((e & 3) == 3) o[e >> 2] = (int)rq_pack<RQ>(q[0], q[1], q[2], q[3]);
+                            if ((e & 3) == 3) o[e >> 2] = (int)rq_pack<RQ>(q[0], q[1], q[2], q[3], k.layer);
                         },
                         [&](int i) { *(v4i *)(T + offset(i) + wc.out) = o; });
                 }
@@ -624,11 +625,11 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 const int dst = last && p.tail ? wc.out_strided : wc.out;
                 int q[4];
                 v4i o, rv[2];   // residuals of the two fragments of a group
-                wide_fragments<FRAGS, RQ, RQA == RQ_TOP>(wc, fa, k, nxt.w1(), [&](int i) { return T + offset(i); },
+                wide_fragments<FRAGS, RQ, RQA == RQ_PAIR>(wc, fa, k, nxt.w1(), [&](int i) { return T + offset(i); },
                     [&](int i, int j) { rv[j] = *(const v4i *)(X + offset(i) + wc.out); },
                     [&](int, int j, int e, int a) {
-                        q[e & 3] = rq_add<RQ, RQA>(k.conv(a, e, lo2), (uint32_t)rv[j][e >> 2], e & 3, ac);
-                        if ((e & 3) == 3) o[e >> 2] = (int)rq_pack<RQA>(q[0], q[1], q[2], q[3]);
+                        q[e & 3] = k.conv(a, e, lo2);
+                        if ((e & 3) == 3) o[e >> 2] = (int)rq_add4<RQ, RQA>(q[0], q[1], q[2], q[3], (uint32_t)rv[j][e >> 2], ac, k.layer);
                     },
                     [&](int i) { *(v4i *)(X + offset(i) + dst) = o; });
             }
@@ -649,7 +650,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
             constexpr int FRAG1 = 2 * (32 / S2) * P * C;   // input bytes from one output fragment to the next (an even number of rows)
             lds_barrier();            // x is complete, the last block is done with t
             fill_ring<C2, S2, NI, NT>(T, p.tzp_t, tid);
-            with_form<RQ_TOP_WIDE>(p.tform, [&](auto rq, auto rqa) {
+            with_form(p.tform, [&](auto rq, auto rqa) {
                 constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
                 int ln = lane;
                 asm volatile("" : "+v"(ln));
@@ -684,7 +685,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                         int q[16];
 #pragma unroll
                         for (int e = 0; e < 16; ++e) q[e] = k.conv(a[e], e, p.tlo1);
-                        const v4i o = rq_pack16<RQ>(q);
+                        const v4i o = rq_pack16<RQ>(q, k.layer);
                         const long g = img0 + im;
                         if (!store) *(v4i *)(T + im * TB2 + (f % NF) * wc.FRAG + wc.out) = o;
                         else if (g < p.B) *(v4i *)(p.out + ((g * S2 * S2 + (f % NF) * 32 + l) * C2 + c0)) = o;
@@ -705,25 +706,28 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                         const int f = wave / MF + i * (NW / MF), im = f / NF;
                         if (NI * NF * MF < NW && f >= NI * NF) break;
                         asm volatile("" ::: "memory");   // one convolution's constants at a time
-                        int r[16], q[16];
+                        v4i r, y;   // the projection, the sum
                         {
                             const LaneConsts<16, RQ> k(tprm + 2 * 4 * C2, C2, c0);
                             const v16i a = __builtin_amdgcn_mfma_i32_32x32x32_i8(fp, *(const v4i *)(X + im * TB + (f % NF) * FRAG1 + xp), bias_vector<16, RQ>(k), 0, 0, 0);
+                            int q[16];
 #pragma unroll
-                            for (int e = 0; e < 16; ++e) r[e] = k.conv(a[e], e, p.tlop);
+                            for (int e = 0; e < 16; ++e) q[e] = k.conv(a[e], e, p.tlop);
+                            r = rq_pack16<RQ>(q, k.layer);
                         }
                         asm volatile("" ::: "memory");
                         {
                             const LaneConsts<16, RQ> k(tprm + 4 * C2, C2, c0);
                             const v16i a = wc.run(T + im * TB2 + (f % NF) * wc.FRAG, fa, bias_vector<16, RQ>(k));
+                            int u[16];
 #pragma unroll
-                            for (int e = 0; e < 16; ++e) {
-                                const int u = k.conv(a[e], e, p.tlo2);
-                                q[e] = rq_add_value<RQ, RQA>(r[e], rq_is_top(RQ) ? u >> 24 : u, p.tadd);
-                            }
+                            for (int e = 0; e < 16; ++e) u[e] = k.conv(a[e], e, p.tlo2);
+                            const AddConst add = {p.tadd.mr, p.tadd.ms, p.tadd.c0, p.tadd.k, p.tadd.sh, p.tadd.lo};   // "self" is u here
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) y[i] = (int)rq_add4<RQ, RQA>(u[4 * i], u[4 * i + 1], u[4 * i + 2], u[4 * i + 3], (uint32_t)r[i], add, k.layer);
                         }
                         const long g = img0 + im;
-                        if (g < p.B) *(v4i *)(p.out + ((g * S2 * S2 + (f % NF) * 32 + l) * C2 + c0)) = rq_pack16<RQA>(q);
+                        if (g < p.B) *(v4i *)(p.out + ((g * S2 * S2 + (f % NF) * 32 + l) * C2 + c0)) = y;
                     }
                 }
             });

@@ -198,7 +198,8 @@ void fuse_adds(const ParsedModel &pm, const std::vector<DevOp> &plain, std::vect
                     auto fits = [&](int64_t lo, int64_t hi) { return lo * scale >= INT32_MIN && hi * scale <= INT32_MAX; };
                     const bool top = scale && c.conv.add_lo == -128 && mag(m_self) * scale < (1 << 23) && mag(m_res) * scale < (1 << 23) &&
                                      fits(res_lo, res_hi) && fits(self_lo + c0 + k, self_hi + c0 + k);
-                    c.conv.add_rq = add_ties ? 0 : !top ? 1 : fits(self_lo + res_lo, self_hi + res_hi) ? 3 : 4;
+                    c.conv.add_rq = add_ties ? RQ_ANY : !top ? RQ_TIE_FREE : fits(self_lo + res_lo, self_hi + res_hi) ? RQ_TOP : RQ_TOP_WIDE;
+                    if (!add_ties && c.conv.add_lo == -128) c.conv.add_rq |= RQ_PAIR;   // every sum fits int32 as it is: `bound`
                 }
                 c.b = res;
                 c.out = d.out;
@@ -508,6 +509,7 @@ int build_device_ops(const ParsedModel &pm, std::vector<DevOp> &ops, ConstArena 
             std::vector<int32_t> bias(Mp, 0);
             bool tie_free = fast;
             bool top = (o.relu ? to.zp : -128) == -128;   // top form of the requantisation (conv_device.h)
+            bool pair = top && fast;                      // pair form
             const int64_t maxdev = std::max<int64_t>(127 - ti.zp, ti.zp + 128);   // |q - z_in| of an int8 input
             std::vector<uint32_t> m0x2(Mp, 0x80000000u), rlo(Mp, 0), rhi(Mp, 1), sh(Mp, 1);
             std::vector<int32_t> m0s(Mp, 1 << 30), chi(Mp, 1 + 2 * to.zp), shm1(Mp, 1);
@@ -530,6 +532,7 @@ int build_device_ops(const ParsedModel &pm, std::vector<DevOp> &ops, ConstArena 
                     if (need < 40 && accmax >= (1ll << need)) tie_free = false;
                     // |mulhi(acc, M0)| < 2^23 and 2^(24 - shm1) < 2^23 as 24-bit operands
                     if ((__int128)accmax * o.M0[oc] >= ((__int128)((1 << 23) - 1) << 32) || o.shift[oc] < 3) top = false;
+                    pair = pair && o.shift[oc] == o.shift[0];
                 }
                 int64_t b = (int64_t)o.bias[oc] - (int64_t)ti.zp * wsum;
                 if (b < INT32_MIN || b > INT32_MAX) return ISR_ERR_UNSUPPORTED;
@@ -570,7 +573,7 @@ int build_device_ops(const ParsedModel &pm, std::vector<DevOp> &ops, ConstArena 
             c.shm1 = (const int32_t *)arena.put(shm1.data(), shm1.size() * 4);
             c.fast_requant = fast ? 1 : 0;
             c.tie_free = tie_free ? 1 : 0;
-            c.rq = (tie_free ? 1 : 0) | (top ? 2 : 0);
+            c.rq = (tie_free ? RQ_TIE_FREE : 0) | (top ? RQ_TOP_TIES : 0) | (tie_free && pair ? RQ_PAIR : 0);
             const std::vector<int8_t> zfill(16, (int8_t)ti.zp);
             c.zpad = (const int8_t *)arena.put(zfill.data(), zfill.size());
             // fragment-major copies for the kernel that runs an expanding 1x1 + add and the next reducing 1x1 together
@@ -717,7 +720,7 @@ void fuse_block_and_next(const ParsedModel &pm, std::vector<DevOp> &ops) {
             c.fuse_add || c.k != 1 || c.stride != 1 || c.pad != 0 || c.Cin_p != 256 || c.Kp != 256 || c.Cout_p != 128 || !c.fast_requant || c.c4 || !c.wfrag)
             continue;
         const int rq = a.conv.rq & a.conv2.rq & a.conv3.rq;
-        if ((rq & c.rq) != rq) continue;   // the kernel has one form for all its convolutions: not a longer one for this
+        if (rq_form(rq & c.rq) != rq_form(rq)) continue;   // the kernel has one form for all its convolutions: not a longer one for this
         bool others = false, sparse = true;
         for (size_t j = i + 2; j < ops.size(); ++j) {
             if (ops[j].b == a.out) { others = true; sparse = false; }

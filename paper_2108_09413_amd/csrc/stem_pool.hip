@@ -141,12 +141,13 @@ __global__ __launch_bounds__(SP_NT, 4) void stem_pool_kernel(const StemPoolParam
     int v[16];                                // running maxima of the current pooled row, bias not yet added
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = INT_MIN;
+    const RqLayer L = rq_layer<RQ>(prm[2][0], prm[3][0]);
     auto emit = [&](int py) {
         if (!pxok) return;
         int q[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(v[i] + prm[0][oc + i], prm[1][oc + i], prm[2][oc + rq_chi_at<RQ>(i)], prm[3][oc + i], lo);
-        *(v4i *)(p.out + ((((long)b * p.Hp + py) * p.Wp + px) << 6) + oc) = rq_pack16<RQ>(q);
+        for (int i = 0; i < 16; ++i) q[i] = rq_conv<RQ>(v[i] + prm[0][oc + i], prm[1][oc + i], prm[2][oc + rq_chi_at<RQ>(i)], prm[3][oc + i], lo, L);
+        *(v4i *)(p.out + ((((long)b * p.Hp + py) * p.Wp + px) << 6) + oc) = rq_pack16<RQ>(q, L);
     };
     // pooled row j takes convolution rows 2 j, 2 j + 1, 2 j + 2 of the wave's nine
 #pragma unroll

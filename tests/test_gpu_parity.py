@@ -672,8 +672,27 @@ def test_forms_of_the_requantisation(isr, sh, m0, zp, relu_a, ma, mb, add_sh):
     """Every form of the epilogue (value or top byte, with and without ties, narrow and wide add) at the ends of its
     range, in the direct-to-LDS kernel (plain, fused add, dual convolution) and the bottleneck kernel."""
     _say(f"requantisation forms {sh} {m0} {zp} {relu_a} {ma} {mb} {add_sh}")
+    _check_forms(isr, lambda c: np.full(c, sh), m0, zp, relu_a, ma, mb, add_sh)
+
+
+@pytest.mark.parametrize("sh,by_channel,m0,zp,relu_a,ma,mb,add_sh", [
+    (9, True, None, 0, True, 700001, 800003, 20),                    # shifts that differ: the top-byte form, narrow and wide add
+    (9, True, None, 5, False, 900001, 1000003, 20),
+    (3, True, (1 << 31) - 1, -128, True, (1 << 20) - 1, (1 << 20) - 3, 20),
+    (2, False, (1 << 31) - 1, 0, True, 3, 1, 1),                     # one shift, pairs of results: the ends of the shifts
+    (2, False, None, 127, False, (1 << 22) - 1, (1 << 21) + 1, 24),
+    (22, False, (1 << 31) - 1, -128, False, (1 << 22) + 1, -(1 << 21) - 1, 23),
+    (5, False, None, 3, True, 40000001 >> 4, 3, 22),                 # high words beyond 24 bits
+])
+def test_forms_of_the_requantisation_by_the_layers_shifts(isr, sh, by_channel, m0, zp, relu_a, ma, mb, add_sh):
+    """Layers whose channels share one shift take results in pairs; those whose shifts differ keep the other forms."""
+    _say(f"requantisation forms by shift {sh} {by_channel} {m0} {zp} {relu_a} {ma} {mb} {add_sh}")
+    _check_forms(isr, lambda c: sh + (np.arange(c) % 3 if by_channel else np.zeros(c, dtype=np.int64)), m0, zp, relu_a, ma, mb, add_sh)
+
+
+def _check_forms(isr, shifts, m0, zp, relu_a, ma, mb, add_sh):
     b = NetBuilder(rng=np.random.default_rng(71), in_shape=(3, 9, 12), num_classes=5)
-    kw = lambda c: dict(sh=np.full(c, sh), m0=None if m0 is None else np.full(c, m0, dtype=np.int64))
+    kw = lambda c: dict(sh=shifts(c), m0=None if m0 is None else np.full(c, m0, dtype=np.int64))
     t0 = b.tensor(3, 9, 12, 0, 74.0)
     t1 = b.conv(t0, 64, 3, 1, 1, relu_a, sh=np.full(64, 8))
     u = b.conv(t1, 64, 1, 1, 0, True, **kw(64))
