@@ -246,9 +246,12 @@ struct NarrowParams {
     const int32_t *fc_bias;
     int32_t classes, classes_p;
     int32_t *logits, *argmax;
-    uint32_t *counts;
+    uint32_t *counts;        // votes are added here, or each goes to
+    uint64_t *votes;         // the host's memory, by its place in the list: class, and `seq` in the high word
+    uint32_t seq;
     Slots slots;             // of the votes
 };
+constexpr uint64_t DIRECT_VOTES = 256;   // most votes of a call that go to the host one by one
 
 // Bottleneck block in one kernel: conv1x1 -> conv3x3 [-> conv1x1 + residual add with the block input
 // when tail != 0]; 64 middle channels (bottleneck.hip) or 128 (bottleneck128.hip, tail only).

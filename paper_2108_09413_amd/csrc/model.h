@@ -32,7 +32,10 @@ struct isr_model {
     uint32_t *dcounts = nullptr;        // 2 * classes
     uint32_t *hcounts = nullptr, *hcounts_dev = nullptr;   // pinned, 2 * classes, and its address for kernels
     uint32_t *hflag = nullptr, *hflag_dev = nullptr;       // one word in the same pinned allocation: number of the last call whose tallies arrived
-    uint32_t published = 0;                                // of the last call that published some
+    uint64_t *hvotes = nullptr, *hvotes_dev = nullptr;     // DIRECT_VOTES words in the same pinned allocation: votes that go to the host one by one
+    uint32_t published = 0;                                // number of the last call that had its tallies or votes sent
+    isr::Slots direct{};                // of the running call's votes that go one by one; direct_votes of them, 0: none
+    uint32_t direct_votes = 0;
     hipEvent_t end = nullptr;           // recorded behind tallies whose arrival the host watches
     uint32_t launches = 0;              // of the call that is running
     bool staging_busy = false;          // copies out of htables or hitems may be under way

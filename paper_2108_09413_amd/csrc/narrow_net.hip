@@ -308,6 +308,9 @@ __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t 
         }
         if (lane == 0) {
             if (p.argmax && g < p.B) p.argmax[g] = best_idx;
+            // a call of few copies: the host watches for every vote, no launch behind this one
+            if (p.votes && g < p.B)
+                __hip_atomic_store(&p.votes[p.slots.begin + (uint64_t)g], (uint64_t)p.seq << 32 | (uint32_t)best_idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             best_of[im] = g < p.B ? best_idx : -1;
         }
     }
@@ -797,6 +800,7 @@ static bool narrow_valid(const NarrowParams &p, int channels) {
                    p.classes_p < p.classes || (channels == 64 && p.nblocks == 0)))
         return false;
     if (p.head && p.counts && !valid_slots(p.slots)) return false;
+    if (p.votes && (!p.head || p.counts || p.slots.begin + (uint64_t)p.B > DIRECT_VOTES)) return false;
     return true;
 }
 

@@ -1213,6 +1213,26 @@ def test_tallies_of_every_size_reach_the_host(isr):
     m.close()
 
 
+@pytest.mark.parametrize("net,chunk", [(0, 512), (0, 200), (1, 512)])
+def test_votes_of_few_copies_reach_the_host_one_by_one(isr, net, chunk):
+    """Calls of up to 256 copies in one chunk, whose votes the host tallies, between calls of more: predictions, both phases of a
+    certification, several pairs.  Against the oracle; what one call left in the host's memory counts in no other."""
+    _say(f"single votes, net {net}, chunk {chunk}")
+    blob = synth.build_model(net)
+    m, om = _load(isr, blob, chunk), oracle.Model(blob)
+    x = synth.make_image(net, 1)
+    for k, n in enumerate([256, 1, 255, 257, 201, 200, 3]):
+        res, counts = isr.isr_predict(m, x, 64, n, ALPHA, seed=k, image_id=k)
+        assert np.array_equal(counts, om.mc(x, 64, k, k, 0, 0, n)[2]), n
+    for n0, n in [(100, 156), (100, 157), (1, 1), (20, 170)]:
+        res, c0, c1 = isr.isr_certify(m, x, 32, n0, n, ALPHA, seed=n, image_id=3)
+        assert np.array_equal(c0, om.mc(x, 32, n, 3, 0, 0, n0)[2]) and np.array_equal(c1, om.mc(x, 32, n, 3, 1, 0, n)[2]), (n0, n)
+    for pairs, n0, n in [(5, 20, 31), (5, 20, 32), (1, 30, 40)]:
+        items = [(0, 32 + i, 7 + i) for i in range(pairs)]
+        _check_batch_against_oracle(isr, m, om, x[None], items, n0, n, seed=n)
+    m.close()
+
+
 @pytest.mark.parametrize("pairs,chunk,fusion", [(256, 4096, 1), (257, 4096, 1), (1, 8, 0), (2, 8, 0)])
 def test_calls_in_a_row_whichever_way_they_end(isr, pairs, chunk, fusion):
     """Batched calls one right behind the other, with other noise levels and pairs each time, whose descriptors and tables go through the
