@@ -226,7 +226,10 @@ int build_narrow_ops(isr_model *m, ConstArena &arena, size_t limit) {
             if (!d.narrow) continue;
             if (np.prm0) np.prm0 = dconsts + (size_t)np.prm0 - 1;
             if (np.tprm) np.tprm = dconsts + (size_t)np.tprm - 1;
-            if (np.blocks) np.blocks = (const NarrowBlock *)dnarrow + (size_t)np.blocks - 1;
+            if (np.blocks) {
+                np.first = blocks[(size_t)np.blocks - 1];
+                np.blocks = (const NarrowBlock *)dnarrow + (size_t)np.blocks - 1;
+            }
         }
     const size_t at = arena.host.size();
     arena.host.resize(at + block_bytes + consts.size() * 4);

@@ -234,6 +234,7 @@ struct NarrowParams {
     // chain of identity blocks
     int32_t nblocks;
     const NarrowBlock *blocks;
+    NarrowBlock first;       // blocks[0], which a kernel then has without a load of its descriptor
     // tail 1: down-sampling block t = conv3x3/2(x), u = conv3x3(t), r = conv1x1/2(x), y = add(r, u); 2: t alone
     int32_t tail, tform;     // form as above
     const int8_t *tw1, *tw2, *twp;

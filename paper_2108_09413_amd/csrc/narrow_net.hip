@@ -13,7 +13,8 @@
 // (and the same of the upper half), from 64 banks of 4 bytes.  At 32 channels (a fragment is two rows of 16 pixels, 32
 // bytes a pixel) each of these sets takes from either row 8 pixels that are all different mod 8, at 64 channels (four rows of
 // 8 pixels, 64 bytes a pixel) from each row 4 that are different mod 4: with chunk c of the pixel at padded (y, x) at chunk
-// c ^ (y mod 2), resp. c ^ (y mod 4), no two lanes of a set meet in a bank.  Columns and rows of a tap are immediate
+// c ^ (y mod 2), resp. c ^ (0, 2, 1, 3 for y mod 4), no two lanes of a set meet in a bank, nor those of a read of two rows of 8
+// pixels and four chunks.  Columns and rows of a tap are immediate
 // offsets from a base address per parity of the row.
 //
 // What bounds it: issue of the requantisation arithmetic, the matrix unit and the LDS reads of the pixel operands, all three
@@ -43,7 +44,7 @@ typedef int v4acc __attribute__((ext_vector_type(4)));
 // all rows of a read have the same parity and columns 8 apart must differ.
 template <int C, int S, bool STRIDED = false>
 __device__ __forceinline__ int tile_at(int y, int x, int chunk) {
-    const int s = C == 64 ? (y & 3) : C == 32 ? (STRIDED ? (x >> 3) & 1 : y & 1) : 0;
+    const int s = C == 64 ? 2 * (y & 1) + (y >> 1 & 1) : C == 32 ? (STRIDED ? (x >> 3) & 1 : y & 1) : 0;
     return ((y * (S + 2) + x) * (C / 16) + (chunk ^ s)) * 16;
 }
 template <int C, int S>
@@ -383,8 +384,6 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const long img0 = (long)blockIdx.x * NI;
-    typedef const __attribute__((address_space(4))) NarrowBlock *block_ptr;   // scalar loads
-    const block_ptr blocks = (block_ptr)(uintptr_t)p.blocks;
 
     // ---- the stage's input ----
     // constants, the sampler's table and the first weights are all on their way before any of them is waited for
@@ -407,12 +406,22 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
             vn = fetch_noise_table<NT>(table, tid);
         }
     }
-    if (p.nblocks && tid < 4 * C) v0 = blocks[0].prm1[tid];
+    if (p.nblocks && tid < 4 * C) v0 = p.first.prm1[tid];
     if (TAIL && p.tail)
 #pragma unroll
         for (int j = 0; j < NTP; ++j)
             if (tid + NT * j < 3 * 4 * C2) vt[j] = p.tprm[tid + NT * j];
-    v4i fa[WIDE ? WideConv<WIDE ? C : 32, WIDE ? S : 16>::KS : 3];   // weights of the convolution to come
+    // One image of 64 channels: a wave makes 16 channels of all pixels, so that every weight enters the CU once; with 32 channels x half of
+    // the pixels a wave, each weight twice, those 72 KB took most of a convolution's 2900 to 3600 cycles (prediction of the 110-layer
+    // net with 100 copies 141.6 -> 131.9 us, together with the down-sampling weights fetched ahead and the first descriptor as an
+    // argument; ResNet-20 40.3 -> 39.6).
+    constexpr bool SLIM = C == 64 && NI == 1;
+    v4i fa[SLIM ? 9 : WIDE ? WideConv<WIDE ? C : 32, WIDE ? S : 16>::KS : 3];   // weights of the convolution to come
+    auto slim_weights = [&](const int8_t *w, v4i (&f)[9]) {
+        const int row = 32 * (wave >> 1) + 8 * ((lane & 15) >> 2) + 4 * (wave & 1) + (lane & 3);   // of channel 16 wave + (lane & 15), in MFMA row order
+#pragma unroll
+        for (int ks = 0; ks < 9; ++ks) f[ks] = *(const v4i *)(w + row * 576 + ks * 64 + (lane >> 4) * 16);
+    };
     // 16 channels: a lane's weights, by kernel row; the fourth lane group's are the zeros behind the nine taps
     auto narrow_weights = [&](const int8_t *w, v4i (&f)[3]) {
         constexpr int KP = (9 * 16 + 63) / 64 * 64;
@@ -423,10 +432,20 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
     int vp = 0;   // AHEAD: constants of the convolution after the next
     Block<AHEAD> cur(p, 0, lane), nxt(p, 1, lane);
     if (p.nblocks) {
-        if constexpr (WIDE) WideConv<C, S>(lane, wave).load_weights(blocks[0].w1, fa);
-        else if constexpr (AHEAD) narrow_weights(blocks[0].w1, fa);
-        if (AHEAD && tid < 4 * C) vp = blocks[0].prm2[tid];
+        if constexpr (SLIM) slim_weights(p.first.w1, fa);
+        else if constexpr (WIDE) WideConv<C, S>(lane, wave).load_weights(p.first.w1, fa);
+        else if constexpr (AHEAD) narrow_weights(p.first.w1, fa);
+        if (AHEAD && tid < 4 * C) vp = p.first.prm2[tid];
     }
+    // weights of the down-sampling block's first convolution; AHEAD: fetched while the last block's second one runs
+    constexpr int KP1 = (9 * C + 63) / 64 * 64, KS1 = TAIL ? (9 * C + 31) / 32 : 1;
+    v4i f1[KS1];
+    auto tail_weights = [&]() {
+        const int mf = wave % (C2 / 32);
+#pragma unroll
+        for (int ks = 0; ks < KS1; ++ks) f1[ks] = *(const v4i *)(p.tw1 + (mf * 32 + (lane & 31)) * KP1 + ks * 32 + (lane >> 5) * 16);
+    };
+    if (AHEAD && TAIL && p.tail && !p.nblocks) tail_weights();
     auto store_constants = [&]() {
         if (p.nblocks && tid < 4 * C) prm[0][tid] = v0;
         if (TAIL && p.tail)
@@ -434,7 +453,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
             for (int j = 0; j < NTP; ++j)
                 if (tid + NT * j < 3 * 4 * C2) tprm[tid + NT * j] = vt[j];
     };
-    if (p.nblocks) fill_ring<C, S, NI, NT>(X, blocks[0].zp_x, tid);
+    if (p.nblocks) fill_ring<C, S, NI, NT>(X, p.first.zp_x, tid);
     else if (p.tail) fill_ring<C, S, NI, NT>(X, p.tzp_x, tid);
     if (from_image) {
         if constexpr (C == 16) {
@@ -536,6 +555,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 if (AHEAD) vp = nxt.prm2()[tid];
             }
             if (zp_next != zp_x) fill_ring<C, S, NI, NT>(X, zp_next, tid);
+            if (AHEAD && TAIL && last && p.tail) tail_weights();
         };
         with_form(cur.form(), [&](auto rq, auto rqa) {
             constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
@@ -600,6 +620,54 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                         }
                     };
                 });
+            } else if constexpr (SLIM) {
+                // v_mfma_i32_16x16x64_i8, a K step is a tap: lane group g holds its chunk g, a block of 16 pixels is two rows, the lane's
+                // result four channels of a pixel of each of the four blocks
+                const int px = lane & 15, g = lane >> 4, r = px >> 3;
+                int base[4];   // by the row of the tap, mod 4, of the lane's upper pixel
+#pragma unroll
+                for (int j = 0; j < 4; ++j) base[j] = tile_at<C, S>(r + j, px & 7, g) - j * P * C;
+                const int out = tile_at<C, S>(r + 1, (px & 7) + 1, wave) + 4 * g, out2 = tile_at<C, S>(r + 3, (px & 7) + 1, wave) + 4 * g;   // blocks 0 and 1
+                auto place = [&](int nb) { return (nb & 1 ? out2 : out) + (nb >> 1) * 4 * P * C; };
+                // weights w; those at `next` are fetched into `wn` meanwhile; result(block, accumulators, constants)
+                auto conv = [&](const int8_t *src, const v4i (&w)[9], const int8_t *next, v4i (&wn)[9], const int *pr, auto result) {
+                    slim_weights(next, wn);
+                    const LaneConsts<4, RQ> k(pr, C, 16 * wave + 4 * g);
+                    k.fragment();
+                    auto operand = [&](int ks, int nb) { const int y = 2 * nb + ks / 3; return *(const v4i *)(src + base[y & 3] + (y * P + ks % 3) * C); };
+                    constexpr int RING = 3;
+                    v4i b[RING][4];
+                    v4acc acc[4];
+#pragma unroll
+                    for (int ks = 0; ks < RING - 1; ++ks)
+#pragma unroll
+                        for (int nb = 0; nb < 4; ++nb) b[ks][nb] = operand(ks, nb);
+#pragma unroll
+                    for (int nb = 0; nb < 4; ++nb) acc[nb] = bias_vector<4, RQ>(k);
+#pragma unroll
+                    for (int ks = 0; ks < 9; ++ks) {
+                        if (ks + RING - 1 < 9)
+#pragma unroll
+                            for (int nb = 0; nb < 4; ++nb) b[(ks + RING - 1) % RING][nb] = operand(ks + RING - 1, nb);
+#pragma unroll
+                        for (int nb = 0; nb < 4; ++nb) acc[nb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[ks], b[ks % RING][nb], acc[nb], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+#pragma unroll
+                    for (int nb = 0; nb < 4; ++nb) result(nb, acc[nb], k);
+                };
+                v4i fn[9];
+                conv(X, fa, cur.w2(), fn, prm[0], [&](int nb, const v4acc &a, const LaneConsts<4, RQ> &k) {
+                    *(uint32_t *)(T + place(nb)) = rq_pack<RQ>(k.conv(a[0], 0, lo1), k.conv(a[1], 1, lo1), k.conv(a[2], 2, lo1), k.conv(a[3], 3, lo1), k.layer);
+                });
+                second_constants();
+                const AddConst ac = cur.add();
+                uint32_t rv[4];
+#pragma unroll
+                for (int nb = 0; nb < 4; ++nb) rv[nb] = *(const uint32_t *)(X + place(nb));
+                conv(T, fn, nxt.w1(), fa, prm[1], [&](int nb, const v4acc &a, const LaneConsts<4, RQ> &k) {
+                    *(uint32_t *)(X + place(nb)) = rq_add4<RQ, RQA>(k.conv(a[0], 0, lo2), k.conv(a[1], 1, lo2), k.conv(a[2], 2, lo2), k.conv(a[3], 3, lo2), rv[nb], ac, k.layer);
+                });
             } else {
                 typedef WideConv<C, S> Wide;
                 constexpr int MF = Wide::MF, NF = Wide::NF, FRAGS = NI * NF * MF / NW;   // fragments per wave
@@ -646,7 +714,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
     // ---- down-sampling into the next stage ----
     if constexpr (TAIL) {
         if (p.tail) {
-            constexpr int TB2 = tile_bytes<C2, S2>(), KP1 = (9 * C + 63) / 64 * 64, KS1 = (9 * C + 31) / 32;
+            constexpr int TB2 = tile_bytes<C2, S2>();
             static_assert(NI * TB2 <= NI * TB, "the next stage's tile fits the middle tensor's");
             typedef WideConv<C2, S2> Wide;
             constexpr int MF = Wide::MF, NF = Wide::NF, FRAGS = (NI * NF * MF + NW - 1) / NW;   // fragments per wave (of fewer fragments than waves: one of the first waves)
@@ -657,13 +725,17 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
                 int ln = lane;
                 asm volatile("" : "+v"(ln));
+                if (!AHEAD) tail_weights();
+                v4i fa[Wide::KS], fp;   // of the other two convolutions; AHEAD: on their way while the first runs
+                auto more_weights = [&](const Wide &wc) {
+                    wc.load_weights(p.tw2, fa);
+                    fp = *(const v4i *)(p.twp + (wc.mf * 32 + wc.l) * 64 + wc.half * 16);   // channels 0 .. 31 (zeros past C)
+                };
+                if (AHEAD && p.tail == 1) more_weights(Wide(ln, wave));
                 {
                     const Wide wc(ln, wave);
                     const int l = wc.l, half = wc.half, mf = wc.mf, c0 = mf * 32 + half * 16;
                     const int oy0 = l / S2, ox = l % S2;       // the lane's output pixel in fragment 0
-                    v4i f1[KS1];
-#pragma unroll
-                    for (int ks = 0; ks < KS1; ++ks) f1[ks] = *(const v4i *)(p.tw1 + (mf * 32 + l) * KP1 + ks * 32 + half * 16);
                     // tap (ky, kx) of output (oy, ox) is padded input (2 oy + ky, 2 ox + kx).  16 input channels: a K step is two taps,
                     // the lane half picks one (the tenth has zero weights); 32: one tap, the half picks 16 channels
                     int b1[KS1];
@@ -699,9 +771,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                     const Wide wc(ln, wave);
                     const int l = wc.l, half = wc.half, mf = wc.mf, c0 = mf * 32 + half * 16;
                     const int oy0 = l / S2, ox = l % S2;
-                    v4i fa[Wide::KS];
-                    wc.load_weights(p.tw2, fa);
-                    const v4i fp = *(const v4i *)(p.twp + (mf * 32 + l) * 64 + half * 16);   // channels 0 .. 31 (zeros past C)
+                    if (!AHEAD) more_weights(wc);
                     const int xp = tile_at<C, S, true>(2 * oy0 + 1, 2 * ox + 1, C == 16 ? 0 : half);
                     lds_barrier();
 #pragma unroll 1
@@ -754,7 +824,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
 }
 
 template <int C, int S, int NI, int NW>
-__global__ __launch_bounds__(64 * NW, C == 16 ? 4 : 2) void narrow_kernel(const NarrowParams p) { narrow_stage<C, S, NI, NW>(p); }
+__global__ __launch_bounds__(64 * NW, C == 16 && NW == 4 ? 4 : 2) void narrow_kernel(const NarrowParams p) { narrow_stage<C, S, NI, NW>(p); }
 
 // The three stages of a net in one launch (narrow_chain_wanted): a workgroup reads back only what it has written, so that nothing but
 // its barrier orders the stages; other images are at other stages meanwhile, so that the tensors have to lie apart (images_apart).
