@@ -22,7 +22,8 @@
 // 4: 23 for 16), waves of 4 pooled rows compute 9 convolution rows for 8 (waves of 2: 5 for 4), the bias joins the maxima
 // and not the accumulators, and a column outside the image is replaced by one of the same window instead of being masked:
 // 668 copies of 224 x 224 303 -> 269 us by the bands, the waves and the bias, 291 -> 246 us with the columns as well (each pair
-// on a card of its own).
+// on a card of its own).  Even columns read as 16 bytes a lane (two reads of 8, 16 bytes apart from lane to lane, take half of the
+// banks each: conflicts were 41 % of the cycles) and the neighbour's maximum in the DPP operand: 256 -> 239.5 us.
 #include <climits>
 
 #include "conv_device.h"
@@ -160,9 +161,8 @@ __global__ __launch_bounds__(SP_NT, 4) void stem_pool_kernel(const StemPoolParam
 #pragma unroll
             for (int ky = 0; ky < SP_K; ++ky) {
                 const int off = (2 * cyl + ky) * rowbytes;
-                const long long e0 = *(const long long *)(srce + off), e1 = *(const long long *)(srce + off + 8);
                 const long long o0 = *(const long long *)(srco + off), o1 = *(const long long *)(srco + off + 8);
-                const v4i fe = {(int)e0, (int)(e0 >> 32), (int)e1, (int)(e1 >> 32)};
+                const v4i fe = *(const v4i *)(srce + off);   // a row is a multiple of 16 bytes, an even column at one
                 const v4i fo = {(int)o0, (int)(o0 >> 32), (int)o1, (int)(o1 >> 32)};
                 ae = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ky], fe, ae, 0, 0, 0);
                 ao = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ky], fo, ao, 0, 0, 0);
@@ -172,7 +172,9 @@ __global__ __launch_bounds__(SP_NT, 4) void stem_pool_kernel(const StemPoolParam
                 // lane + 1 holds column 2 px + 1 (wave_shl:1 reads the next lane; the last one, which has none, makes no pixel)
                 const int right = __builtin_amdgcn_mov_dpp(ao[i], 0x130, 0xf, 0xf, true);
                 if (r % 2) {
-                    v[i] = max(max(v[i], max(ae[i], ao[i])), right);
+                    int m = max(v[i], max(ae[i], ao[i]));
+                    asm("" : "+v"(m));   // three operands in one instruction and the neighbour in the next, which reads it by DPP
+                    v[i] = max(m, right);
                 } else {
                     h[i] = max(max(ae[i], ao[i]), right);
                     v[i] = max(v[i], h[i]);
