@@ -25,17 +25,22 @@ constexpr int PBN = 256;                         // pixels per tile
 constexpr int PROWS = 320;                       // staged pixel rows per buffer: 256 + 2 (W + 1) <= 320 for W <= 31
 constexpr int PZBYTES = 256;                     // zero points behind them: one pass over the 64 LDS banks
 
+// Who issues the loads of a step: every wave its share; one wave per SIMD, the groups of waves in turn; or four waves that do nothing else.
+enum PatchLoads { EACH, DUTY_GROUP, LOADERS };
+constexpr int patch_threads(int bm, int loads) { return ((bm / 64) * (PBN / 64) + (loads == LOADERS ? 4 : 0)) * 64; }
+
 // NAB: weight buffers; the weights of step t + NAB - 1 are fetched as step t begins.
-template <int BM, int KB, int NAB, int MINB, int RQ, bool DUTY>
-__global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_kernel(const ConvParams p) {
-    constexpr int WGM = BM / 64, NW = WGM * (PBN / 64), NT = NW * 64;
+template <int BM, int KB, int NAB, int MINB, int RQ, int LOADS>
+__global__ __launch_bounds__(patch_threads(BM, LOADS), MINB) void conv_patch_kernel(const ConvParams p) {
+    constexpr bool DUTY = LOADS == DUTY_GROUP, EVERY = LOADS == EACH;
+    constexpr int WGM = BM / 64, NW = WGM * (PBN / 64), NT = patch_threads(BM, LOADS);   // NW: waves that multiply
     constexpr int CPR = KB / 16;                 // 16-byte chunks per row
-    constexpr int RPP = NT / CPR;                // rows covered by one pass of all threads
-    constexpr int NA = BM / RPP;                 // weight loads per lane per step
+    constexpr int RPP = EVERY ? NT / CPR : 128;  // rows covered by one pass of all threads
+    constexpr int NA = EVERY ? BM / RPP : 1;     // weight loads per lane per step
     constexpr int KS = KB / 32;
     constexpr int ABUF = BM * KB, ZOFF = PROWS * KB, BBUF = ZOFF + PZBYTES;
     constexpr int BPP = (PROWS + RPP - 1) / RPP; // pixel rows of a lane
-    static_assert((RPP == 128 || (RPP < 128 && RPP % 32 == 0 && !DUTY)) && BM % RPP == 0 && (KB == 64 || KB == 128) && ZOFF % 256 == 0, "tile shape");
+    static_assert((!EVERY || (RPP <= 128 && RPP % 32 == 0 && BM % RPP == 0)) && (KB == 64 || KB == 128) && ZOFF % 256 == 0, "tile shape");
 
     __shared__ __attribute__((aligned(256))) int8_t Bs[2][BBUF];
     __shared__ __attribute__((aligned(16))) int8_t As[NAB][ABUF];
@@ -58,13 +63,17 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     // waves 4 g .. 4 g + 3), the other waves go straight to their fragment reads and MFMAs.  A wave is held about
     // 200 cycles at each direct-to-LDS load it issues (in-kernel timestamps), whoever else issues; the other waves of
     // its SIMD, and the second workgroup of the CU, keep the matrix pipe busy meanwhile.
-    constexpr int RW = 1024 / KB, NG = NW / 4, LA = BM / RW / 4, LB = 128 / RW / 4;
-    static_assert(!DUTY || (NW % 4 == 0 && LA >= 1 && LB >= 2), "duty groups");
+    // LOADERS: in launches of few tiles one or two waves multiply on a SIMD, and nothing covers the 300 to 500 cycles of a step's 1500
+    // that they are held (the loads themselves are waited for by nobody); four waves more, one on each SIMD, issue all loads. 100
+    // copies of 512 channels at 7 x 7: 25.0 -> 21.3 us, of 256 at 14 x 14: 20.1 -> 19.2.
+    constexpr int RW = 1024 / KB, NG = DUTY ? NW / 4 : 1, LA = BM / RW / 4, LB = 128 / RW / 4;
+    static_assert(EVERY || (NW % 4 == 0 && LA >= 1 && LB >= 2), "duty groups");
     const int sigma = wave & 3, grp = wave >> 2;
+    const bool loader = LOADS == LOADERS && wave >= NW;
     const int lrow = lane / CPR, lcol = lane % CPR;
     const uint32_t a_lds0 = lds_address(&As[0][0]), b_lds0 = lds_address(&Bs[0][0]);
-    uint32_t aofs[DUTY ? LA : 1];   // DUTY: byte offset in the weight matrix of the lane's 16 bytes of wave-load sigma LA + j
-    if constexpr (DUTY) {
+    uint32_t aofs[EVERY ? 1 : LA];   // byte offset in the weight matrix of the lane's 16 bytes of wave-load sigma LA + j
+    if constexpr (!EVERY) {
 #pragma unroll
         for (int j = 0; j < LA; ++j) {
             const int row = (sigma * LA + j) * RW + lrow, r = m0 + row;
@@ -94,9 +103,9 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     // every wave its share: lane (row0, col) of a pass of all threads fetches chunk col ^ swz(row0) of row row0 + 128 j
     const int col = tid % CPR, row0 = tid / CPR;
     const int cl = col ^ swz<CPR>(row0);
-    const int8_t *wrow[DUTY ? 1 : NA];
-    uint32_t prow[DUTY ? 1 : BPP];
-    if constexpr (!DUTY) {
+    const int8_t *wrow[NA];
+    uint32_t prow[EVERY ? BPP : 1];
+    if constexpr (EVERY) {
 #pragma unroll
         for (int j = 0; j < NA; ++j) {
             const int r = m0 + row0 + RPP * j;
@@ -112,7 +121,7 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     }
     // weights of step t = (slice, tap) into buffer t mod NAB
     auto issue_a = [&](int slice, int tap, int buf) {
-        if constexpr (DUTY) issue_a_duty(slice, tap, buf);
+        if constexpr (!EVERY) issue_a_duty(slice, tap, buf);
         else {
             const uint32_t sa = a_lds0 + wave * 1024 + buf * ABUF;
             const long koff = (long)tap * p.Cin_p + slice * KB;
@@ -122,7 +131,7 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     };
     // pass j (128 rows; the third pass covers rows 256..319 with the first half of the waves) of a slice's pixel rows
     auto issue_b = [&](int slice, int j, int buf) {
-        if constexpr (DUTY) issue_b_duty(slice, j, buf);
+        if constexpr (!EVERY) issue_b_duty(slice, j, buf);
         else {
 #pragma unroll
             for (int h = 0; h < 128 / RPP; ++h) {
@@ -142,7 +151,7 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
 #pragma unroll
         for (int u = 1; u < NAB; ++u)
             if (grp == u % NG) issue_a(0, u, u);
-    } else {
+    } else if (EVERY || loader) {
         issue_b(0, 0, 0); issue_b(0, 1, 0); issue_b(0, 2, 0);
 #pragma unroll
         for (int u = 0; u < NAB; ++u) issue_a(0, u, u);   // steps 0 .. are taps 0 .. of slice 0
@@ -217,7 +226,7 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     // u - 1 used, and, during the first three taps of a slice, a pass of the next slice's pixel rows into the
     // activation buffer that was last read in the previous slice
     auto refill = [&](int u, int slice, int tap) {
-        if (!DUTY || (u & (NG - 1)) == grp) {
+        if (DUTY ? (u & (NG - 1)) == grp : EVERY || loader) {
             if (u >= 1 && u + NAB - 1 < nk) {
                 const int nt = tap + NAB - 1, wrap = nt >= 9;
                 issue_a(slice + wrap, wrap ? nt - 9 : nt, (u + NAB - 1) % NAB);
@@ -243,11 +252,23 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     };
     int slice = 0, tap = 0;
     int brow[2];
-    constexpr int PENDING = DUTY ? (NAB - 2) / NG * LA : (NAB - 2) * NA;
-    if (!DUTY) wait_vmcnt<(NAB - 1) * NA>();
+    constexpr int STEP_LOADS = EVERY ? NA : LA;   // of the weights, by a wave that issues any
+    constexpr int PENDING = DUTY ? (NAB - 2) / NG * LA : (NAB - 2) * STEP_LOADS;
+    if (!DUTY) wait_vmcnt<(NAB - 1) * STEP_LOADS>();
     else wait_vmcnt<0>();
     lds_barrier();   // step 0 landed
     refill(0, 0, 0);
+    if (loader) {
+#pragma unroll 1
+        for (int t = 0; t + 1 < nk; ++t) {
+            if (PENDING > 0 && t + NAB - 1 < nk) wait_vmcnt<PENDING>();
+            else wait_vmcnt<0>();
+            lds_barrier();   // as below
+            if (++tap == 9) { tap = 0; ++slice; }
+            refill(t + 1, slice, tap);
+        }
+        return;
+    }
     tap_rows(0, brow);
     read_fragments(As[0], Bs[0], brow, 0, 0);
 #pragma unroll 1
@@ -259,8 +280,10 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
             if (ksub + 1 < KS) {
                 read_fragments(abase, bbase, brow, ksub + 1, slot ^ 1);
             } else if (t + 1 < nk) {
-                if (PENDING > 0 && t + NAB - 1 < nk) wait_vmcnt<PENDING>();
-                else wait_vmcnt<0>();
+                if (LOADS != LOADERS) {
+                    if (PENDING > 0 && t + NAB - 1 < nk) wait_vmcnt<PENDING>();
+                    else wait_vmcnt<0>();
+                }
                 lds_barrier();   // every wave's loads of step t + 1 landed; every wave is done reading step t
                 if (++tap == 9) { tap = 0; ++slice; }
                 refill(t + 1, slice, tap);
@@ -299,13 +322,13 @@ __global__ __launch_bounds__((BM / 64) * (PBN / 64) * 64, MINB) void conv_patch_
     }
 }
 
-template <int BM, int KB, int NAB, int MINB, bool DUTY>
+template <int BM, int KB, int NAB, int MINB, int LOADS>
 hipError_t launch_patch(const ConvParams &p, hipStream_t st, const char *name) {
     const dim3 grid((unsigned)(((p.npix + PBN - 1) / PBN) * ((p.Cout_p + BM - 1) / BM)));
-    const dim3 block((BM / 64) * (PBN / 64) * 64);
+    const dim3 block(patch_threads(BM, LOADS));
     set_kernel_name(name);
     with_rq(p.rq, [&](auto rq) {
-        hipLaunchKernelGGL((conv_patch_kernel<BM, KB, NAB, MINB, decltype(rq)::value, DUTY>), grid, block, 0, st, p);
+        hipLaunchKernelGGL((conv_patch_kernel<BM, KB, NAB, MINB, decltype(rq)::value, LOADS>), grid, block, 0, st, p);
     });
     return hipGetLastError();
 }
@@ -331,13 +354,14 @@ hipError_t launch_conv_patch(const ConvParams &p, hipStream_t st) {
     // One issuing wave per SIMD and step pays with two workgroups per CU (the other workgroup computes while that wave
     // is held at its loads: 1720 -> 1810 TOP/s on 3x3 128 -> 128 at 28 x 28); with one workgroup per CU the issuing
     // wave, which still has its own MFMAs to do, becomes the last to reach the barrier (2120 -> 2060).
-    if (p.Cout_p < 256) return launch_patch<128, 64, 4, 2, true>(p, st, "conv_patch_kernel<128, 256, 64>");
+    if (p.Cout_p < 256) return launch_patch<128, 64, 4, 2, DUTY_GROUP>(p, st, "conv_patch_kernel<128, 256, 64>");
     // Launches with tiles for less than half of the CUs are a chain of K steps that wait for weights, which nobody has
-    // brought into the caches before: half or a quarter of the channels per workgroup, weights fetched three steps ahead.
+    // brought into the caches before: half or a quarter of the channels per workgroup, weights fetched three steps ahead by waves
+    // of their own.
     const long tiles = conv_patch_tiles(p);
-    if (tiles < 64) return launch_patch<64, 128, 4, 1, false>(p, st, "conv_patch_kernel<64, 256, 128>");
-    if (tiles < 128) return launch_patch<128, 128, 4, 1, false>(p, st, "conv_patch_kernel<128, 256, 128>");
-    return launch_patch<256, 128, 2, 1, false>(p, st, "conv_patch_kernel<256, 256, 128>");
+    if (tiles < 64) return launch_patch<64, 128, 4, 1, LOADERS>(p, st, "conv_patch_kernel<64, 256, 128>");
+    if (tiles < 128) return launch_patch<128, 128, 4, 1, LOADERS>(p, st, "conv_patch_kernel<128, 256, 128>");
+    return launch_patch<256, 128, 2, 1, EACH>(p, st, "conv_patch_kernel<256, 256, 128>");
 }
 
 }  // namespace isr
