@@ -222,6 +222,13 @@ struct NarrowBlock {         // identity residual block, stored in device memory
     AddConst add;
     int32_t pad_;
 };
+// Counters of a launch whose last workgroup sends the tallies, zero before and after: votes and finished workgroups of every sixteenth
+// workgroup, and how many of these parts are complete.  Additions to one word come through 10 ns apart, whichever workgroups make them.
+constexpr uint32_t TALLY_PARTS = 16, SENT_TALLIES = 256, SENT_COPIES = 4096;   // most tallies and copies of a call that ends this way
+struct TallyParts {
+    struct { uint32_t finished, unused[31], votes[SENT_TALLIES]; } part[TALLY_PARTS];
+    uint32_t complete;
+};
 struct NarrowParams {
     const int8_t *in;        // [B][S][S][C], or the NHWC4 image [B][S][S][4] (stem != 0)
     int8_t *out;             // [B][S][S][C]; tail != 0: [B][S/2][S/2][2C]; unused with a head
@@ -250,6 +257,11 @@ struct NarrowParams {
     uint32_t *counts;        // votes are added here, or each goes to
     uint64_t *votes;         // the host's memory, by its place in the list: class, and `seq` in the high word
     uint32_t seq;
+    // with counts, in the last launch of a call: votes go to `parts`, and the last workgroup to finish sends the `tallies` sums of these and
+    // the counters to `tally_host`, leaves zeros in their place and stores `seq` to `flag`.  0: none
+    uint32_t tallies;
+    uint32_t *tally_host, *flag;
+    TallyParts *parts;
     Slots slots;             // of the votes
 };
 constexpr uint64_t DIRECT_VOTES = 256;   // most votes of a call that go to the host one by one

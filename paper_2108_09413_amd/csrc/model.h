@@ -30,16 +30,18 @@ struct isr_model {
     uint32_t table_sigma[TABLE_SLOTS] = {0};
     int table_next = 0;
     uint32_t *dcounts = nullptr;        // 2 * classes
+    isr::TallyParts *dparts = nullptr;  // in the same allocation
     uint32_t *hcounts = nullptr, *hcounts_dev = nullptr;   // pinned, 2 * classes, and its address for kernels
     uint32_t *hflag = nullptr, *hflag_dev = nullptr;       // one word in the same pinned allocation: number of the last call whose tallies arrived
     uint64_t *hvotes = nullptr, *hvotes_dev = nullptr;     // DIRECT_VOTES words in the same pinned allocation: votes that go to the host one by one
     uint32_t published = 0;                                // number of the last call that had its tallies or votes sent
     isr::Slots direct{};                // of the running call's votes that go one by one; direct_votes of them, 0: none
     uint32_t direct_votes = 0;
+    uint32_t sent_tallies = 0;          // of the running call's tallies, by its last stage kernel itself; 0: none
     hipEvent_t end = nullptr;           // recorded behind tallies whose arrival the host watches
     uint32_t launches = 0;              // of the call that is running
     bool staging_busy = false;          // copies out of htables or hitems may be under way
-    bool counts_clean = false, counts_b_clean = false;     // dcounts, dcounts_b hold zeros
+    bool counts_clean = false, counts_b_clean = false, parts_clean = false;   // dcounts, dcounts_b, dparts hold zeros
     // batched calls: item descriptors and per-item vote counters, grown on demand
     NoiseItem *ditems = nullptr, *hitems = nullptr;
     uint32_t *dcounts_b = nullptr, *hcounts_b = nullptr, *hcounts_b_dev = nullptr;   // 2 * items_cap * classes each

@@ -1233,6 +1233,30 @@ def test_votes_of_few_copies_reach_the_host_one_by_one(isr, net, chunk):
     m.close()
 
 
+@pytest.mark.parametrize("net", [0, 1])
+def test_tallies_that_the_last_workgroup_sends(isr, net):
+    """Calls of more than 256 votes whose last launch is of 1 to 33 workgroups and of all (16 parts count them), with and without another
+    launch before it, and of up to 256 tallies and more (10 classes, two phases, 12 pairs and 13), one behind the other: the counters
+    are zero again after each, also for a call whose votes go to the host one by one.  Against the oracle."""
+    _say(f"tallies of the last workgroup, net {net}")
+    blob = synth.build_model(net)
+    om = oracle.Model(blob)
+    x = synth.make_image(net, 1)
+    for chunk, ns in [(8, (257, 264, 263)), (17, (288, 289, 17, 290)), (512, (257, 272, 300, 512))]:
+        m = _load(isr, blob, chunk)
+        isr.isr_set_fusion(m, 2)
+        for k, n in enumerate(ns):
+            res, counts = isr.isr_predict(m, x, 64, n, ALPHA, seed=k, image_id=k)
+            assert np.array_equal(counts, om.mc(x, 64, k, k, 0, 0, n)[2]), (chunk, n)
+        m.close()
+    m = _load(isr, blob, 512)
+    for pairs in (12, 13, 2):
+        _check_batch_against_oracle(isr, m, om, x[None], [(0, 32 + i % 5, 7 + i) for i in range(pairs)], 7, 300 // pairs, seed=pairs)
+        res, c0, c1 = isr.isr_certify(m, x, 32, 20, 280, ALPHA, seed=pairs, image_id=3)
+        assert np.array_equal(c0, om.mc(x, 32, pairs, 3, 0, 0, 20)[2]) and np.array_equal(c1, om.mc(x, 32, pairs, 3, 1, 0, 280)[2])
+    m.close()
+
+
 @pytest.mark.parametrize("pairs,chunk,fusion", [(256, 4096, 1), (257, 4096, 1), (1, 8, 0), (2, 8, 0)])
 def test_calls_in_a_row_whichever_way_they_end(isr, pairs, chunk, fusion):
     """Batched calls one right behind the other, with other noise levels and pairs each time, whose descriptors and tables go through the
