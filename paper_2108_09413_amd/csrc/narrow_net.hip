@@ -391,7 +391,8 @@ struct Block {
 #undef ISR_FIELD
 };
 
-template <int C, int S, int NI, int NW>
+// SHORT: a whole net of two convolutions, the second with stride 2, in LDS for five workgroups a CU (narrow_short).
+template <int C, int S, int NI, int NW, bool SHORT = false>
 __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
     constexpr int NT = 64 * NW;                      // threads
     constexpr int P = S + 2, CH = C / 16, C2 = 2 * C, S2 = S / 2;
@@ -402,10 +403,13 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
     // are therefore all fetched while the one before runs.
     constexpr bool AHEAD = NI == 1 && (C > 16 || NW > 4);
     static_assert((C == 16 && S == 32 && NI == 1) || (C == 32 && S == 16) || (C == 64 && S == 8), "shape");
+    static_assert(!SHORT || C == 16, "from the image");
+    constexpr int TPRM = TAIL ? (SHORT ? 1 : 3) * 4 * C2 : 4;
     __shared__ __attribute__((aligned(256))) int8_t X[NI * TB];
-    __shared__ __attribute__((aligned(256))) int8_t T[NI * TB];
+    __shared__ __attribute__((aligned(256))) int8_t T[SHORT ? tile_bytes<C2, S2>() : NI * TB];
     __shared__ __attribute__((aligned(16))) int prm[2][4 * C];                // constants of a block's two convolutions
-    __shared__ __attribute__((aligned(16))) int tprm[TAIL ? 3 * 4 * C2 : 4];  // of the tail
+    __shared__ __attribute__((aligned(16))) int tprm[TPRM];                   // of the tail
+    const int nblocks = SHORT ? 0 : p.nblocks, tail = SHORT ? 2 : p.tail;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const long img0 = (long)blockIdx.x * NI;
@@ -413,9 +417,9 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
     // ---- the stage's input ----
     // constants, the sampler's table and the first weights are all on their way before any of them is waited for
     constexpr bool WIDE = C > 16;
-    constexpr int NTP = TAIL ? (3 * 4 * C2 + NT - 1) / NT : 1;
+    constexpr int NTP = TAIL ? (TPRM + NT - 1) / NT : 1;
     static_assert(4 * C <= 256, "one constant a thread");
-    const bool from_image = C == 16 && p.stem;
+    const bool from_image = SHORT || (C == 16 && p.stem);
     int v0 = 0, v1 = 0, vt[NTP] = {};
     v4i fa0 = {0, 0, 0, 0};
     NoiseStage<NT> vn;
@@ -431,11 +435,11 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
             vn = fetch_noise_table<NT>(table, tid);
         }
     }
-    if (p.nblocks && tid < 4 * C) v0 = p.first.prm1[tid];
-    if (TAIL && p.tail)
+    if (nblocks && tid < 4 * C) v0 = p.first.prm1[tid];
+    if (TAIL && tail)
 #pragma unroll
         for (int j = 0; j < NTP; ++j)
-            if (tid + NT * j < 3 * 4 * C2) vt[j] = p.tprm[tid + NT * j];
+            if (tid + NT * j < TPRM) vt[j] = p.tprm[tid + NT * j];
     // One image of 64 channels: a wave makes 16 channels of all pixels, so that every weight enters the CU once; with 32 channels x half of
     // the pixels a wave, each weight twice, those 72 KB took most of a convolution's 2900 to 3600 cycles (prediction of the 110-layer
     // net with 100 copies 141.6 -> 131.9 us, together with the down-sampling weights fetched ahead and the first descriptor as an
@@ -456,7 +460,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
     };
     int vp = 0;   // AHEAD: constants of the convolution after the next
     Block<AHEAD> cur(p, 0, lane), nxt(p, 1, lane);
-    if (p.nblocks) {
+    if (nblocks) {
         if constexpr (SLIM) slim_weights(p.first.w1, fa);
         else if constexpr (WIDE) WideConv<C, S>(lane, wave).load_weights(p.first.w1, fa);
         else if constexpr (AHEAD) narrow_weights(p.first.w1, fa);
@@ -470,23 +474,23 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
 #pragma unroll
         for (int ks = 0; ks < KS1; ++ks) f1[ks] = *(const v4i *)(p.tw1 + (mf * 32 + (lane & 31)) * KP1 + ks * 32 + (lane >> 5) * 16);
     };
-    if (AHEAD && TAIL && p.tail && !p.nblocks) tail_weights();
+    if (AHEAD && TAIL && tail && !nblocks) tail_weights();
     auto store_constants = [&]() {
-        if (p.nblocks && tid < 4 * C) prm[0][tid] = v0;
-        if (TAIL && p.tail)
+        if (nblocks && tid < 4 * C) prm[0][tid] = v0;
+        if (TAIL && tail)
 #pragma unroll
             for (int j = 0; j < NTP; ++j)
-                if (tid + NT * j < 3 * 4 * C2) tprm[tid + NT * j] = vt[j];
+                if (tid + NT * j < TPRM) tprm[tid + NT * j] = vt[j];
     };
-    if (p.nblocks) fill_ring<C, S, NI, NT>(X, p.first.zp_x, tid);
-    else if (p.tail) fill_ring<C, S, NI, NT>(X, p.tzp_x, tid);
+    if (nblocks) fill_ring<C, S, NI, NT>(X, p.first.zp_x, tid);
+    else if (!SHORT && tail) fill_ring<C, S, NI, NT>(X, p.tzp_x, tid);
     if (from_image) {
         if constexpr (C == 16) {
             // the noisy image as NHWC4 words, one pixel of padding left, three right; behind it the sampler's table
             constexpr int PW = S + 4;
             int *img = (int *)T;
-            NoiseLds *tab = (NoiseLds *)(T + (S + 2) * PW * 4);
-            static_assert((S + 2) * PW * 4 % 16 == 0 && (S + 2) * PW * 4 + sizeof(NoiseLds) <= sizeof(T), "image and table fit");
+            NoiseLds *tab = (NoiseLds *)(SHORT ? X : T + (S + 2) * PW * 4);
+            static_assert((S + 2) * PW * 4 % 16 == 0 && (SHORT ? sizeof(NoiseLds) <= sizeof(X) : (S + 2) * PW * 4 + sizeof(NoiseLds) <= sizeof(T)), "image and table fit");
             const int zb = (int)((uint32_t)(p.zp_in & 0xFF) * 0x01010101u);
             for (int i = tid; i < 2 * PW + 4 * S; i += NT) {
                 int y, x;
@@ -524,6 +528,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
             if (tid < 64) prm[1][tid] = v1;
             store_constants();
             lds_barrier();
+            if (SHORT) fill_ring<C, S, NI, NT>(X, p.tzp_x, tid);   // the table is done with
             // one v_mfma_i32_16x16x64_i8 per 16 pixels: lane group ky reads the 16 contiguous bytes of kernel row ky (4 pixels x
             // 4 stored channels, the fourth pixel and channel meeting zero weights), the fourth group zero weights
             const int l = lane & 15, kg = lane >> 4, kr = kg < 3 ? kg : 0;
@@ -549,7 +554,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
             long g = img0 + im;
             if (g >= p.B) g = p.B - 1;                   // images past the end repeat the last one; never stored
             const int y = pix / S + 1, x = pix % S + 1;
-            const int at = p.nblocks ? tile_at<C, S>(y, x, c) : tile_at<C, S, true>(y, x, c);
+            const int at = nblocks ? tile_at<C, S>(y, x, c) : tile_at<C, S, true>(y, x, c);
             *(v4i *)(X + im * TB + at) = *(const v4i *)(p.in + (g * S * S + pix) * C + c * 16);
         }
         store_constants();
@@ -557,8 +562,8 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
 
     // ---- identity blocks ----
     int zp_t = 256;   // zero-point in the border of t; none yet
-    for (int blk = 0; blk < p.nblocks; ++blk) {
-        const bool last = blk + 1 == p.nblocks;
+    for (int blk = 0; blk < nblocks; ++blk) {
+        const bool last = blk + 1 == nblocks;
         if constexpr (!AHEAD) {   // nothing of a descriptor is kept across the convolutions
             cur = Block<AHEAD>(p, blk, lane);
             nxt = Block<AHEAD>(p, last ? blk : blk + 1, lane);
@@ -572,7 +577,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
         }
         if (zp_mid != zp_t) { fill_ring<C, S, NI, NT>(T, zp_mid, tid); zp_t = zp_mid; }
         // what the next user of x wants in its border (this block reads x's border in its first convolution only)
-        const int zp_next = last ? (p.tail ? p.tzp_x : zp_x) : nxt.zp_x();
+        const int zp_next = last ? (tail ? p.tzp_x : zp_x) : nxt.zp_x();
         auto second_constants = [&]() {   // between the convolutions
             lds_barrier();
             if (tid < 4 * C && !last) {
@@ -580,7 +585,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 if (AHEAD) vp = nxt.prm2()[tid];
             }
             if (zp_next != zp_x) fill_ring<C, S, NI, NT>(X, zp_next, tid);
-            if (AHEAD && TAIL && last && p.tail) tail_weights();
+            if (AHEAD && TAIL && last && tail) tail_weights();
         };
         with_form(cur.form(), [&](auto rq, auto rqa) {
             constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
@@ -718,7 +723,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 const Wide wc(ln, wave);
                 const LaneConsts<16, RQ> k(prm[1], C, wc.mf * 32 + wc.half * 16);
                 // a lane writes where it, or the lane with the other half of its pixel in this wave, has read
-                const int dst = last && p.tail ? wc.out_strided : wc.out;
+                const int dst = last && tail ? wc.out_strided : wc.out;
                 int q[4];
                 v4i o, rv[2];   // residuals of the two fragments of a group
                 wide_fragments<FRAGS, RQ, RQA == RQ_PAIR>(wc, fa, k, nxt.w1(), [&](int i) { return T + offset(i); },
@@ -738,7 +743,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
 
     // ---- down-sampling into the next stage ----
     if constexpr (TAIL) {
-        if (p.tail) {
+        if (tail) {
             constexpr int TB2 = tile_bytes<C2, S2>();
             static_assert(NI * TB2 <= NI * TB, "the next stage's tile fits the middle tensor's");
             typedef WideConv<C2, S2> Wide;
@@ -756,7 +761,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                     wc.load_weights(p.tw2, fa);
                     fp = *(const v4i *)(p.twp + (wc.mf * 32 + wc.l) * 64 + wc.half * 16);   // channels 0 .. 31 (zeros past C)
                 };
-                if (AHEAD && p.tail == 1) more_weights(Wide(ln, wave));
+                if (AHEAD && tail == 1) more_weights(Wide(ln, wave));
                 {
                     const Wide wc(ln, wave);
                     const int l = wc.l, half = wc.half, mf = wc.mf, c0 = mf * 32 + half * 16;
@@ -771,7 +776,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                         b1[ks] = tile_at<C, S, true>(2 * oy0 + tap / 3, 2 * ox + tap % 3, C == 16 ? 0 : half);
                     }
                     const LaneConsts<16, RQ> k(tprm, C2, c0);
-                    const bool store = p.tail == 2 && !p.head;
+                    const bool store = !SHORT && tail == 2 && !p.head;
 #pragma unroll 1
                     for (int i = 0; i < FRAGS; ++i) {
                         const int f = wave / MF + i * (NW / MF), im = f / NF;
@@ -791,7 +796,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                         else if (g < p.B) *(v4i *)(p.out + ((g * S2 * S2 + (f % NF) * 32 + l) * C2 + c0)) = o;
                     }
                 }
-                if (p.tail == 1) {
+                if (tail == 1) {
                     asm volatile("" : "+v"(ln));
                     const Wide wc(ln, wave);
                     const int l = wc.l, half = wc.half, mf = wc.mf, c0 = mf * 32 + half * 16;
@@ -829,7 +834,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                     }
                 }
             });
-            if (p.head) {   // tail == 2: the pooling reads the convolution just computed
+            if (SHORT || p.head) {   // tail == 2: the pooling reads the convolution just computed
                 lds_barrier();
                 if constexpr (C == 16) narrow_head<C2, S2, NI, NT>(p, T, X, img0, tid);
             }
@@ -850,6 +855,10 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
 
 template <int C, int S, int NI, int NW>
 __global__ __launch_bounds__(64 * NW, C == 16 && NW == 4 ? 4 : 2) void narrow_kernel(const NarrowParams p) { narrow_stage<C, S, NI, NW>(p); }
+// A whole net without blocks: bound by instruction issue (the noise, the requantisations) and, a few to a CU, by latencies, so that five
+// workgroups a CU (92 registers, 30 KB of LDS: the sampler's table lies where the first layer then writes) instead of the general
+// kernel's four (120, 39 KB) help at all sizes: us a call with 1100 / 5100 / 20 100 copies 34.0 / 76.0 / 236 -> 32.6 / 71.6 / 218.
+__global__ __launch_bounds__(256, 5) void narrow_short_kernel(const NarrowParams p) { narrow_stage<16, 32, 1, 4, true>(p); }
 
 // The three stages of a net in one launch (narrow_chain_wanted): a workgroup reads back only what it has written, so that nothing but
 // its barrier orders the stages; other images are at other stages meanwhile, so that the tensors have to lie apart (images_apart).
@@ -871,6 +880,13 @@ hipError_t launch_stage(const NarrowParams &p, hipStream_t st) {
     hipLaunchKernelGGL((narrow_kernel<C, S, NI, NW>), dim3((unsigned)((p.B + NI - 1) / NI)), dim3(64 * NW), 0, st, p);
     return hipGetLastError();
 }
+
+hipError_t launch_short(const NarrowParams &p, hipStream_t st) {
+    set_kernel_name("narrow_short_kernel");
+    hipLaunchKernelGGL(narrow_short_kernel, dim3((unsigned)p.B), dim3(256), 0, st, p);
+    return hipGetLastError();
+}
+bool narrow_short(const NarrowParams &p) { return p.stem && p.nblocks == 0 && p.tail == 2 && p.head; }
 
 }  // namespace
 
@@ -913,6 +929,8 @@ hipError_t launch_narrow(const NarrowParams &p, int channels, hipStream_t st) {
     // Waves: eight for 16 channels while every image has a CU for itself, where a convolution is a chain of latencies (first kernel of
     // ResNet-20 / -110 at 100 copies 2.1 / 11 us shorter; from two workgroups a CU on the same or longer: 300 copies + 0.2,
     // 1000 + 2).  At 32 channels four waves stay ahead at all sizes: each fetches the whole weight matrix (3 us more for 9 blocks).
+    // (A net of two convolutions with 156 / 256 copies 21.1 / 21.8 us so, 22.5 / 22.9 by its own kernel's four waves; that is ahead from there on.)
+    if (channels == 16 && !one && narrow_short(p)) return launch_short(p, st);
     if (channels == 16) return one ? launch_stage<16, 32, 1, 8>(p, st) : launch_stage<16, 32, 1, 4>(p, st);
     if (channels == 32) return one ? launch_stage<32, 16, 1, 4>(p, st) : two ? launch_stage<32, 16, 2, 4>(p, st) : launch_stage<32, 16, 3, 4>(p, st);
     if (channels == 64) return one ? launch_stage<64, 8, 1, 4>(p, st) : two ? launch_stage<64, 8, 2, 4>(p, st) : launch_stage<64, 8, 6, 4>(p, st);

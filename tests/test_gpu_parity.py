@@ -1233,6 +1233,28 @@ def test_votes_of_few_copies_reach_the_host_one_by_one(isr, net, chunk):
     m.close()
 
 
+@pytest.mark.parametrize("by_channel", [(False, False), (True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("classes", [2, 131])
+def test_two_convolutions_as_one_kernel(isr, by_channel, classes):
+    """A net of two convolutions on both sides of 256 copies, where another kernel takes it, its layers' shifts equal and by channel, with
+    zero points that are not zero: logits, argmax and votes against the oracle."""
+    _say(f"two convolutions {by_channel} {classes}")
+    b = NetBuilder(rng=np.random.default_rng(5), in_shape=(3, 32, 32), num_classes=classes)
+    kw = lambda c, own: dict(sh=8 + (np.arange(c) % 3 if own else np.zeros(c, dtype=np.int64)))
+    t = b.conv(b.tensor(3, 32, 32, 0, 74.0), 16, 3, 1, 1, False, zp_out=9, **kw(16, by_channel[0]))
+    t = b.conv(t, 32, 3, 2, 1, True, zp_out=-31, **kw(32, by_channel[1]))
+    b.fc(b.gap(t), classes)
+    blob = b.blob()
+    om = oracle.Model(blob)
+    m = _load(isr, blob, 320)
+    x = np.random.default_rng(3).integers(0, 256, size=(3, 32, 32)).astype(np.uint8)
+    for n in (257, 256, 319):
+        lg, am, cnt = isr.isr_debug_forward(m, x, 64, n, 2, 1, 0, n)
+        olg, oam, ocnt = om.mc(x, 64, n, 2, 1, 0, n)
+        assert np.array_equal(lg, olg) and np.array_equal(am, oam) and np.array_equal(cnt, ocnt), n
+    m.close()
+
+
 @pytest.mark.parametrize("net", [0, 1])
 def test_tallies_that_the_last_workgroup_sends(isr, net):
     """Calls of more than 256 votes whose last launch is of 1 to 33 workgroups and of all (16 parts count them), with and without another
