@@ -858,7 +858,7 @@ __global__ __launch_bounds__(64 * NW, C == 16 && NW == 4 ? 4 : 2) void narrow_ke
 // A whole net without blocks: bound by instruction issue (the noise, the requantisations) and, a few to a CU, by latencies, so that five
 // workgroups a CU (92 registers, 30 KB of LDS: the sampler's table lies where the first layer then writes) instead of the general
 // kernel's four (120, 39 KB) help at all sizes: us a call with 1100 / 5100 / 20 100 copies 34.0 / 76.0 / 236 -> 32.6 / 71.6 / 218.
-__global__ __launch_bounds__(256, 5) void narrow_short_kernel(const NarrowParams p) { narrow_stage<16, 32, 1, 4, true>(p); }
+__global__ __launch_bounds__(256, 5) void short_net_kernel(const NarrowParams p) { narrow_stage<16, 32, 1, 4, true>(p); }
 
 // The three stages of a net in one launch (narrow_chain_wanted): a workgroup reads back only what it has written, so that nothing but
 // its barrier orders the stages; other images are at other stages meanwhile, so that the tensors have to lie apart (images_apart).
@@ -882,8 +882,8 @@ hipError_t launch_stage(const NarrowParams &p, hipStream_t st) {
 }
 
 hipError_t launch_short(const NarrowParams &p, hipStream_t st) {
-    set_kernel_name("narrow_short_kernel");
-    hipLaunchKernelGGL(narrow_short_kernel, dim3((unsigned)p.B), dim3(256), 0, st, p);
+    set_kernel_name("short_net_kernel");
+    hipLaunchKernelGGL(short_net_kernel, dim3((unsigned)p.B), dim3(256), 0, st, p);
     return hipGetLastError();
 }
 bool narrow_short(const NarrowParams &p) { return p.stem && p.nblocks == 0 && p.tail == 2 && p.head; }
