@@ -149,8 +149,8 @@ __device__ __forceinline__ void wide_group(const WideConv<C, S> &wc, const int8_
 }
 
 // A lane's constants of N consecutive output channels from the packed form [4][C].  The pair form keeps them in registers
-// across the fragments of a convolution; the other, for the few layers that need it, reads them where they are used.
-template <int N, int RQ, bool PAIR = RQ == RQ_PAIR>
+// across the fragments of a convolution; the other reads them for each fragment, where they are used or (FETCH) ahead of its products.
+template <int N, int RQ, bool FETCH = false, bool PAIR = RQ == RQ_PAIR>
 struct LaneConsts {
     int m0[N], b4[4];
     RqLayer layer;
@@ -166,20 +166,25 @@ struct LaneConsts {
     __device__ __forceinline__ int bias(int i) const { return N == 4 ? b4[i & 3] : b[i]; }
     __device__ __forceinline__ int conv(int acc, int i, int lo) const { return rq_conv<RQ>(acc, m0[i], 0, 0, lo, layer); }
 };
-template <int N, int RQ>
-struct LaneConsts<N, RQ, false> {
+template <int N, int RQ, bool FETCH>
+struct LaneConsts<N, RQ, FETCH, false> {
     const int *at;
-    int C;
+    int C, m0[N], chi[N], sh[N];   // FETCH: of the fragment under way
     RqLayer layer = {};
     __device__ __forceinline__ LaneConsts(const int *prm, int C_, int c0) : at(prm + c0), C(C_) {}
-    __device__ __forceinline__ void fragment() const { asm volatile("" ::: "memory"); }   // no constant is carried over in a register
+    __device__ __forceinline__ void fragment() {
+        asm volatile("" ::: "memory");   // no constant is carried over in a register
+        if (FETCH)
+#pragma unroll
+            for (int i = 0; i < N; ++i) { m0[i] = at[C + i]; chi[i] = at[2 * C + i]; sh[i] = at[3 * C + i]; }
+    }
     __device__ __forceinline__ int bias(int i) const { return at[i]; }
     __device__ __forceinline__ int conv(int acc, int i, int lo) const {
-        return rq_conv<RQ>(acc, at[C + i], at[2 * C + i], at[3 * C + i], lo, layer);
+        return FETCH ? rq_conv<RQ>(acc, m0[i], chi[i], sh[i], lo, layer) : rq_conv<RQ>(acc, at[C + i], at[2 * C + i], at[3 * C + i], lo, layer);
     }
 };
-template <int N, int RQ>
-__device__ __forceinline__ auto bias_vector(const LaneConsts<N, RQ> &k) {
+template <int N, int RQ, bool FETCH>
+__device__ __forceinline__ auto bias_vector(const LaneConsts<N, RQ, FETCH> &k) {
     typedef int vec __attribute__((ext_vector_type(N)));
     vec v;
 #pragma unroll
@@ -190,8 +195,13 @@ __device__ __forceinline__ auto bias_vector(const LaneConsts<N, RQ> &k) {
 // FRAGS fragments of one convolution of a wave, weights in `fa`, which afterwards holds those at `next`: source(i) is
 // fragment i's tile address; element(i, q, e, value) consumes the accumulator of element e (in the order of e), after
 // start(i, q) and before finish(i); q: which of a group's fragments, a constant wherever it indexes registers.
-template <int FRAGS, int RQ, bool PAIRS, int C, int S, class Source, class Start, class Element, class Finish>
-__device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&fa)[WideConv<C, S>::KS], const LaneConsts<16, RQ> &k, const int8_t *next,
+// The general form (shifts that differ by channel, exact halves) takes one fragment after the other, its arithmetic covered by other
+// workgroups.  With several images a workgroup (FETCH) its operands too are read three steps ahead and its constants before the products:
+// left to the compiler, whether a product waits for the read in front of it changed with the code around it.  us of the 64-channel
+// stage of a 110-layer net with 300 / 10 000 copies 118 / 1150 -> 105 / 975, of the 32-channel one 109 / 1380 -> 106 / 1323.  The
+// one-image kernels have no registers for it.
+template <int FRAGS, bool PAIRS, int RQ, bool FETCH, int C, int S, class Source, class Start, class Element, class Finish>
+__device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&fa)[WideConv<C, S>::KS], LaneConsts<16, RQ, FETCH> &k, const int8_t *next,
                                                Source source, Start start, Element element, Finish finish) {
     if constexpr (RQ == RQ_PAIR) {
         constexpr int P = PAIRS && FRAGS >= 2 ? 2 : 1, G = FRAGS / P;
@@ -201,7 +211,7 @@ __device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&f
         auto begin = [&](int g, const int8_t *(&src)[P]) {
             k.fragment();
 #pragma unroll
-            for (int q = 0; q < P; ++q) { src[q] = source(g * P + q); acc[q] = bias_vector<16, RQ>(k); }
+            for (int q = 0; q < P; ++q) { src[q] = source(g * P + q); acc[q] = bias_vector(k); }
         };
         {
             const int8_t *src[P];
@@ -234,10 +244,13 @@ __device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&f
 #pragma unroll 1
         for (int i = 0; i < FRAGS; ++i) {
             k.fragment();
-            const v16i acc = wc.run(source(i), fa, bias_vector<16, RQ>(k));
+            v16i acc[1] = {bias_vector(k)};
+            const int8_t *const src[1] = {source(i)};
+            if constexpr (FETCH) wide_group<1, false, false>(wc, src, fa, acc, nullptr, [](int) {});
+            else acc[0] = wc.run(src[0], fa, acc[0]);
             start(i, 0);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) element(i, 0, e, acc[e]);
+            for (int e = 0; e < 16; ++e) element(i, 0, e, acc[0][e]);
             finish(i);
         }
         wc.load_weights(next, fa);
@@ -535,14 +548,14 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
             const int x = 16 * (wave & 1) + l, row0 = R * (wave >> 1);
             with_form(p.form0, [&](auto rq, auto) {
                 constexpr int RQ = decltype(rq)::value;
-                const LaneConsts<4, RQ> k(prm[1], 16, 4 * kg);
+                LaneConsts<4, RQ> k(prm[1], 16, 4 * kg);
                 const int *src = img + (row0 + kr) * PW + x;
                 int8_t *dst = X + ((row0 + 1) * P + x + 1) * 16 + 4 * kg;
 #pragma unroll 4
                 for (int r = 0; r < R; ++r) {
                     const v4i fb = {src[r * PW], src[r * PW + 1], src[r * PW + 2], src[r * PW + 3]};
                     k.fragment();
-                    const v4acc acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa0, fb, bias_vector<4, RQ>(k), 0, 0, 0);
+                    const v4acc acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa0, fb, bias_vector(k), 0, 0, 0);
                     const uint32_t q = rq_pack<RQ>(k.conv(acc[0], 0, p.lo0), k.conv(acc[1], 1, p.lo0), k.conv(acc[2], 2, p.lo0), k.conv(acc[3], 3, p.lo0), k.layer);
                     *(uint32_t *)(dst + r * P * 16) = q;
                 }
@@ -599,13 +612,13 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 auto conv = [&](const int8_t *src, const int8_t *w, const int *pr, auto make) {   // w: AHEAD the next convolution's
                     v4i fn[3];
                     narrow_weights(w, AHEAD ? fn : fa);
-                    const LaneConsts<4, RQ> k(pr, 16, 4 * kg);
+                    LaneConsts<4, RQ> k(pr, 16, 4 * kg);
                     const int8_t *col = src + (row0 * P + x + kx) * C;   // padded (row0, x + kx) = tap (0, kx) of output (row0, x)
                     auto operand = [&](int y) { return *(const v4i *)(col + (y < R + 2 ? y : R + 1) * P * C); };   // tile rows of the strip: 0 .. R + 1
                     v4i b[6];   // rows r + 1 .. r + 5 of the ring, read four rows ahead
 #pragma unroll
                     for (int y = 0; y < 6; ++y) b[y] = operand(y);
-                    v4acc acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[0], b[0], bias_vector<4, RQ>(k), 0, 0, 0);
+                    v4acc acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[0], b[0], bias_vector(k), 0, 0, 0);
                     acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[1], b[1], acc, 0, 0, 0);
                     acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[2], b[2], acc, 0, 0, 0);
                     auto row = make(k);
@@ -615,7 +628,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                         k.fragment();
                         v4acc next = acc;
                         // (no row R: the last step has no MFMAs)
-                        if (r < R - 1) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[0], b[(r + 1) % 6], bias_vector<4, RQ>(k), 0, 0, 0);
+                        if (r < R - 1) next = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[0], b[(r + 1) % 6], bias_vector(k), 0, 0, 0);
                         row(r, 0, acc[0]);
                         row(r, 1, acc[1]);
                         if (RQ == RQ_PAIR) __builtin_amdgcn_sched_barrier(0);
@@ -662,7 +675,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 // weights w; those at `next` are fetched into `wn` meanwhile; result(block, accumulators, constants)
                 auto conv = [&](const int8_t *src, const v4i (&w)[9], const int8_t *next, v4i (&wn)[9], const int *pr, auto result) {
                     slim_weights(next, wn);
-                    const LaneConsts<4, RQ> k(pr, C, 16 * wave + 4 * g);
+                    LaneConsts<4, RQ> k(pr, C, 16 * wave + 4 * g);
                     k.fragment();
                     auto operand = [&](int ks, int nb) { const int y = 2 * nb + ks / 3; return *(const v4i *)(src + base[y & 3] + (y * P + ks % 3) * C); };
                     constexpr int RING = 3;
@@ -673,7 +686,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
 #pragma unroll
                         for (int nb = 0; nb < 4; ++nb) b[ks][nb] = operand(ks, nb);
 #pragma unroll
-                    for (int nb = 0; nb < 4; ++nb) acc[nb] = bias_vector<4, RQ>(k);
+                    for (int nb = 0; nb < 4; ++nb) acc[nb] = bias_vector(k);
 #pragma unroll
                     for (int ks = 0; ks < 9; ++ks) {
                         if (ks + RING - 1 < 9)
@@ -707,10 +720,10 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 asm volatile("" : "+v"(ln));
                 {
                     const Wide wc(ln, wave);
-                    const LaneConsts<16, RQ> k(prm[0], C, wc.mf * 32 + wc.half * 16);
+                    LaneConsts<16, RQ, (NI > 1)> k(prm[0], C, wc.mf * 32 + wc.half * 16);
                     int q[4];
                     v4i o;
-                    wide_fragments<FRAGS, RQ, true>(wc, fa, k, cur.w2(), [&](int i) { return X + offset(i); }, [](int, int) {},
+                    wide_fragments<FRAGS, true>(wc, fa, k, cur.w2(), [&](int i) { return X + offset(i); }, [](int, int) {},
                         [&](int, int, int e, int a) {
                             q[e & 3] = k.conv(a, e, lo1);
                             if ((e & 3) == 3) o[e >> 2] = (int)rq_pack<RQ>(q[0], q[1], q[2], q[3], k.layer);
@@ -721,12 +734,12 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 second_constants();
                 const AddConst ac = cur.add();
                 const Wide wc(ln, wave);
-                const LaneConsts<16, RQ> k(prm[1], C, wc.mf * 32 + wc.half * 16);
+                LaneConsts<16, RQ, (NI > 1)> k(prm[1], C, wc.mf * 32 + wc.half * 16);
                 // a lane writes where it, or the lane with the other half of its pixel in this wave, has read
                 const int dst = last && tail ? wc.out_strided : wc.out;
                 int q[4];
                 v4i o, rv[2];   // residuals of the two fragments of a group
-                wide_fragments<FRAGS, RQ, RQA == RQ_PAIR>(wc, fa, k, nxt.w1(), [&](int i) { return T + offset(i); },
+                wide_fragments<FRAGS, RQA == RQ_PAIR>(wc, fa, k, nxt.w1(), [&](int i) { return T + offset(i); },
                     [&](int i, int j) { rv[j] = *(const v4i *)(X + offset(i) + wc.out); },
                     [&](int, int j, int e, int a) {
                         q[e & 3] = k.conv(a, e, lo2);
@@ -775,7 +788,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                         if (tap > 8) tap = 0;
                         b1[ks] = tile_at<C, S, true>(2 * oy0 + tap / 3, 2 * ox + tap % 3, C == 16 ? 0 : half);
                     }
-                    const LaneConsts<16, RQ> k(tprm, C2, c0);
+                    LaneConsts<16, RQ> k(tprm, C2, c0);
                     const bool store = !SHORT && tail == 2 && !p.head;
 #pragma unroll 1
                     for (int i = 0; i < FRAGS; ++i) {
@@ -783,7 +796,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                         if (NI * NF * MF < NW && f >= NI * NF) break;
                         const int8_t *src = X + im * TB + (f % NF) * FRAG1;
                         k.fragment();
-                        v16i a = bias_vector<16, RQ>(k);
+                        v16i a = bias_vector(k);
 #pragma unroll
                         for (int ks = 0; ks < KS1; ++ks)
                             a = __builtin_amdgcn_mfma_i32_32x32x32_i8(f1[ks], *(const v4i *)(src + b1[ks]), a, 0, 0, 0);
@@ -811,8 +824,8 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                         asm volatile("" ::: "memory");   // one convolution's constants at a time
                         v4i r, y;   // the projection, the sum
                         {
-                            const LaneConsts<16, RQ> k(tprm + 2 * 4 * C2, C2, c0);
-                            const v16i a = __builtin_amdgcn_mfma_i32_32x32x32_i8(fp, *(const v4i *)(X + im * TB + (f % NF) * FRAG1 + xp), bias_vector<16, RQ>(k), 0, 0, 0);
+                            LaneConsts<16, RQ> k(tprm + 2 * 4 * C2, C2, c0);
+                            const v16i a = __builtin_amdgcn_mfma_i32_32x32x32_i8(fp, *(const v4i *)(X + im * TB + (f % NF) * FRAG1 + xp), bias_vector(k), 0, 0, 0);
                             int q[16];
 #pragma unroll
                             for (int e = 0; e < 16; ++e) q[e] = k.conv(a[e], e, p.tlop);
@@ -820,8 +833,8 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                         }
                         asm volatile("" ::: "memory");
                         {
-                            const LaneConsts<16, RQ> k(tprm + 4 * C2, C2, c0);
-                            const v16i a = wc.run(T + im * TB2 + (f % NF) * wc.FRAG, fa, bias_vector<16, RQ>(k));
+                            LaneConsts<16, RQ> k(tprm + 4 * C2, C2, c0);
+                            const v16i a = wc.run(T + im * TB2 + (f % NF) * wc.FRAG, fa, bias_vector(k));
                             int u[16];
 #pragma unroll
                             for (int e = 0; e < 16; ++e) u[e] = k.conv(a[e], e, p.tlo2);

@@ -1,6 +1,8 @@
 """GPU parity: the HIP path, called through the C ABI, against the CPU oracle
 on the same seeded inputs.  Integer results (noisy copies, layer tensors,
 logits, argmax, votes) must be bit-exact; radii agree to 1e-9 relative."""
+import sys
+
 import numpy as np
 import pytest
 
@@ -713,6 +715,29 @@ def _check_forms(isr, shifts, m0, zp, relu_a, ma, mb, add_sh):
     b.fc(b.gap(t5), 5)
     x = np.random.default_rng(9).integers(0, 256, size=(3, 9, 12)).astype(np.uint8)
     _check_all_tensors(isr, b.blob(), x, 64, sample=2, chunk=3)
+
+
+class _ByChannel(NetBuilder):
+    """Networks quantised per channel: where a test gives no shifts, they differ from channel to channel."""
+
+    def conv(self, tin, cout, k, stride, pad, relu, sh=None, **kw):
+        tout = super().conv(tin, cout, k, stride, pad, relu, sh=sh, **kw)
+        if sh is None:
+            op, payload = self.ops[-1]
+            shifts = np.frombuffer(payload[-4 * cout:], dtype="<i4") + np.arange(cout, dtype="<i4") % 3
+            self.ops[-1] = (op, payload[:-4 * cout] + shifts.astype("<i4").tobytes())
+        return tout
+
+
+@pytest.fixture
+def by_channel(monkeypatch):
+    monkeypatch.setattr(sys.modules[__name__], "NetBuilder", _ByChannel)
+
+
+@pytest.mark.parametrize("copies", [3, 257, 1025])
+def test_stages_of_nets_quantised_per_channel(isr, by_channel, copies):
+    """The general form of the stage kernels in every layer, with one image a workgroup and with several."""
+    test_stages_of_the_nets_on_32x32_images(isr, "stages", copies)
 
 
 # ---- S6-S8: logits, votes, decisions -----------------------------------------

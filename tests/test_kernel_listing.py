@@ -121,3 +121,27 @@ def test_stage_kernels_keep_to_their_registers(code_objects):
                 assert (field["vgpr_spill_count"], field["private_segment_fixed_size"]) == ("0", "0"), field
                 seen += 1
     assert seen == 9
+
+
+def test_products_of_the_64_channel_stage_do_not_wait_for_the_read_in_front(kernels):
+    """With several images a workgroup the pixel operands are read steps ahead of their products, in the general form of the requantisation
+    as in the others: a product whose wait empties the queue that its own operand was put in last had none ahead."""
+    checked = 0
+    for name, code in kernels.items():
+        if not re.search(r"narrow_kernelILi64ELi8ELi[26]E", name):
+            continue
+        read = empty = False
+        late = products = 0
+        for _, text, _ in code:
+            op = text.split()[0]
+            if op.startswith("ds_read"):
+                read, empty = True, False
+            elif op == "s_waitcnt" and "lgkmcnt" in text:
+                empty = "lgkmcnt(0)" in text
+            elif op.startswith("v_mfma"):
+                products += 1
+                late += read and empty
+                read = False
+        assert products > 100 and late <= 2, (name, late)
+        checked += 1
+    assert checked == 2
