@@ -264,9 +264,11 @@ int run_slots(isr_model *m, const Plan &pl, const Draw &draw, int32_t *logits_ho
     const bool direct = heads && count <= DIRECT_VOTES && count <= per_chunk;
     // and the few tallies of more by that kernel's last workgroup.  Calls of up to 4096 copies are 0.7 to 2.5 us shorter for it (narrow_head,
     // narrow_net.hip); without the pause that a kernel of one workgroup is, 10 100 copies of ResNet-20 one call after the other ran at a
-    // lower clock, 609 us instead of 599, on one of two cards.
+    // lower clock, 609 us instead of 599, on one of two cards.  Nets of two convolutions end this way whatever the number: added to one
+    // place, their votes are what bounds the call (narrow_head).
     const uint64_t words = (uint64_t)(slots.n[1] ? 2 : 1) * slots.pairs * pm.classes;
-    const bool sends = heads && !direct && count <= SENT_COPIES && words <= SENT_TALLIES && (dcounts == m->dcounts || dcounts == m->dcounts_b);
+    const bool sends = heads && !direct && words <= SENT_TALLIES && (count <= SENT_COPIES || narrow_short(pl.ops.back().np)) &&
+                       (dcounts == m->dcounts || dcounts == m->dcounts_b);
     if (direct) {
         ++m->published;
         m->direct = slots;
@@ -350,14 +352,16 @@ int run_slots(isr_model *m, const Plan &pl, const Draw &draw, int32_t *logits_ho
                 np.votes = direct ? m->hvotes_dev : nullptr;
                 np.seq = m->published;
                 np.slots = slots_at(j0);
+                if (sends) {
+                    np.parts = m->dparts;
+                    m->parts_clean = false;
+                }
                 if (sends && done + j0 + bn == count) {   // the call's last launch
                     const bool batch = dcounts == m->dcounts_b;
                     np.seq = ++m->published;
                     np.tallies = m->sent_tallies = (uint32_t)words;
                     np.tally_host = batch ? m->hcounts_b_dev : m->hcounts_dev;
                     np.flag = m->hflag_dev;
-                    np.parts = m->dparts;
-                    m->parts_clean = false;
                 }
             }
             return np;

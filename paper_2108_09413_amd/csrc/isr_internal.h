@@ -222,9 +222,10 @@ struct NarrowBlock {         // identity residual block, stored in device memory
     AddConst add;
     int32_t pad_;
 };
-// Counters of a launch whose last workgroup sends the tallies, zero before and after: votes and finished workgroups of every sixteenth
-// workgroup, and how many of these parts are complete.  Additions to one word come through 10 ns apart, whichever workgroups make them.
-constexpr uint32_t TALLY_PARTS = 16, SENT_TALLIES = 256, SENT_COPIES = 4096;   // most tallies and copies of a call that ends this way
+// Counters of a call whose last workgroup sends the tallies, zero before and after: votes and, in the last launch, finished workgroups of
+// every sixteenth workgroup, and how many of these parts are complete.  Additions to 64 bytes come through 10 to 15 ns apart, whichever
+// workgroups make them.
+constexpr uint32_t TALLY_PARTS = 16, SENT_TALLIES = 256, SENT_COPIES = 4096;   // most tallies, and copies of a net with blocks, of such a call
 struct TallyParts {
     struct { uint32_t finished, unused[31], votes[SENT_TALLIES]; } part[TALLY_PARTS];
     uint32_t complete;
@@ -257,8 +258,8 @@ struct NarrowParams {
     uint32_t *counts;        // votes are added here, or each goes to
     uint64_t *votes;         // the host's memory, by its place in the list: class, and `seq` in the high word
     uint32_t seq;
-    // with counts, in the last launch of a call: votes go to `parts`, and the last workgroup to finish sends the `tallies` sums of these and
-    // the counters to `tally_host`, leaves zeros in their place and stores `seq` to `flag`.  0: none
+    // with counts: votes go to `parts`, where given, instead; in the last launch of such a call the last workgroup to finish sends the
+    // `tallies` sums of these and the counters to `tally_host`, leaves zeros in their place and stores `seq` to `flag`.  0: none
     uint32_t tallies;
     uint32_t *tally_host, *flag;
     TallyParts *parts;
@@ -445,6 +446,7 @@ hipError_t launch_stem16(const Stem16Params &p, hipStream_t st);
 bool stem16_supported(int k, int stride, int pad, int cout_p, int H, int W, int fast_requant);
 hipError_t launch_narrow(const NarrowParams &p, int channels, hipStream_t st);   // narrow_net.hip
 bool narrow_chain_wanted(int copies);   // all three stages in one launch
+bool narrow_short(const NarrowParams &p);   // a whole net of two convolutions, from the image to the votes
 hipError_t launch_narrow_chain(const NarrowParams &s16, const NarrowParams &s32, const NarrowParams &s64, hipStream_t st);
 bool basic_block_supported(int channels, int size);
 hipError_t launch_bottleneck(const BneckParams &p, hipStream_t st);

@@ -331,7 +331,7 @@ __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t 
     if (!p.counts) return;
     lds_barrier();
     if (wave) return;
-    auto &part = p.parts->part[blockIdx.x % TALLY_PARTS];
+    auto *const part = p.parts ? &p.parts->part[blockIdx.x % TALLY_PARTS] : nullptr;
     if (tid < NI && best_of[tid] >= 0) {
         // one global addition per distinct (row, class) of the workgroup, by its first image
         auto row = [&](int im) { return slot_use(p.slots, (uint64_t)(img0 + im)).row; };
@@ -343,17 +343,18 @@ __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t 
                 ++n;
                 first = first && im >= tid;
             }
-        if (first) atomicAdd((p.tallies ? part.votes : p.counts) + (size_t)r * p.classes + best_of[tid], n);
+        if (first) atomicAdd((part ? part->votes : p.counts) + (size_t)r * p.classes + best_of[tid], n);
     }
     // A call's tallies by the last workgroup to finish, with no launch for them behind this one (us a call, three models in turn:
     // two-convolution net with 1100 copies 35.3 -> 34.1, ResNet-20 with 400 / 1100 63.0 -> 61.5 / 103.1 -> 102.4).  Additions are complete
     // (vmcnt) before the next level counts them, and the exchanges read each counter where they were made.  One word for all workgroups
-    // held the two-convolution net's 1100 up for 11 us.
+    // held the two-convolution net's 1100 up for 11 us, and the votes of a prediction with 10 000 copies, whose counters lie in one line of
+    // 64 bytes, took 149 us there; in parts the call is 121.
     if (p.tallies) {
         const uint32_t parts = gridDim.x < TALLY_PARTS ? gridDim.x : TALLY_PARTS;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         uint32_t last = 0;
-        if (lane == 0 && __hip_atomic_fetch_add(&part.finished, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (gridDim.x - 1 - blockIdx.x % TALLY_PARTS) / TALLY_PARTS)
+        if (lane == 0 && __hip_atomic_fetch_add(&part->finished, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (gridDim.x - 1 - blockIdx.x % TALLY_PARTS) / TALLY_PARTS)
             last = __hip_atomic_fetch_add(&p.parts->complete, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
         if (!__builtin_amdgcn_readfirstlane(last)) return;
         auto take = [](uint32_t *w) { return __hip_atomic_exchange(w, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
@@ -899,9 +900,9 @@ hipError_t launch_short(const NarrowParams &p, hipStream_t st) {
     hipLaunchKernelGGL(short_net_kernel, dim3((unsigned)p.B), dim3(256), 0, st, p);
     return hipGetLastError();
 }
-bool narrow_short(const NarrowParams &p) { return p.stem && p.nblocks == 0 && p.tail == 2 && p.head; }
-
 }  // namespace
+
+bool narrow_short(const NarrowParams &p) { return p.stem && p.nblocks == 0 && p.tail == 2 && p.head; }
 
 // Shapes with a kernel: identity blocks of 16 channels at 32 x 32, 32 at 16 x 16, 64 at 8 x 8 (the three stages of
 // the CIFAR-style residual nets), down-sampling blocks 16 -> 32 at 32 x 32 -> 16 x 16 and 32 -> 64 at 16 x 16 -> 8 x 8.
@@ -924,7 +925,8 @@ static bool narrow_valid(const NarrowParams &p, int channels) {
                    p.classes_p < p.classes || (channels == 64 && p.nblocks == 0)))
         return false;
     if (p.head && p.counts && !valid_slots(p.slots)) return false;
-    if (p.tallies && (!p.head || !p.counts || p.tallies > SENT_TALLIES || !p.tally_host || !p.flag || !p.parts)) return false;
+    if (p.parts && (!p.head || !p.counts || (uint64_t)(p.slots.n[1] ? 2 : 1) * p.slots.pairs * (uint64_t)p.classes > SENT_TALLIES)) return false;
+    if (p.tallies && (!p.parts || p.tallies > SENT_TALLIES || !p.tally_host || !p.flag)) return false;
     if (p.votes && (!p.head || p.counts || p.slots.begin + (uint64_t)p.B > DIRECT_VOTES)) return false;
     return true;
 }

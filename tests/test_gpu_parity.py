@@ -1304,6 +1304,25 @@ def test_tallies_that_the_last_workgroup_sends(isr, net):
     m.close()
 
 
+@pytest.mark.parametrize("chunk", [8, 1024])
+def test_tallies_of_many_copies_of_a_two_convolution_net(isr, chunk):
+    """Calls of more than 4096 copies, in one launch and in several, whose votes are counted in parts until the last workgroup sends them;
+    batched ones of up to 256 tallies and of more in between: the counters are zero again after each.  Against the oracle."""
+    _say(f"tallies of many copies, chunk {chunk}")
+    blob = synth.build_model(0)
+    om = oracle.Model(blob)
+    x = synth.make_image(0, 1)
+    m = _load(isr, blob, chunk)
+    for k, n in enumerate([4097, 4096, 6001]):
+        res, counts = isr.isr_predict(m, x, 64, n, ALPHA, seed=k, image_id=k)
+        assert np.array_equal(counts, om.mc(x, 64, k, k, 0, 0, n)[2]), n
+        res, c0, c1 = isr.isr_certify(m, x, 32, 300 + k, n, ALPHA, seed=k, image_id=3)
+        assert np.array_equal(c0, om.mc(x, 32, k, 3, 0, 0, 300 + k)[2]) and np.array_equal(c1, om.mc(x, 32, k, 3, 1, 0, n)[2]), n
+        pairs = (12, 13, 1)[k]
+        _check_batch_against_oracle(isr, m, om, x[None], [(0, 32 + i % 5, 7 + i) for i in range(pairs)], 7, 4200 // pairs, seed=pairs)
+    m.close()
+
+
 @pytest.mark.parametrize("pairs,chunk,fusion", [(256, 4096, 1), (257, 4096, 1), (1, 8, 0), (2, 8, 0)])
 def test_calls_in_a_row_whichever_way_they_end(isr, pairs, chunk, fusion):
     """Batched calls one right behind the other, with other noise levels and pairs each time, whose descriptors and tables go through the
