@@ -10,6 +10,7 @@
 #include <new>
 #include <string>
 
+#include "host_watch.h"
 #include "isr_internal.h"
 #include "model.h"
 #include "plan.h"
@@ -621,42 +622,34 @@ constexpr uint32_t WATCHED_LAUNCHES = 5;
 // its memory and no launch stands behind the last one (prediction of ResNet-20 with 100 copies 42.2 -> 39.7 us).  More are tallied
 // there: stores of single words to the host are 20 ns apart.  Up to 256 tallies of up to 4096 copies of such a net are sent by the last
 // workgroup of its last kernel, with no launch of their own either.
-//
-// Waits until *word's high part says `seq` (of the flag: the word itself), or for the stream's end after 2 ms.
-template <class Word>
-static int watch(isr_model *m, const Word *word, uint32_t seq, std::chrono::steady_clock::time_point patience) {
-    for (uint32_t spins = 1; (uint32_t)(__atomic_load_n(word, __ATOMIC_ACQUIRE) >> (8 * (sizeof(Word) - 4))) != seq; ++spins) {
-        if (spins % 64 == 0 && std::chrono::steady_clock::now() > patience) {
-            HIP_TRY(hipStreamSynchronize(m->stream));
-            break;
-        }
-        __builtin_ia32_pause();
-    }
-    return ISR_OK;
-}
 static int publish(isr_model *m, uint32_t *counts, uint32_t *host, uint32_t *host_dev, size_t n) {
     const auto patience = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+    auto stream_end = [m]() -> int {
+        HIP_TRY(hipStreamSynchronize(m->stream));
+        return ISR_OK;
+    };
     int rc;
     if (m->direct_votes) {
         HIP_TRY(hipEventRecord(m->end, m->stream));
         std::fill(host, host + n, 0u);
         for (uint32_t i = 0; i < m->direct_votes; ++i) {
-            if ((rc = watch(m, &m->hvotes[i], m->published, patience)) != ISR_OK) return rc;
+            if ((rc = watch(&m->hvotes[i], m->published, patience, stream_end)) != ISR_OK) return rc;
             host[(size_t)slot_use(m->direct, i).row * m->pm.classes + (uint32_t)m->hvotes[i]] += 1;
         }
     } else if (m->sent_tallies) {
         if (m->sent_tallies != n) return ISR_ERR_ARG;   // cannot happen: the counters of all phases and pairs
         if (m->launches <= WATCHED_LAUNCHES + 1) {
             HIP_TRY(hipEventRecord(m->end, m->stream));
-            if ((rc = watch(m, m->hflag, m->published, patience)) != ISR_OK) return rc;
+            if ((rc = watch(m->hflag, m->published, patience, stream_end)) != ISR_OK) return rc;
         } else {
             HIP_TRY(hipStreamSynchronize(m->stream));
+            if (!arrived(m->hflag, m->published)) return ISR_ERR_DEVICE;
         }
         m->parts_clean = true;
     } else if (n <= PUBLISH_WATCHED && m->launches <= WATCHED_LAUNCHES) {
         HIP_TRY(launch_publish(counts, host_dev, n, m->hflag_dev, ++m->published, m->stream));
         HIP_TRY(hipEventRecord(m->end, m->stream));
-        if ((rc = watch(m, m->hflag, m->published, patience)) != ISR_OK) return rc;
+        if ((rc = watch(m->hflag, m->published, patience, stream_end)) != ISR_OK) return rc;
     } else {
         HIP_TRY(launch_publish(counts, host_dev, n, nullptr, 0, m->stream));
         HIP_TRY(hipStreamSynchronize(m->stream));
