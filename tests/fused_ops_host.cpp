@@ -26,10 +26,13 @@ int main(int argc, char **argv) {
     std::vector<DevOp> fused;
     build_fused_plan(pm, ops, fused, false);
     for (const DevOp &d : fused) {
-        int rq = d.conv.rq;
-        if (d.bneck) rq &= d.conv2.rq & (d.bneck >= 2 ? d.conv3.rq : ~0);
+        const ConvParams &c = d.conv;
+        int rq = c.rq & (c.fuse_add == 2 ? c.rq2 : ~0);
+        if (d.bneck) rq &= d.conv2.rq & (d.bneck >= 2 ? d.conv3.rq : ~0) & (d.bneck == 4 ? d.conv3.rq2 : ~0);
         if (d.reduce) rq &= d.conv4.rq;
-        std::printf("type %d bneck %d reduce %d form %d\n", (int)d.type, d.bneck, d.reduce, d.type == OP_CONV ? rq_form(rq) : -1);
+        if (d.xr) rq &= d.conv2.rq;
+        std::printf("type %d stem %d bneck %d reduce %d xr %d k %d stride %d cin %d cout %d next %d form %d\n", (int)d.type, d.stem_pool, d.bneck, d.reduce, d.xr, c.k, c.stride,
+                    c.Cin_p, c.Cout_p, d.xr ? d.conv2.Cout_p : 0, d.type == OP_CONV ? rq_form(rq) : -1);
     }
     return 0;
 }

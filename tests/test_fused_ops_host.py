@@ -31,8 +31,7 @@ def fused_ops(tmp_path_factory):
         (where / "net.isrm").write_bytes(blob)
         out = subprocess.run([exe, str(where / "net.isrm")], capture_output=True, text=True, timeout=120)
         assert out.returncode == 0, out.stdout + out.stderr
-        return [dict(zip(("type", "bneck", "reduce", "form"), map(int, r)))
-                for r in re.findall(r"type (-?\d+) bneck (\d+) reduce (\d+) form (-?\d+)", out.stdout)]
+        return [{k: int(v) for k, v in re.findall(r"(\w+) (-?\d+)", line)} for line in out.stdout.splitlines()]
     return ops
 
 
@@ -62,3 +61,51 @@ def test_block_and_the_next_stages_first_convolution(fused_ops, block, after, fu
     b.fc(b.conv(t, 16, 1, 1, 0, True), 9)
     blocks = [o for o in fused_ops(b.blob()) if o["bneck"] == 2]
     assert [(bool(o["reduce"]), o["form"]) for o in blocks] == [(fused, form)]
+
+
+class _Blob(Exception):
+    pass
+
+
+class _Recorder:
+    """Stands for the library in a test that builds a net and loads it."""
+
+    def isr_load_model(self, blob):
+        raise _Blob(blob)
+
+
+def _kernel(o):
+    if o["stem"]:
+        return "first layer with pooling"
+    if o["bneck"]:
+        return {1: "bottleneck head", 2: "bottleneck block", 4: "bottleneck block with projection"}[o["bneck"]] + (" and next" if o["reduce"] else "")
+    if o["xr"]:
+        return f"expand {o['cout']} reduce {o['next']}"
+    if (o["k"], o["stride"]) == (3, 1) and o["cout"] in (128, 256, 512):
+        return f"staged rows {128 if o['cout'] == 128 else 256}"
+    return "other"
+
+
+# what the GPU tests of these names run in the top-byte form, and the first layer's in pairs
+@pytest.mark.parametrize("test,args,form,kernels", [
+    ("test_first_layer_with_pooling_in_the_short_forms", ((37, 28), "pairs"), PAIR, {"first layer with pooling"}),
+    ("test_first_layer_with_pooling_in_the_short_forms", ((37, 28), "top byte"), TOP, {"first layer with pooling"}),
+    ("test_top_form_in_bottleneck_heads", (256,), TOP, {"bottleneck head"}),
+    ("test_top_form_in_bottleneck_blocks", ((30, 20),), TOP, {"bottleneck block", "bottleneck block with projection"}),
+    ("test_top_form_in_a_block_with_the_next_stages_first_convolution", ((32, 56), 2, 2, "_TopForm"), TOP, {"bottleneck block and next"}),
+    ("test_top_form_in_a_block_with_the_next_stages_first_convolution", ((32, 56), 2, 2, "_NextByChannel"), TOP, {"bottleneck block and next"}),
+    ("test_top_form_in_staged_rows_of_256_channels", (9,), TOP, {"staged rows 256"}),
+    ("test_top_form_in_staged_rows_against_the_oracle", ((10, 4), 2, 1), TOP, {"staged rows 128", "staged rows 256"}),
+    ("test_top_form_in_expand_add_and_next_reduce", (), TOP, {"expand 512 reduce 128", "expand 512 reduce 256", "expand 1024 reduce 256"}),
+])
+def test_forms_that_the_gpu_tests_run(fused_ops, monkeypatch, test, args, form, kernels):
+    """Where the planner prefers another form, a test of one that is still in use would silently run the other."""
+    import test_gpu_parity as gpu
+
+    def builder(cls):
+        monkeypatch.setattr(gpu, "NetBuilder", cls)
+    args = [getattr(gpu, a) if isinstance(a, str) and hasattr(gpu, a) else a for a in args]
+    f = getattr(gpu, test)
+    with pytest.raises(_Blob) as net:
+        f(_Recorder(), *([builder] if "builder" in f.__code__.co_varnames[:2] else []), *args)
+    assert kernels <= {_kernel(o) for o in fused_ops(net.value.args[0]) if o["form"] == form}

@@ -720,24 +720,102 @@ def _check_forms(isr, shifts, m0, zp, relu_a, ma, mb, add_sh):
 class _ByChannel(NetBuilder):
     """Networks quantised per channel: where a test gives no shifts, they differ from channel to channel."""
 
+    def chosen(self, cout, k):
+        return True
+
     def conv(self, tin, cout, k, stride, pad, relu, sh=None, **kw):
         tout = super().conv(tin, cout, k, stride, pad, relu, sh=sh, **kw)
-        if sh is None:
+        if sh is None and self.chosen(cout, k):
             op, payload = self.ops[-1]
             shifts = np.frombuffer(payload[-4 * cout:], dtype="<i4") + np.arange(cout, dtype="<i4") % 3
             self.ops[-1] = (op, payload[:-4 * cout] + shifts.astype("<i4").tobytes())
         return tout
 
 
+class _TopForm(_ByChannel):
+    """The same with lower clamps of -128 throughout: without exact halves every layer takes the top-byte form."""
+
+    def conv(self, tin, cout, k, stride, pad, relu, zp_out=None, **kw):
+        return super().conv(tin, cout, k, stride, pad, relu, zp_out=-128 if relu else zp_out, **kw)
+
+
+class _NextByChannel(_ByChannel):
+    """One shift in every layer but the 1x1 convolutions into 128 channels."""
+
+    def chosen(self, cout, k):
+        return cout == 128 and k == 1
+
+
 @pytest.fixture
-def by_channel(monkeypatch):
-    monkeypatch.setattr(sys.modules[__name__], "NetBuilder", _ByChannel)
+def builder(monkeypatch):
+    return lambda cls: monkeypatch.setattr(sys.modules[__name__], "NetBuilder", cls)
 
 
 @pytest.mark.parametrize("copies", [3, 257, 1025])
-def test_stages_of_nets_quantised_per_channel(isr, by_channel, copies):
+def test_stages_of_nets_quantised_per_channel(isr, builder, copies):
     """The general form of the stage kernels in every layer, with one image a workgroup and with several."""
+    builder(_ByChannel)
     test_stages_of_the_nets_on_32x32_images(isr, "stages", copies)
+
+
+# Layers whose channels share one shift take results in pairs; the top-byte form, which networks quantised per channel take, in each
+# kernel that has it:
+
+@pytest.mark.parametrize("form", ["pairs", "top byte"])
+@pytest.mark.parametrize("shape", [(224, 224), (37, 28), (9, 8), (150, 100), (35, 224)])
+def test_first_layer_with_pooling_in_the_short_forms(isr, shape, form):
+    """Ragged strips and bands, with a lower clamp of -128."""
+    h, w = shape
+    _say(f"first layer with pooling {h}x{w}, {form}")
+    b = (NetBuilder if form == "pairs" else _TopForm)(rng=np.random.default_rng(31), in_shape=(3, h, w), num_classes=5)
+    t = b.maxpool(b.conv(b.tensor(3, h, w, 0, 74.0), 61, 7, 2, 3, True), 3, 2, 1)
+    b.fc(b.gap(b.conv(t, 64, 1, 1, 0, True)), 5)
+    x = np.random.default_rng(7).integers(0, 256, size=(3, h, w)).astype(np.uint8)
+    _check_all_tensors(isr, b.blob(), x, 64, sample=3, chunk=5)
+
+
+@pytest.mark.parametrize("cin", [256, 320])
+def test_top_form_in_bottleneck_heads(isr, builder, cin):
+    builder(_TopForm)
+    test_bottleneck_heads_of_three_to_eight_k_steps(isr, cin)
+
+
+@pytest.mark.parametrize("shape", [(30, 20), (5, 40)])
+def test_top_form_in_bottleneck_blocks(isr, builder, shape):
+    builder(_TopForm)
+    test_bottleneck_blocks_in_one_kernel(isr, shape)
+
+
+@pytest.mark.parametrize("layers", [_TopForm, _NextByChannel])
+@pytest.mark.parametrize("shape,first,stride", [((32, 56), 2, 2), ((20, 60), 2, 1), ((36, 124), 4, 2)])
+def test_top_form_in_a_block_with_the_next_stages_first_convolution(isr, builder, shape, first, stride, layers):
+    """Also where only that convolution's shifts differ, for which the block leaves its pairs."""
+    builder(layers)
+    test_identity_block_with_the_next_stages_first_convolution(isr, shape, first, stride)
+
+
+@pytest.mark.parametrize("copies", [9, 84, 168])
+def test_top_form_in_staged_rows_of_256_channels(isr, builder, copies):
+    """Against the implicit-GEMM tile, in launches of few, more and many tiles."""
+    builder(_TopForm)
+    test_staged_rows_in_launches_of_few_and_many_tiles(isr, copies)
+
+
+@pytest.mark.parametrize("in_shape,stride,copies", [((28, 28), 4, 150), ((28, 28), 1, 11), ((36, 124), 4, 13)])
+def test_top_form_in_staged_rows_against_the_oracle(isr, builder, in_shape, stride, copies):
+    builder(_TopForm)
+    test_3x3_layers_with_staged_pixel_rows_against_the_oracle(isr, in_shape, stride, copies)
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5, 6])
+def test_top_form_in_every_conv_tile(isr, builder, tile):
+    builder(_TopForm)
+    test_every_conv_tile_against_the_oracle(isr, tile)
+
+
+def test_top_form_in_expand_add_and_next_reduce(isr, builder):
+    builder(_TopForm)
+    test_expand_add_and_next_reduce_in_one_kernel(isr)
 
 
 # ---- S6-S8: logits, votes, decisions -----------------------------------------
@@ -1258,25 +1336,28 @@ def test_votes_of_few_copies_reach_the_host_one_by_one(isr, net, chunk):
     m.close()
 
 
+@pytest.mark.parametrize("relu", [True, False])   # the second layer's lower clamp: -31, which has no pairs of results, and -128
 @pytest.mark.parametrize("by_channel", [(False, False), (True, False), (False, True), (True, True)])
 @pytest.mark.parametrize("classes", [2, 131])
-def test_two_convolutions_as_one_kernel(isr, by_channel, classes):
+def test_two_convolutions_as_one_kernel(isr, by_channel, classes, relu):
     """A net of two convolutions on both sides of 256 copies, where another kernel takes it, its layers' shifts equal and by channel, with
-    zero points that are not zero: logits, argmax and votes against the oracle."""
-    _say(f"two convolutions {by_channel} {classes}")
+    zero points that are not zero: logits, argmax and votes against the oracle, and which kernel it was."""
+    _say(f"two convolutions {by_channel} {classes} {relu}")
     b = NetBuilder(rng=np.random.default_rng(5), in_shape=(3, 32, 32), num_classes=classes)
     kw = lambda c, own: dict(sh=8 + (np.arange(c) % 3 if own else np.zeros(c, dtype=np.int64)))
     t = b.conv(b.tensor(3, 32, 32, 0, 74.0), 16, 3, 1, 1, False, zp_out=9, **kw(16, by_channel[0]))
-    t = b.conv(t, 32, 3, 2, 1, True, zp_out=-31, **kw(32, by_channel[1]))
+    t = b.conv(t, 32, 3, 2, 1, relu, zp_out=-31, **kw(32, by_channel[1]))
     b.fc(b.gap(t), classes)
     blob = b.blob()
     om = oracle.Model(blob)
     m = _load(isr, blob, 320)
     x = np.random.default_rng(3).integers(0, 256, size=(3, 32, 32)).astype(np.uint8)
     for n in (257, 256, 319):
+        isr.isr_profile(m, 1)
         lg, am, cnt = isr.isr_debug_forward(m, x, 64, n, 2, 1, 0, n)
         olg, oam, ocnt = om.mc(x, 64, n, 2, 1, 0, n)
         assert np.array_equal(lg, olg) and np.array_equal(am, oam) and np.array_equal(cnt, ocnt), n
+        assert [k["name"] for k in isr.isr_profile_read(m)] == ["short_net_kernel" if n > 256 else "narrow_kernel<16, 32, 1, 8 waves>"], n
     m.close()
 
 

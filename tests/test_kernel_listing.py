@@ -111,16 +111,16 @@ def test_fexpand_stores_are_what_its_waits_count(kernels):
 
 
 def test_stage_kernels_keep_to_their_registers(code_objects):
-    """The kernels of the nets on 32 x 32 images, whose rates rest on two workgroups a CU with everything in registers."""
+    """The kernels of the nets on 32 x 32 images, whose rates rest on two to five workgroups a CU with everything in registers."""
     seen = 0
     for f in code_objects:
         notes = subprocess.check_output([os.path.join(LLVM, "llvm-readelf"), "--notes", f], text=True)
         for kernel in notes.split("  - .agpr_count:")[1:]:
             field = {k: re.search(rf"\.{k}:\s+(\S+)", kernel).group(1) for k in ("name", "vgpr_spill_count", "private_segment_fixed_size")}
-            if "narrow_" in field["name"]:
+            if "narrow_" in field["name"] or "short_net" in field["name"]:
                 assert (field["vgpr_spill_count"], field["private_segment_fixed_size"]) == ("0", "0"), field
                 seen += 1
-    assert seen == 9
+    assert seen == 10
 
 
 def test_products_of_the_64_channel_stage_do_not_wait_for_the_read_in_front(kernels):
