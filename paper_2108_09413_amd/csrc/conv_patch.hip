@@ -35,12 +35,12 @@ __global__ __launch_bounds__(patch_threads(BM, LOADS), MINB) void conv_patch_ker
     constexpr bool DUTY = LOADS == DUTY_GROUP, EVERY = LOADS == EACH;
     constexpr int WGM = BM / 64, NW = WGM * (PBN / 64), NT = patch_threads(BM, LOADS);   // NW: waves that multiply
     constexpr int CPR = KB / 16;                 // 16-byte chunks per row
-    constexpr int RPP = EVERY ? NT / CPR : 128;  // rows covered by one pass of all threads
-    constexpr int NA = EVERY ? BM / RPP : 1;     // weight loads per lane per step
+    constexpr int RPP = 128;                     // rows of a pass
+    constexpr int NA = EVERY ? BM / RPP : 1;     // EACH: weight loads per lane per step
     constexpr int KS = KB / 32;
     constexpr int ABUF = BM * KB, ZOFF = PROWS * KB, BBUF = ZOFF + PZBYTES;
-    constexpr int BPP = (PROWS + RPP - 1) / RPP; // pixel rows of a lane
-    static_assert((!EVERY || (RPP <= 128 && RPP % 32 == 0 && BM % RPP == 0)) && (KB == 64 || KB == 128) && ZOFF % 256 == 0, "tile shape");
+    constexpr int PASSES = (PROWS + RPP - 1) / RPP;   // over a slice's pixel rows
+    static_assert((!EVERY || (NT / CPR == RPP && BM % RPP == 0)) && PROWS == 2 * RPP + RPP / 2 && (KB == 64 || KB == 128) && ZOFF % 256 == 0, "tile shape");
 
     __shared__ __attribute__((aligned(256))) int8_t Bs[2][BBUF];
     __shared__ __attribute__((aligned(16))) int8_t As[NAB][ABUF];
@@ -100,11 +100,11 @@ __global__ __launch_bounds__(patch_threads(BM, LOADS), MINB) void conv_patch_ker
         }
     };
 
-    // every wave its share: lane (row0, col) of a pass of all threads fetches chunk col ^ swz(row0) of row row0 + 128 j
+    // EACH: lane (row0, col) of a pass of all threads fetches chunk col ^ swz(row0) of row row0 + 128 j
     const int col = tid % CPR, row0 = tid / CPR;
     const int cl = col ^ swz<CPR>(row0);
     const int8_t *wrow[NA];
-    uint32_t prow[EVERY ? BPP : 1];
+    uint32_t prow[EVERY ? PASSES : 1];
     if constexpr (EVERY) {
 #pragma unroll
         for (int j = 0; j < NA; ++j) {
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(patch_threads(BM, LOADS), MINB) void conv_patch_ker
         }
         // staged row rho holds pixel n0 - halo + rho; pixels outside the tensor are clamped (only taps outside the image would read them)
 #pragma unroll
-        for (int j = 0; j < BPP; ++j) {
+        for (int j = 0; j < PASSES; ++j) {
             int g = n0 - halo + row0 + RPP * j;
             g = g < 0 ? 0 : (g >= p.npix ? p.npix - 1 : g);
             prow[j] = (uint32_t)g * (uint32_t)p.Cin_p + cl * 16;
@@ -132,14 +132,8 @@ __global__ __launch_bounds__(patch_threads(BM, LOADS), MINB) void conv_patch_ker
     // pass j (128 rows; the third pass covers rows 256..319 with the first half of the waves) of a slice's pixel rows
     auto issue_b = [&](int slice, int j, int buf) {
         if constexpr (!EVERY) issue_b_duty(slice, j, buf);
-        else {
-#pragma unroll
-            for (int h = 0; h < 128 / RPP; ++h) {
-                const int r = j * (128 / RPP) + h;
-                if (r < BPP && (r + 1 < BPP || PROWS % RPP == 0 || wave < NW / 2))
-                    ISR_GLOBAL_TO_LDS16_AT(p.in + (prow[r < BPP ? r : 0] + (uint32_t)(slice * KB)), b_lds0 + wave * 1024 + buf * BBUF + r * (NT * 16));
-            }
-        }
+        else if (j + 1 < PASSES || wave < NW / 2)
+            ISR_GLOBAL_TO_LDS16_AT(p.in + (prow[j] + (uint32_t)(slice * KB)), b_lds0 + wave * 1024 + buf * BBUF + j * (NT * 16));
     };
 
     if constexpr (DUTY) {
