@@ -263,10 +263,10 @@ int run_slots(isr_model *m, const Plan &pl, const Draw &draw, int32_t *logits_ho
     // votes of few copies in one chunk go to the host one by one where the last op is a stage kernel
     const bool heads = dcounts && stop_tensor < 0 && !pl.ops.empty() && pl.ops.back().narrow && pl.ops.back().head;
     const bool direct = heads && count <= DIRECT_VOTES && count <= per_chunk;
-    // and the few tallies of more by that kernel's last workgroup.  Calls of up to 4096 copies are 0.7 to 2.5 us shorter for it (narrow_head,
-    // narrow_net.hip); without the pause that a kernel of one workgroup is, 10 100 copies of ResNet-20 one call after the other ran at a
-    // lower clock, 609 us instead of 599, on one of two cards.  Nets of two convolutions end this way whatever the number: added to one
-    // place, their votes are what bounds the call (narrow_head).
+    // and the few tallies of more by that kernel's last workgroup.  Calls of ResNet-20 are 0.8 us shorter for it (narrow_head,
+    // narrow_net.hip); above 4096 copies, without the pause that a kernel of one workgroup is, 10 100 copies one call after the other ran
+    // at a lower clock, 609 us instead of 599, on one of two cards.  Nets of two convolutions end this way whatever the number: added to
+    // one place, their votes are what bounds the call (narrow_head).
     const uint64_t words = (uint64_t)(slots.n[1] ? 2 : 1) * slots.pairs * pm.classes;
     const bool sends = heads && !direct && words <= SENT_TALLIES && (count <= SENT_COPIES || narrow_short(pl.ops.back().np)) &&
                        (dcounts == m->dcounts || dcounts == m->dcounts_b);
@@ -620,8 +620,8 @@ int isr::open_counts(isr_model *m) {
 constexpr uint32_t WATCHED_LAUNCHES = 5;
 // Up to 256 votes (a launch whose workgroups all run at once) are not even tallied on the device: the host watches for each of them in
 // its memory and no launch stands behind the last one (prediction of ResNet-20 with 100 copies 42.2 -> 39.7 us).  More are tallied
-// there: stores of single words to the host are 20 ns apart.  Up to 256 tallies of up to 4096 copies of such a net are sent by the last
-// workgroup of its last kernel, with no launch of their own either.
+// there: stores of single words to the host are 20 ns apart.  Up to 256 tallies of up to 4096 copies of such a net (of two convolutions: of
+// any number) are sent by the last workgroup of its last kernel, with no launch of their own either.
 static int publish(isr_model *m, uint32_t *counts, uint32_t *host, uint32_t *host_dev, size_t n) {
     const auto patience = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
     auto stream_end = [m]() -> int {

@@ -96,9 +96,9 @@ __device__ __forceinline__ uint32_t pack4(int a, int b, int c, int d) {
 //   RQ_TOP_TIES  the same with ties (a 64-bit multiply-add instead of the multiply)
 //   RQ_PAIR      tie-free, lower clamp -128, ONE shift for all channels of the layer (networks quantised per tensor have one; the
 //                multipliers may differ).  w = high word of acc * M0 + chi 2^32 is one v_mad_i64_i32, and v_ashr_pk_i8_i32
-//                shifts, saturates and packs two of them: 8.4 issue cycles an output against 11.7 of RQ_TOP, 26 against 32 with an
-//                add (measured rates: v_mad_i64_i32 4.24, v_ashr_pk_i8_i32 8.25, v_mul_hi 4.55, v_mad_i32_i24 4.47, v_perm 4.16).
-//                No bound on the range of w, which int32 holds.  Certification of ResNet-50, n = 10 000: 65.4 -> 63.7 ms, of the
+//                shifts, saturates and packs two of them: 9.0 issue cycles an output against 12.3 of RQ_TOP, 27 against 31 with an
+//                add (measured, a wave instruction: v_mad_i64_i32, v_mul_hi, v_mad_i32_i24, 24-bit multiplies, v_add3, v_perm 4.65,
+//                v_ashr_pk_i8_i32 8.6, v_or 2.55).  No bound on the range of w, which int32 holds.  Certification of ResNet-50, n = 10 000: 65.4 -> 63.7 ms, of the
 //                110-layer net, n = 100 000: 26.71 -> 25.68 ms, ResNet-20 5.24 -> 5.12.
 // An add is RQ_ANY, RQ_TIE_FREE, RQ_TOP, RQ_TOP_WIDE (two signed operands, whose sum may leave int32 and saturates) or RQ_PAIR.
 // The forms of several convolutions combine with & (Rq).

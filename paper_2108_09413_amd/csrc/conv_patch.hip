@@ -12,9 +12,10 @@
 // slice.  The weights stream as before, one [BM channels][KB bytes] block per (slice, tap); integer
 // accumulation makes the changed K order (slice-major, tap-minor) exact.
 //
-// LDS: two weight buffers, two activation buffers of 320 rows + 256 bytes of zero points, the per-channel
-// constants.  <256 channels, 128-byte slices>: 148 KB, sixteen waves of 64 x 64, one workgroup per CU;
-// <128, 64>: 58 KB, eight waves, two workgroups per CU.  Chunk swizzle and epilogue as in conv_dma.h.
+// LDS: two or four weight buffers, two activation buffers of 320 rows + 256 bytes of zero points, the per-channel
+// constants.  <256 channels, 128-byte slices>: 149 KB, sixteen waves of 64 x 64, one workgroup per CU;
+// <128, 64>: 75 KB, eight waves, two workgroups per CU; launches of few tiles <128, 128> and <64, 128>: 147 and 114 KB, eight
+// and four waves and four that issue loads.  Chunk swizzle and epilogue as in conv_dma.h.
 #include "conv_device.h"
 
 namespace isr {

@@ -331,7 +331,7 @@ __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t 
     if (!p.counts) return;
     lds_barrier();
     if (wave) return;
-    auto *const part = p.parts ? &p.parts->part[blockIdx.x % TALLY_PARTS] : nullptr;
+    auto &part = p.parts->part[blockIdx.x % TALLY_PARTS];   // where there are parts
     if (tid < NI && best_of[tid] >= 0) {
         // one global addition per distinct (row, class) of the workgroup, by its first image
         auto row = [&](int im) { return slot_use(p.slots, (uint64_t)(img0 + im)).row; };
@@ -343,18 +343,19 @@ __device__ __forceinline__ void narrow_head(const NarrowParams &p, const int8_t 
                 ++n;
                 first = first && im >= tid;
             }
-        if (first) atomicAdd((part ? part->votes : p.counts) + (size_t)r * p.classes + best_of[tid], n);
+        if (first) atomicAdd((p.parts ? part.votes : p.counts) + (size_t)r * p.classes + best_of[tid], n);
     }
-    // A call's tallies by the last workgroup to finish, with no launch for them behind this one (us a call, three models in turn:
-    // two-convolution net with 1100 copies 35.3 -> 34.1, ResNet-20 with 400 / 1100 63.0 -> 61.5 / 103.1 -> 102.4).  Additions are complete
-    // (vmcnt) before the next level counts them, and the exchanges read each counter where they were made.  One word for all workgroups
-    // held the two-convolution net's 1100 up for 11 us, and the votes of a prediction with 10 000 copies, whose counters lie in one line of
-    // 64 bytes, took 149 us there; in parts the call is 121.
+    // A call's tallies by the last workgroup to finish, with no launch for them behind this one (us a call, in turn: ResNet-20 with
+    // 400 / 1100 copies 61.2 -> 60.3 / 104.5 -> 103.7).  Additions are complete (vmcnt) before the next level counts them, and the
+    // exchanges read each counter where they were made.  One word for the finished workgroups of the two-convolution net held 1100 of them
+    // up for 11 us, and its votes, one a workgroup, are what bounds a call while they are added to one line of 64 bytes, as those of a
+    // prediction are: with 600 / 2000 / 10 000 copies 27.2 -> 25.0 / 45.5 -> 37.1 / 149 -> 121 in parts (certifications of up to 4096, whose
+    // counters lie in two lines, are within 0.8 us either way).
     if (p.tallies) {
         const uint32_t parts = gridDim.x < TALLY_PARTS ? gridDim.x : TALLY_PARTS;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         uint32_t last = 0;
-        if (lane == 0 && __hip_atomic_fetch_add(&part->finished, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (gridDim.x - 1 - blockIdx.x % TALLY_PARTS) / TALLY_PARTS)
+        if (lane == 0 && __hip_atomic_fetch_add(&part.finished, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (gridDim.x - 1 - blockIdx.x % TALLY_PARTS) / TALLY_PARTS)
             last = __hip_atomic_fetch_add(&p.parts->complete, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
         if (!__builtin_amdgcn_readfirstlane(last)) return;
         auto take = [](uint32_t *w) { return __hip_atomic_exchange(w, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
@@ -871,7 +872,7 @@ template <int C, int S, int NI, int NW>
 __global__ __launch_bounds__(64 * NW, C == 16 && NW == 4 ? 4 : 2) void narrow_kernel(const NarrowParams p) { narrow_stage<C, S, NI, NW>(p); }
 // A whole net without blocks: bound by instruction issue (the noise, the requantisations) and, a few to a CU, by latencies, so that five
 // workgroups a CU (92 registers, 30 KB of LDS: the sampler's table lies where the first layer then writes) instead of the general
-// kernel's four (120, 39 KB) help at all sizes: us a call with 1100 / 5100 / 20 100 copies 34.0 / 76.0 / 236 -> 32.6 / 71.6 / 218.
+// kernel's four (120, 39 KB) help at all sizes: us a certification with 1100 / 5100 / 20 100 copies 34.0 / 76.0 / 236 -> 32.6 / 71.6 / 218.
 __global__ __launch_bounds__(256, 5) void short_net_kernel(const NarrowParams p) { narrow_stage<16, 32, 1, 4, true>(p); }
 
 // The three stages of a net in one launch (narrow_chain_wanted): a workgroup reads back only what it has written, so that nothing but
