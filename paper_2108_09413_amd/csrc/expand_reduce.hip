@@ -715,10 +715,13 @@ void expand_reduce_params(const ConvParams &e, const ConvParams &r, const int8_t
     }
 }
 
-// the kernels serve tie-free convolutions only
+// The kernels serve tie-free convolutions only: where with_rq takes the general form for an add with exact halves, they take
+// their own next to it.
 template <class F>
 static void with_tie_free_rq(const XrParams &p, F f) {
-    with_rq(p.rq, p.add_rq, [&](auto rq, auto rqa) { if constexpr ((decltype(rq)::value & (RQ_TIE_FREE | RQ_PAIR)) != 0) f(rq, rqa); });
+    using std::integral_constant;
+    if ((p.rq & ~RQ_PAIR) == RQ_TIE_FREE && p.add_rq == RQ_ANY) f(integral_constant<int, RQ_TIE_FREE>{}, integral_constant<int, RQ_ANY>{});
+    else with_rq(p.rq, p.add_rq, [&](auto rq, auto rqa) { if constexpr ((decltype(rq)::value & (RQ_TIE_FREE | RQ_PAIR)) != 0) f(rq, rqa); });
 }
 
 hipError_t launch_expand_reduce(const XrParams &p, hipStream_t st) {

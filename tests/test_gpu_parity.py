@@ -739,6 +739,13 @@ class _TopForm(_ByChannel):
         return super().conv(tin, cout, k, stride, pad, relu, zp_out=-128 if relu else zp_out, **kw)
 
 
+class _Clamped(NetBuilder):
+    """Rectified layers whose zero point, the lower clamp, is above -128: neither pairs of results nor the top-byte form."""
+
+    def conv(self, tin, cout, k, stride, pad, relu, zp_out=None, **kw):
+        return super().conv(tin, cout, k, stride, pad, relu, zp_out=-100 if relu else zp_out, **kw)
+
+
 class _NextByChannel(_ByChannel):
     """One shift in every layer but the 1x1 convolutions into 128 channels."""
 
@@ -815,6 +822,12 @@ def test_top_form_in_every_conv_tile(isr, builder, tile):
 
 def test_top_form_in_expand_add_and_next_reduce(isr, builder):
     builder(_TopForm)
+    test_expand_add_and_next_reduce_in_one_kernel(isr)
+
+
+def test_clamped_layers_next_to_adds_with_and_without_halves(isr, builder):
+    """The expand-and-reduce kernels in the form of layers without exact halves and nothing else, next to adds that meet some."""
+    builder(_Clamped)
     test_expand_add_and_next_reduce_in_one_kernel(isr)
 
 
