@@ -196,12 +196,12 @@ __device__ __forceinline__ auto bias_vector(const LaneConsts<N, RQ, FETCH> &k) {
 // fragment i's tile address; element(i, q, e, value) consumes the accumulator of element e (in the order of e), after
 // start(i, q) and before finish(i); q: which of a group's fragments, a constant wherever it indexes registers.
 // The general form (shifts that differ by channel, exact halves) takes one fragment after the other, its arithmetic covered by other
-// workgroups.  With several images a workgroup (FETCH) its operands too are read three steps ahead and its constants before the products:
-// left to the compiler, whether a product waits for the read in front of it changed with the code around it.  us of the 64-channel
-// stage of a 110-layer net with 300 / 10 000 copies 118 / 1150 -> 105 / 975, of the 32-channel one 109 / 1380 -> 106 / 1323.  The
-// one-image kernels have no registers for it.
-template <int FRAGS, bool PAIRS, int RQ, bool FETCH, int C, int S, class Source, class Start, class Element, class Finish>
-__device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&fa)[WideConv<C, S>::KS], LaneConsts<16, RQ, FETCH> &k, const int8_t *next,
+// workgroups.  Its operands too are read three steps ahead and its constants (FETCH) before the products: left to the compiler, whether
+// a product waits for the read in front of it changed with the code around it.  us of the 64-channel stage of a 110-layer net with
+// 300 / 10 000 copies 118 / 1150 -> 105 / 975, of the 32-channel one 109 / 1380 -> 106 / 1323; the whole net with 100 copies in one
+// launch 200 -> 188.
+template <int FRAGS, bool PAIRS, int RQ, int C, int S, class Source, class Start, class Element, class Finish>
+__device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&fa)[WideConv<C, S>::KS], LaneConsts<16, RQ, true> &k, const int8_t *next,
                                                Source source, Start start, Element element, Finish finish) {
     if constexpr (RQ == RQ_PAIR) {
         constexpr int P = PAIRS && FRAGS >= 2 ? 2 : 1, G = FRAGS / P;
@@ -246,8 +246,7 @@ __device__ __forceinline__ void wide_fragments(const WideConv<C, S> &wc, v4i (&f
             k.fragment();
             v16i acc[1] = {bias_vector(k)};
             const int8_t *const src[1] = {source(i)};
-            if constexpr (FETCH) wide_group<1, false, false>(wc, src, fa, acc, nullptr, [](int) {});
-            else acc[0] = wc.run(src[0], fa, acc[0]);
+            wide_group<1, false, false>(wc, src, fa, acc, nullptr, [](int) {});
             start(i, 0);
 #pragma unroll
             for (int e = 0; e < 16; ++e) element(i, 0, e, acc[0][e]);
@@ -456,9 +455,9 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
         for (int j = 0; j < NTP; ++j)
             if (tid + NT * j < TPRM) vt[j] = p.tprm[tid + NT * j];
     // One image of 64 channels: a wave makes 16 channels of all pixels, so that every weight enters the CU once; with 32 channels x half of
-    // the pixels a wave, each weight twice, those 72 KB took most of a convolution's 2900 to 3600 cycles (prediction of the 110-layer
-    // net with 100 copies 141.6 -> 131.9 us, together with the down-sampling weights fetched ahead and the first descriptor as an
-    // argument; ResNet-20 40.3 -> 39.6).
+    // the pixels a wave, each weight twice, those 72 KB took most of a convolution's 2900 to 3600 cycles (the one launch of the 110-layer
+    // net with 100 copies 136 -> 121.5 us, ResNet-20's 33.3 -> 30.6, together with the results in pairs).  The down-sampling
+    // block's weights are fetched where they are used: a convolution ahead they took registers from it all, 126 and 31.8 us.
     constexpr bool SLIM = C == 64 && NI == 1;
     v4i fa[SLIM ? 9 : WIDE ? WideConv<WIDE ? C : 32, WIDE ? S : 16>::KS : 3];   // weights of the convolution to come
     auto slim_weights = [&](const int8_t *w, v4i (&f)[9]) {
@@ -481,15 +480,6 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
         else if constexpr (AHEAD) narrow_weights(p.first.w1, fa);
         if (AHEAD && tid < 4 * C) vp = p.first.prm2[tid];
     }
-    // weights of the down-sampling block's first convolution; AHEAD: fetched while the last block's second one runs
-    constexpr int KP1 = (9 * C + 63) / 64 * 64, KS1 = TAIL ? (9 * C + 31) / 32 : 1;
-    v4i f1[KS1];
-    auto tail_weights = [&]() {
-        const int mf = wave % (C2 / 32);
-#pragma unroll
-        for (int ks = 0; ks < KS1; ++ks) f1[ks] = *(const v4i *)(p.tw1 + (mf * 32 + (lane & 31)) * KP1 + ks * 32 + (lane >> 5) * 16);
-    };
-    if (AHEAD && TAIL && tail && !nblocks) tail_weights();
     auto store_constants = [&]() {
         if (nblocks && tid < 4 * C) prm[0][tid] = v0;
         if (TAIL && tail)
@@ -600,7 +590,6 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 if (AHEAD) vp = nxt.prm2()[tid];
             }
             if (zp_next != zp_x) fill_ring<C, S, NI, NT>(X, zp_next, tid);
-            if (AHEAD && TAIL && last && tail) tail_weights();
         };
         with_form(cur.form(), [&](auto rq, auto rqa) {
             constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
@@ -722,7 +711,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 asm volatile("" : "+v"(ln));
                 {
                     const Wide wc(ln, wave);
-                    LaneConsts<16, RQ, (NI > 1)> k(prm[0], C, wc.mf * 32 + wc.half * 16);
+                    LaneConsts<16, RQ, true> k(prm[0], C, wc.mf * 32 + wc.half * 16);
                     int q[4];
                     v4i o;
                     wide_fragments<FRAGS, true>(wc, fa, k, cur.w2(), [&](int i) { return X + offset(i); }, [](int, int) {},
@@ -736,7 +725,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 second_constants();
                 const AddConst ac = cur.add();
                 const Wide wc(ln, wave);
-                LaneConsts<16, RQ, (NI > 1)> k(prm[1], C, wc.mf * 32 + wc.half * 16);
+                LaneConsts<16, RQ, true> k(prm[1], C, wc.mf * 32 + wc.half * 16);
                 // a lane writes where it, or the lane with the other half of its pixel in this wave, has read
                 const int dst = last && tail ? wc.out_strided : wc.out;
                 int q[4];
@@ -759,7 +748,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
     // ---- down-sampling into the next stage ----
     if constexpr (TAIL) {
         if (tail) {
-            constexpr int TB2 = tile_bytes<C2, S2>();
+            constexpr int TB2 = tile_bytes<C2, S2>(), KP1 = (9 * C + 63) / 64 * 64, KS1 = (9 * C + 31) / 32;
             static_assert(NI * TB2 <= NI * TB, "the next stage's tile fits the middle tensor's");
             typedef WideConv<C2, S2> Wide;
             constexpr int MF = Wide::MF, NF = Wide::NF, FRAGS = (NI * NF * MF + NW - 1) / NW;   // fragments per wave (of fewer fragments than waves: one of the first waves)
@@ -770,17 +759,13 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                 constexpr int RQ = decltype(rq)::value, RQA = decltype(rqa)::value;
                 int ln = lane;
                 asm volatile("" : "+v"(ln));
-                if (!AHEAD) tail_weights();
-                v4i fa[Wide::KS], fp;   // of the other two convolutions; AHEAD: on their way while the first runs
-                auto more_weights = [&](const Wide &wc) {
-                    wc.load_weights(p.tw2, fa);
-                    fp = *(const v4i *)(p.twp + (wc.mf * 32 + wc.l) * 64 + wc.half * 16);   // channels 0 .. 31 (zeros past C)
-                };
-                if (AHEAD && tail == 1) more_weights(Wide(ln, wave));
                 {
                     const Wide wc(ln, wave);
                     const int l = wc.l, half = wc.half, mf = wc.mf, c0 = mf * 32 + half * 16;
                     const int oy0 = l / S2, ox = l % S2;       // the lane's output pixel in fragment 0
+                    v4i f1[KS1];
+#pragma unroll
+                    for (int ks = 0; ks < KS1; ++ks) f1[ks] = *(const v4i *)(p.tw1 + (mf * 32 + l) * KP1 + ks * 32 + half * 16);
                     // tap (ky, kx) of output (oy, ox) is padded input (2 oy + ky, 2 ox + kx).  16 input channels: a K step is two taps,
                     // the lane half picks one (the tenth has zero weights); 32: one tap, the half picks 16 channels
                     int b1[KS1];
@@ -816,7 +801,9 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
                     const Wide wc(ln, wave);
                     const int l = wc.l, half = wc.half, mf = wc.mf, c0 = mf * 32 + half * 16;
                     const int oy0 = l / S2, ox = l % S2;
-                    if (!AHEAD) more_weights(wc);
+                    v4i fa[Wide::KS];
+                    wc.load_weights(p.tw2, fa);
+                    const v4i fp = *(const v4i *)(p.twp + (mf * 32 + l) * 64 + half * 16);   // channels 0 .. 31 (zeros past C)
                     const int xp = tile_at<C, S, true>(2 * oy0 + 1, 2 * ox + 1, C == 16 ? 0 : half);
                     lds_barrier();
 #pragma unroll 1
@@ -869,7 +856,7 @@ __device__ __forceinline__ void narrow_stage(const NarrowParams &p) {
 }
 
 template <int C, int S, int NI, int NW>
-__global__ __launch_bounds__(64 * NW, C == 16 && NW == 4 ? 4 : 2) void narrow_kernel(const NarrowParams p) { narrow_stage<C, S, NI, NW>(p); }
+__global__ __launch_bounds__(64 * NW, C == 16 ? 4 : 2) void narrow_kernel(const NarrowParams p) { narrow_stage<C, S, NI, NW>(p); }
 // A whole net without blocks: bound by instruction issue (the noise, the requantisations) and, a few to a CU, by latencies, so that five
 // workgroups a CU (92 registers, 30 KB of LDS: the sampler's table lies where the first layer then writes) instead of the general
 // kernel's four (120, 39 KB) help at all sizes: us a certification with 1100 / 5100 / 20 100 copies 34.0 / 76.0 / 236 -> 32.6 / 71.6 / 218.

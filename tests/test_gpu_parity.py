@@ -765,6 +765,13 @@ def test_stages_of_nets_quantised_per_channel(isr, builder, copies):
     test_stages_of_the_nets_on_32x32_images(isr, "stages", copies)
 
 
+@pytest.mark.parametrize("blocks", [(0, 3, 1), (2, 1, 0)])
+def test_three_stages_of_nets_quantised_per_channel(isr, builder, blocks):
+    """The general form in the kernel of all stages, and, without blocks in the last, in those of one image a workgroup."""
+    builder(_ByChannel)
+    test_three_stages_of_few_copies_in_one_launch(isr, blocks, 256)
+
+
 # Layers whose channels share one shift take results in pairs; the top-byte form, which networks quantised per channel take, in each
 # kernel that has it:
 

@@ -123,12 +123,12 @@ def test_stage_kernels_keep_to_their_registers(code_objects):
     assert seen == 10
 
 
-def test_products_of_the_64_channel_stage_do_not_wait_for_the_read_in_front(kernels):
-    """With several images a workgroup the pixel operands are read steps ahead of their products, in the general form of the requantisation
-    as in the others: a product whose wait empties the queue that its own operand was put in last had none ahead."""
+def test_products_of_the_wide_stages_do_not_wait_for_the_read_in_front(kernels):
+    """The pixel operands of the stages of 32 and 64 channels are read steps ahead of their products, in the general form of the
+    requantisation as in the others: a product whose wait empties the queue that its own operand was put in last had none ahead."""
     checked = 0
     for name, code in kernels.items():
-        if not re.search(r"narrow_kernelILi64ELi8ELi[26]E", name):
+        if not re.search(r"narrow_kernelILi(64ELi8ELi[26]|32ELi16ELi1)E", name):
             continue
         read = empty = False
         late = products = 0
@@ -144,4 +144,4 @@ def test_products_of_the_64_channel_stage_do_not_wait_for_the_read_in_front(kern
                 read = False
         assert products > 100 and late <= 2, (name, late)
         checked += 1
-    assert checked == 2
+    assert checked == 3
