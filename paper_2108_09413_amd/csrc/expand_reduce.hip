@@ -494,53 +494,67 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
 }
 
 // ---- the 14x14 stage: 256 middle and 1024 block channels ----
-// Same scheme, sixteen waves: wave w owns channels 64 w .. 64 w + 63 of the expanding convolution (K = 256: 64 registers
-// of fragments, kept for the whole launch) and channels 16 w .. 16 w + 15 of the reducing one, whose K = 1024 no longer
-// fits next to them: its fragments are re-read from L2 per tile, two K steps at a time, one group ahead of the MFMAs
-// (256 KB per tile and workgroup, contiguous 1 KB wave-loads).  Rows of the x / y tile are 1024 bytes, of the t2 tile
-// 256 bytes; chunk c of pixel p sits at chunk c ^ (p & 15) in both.
+// Sixteen waves: wave w owns channels 64 w .. 64 w + 63 of the expanding convolution (K = 256: 64 registers of fragments, kept
+// for the whole launch) and channels 16 w .. 16 w + 15 of the reducing one, whose 256 KB of weights no longer fit next to
+// them: its fragments are read from L2 for each tile, AW K steps ahead of their MFMAs (contiguous 1 KB wave-loads).
+// Tiles of 64 pixels, the most that LDS holds with the next tile of x on its way: half the bytes of weights a pixel and half the barriers.
+// Two tiles of x take turns; t2 has one buffer, refilled behind the expanding convolution.
+// Bounds (a tile's cycles, of about 21 000): requantisations and add 8000 and the expanding MFMAs 4100 in one phase of 11 000, the reducing
+// MFMAs 4100 and the LDS reads for them 4400 in one of 8000, 1300 for the stores; memory 65 us a launch of 668 copies at the rate
+// of a large copy.  668 copies: 119 -> 100 us (115 -> 99, another card), 32-pixel tiles with the same order of reads 114.  The y tile is stored in whole rows from LDS
+// (in pieces of 32 bytes from the registers: 113 -> 134), the loads of x are spread over the expanding phase (all at its start: each
+// wave is held up to 8000 cycles at its four).
+// No faster: the two phases of neighbouring tiles side by side in two groups of waves (32 pixels a tile, four buffers; 125).
 
 constexpr int DK1 = 256, DC = 1024, DN2 = 256;
 
-template <int RQ, int RQA>
+// PX: pixels of a tile
+template <int RQ, int RQA, int PX>
 __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrParams p) {
-    __shared__ __attribute__((aligned(256))) int8_t XY[XNB][XPX * DC];
-    __shared__ __attribute__((aligned(256))) int8_t T2[XNB][XPX * DK1];
-    __shared__ __attribute__((aligned(16))) int prm1[4][DC];     // bias, M0, chi, shift-1 of the expanding convolution
-    __shared__ __attribute__((aligned(16))) int prm2[4][DN2];    // of the reducing convolution
+    constexpr int NF = PX / 32, NB = PX / 16;              // fragments of 32 (expand) and 16 pixels (reduce)
+    constexpr int ROWS = PX / 16;                          // rows of the x / y tile that a wave loads and stores
+    constexpr bool CHANNEL_SHIFT = RQ != RQ_PAIR;          // the pair form has one shift for a layer
+    constexpr int NPRM = CHANNEL_SHIFT ? 3 : 2;
+    __shared__ __attribute__((aligned(256))) int8_t XY[2][PX * DC];   // rows of 1024 bytes, chunk c of pixel p at chunk c ^ (p & 15)
+    __shared__ __attribute__((aligned(256))) int8_t T2[PX * DK1];     // rows of 256 bytes, the same
+    __shared__ __attribute__((aligned(16))) int prm1[NPRM][DC];       // bias, M0, shift-1 in the form's way, of the expanding convolution
+    __shared__ __attribute__((aligned(16))) int prm2[NPRM][DN2];      // of the reducing convolution
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ntiles = (p.npix + XPX - 1) / XPX, G = gridDim.x;
+    const int ntiles = (p.npix + PX - 1) / PX, G = gridDim.x;
     const AddConst ac = add_const<RQA>(p);
-    const uint32_t xy_lds = lds_address(&XY[0][0]), t2_lds = lds_address(&T2[0][0]);
+    const uint32_t xy_lds = lds_address(&XY[0][0]), t2_lds = lds_address(&T2[0]);
 
-    // direct-to-LDS loads of a tile: wave w fetches pixels 2 w and 2 w + 1 of the x tile (one 1024-byte row per load),
-    // waves 0 .. 7 also pixels 4 w .. 4 w + 3 of the t2 tile
-    auto issue_tile = [&](int tile, int buf) {
-        const int n0 = tile * XPX;
+    // direct-to-LDS loads of a tile: a wave fetches ROWS pixels of x (one 1024-byte row per load) and, a wave for each four pixels, of t2.
+    // Pixels past the end re-read the last one; their results are never stored.
+    auto issue_x = [&](int tile, int buf, int j) {
         int l = lane;
         asm volatile("" : "+v"(l));   // recompute the per-lane offsets per call: kept across the tile loop they would be spilled
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int px = 2 * wave + j, c = l ^ (px & 15);
-            int n = n0 + px;
-            n = n < p.npix ? n : p.npix - 1;
-            ISR_GLOBAL_TO_LDS16_AT(p.x + ((uint32_t)n * (uint32_t)DC + (uint32_t)(c * 16)), xy_lds + buf * (XPX * DC) + px * 1024);
-        }
-        if (wave < 8) {
-            const int px = 4 * wave + (l >> 4), c = (l & 15) ^ (px & 15);
-            int n = n0 + px;
-            n = n < p.npix ? n : p.npix - 1;
-            ISR_GLOBAL_TO_LDS16_AT(p.t2 + ((uint32_t)n * (uint32_t)DK1 + (uint32_t)(c * 16)), t2_lds + buf * (XPX * DK1) + wave * 1024);
-        }
+        const int px = ROWS * wave + j, c = l ^ (px & 15);
+        int n = tile * PX + px;
+        n = n < p.npix ? n : p.npix - 1;
+        ISR_GLOBAL_TO_LDS16_AT(p.x + ((uint32_t)n * (uint32_t)DC + (uint32_t)(c * 16)), xy_lds + buf * (PX * DC) + px * 1024);
+    };
+    auto issue_t2 = [&](int tile) {
+        if (wave >= PX / 4) return;
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        const int px = 4 * wave + (l >> 4), c = (l & 15) ^ (px & 15);
+        int n = tile * PX + px;
+        n = n < p.npix ? n : p.npix - 1;
+        ISR_GLOBAL_TO_LDS16_AT(p.t2 + ((uint32_t)n * (uint32_t)DK1 + (uint32_t)(c * 16)), t2_lds + wave * 1024);
     };
 
     int tile = blockIdx.x;
-    if (tile < ntiles) issue_tile(tile, 0);
-    if (tile + G < ntiles) issue_tile(tile + G, 1);
+    if (tile < ntiles) {
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) issue_x(tile, 0, j);
+        issue_t2(tile);
+    }
     // constants and weights, all on their way before any is waited for
     const int i1 = tid < DC ? tid : 0, i2 = tid < DN2 ? tid : 0;
-    const RqRaw r1 = rq_fetch(p.bias1, p.m0s1, p.chi1, p.shm11, i1), r2 = rq_fetch(p.bias2, p.m0s2, p.chi2, p.shm12, i2);
+    const int b1 = p.bias1[i1], m1 = p.m0s1[i1], s1 = p.shm11[i1], b2 = p.bias2[i2], m2 = p.m0s2[i2], s2 = p.shm12[i2];
+    const int chi1 = p.chi1[0], sh1 = p.shm11[0], chi2 = p.chi2[0], sh2 = p.shm12[0];
     const uint32_t lane16 = (uint32_t)lane * 16;
     // expand fragments [fm][ksub], kept in registers for the whole launch
     const int8_t *a1w = p.a1 + (size_t)wave * (2 * (DK1 / 32) * 1024);
@@ -552,104 +566,133 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
     // loop and waits for every outstanding memory operation at their first use in each tile)
 #pragma unroll
     for (int f = 0; f < 2 * (DK1 / 32); ++f) asm volatile("" : "+v"(a1[f]));
-    if (tid < DC) rq_store<RQ>(prm1, r1, i1);
-    if (tid < DN2) rq_store<RQ>(prm2, r2, i2);
+    if (tid < DC) {
+        prm1[0][i1] = b1; prm1[1][i1] = m1;
+        if constexpr (CHANNEL_SHIFT) prm1[NPRM - 1][i1] = rq_sh<RQ>(s1);
+    }
+    if (tid < DN2) {
+        prm2[0][i2] = b2; prm2[1][i2] = m2;
+        if constexpr (CHANNEL_SHIFT) prm2[NPRM - 1][i2] = rq_sh<RQ>(s2);
+    }
     wait_vmcnt<0>();
     __syncthreads();   // the constants are in LDS, the first tile has landed
-    const RqLayer L1 = rq_layer<RQ>(prm1[2][0], prm1[3][0]), L2 = rq_layer<RQ>(prm2[2][0], prm2[3][0]);
+    const RqLayer L1 = rq_layer<RQ>(rq_chi<RQ>(chi1, sh1), rq_sh<RQ>(sh1)), L2 = rq_layer<RQ>(rq_chi<RQ>(chi2, sh2), rq_sh<RQ>(sh2));
+    // A channel's addend (2 z_out + 1) 2^(shift-2) from its shift, where it is not the same for the layer
+    const int z1 = rq_is_top(RQ) ? rq_chi<RQ>(chi1, sh1) : chi1 >> (sh1 - 1), z2 = rq_is_top(RQ) ? rq_chi<RQ>(chi2, sh2) : chi2 >> (sh2 - 1);
+    auto addend = [](int z, int s) { return rq_is_top(RQ) ? z : z << (s - 1); };
 
+    // AW weight and FR pixel fragments of the reduce are on their way or in use (more of either is spilled)
+    constexpr int AW = CHANNEL_SHIFT ? 3 : 4, FR = CHANNEL_SHIFT ? 3 : 4;
     int buf = 0;
-    for (int it = 0; tile < ntiles; tile += G, ++it) {
-        const int n0 = tile * XPX;
-        const bool prefetch = tile + 2 * G < ntiles;
+    for (int it = 0; tile < ntiles; tile += G, ++it, buf ^= 1) {
+        const int n0 = tile * PX;
+        const bool more = tile + G < ntiles;
         if (it > 0) {
-            // Vector memory operations complete in issue order and the reduce below has already waited for its own fragment
-            // loads, which were issued after the loads of this tile: all that may still be under way are the two stores that
-            // ended the previous tile.
-            wait_vmcnt<2>();
-            lds_barrier();   // every wave's loads of this tile landed; every wave is done with the previous tile
+            // Vector memory operations complete in issue order: the loads of x stand in front of fragments that have been waited for, the
+            // load of t2 in front of the ROWS + NB stores that ended the previous tile (a tile with another behind it is whole).
+            wait_vmcnt<ROWS + NB>();
+            lds_barrier();   // every wave's loads of this tile have landed; every wave is done with the previous tile
         }
-        if (prefetch) issue_tile(tile + 2 * G, buf >= 1 ? buf - 1 : XNB - 1);
-        int l = lane;
-        asm volatile("" : "+v"(l));   // per-lane values below are recomputed per tile, loads from them are not hoisted out of the loop
-        const int half = l >> 5, px1 = l & 31;
-        const int g = l >> 4, px2 = l & 15;
         int8_t *xyb = XY[buf];
 
-        // ---- expand + add: 64 channels x 32 pixels per wave, 32 channels at a time ----
-        const int8_t *t2b = T2[buf];
-        const int b_off1 = px1 * DK1 + ((half ^ (px1 & 15)) << 4);   // chunk (2 k + half) ^ (px & 15): sub-step k flips bits 5..7 by k
-        const long n1 = (long)n0 + px1;
+        // ---- expand + add into the tile of x: 64 channels x 32 pixels at a time, pixel fragments read two K sub-steps ahead ----
+#pragma unroll 1
+        for (int nf = 0; nf < NF; ++nf) {
+            int l = lane;
+            asm volatile("" : "+v"(l));   // per-lane values are recomputed, loads from them are not hoisted out of the loop
+            const int half = l >> 5, px1 = nf * 32 + (l & 31);
+            if (more) issue_x(tile + G, buf ^ 1, 2 * nf);
+            v16i acc[2];
 #pragma unroll
-        for (int fm = 0; fm < 2; ++fm) {
-            const int oc = wave * 64 + fm * 32 + half * 16;
-            v16i acc;
+            for (int fm = 0; fm < 2; ++fm)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[i] = prm1[0][oc + i];
+                for (int i = 0; i < 16; ++i) acc[fm][i] = prm1[0][wave * 64 + fm * 32 + half * 16 + i];
+            const int b_off1 = px1 * DK1 + ((half ^ (px1 & 15)) << 4);   // chunk (2 k + half) ^ (px & 15): sub-step k flips bits 5..7 by k
+            auto operand = [&](int ks) { return *(const v4i *)(T2 + (b_off1 ^ (ks << 5))); };
+            v4i fb[3] = {operand(0), operand(1)};
 #pragma unroll
             for (int ks = 0; ks < DK1 / 32; ++ks) {
-                const v4i fb = *(const v4i *)(t2b + (b_off1 ^ (ks << 5)));
-                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1[fm * (DK1 / 32) + ks], fb, acc, 0, 0, 0);
-            }
-            int8_t *cell = xyb + px1 * DC + (((oc >> 4) ^ (px1 & 15)) << 4);
-            const v4i rv = *(const v4i *)cell;
-            v4i yv;
+                if (ks + 2 < DK1 / 32) fb[(ks + 2) % 3] = operand(ks + 2);
 #pragma unroll
-            for (int gi = 0; gi < 4; ++gi) {
-                __builtin_amdgcn_sched_barrier(0);   // one group's constants at a time: the registers are needed for weight fragments
-                const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = rq_chi4<RQ>(&prm1[2][oc + 4 * gi]), ss = *(const v4i *)&prm1[3][oc + 4 * gi];
-                int q[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) q[i] = rq_conv<RQ>(acc[4 * gi + i], mm[i], ch[i], ss[i], p.lo1, L1);
-                yv[gi] = (int)rq_add4<RQ, RQA>(q[0], q[1], q[2], q[3], (uint32_t)rv[gi], ac, L1);
+                for (int fm = 0; fm < 2; ++fm) acc[fm] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1[fm * (DK1 / 32) + ks], fb[ks % 3], acc[fm], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            *(v4i *)cell = yv;
-            if (n1 < p.npix) *(v4i *)(p.y + n1 * DC + oc) = yv;
+#pragma unroll
+            for (int fm = 0; fm < 2; ++fm) {
+                const int oc = wave * 64 + fm * 32 + half * 16;
+                int8_t *cell = xyb + px1 * DC + (((oc >> 4) ^ (px1 & 15)) << 4);
+                const v4i rv = *(const v4i *)cell;
+                v4i yv;
+#pragma unroll
+                for (int gi = 0; gi < 4; ++gi) {
+                    __builtin_amdgcn_sched_barrier(0);   // one group's constants at a time: the registers are needed for weight fragments
+                    const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ss = *(const v4i *)&prm1[NPRM - 1][oc + 4 * gi];
+                    int q[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) q[i] = rq_conv<RQ>(acc[fm][4 * gi + i], mm[i], addend(z1, ss[i]), ss[i], p.lo1, L1);
+                    yv[gi] = (int)rq_add4<RQ, RQA>(q[0], q[1], q[2], q[3], (uint32_t)rv[gi], ac, L1);
+                }
+                *(v4i *)cell = yv;
+                if (fm == 0 && more) issue_x(tile + G, buf ^ 1, 2 * nf + 1);
+            }
         }
-        // the first group of reduce fragments is on its way while the workgroup meets at the barrier
-        constexpr int GK = 2;   // K steps per group of reduce fragments (four measured no faster)
-        v4i a2c[2][GK];
+        // ---- reduce: 16 channels of the PX pixels, K = 1024; pixel fragments read FR - 1 ahead ----
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        v4i a2c[AW];
 #pragma unroll
-        for (int i = 0; i < GK; ++i) a2c[0][i] = *(const v4i *)(a2w + ((uint32_t)l * 16 + (uint32_t)(i * 1024)));
-        lds_barrier();   // the y tile is complete
-        asm volatile("" ::: "memory");
-
-        // ---- reduce: wave w computes channels 16 w .. 16 w + 15 of the 32 pixels, K = 1024 ----
+        for (int i = 0; i < AW; ++i) {   // in the order of their use
+            __builtin_amdgcn_sched_barrier(0);
+            a2c[i] = *(const v4i *)(a2w + ((uint32_t)l * 16 + (uint32_t)(i * 1024)));
+        }
+        lds_barrier();   // the y tile is complete, everybody is done with t2
+        if (more) issue_t2(tile + G);
+        v4acc acc2[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc2[nb][i] = prm2[0][wave * 16 + (l >> 4) * 4 + i];
         {
-            v4acc acc2[2];
+            const int g = l >> 4, px2 = l & 15;
+            const int y_off = px2 * DC + ((g ^ px2) << 4);   // chunk (4 k + g) ^ px2: step k flips bits 6..9 by k
+            auto operand = [&](int i) { return *(const v4i *)(xyb + (y_off ^ (i / NB << 6)) + i % NB * (16 * DC)); };
+            constexpr int KS = DC / 64;
+            v4i fb[FR];
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
+            for (int i = 0; i < FR - 1; ++i) fb[i] = operand(i);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc2[nb][i] = prm2[0][wave * 16 + g * 4 + i];
+            for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
-            for (int j = 0; j < DC / 64 / GK; ++j) {
-                if (j + 1 < DC / 64 / GK) {
-#pragma unroll
-                    for (int i = 0; i < GK; ++i) a2c[(j + 1) & 1][i] = *(const v4i *)(a2w + ((uint32_t)l * 16 + (uint32_t)(((j + 1) * GK + i) * 1024)));
+                for (int nb = 0; nb < NB; ++nb) {
+                    const int i = ks * NB + nb;
+                    if (i + FR - 1 < KS * NB) fb[(i + FR - 1) % FR] = operand(i + FR - 1);
+                    acc2[nb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a2c[ks % AW], fb[i % FR], acc2[nb], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-#pragma unroll
-                for (int i = 0; i < GK; ++i) {
-                    const int ks = GK * j + i;
-#pragma unroll
-                    for (int nb = 0; nb < 2; ++nb) {
-                        const v4i fb = *(const v4i *)(xyb + (px2 + 16 * nb) * DC + (((4 * ks + g) ^ px2) << 4));
-                        acc2[nb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a2c[j & 1][i], fb, acc2[nb], 0, 0, 0);
-                    }
-                }
-            }
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
-                const long n2 = (long)n0 + px2 + 16 * nb;
-                int q[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int c = wave * 16 + g * 4 + i;
-                    q[i] = rq_conv<RQ>(acc2[nb][i], prm2[1][c], prm2[2][rq_chi_at<RQ>(c)], prm2[3][c], p.lo2, L2);
-                }
-                if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * DN2 + wave * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3], L2);
+                if (ks + AW < KS) a2c[ks % AW] = *(const v4i *)(a2w + ((uint32_t)l * 16 + (uint32_t)((ks + AW) * 1024)));
+                // behind the last of them: a fragment would wait for what is issued in front of it, which comes from memory
             }
         }
-        buf = buf + 1 == XNB ? 0 : buf + 1;
+        l = lane;
+        asm volatile("" : "+v"(l)::"memory");
+        const int g = l >> 4, px2 = l & 15;
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) {   // y in whole rows
+            const int px = ROWS * wave + j;
+            const long n1 = (long)n0 + px;
+            if (n1 < p.npix) *(v4i *)(p.y + n1 * DC + (uint32_t)l * 16) = *(const v4i *)(xyb + px * DC + ((l ^ (px & 15)) << 4));
+        }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const long n2 = (long)n0 + px2 + 16 * nb;
+            int q[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int c = wave * 16 + g * 4 + i, ss = prm2[NPRM - 1][c];
+                q[i] = rq_conv<RQ>(acc2[nb][i], prm2[1][c], addend(z2, ss), ss, p.lo2, L2);
+            }
+            if (n2 < p.npix) *(uint32_t *)(p.t1n + n2 * DN2 + wave * 16 + g * 4) = rq_pack<RQ>(q[0], q[1], q[2], q[3], L2);
+        }
     }
 }
 
@@ -730,9 +773,17 @@ hipError_t launch_expand_reduce(const XrParams &p, hipStream_t st) {
     if ((long)p.npix * DC >= (1l << 32)) return hipErrorInvalidValue;   // 32-bit byte offsets inside the tensors
     const int ntiles = (p.npix + XPX - 1) / XPX;
     if (p.k1 == DK1) {
-        const dim3 grid((unsigned)(ntiles < 256 ? ntiles : 256));
+        // us of a launch with r rounds of 256 tiles: 8.5 + 10.7 r with 64 pixels, 7 + 6.7 r with 32 (copies of 14 x 14 pixels 60 / 84 / 100 / 150 /
+        // 250 / 668: 17.4 / 27.4 / 29.0 / 30.8 / 42.5 / 100 and 19.0 / 25.5 / 26.2 / 32.8 / 46.2 / 114)
+        const int wide = (p.npix + 63) / 64, rounds = (ntiles + 255) / 256, wide_rounds = (wide + 255) / 256;
+        const bool narrow = 15 + 107 * wide_rounds > 67 * rounds;
+        const int tiles = narrow ? ntiles : wide;
+        const dim3 grid((unsigned)(tiles < 256 ? tiles : 256));
         set_kernel_name("expand_reduce_kernel<256, 1024, 256>");
-        with_tie_free_rq(p, [&](auto rq, auto rqa) { hipLaunchKernelGGL((expand_reduce1024_kernel<decltype(rq)::value, decltype(rqa)::value>), grid, dim3(XNT2), 0, st, p); });
+        with_tie_free_rq(p, [&](auto rq, auto rqa) {
+            if (narrow) hipLaunchKernelGGL((expand_reduce1024_kernel<decltype(rq)::value, decltype(rqa)::value, 32>), grid, dim3(XNT2), 0, st, p);
+            else hipLaunchKernelGGL((expand_reduce1024_kernel<decltype(rq)::value, decltype(rqa)::value, 64>), grid, dim3(XNT2), 0, st, p);
+        });
         return hipGetLastError();
     }
     if (p.in2) {

@@ -1229,6 +1229,46 @@ def test_expand_add_and_next_reduce_in_one_kernel(isr):
     m.close()
 
 
+@pytest.mark.parametrize("layers", [None, _ByChannel, _TopForm, _Clamped])
+@pytest.mark.parametrize("copies", [1, 3, 11, 329, 656, 1000, 1967])
+def test_expand_and_reduce_in_launches_of_few_and_many_tiles(isr, builder, copies, layers):
+    """The four kernels on 5x5 maps, in each form of the requantisation: tiles of 32 pixels for 256 persistent workgroups, 1 to 1537 of
+    them, so that a workgroup has none, one, or up to seven, the last one ragged; with 1024 channels tiles of 64 pixels where those
+    take fewer rounds (329, 1000 and 1967 copies).  Logits that depend on every pixel: against one kernel per op, and three copies against the oracle."""
+    _say(f"expand + reduce, {copies} copies, {layers and layers.__name__}")
+    if layers:
+        builder(layers)
+    b = NetBuilder(rng=np.random.default_rng(64), in_shape=(3, 20, 20), num_classes=7)
+    ta = b.conv(b.tensor(3, 20, 20, 0, 74.0), 256, 3, 2, 1, True)
+    u = b.conv(b.conv(ta, 128, 1, 1, 0, True), 128, 3, 2, 1, True)
+    u = b.conv(u, 512, 1, 1, 0, False)
+    t1 = b.add(b.conv(ta, 512, 1, 2, 0, False, zp_out=-9), u, True)       # projection, stride 2
+    u = b.conv(b.conv(t1, 128, 1, 1, 0, True), 128, 3, 1, 1, True)
+    t2 = b.add(t1, b.conv(u, 512, 1, 1, 0, False, zp_out=4), True, ma=1 << 19, mb=1 << 19, sh=20)   # exact halves in the add
+    u = b.conv(b.conv(t2, 128, 1, 1, 0, True), 128, 3, 1, 1, True)
+    t3 = b.add(t2, b.conv(u, 512, 1, 1, 0, False), True)
+    tc = b.conv(b.conv(t3, 256, 1, 1, 0, True), 1024, 1, 1, 0, True)
+    u = b.conv(b.conv(tc, 256, 1, 1, 0, True), 256, 3, 1, 1, True)
+    t4 = b.add(tc, b.conv(u, 1024, 1, 1, 0, False, zp_out=-3), True)
+    u = b.conv(b.conv(t4, 256, 1, 1, 0, True), 256, 3, 1, 1, True)
+    t5 = b.add(b.conv(u, 1024, 1, 1, 0, False), t4, True, ma=1 << 19, mb=1 << 19, sh=20)
+    b.fc(b.conv(b.conv(t5, 256, 1, 1, 0, True), 16, 1, 1, 0, True), 7)
+    m = _load(isr, b.blob(), copies)
+    x = np.random.default_rng(65).integers(0, 256, size=(3, 20, 20)).astype(np.uint8)
+    isr.isr_profile(m, 1)
+    lg, am, cnt = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 3, copies)
+    names = {s["name"]: s["launches"] for s in isr.isr_profile_read(m)}
+    for kernel, launches in (("proj_expand_reduce_kernel<256, 128, 512, 128>", 1), ("expand_reduce_kernel<128, 512, 128>", 1),
+                             ("expand_reduce_kernel<128, 512, 256>", 1), ("expand_reduce_kernel<256, 1024, 256>", 2)):
+        assert names.get(kernel, 0) == launches, names
+    isr.isr_set_fusion(m, 0)
+    lg0, am0, cnt0 = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 3, copies)
+    m.close()
+    assert np.array_equal(lg, lg0) and np.array_equal(am, am0) and np.array_equal(cnt, cnt0)
+    few = min(3, copies)
+    assert np.array_equal(lg[:few], oracle.Model(b.blob()).mc(x, 64, 2, 1, 1, 3, few)[0])
+
+
 # ---- many (image, sigma) pairs in one pass -------------------------------------
 
 def _check_batch_against_oracle(isr, m, om, xs, items, n0, n, seed):
