@@ -110,6 +110,29 @@ def test_fexpand_stores_are_what_its_waits_count(kernels):
     assert checked == 5
 
 
+def test_expand_and_reduce_stores_are_what_the_waits_count(kernels):
+    """The expand-and-reduce kernels of sixteen waves wait until only the stores and loads behind a tile's loads are left: so many stores, in
+    both orders of a tile's two halves and of the first tile alone, or behind the last barrier of a tile."""
+    wanted = {"proj_expand_reduce_kernel": (3, 2), "expand_reduce256_kernel": (3, 4)}
+    checked = 0
+    for name, code in kernels.items():
+        ops = [t.split()[0] for _, t, _ in code]
+        for kernel, (wide, narrow) in wanted.items():
+            if kernel in name:
+                assert (ops.count("global_store_dwordx4"), ops.count("global_store_dword")) == (wide, narrow), name
+                checked += 1
+        tile = re.search(r"expand_reduce1024_kernelILi\d+ELi\d+ELi(\d+)E", name)
+        if tile:
+            n = int(tile.group(1)) // 16
+            last = len(ops) - 1 - ops[::-1].index("s_barrier")
+            assert (ops[last:].count("global_store_dwordx4"), ops[last:].count("global_store_dword")) == (n, n), name
+            assert not any("global_store" in o for o in ops[:last]), name
+            checked += 1
+        if tile or any(kernel in name for kernel in wanted):
+            assert not any("store" in o and not o.startswith("global_store_dword") for o in ops), name
+    assert checked == 24
+
+
 def test_stage_kernels_keep_to_their_registers(code_objects):
     """The kernels of the nets on 32 x 32 images, whose rates rest on two to five workgroups a CU with everything in registers."""
     seen = 0
