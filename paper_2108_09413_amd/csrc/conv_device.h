@@ -42,7 +42,7 @@ __device__ __forceinline__ int requant_fast(int acc, int m0, int chi, int shm1) 
     return (int)(w >> 32) >> shm1;
 }
 
-// The same again for a layer whose products acc * M0 can never be an exact half
+// The same again for a layer whose products acc * M0 are never a negative exact half above the clamp
 // (ConvParams::tie_free): with the low word of the rounding term gone only the high
 // word of the product is needed.
 __device__ __forceinline__ int requant_tie_free(int acc, int m0, int chi, int shm1) {
@@ -84,7 +84,8 @@ __device__ __forceinline__ uint32_t pack4(int a, int b, int c, int d) {
 
 // How a layer's requantisation and its fused residual add are computed; chosen per layer when the model is loaded.
 //   RQ_ANY       any layer of the single-multiply form
-//   RQ_TIE_FREE  no accumulator value meets an exact half (ConvParams::tie_free)
+//   RQ_TIE_FREE  no accumulator value meets an exact half whose rounding would show (ConvParams::tie_free): rectified layers, and
+//                nearly all others
 //   RQ_TOP       tie-free, lower clamp -128, and every intermediate fits (plan.cpp): the int8 result is kept in the TOP
 //                byte of a word, where int32 saturation is its clamp.  w = mulhi(acc, M0) fits 24 bits, so
 //                  sat32(w * 2^(24 - shm1) + (2^23 + z_out 2^24))

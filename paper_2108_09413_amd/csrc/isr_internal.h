@@ -151,8 +151,8 @@ struct ConvParams {
     const int32_t *chi;      // [Mp] 2^(shift-2) + z_out * 2^(shift-1)   } valid when every
     const int32_t *shm1;     // [Mp] shift - 1                           } shift is in [2, 22]
     int32_t fast_requant;
-    // 1: no output channel can meet acc * M0 = (odd) * 2^(30 + shift) within its accumulator range, so RHA
-    // never rounds an exact half and the sign correction of the rounding term is dead: the kernel then
+    // 1: no output channel can meet a negative acc * M0 = (odd) * 2^(30 + shift) within its accumulator range and above its
+    // clamp, so that the sign correction of the rounding term changes nothing: the kernel then
     // takes (mulhi(acc, M0) + chi) >> (shift - 1) (decided per layer when the model is loaded)
     int32_t tie_free;
     int32_t rq;              // Rq class of this convolution's requantisation (conv_device.h)
@@ -162,7 +162,7 @@ struct ConvParams {
     const int8_t *res;       // [B][Ho][Wo][Cout_p] other input of the add
     int32_t fuse_add, add_mul_self, add_mul_res, add_c0, add_k, add_sh, add_lo;
     int32_t add_rq;          // Rq class of the add
-    int32_t add_tie_free;    // 1: no pair of int8 inputs makes v a negative exact half: out = clamp((v + add_k) >> add_sh)
+    int32_t add_tie_free;    // 1: no pair of int8 inputs makes v a negative exact half above the clamp: out = clamp((v + add_k) >> add_sh)
     // fuse_add == 2: the residual is itself the output of a 1x1 stride-1 convolution (same pixels, same
     // channels) that has no other reader; the kernel computes it first, keeps it in registers and never
     // stores it.  Its operands:

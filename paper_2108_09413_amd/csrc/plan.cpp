@@ -181,13 +181,14 @@ void fuse_adds(const ParsedModel &pm, const std::vector<DevOp> &plain, std::vect
                 c.conv.add_k = (int32_t)k;
                 c.conv.add_sh = a.sh;
                 c.conv.add_lo = a.relu ? a.zo : -128;
-                // v = q Ms + r Mr + c0 over all int8 pairs: is a negative exact half of 2^sh ever met?
+                // v = q Ms + r Mr + c0 over all int8 pairs: does a negative exact half of 2^sh, which is rounded away from zero, give
+                // another result where it is rounded up?  A rectified sum never does: either lies below its clamp.
                 bool add_ties = false;
                 const int64_t halfbit = 1ll << (a.sh - 1), mask = (1ll << a.sh) - 1;
                 for (int q = -128; q <= 127 && !add_ties; ++q)
                     for (int r = -128; r <= 127; ++r) {
-                        const int64_t v = q * m_self + r * m_res + c0;
-                        if (v < 0 && (v & mask) == halfbit) { add_ties = true; break; }
+                        const int64_t v = q * m_self + r * m_res + c0, up = (v + k) >> a.sh;
+                        if (v < 0 && (v & mask) == halfbit && up > c.conv.add_lo) { add_ties = true; break; }
                     }
                 c.conv.add_tie_free = add_ties ? 0 : 1;
                 {   // top form (conv_device.h): multipliers in 24 bits; every sum, or at least each half of it, in
@@ -526,10 +527,13 @@ int build_device_ops(const ParsedModel &pm, std::vector<DevOp> &ops, ConstArena 
                             wabs += v < 0 ? -v : v;
                         }
                 {
-                    // acc * M0 is an exact half of 2^(31 + shift) only if acc = (odd) * 2^(30 + shift - tz(M0))
+                    // acc * M0 is an exact half of 2^(31 + shift) only if acc = (odd) * 2^(30 + shift - tz(M0)), and then at least
+                    // (M0 >> tz(M0)) / 2 steps from zero.  A negative one, rounded away from zero, gives another result than
+                    // rounded up only if neither lies below the clamp: never in a rectified layer, and hardly ever in
+                    // others, where the steps have to be fewer than 256 and M0 a multiple of 2^21.
                     const int64_t accmax = std::llabs((int64_t)o.bias[oc]) + maxdev * wabs;
-                    const int need = 30 + o.shift[oc] - __builtin_ctz((unsigned)o.M0[oc]);
-                    if (need < 40 && accmax >= (1ll << need)) tie_free = false;
+                    const int tz = __builtin_ctz((unsigned)o.M0[oc]), need = 30 + o.shift[oc] - tz, lo = o.relu ? to.zp : -128;
+                    if (need < 40 && accmax >= (1ll << need) && (o.M0[oc] >> tz) / 2 < to.zp - lo) tie_free = false;
                     // |mulhi(acc, M0)| < 2^23 and 2^(24 - shm1) < 2^23 as 24-bit operands
                     if ((__int128)accmax * o.M0[oc] >= ((__int128)((1 << 23) - 1) << 32) || o.shift[oc] < 3) top = false;
                     pair = pair && o.shift[oc] == o.shift[0];

@@ -31,8 +31,8 @@ int main(int argc, char **argv) {
         if (d.bneck) rq &= d.conv2.rq & (d.bneck >= 2 ? d.conv3.rq : ~0) & (d.bneck == 4 ? d.conv3.rq2 : ~0);
         if (d.reduce) rq &= d.conv4.rq;
         if (d.xr) rq &= d.conv2.rq;
-        std::printf("type %d stem %d bneck %d reduce %d xr %d k %d stride %d cin %d cout %d next %d form %d\n", (int)d.type, d.stem_pool, d.bneck, d.reduce, d.xr, c.k, c.stride,
-                    c.Cin_p, c.Cout_p, d.xr ? d.conv2.Cout_p : 0, d.type == OP_CONV ? rq_form(rq) : -1);
+        std::printf("type %d stem %d bneck %d reduce %d xr %d k %d stride %d cin %d cout %d next %d form %d tie_free %d add_tie_free %d\n", (int)d.type, d.stem_pool, d.bneck, d.reduce, d.xr, c.k, c.stride,
+                    c.Cin_p, c.Cout_p, d.xr ? d.conv2.Cout_p : 0, d.type == OP_CONV ? rq_form(rq) : -1, c.tie_free, c.fuse_add ? c.add_tie_free : -1);
     }
     return 0;
 }

@@ -63,6 +63,30 @@ def test_block_and_the_next_stages_first_convolution(fused_ops, block, after, fu
     assert [(bool(o["reduce"]), o["form"]) for o in blocks] == [(fused, form)]
 
 
+# halves of a multiplier (odd) * 2^tz lie (odd) / 2 steps and more from zero, its accumulators 2^(30 + shift - tz) and more
+@pytest.mark.parametrize("tz,sh,zp,relu,free", [
+    (29, 9, -128, True, True), (29, 9, 100, True, True), (29, 9, -128, False, True), (29, 9, -126, False, False), (29, 9, 0, False, False),
+    (18, 9, 127, False, True), (21, 9, 127, False, True), (22, 9, 127, False, False), (22, 9, 0, False, True), (22, 22, 127, False, True),
+    (30, 9, -127, False, False), (30, 9, -128, False, True),
+])
+def test_halves_that_no_clamp_hides(fused_ops, tz, sh, zp, relu, free):
+    b = NetBuilder(rng=np.random.default_rng(84), in_shape=(3, 8, 8), num_classes=9)
+    t = b.conv(b.tensor(3, 8, 8, 0, 74.0), 64, 3, 1, 1, True)
+    odd = ((1 << 30) >> tz) + (1 if tz < 30 else 0)          # the fewest steps
+    t = b.conv(t, 256, 1, 1, 0, relu, m0=np.full(256, odd << tz), sh=np.full(256, sh), zp_out=zp)
+    b.fc(b.conv(t, 16, 1, 1, 0, True), 9)
+    assert [bool(o["tie_free"]) for o in fused_ops(b.blob()) if o["cout"] == 256] == [free]
+
+
+@pytest.mark.parametrize("relu,ma,mb,free", [(True, 1 << 19, 1 << 19, True), (False, 1 << 19, 1 << 19, False), (False, 700001, 800003, True), (True, -(1 << 19), 1 << 19, True)])
+def test_halves_in_an_add_that_no_clamp_hides(fused_ops, relu, ma, mb, free):
+    b = NetBuilder(rng=np.random.default_rng(85), in_shape=(3, 8, 8), num_classes=9)
+    t = b.conv(b.conv(b.tensor(3, 8, 8, 0, 74.0), 64, 3, 1, 1, True), 192, 1, 1, 0, True)
+    u = b.conv(b.conv(t, 64, 3, 1, 1, True), 192, 1, 1, 0, False)
+    b.fc(b.conv(b.add(t, u, relu, ma=ma, mb=mb, sh=20, zp_out=-7), 16, 1, 1, 0, True), 9)
+    assert [bool(o["add_tie_free"]) for o in fused_ops(b.blob()) if o["add_tie_free"] >= 0] == [free]
+
+
 class _Blob(Exception):
     pass
 

@@ -838,6 +838,73 @@ def test_clamped_layers_next_to_adds_with_and_without_halves(isr, builder):
     test_expand_add_and_next_reduce_in_one_kernel(isr)
 
 
+class _HalvesInAdds(NetBuilder):
+    """Adds without rectification that meet negative exact halves: the general form of the add next to pairs of results."""
+
+    def add(self, ta, tb, relu=True, ma=None, mb=None, sh=20, zp_out=None):
+        return super().add(ta, tb, False, ma=1 << 19, mb=1 << 19, sh=20, zp_out=0 if zp_out in (None, -128) else zp_out)
+
+
+class _HalvesInBoth(_HalvesInAdds):
+    """The convolutions in front of them as well."""
+
+    def conv(self, tin, cout, k, stride, pad, relu, m0=None, **kw):
+        if not relu and m0 is None:
+            m0 = np.full(cout, 3 << 29, dtype=np.int64)
+        return super().conv(tin, cout, k, stride, pad, relu, m0=m0, **kw)
+
+
+class _HalvesByChannel(_HalvesInAdds, _ByChannel):
+    """Next to layers whose shifts differ."""
+
+
+class _HalvesClamped(_HalvesInAdds, _Clamped):
+    """Next to layers without exact halves and nothing else."""
+
+
+@pytest.mark.parametrize("layers", [_HalvesInAdds, _HalvesInBoth, _HalvesByChannel, _HalvesClamped])
+@pytest.mark.parametrize("net", ["stages", "down", "blocks of 16, 32, 64", "down-sampling blocks", "bottleneck", "bottleneck 128", "second convolution"])
+def test_negative_exact_halves_that_show(isr, builder, net, layers):
+    """A negative exact half is rounded away from zero, which shows only above a layer's clamp: rectified layers and sums take the forms
+    without halves, so the general ones, in each kernel, run with sums that are not rectified."""
+    builder(layers)
+    {"stages": lambda: test_stages_of_the_nets_on_32x32_images(isr, "stages", 257),
+     "down": lambda: test_stages_of_the_nets_on_32x32_images(isr, "down", 3),
+     "blocks of 16, 32, 64": lambda: test_identity_residual_blocks_in_one_kernel(isr),
+     "down-sampling blocks": lambda: test_downsampling_residual_blocks_in_one_kernel(isr),
+     "bottleneck": lambda: test_bottleneck_blocks_in_one_kernel(isr, (30, 20)),
+     "bottleneck 128": lambda: test_bottleneck_blocks_with_128_middle_channels_in_one_kernel(isr, (5, 40)),
+     "second convolution": lambda: test_residual_computed_by_a_second_convolution(isr)}[net]()
+
+
+@pytest.mark.parametrize("layers", [_HalvesInAdds, _HalvesByChannel, _HalvesClamped])
+@pytest.mark.parametrize("copies", [11, 329])
+def test_negative_exact_halves_in_expand_and_reduce(isr, builder, copies, layers):
+    builder(layers)
+    test_expand_and_reduce_in_launches_of_few_and_many_tiles(isr, lambda cls: None, copies, None)
+
+
+@pytest.mark.parametrize("tz", [18, 20, 21, 22, 23, 26, 29, 30])
+@pytest.mark.parametrize("by_channel", [False, True])
+def test_exact_halves_on_both_sides_of_the_clamp(isr, tz, by_channel):
+    """Multipliers (odd) * 2^tz meet exact halves (odd) / 2 steps from zero: beyond every clamp up to tz = 21, within those of zero points up to
+    127, 0 and -128 + 2^(30 - tz) / 2 from 22, 23 and 30 on.  Shifts so small that the accumulators reach them."""
+    _say(f"exact halves, tz {tz}, {by_channel}")
+    rng = np.random.default_rng(tz)
+    b = NetBuilder(rng=np.random.default_rng(91), in_shape=(3, 8, 8), num_classes=5)
+    t = b.conv(b.tensor(3, 8, 8, 0, 74.0), 64, 3, 1, 1, True)
+    for sh in (3, 8):
+        for zp in (127, 0, -126, -128):
+            odd = rng.integers(1 << (29 - tz), 1 << (30 - tz), size=64) * 2 + 1 if tz < 30 else np.ones(64, dtype=np.int64)
+            shifts = np.full(64, sh) + (np.arange(64) % 3 if by_channel else 0)
+            for relu in (False, True):
+                u = b.conv(t, 64, 1, 1, 0, relu, m0=odd << tz, sh=shifts, zp_out=zp)
+            t = b.conv(b.add(u, b.conv(t, 64, 1, 1, 0, False, m0=odd << tz, sh=shifts, zp_out=zp), True), 64, 1, 1, 0, True)
+    b.fc(b.gap(t), 5)
+    x = np.random.default_rng(92).integers(0, 256, size=(3, 8, 8)).astype(np.uint8)
+    _check_all_tensors(isr, b.blob(), x, 64, sample=2, chunk=3)
+
+
 # ---- S6-S8: logits, votes, decisions -----------------------------------------
 
 def test_config0_full_certify_and_predict(isr):
