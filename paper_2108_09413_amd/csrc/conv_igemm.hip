@@ -354,19 +354,41 @@ static hipError_t launch_dma(const ConvParams &p, hipStream_t st) {
     return hipGetLastError();
 }
 
+// With a residual that a second convolution computes: 64-byte K steps in two buffers.
+// PAIRS: of results only, the other forms take more registers than four waves a SIMD have.
+template <int BM, int BN, int MINB, bool PAIRS = false>
+static hipError_t launch_dma_pair(const ConvParams &p, hipStream_t st) {
+    constexpr int NT = (BM / 64) * (BN / 64) * 64;
+    dim3 grid((unsigned)(((p.npix + BN - 1) / BN) * ((p.Cout_p + BM - 1) / BM)));
+    if (!p.in2 || !p.w2 || p.Cin2_p < 64 || p.Cin2_p % 64 != 0) return hipErrorInvalidValue;
+    set_kernel_name(conv_dma_name<BM, BN, 64, 2, 2, MINB, 64, 64>());
+    with_rq(p.rq & p.rq2, p.add_rq, [&](auto rq, auto rqa) {
+        if constexpr (!PAIRS || decltype(rq)::value == RQ_PAIR)
+            hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 2, 2, MINB, decltype(rq)::value, 64, 64, decltype(rqa)::value>), grid, dim3(NT), 0, st, p);
+    });
+    return hipGetLastError();
+}
+
+// 256 channels a workgroup, two workgroups of eight waves a CU, move three quarters of the bytes of 128 x 128 tiles and set up half as many
+// tiles; with less than one and a half rounds of them the smaller ones, three a CU, fill the CUs better.  us of the pairs at
+// 14 x 14 (512 and 256 into 1024 channels) and 7 x 7 (1024 and 512 into 2048), 128 x 128 / 256 x 128:
+//   copies    100          125          200          250          334          668
+//   14 x 14   28.7 / 30.9  31.8 / 31.8  48.6 / 46.1  60.2 / 56.9  79.8 / 78.8  161 / 160 (another card 185 / 178)
+//   7 x 7     26.3 / 28.9  29.5 / 29.8  46.8 / 48.3  54.1 / 50.9  70.9 / 63.8  140 / 127
+// (668 copies, 128 x 256: 190 and 142, 256 x 256: 198 and 147, with three buffers 151 and 146 at 7 x 7)
+static hipError_t launch_dma_pair(const ConvParams &p, hipStream_t st) {
+    if (p.Cout_p <= 64) return launch_dma_pair<64, 256, 3>(p, st);
+    const bool wide = p.Cout_p % 256 == 0 && ((long)p.npix + 127) / 128 * (p.Cout_p / 256) >= 768 && (p.rq & p.rq2 & p.add_rq & RQ_PAIR);
+    return wide ? launch_dma_pair<256, 128, 4, true>(p, st) : launch_dma_pair<128, 128, 3>(p, st);
+}
+
 // With a fused residual add: 64-byte K steps in two buffers (any Kp is a multiple of 64),
 // the second of which also receives the residual tile; small tiles, 3-4 workgroups per CU.
-template <int BM, int BN, int MINB, int MINB2>
+template <int BM, int BN, int MINB>
 static hipError_t launch_dma_fused(const ConvParams &p, hipStream_t st) {
     constexpr int NT = (BM / 64) * (BN / 64) * 64;
     dim3 grid((unsigned)(((p.npix + BN - 1) / BN) * ((p.Cout_p + BM - 1) / BM)));
-    if (p.fuse_add == 2) {
-        if (!p.in2 || !p.w2 || p.Cin2_p < 64 || p.Cin2_p % 64 != 0) return hipErrorInvalidValue;
-        set_kernel_name(conv_dma_name<BM, BN, 64, 2, 2, MINB2, 64, 64>());
-        with_rq(p.rq & p.rq2, p.add_rq, [&](auto rq, auto rqa) {
-            hipLaunchKernelGGL((conv_dma_kernel<BM, BN, 64, 2, 2, MINB2, decltype(rq)::value, 64, 64, decltype(rqa)::value>), grid, dim3(NT), 0, st, p);
-        });
-    } else if (BM == 128 && p.Kp == 128) {
+    if (BM == 128 && p.Kp == 128) {
         // two K steps: with a third buffer the residual tile is fetched at the start instead of
         // during the last step, which measured faster than the fourth workgroup per CU
         if constexpr (BM == 128) {
@@ -442,7 +464,8 @@ hipError_t launch_conv(const ConvParams &p, hipStream_t st) {
     if (dma_path(p.Cout_p, p.fast_requant, p.c4)) {
         if (!p.zpad) return hipErrorInvalidValue;
         const bool k128 = p.kb == 128;
-        if (p.fuse_add) return p.Cout_p <= 64 ? launch_dma_fused<64, 256, 3, 3>(p, st) : launch_dma_fused<128, 128, 4, 3>(p, st);
+        if (p.fuse_add == 2) return launch_dma_pair(p, st);
+        if (p.fuse_add) return p.Cout_p <= 64 ? launch_dma_fused<64, 256, 3>(p, st) : launch_dma_fused<128, 128, 4>(p, st);
         switch (pick_tile(p)) {
         case T64x256:
             // two steps in flight and three workgroups per CU measured faster than three and two

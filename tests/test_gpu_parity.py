@@ -636,6 +636,35 @@ def test_residual_computed_by_a_second_convolution(isr):
     m.close()
 
 
+@pytest.mark.parametrize("copies,one_shift,tile", [(975, True, "128, 128"), (983, True, "256, 128"), (1967, True, "256, 128"), (983, False, "128, 128")])
+def test_convolution_pairs_in_launches_of_many_tiles(isr, builder, copies, one_shift, tile):
+    """Pairs of 256 channels a workgroup from 768 tiles of 128 pixels on, where results come in pairs; the last tile ragged.  A main
+    convolution of stride 2 and one that is a plain GEMM, K steps of both unequal: against one kernel per op, and two copies against the oracle."""
+    _say(f"convolution pairs, {copies} copies, {one_shift}")
+    if not one_shift:
+        builder(_ByChannel)
+    b = NetBuilder(rng=np.random.default_rng(66), in_shape=(3, 20, 20), num_classes=8)
+    ta = b.conv(b.tensor(3, 20, 20, 0, 74.0), 64, 3, 2, 1, True)
+    u = b.conv(b.conv(ta, 128, 1, 1, 0, True), 192, 3, 2, 1, True)
+    r = b.conv(u, 1024, 1, 1, 0, False)                                       # the residual, K = 192
+    t = b.add(b.conv(ta, 1024, 1, 2, 0, False, zp_out=-9), r, True)           # main: stride 2, K = 64
+    u = b.conv(t, 64, 1, 1, 0, True)
+    r = b.conv(t, 1024, 1, 1, 0, False, zp_out=5)                             # K = 1024
+    t = b.add(r, b.conv(u, 1024, 1, 1, 0, False), False)                      # main: K = 64
+    b.fc(b.conv(t, 16, 1, 1, 0, True), 8)
+    m = _load(isr, b.blob(), copies)
+    x = np.random.default_rng(67).integers(0, 256, size=(3, 20, 20)).astype(np.uint8)
+    isr.isr_profile(m, 1)
+    lg, am, cnt = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 3, copies)
+    pairs = {s["name"]: s["launches"] for s in isr.isr_profile_read(m) if ", 64, 2, 2, " in s["name"]}
+    assert sum(pairs.values()) == 2 and all(f"<{tile}, " in n for n in pairs), pairs
+    isr.isr_set_fusion(m, 0)
+    lg0, am0, cnt0 = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 3, copies)
+    m.close()
+    assert np.array_equal(lg, lg0) and np.array_equal(am, am0) and np.array_equal(cnt, cnt0)
+    assert np.array_equal(lg[:2], oracle.Model(b.blob()).mc(x, 64, 2, 1, 1, 3, 2)[0])
+
+
 def test_exact_halves_in_both_requantisations(isr):
     """Power-of-two multipliers make acc * M0 and the residual sum land on exact halves
     all the time (negative ones included), so the rounding's sign correction decides
