@@ -474,6 +474,12 @@ hipError_t launch_bottleneck(const BneckParams &p, hipStream_t st) {
     if (tiles > 0x7fffffffL || (long)p.B * p.H * p.W * (p.Cin_p > 64 ? p.Cin_p : 64) >= (1L << 31)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles), block(512);
     const int mode = p.tail ? (p.proj ? 2 : p.reduce ? 3 : 1) : 0;
+    // Resident workgroups that keep the weights pay from five tiles a CU on (seven with a projection, which has fewer operands to fetch ahead): 1400
+    // tiles of an identity block 59.0 -> 56.6 us, 840 tiles 38.8 -> 39.0, of a first block 54.5 -> 55.2, 2100 tiles 80.6 -> 76.6.  The forms with more
+    // constants read them again for each fragment: RQ_TOP at 2100 tiles 86.0 -> 88.9, at 9352 383 -> 365; RQ_TIE_FREE 123 -> 115, 468 -> 448.
+    const long many = !(p.rq & p.add_rq & RQ_PAIR) ? 2560 : p.proj ? 1792 : 1280;
+    if (((mode == 1 && p.Cin_p == 256) || (mode == 2 && p.Cout_p == 256)) && tiles >= many && (long)p.B * p.H * p.W * 256 < (1L << 31))
+        return launch_bottleneck_stream(p, (int)tiles, st);
     static const char *const names[4][2] = {{"bottleneck_kernel<head, false>", "bottleneck_kernel<head, true>"},
                                             {"bottleneck_kernel<block, false>", "bottleneck_kernel<block, true>"},
                                             {"bottleneck_kernel<block + projection, false>", "bottleneck_kernel<block + projection, true>"},

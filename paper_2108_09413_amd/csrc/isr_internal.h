@@ -450,6 +450,7 @@ bool narrow_short(const NarrowParams &p);   // a whole net of two convolutions, 
 hipError_t launch_narrow_chain(const NarrowParams &s16, const NarrowParams &s32, const NarrowParams &s64, hipStream_t st);
 bool basic_block_supported(int channels, int size);
 hipError_t launch_bottleneck(const BneckParams &p, hipStream_t st);
+hipError_t launch_bottleneck_stream(const BneckParams &p, int ntiles, hipStream_t st);   // blocks of 256 channels in launches of many tiles (bottleneck_stream.hip)
 bool bottleneck_supported(int cin_p, int cmid_p, int cout_p, int tail);
 hipError_t launch_bottleneck128(const BneckParams &p, hipStream_t st);
 bool expand_reduce_supported(const ConvParams &expand, const ConvParams &reduce);

@@ -53,12 +53,15 @@ def library_name(profiler_name: str) -> str:
     forms = r"<%s(?:, %s)?>" % (form, form)
     if re.match("proj_expand_reduce_kernel" + forms, n):
         return "proj_expand_reduce_kernel<256, 128, 512, 128>"     # block input, middle, block and next middle channels
-    if re.match("expand_reduce1024_kernel" + forms, n):
+    if re.match(r"expand_reduce1024_kernel<%s(?:, %s(?:, \d+)?)?>" % (form, form), n):
         return "expand_reduce_kernel<256, 1024, 256>"
     if re.match("expand_reduce256_kernel" + forms, n):
         return "expand_reduce_kernel<128, 512, 256>"
     if re.match("expand_reduce_kernel" + forms, n):
         return "expand_reduce_kernel<128, 512, 128>"               # middle, block and next middle channels
+    m = re.match(r"bottleneck_stream_kernel<(true|false), \d, \d>", n)
+    if m:
+        return "bottleneck_stream_kernel<%s>" % ("block + projection" if m.group(1) == "true" else "block")
     m = re.match(r"bottleneck_kernel<(\d), (true|false)>", n)
     if m:
         return "bottleneck_kernel<%s, %s>" % (MODES[m.group(1)], m.group(2))
@@ -86,7 +89,7 @@ def library_name(profiler_name: str) -> str:
 
 
 def is_conv(name: str) -> bool:
-    return name.startswith(("conv_dma_kernel", "conv_patch_kernel", "expand_reduce_kernel", "proj_expand_reduce_kernel", "bottleneck_kernel", "stem_pool_kernel", "fconv_kernel",
+    return name.startswith(("conv_dma_kernel", "conv_patch_kernel", "expand_reduce_kernel", "proj_expand_reduce_kernel", "bottleneck_kernel", "bottleneck_stream_kernel", "stem_pool_kernel", "fconv_kernel",
                             "fexpand_kernel", "fpatch_kernel", "fpatch16_kernel", "fstem_pool_kernel"))
 
 

@@ -537,6 +537,41 @@ def test_bottleneck_blocks_in_one_kernel(isr, shape):
     m.close()
 
 
+@pytest.mark.parametrize("shape,copies,layers,kernels", [
+    ((8, 28), 1793, None, (2, 1)),          # one tile an image, 256 workgroups with seven of them, one with an eighth
+    ((9, 32), 448, None, (2, 1)),           # four tiles an image, three of them nearly outside; seven tiles each
+    ((9, 32), 320, None, (2, 0)),           # five tiles each: identity blocks only
+    ((5, 40), 1281, "_ByChannel", (2, 1)), ((9, 32), 641, "_TopForm", (2, 1)), ((8, 28), 2560, "_Clamped", (2, 1)),
+    ((9, 32), 641, "_HalvesInAdds", (2, 1)), ((5, 40), 1280, "_HalvesByChannel", (2, 1))])
+def test_bottleneck_blocks_in_resident_workgroups(isr, builder, shape, copies, layers, kernels):
+    """Blocks of 256 channels in launches of many tiles, in each form of the requantisation, on images that leave tiles ragged in both
+    directions: against one kernel per op, and two copies against the oracle.  Logits that depend on every pixel."""
+    h, w = shape
+    _say(f"resident bottleneck blocks {h}x{w}, {copies} copies, {layers}")
+    if layers:
+        builder(globals()[layers])
+    b = NetBuilder(rng=np.random.default_rng(85), in_shape=(3, h, w), num_classes=6)
+    t = b.conv(b.tensor(3, h, w, 0, 74.0), 64, 3, 1, 1, True)
+    u = b.conv(b.conv(t, 64, 1, 1, 0, False, zp_out=-100), 64, 3, 1, 1, True)
+    r = b.conv(t, 256, 1, 1, 0, False, zp_out=5)
+    t = b.add(r, b.conv(u, 256, 1, 1, 0, False, zp_out=3), True)
+    for k in range(2):
+        u = b.conv(b.conv(t, 64, 1, 1, 0, True), 64, 3, 1, 1, False, zp_out=-20 * k)
+        t = b.add(t, b.conv(u, 256, 1, 1, 0, False, zp_out=k), k == 1)
+    b.fc(b.conv(t, 16, 1, 1, 0, True), 6)
+    m = _load(isr, b.blob(), copies)
+    x = np.random.default_rng(86).integers(0, 256, size=(3, h, w)).astype(np.uint8)
+    isr.isr_profile(m, 1)
+    lg, am, cnt = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 3, copies)
+    names = {s["name"]: s["launches"] for s in isr.isr_profile_read(m)}
+    assert (names.get("bottleneck_stream_kernel<block>", 0), names.get("bottleneck_stream_kernel<block + projection>", 0)) == kernels, names
+    isr.isr_set_fusion(m, 0)
+    lg0, am0, cnt0 = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 3, copies)
+    m.close()
+    assert np.array_equal(lg, lg0) and np.array_equal(am, am0) and np.array_equal(cnt, cnt0)
+    assert np.array_equal(lg[:2], oracle.Model(b.blob()).mc(x, 64, 2, 1, 1, 3, 2)[0])
+
+
 @pytest.mark.parametrize("cin", [192, 256, 320, 512])
 def test_bottleneck_heads_of_three_to_eight_k_steps(isr, cin):
     """The opening 1x1 and the 3x3 convolution (64 middle channels) in one kernel for wider inputs than a block's own: more K
