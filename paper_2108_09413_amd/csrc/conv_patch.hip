@@ -237,6 +237,9 @@ __global__ __launch_bounds__(patch_threads(BM, LOADS), MINB) void conv_patch_ker
     // passes the next step's barrier, issues its refill and reads the next step's first fragments BEFORE it issues
     // those four MFMAs, so the matrix pipe has work queued while the workgroup goes through barrier, refill and
     // the first fragment reads (measured +1 to +3 % over reading each sub-step's fragments right before its MFMAs).
+    // With one workgroup a CU, all four waves of a SIMD go through the same step, and the oldest would be done with it first: the fewer sub-steps a
+    // wave has behind it, the higher its priority (71.5 -> 69.4 us; with two workgroups a CU 84.4 -> 87.6, which keep the hardware's order).
+    static_assert(!EVERY || KS == 4, "three priorities and the one behind the barrier");
     static_assert(KS % 2 == 0, "register sets alternate");
     v4i fa[2][2], fb[2][2];
     auto read_fragments = [&](const int8_t *abase, const int8_t *bbase, const int (&brow)[2], int ksub, int slot) {
@@ -273,6 +276,9 @@ __global__ __launch_bounds__(patch_threads(BM, LOADS), MINB) void conv_patch_ker
         for (int ksub = 0; ksub < KS; ++ksub) {
             const int slot = ksub & 1;
             if (ksub + 1 < KS) {
+                if (EVERY && ksub == 0) __builtin_amdgcn_s_setprio(2);
+                if (EVERY && ksub == 1) __builtin_amdgcn_s_setprio(1);
+                if (EVERY && ksub == 2) __builtin_amdgcn_s_setprio(0);
                 read_fragments(abase, bbase, brow, ksub + 1, slot ^ 1);
             } else if (t + 1 < nk) {
                 if (LOADS != LOADERS) {
@@ -281,6 +287,7 @@ __global__ __launch_bounds__(patch_threads(BM, LOADS), MINB) void conv_patch_ker
                 }
                 lds_barrier();   // every wave's loads of step t + 1 landed; every wave is done reading step t
                 if (++tap == 9) { tap = 0; ++slice; }
+                if constexpr (EVERY) __builtin_amdgcn_s_setprio(3);
                 refill(t + 1, slice, tap);
                 tap_rows(tap, brow);
                 read_fragments(As[(t + 1) % NAB], Bs[slice & 1], brow, 0, slot ^ 1);

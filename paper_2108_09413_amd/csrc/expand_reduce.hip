@@ -255,6 +255,7 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
 
     // the y tile: projection of the block input (the residual), expand, add; 32 channels x 32 pixels per wave
     auto make = [&](int tile, int buf, int8_t *Yb) {
+        if constexpr (RQ == RQ_PAIR) __builtin_amdgcn_s_setprio(3);
         int l = lane;
         asm volatile("" : "+v"(l));   // per-lane values are recomputed per tile
         const int half = l >> 5, px1 = l & 31, oc = wave * 32 + half * 16;
@@ -283,6 +284,7 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
                 rq[gi] = (int)rq_pack<RQ>(q[0], q[1], q[2], q[3], Lp);
             }
         }
+        if constexpr (RQ == RQ_PAIR) __builtin_amdgcn_s_setprio(2);
         {
             v16i acc;
 #pragma unroll
@@ -297,6 +299,7 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
                 acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1[ks], fb[ks % 3], acc, 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if constexpr (RQ == RQ_PAIR) __builtin_amdgcn_s_setprio(1);
             v4i yv;
 #pragma unroll
             for (int gi = 0; gi < 4; ++gi) {
@@ -341,6 +344,10 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
     // One barrier a tile: between two of them the workgroup reduces a tile and makes the next, half of the waves of each SIMD in this order,
     // the others in the other, so that one half's MFMAs and LDS reads stand beside the other's arithmetic (two barriers, all waves in step:
     // 226 -> 219 us for 668 copies; expand_reduce256_kernel 200 -> 189).
+    // The fewer steps a wave has behind it, the higher its priority: in the hardware's order the oldest wave of a SIMD reaches the barrier
+    // long before the youngest, which then runs alone (214 -> 210 us; expand_reduce256_kernel 185 -> 183, expand_reduce1024_kernel 103 -> 100; in
+    // expand_reduce_kernel, whose CUs hold two workgroups, 149 -> 151, so not there).  In the pair form: in the others of this kernel the compiler
+    // would spill around them.
     if (tile < ntiles) make(tile, 0, Y[0]);
     int buf = 0;
     for (int it = 0; tile < ntiles; tile += G, ++it) {
@@ -360,8 +367,10 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
         if (tile + 3 * G < ntiles) issue_tile(tile + 3 * G, buf);
         if (wave >= 8) {
             if (more) make(tile + G, nbuf, Y[(it + 1) & 1]);
+            if constexpr (RQ == RQ_PAIR) __builtin_amdgcn_s_setprio(0);
             reduce(tile, Y[it & 1]);
         } else {
+            if constexpr (RQ == RQ_PAIR) __builtin_amdgcn_s_setprio(3);
             reduce(tile, Y[it & 1]);
             if (more) make(tile + G, nbuf, Y[(it + 1) & 1]);
         }
@@ -428,6 +437,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
 
     // expand + add into the tile of x: 32 channels x 32 pixels per wave
     auto expand = [&](int tile, int buf) {
+        __builtin_amdgcn_s_setprio(3);
         int l = lane;
         asm volatile("" : "+v"(l));   // per-lane values are recomputed per tile
         const int half = l >> 5, px1 = l & 31, oc = wave * 32 + half * 16;
@@ -448,6 +458,8 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
 #pragma unroll
         for (int gi = 0; gi < 4; ++gi) {
             __builtin_amdgcn_sched_barrier(0);
+            if (gi == 0) __builtin_amdgcn_s_setprio(2);
+            if (gi == 2) __builtin_amdgcn_s_setprio(1);
             const v4i mm = *(const v4i *)&prm1[1][oc + 4 * gi], ch = rq_chi4<RQ>(&prm1[2][oc + 4 * gi]), ss = *(const v4i *)&prm1[3][oc + 4 * gi];
             int q[4];
 #pragma unroll
@@ -516,8 +528,10 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
         if (tile + 3 * G < ntiles) issue_tile(tile + 3 * G, (buf + 3) % (XNB + 1));
         if (wave >= 8) {
             if (more) expand(tile + G, nbuf);
+            __builtin_amdgcn_s_setprio(0);
             reduce(tile, buf);
         } else {
+            __builtin_amdgcn_s_setprio(3);
             reduce(tile, buf);
             if (more) expand(tile + G, nbuf);
         }
@@ -633,6 +647,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
             int l = lane;
             asm volatile("" : "+v"(l));   // per-lane values are recomputed, loads from them are not hoisted out of the loop
             const int half = l >> 5, px1 = nf * 32 + (l & 31);
+            if (nf == 0) __builtin_amdgcn_s_setprio(3); else __builtin_amdgcn_s_setprio(1);
             if (more) issue_x(tile + G, buf ^ 1, 2 * nf);
             v16i acc[2];
 #pragma unroll
@@ -651,6 +666,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
             }
 #pragma unroll
             for (int fm = 0; fm < 2; ++fm) {
+                if (nf == 0) __builtin_amdgcn_s_setprio(2); else if (fm == 0) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
                 const int oc = wave * 64 + fm * 32 + half * 16;
                 int8_t *cell = xyb + px1 * DC + (((oc >> 4) ^ (px1 & 15)) << 4);
                 const v4i rv = *(const v4i *)cell;
@@ -694,6 +710,9 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
             for (int i = 0; i < FR - 1; ++i) fb[i] = operand(i);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
+                if (ks == 0) __builtin_amdgcn_s_setprio(3);
+                if (ks == 5) __builtin_amdgcn_s_setprio(2);
+                if (ks == 10) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
                     const int i = ks * NB + nb;
@@ -710,6 +729,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
         const int g = l >> 4, px2 = l & 15;
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {   // y in whole rows
+            if (j == 0) __builtin_amdgcn_s_setprio(0);
             const int px = ROWS * wave + j;
             const long n1 = (long)n0 + px;
             if (n1 < p.npix) *(v4i *)(p.y + n1 * DC + (uint32_t)l * 16) = *(const v4i *)(xyb + px * DC + ((l ^ (px & 15)) << 4));

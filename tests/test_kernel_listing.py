@@ -133,6 +133,18 @@ def test_expand_and_reduce_stores_are_what_the_waits_count(kernels):
     assert checked == 24
 
 
+def test_resident_bottleneck_stores_are_what_the_waits_count(kernels):
+    """bottleneck_stream_kernel waits until only the four stores behind the next tile's loads are left."""
+    checked = 0
+    for name, code in kernels.items():
+        if "bottleneck_stream_kernel" in name:
+            ops = [t.split()[0] for _, t, _ in code]
+            stores = [o for o in ops if "store" in o and not o.startswith("scratch_")]   # scratch only adds to what is waited for
+            assert sorted(stores) == ["buffer_store_dwordx2"] + 3 * ["buffer_store_dwordx4"], name
+            checked += 1
+    assert checked == 14
+
+
 def test_stage_kernels_keep_to_their_registers(code_objects):
     """The kernels of the nets on 32 x 32 images, whose rates rest on two to five workgroups a CU with everything in registers."""
     seen = 0
