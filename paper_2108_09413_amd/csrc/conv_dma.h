@@ -24,7 +24,8 @@ inline const char *conv_dma_name() {
 // FUSE: 0 plain, 1 residual add with the residual read from memory, 2 residual add with the
 // residual computed here by a second (1x1, stride 1) convolution.
 // WTM x WTN: output block of one wave (channels x pixels): 64 x 64 = 2 x 2 MFMA tiles, 128 x 64 = 4 x 2,
-// 128 x 128 = 4 x 4.  A larger block reads fewer operand bytes from LDS per multiply.
+// 128 x 128 = 4 x 4.  A larger block reads fewer operand bytes from LDS per multiply; smaller ones, 32 x 32 and 64 x 32, put more waves on a
+// CU that has one workgroup: a wave is held at each direct-to-LDS load that it issues, and more of them share those of a step.
 // RQ, RQA: form of the convolutions' requantisations and of the fused add (conv_device.h).
 template <int BM, int BN, int KB, int NST, int FUSE, int MINB, int RQ, int WTM = 64, int WTN = 64, int RQA = RQ>
 __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_kernel(const ConvParams p) {
@@ -39,7 +40,7 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64, MINB) void conv_dma_k
     constexpr int ACC = 16;
     constexpr int STAGE = (BM + BN) * KB;
     constexpr int KS = KB / 32;
-    static_assert(BM % WTM == 0 && BN % WTN == 0 && (WTM == 64 || WTM == 128) && (WTN == 64 || WTN == 128) && BM % RPP == 0 && BN % RPP == 0 && RPP % 32 == 0 && NST >= 2 &&
+    static_assert(BM % WTM == 0 && BN % WTN == 0 && (WTM == 32 || WTM == 64 || WTM == 128) && (WTN == 32 || WTN == 64 || WTN == 128) && BM % RPP == 0 && BN % RPP == 0 && RPP % 32 == 0 && NST >= 2 &&
                       NST <= 3 && (KB == 64 || KB == 128),
                   "tile shape");
 

@@ -343,13 +343,13 @@ static hipError_t launch_staged(const ConvParams &p, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int BM, int BN, int KB, int NST, int MINB>
+template <int BM, int BN, int KB, int NST, int MINB, int WTM = 64, int WTN = 64>
 static hipError_t launch_dma(const ConvParams &p, hipStream_t st) {
-    constexpr int NT = (BM / 64) * (BN / 64) * 64;
+    constexpr int NT = (BM / WTM) * (BN / WTN) * 64;
     dim3 grid((unsigned)(((p.npix + BN - 1) / BN) * ((p.Cout_p + BM - 1) / BM)));
-    set_kernel_name(conv_dma_name<BM, BN, KB, NST, 0, MINB, 64, 64>());
+    set_kernel_name(conv_dma_name<BM, BN, KB, NST, 0, MINB, WTM, WTN>());
     with_rq(p.rq, [&](auto rq) {
-        hipLaunchKernelGGL((conv_dma_kernel<BM, BN, KB, NST, 0, MINB, decltype(rq)::value>), grid, dim3(NT), 0, st, p);
+        hipLaunchKernelGGL((conv_dma_kernel<BM, BN, KB, NST, 0, MINB, decltype(rq)::value, WTM, WTN>), grid, dim3(NT), 0, st, p);
     });
     return hipGetLastError();
 }
@@ -475,11 +475,13 @@ hipError_t launch_conv(const ConvParams &p, hipStream_t st) {
             // shallow layers are epilogue-bound: two steps in flight suffice and a fourth
             // workgroup per CU hides more of the epilogue's memory latency
             if (!p.fuse_add && p.Kp < 1024 && !k128) return launch_dma<128, 128, 64, 2, 4>(p, st);
-            // one workgroup a CU has the LDS for three steps of 128 bytes
-            if (k128 && ((p.npix + 127) / 128) * ((p.Cout_p + 127) / 128) <= 256) return launch_dma<128, 128, 128, 3, 1>(p, st);
+            // one workgroup a CU has the LDS for three steps of 128 bytes, whose loads sixteen waves of 32 x 32 issue (four of 64 x 64 / eight of 64 x 32:
+            // the layers of 60 / 100 copies at 7 x 7 18.9 / 17.2 -> 16.7, 22.4 / 20.3 -> 19.7 us)
+            if (k128 && ((p.npix + 127) / 128) * ((p.Cout_p + 127) / 128) <= 256) return launch_dma<128, 128, 128, 3, 1, 32, 32>(p, st);
             return k128 ? launch_dma<128, 128, 128, 2, 2>(p, st) : launch_dma<128, 128, 64, 3, 3>(p, st);
         case T128x256:
-            return k128 ? launch_dma<128, 256, 128, 2, 1>(p, st) : launch_dma<128, 256, 64, 3, 2>(p, st);
+            // sixteen waves here too (eight: 60 / 100 / 150 copies at 14 x 14 15.0 / 21.3 / 22.5 -> 14.7 / 20.9 / 22.2 us)
+            return k128 ? launch_dma<128, 256, 128, 2, 1, 64, 32>(p, st) : launch_dma<128, 256, 64, 3, 2>(p, st);
         case T256x128:
             return k128 ? launch_dma<256, 128, 128, 2, 1>(p, st) : launch_dma<256, 128, 64, 3, 2>(p, st);
         case T256x256: return k128 ? launch_dma<256, 256, 128, 2, 1>(p, st) : launch_dma<256, 256, 64, 3, 1>(p, st);
