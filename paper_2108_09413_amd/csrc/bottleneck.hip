@@ -22,6 +22,7 @@
 //      x at the wave's own channels, input channels of one K step of step 1 -- was
 //      copied from that step's LDS stage into registers: x is read from memory once.
 // x is read once (plus halo, mostly cache hits), t1 and t2 never leave the CU.
+// Blocks of 256 channels in launches of many tiles run in resident workgroups (bottleneck_stream.hip; the rule is in launch_bottleneck).
 //
 // Bounds, 668 images of 56 x 56 x 256 (identity block): memory 1.07 GB = 210 us at the rate of a large copy, issue of the
 // requantisation and its data movement about 180 us, matrix unit 75 us, in phases that barriers separate.
