@@ -365,6 +365,7 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
         }
         lds_barrier();   // this tile's y is complete, the next tile's operands have landed, everybody is done with the tile before
         if (tile + 3 * G < ntiles) issue_tile(tile + 3 * G, buf);
+        asm volatile("" ::: "memory");   // the stores that the wait counts come behind these loads
         if (wave >= 8) {
             if (more) make(tile + G, nbuf, Y[(it + 1) & 1]);
             if constexpr (RQ == RQ_PAIR) __builtin_amdgcn_s_setprio(0);
@@ -526,6 +527,7 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce256_kernel(const XrParam
         }
         lds_barrier();   // this tile's y is complete, the next tile's operands have landed, everybody is done with the tile before
         if (tile + 3 * G < ntiles) issue_tile(tile + 3 * G, (buf + 3) % (XNB + 1));
+        asm volatile("" ::: "memory");   // the stores that the wait counts come behind these loads
         if (wave >= 8) {
             if (more) expand(tile + G, nbuf);
             __builtin_amdgcn_s_setprio(0);

@@ -145,6 +145,61 @@ def test_resident_bottleneck_stores_are_what_the_waits_count(kernels):
     assert checked == 14
 
 
+def _is_load_into_lds(text):
+    return "load" in text.split()[0] and ("_lds_" in text or text.endswith(" lds"))
+
+
+def _loads_behind_stores(code):
+    """Addresses of the loads into LDS that some path reaches with a store issued since the last barrier."""
+    index = {a: i for i, (a, _, _) in enumerate(code)}
+    seen, todo, bad = set(), [(0, False)], set()
+    while todo:
+        i, stored = todo.pop()
+        while i < len(code) and (i, stored) not in seen:
+            seen.add((i, stored))
+            address, text, target = code[i]
+            op = text.split()[0]
+            if _is_load_into_lds(text):
+                if stored:
+                    bad.add(address)
+            elif op.startswith(("global_store", "buffer_store")):
+                stored = True
+            elif op == "s_barrier":
+                stored = False
+            elif op == "s_endpgm":
+                break
+            if target is not None and op.startswith("s_cbranch"):
+                todo.append((index[target], stored))
+            i = index[target] if op == "s_branch" else i + 1
+    return bad
+
+
+def test_a_path_with_a_load_behind_a_store_is_found():
+    def code(*ops):
+        return [(4 * i, op, 12 if op.startswith("s_cbranch") else None) for i, op in enumerate(ops + ("s_endpgm",))]
+    store, load, other = "global_store_dword v0, v1, s[0:1]", "global_load_lds_dwordx4 v[0:1], off", "buffer_load_dwordx4 v0, s[0:3], 0 offen lds"
+    assert _loads_behind_stores(code(store, load)) == {4} and _loads_behind_stores(code(store, "s_cbranch_scc1 1", "s_barrier", other)) == {12}
+    assert _loads_behind_stores(code(store, "s_barrier", load, other, store)) == set()
+
+
+def test_loads_into_lds_stand_in_front_of_the_stores_that_the_waits_count(kernels):
+    """The kernels that wait until only the stores behind a tile's loads are left: in an interval between two barriers the loads come first.
+    (expand_reduce1024_kernel passes its first barrier in all rounds but the first, which has no stores behind it: there what follows the last
+    barrier is looked at.)"""
+    checked = 0
+    for name, code in kernels.items():
+        if re.search("proj_expand_reduce_kernel|expand_reduce256_kernel|bottleneck_stream_kernel", name):
+            assert sum(_is_load_into_lds(t) for _, t, _ in code) >= 3 and not _loads_behind_stores(code), name
+            checked += 1
+        elif "expand_reduce1024_kernel" in name:
+            texts = [t for _, t, _ in code]
+            tail = texts[len(texts) - texts[::-1].index("s_barrier"):]
+            loads, stores = [i for i, t in enumerate(tail) if _is_load_into_lds(t)], [i for i, t in enumerate(tail) if t.startswith("global_store")]
+            assert loads and max(loads) < min(stores), name
+            checked += 1
+    assert checked == 38
+
+
 def test_stage_kernels_keep_to_their_registers(code_objects):
     """The kernels of the nets on 32 x 32 images, whose rates rest on two to five workgroups a CU with everything in registers."""
     seen = 0
