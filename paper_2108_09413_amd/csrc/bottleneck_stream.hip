@@ -49,6 +49,11 @@ template <bool PROJ, int RQ, int RQA>
 __global__ __launch_bounds__(NT, 4) void bottleneck_stream_kernel(const BneckParams p, const int ntiles) {
     constexpr int CIN = PROJ ? 64 : 256, COUT = 256, KS1 = CIN / 64, XB = NROWS * CIN;
     constexpr int NXB = PROJ ? 3 : 1;   // the projection reads the x of the tile before, next to this one's and the next one's
+    // Per-lane positions are computed again for each tile where registers are short: kept, they go to scratch, and a reload waits for the stores and
+    // loads in flight.  us of a launch, first block: RQ_ANY 9352 / 5600 tiles 457 / 266 -> 448 / 256, RQ_TIE_FREE 388 / 226 -> 385 / 223, RQ_TOP
+    // 2800 tiles 95.9 -> 94.5, at 9352 the same; identity block, RQ_TIE_FREE 345 / 206 -> 338 / 199.  The identity blocks of the forms with exact
+    // halves keep 12 to 20 bytes a lane there, which cost nothing that could be measured (RQ_ANY 1 % slower with the places computed again).
+    constexpr bool RECOMPUTE = !PROJ || RQ != RQ_PAIR, RECOMPUTE_FIND = PROJ ? RQ != RQ_PAIR : RQ == RQ_TIE_FREE;
     __shared__ __attribute__((aligned(256))) int8_t X[NXB][XB];
     __shared__ __attribute__((aligned(16))) int8_t T1[(TH + 2) * TROW];      // [halo row][column][64 channels]
     __shared__ __attribute__((aligned(16))) int8_t T2[NPX * 64];             // [row half][fragment][pixel of the group][64 channels], 16-byte chunks swizzled
@@ -83,7 +88,7 @@ __global__ __launch_bounds__(NT, 4) void bottleneck_stream_kernel(const BneckPar
     auto issue = [&](int abuf, int buf) {
         constexpr int CH = CIN / 16, RPP = 512 / CH, PASSES = (NROWS + RPP - 1) / RPP;   // chunks a row, rows a pass
         int i = cb * 64 + lane;
-        if constexpr (!PROJ) asm volatile("" : "+v"(i));   // recomputed per tile: registers are short
+        if constexpr (RECOMPUTE) asm volatile("" : "+v"(i));
         const int r0 = i / CH, c = (i % CH) ^ (PROJ ? swz<4>(r0) : r0 & 15);
 #pragma unroll
         for (int j = 0; j < PASSES; ++j)
@@ -186,7 +191,7 @@ __global__ __launch_bounds__(NT, 4) void bottleneck_stream_kernel(const BneckPar
     v2i resid[PROJ ? 1 : NP_FR];
     auto first_conv = [&](int abuf, int buf) {
         int l = lane;
-        if constexpr (!PROJ) asm volatile("" : "+v"(l));
+        if constexpr (RECOMPUTE) asm volatile("" : "+v"(l));
         const int g = l >> 4, n = l & 15, c = cg * 16 + 4 * g, h0 = pq * 80 + n;
         const v4i b4 = *(const v4i *)&prm[0][0][c];
         const int8_t *xb = X[buf] + h0 * CIN + (PROJ ? (g ^ swz<4>(n)) << 4 : 0);
@@ -217,7 +222,7 @@ __global__ __launch_bounds__(NT, 4) void bottleneck_stream_kernel(const BneckPar
     auto second_conv = [&]() {
         if (wave >= 2 * NP_FR) return;   // wave-uniform
         int l = lane;
-        if constexpr (!PROJ) asm volatile("" : "+v"(l));
+        if constexpr (RECOMPUTE) asm volatile("" : "+v"(l));
         const int half = l >> 5, l32 = l & 31, c16 = wm * 32 + 16 * half;
         const int8_t *const t1_tap = T1 + (l32 >> 2) * TROW + (4 * f2 + (l32 & 3)) * 64 + half * 16, *const w2_row = W2 + ((wm * 32 + l32) * W2_CHUNKS + half) * 16;
         v16i acc;
@@ -327,7 +332,11 @@ __global__ __launch_bounds__(NT, 4) void bottleneck_stream_kernel(const BneckPar
         lds_barrier();   // x has landed; everybody is done with t1 and with the last t2
         const int nabuf = abuf == 2 ? 0 : abuf + 1, pabuf = abuf == 0 ? 2 : abuf - 1;
         if (it > 0) store_t2();
-        if (more && wave >= 11) find(id + G, nabuf, tid - 11 * 64);
+        if (more && wave >= 11) {
+            int l = lane;
+            if constexpr (RECOMPUTE_FIND) asm volatile("" : "+v"(l));
+            find(id + G, nabuf, RECOMPUTE_FIND ? (wave - 11) * 64 + l : tid - 11 * 64);
+        }
         v2i rnew[PROJ ? 1 : NP_FR];
         if (have) {
             __builtin_amdgcn_s_setprio(0);

@@ -200,6 +200,13 @@ def test_loads_into_lds_stand_in_front_of_the_stores_that_the_waits_count(kernel
     assert checked == 38
 
 
+def test_resident_bottleneck_blocks_keep_to_their_registers(kernels):
+    """A reload from scratch waits for the stores and loads in flight: first blocks have none, identity blocks only next to exact halves."""
+    scratch = {name: any(t.startswith("scratch_") for _, t, _ in code) for name, code in kernels.items() if "bottleneck_stream_kernel" in name}
+    assert len(scratch) == 14
+    assert not [name for name, used in scratch.items() if used and not re.search(r"ILb0ELi\d+ELi0E", name)]
+
+
 def test_stage_kernels_keep_to_their_registers(code_objects):
     """The kernels of the nets on 32 x 32 images, whose rates rest on two to five workgroups a CU with everything in registers."""
     seen = 0
