@@ -475,11 +475,23 @@ hipError_t launch_bottleneck(const BneckParams &p, hipStream_t st) {
     if (tiles > 0x7fffffffL || (long)p.B * p.H * p.W * (p.Cin_p > 64 ? p.Cin_p : 64) >= (1L << 31)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles), block(512);
     const int mode = p.tail ? (p.proj ? 2 : p.reduce ? 3 : 1) : 0;
-    // Resident workgroups that keep the weights pay from five tiles a CU on (seven with a projection, which has fewer operands to fetch ahead): 1400
-    // tiles of an identity block 59.0 -> 56.6 us, 840 tiles 38.8 -> 39.0, of a first block 54.5 -> 55.2, 2100 tiles 80.6 -> 76.6.  The forms with more
-    // constants read them again for each fragment: RQ_TOP at 2100 tiles 86.0 -> 88.9, at 9352 383 -> 365; RQ_TIE_FREE 123 -> 115, 468 -> 448.
-    const long many = !(p.rq & p.add_rq & RQ_PAIR) ? 2560 : p.proj ? 1792 : 1280;
-    if (((mode == 1 && p.Cin_p == 256) || (mode == 2 && p.Cout_p == 256)) && tiles >= many && (long)p.B * p.H * p.W * 256 < (1L << 31))
+    // Resident workgroups keep the weights, but their time goes in rounds of 256 tiles, that of this file's kernel with the tiles.  The lines lie where a
+    // round just begun costs no more, or hardly.  us, this file's / resident, at 5.03, 6.02, 8.04, 10.01, 12.03, 16.02 and 36.5 rounds:
+    //   identity block  RQ_PAIR      55.0/53.4  63.1/59.4  77.7/72.1    97.7/84.9    114/101  149/129  329/288
+    //                   RQ_TOP       55.5/55.0  64.2/62.0  79.3/75.3    100/88.4     114/103  149/131  310/279
+    //                   RQ_TIE_FREE  64.5/61.4  76.2/69.0  92.7/85.5    116/99.7     135/117  175/153  393/338
+    //                   RQ_ANY       71.8/69.1  83.1/76.8  108/98.9     128/116      149/135  191/175  433/390
+    //                   RQ_TOP_TIES  64.4/64.9  74.5/72.3  94.8/92.1    113/108      130/126  167/162  371/357
+    //   first block     RQ_PAIR      48.6/49.7  56.6/56.2  72.6/68.8    85.3/81.7    101/95   134/124  319/278
+    //                   RQ_TIE_FREE  67.3/64.8  77.2/74.1  98.8/93.1    119/112      139/131  182/171  426/385
+    //                   RQ_ANY       76.6/75.9  88.6/86.4  116/110      136/131      161/155  207/196  484/448
+    //                   RQ_TOP_TIES  69.2/69.8  79.7/79.6  101.5/101.4  121/120      145/142  187/180  425/411
+    //                   RQ_TOP       52.5/56.4  61.2/63.2  77.0/78.2    90.2/93.1    107/109  140/140  322/307
+    //                     (an add with exact halves: 57.0/60.2, 82.9/84.6, 97.8/100, 116/119, 153/152, 347/335)
+    // (at 3.3 rounds 39.0/39.1, 39.2/40.6, 46.6/45.1, 50.7/50.2, 46.1/47.2; 37.3/38.1, 48.9/47.5, 54.7/55.0, 49.8/50.4, 39.0/42.3)
+    const int form = p.rq & p.add_rq & RQ_PAIR ? (int)RQ_PAIR : p.rq & ~RQ_PAIR;
+    const int rounds = p.proj ? (form == RQ_TOP ? 16 : form == RQ_TOP_TIES ? 9 : 6) : form == RQ_TOP_TIES ? 6 : 5;
+    if (((mode == 1 && p.Cin_p == 256) || (mode == 2 && p.Cout_p == 256)) && tiles >= 256 * rounds && (long)p.B * p.H * p.W * 256 < (1L << 31))
         return launch_bottleneck_stream(p, (int)tiles, st);
     static const char *const names[4][2] = {{"bottleneck_kernel<head, false>", "bottleneck_kernel<head, true>"},
                                             {"bottleneck_kernel<block, false>", "bottleneck_kernel<block, true>"},

@@ -541,8 +541,14 @@ def test_bottleneck_blocks_in_one_kernel(isr, shape):
     ((8, 28), 1793, None, (2, 1)),          # one tile an image, 256 workgroups with seven of them, one with an eighth
     ((9, 32), 448, None, (2, 1)),           # four tiles an image, three of them nearly outside; seven tiles each
     ((9, 32), 320, None, (2, 0)),           # five tiles each: identity blocks only
-    ((5, 40), 1281, "_ByChannel", (2, 1)), ((9, 32), 641, "_TopForm", (2, 1)), ((8, 28), 2560, "_Clamped", (2, 1)),
-    ((9, 32), 641, "_HalvesInAdds", (2, 1)), ((5, 40), 1280, "_HalvesByChannel", (2, 1))])
+    ((8, 28), 1279, None, (0, 0)), ((8, 28), 1535, None, (2, 0)),
+    # first blocks in the top-byte form from sixteen rounds of 256 tiles on, the others earlier
+    ((5, 40), 1281, "_ByChannel", (2, 0)), ((5, 40), 2047, "_HalvesByChannel", (2, 0)),
+    ((5, 40), 2049, "_ByChannel", (2, 1)), ((9, 32), 1025, "_TopForm", (2, 1)), ((9, 32), 1025, "_HalvesInAdds", (2, 1)), ((5, 40), 2048, "_HalvesByChannel", (2, 1)),
+    ((8, 28), 1279, "_Clamped", (0, 0)), ((8, 28), 1281, "_Clamped", (2, 0)), ((9, 32), 385, "_Clamped", (2, 1)), ((8, 28), 2560, "_Clamped", (2, 1)),
+    # exact halves in the convolutions, next to clamps of -128 and others
+    ((8, 28), 1281, "_HalvesInBoth", (0, 0)), ((9, 32), 385, "_HalvesInBoth", (2, 0)), ((5, 40), 1153, "_HalvesInBoth", (2, 1)),
+    ((8, 28), 1281, "_HalvesInBothClamped", (2, 0)), ((5, 40), 769, "_HalvesInBothClamped", (2, 1))])
 def test_bottleneck_blocks_in_resident_workgroups(isr, builder, shape, copies, layers, kernels):
     """Blocks of 256 channels in launches of many tiles, in each form of the requantisation, on images that leave tiles ragged in both
     directions: against one kernel per op, and two copies against the oracle.  Logits that depend on every pixel."""
@@ -916,6 +922,10 @@ class _HalvesInBoth(_HalvesInAdds):
         if not relu and m0 is None:
             m0 = np.full(cout, 3 << 29, dtype=np.int64)
         return super().conv(tin, cout, k, stride, pad, relu, m0=m0, **kw)
+
+
+class _HalvesInBothClamped(_HalvesInBoth, _Clamped):
+    """And clamps above -128: no short form anywhere."""
 
 
 class _HalvesByChannel(_HalvesInAdds, _ByChannel):
