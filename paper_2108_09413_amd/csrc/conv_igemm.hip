@@ -480,8 +480,10 @@ hipError_t launch_conv(const ConvParams &p, hipStream_t st) {
             if (k128 && ((p.npix + 127) / 128) * ((p.Cout_p + 127) / 128) <= 256) return launch_dma<128, 128, 128, 3, 1, 32, 32>(p, st);
             return k128 ? launch_dma<128, 128, 128, 2, 2>(p, st) : launch_dma<128, 128, 64, 3, 3>(p, st);
         case T128x256:
-            // sixteen waves here too (eight: 60 / 100 / 150 copies at 14 x 14 15.0 / 21.3 / 22.5 -> 14.7 / 20.9 / 22.2 us)
-            return k128 ? launch_dma<128, 256, 128, 2, 1, 64, 32>(p, st) : launch_dma<128, 256, 64, 3, 2>(p, st);
+            // sixteen waves here too (eight: 60 / 100 / 150 copies at 14 x 14 15.0 / 21.3 / 22.5 -> 14.7 / 20.9 / 22.2 us); in launches of several rounds,
+            // eight (sixteen: 642 to 766 tiles of 256 channels at 14 x 14 57.8 -> 58.4 us and 60.5 -> 61.7)
+            if (k128 && ((p.npix + 255) / 256) * ((p.Cout_p + 127) / 128) <= 256) return launch_dma<128, 256, 128, 2, 1, 64, 32>(p, st);
+            return k128 ? launch_dma<128, 256, 128, 2, 1>(p, st) : launch_dma<128, 256, 64, 3, 2>(p, st);
         case T256x128:
             return k128 ? launch_dma<256, 128, 128, 2, 1>(p, st) : launch_dma<256, 128, 64, 3, 2>(p, st);
         case T256x256: return k128 ? launch_dma<256, 256, 128, 2, 1>(p, st) : launch_dma<256, 256, 64, 3, 1>(p, st);

@@ -1222,6 +1222,34 @@ def test_every_conv_tile_against_the_oracle(isr, tile):
         _check_all_tensors(isr, blob, x, 64)
 
 
+@pytest.mark.parametrize("copies,kernel,layers", [
+    (3, "128, 128, 128, 3, 0, 1, 32x32", None), (819, "128, 128, 128, 3, 0, 1, 32x32", "_HalvesInBoth"), (819, "128, 128, 128, 3, 0, 1, 32x32", "_ByChannel"),
+    (820, "128, 256, 128, 2, 0, 1, 64x32", None), (1638, "128, 256, 128, 2, 0, 1, 64x32", "_ByChannel"), (1638, "128, 256, 128, 2, 0, 1, 64x32", "_HalvesInBoth"),
+    (820, "128, 256, 128, 2, 0, 1, 64x32", "_Clamped"), (4097, "128, 256, 128, 2, 0, 1, 64x64", None), (4097, "128, 256, 128, 2, 0, 1, 64x64", "_Clamped")])
+def test_deep_layers_in_launches_of_few_and_many_tiles(isr, builder, copies, kernel, layers):
+    """1024 -> 256 channels on 5x4 maps: sixteen waves a workgroup where all tiles run at once (at most 256 of them), the last one ragged, eight in
+    launches of several rounds.  Logits that depend on every pixel: against tiles of 256 x 256, and a few copies against the oracle."""
+    _say(f"deep layers, {copies} copies, {layers}")
+    if layers:
+        builder(globals()[layers])
+    b = NetBuilder(rng=np.random.default_rng(68), in_shape=(3, 5, 4), num_classes=6)
+    t = b.conv(b.conv(b.tensor(3, 5, 4, 0, 74.0), 64, 3, 1, 1, True), 1024, 1, 1, 0, True)
+    b.fc(b.conv(b.conv(t, 256, 1, 1, 0, False, zp_out=-30), 16, 1, 1, 0, True), 6)
+    m = _load(isr, b.blob(), copies)
+    x = np.random.default_rng(69).integers(0, 256, size=(3, 5, 4)).astype(np.uint8)
+    isr.isr_profile(m, 1)
+    lg, am, cnt = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 3, copies)
+    names = {s["name"]: s["launches"] for s in isr.isr_profile_read(m)}
+    assert names.get(f"conv_dma_kernel<{kernel}>") == 1, names
+    isr.isr_set_conv_tile(m, 4)
+    lg0, am0, cnt0 = isr.isr_debug_forward(m, x, 64, 2, 1, 1, 3, copies)
+    m.close()
+    assert np.array_equal(lg, lg0) and np.array_equal(am, am0) and np.array_equal(cnt, cnt0)
+    picks = sorted({0, 1, copies // 2, copies - 2, copies - 1})
+    olg, oam = _oracle_at(oracle.Model(b.blob()), x, 64, 2, 1, 1, [3 + i for i in picks])
+    assert np.array_equal(lg[picks], olg) and np.array_equal(am[picks], oam)
+
+
 @pytest.mark.parametrize("in_shape,stride,copies", [((28, 28), 2, 37), ((28, 28), 4, 150), ((28, 28), 1, 11), ((12, 20), 2, 61),
                                                     ((36, 124), 4, 13), ((10, 4), 2, 333)])
 def test_3x3_layers_with_staged_pixel_rows_against_the_oracle(isr, in_shape, stride, copies):
