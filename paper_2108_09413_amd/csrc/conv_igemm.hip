@@ -370,15 +370,20 @@ static hipError_t launch_dma_pair(const ConvParams &p, hipStream_t st) {
 }
 
 // 256 channels a workgroup, two workgroups of eight waves a CU, move three quarters of the bytes of 128 x 128 tiles and set up half as many
-// tiles; with less than one and a half rounds of them the smaller ones, three a CU, fill the CUs better.  us of the pairs at
-// 14 x 14 (512 and 256 into 1024 channels) and 7 x 7 (1024 and 512 into 2048), 128 x 128 / 256 x 128:
-//   copies    100          125          200          250          334          668
-//   14 x 14   28.7 / 30.9  31.8 / 31.8  48.6 / 46.1  60.2 / 56.9  79.8 / 78.8  161 / 160 (another card 185 / 178)
-//   7 x 7     26.3 / 28.9  29.5 / 29.8  46.8 / 48.3  54.1 / 50.9  70.9 / 63.8  140 / 127
+// tiles; with less than one and a half rounds of them the smaller ones, three a CU, fill the CUs better, and so they do where the last 256 tiles
+// leave many CUs idle: what a tile gains grows with its K steps.  us of the pairs at 14 x 14 (512 and 256 into 1024 channels, 12 steps) and 7 x 7
+// (1024 and 512 into 2048, 24 steps), 128 x 128 / 256 x 128:
+//   14 x 14, tiles of 256 x 128   616    768    860    920    1024   1032   1124   1164   1288   1412   1532   1840   2048   2328   3064   4092
+//                                 31.2   34.2   37.5   41.4   42.5   47.0   47.3   49.2   52.2   57.0   60.4   73.1   82.0   91.7   118    158
+//                                 33.7   34.5   39.2   39.9   41.4   48.7   48.6   48.3   54.0   56.0   58.4   75.2   81.6   93.7   116    160
+//   7 x 7                         616    768    784    832    864    920    1024   1032   1104   1168   1288   1536   1720   2048
+//                                 48.7   54.3   57.9   59.6   61.5   67.0   70.9   77.8   78.8   82.2   91.3   102    117    139
+//                                 51.0   52.8   60.1   60.2   60.3   60.9   64.3   78.7   78.3   79.0   88.5   93.7   108    124
 // (668 copies, 128 x 256: 190 and 142, 256 x 256: 198 and 147, with three buffers 151 and 146 at 7 x 7)
 static hipError_t launch_dma_pair(const ConvParams &p, hipStream_t st) {
     if (p.Cout_p <= 64) return launch_dma_pair<64, 256, 3>(p, st);
-    const bool wide = p.Cout_p % 256 == 0 && ((long)p.npix + 127) / 128 * (p.Cout_p / 256) >= 768 && (p.rq & p.rq2 & p.add_rq & RQ_PAIR);
+    const long tiles = ((long)p.npix + 127) / 128 * (p.Cout_p / 256), idle = (256 - tiles % 256) % 256;
+    const bool wide = p.Cout_p % 256 == 0 && tiles >= 768 && idle * 90 <= tiles * ((p.Kp + p.Cin2_p) / 64) && (p.rq & p.rq2 & p.add_rq & RQ_PAIR);
     return wide ? launch_dma_pair<256, 128, 4, true>(p, st) : launch_dma_pair<128, 128, 3>(p, st);
 }
 
