@@ -833,7 +833,7 @@ hipError_t launch_expand_reduce(const XrParams &p, hipStream_t st) {
         const bool narrow = 15 + 107 * wide_rounds > 67 * rounds;
         const int tiles = narrow ? ntiles : wide;
         const dim3 grid((unsigned)(tiles < 256 ? tiles : 256));
-        set_kernel_name("expand_reduce_kernel<256, 1024, 256>");
+        set_kernel_name(narrow ? "expand_reduce_kernel<256, 1024, 256, 32 pixels>" : "expand_reduce_kernel<256, 1024, 256, 64 pixels>");
         with_tie_free_rq(p, [&](auto rq, auto rqa) {
             if (narrow) hipLaunchKernelGGL((expand_reduce1024_kernel<decltype(rq)::value, decltype(rqa)::value, 32>), grid, dim3(XNT2), 0, st, p);
             else hipLaunchKernelGGL((expand_reduce1024_kernel<decltype(rq)::value, decltype(rqa)::value, 64>), grid, dim3(XNT2), 0, st, p);

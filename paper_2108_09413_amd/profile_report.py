@@ -53,8 +53,9 @@ def library_name(profiler_name: str) -> str:
     forms = r"<%s(?:, %s)?>" % (form, form)
     if re.match("proj_expand_reduce_kernel" + forms, n):
         return "proj_expand_reduce_kernel<256, 128, 512, 128>"     # block input, middle, block and next middle channels
-    if re.match(r"expand_reduce1024_kernel<%s(?:, %s(?:, \d+)?)?>" % (form, form), n):
-        return "expand_reduce_kernel<256, 1024, 256>"
+    m = re.match(r"expand_reduce1024_kernel<%s(?:, %s(?:, (\d+))?)?>" % (form, form), n)
+    if m:
+        return "expand_reduce_kernel<256, 1024, 256%s>" % (", %s pixels" % m.group(1) if m.group(1) else "")
     if re.match("expand_reduce256_kernel" + forms, n):
         return "expand_reduce_kernel<128, 512, 256>"
     if re.match("expand_reduce_kernel" + forms, n):

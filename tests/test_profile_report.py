@@ -28,7 +28,7 @@ def test_profiler_names_map_to_the_librarys_instance_names():
     assert f("void isr::(anonymous namespace)::bottleneck_kernel<2, true>(isr::BneckParams)") == \
         "bottleneck_kernel<block + projection, true>"
     assert f("void isr::(anonymous namespace)::bottleneck_stream_kernel<true, 8, 8>(isr::BneckParams, int)") == "bottleneck_stream_kernel<block + projection>"
-    assert f("void isr::(anonymous namespace)::expand_reduce1024_kernel<8, 8, 64>(isr::XrParams)") == "expand_reduce_kernel<256, 1024, 256>"
+    assert f("void isr::(anonymous namespace)::expand_reduce1024_kernel<8, 8, 64>(isr::XrParams)") == "expand_reduce_kernel<256, 1024, 256, 64 pixels>"
     assert f("void isr::(anonymous namespace)::fconv_kernel<2, 2, 2, 2>(isr::FConvParams)") == "fconv_kernel<128 x 128>"
     assert f("isr::(anonymous namespace)::stem_pool_kernel(isr::StemPoolParams)") == "stem_pool_kernel (+noise)"
     assert f("isr::gap_kernel(isr::GapParams)") == "gap_kernel"
