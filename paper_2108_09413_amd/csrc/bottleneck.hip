@@ -39,7 +39,6 @@ namespace isr {
 
 namespace {
 
-typedef int v4acc __attribute__((ext_vector_type(4)));
 template <int N>
 using Frag = std::integral_constant<int, N>;
 

@@ -24,7 +24,6 @@ namespace isr {
 
 namespace {
 
-typedef int v4acc __attribute__((ext_vector_type(4)));
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
@@ -37,13 +36,6 @@ constexpr int NT = 1024;
 constexpr uint32_t OUTSIDE = 1u << 23;                // tensors are below 2 GiB: at 256 bytes a pixel an index is smaller
 constexpr int TPAD = 144, TROW = HW * 64 + TPAD;      // a row of t1: its 4 x 4 pixels lie in different banks without a swizzle, so that taps are immediate offsets
 constexpr int W2_CHUNKS = 37;                        // 16-byte chunks per 3x3 weight row: 36 + 1 pad (bank spread)
-
-// four channels' addends of the requantisation (one value for a whole layer where the form has one)
-template <int RQ>
-__device__ __forceinline__ v4i rq_chi4(const int *c) {
-    if constexpr (rq_chi_at<RQ>(1) == 0) return v4i{c[0], c[0], c[0], c[0]};
-    else return *(const v4i *)c;
-}
 
 template <bool PROJ, int RQ, int RQA>
 __global__ __launch_bounds__(NT, 4) void bottleneck_stream_kernel(const BneckParams p, const int ntiles) {

@@ -10,6 +10,7 @@
 namespace isr {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v4acc __attribute__((ext_vector_type(4)));   // result of a 16x16 MFMA
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 // 16-byte chunk swizzle inside an LDS row of CPR chunks (64 or 128 bytes): spreads equal chunk indices of
@@ -119,6 +120,12 @@ __device__ __forceinline__ int rq_sh(int shm1) { return rq_is_top(RQ) ? 1 << (24
 // index of channel i's addend
 template <int RQ>
 __device__ __forceinline__ constexpr int rq_chi_at(int i) { return rq_is_top(RQ) || RQ == RQ_PAIR ? 0 : i; }
+// four channels' addends (one value for a whole layer where the form has one)
+template <int RQ>
+__device__ __forceinline__ v4i rq_chi4(const int *c) {
+    if constexpr (rq_chi_at<RQ>(1) == 0) return v4i{c[0], c[0], c[0], c[0]};
+    else return *(const v4i *)c;
+}
 
 // RQ_PAIR: a layer's addend and shift, in scalar registers; the other forms have theirs per channel.
 struct RqLayer {

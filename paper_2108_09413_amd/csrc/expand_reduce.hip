@@ -29,14 +29,6 @@ namespace {
 
 constexpr int XK1 = 128, XC = 512, XN2 = 128, XPX = 32, XNW = 8, XNT = XNW * 64;
 constexpr int XNB = 3;   // tile buffers: loads run two tiles ahead
-typedef int v4acc __attribute__((ext_vector_type(4)));
-
-// four channels' addends of the requantisation (one value for a whole layer where the form has one)
-template <int RQ>
-__device__ __forceinline__ v4i rq_chi4(const int *c) {
-    if constexpr (rq_chi_at<RQ>(1) == 0) return v4i{c[0], c[0], c[0], c[0]};
-    else return *(const v4i *)c;
-}
 
 template <int RQ, int RQA>
 __global__ __launch_bounds__(XNT, 4) void expand_reduce_kernel(const XrParams p) {

@@ -38,8 +38,6 @@ namespace isr {
 
 namespace {
 
-typedef int v4acc __attribute__((ext_vector_type(4)));
-
 // byte offset of a chunk of the pixel at padded (y, x).  STRIDED: the layout of x for the stride-2 reads of the tail, where
 // all rows of a read have the same parity and columns 8 apart must differ.
 template <int C, int S, bool STRIDED = false>
