@@ -22,12 +22,14 @@
 //      x at the wave's own channels, input channels of one K step of step 1 -- was
 //      copied from that step's LDS stage into registers: x is read from memory once.
 // x is read once (plus halo, mostly cache hits), t1 and t2 never leave the CU.
-// Blocks of 256 channels in launches of many tiles run in resident workgroups (bottleneck_stream.hip; the rule is in launch_bottleneck).
+// Blocks of 256 channels without the next stage's 1x1 run in resident workgroups in launches of many tiles (bottleneck_stream.hip; the rule is
+// in launch_bottleneck).
 //
-// Bounds, 668 images of 56 x 56 x 256 (identity block): memory 1.07 GB = 210 us at the rate of a large copy, issue of the
-// requantisation and its data movement about 180 us, matrix unit 75 us, in phases that barriers separate.
-// Two workgroups of eight waves a CU instead of two of four: 344 -> 322 us (projection block 360 -> 340).
-// All operands of step 1 on their way at once, the weights of steps 3 and 4 fetched a step early, the residual's and the
+// Bounds, 668 images of 56 x 56 x 256, block and next stage's 1x1, 395 to 410 us: memory 0.94 GB = 183 us at the rate of a large copy, vector
+// instructions issue for 46 % of the time, the matrix unit works for 22 %, in phases that barriers separate.
+// What it gained, measured with blocks of 668 images that run in resident workgroups now: two workgroups of eight waves a CU instead of two of
+// four 344 -> 322 us (projection block 360 -> 340);
+// all operands of step 1 on their way at once, the weights of steps 3 and 4 fetched a step early, the residual's and the
 // output's places in a table (224 divisions by the tile's width instead of one per wave and fragment), t1 and t2 at 80 bytes a
 // pixel (taps as immediate offsets): 1640 -> 1350 vector instructions a wave, 354 -> 327 us; projection block 382 -> 344,
 // block + next 486 -> 428 (one card).

@@ -12,12 +12,13 @@
 //               pixels).  One half of each SIMD's waves do it in this order, the other half in the other, so that matrix unit and LDS work
 //               of the one stands beside the requantisation arithmetic of the other.
 //
-// What bounds it: a tile takes 14 400 cycles a SIMD, of which the vector instructions issue for about 8600 and the matrix unit works for 3700;
-// with loads from the cache and no stores it is as fast (identity block 331 against 322 us), so memory is hidden.  Against two workgroups a CU that
-// start, load their weights and end with each tile (bottleneck.hip), us of a launch at 56 x 56, 668 / 400 / 250 / 150 / 100 / 60 copies: identity
-// block 342 / 214 / 142 / 85 / 59.0 / 38.8 -> 311 / 191 / 127 / 80 / 56.6 / 39.0, first block 342 / 208 / 122 / 80.6 / 54.5 / 37.4 -> 297 / 182 / 116 /
-// 76.6 / 55.2 / 38.7.  Of that: the waves' priority by what they still have to do 5 %, the closing convolution in fragments of 16 rows, whose constants are
-// read once a tile instead of once a fragment, 5 %, the pixels' places found by five waves for all 4 %.
+// What bounds it (pair form, 668 copies at 56 x 56, counters): a tile of an identity block takes 17 000 cycles a SIMD, for 9600 of which vector
+// instructions issue and for 4128 of which the matrix unit works; one of a first block 16 400, 10 600 and 4112.  The two overlap only partly.
+// With loads from the cache and no stores a first block takes 280 instead of 283 us, an identity block 254 instead of 286.
+// Two workgroups a CU that start, load their weights and end with each tile (bottleneck.hip) take 319 and 329 us where this kernel takes 278 and 288;
+// launch_bottleneck has the times of other launches and forms.  Of that: the waves' priority by what they still have to do 3 % (first blocks 5 to
+// 10 % in the forms with more constants), the closing convolution in fragments of 16 rows, whose constants are read once a tile instead of once a
+// fragment, 5 %, the pixels' places found by five waves for all 4 %.
 #include "conv_device.h"
 
 namespace isr {

@@ -238,7 +238,8 @@ __global__ __launch_bounds__(patch_threads(BM, LOADS), MINB) void conv_patch_ker
     // those four MFMAs, so the matrix pipe has work queued while the workgroup goes through barrier, refill and
     // the first fragment reads (measured +1 to +3 % over reading each sub-step's fragments right before its MFMAs).
     // With one workgroup a CU, all four waves of a SIMD go through the same step, and the oldest would be done with it first: the fewer sub-steps a
-    // wave has behind it, the higher its priority (71.5 -> 69.4 us; with two workgroups a CU 84.4 -> 87.6, which keep the hardware's order).
+    // wave has behind it, the higher its priority (71.5 -> 69.4 us, 2 to 6 % in each form of the requantisation; with two
+    // workgroups a CU 84.4 -> 87.6, which keep the hardware's order).
     static_assert(!EVERY || KS == 4, "three priorities and the one behind the barrier");
     static_assert(KS % 2 == 0, "register sets alternate");
     v4i fa[2][2], fb[2][2];

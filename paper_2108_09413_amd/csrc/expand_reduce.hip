@@ -338,8 +338,8 @@ __global__ __launch_bounds__(XNT2, 4) void proj_expand_reduce_kernel(const XrPar
     // 226 -> 219 us for 668 copies; expand_reduce256_kernel 200 -> 189).
     // The fewer steps a wave has behind it, the higher its priority: in the hardware's order the oldest wave of a SIMD reaches the barrier
     // long before the youngest, which then runs alone (214 -> 210 us; expand_reduce256_kernel 185 -> 183, expand_reduce1024_kernel 103 -> 100; in
-    // expand_reduce_kernel, whose CUs hold two workgroups, 149 -> 151, so not there).  In the pair form: in the others of this kernel the compiler
-    // would spill around them.
+    // expand_reduce_kernel, whose CUs hold two workgroups, 149 -> 151, so not there; 4 % in all forms of expand_reduce1024_kernel, 0 to 4 % in those of
+    // expand_reduce256_kernel).  In the pair form: in the others of this kernel the compiler would spill around them.
     if (tile < ntiles) make(tile, 0, Y[0]);
     int buf = 0;
     for (int it = 0; tile < ntiles; tile += G, ++it) {
@@ -688,6 +688,8 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
             a2c[i] = *(const v4i *)(a2w + ((uint32_t)l * 16 + (uint32_t)(i * 1024)));
         }
         lds_barrier();   // the y tile is complete, everybody is done with t2
+        // Here and not behind the last weight fragment, whose wait this load then lengthens: from there it lands too late for the next tile (668 copies,
+        // pair form: 99 -> 106 us; the other forms the same within 2 %).
         if (more) issue_t2(tile + G);
         v4acc acc2[NB];
 #pragma unroll
@@ -715,7 +717,6 @@ __global__ __launch_bounds__(XNT2, 4) void expand_reduce1024_kernel(const XrPara
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (ks + AW < KS) a2c[ks % AW] = *(const v4i *)(a2w + ((uint32_t)l * 16 + (uint32_t)((ks + AW) * 1024)));
-                // behind the last of them: a fragment would wait for what is issued in front of it, which comes from memory
             }
         }
         l = lane;

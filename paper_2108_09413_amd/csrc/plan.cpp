@@ -530,7 +530,7 @@ int build_device_ops(const ParsedModel &pm, std::vector<DevOp> &ops, ConstArena 
                     // acc * M0 is an exact half of 2^(31 + shift) only if acc = (odd) * 2^(30 + shift - tz(M0)), and then at least
                     // (M0 >> tz(M0)) / 2 steps from zero.  A negative one, rounded away from zero, gives another result than
                     // rounded up only if neither lies below the clamp: never in a rectified layer, and hardly ever in
-                    // others, where the steps have to be fewer than 256 and M0 a multiple of 2^21.
+                    // others, where the steps have to be fewer than 256 and M0 a multiple of 2^22.
                     const int64_t accmax = std::llabs((int64_t)o.bias[oc]) + maxdev * wabs;
                     const int tz = __builtin_ctz((unsigned)o.M0[oc]), need = 30 + o.shift[oc] - tz, lo = o.relu ? to.zp : -128;
                     if (need < 40 && accmax >= (1ll << need) && (o.M0[oc] >> tz) / 2 < to.zp - lo) tie_free = false;
